@@ -57,8 +57,8 @@ BwdWs bwd_layout(const Dims &m) {
     w.dA = take((size_t)m.S * m.F * m.eb);
     w.dB = take((size_t)m.S * m.F * m.eb);
     w.tiles = take(mf ? mfma_tiles_bytes(m.S, m.E) : 0);
-    w.part = take(use_mfma_router(m) ? mfma_dwr_ws_bytes(m.T, m.d, m.E) : 0);
-    w.tok = take(mfma_row_tokens_bytes(m.S));                    // row -> token list
+    w.part = take(use_mfma_router(m) ? mfma_dwr_ws_bytes(m.T, m.d, m.E) : plain_dwr_ws_bytes(m.T, m.d, m.E));
+    w.tok = take(mf ? mfma_row_tokens_bytes(m.S) : 0);           // row -> token list
     w.Hg = take(mf ? (size_t)m.S * m.F * m.eb : 0);              // gate-scaled H rows
     w.grow = take(mf ? (size_t)m.S * sizeof(float) : 0);         // row -> gate list
     w.wpart = take(mf ? (size_t)m.S * row_parts(m) * sizeof(float) : 0);
@@ -76,8 +76,8 @@ FwdWs fwd_layout(const Dims &m) {
     w.gate = take((size_t)m.T * m.E * sizeof(float));
     w.perm = take(permute_ws_bytes(m.T, m.E, m.K));
     w.ffn = take(use_mfma_ffn(m) ? mfma_tiles_bytes(m.S, m.E) : 0);
-    w.tok = take(mfma_row_tokens_bytes(m.S));
-    w.grow = take((size_t)m.S * sizeof(float));
+    w.tok = take(use_mfma_ffn(m) ? mfma_row_tokens_bytes(m.S) : 0);
+    w.grow = take(use_mfma_ffn(m) ? (size_t)m.S * sizeof(float) : 0);
     w.total = o;
     return w;
 }
@@ -163,7 +163,7 @@ int r3_replay_gate(const r3_layer_desc *desc, const void *x, const void *W_r, co
     }
     hipError_t e;
     if (use_mfma_router(m)) e = mfma_router_logits(m.T, m.d, m.E, x, W_r, bias, logits, s);
-    else e = simt_router_logits(m.T, m.d, m.E, m.act, x, W_r, bias, logits, s);
+    else e = plain_router_logits(m.T, m.d, m.E, m.act, x, W_r, bias, logits, s);
     if (e != hipSuccess) return R3_ERR_HIP;
     e = launch_gate(m.T, m.E, m.K, logits, idx, m.idx, m.stride, gates, status_word, s);
     if (e != hipSuccess) return R3_ERR_HIP;
@@ -223,11 +223,10 @@ int r3_grouped_ffn(const r3_layer_desc *desc, const void *Xp, const void *x, con
         return hip_rc(mfma_ffn_forward(m.S, m.d, m.E, m.F, rows, via, m.K, m.T, offsets, tiles, W_gate, W_up, W_down,
                                        Yp, H, FA_save, FB_save, nullptr, s));
     }
-    if (simt_ffn1((int)m.S, m.d, m.E, m.F, m.act, rows, via, m.K, offsets, W_gate, W_up, H, FA_save, FB_save, nullptr,
-                  s) !=
-        hipSuccess)
+    if (plain_ffn1((int)m.S, m.d, m.E, m.F, m.act, rows, via, m.K, offsets, W_gate, W_up, H, FA_save, FB_save, nullptr,
+                   s) != hipSuccess)
         return R3_ERR_HIP;
-    return hip_rc(simt_ffn2((int)m.S, m.d, m.E, m.F, m.act, H, offsets, W_down, Yp, s));
+    return hip_rc(plain_ffn2((int)m.S, m.d, m.E, m.F, m.act, H, offsets, W_down, Yp, s));
 }
 
 int r3_combine(const r3_layer_desc *desc, const void *Yp, const float *gates, const int32_t *inv_perm,
@@ -269,9 +268,9 @@ int r3_moe_forward(const r3_layer_desc *desc, const void *x, const void *W_r, co
     if (rc) return rc;
     // the gate of every expert-sorted row: the first contraction's epilogue scales H with it, so the
     // down projection yields gated rows and the combination is a plain sum of each token's K rows
-    int32_t *tok = (int32_t *)(base + w.tok);
-    float *grow = (float *)(base + w.grow);
     if (use_mfma_ffn(m)) {
+        int32_t *tok = (int32_t *)(base + w.tok);
+        float *grow = (float *)(base + w.grow);
         int32_t *tiles = (int32_t *)(base + w.ffn);
         if (mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, -1, (int)m.S, m.K, perm, gates, tok, grow, s) !=
             hipSuccess)
@@ -280,11 +279,10 @@ int r3_moe_forward(const r3_layer_desc *desc, const void *x, const void *W_r, co
                              FA_save, FB_save, grow, s) != hipSuccess)
             return R3_ERR_HIP;
     } else {
-        if (mfma_row_tokens((int)m.S, m.K, perm, gates, tok, grow, s) != hipSuccess) return R3_ERR_HIP;
-        if (simt_ffn1((int)m.S, m.d, m.E, m.F, m.act, x, perm, m.K, offsets, W_gate, W_up, H, FA_save, FB_save, grow,
-                      s) != hipSuccess)
+        if (plain_ffn1((int)m.S, m.d, m.E, m.F, m.act, x, perm, m.K, offsets, W_gate, W_up, H, FA_save, FB_save, gates,
+                       s) != hipSuccess)
             return R3_ERR_HIP;
-        if (simt_ffn2((int)m.S, m.d, m.E, m.F, m.act, H, offsets, W_down, Yp, s) != hipSuccess) return R3_ERR_HIP;
+        if (plain_ffn2((int)m.S, m.d, m.E, m.F, m.act, H, offsets, W_down, Yp, s) != hipSuccess) return R3_ERR_HIP;
     }
     return hip_rc(launch_combine(m.T, m.d, m.K, m.act, Yp, nullptr, inv_perm, y, s));
 }
@@ -357,28 +355,16 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
         if (launch_gate_backward(m.T, m.d, m.E, m.K, m.act, dy, Yp, gates, inv_perm, idx, m.idx, m.stride, dYp, dz,
                                  ds, gated ? 1 : 0, s) != hipSuccess)
             return R3_ERR_HIP;
-        if (simt_dh(S, m.d, m.E, m.F, m.act, dYp, offsets, W_down, FA, FB, dA, dB, s) != hipSuccess) return R3_ERR_HIP;
-        const int32_t *tok = nullptr;
-        if (gated || !Xp) {   // rows of dy / x through the row -> token list
-            int32_t *t = (int32_t *)(base + w.tok);
-            if (mfma_row_tokens(S, m.K, perm, nullptr, t, nullptr, s) != hipSuccess) return R3_ERR_HIP;
-            tok = t;
-        }
-        // gated: H is g H already, so its partner is the plain dy row, not g dy
-        e = gated ? simt_wgrad(m.E, m.F, m.d, m.act, H, nullptr, dy, tok, offsets, dW_down, accumulate, s)
-                  : simt_wgrad(m.E, m.F, m.d, m.act, H, nullptr, dYp, nullptr, offsets, dW_down, accumulate, s);
-        if (e != hipSuccess) return R3_ERR_HIP;
-        const void *rows = Xp ? Xp : x;          // the token rows, gathered or through the list
-        const int32_t *rtok = Xp ? nullptr : tok;
-        if (simt_wgrad(m.E, m.d, m.F, m.act, rows, rtok, dA, nullptr, offsets, dW_gate, accumulate, s) != hipSuccess)
+        if (plain_dh(S, m.d, m.E, m.F, m.act, dYp, offsets, W_down, FA, FB, dA, dB, s) != hipSuccess) return R3_ERR_HIP;
+        // gated: H is g H already, so its partner is the plain dy row (read through perm), not g dy
+        if (plain_wgrads(m.d, m.E, m.F, m.K, m.act, offsets, H, gated ? dy : dYp, gated ? perm : nullptr, Xp ? Xp : x,
+                         Xp ? nullptr : perm, dA, dB, dW_gate, dW_up, dW_down, accumulate, s) != hipSuccess)
             return R3_ERR_HIP;
-        if (simt_wgrad(m.E, m.d, m.F, m.act, rows, rtok, dB, nullptr, offsets, dW_up, accumulate, s) != hipSuccess)
-            return R3_ERR_HIP;
-        if (simt_dxp(S, m.d, m.E, m.F, m.act, dA, dB, offsets, W_gate, W_up, dXp, s) != hipSuccess) return R3_ERR_HIP;
+        if (plain_dxp(S, m.d, m.E, m.F, m.act, dA, dB, offsets, W_gate, W_up, dXp, s) != hipSuccess) return R3_ERR_HIP;
     }
     // router:  dW_r = x^T ds, dbias = column sums
     if (use_mfma_router(m)) e = mfma_dwr(m.T, m.d, m.E, x, ds, (float *)(base + w.part), dW_r, accumulate, s);
-    else e = simt_dwr(m.T, m.d, m.E, m.act, x, ds, dW_r, accumulate, s);
+    else e = plain_dwr(m.T, m.d, m.E, m.act, x, ds, (float *)(base + w.part), dW_r, accumulate, s);
     if (e != hipSuccess) return R3_ERR_HIP;
     if (dbias && launch_colsum(m.T, m.E, m.act, ds, dbias, accumulate, s) != hipSuccess) return R3_ERR_HIP;
     if (launch_transpose(m.d, m.E, m.act, W_r, WrT, s) != hipSuccess) return R3_ERR_HIP;

@@ -1156,29 +1156,7 @@ hipError_t mfma_wgrad_pair(int E, int NQd, int NPd, const void *Qs, const int32_
     return hipGetLastError();
 }
 
-// tok[r] = perm[r] / K for r < S (the token whose row sits at position r of the expert-sorted order),
-// followed by `pad` zeros, so that index fetches one past a segment's end stay inside the array;
-// grow[r] = gates[perm[r]], the gate of that row's slot (gates may be NULL: grow is then not written)
-__global__ void __launch_bounds__(256) row_tokens_kernel(int S, int K, int pad, const int32_t *__restrict__ perm,
-                                                         const float *__restrict__ gates, int32_t *__restrict__ tok,
-                                                         float *__restrict__ grow) {
-    const int r = blockIdx.x * 256 + threadIdx.x;
-    if (r < S) {
-        const int slot = perm[r];
-        tok[r] = slot / K;
-        if (gates) grow[r] = gates[slot];
-    } else if (r < S + pad) {
-        tok[r] = 0;
-    }
-}
-
 size_t mfma_row_tokens_bytes(int64_t S) { return (size_t)(S + kRowTokensPad) * sizeof(int32_t); }
-
-hipError_t mfma_row_tokens(int S, int K, const int32_t *perm, const float *gates, int32_t *tok, float *grow,
-                           hipStream_t s) {
-    row_tokens_kernel<<<(S + kRowTokensPad + 255) / 256, 256, 0, s>>>(S, K, kRowTokensPad, perm, gates, tok, grow);
-    return hipGetLastError();
-}
 
 hipError_t mfma_router_logits(int T, int d, int E, const void *x, const void *Wr, const float *bias,
                               float *logits, hipStream_t s) {

@@ -67,25 +67,28 @@ hipError_t launch_cache_gather(int idx_bytes, int L, int K, int P, const void *p
                                const int32_t *block_table, int nseq, int max_blocks, const int32_t *seq_start,
                                int T, void *out, int32_t *status, hipStream_t s);
 
-// r3_simt.hip
-hipError_t simt_router_logits(int T, int d, int E, int act, const void *x, const void *Wr, const float *bias,
-                              float *logits, hipStream_t s);
-// perm != NULL: `Xp` is x [T,d] and row r of the grouped operand is x[perm[r] / K] (no gathered copy)
-// grow != NULL: H is stored scaled by the row's gate (grow [S] f32)
-hipError_t simt_ffn1(int S, int d, int E, int F, int act, const void *Xp, const int32_t *perm, int K,
-                     const int32_t *offsets, const void *Wg, const void *Wu, void *H, void *A, void *B,
-                     const float *grow, hipStream_t s);
-hipError_t simt_ffn2(int S, int d, int E, int F, int act, const void *H, const int32_t *offsets, const void *Wd,
-                     void *Yp, hipStream_t s);
-hipError_t simt_dh(int S, int d, int E, int F, int act, const void *dYp, const int32_t *offsets, const void *Wd,
-                   const void *A, const void *B, void *dA, void *dB, hipStream_t s);
-hipError_t simt_dxp(int S, int d, int E, int F, int act, const void *dA, const void *dB, const int32_t *offsets,
-                    const void *Wg, const void *Wu, void *dXp, hipStream_t s);
-// ptok / qtok != NULL: that operand is an un-permuted matrix and row r of the reduction is its row tok[r]
-hipError_t simt_wgrad(int E, int NP, int NQ, int act, const void *P, const int32_t *ptok, const void *Q,
-                      const int32_t *qtok, const int32_t *offsets, float *out, int accumulate, hipStream_t s);
-hipError_t simt_dwr(int T, int d, int E, int act, const void *x, const void *ds, float *dWr, int accumulate,
-                    hipStream_t s);
+// r3_plain.hip (f32 arithmetic, any widths, both activation types)
+hipError_t plain_router_logits(int T, int d, int E, int act, const void *x, const void *Wr, const float *bias,
+                               float *logits, hipStream_t s);
+// perm != NULL: `rows` is x [T,d] and row r of the grouped operand is x[perm[r] / K] (no gathered copy);
+// gates != NULL (with perm): H is stored scaled by the gate of the row's slot, gates[perm[r]]
+hipError_t plain_ffn1(int S, int d, int E, int F, int act, const void *rows, const int32_t *perm, int K,
+                      const int32_t *offsets, const void *Wg, const void *Wu, void *H, void *FA, void *FB,
+                      const float *gates, hipStream_t s);
+hipError_t plain_ffn2(int S, int d, int E, int F, int act, const void *H, const int32_t *offsets, const void *Wd,
+                      void *Yp, hipStream_t s);
+hipError_t plain_dh(int S, int d, int E, int F, int act, const void *dYp, const int32_t *offsets, const void *Wd,
+                    const void *FA, const void *FB, void *dA, void *dB, hipStream_t s);
+hipError_t plain_dxp(int S, int d, int E, int F, int act, const void *dA, const void *dB, const int32_t *offsets,
+                     const void *Wg, const void *Wu, void *dXp, hipStream_t s);
+// dWd (+)= H^T dYrows, dWg (+)= xrows^T dA, dWu (+)= xrows^T dB per expert.  dyperm / xperm != NULL: that operand is
+// an un-permuted matrix and row r of the reduction is its row perm[r] / K
+hipError_t plain_wgrads(int d, int E, int F, int K, int act, const int32_t *offsets, const void *H, const void *dYrows,
+                        const int32_t *dyperm, const void *xrows, const int32_t *xperm, const void *dA, const void *dB,
+                        float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s);
+size_t plain_dwr_ws_bytes(int T, int d, int E);   // partial products of plain_dwr
+hipError_t plain_dwr(int T, int d, int E, int act, const void *x, const void *ds, float *part, float *dWr, int accumulate,
+                     hipStream_t s);
 
 // r3_gemm.hip (bf16 MFMA)
 bool mfma_ffn_supported(int d, int F);
@@ -132,11 +135,8 @@ hipError_t mfma_wgrad(int E, int NQd, int NPd, const void *Qs, const void *Ps, c
 hipError_t mfma_wgrad_pair(int E, int NQd, int NPd, const void *Qs, const int32_t *tok, int nrows, const void *P0,
                            const void *P1, const int32_t *tiles, int launch, float *out0, float *out1, float *part,
                            int accumulate, hipStream_t s);
-// tok[r] = perm[r] / K (r < S), padded; mfma_row_tokens_bytes(S) bytes.  gates != NULL: also
-// grow[r] = gates[perm[r]] (f32 [S])
-size_t mfma_row_tokens_bytes(int64_t S);   // (the kernel is plain: every path may use it)
-hipError_t mfma_row_tokens(int S, int K, const int32_t *perm, const float *gates, int32_t *tok, float *grow,
-                           hipStream_t s);
+// the list above: tok[r] = perm[r] / K (r < S), padded
+size_t mfma_row_tokens_bytes(int64_t S);
 hipError_t mfma_router_logits(int T, int d, int E, const void *x, const void *Wr, const float *bias,
                               float *logits, hipStream_t s);
 // logits + replay gate (+ agreement counts) in one launch; E = 128 (see gate_fused_kernel)

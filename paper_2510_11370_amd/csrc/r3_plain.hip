@@ -1,0 +1,640 @@
+// The expert network and the router in f32 arithmetic, for any widths and both activation types: the f32
+// layer, and the bf16 shapes that the bf16 MFMA kernels do not take.  Tiles run on the f32 matrix
+// instruction (16x16x4): products and sums are those of an f32 FMA chain (bf16 operands are widened, so their
+// products are exact).
+//
+// What bounds it: the f32 matrix pipe (154 TFLOP/s is what a large library product reaches here) where a
+// shape has work, launch and load latency where it has not.  Operands go through registers into a
+// double-buffered LDS tile of 32 k, the next tile's loads in flight while the current one is multiplied; the
+// f32 instruction takes 32 cycles, so the fragment reads (16 bytes per lane and 16 k from a row-major tile,
+// 4 bytes from a k-major one) are far from being felt.  Tiles are 128 x 128 (4 waves of 64 x 64) where
+// that still gives every compute unit two of them, else 64 x 64 (4 waves of 32 x 32).
+// Measured on T=2048 d=512 E=16 K=4 F=1024 f32, forward + backward (77 GFLOP): 65.3 ms with one thread per
+// output element (uncoalesced weight rows), 1.06 ms now; T=256 d=128 E=8 K=2 F=256 f32: 0.435 -> 0.099 ms;
+// T=3001 d=1000 E=64 K=6 F=704 bf16: 193 -> 4.2 ms.
+#include <algorithm>
+
+#include "r3_kernels.h"
+
+namespace r3 {
+
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+
+template <int BP_, int BQ_>
+struct PlainCfg {
+    static constexpr int BP = BP_, BQ = BQ_, BK = 32, NT = 256;
+    static constexpr int WTP = BP / 2, WTQ = BQ / 2, TP = WTP / 16, TQ = WTQ / 16;   // 2 x 2 waves
+    static constexpr int KP = BK + 4;                 // floats per row of a row-major tile (reads spread over the banks)
+    static constexpr int PBYTES = (BP * KP > BK * (BP + 4) ? BP * KP : BK * (BP + 4)) * 4;
+    static constexpr int QBYTES = (BQ * KP > BK * (BQ + 4) ? BQ * KP : BK * (BQ + 4)) * 4;
+    static constexpr int STAGE = PBYTES + QBYTES;
+    static constexpr int LDS = 2 * STAGE;
+};
+typedef PlainCfg<128, 128> PlainBig;
+typedef PlainCfg<64, 64> PlainSmall;
+
+// four consecutive elements as floats; elements at or past `n` (counted from p) read as zero.  VEC: p is
+// aligned to four elements and n is a multiple of four or <= 0
+template <typename T, bool VEC>
+__device__ __forceinline__ float4 load4(const T *p, int n) {
+    float4 v = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    if constexpr (VEC) {
+        if (n > 0) {
+            if constexpr (sizeof(T) == 4) {
+                v = *(const float4 *)p;
+            } else {
+                const uint2 u = *(const uint2 *)p;
+                v = make_float4(__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xffff0000u), __uint_as_float(u.y << 16),
+                                __uint_as_float(u.y & 0xffff0000u));
+            }
+        }
+    } else {
+        if (n > 0) v.x = Elem<T>::ld(p);
+        if (n > 1) v.y = Elem<T>::ld(p + 1);
+        if (n > 2) v.z = Elem<T>::ld(p + 2);
+        if (n > 3) v.w = Elem<T>::ld(p + 3);
+    }
+    return v;
+}
+template <typename T, bool VEC>
+__device__ __forceinline__ void store4(T *p, const float (&v)[4], int n) {
+    if constexpr (VEC) {
+        if (n > 0) {
+            if constexpr (sizeof(T) == 4) *(float4 *)p = make_float4(v[0], v[1], v[2], v[3]);
+            else *(uint2 *)p = make_uint2(pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3]));
+        }
+    } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            if (i < n) Elem<T>::st(p + i, v[i]);
+    }
+}
+
+template <class C> using PlainAcc = f32x4_t[C::TP][C::TQ];
+
+// D[p][q] = sum_k P[p][k] Q[q][k] over k in [0, nk * BK).  A k-major operand's loader is called as
+// f(i, k, column), a row-major one's as f(i, row, k), for the thread's i-th piece of the tile (i is a constant
+// after unrolling); both return four consecutive values (zero outside the matrix).  pre(kt) runs one k-tile before tile kt is loaded (index fetches).
+template <class C, bool PTR, bool QTR, class FP, class FQ, class Pre>
+__device__ __forceinline__ void plain_mainloop(PlainAcc<C> &acc, int nk, FP fp, FQ fq, Pre pre, char *lds) {
+    constexpr int NP = C::BP * C::BK / 4 / C::NT, NQ = C::BQ * C::BK / 4 / C::NT;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wp = wave & 1, wq = wave >> 1;
+    float4 rp[NP], rq[NQ];
+    auto gload = [&](int kt) {
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int id = tid + i * C::NT;
+            if constexpr (PTR) rp[i] = fp(i, kt * C::BK + id / (C::BP / 4), id % (C::BP / 4) * 4);
+            else rp[i] = fp(i, id / (C::BK / 4), kt * C::BK + id % (C::BK / 4) * 4);
+        }
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const int id = tid + i * C::NT;
+            if constexpr (QTR) rq[i] = fq(i, kt * C::BK + id / (C::BQ / 4), id % (C::BQ / 4) * 4);
+            else rq[i] = fq(i, id / (C::BK / 4), kt * C::BK + id % (C::BK / 4) * 4);
+        }
+    };
+    auto lstore = [&](int stage) {
+        float *pb = (float *)(lds + stage * C::STAGE), *qb = (float *)(lds + stage * C::STAGE + C::PBYTES);
+#pragma unroll
+        for (int i = 0; i < NP; ++i) {
+            const int id = tid + i * C::NT;
+            if constexpr (PTR) *(float4 *)(pb + id / (C::BP / 4) * (C::BP + 4) + id % (C::BP / 4) * 4) = rp[i];
+            else *(float4 *)(pb + id / (C::BK / 4) * C::KP + id % (C::BK / 4) * 4) = rp[i];
+        }
+#pragma unroll
+        for (int i = 0; i < NQ; ++i) {
+            const int id = tid + i * C::NT;
+            if constexpr (QTR) *(float4 *)(qb + id / (C::BQ / 4) * (C::BQ + 4) + id % (C::BQ / 4) * 4) = rq[i];
+            else *(float4 *)(qb + id / (C::BK / 4) * C::KP + id % (C::BK / 4) * 4) = rq[i];
+        }
+    };
+    // a lane's four k of a 16-k group are 4 (lane / 16) .. + 3, for both operands alike (the order of the
+    // sum over k is free): 16 contiguous bytes of a row-major tile
+    const int r16 = lane & 15, k4 = 4 * (lane >> 4);
+    auto frag = [&](const float *b, bool tr, int pitch, int row, int k, float (&f)[4]) {
+        if (tr) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) f[i] = b[(k + i) * pitch + row];
+        } else {
+            const float4 v = *(const float4 *)(b + row * pitch + k);
+            f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+        }
+    };
+    if (nk <= 0) return;
+    pre(0);
+    gload(0);
+    pre(1);
+    lstore(0);
+    __syncthreads();
+    for (int kt = 0; kt < nk; ++kt) {
+        const bool more = kt + 1 < nk;
+        if (more) {
+            gload(kt + 1);
+            pre(kt + 2);
+        }
+        const float *pb = (const float *)(lds + (kt & 1) * C::STAGE);
+        const float *qb = (const float *)(lds + (kt & 1) * C::STAGE + C::PBYTES);
+#pragma unroll
+        for (int g = 0; g < C::BK / 16; ++g) {
+            float a[C::TP][4], b[C::TQ][4];
+#pragma unroll
+            for (int i = 0; i < C::TP; ++i)
+                frag(pb, PTR, PTR ? C::BP + 4 : C::KP, wp * C::WTP + 16 * i + r16, 16 * g + k4, a[i]);
+#pragma unroll
+            for (int j = 0; j < C::TQ; ++j)
+                frag(qb, QTR, QTR ? C::BQ + 4 : C::KP, wq * C::WTQ + 16 * j + r16, 16 * g + k4, b[j]);
+#pragma unroll
+            for (int s = 0; s < 4; ++s)
+#pragma unroll
+                for (int i = 0; i < C::TP; ++i)
+#pragma unroll
+                    for (int j = 0; j < C::TQ; ++j)
+                        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][s], b[j][s], acc[i][j], 0, 0, 0);
+        }
+        if (more) lstore((kt + 1) & 1);
+        __syncthreads();
+    }
+}
+
+template <class C>
+__device__ __forceinline__ void plain_zero(PlainAcc<C> &acc) {
+#pragma unroll
+    for (int i = 0; i < C::TP; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TQ; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+}
+// the lane's results: f(tp, tq, p, q), acc[tp][tq][0..3] = D[p .. p + 3][q] (tile-local)
+template <class C, class F>
+__device__ __forceinline__ void plain_results(F f) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int tq = 0; tq < C::TQ; ++tq)
+#pragma unroll
+        for (int tp = 0; tp < C::TP; ++tp)
+            f(tp, tq, (wave & 1) * C::WTP + 16 * tp + 4 * (lane >> 4), (wave >> 1) * C::WTQ + 16 * tq + (lane & 15));
+}
+
+// The expert and first row of row tile `want` (tiles of BQ rows, experts ascending), or e = -1 past the
+// last one.  Every wave finds it by itself: a lane adds up the tiles of its share of the experts, the wave
+// scans the sums and the lane that holds the tile walks its share.  (A table made by a launch of its own
+// costs more than this: the layers that come here are small.)
+struct RowTile {
+    int e, row0, row1;
+};
+__device__ __forceinline__ RowTile find_row_tile(const int32_t *__restrict__ offsets, int E, int BQ, int want) {
+    const int lane = lane_id(), per = (E + kWave - 1) / kWave;
+    const int e0 = min(lane * per, E), e1 = min(e0 + per, E);
+    int mine = 0, lo = offsets[e0];
+    for (int e = e0; e < e1; ++e) {
+        const int hi = offsets[e + 1];
+        mine += (hi - lo + BQ - 1) / BQ;
+        lo = hi;
+    }
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int v = __shfl_up(incl, o, kWave);
+        if (lane >= o) incl += v;
+    }
+    const uint64_t past = __ballot(incl > want);
+    RowTile t = {-1, 0, 0};
+    if (past == 0) return t;
+    const int owner = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)past) - 1);
+    int left = want - __builtin_amdgcn_readlane(incl - mine, owner);
+    for (int e = owner * per; e < min((owner + 1) * per, E); ++e) {   // wave-uniform
+        const int a = offsets[e], b = offsets[e + 1], n = (b - a + BQ - 1) / BQ;
+        if (left < n) {
+            t.e = e;
+            t.row0 = a + left * BQ;
+            t.row1 = min(b, t.row0 + BQ);
+            return t;
+        }
+        left -= n;
+    }
+    return t;
+}
+
+// ---------------------------------------------------------------------------
+// Row-tiled contractions over the expert-sorted rows:
+//   FFN1: A = rows Wg, B = rows Wu; H = (g) silu(A) B; FA = B silu'(A), FB = silu(A)   (P: gate | up halves)
+//   DOWN: Yp = H Wd        DH: dh = dYp Wd^T, dA = dh FA, dB = dh FB        DXP: dA Wg^T + dB Wu^T
+// `in0` holds the rows; FFN1 with perm != NULL reads row r as in0[perm[r] / K], and with gates != NULL
+// scales H by the gate of the row's slot.
+// ---------------------------------------------------------------------------
+enum { PLAIN_FFN1, PLAIN_DOWN, PLAIN_DH, PLAIN_DXP };
+
+template <class C, int MODE, typename T, bool VEC>
+__global__ void __launch_bounds__(C::NT)
+plain_rows_kernel(int d, int E, int F, const int32_t *__restrict__ offsets, const T *__restrict__ in0,
+                  const T *__restrict__ in1, const int32_t *__restrict__ perm, int K, const float *__restrict__ gates,
+                  const T *__restrict__ W0, const T *__restrict__ W1, const T *__restrict__ FAin,
+                  const T *__restrict__ FBin, T *__restrict__ out0, T *__restrict__ out1, T *__restrict__ out2) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    constexpr int BF = MODE == PLAIN_FFN1 ? C::BP / 2 : C::BP;            // output features per tile
+    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d;
+    const int KK = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? d : F;      // width of the row operand
+    const int npt = (NOUT + BF - 1) / BF;
+    const int qt = blockIdx.x / npt, p0 = (blockIdx.x - qt * npt) * BF;
+    const RowTile t = find_row_tile(offsets, E, C::BQ, qt);
+    if (t.e < 0) return;
+    const int rows = t.row1 - t.row0;
+    const T *w0 = W0 + (int64_t)t.e * d * F;
+    const T *w1 = (MODE == PLAIN_FFN1 || MODE == PLAIN_DXP) ? W1 + (int64_t)t.e * d * F : nullptr;
+
+    // the thread's rows of the row operand do not change over k
+    constexpr int NQ = C::BQ * C::BK / 4 / C::NT, RSTEP = C::NT / (C::BK / 4);
+    const T *qrow[NQ], *qrow1[MODE == PLAIN_DXP ? NQ : 1];
+#pragma unroll
+    for (int i = 0; i < NQ; ++i) {
+        const int r = threadIdx.x / (C::BK / 4) + i * RSTEP;
+        const int row = t.row0 + min(r, rows - 1);
+        const int src = (MODE == PLAIN_FFN1 && perm) ? perm[row] / K : row;
+        qrow[i] = in0 + (int64_t)src * KK;
+        if constexpr (MODE == PLAIN_DXP) qrow1[i] = in1 + (int64_t)row * KK;
+    }
+    PlainAcc<C> acc;
+    plain_zero<C>(acc);
+    auto none = [](int) {};
+    const int nk = (KK + C::BK - 1) / C::BK;
+    auto fq = [&](int i, int, int k) { return load4<T, VEC>(qrow[i] + k, KK - k); };
+    if constexpr (MODE == PLAIN_FFN1) {
+        // P columns: per wave WTP / 2 features of W_gate, then the same features of W_up, so that a lane holds
+        // both pre-activations of its (row, feature) pairs
+        auto fp = [&](int, int k, int c) {
+            const int w = c / C::WTP, cc = c % C::WTP, f = p0 + w * (C::WTP / 2) + cc % (C::WTP / 2);
+            return load4<T, VEC>((cc < C::WTP / 2 ? w0 : w1) + (int64_t)k * F + f, k < d ? F - f : 0);
+        };
+        plain_mainloop<C, true, false>(acc, nk, fp, fq, none, lds);
+    } else if constexpr (MODE == PLAIN_DOWN) {
+        auto fp = [&](int, int k, int c) { return load4<T, VEC>(w0 + (int64_t)k * d + p0 + c, k < F ? d - p0 - c : 0); };
+        plain_mainloop<C, true, false>(acc, nk, fp, fq, none, lds);
+    } else {
+        auto fp = [&](int, int r, int k) { return load4<T, VEC>(w0 + (int64_t)(p0 + r) * KK + k, p0 + r < NOUT ? KK - k : 0); };
+        plain_mainloop<C, false, false>(acc, nk, fp, fq, none, lds);
+        if constexpr (MODE == PLAIN_DXP) {
+            auto fq1 = [&](int i, int, int k) { return load4<T, VEC>(qrow1[i] + k, KK - k); };
+            auto fp1 = [&](int, int r, int k) { return load4<T, VEC>(w1 + (int64_t)(p0 + r) * KK + k, p0 + r < NOUT ? KK - k : 0); };
+            plain_mainloop<C, false, false>(acc, nk, fp1, fq1, none, lds);
+        }
+    }
+    plain_results<C>([&](int tp, int tq, int p, int q) {
+        if (q >= rows) return;
+        const int row = t.row0 + q;
+        if constexpr (MODE == PLAIN_FFN1) {
+            if (tp >= C::TP / 2) return;
+            const int f = p0 + p / C::WTP * (C::WTP / 2) + p % C::WTP;
+            if (f >= F) return;
+            const float gq = gates ? gates[perm[row]] : 1.0f;
+            float h[4], fa[4], fb[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float a = acc[tp][tq][i], b = acc[tp + C::TP / 2][tq][i];
+                const float sg = sigmoidf_(a);
+                h[i] = gq * (a * sg * b);
+                fa[i] = b * sg * (1.0f + a * (1.0f - sg));
+                fb[i] = a * sg;
+            }
+            const int64_t o = (int64_t)row * F + f;
+            store4<T, VEC>(out0 + o, h, F - f);
+            if (out1) store4<T, VEC>(out1 + o, fa, F - f);
+            if (out2) store4<T, VEC>(out2 + o, fb, F - f);
+        } else {
+            const int c = p0 + p;
+            if (c >= NOUT) return;
+            const int64_t o = (int64_t)row * NOUT + c;
+            float v[4] = {acc[tp][tq][0], acc[tp][tq][1], acc[tp][tq][2], acc[tp][tq][3]};
+            if constexpr (MODE == PLAIN_DH) {
+                const float4 a = load4<T, VEC>(FAin + o, F - c), b = load4<T, VEC>(FBin + o, F - c);
+                float va[4] = {v[0] * a.x, v[1] * a.y, v[2] * a.z, v[3] * a.w};
+                float vb[4] = {v[0] * b.x, v[1] * b.y, v[2] * b.z, v[3] * b.w};
+                store4<T, VEC>(out0 + o, va, F - c);
+                store4<T, VEC>(out1 + o, vb, F - c);
+            } else {
+                store4<T, VEC>(out0 + o, v, NOUT - c);
+            }
+        }
+    });
+}
+
+// ---------------------------------------------------------------------------
+// The three weight gradients of every expert in one launch, out[q][p] (+)= sum_r Qs[r][q] Ps[r][p] over the
+// expert's rows:  dW_down: Qs = H, Ps = dYp (or dy through perm);  dW_gate, dW_up: Qs = the token rows,
+// Ps = dA, dB.  A row operand with a perm is the un-permuted matrix and row r is its row perm[r] / K.
+// ---------------------------------------------------------------------------
+template <typename T>
+struct PlainWgrad {
+    const T *Qs, *Ps;
+    const int32_t *qperm, *pperm;
+    float *out;
+    int NQ, NP, tiles;   // tiles: per expert
+};
+template <typename T>
+struct PlainWgrad3 {
+    PlainWgrad<T> g[3];
+};
+
+template <class C, typename T, bool VEC>
+__global__ void __launch_bounds__(C::NT)
+plain_wgrad_kernel(int E, int K, const int32_t *__restrict__ offsets, PlainWgrad3<T> all, int accumulate) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int per = all.g[0].tiles + all.g[1].tiles + all.g[2].tiles;
+    const int e = blockIdx.x / per;
+    int rem = blockIdx.x - e * per, which = 0;
+    while (rem >= all.g[which].tiles) rem -= all.g[which++].tiles;
+    const PlainWgrad<T> g = all.g[which];
+    const int npt = (g.NP + C::BP - 1) / C::BP;
+    const int qt = rem / npt, q0 = qt * C::BQ, p0 = (rem - qt * npt) * C::BP;
+    const int r0 = offsets[e], n = offsets[e + 1] - r0;
+    // a thread's k-rows of a tile: one of the gathered matrix's rows each, fetched a tile ahead
+    constexpr int NPL = C::BP * C::BK / 4 / C::NT, NQL = C::BQ * C::BK / 4 / C::NT;
+    constexpr int PSTEP = C::NT / (C::BP / 4), QSTEP = C::NT / (C::BQ / 4);
+    int prow[NPL], qrow[NQL], pnext[NPL] = {}, qnext[NQL] = {};
+    auto pre = [&](int kt) {
+#pragma unroll
+        for (int i = 0; i < NPL; ++i) {
+            prow[i] = pnext[i];
+            const int r = r0 + min(kt * C::BK + (int)threadIdx.x / (C::BP / 4) + i * PSTEP, max(n - 1, 0));
+            pnext[i] = n > 0 && g.pperm ? g.pperm[r] / K : r;
+        }
+#pragma unroll
+        for (int i = 0; i < NQL; ++i) {
+            qrow[i] = qnext[i];
+            const int r = r0 + min(kt * C::BK + (int)threadIdx.x / (C::BQ / 4) + i * QSTEP, max(n - 1, 0));
+            qnext[i] = n > 0 && g.qperm ? g.qperm[r] / K : r;
+        }
+    };
+    pre(0);   // (plain_mainloop shifts once more before it loads tile 0)
+    auto fp = [&](int i, int k, int c) {
+        return load4<T, VEC>(g.Ps + (int64_t)prow[i] * g.NP + p0 + c, k < n ? g.NP - p0 - c : 0);
+    };
+    auto fq = [&](int i, int k, int c) {
+        return load4<T, VEC>(g.Qs + (int64_t)qrow[i] * g.NQ + q0 + c, k < n ? g.NQ - q0 - c : 0);
+    };
+    PlainAcc<C> acc;
+    plain_zero<C>(acc);
+    plain_mainloop<C, true, true>(acc, (n + C::BK - 1) / C::BK, fp, fq, [&](int kt) { pre(kt + 1); }, lds);
+    float *o = g.out + (int64_t)e * g.NQ * g.NP;
+    plain_results<C>([&](int tp, int tq, int p, int q) {
+        if (q0 + q >= g.NQ || p0 + p >= g.NP) return;
+        const int64_t at = (int64_t)(q0 + q) * g.NP + p0 + p;
+        float v[4] = {acc[tp][tq][0], acc[tp][tq][1], acc[tp][tq][2], acc[tp][tq][3]};
+        if (accumulate) {
+            const float4 old = load4<float, VEC>(o + at, g.NP - p0 - p);
+            v[0] += old.x; v[1] += old.y; v[2] += old.z; v[3] += old.w;
+        }
+        store4<float, VEC>(o + at, v, g.NP - p0 - p);
+    });
+}
+
+// ---------------------------------------------------------------------------
+// Router: logits s[t][e] = sum_c x[t][c] W_r[c][e] (+ bias), and the parts of dW_r[c][e] = sum_t x[t][c] ds[t][e]
+// over `rows` tokens each (bf16 activations: ds rows are [hi(E) | lo(E)], widened and added).
+// ---------------------------------------------------------------------------
+template <class C, typename T, bool VECX, bool VECE>
+__global__ void __launch_bounds__(C::NT)
+plain_logits_kernel(int Tn, int d, int E, const T *__restrict__ x, const T *__restrict__ Wr, const float *__restrict__ bias,
+                    float *__restrict__ logits) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int npt = (E + C::BP - 1) / C::BP;
+    const int qt = blockIdx.x / npt, t0 = qt * C::BQ, p0 = (blockIdx.x - qt * npt) * C::BP;
+    auto fp = [&](int, int k, int c) { return load4<T, VECE>(Wr + (int64_t)k * E + p0 + c, k < d ? E - p0 - c : 0); };
+    auto fq = [&](int, int r, int k) { return load4<T, VECX>(x + (int64_t)min(t0 + r, Tn - 1) * d + k, d - k); };
+    PlainAcc<C> acc;
+    plain_zero<C>(acc);
+    plain_mainloop<C, true, false>(acc, (d + C::BK - 1) / C::BK, fp, fq, [](int) {}, lds);
+    plain_results<C>([&](int tp, int tq, int p, int q) {
+        if (t0 + q >= Tn || p0 + p >= E) return;
+        float v[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) v[i] = acc[tp][tq][i] + (bias && p0 + p + i < E ? bias[p0 + p + i] : 0.0f);
+        store4<float, VECE>(logits + (int64_t)(t0 + q) * E + p0 + p, v, E - p0 - p);
+    });
+}
+
+template <class C, typename T, bool VECX, bool VECE>
+__global__ void __launch_bounds__(C::NT)
+plain_dwr_kernel(int Tn, int d, int E, int rows, const T *__restrict__ x, const T *__restrict__ ds,
+                 float *__restrict__ part) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int npt = (E + C::BP - 1) / C::BP, nqt = (d + C::BQ - 1) / C::BQ;
+    const int sp = blockIdx.x / (npt * nqt), rem = blockIdx.x - sp * npt * nqt;
+    const int qt = rem / npt, q0 = qt * C::BQ, p0 = (rem - qt * npt) * C::BP;
+    const int t0 = sp * rows, n = min(rows, Tn - t0);
+    constexpr bool HILO = sizeof(T) == 2;
+    const int dsw = HILO ? 2 * E : E;
+    auto fp = [&](int, int k, int c) {
+        const T *p = ds + (int64_t)(t0 + min(k, n - 1)) * dsw + p0 + c;
+        const int m = k < n ? E - p0 - c : 0;
+        float4 v = load4<T, VECE>(p, m);
+        if constexpr (HILO) {
+            const float4 lo = load4<T, VECE>(p + E, m);
+            v.x += lo.x; v.y += lo.y; v.z += lo.z; v.w += lo.w;
+        }
+        return v;
+    };
+    auto fq = [&](int, int k, int c) { return load4<T, VECX>(x + (int64_t)(t0 + min(k, n - 1)) * d + q0 + c, k < n ? d - q0 - c : 0); };
+    PlainAcc<C> acc;
+    plain_zero<C>(acc);
+    plain_mainloop<C, true, true>(acc, (n + C::BK - 1) / C::BK, fp, fq, [](int) {}, lds);
+    float *o = part + (int64_t)sp * d * E;
+    plain_results<C>([&](int tp, int tq, int p, int q) {
+        if (q0 + q >= d || p0 + p >= E) return;
+        float v[4] = {acc[tp][tq][0], acc[tp][tq][1], acc[tp][tq][2], acc[tp][tq][3]};
+        store4<float, VECE>(o + (int64_t)(q0 + q) * E + p0 + p, v, E - p0 - p);
+    });
+}
+
+// out[i] (+)= sum_s part[s][i], s ascending
+__global__ void __launch_bounds__(256)
+plain_sum_parts_kernel(int64_t n, int nsplit, const float *__restrict__ part, float *__restrict__ out, int accumulate) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    float acc = accumulate ? out[i] : 0.0f;
+    for (int s = 0; s < nsplit; ++s) acc += part[(int64_t)s * n + i];
+    out[i] = acc;
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+namespace {
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+constexpr int kFill = 512;   // 128 x 128 tiles from two per compute unit on; below, four times as many 64 x 64 ones
+
+template <class K>
+void allow_lds(K kernel, int bytes) {
+    (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
+
+// row tiles of BQ rows over E ragged segments of S rows: at most this many
+int64_t row_tiles(int64_t S, int E, int BQ) { return S / BQ + std::min<int64_t>(E, S); }
+
+template <class C, int MODE, typename T, bool VEC>
+void rows_launch(int S, int d, int E, int F, const int32_t *offsets, const T *in0, const T *in1, const int32_t *perm, int K,
+                 const float *gates, const T *W0, const T *W1, const T *FA, const T *FB, T *o0, T *o1, T *o2, hipStream_t s) {
+    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d, BF = MODE == PLAIN_FFN1 ? C::BP / 2 : C::BP;
+    auto k = plain_rows_kernel<C, MODE, T, VEC>;
+    allow_lds(k, C::LDS);
+    k<<<(unsigned)(row_tiles(S, E, C::BQ) * ceil_div(NOUT, BF)), C::NT, C::LDS, s>>>(d, E, F, offsets, in0, in1, perm, K, gates,
+                                                                                     W0, W1, FA, FB, o0, o1, o2);
+}
+
+template <int MODE, typename T>
+hipError_t rows_any(int S, int d, int E, int F, const int32_t *offsets, const void *in0, const void *in1, const int32_t *perm,
+                    int K, const float *gates, const void *W0, const void *W1, const void *FA, const void *FB, void *o0,
+                    void *o1, void *o2, hipStream_t s) {
+    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d;
+    const bool vec = d % 4 == 0 && F % 4 == 0;
+    const bool big = ceil_div(S, 128) * ceil_div(NOUT, MODE == PLAIN_FFN1 ? 64 : 128) >= kFill;
+#define R3_ROWS(C, V)                                                                                                   \
+    rows_launch<C, MODE, T, V>(S, d, E, F, offsets, (const T *)in0, (const T *)in1, perm, K, gates, (const T *)W0,      \
+                               (const T *)W1, (const T *)FA, (const T *)FB, (T *)o0, (T *)o1, (T *)o2, s)
+    if (vec && big) R3_ROWS(PlainBig, true);
+    else if (vec) R3_ROWS(PlainSmall, true);
+    else R3_ROWS(PlainSmall, false);
+#undef R3_ROWS
+    return hipGetLastError();
+}
+
+template <int MODE>
+hipError_t rows_by_act(int act, int S, int d, int E, int F, const int32_t *offsets, const void *in0, const void *in1,
+                       const int32_t *perm, int K, const float *gates, const void *W0, const void *W1, const void *FA,
+                       const void *FB, void *o0, void *o1, void *o2, hipStream_t s) {
+    return act == R3_BF16 ? rows_any<MODE, bf16_t>(S, d, E, F, offsets, in0, in1, perm, K, gates, W0, W1, FA, FB, o0, o1, o2, s)
+                          : rows_any<MODE, float>(S, d, E, F, offsets, in0, in1, perm, K, gates, W0, W1, FA, FB, o0, o1, o2, s);
+}
+
+template <class C, typename T, bool VEC>
+void wgrad_launch(int E, int K, const int32_t *offsets, PlainWgrad3<T> all, int accumulate, hipStream_t s) {
+    int per = 0;
+    for (auto &g : all.g) per += g.tiles = (int)(g.out ? ceil_div(g.NQ, C::BQ) * ceil_div(g.NP, C::BP) : 0);
+    auto k = plain_wgrad_kernel<C, T, VEC>;
+    allow_lds(k, C::LDS);
+    k<<<(unsigned)((int64_t)E * per), C::NT, C::LDS, s>>>(E, K, offsets, all, accumulate);
+}
+
+template <typename T>
+hipError_t wgrads_any(int d, int E, int F, int K, const int32_t *offsets, const T *H, const T *dYrows,
+                      const int32_t *dyperm, const T *xrows, const int32_t *xperm, const T *dA, const T *dB, float *dWg,
+                      float *dWu, float *dWd, int accumulate, hipStream_t s) {
+    PlainWgrad3<T> all = {{{H, dYrows, nullptr, dyperm, dWd, F, d, 0},
+                           {xrows, dA, xperm, nullptr, dWg, d, F, 0},
+                           {xrows, dB, xperm, nullptr, dWu, d, F, 0}}};
+    const bool vec = d % 4 == 0 && F % 4 == 0;
+    const bool big = 3 * (int64_t)E * ceil_div(d, 128) * ceil_div(F, 128) >= kFill;
+    if (vec && big) wgrad_launch<PlainBig, T, true>(E, K, offsets, all, accumulate, s);
+    else if (vec) wgrad_launch<PlainSmall, T, true>(E, K, offsets, all, accumulate, s);
+    else wgrad_launch<PlainSmall, T, false>(E, K, offsets, all, accumulate, s);
+    return hipGetLastError();
+}
+
+// tokens per part of dW_r: enough parts to give every compute unit a tile, at least 64 tokens each
+int dwr_rows(int T, int d, int E) {
+    const int64_t tiles = ceil_div(d, 64) * ceil_div(E, 64);
+    const int64_t ns = std::max<int64_t>(1, std::min<int64_t>(ceil_div(T, 64), ceil_div(256, tiles)));
+    return (int)(ceil_div(ceil_div(T, ns), 32) * 32);
+}
+
+template <typename T>
+hipError_t dwr_any(int Tn, int d, int E, const T *x, const T *ds, float *part, float *dWr, int accumulate, hipStream_t s) {
+    typedef PlainSmall C;
+    const int rows = dwr_rows(Tn, d, E), ns = (int)ceil_div(Tn, rows);
+    const unsigned grid = (unsigned)(ns * ceil_div(d, C::BQ) * ceil_div(E, C::BP));
+    const bool vx = d % 4 == 0, ve = E % 4 == 0;
+#define R3_DWR(VX, VE)                                                                              \
+    do {                                                                                            \
+        allow_lds(plain_dwr_kernel<C, T, VX, VE>, C::LDS);                                          \
+        plain_dwr_kernel<C, T, VX, VE><<<grid, C::NT, C::LDS, s>>>(Tn, d, E, rows, x, ds, part);    \
+    } while (0)
+    if (vx && ve) R3_DWR(true, true);
+    else if (vx) R3_DWR(true, false);
+    else if (ve) R3_DWR(false, true);
+    else R3_DWR(false, false);
+#undef R3_DWR
+    const int64_t n = (int64_t)d * E;
+    plain_sum_parts_kernel<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(n, ns, part, dWr, accumulate);
+    return hipGetLastError();
+}
+
+template <typename T>
+hipError_t logits_any(int Tn, int d, int E, const T *x, const T *Wr, const float *bias, float *logits, hipStream_t s) {
+    typedef PlainSmall C;
+    const unsigned grid = (unsigned)(ceil_div(Tn, C::BQ) * ceil_div(E, C::BP));
+    const bool vx = d % 4 == 0, ve = E % 4 == 0;
+#define R3_LOGITS(VX, VE)                                                                             \
+    do {                                                                                              \
+        allow_lds(plain_logits_kernel<C, T, VX, VE>, C::LDS);                                         \
+        plain_logits_kernel<C, T, VX, VE><<<grid, C::NT, C::LDS, s>>>(Tn, d, E, x, Wr, bias, logits); \
+    } while (0)
+    if (vx && ve) R3_LOGITS(true, true);
+    else if (vx) R3_LOGITS(true, false);
+    else if (ve) R3_LOGITS(false, true);
+    else R3_LOGITS(false, false);
+#undef R3_LOGITS
+    return hipGetLastError();
+}
+
+}  // namespace
+
+hipError_t plain_router_logits(int T, int d, int E, int act, const void *x, const void *Wr, const float *bias, float *logits,
+                               hipStream_t s) {
+    ProfScope ps(PROF_LOGITS, s);
+    return act == R3_BF16 ? logits_any(T, d, E, (const bf16_t *)x, (const bf16_t *)Wr, bias, logits, s)
+                          : logits_any(T, d, E, (const float *)x, (const float *)Wr, bias, logits, s);
+}
+
+hipError_t plain_ffn2(int S, int d, int E, int F, int act, const void *H, const int32_t *offsets, const void *Wd, void *Yp,
+                      hipStream_t s) {
+    ProfScope ps(PROF_FFN2, s);
+    return rows_by_act<PLAIN_DOWN>(act, S, d, E, F, offsets, H, nullptr, nullptr, 1, nullptr, Wd, nullptr, nullptr, nullptr, Yp,
+                                   nullptr, nullptr, s);
+}
+
+hipError_t plain_ffn1(int S, int d, int E, int F, int act, const void *rows, const int32_t *perm, int K,
+                      const int32_t *offsets, const void *Wg, const void *Wu, void *H, void *FA, void *FB, const float *gates,
+                      hipStream_t s) {
+    ProfScope ps(PROF_FFN1, s);
+    return rows_by_act<PLAIN_FFN1>(act, S, d, E, F, offsets, rows, nullptr, perm, K, gates, Wg, Wu, nullptr, nullptr, H, FA, FB,
+                                   s);
+}
+
+hipError_t plain_dh(int S, int d, int E, int F, int act, const void *dYp, const int32_t *offsets, const void *Wd,
+                    const void *FA, const void *FB, void *dA, void *dB, hipStream_t s) {
+    ProfScope ps(PROF_DH, s);
+    return rows_by_act<PLAIN_DH>(act, S, d, E, F, offsets, dYp, nullptr, nullptr, 1, nullptr, Wd, nullptr, FA, FB, dA, dB,
+                                 nullptr, s);
+}
+
+hipError_t plain_dxp(int S, int d, int E, int F, int act, const void *dA, const void *dB, const int32_t *offsets,
+                     const void *Wg, const void *Wu, void *dXp, hipStream_t s) {
+    ProfScope ps(PROF_DXP, s);
+    return rows_by_act<PLAIN_DXP>(act, S, d, E, F, offsets, dA, dB, nullptr, 1, nullptr, Wg, Wu, nullptr, nullptr, dXp, nullptr,
+                                  nullptr, s);
+}
+
+hipError_t plain_wgrads(int d, int E, int F, int K, int act, const int32_t *offsets, const void *H, const void *dYrows,
+                        const int32_t *dyperm, const void *xrows, const int32_t *xperm, const void *dA, const void *dB,
+                        float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s) {
+    ProfScope ps(PROF_WGRAD, s);
+    return act == R3_BF16
+               ? wgrads_any<bf16_t>(d, E, F, K, offsets, (const bf16_t *)H, (const bf16_t *)dYrows, dyperm, (const bf16_t *)xrows,
+                                    xperm, (const bf16_t *)dA, (const bf16_t *)dB, dWg, dWu, dWd, accumulate, s)
+               : wgrads_any<float>(d, E, F, K, offsets, (const float *)H, (const float *)dYrows, dyperm, (const float *)xrows,
+                                   xperm, (const float *)dA, (const float *)dB, dWg, dWu, dWd, accumulate, s);
+}
+
+size_t plain_dwr_ws_bytes(int T, int d, int E) {
+    return align_up((size_t)ceil_div(T, dwr_rows(T, d, E)) * d * E * sizeof(float), 256);
+}
+
+hipError_t plain_dwr(int T, int d, int E, int act, const void *x, const void *ds, float *part, float *dWr, int accumulate,
+                     hipStream_t s) {
+    ProfScope ps(PROF_DWR, s);
+    return act == R3_BF16 ? dwr_any(T, d, E, (const bf16_t *)x, (const bf16_t *)ds, part, dWr, accumulate, s)
+                          : dwr_any(T, d, E, (const float *)x, (const float *)ds, part, dWr, accumulate, s);
+}
+
+}  // namespace r3

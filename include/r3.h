@@ -211,14 +211,13 @@ int r3_moe_forward(const r3_layer_desc *desc, const void *x, const void *W_r, co
  * NULL.  accumulate = 0 overwrites the weight gradients, 1 adds to them.
  * Experts outside a token's recorded set get exactly zero router gradient from
  * that token.
- * bf16 shapes the MFMA kernels tile (d and F multiples of 256): perm is
+ * bf16 with d and F multiples of 256: perm is
  * required and T*d*sizeof(act) < 2^31 (else R3_ERR_UNSUPPORTED).  The expert
  * gradients read the rows of dy (and of x when Xp is NULL) through perm inside
  * their tile loads, and the softmax backward takes its dot products
  * <dy_t, o_j> from the down projection's gradient GEMM (<dy, H W_down> =
  * <dy W_down^T, H>), so no per-slot copy of dy is made and Yp is not read: Yp
- * and Xp may be NULL.  Other shapes and f32 run plain kernels, which need Xp
- * and Yp and do not read perm.
+ * and Xp may be NULL.  Other shapes and f32 need Yp, and Xp or perm.
  * desc->flags = R3_FLAG_GATED_H: H and Yp are the gate-scaled tensors that
  * r3_moe_forward wrote (H = g silu(A) B, Yp = g o); perm is then required on
  * every path and Xp may be NULL on every path.

@@ -38,13 +38,13 @@ bool force_simt() {
     const char *v = getenv("R3_FORCE_SIMT");
     return v && v[0] == '1';
 }
-bool use_mfma_ffn(const Dims &m) { return m.act == R3_BF16 && mfma_ffn_supported(m.d, m.F) && !force_simt(); }
+bool use_mfma_ffn(const Dims &m) { return m.act == R3_BF16 && mfma_ffn_supported(m.S, m.d, m.F) && !force_simt(); }
 bool use_mfma_router(const Dims &m) { return m.act == R3_BF16 && mfma_router_supported(m.d, m.E) && !force_simt(); }
 
 struct BwdWs {
     size_t dXp, dz, ds, WrT, dA, dB, tiles, part, tok, Hg, grow, wpart, total;
 };
-int row_parts(const Dims &m) { return 2 * (m.F / 256); }   // partial dot products per row (MFMA path)
+int row_parts(const Dims &m) { return 2 * ((m.F + 255) / 256); }   // partial dot products per row (MFMA path)
 BwdWs bwd_layout(const Dims &m) {
     BwdWs w;
     size_t o = 0;
@@ -296,7 +296,9 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
     Dims m;
     int rc = check_desc(desc, m);
     if (rc) return rc;
-    const bool mf = use_mfma_ffn(m);
+    // (ragged widths also have the plain kernels, for callers that give no perm or a token matrix of 2 GB and more)
+    const bool mf = use_mfma_ffn(m) &&
+                    (!mfma_ffn_ragged(m.d, m.F) || (perm && (int64_t)m.T * m.d * m.eb < (1ll << 31)));
     const bool gated = (m.flags & R3_FLAG_GATED_H) != 0;   // H = g H and Yp = g o, as r3_moe_forward leaves them
     const void *ptrs[] = {dy, x, W_r, idx, gates, inv_perm, offsets, FA, FB, H, W_gate, W_up, W_down,
                           dx, dW_r, dW_gate, dW_up, dW_down};
@@ -332,7 +334,7 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
         // sit in the dXp buffer, which nothing uses before the parts are summed (dW_down's first, then, in
         // the same place, dW_gate's and dW_up's side by side)
         const size_t slot_bytes = 2 * (size_t)m.F * m.d * sizeof(float);
-        const int split = mfma_wgrad_split_rows(m.S, (m.F / 256) * (m.d / 256), (size_t)m.S * m.d * m.eb, slot_bytes);
+        const int split = mfma_wgrad_split_rows(m.S, ((m.F + 255) / 256) * ((m.d + 255) / 256), (size_t)m.S * m.d * m.eb, slot_bytes);
         if (mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, split, S, m.K, perm, gates, tok, grow, s) != hipSuccess)
             return R3_ERR_HIP;
         if (mfma_ffn_dh(m.S, m.d, m.E, m.F, dy, tok, m.T, grow, offsets, tiles, W_down, FA, FB, H, dA, dB, Hg, wpart,

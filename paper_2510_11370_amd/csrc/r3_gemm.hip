@@ -259,7 +259,12 @@ __device__ __forceinline__ void unpack4(uint2 v, float *f) {
 // (dB = dh FB); the sigmoid is in registers here anyway, and the backward's
 // epilogue is left with two multiplications per element.
 // ---------------------------------------------------------------------------
-template <bool GATHER>
+// RAGGED (this and the following expert GEMMs): widths that are multiples of 8 but not of the tile.  Loads past
+// a matrix's end read zero by the buffer bounds, chunks past the end of a reduction are masked (OpKC64's TAIL),
+// features past an output's width are computed on whatever their columns hold and not stored.  The flag is a
+// template parameter because the whole-tile kernels have no registers to spare for the guards.
+// T=3001 d=1000 E=64 K=6 F=704, forward + backward: 4.2 ms on f32 tiles, 0.72 ms on these.
+template <bool GATHER, bool RAGGED>
 __global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
 ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *__restrict__ perm, int K, int T,
             const int32_t *__restrict__ offsets, const int32_t *__restrict__ tiles, const bf16_t *__restrict__ Wg,
@@ -269,11 +274,12 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
     char *const bufA = lds, *const bufB = lds + kSuperBytes;
     char *const s0 = bufA, *const s1 = bufA + kStageBytes, *const s2 = bufB, *const s3 = bufB + kStageBytes;
     constexpr int BF = 128;  // features per tile
-    const int npt = F / BF;
+    const int npt = RAGGED ? (F + BF - 1) / BF : F / BF, nw = RAGGED ? (d + kBK3 - 1) / kBK3 : d / kBK3;
     OpTR128x2 P;
     P.init(F * 2, 0, 64 * ((threadIdx.x >> 6) % kWP2));
-    OpKC64<GATHER> Q;
+    OpKC64<GATHER, false, false, RAGGED> Q;
     Q.init(d * 2, kWaveRowsQ * ((threadIdx.x >> 6) / kWP2));
+    if constexpr (RAGGED) Q.set_tail(d);
     __shared__ int mailbox[2];
     RowTileLoop tl(tiles + kTileX, npt, tile_counters(tiles, 0));
     struct Tile {
@@ -319,8 +325,8 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
 
     Acc2 acc;
     zero_acc2(acc);
-    if (row_end - row0 <= kWaveRowsQ) mfma_tail_loop3(acc, d / kBK3, P, Q, lds);
-    else mfma_mainloop3(acc, d / kBK3, P, Q, lds, row_end - row0);
+    if (row_end - row0 <= kWaveRowsQ) mfma_tail_loop3(acc, nw, P, Q, lds);
+    else mfma_mainloop3(acc, nw, P, Q, lds, row_end - row0);
     tl.prefetch();
     if (more) aim(nxt);   // here, so that the row-index loads of a gathered tile hide behind the epilogue
 
@@ -360,10 +366,11 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
                     sb.put8(q, bo, pack4(fb[0], fb[1], fb[2], fb[3]));
                 }
             }
-        sh.flush((char *)H + o, (int64_t)F * 2, valid);
+        const int width = RAGGED ? (F - f0 - wp * 64) * 2 : 128;
+        sh.flush((char *)H + o, (int64_t)F * 2, valid, width);
         if (save) {
-            sa.flush((char *)FA + o, (int64_t)F * 2, valid);
-            sb.flush((char *)FB + o, (int64_t)F * 2, valid);
+            sa.flush((char *)FA + o, (int64_t)F * 2, valid, width);
+            sb.flush((char *)FB + o, (int64_t)F * 2, valid, width);
         }
     }
     const int after = tl.finish(mailbox);
@@ -390,7 +397,7 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
 // MODE 2: dXp = dA Wg^T + dB Wu^T   P from Wg[e], Wu[e] [d,F] (KC: rows c), K = 2F
 //         (two-phase reduction: first F over (dA, Wg), then F over (dB, Wu))
 // ---------------------------------------------------------------------------
-template <int MODE, bool GATED = false>
+template <int MODE, bool GATED, bool RAGGED>
 __global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
 rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t *__restrict__ Q1,
                const int32_t *__restrict__ offsets, const int32_t *__restrict__ tiles,
@@ -403,27 +410,30 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     char *const s0 = bufA, *const s1 = bufA + kStageBytes, *const s2 = bufB, *const s3 = bufB + kStageBytes;
     const int NOUT = (MODE == 1) ? F : d;  // width of the output
     const int KQ = (MODE == 1) ? d : F;    // width of the Q source rows
-    const int npt = NOUT / kTile;
-    const int nw = (MODE == 0) ? F / kBK3 : (MODE == 1) ? d / kBK3 : 2 * (F / kBK3);   // windows of 64 k
+    const int npt = RAGGED ? (NOUT + kTile - 1) / kTile : NOUT / kTile;
+    const int nwk = RAGGED ? (KQ + kBK3 - 1) / kBK3 : KQ / kBK3;   // windows of 64 k
+    const int nw = (MODE == 2) ? 2 * nwk : nwk;
     const int wp0 = (threadIdx.x >> 6) % kWP2, wq0 = (threadIdx.x >> 6) / kWP2;
     // operand forms: the weights are feature-contiguous (TR) for MODE 0, K-contiguous otherwise
-    typedef typename std::conditional<MODE == 0, OpTR256, OpKC64<false, false, true>>::type POp;
+    typedef typename std::conditional<MODE == 0, OpTR256, OpKC64<false, false, !RAGGED, RAGGED>>::type POp;
     constexpr bool GATHER = MODE == 1;     // Q rows through the row -> token list
     __shared__ int4 qstash[GATHER ? 2 * 256 : 1];   // the gathered rows' offsets (no registers to spare for them)
     POp P;
 #ifndef R3_DH_STASH
 #define R3_DH_STASH 1
 #endif
-    OpKC64<GATHER, GATHER && R3_DH_STASH> Q;
+    OpKC64<GATHER, GATHER && R3_DH_STASH, false, RAGGED> Q;
     if constexpr (MODE == 0) {
         P.kswitch = 0x7fffffff;
         P.init(d * 2, 0, 128 * wp0);
     } else {
         P.init((MODE == 1 ? d : F) * 2, 128 * wp0);
-        if constexpr (MODE == 2) P.wswitch = F / kBK3;
+        if constexpr (MODE == 2) P.wswitch = nwk;
+        if constexpr (RAGGED) P.set_tail(KQ);
     }
     Q.init(KQ * 2, kWaveRowsQ * wq0, qstash);
-    if constexpr (MODE == 2) Q.wswitch = F / kBK3;
+    if constexpr (MODE == 2) Q.wswitch = nwk;
+    if constexpr (RAGGED) Q.set_tail(KQ);
     __shared__ int mailbox[2];
     RowTileLoop tl(tiles + kTileX, npt, tile_counters(tiles, MODE == 1 ? 0 : 1));
     struct Tile {
@@ -499,6 +509,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     const int lane = tid & 63, wq = (tid >> 6) / kWP2, wp = (tid >> 6) % kWP2;
     RowStage<256> st{wave_patch(s0, s1, s2, s3, tid), tid};
     const int q = lane & 31;
+    const int width = RAGGED ? (NOUT - p0 - wp * 128) * 2 : 256;   // bytes of this wave's features that exist
     if constexpr (MODE == 1) {
         // Four rounds of 32 rows x 64 features, each in three phases: FA -> dA, FB -> dB, H -> g H and the
         // row's dot product.  A phase's rows come in row-contiguously into a patch, each lane replaces
@@ -519,7 +530,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
             int valid;
             const int64_t o = where(ph, valid);
             const char *src = ph % 3 == 0 ? (const char *)FA : ph % 3 == 1 ? (const char *)FB : (const char *)Hs;
-            return sa.fetch(src + o, (int64_t)NOUT * 2, valid);
+            return sa.fetch(src + o, (int64_t)NOUT * 2, valid, width - 128 * (ph / 3 & 1));
         };
 #ifndef R3_DH_AHEAD
 #define R3_DH_AHEAD 1
@@ -561,7 +572,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
                     if (!(GATED && which == 2)) sp.put8(q, bo, pack4(o[0], o[1], o[2], o[3]));
                 }
             bf16_t *dst = which == 0 ? out0 : which == 1 ? out1 : out2;
-            if (!(GATED && which == 2)) sp.flush((char *)dst + oh, (int64_t)NOUT * 2, valid);
+            if (!(GATED && which == 2)) sp.flush((char *)dst + oh, (int64_t)NOUT * 2, valid, width - 128 * half);
             if (which == 2 && half == 1) {
                 // the two lanes that hold row q (k-groups 0 and 1 of the MFMA layout) add up
                 const float w = (GATED ? 1.0f : gq) * (wsum + __shfl_xor(wsum, 32, 64));
@@ -582,7 +593,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
                     st.put8(q, (tp * 32 + g * 8 + (lane >> 5) * 4) * 2,
                             pack4(acc[tp][tq][4 * g], acc[tp][tq][4 * g + 1], acc[tp][tq][4 * g + 2],
                                   acc[tp][tq][4 * g + 3]));
-            st.flush((char *)out0 + o, (int64_t)NOUT * 2, valid);
+            st.flush((char *)out0 + o, (int64_t)NOUT * 2, valid, width);
         }
     }
     const int after = tl.finish(mailbox);
@@ -599,7 +610,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
 // ---------------------------------------------------------------------------
 // GATHER: Ps is the un-permuted matrix [nrows, NPd] and row r of the reduction is its row tok[r]
 // (dW_down = Hg^T dy straight from the upstream gradient: no per-slot copy of dy is read).
-template <bool GATHER>
+template <bool GATHER, bool RAGGED>
 __global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
 wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__restrict__ Ps,
              const int32_t *__restrict__ tok, int nrows, const int32_t *__restrict__ tiles,
@@ -610,7 +621,7 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
     __shared__ __attribute__((aligned(1024))) char s3[kStageBytes];
     __shared__ int mailbox[2];
     __shared__ __attribute__((aligned(256))) char ring[GATHER ? kIndexRingBytes : 16];
-    const int nqt = NQd / kTile, npt = NPd / kTile;
+    const int nqt = RAGGED ? (NQd + kTile - 1) / kTile : NQd / kTile, npt = RAGGED ? (NPd + kTile - 1) / kTile : NPd / kTile;
     const int wp0 = (threadIdx.x >> 6) % kWP2, wq0 = (threadIdx.x >> 6) / kWP2;
     // operands are set up once; a tile only moves their source windows (column offset included)
     typename std::conditional<GATHER, OpTR256G, OpTR256>::type P;
@@ -672,7 +683,10 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
                                          acc[tp][tq][4 * g + 3]));
                 }
             const int64_t off = ((int64_t)(q0 + wq * kWaveRowsQ + tq * 32) * NPd + p0 + wp * 128 + half * 64) * 4;
-            st.flush_f32(o + off, (int64_t)NPd * 4, 32, add);
+            if constexpr (RAGGED)
+                st.flush_f32(o + off, (int64_t)NPd * 4, NQd - (q0 + wq * kWaveRowsQ + tq * 32), add,
+                             (NPd - p0 - wp * 128 - half * 64) * 4);
+            else st.flush_f32(o + off, (int64_t)NPd * 4, 32, add);
         }
     } else {
         tl.prefetch();
@@ -692,7 +706,7 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
 // ---------------------------------------------------------------------------
 // GATHER: Qs is the un-permuted matrix [nrows, NQd] and row r of the reduction is its row tok[r]
 // (dW_gate, dW_up straight from x: no gathered copy of the tokens is read).
-template <bool GATHER>
+template <bool GATHER, bool RAGGED>
 __global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
 wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t *__restrict__ tok, int nrows,
                   const bf16_t *__restrict__ P0, const bf16_t *__restrict__ P1, const int32_t *__restrict__ tiles,
@@ -705,7 +719,7 @@ wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t
     __shared__ int mailbox[2];
     __shared__ __attribute__((aligned(256))) char ring[GATHER ? kIndexRingBytes : 16];
     constexpr int BF = 128;  // features of P0 (and of P1) per tile
-    const int nqt = NQd / kTile, npt = NPd / BF;
+    const int nqt = RAGGED ? (NQd + kTile - 1) / kTile : NQd / kTile, npt = RAGGED ? (NPd + BF - 1) / BF : NPd / BF;
     const int wp0 = (threadIdx.x >> 6) % kWP2, wq0 = (threadIdx.x >> 6) / kWP2;
     OpTR128x2 P;
     P.init(NPd * 2, 0, 64 * wp0);
@@ -764,7 +778,10 @@ wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t
             char *o = (char *)(pslot < 0 ? (half ? out1 : out0) + (int64_t)e * NQd * NPd
                                          : (half ? part1 : part0) + (int64_t)pslot * NQd * NPd);
             const int64_t off = ((int64_t)(q0 + wq * kWaveRowsQ + tq * 32) * NPd + p0 + wp * 64) * 4;
-            st.flush_f32(o + off, (int64_t)NPd * 4, 32, pslot < 0 ? accumulate : 0);
+            if constexpr (RAGGED)
+                st.flush_f32(o + off, (int64_t)NPd * 4, NQd - (q0 + wq * kWaveRowsQ + tq * 32), pslot < 0 ? accumulate : 0,
+                             (NPd - p0 - wp * 64) * 4);
+            else st.flush_f32(o + off, (int64_t)NPd * 4, 32, pslot < 0 ? accumulate : 0);
         }
     } else {
         tl.prefetch();
@@ -1030,7 +1047,17 @@ typedef TileCfg<128, 64, 2, 2, 64> TLLogits;   // router: 128 experts x 64 token
 typedef TileCfg<128, 128, 2, 2, 64> TLDwr;     // router (large batches): 128 experts x 128 tokens
 typedef TileCfg<256, 128, 2, 2, 64> TLDwrW;    // router wgrad: 256 columns of ds (hi, lo) x 128 hidden
 
-bool mfma_ffn_supported(int d, int F) { return d % 256 == 0 && F % 256 == 0 && d >= 256 && F >= 256; }
+// Rows come in 16-byte pieces (d, F multiples of 8).  Layers of very small matrices and few rows are left to the
+// f32 tiles (r3_plain.hip): a 256 x 256 tile of 40 x 40 features is nearly all padding and both paths are a chain of
+// launches then.  Where the line lies, forward + backward, bf16 tiles vs f32 tiles: 512 tokens top-4, 16 experts:
+// 96 x 96 134 vs 115 us, 128 x 128 136 vs 123, 200 x 128 148 vs 145; 64 tokens: 256 x 64 125 vs 109, 192 x 192
+// (64 experts) 140 vs 146; 4096 tokens: 64 x 64 188 vs 210, 320 x 320 (64 experts) 262 vs 762.
+bool mfma_ffn_supported(int64_t S, int d, int F) {
+    if (d % 8 != 0 || F % 8 != 0) return false;
+    const int64_t w = (int64_t)d * F;
+    return !(w <= (1 << 15) && S * w <= (1 << 25));
+}
+bool mfma_ffn_ragged(int d, int F) { return d % kTile != 0 || F % kTile != 0; }
 bool mfma_router_supported(int d, int E) { return E % 128 == 0 && d % 128 == 0; }  // 2E % 128 for ds
 
 size_t mfma_tiles_bytes(int64_t S, int E) {
@@ -1056,55 +1083,66 @@ hipError_t mfma_build_tiles_and_row_tokens(int E, const int32_t *offsets, int32_
     return hipGetLastError();
 }
 
+static int64_t tiles_of(int64_t n, int tile) { return (n + tile - 1) / tile; }
+
+template <bool GATHER, bool RAGGED>
+static void launch_ffn1(int64_t S, int d, int E, int F, const void *Xp, const int32_t *perm, int K, int T,
+                        const int32_t *offsets, const int32_t *tiles, const void *Wg, const void *Wu, void *H, void *FA,
+                        void *FB, const float *grow, hipStream_t s) {
+    const int64_t n = max_row_tiles(S, E, kTile) * tiles_of(F, 128);
+    ffn1_kernel<GATHER, RAGGED><<<persistent_grid(n), kThreads2, 0, s>>>(
+        (int)S, d, F, (const bf16_t *)Xp, perm, K, T, offsets, tiles, (const bf16_t *)Wg, (const bf16_t *)Wu, (bf16_t *)H,
+        (bf16_t *)FA, (bf16_t *)FB, grow);
+}
+
+template <int MODE, bool GATED, bool RAGGED>
+static void launch_rowgemm(int64_t S, int d, int E, int F, const void *Q0, const void *Q1, const int32_t *offsets,
+                           const int32_t *tiles, const void *W0, const void *W1, const void *FA, const void *FB, void *out0,
+                           void *out1, const int32_t *tok, int T, const float *grow, const void *H, void *Hg, float *wpart,
+                           hipStream_t s) {
+    const int64_t n = max_row_tiles(S, E, kTile) * tiles_of(MODE == 1 ? F : d, kTile);
+    rowgemm_kernel<MODE, GATED, RAGGED><<<persistent_grid(n), kThreads2, 0, s>>>(
+        (int)S, d, F, (const bf16_t *)Q0, (const bf16_t *)Q1, offsets, tiles, (const bf16_t *)W0, (const bf16_t *)W1,
+        (const bf16_t *)FA, (const bf16_t *)FB, (bf16_t *)out0, (bf16_t *)out1, tok, T, grow, (const bf16_t *)H, (bf16_t *)Hg,
+        wpart);
+}
+
 hipError_t mfma_ffn_forward(int64_t S, int d, int E, int F, const void *Xp, const int32_t *perm, int K, int T,
                             const int32_t *offsets, const int32_t *tiles, const void *Wg, const void *Wu,
                             const void *Wd, void *Yp, void *H, void *FA, void *FB, const float *grow,
                             hipStream_t s) {
-    const int mt = max_row_tiles(S, E, kTile);
+    const bool rag = mfma_ffn_ragged(d, F);
     {
         ProfScope ps(PROF_FFN1, s);
-        if (perm)
-            ffn1_kernel<true><<<persistent_grid((int64_t)mt * (F / 128)), kThreads2, 0, s>>>(
-                (int)S, d, F, (const bf16_t *)Xp, perm, K, T, offsets, tiles, (const bf16_t *)Wg, (const bf16_t *)Wu,
-                (bf16_t *)H, (bf16_t *)FA, (bf16_t *)FB, grow);
-        else
-            ffn1_kernel<false><<<persistent_grid((int64_t)mt * (F / 128)), kThreads2, 0, s>>>(
-                (int)S, d, F, (const bf16_t *)Xp, perm, K, T, offsets, tiles, (const bf16_t *)Wg, (const bf16_t *)Wu,
-                (bf16_t *)H, (bf16_t *)FA, (bf16_t *)FB, grow);
+        auto f = perm ? (rag ? launch_ffn1<true, true> : launch_ffn1<true, false>)
+                      : (rag ? launch_ffn1<false, true> : launch_ffn1<false, false>);
+        f(S, d, E, F, Xp, perm, K, T, offsets, tiles, Wg, Wu, H, FA, FB, grow, s);
     }
     ProfScope ps(PROF_FFN2, s);
-    rowgemm_kernel<0><<<persistent_grid((int64_t)mt * (d / kTile)), kThreads2, 0, s>>>(
-        (int)S, d, F, (const bf16_t *)H, nullptr, offsets, tiles, (const bf16_t *)Wd, nullptr, nullptr, nullptr,
-        (bf16_t *)Yp, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr);
+    auto f = rag ? launch_rowgemm<0, false, true> : launch_rowgemm<0, false, false>;
+    f(S, d, E, F, H, nullptr, offsets, tiles, Wd, nullptr, nullptr, nullptr, Yp, nullptr, nullptr, 0, nullptr, nullptr, nullptr,
+      nullptr, s);
     return hipGetLastError();
 }
 
 hipError_t mfma_ffn_dh(int64_t S, int d, int E, int F, const void *dy, const int32_t *tok, int T, const float *grow,
                        const int32_t *offsets, const int32_t *tiles, const void *Wd, const void *FA, const void *FB,
                        const void *H, void *dA, void *dB, void *Hg, float *wpart, hipStream_t s) {
-    const int mt = max_row_tiles(S, E, kTile);
     ProfScope ps(PROF_DH, s);
-    const int grid = persistent_grid((int64_t)mt * (F / kTile));
-    if (Hg)
-        rowgemm_kernel<1, false><<<grid, kThreads2, 0, s>>>(
-            (int)S, d, F, (const bf16_t *)dy, nullptr, offsets, tiles, (const bf16_t *)Wd, nullptr,
-            (const bf16_t *)FA, (const bf16_t *)FB, (bf16_t *)dA, (bf16_t *)dB, tok, T, grow, (const bf16_t *)H,
-            (bf16_t *)Hg, wpart);
-    else   // H already holds the gate-scaled rows
-        rowgemm_kernel<1, true><<<grid, kThreads2, 0, s>>>(
-            (int)S, d, F, (const bf16_t *)dy, nullptr, offsets, tiles, (const bf16_t *)Wd, nullptr,
-            (const bf16_t *)FA, (const bf16_t *)FB, (bf16_t *)dA, (bf16_t *)dB, tok, T, grow, (const bf16_t *)H,
-            nullptr, wpart);
+    const bool rag = mfma_ffn_ragged(d, F);
+    // Hg == NULL: H already holds the gate-scaled rows
+    auto f = Hg ? (rag ? launch_rowgemm<1, false, true> : launch_rowgemm<1, false, false>)
+                : (rag ? launch_rowgemm<1, true, true> : launch_rowgemm<1, true, false>);
+    f(S, d, E, F, dy, nullptr, offsets, tiles, Wd, nullptr, FA, FB, dA, dB, tok, T, grow, H, Hg, wpart, s);
     return hipGetLastError();
 }
 
 hipError_t mfma_ffn_dxp(int64_t S, int d, int E, int F, const void *dA, const void *dB, const int32_t *offsets,
                         const int32_t *tiles, const void *Wg, const void *Wu, void *dXp, hipStream_t s) {
-    const int mt = max_row_tiles(S, E, kTile);
     ProfScope ps(PROF_DXP, s);
-    rowgemm_kernel<2><<<persistent_grid((int64_t)mt * (d / kTile)), kThreads2, 0, s>>>(
-        (int)S, d, F, (const bf16_t *)dA, (const bf16_t *)dB, offsets, tiles, (const bf16_t *)Wg,
-        (const bf16_t *)Wu, nullptr, nullptr, (bf16_t *)dXp, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr);
+    auto f = mfma_ffn_ragged(d, F) ? launch_rowgemm<2, false, true> : launch_rowgemm<2, false, false>;
+    f(S, d, E, F, dA, dB, offsets, tiles, Wg, Wu, nullptr, nullptr, dXp, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr,
+      s);
     return hipGetLastError();
 }
 
@@ -1123,16 +1161,13 @@ int mfma_wgrad_split_rows(int64_t S, int tiles_per_seg, size_t part_bytes_availa
 
 hipError_t mfma_wgrad(int E, int NQd, int NPd, const void *Qs, const void *Ps, const int32_t *tok, int nrows,
                       const int32_t *tiles, int launch, float *out, float *part, int accumulate, hipStream_t s) {
-    const int64_t ntiles = (int64_t)(E + kMaxSplitSlots + 8) * (NQd / kTile) * (NPd / kTile);
+    const int64_t ntiles = (int64_t)(E + kMaxSplitSlots + 8) * tiles_of(NQd, kTile) * tiles_of(NPd, kTile);
     ProfScope ps(PROF_WGRAD, s);
-    if (tok)
-        wgrad_kernel<true><<<persistent_grid(ntiles), kThreads2, 0, s>>>(
-            NQd, NPd, (const bf16_t *)Qs, (const bf16_t *)Ps, tok, nrows, tiles, out, part, accumulate,
-            const_cast<int *>(tiles) + 2 + 8 * launch);
-    else
-        wgrad_kernel<false><<<persistent_grid(ntiles), kThreads2, 0, s>>>(
-            NQd, NPd, (const bf16_t *)Qs, (const bf16_t *)Ps, nullptr, 0, tiles, out, part, accumulate,
-            const_cast<int *>(tiles) + 2 + 8 * launch);
+    const bool rag = mfma_ffn_ragged(NQd, NPd);
+    auto k = tok ? (rag ? wgrad_kernel<true, true> : wgrad_kernel<true, false>)
+                 : (rag ? wgrad_kernel<false, true> : wgrad_kernel<false, false>);
+    k<<<persistent_grid(ntiles), kThreads2, 0, s>>>(NQd, NPd, (const bf16_t *)Qs, (const bf16_t *)Ps, tok, nrows, tiles, out,
+                                                    part, accumulate, const_cast<int *>(tiles) + 2 + 8 * launch);
     if (part) wgrad_parts_kernel<<<512, 256, 0, s>>>((int64_t)NQd * NPd / 4, tiles, out, part, nullptr, nullptr);
     return hipGetLastError();
 }
@@ -1140,18 +1175,16 @@ hipError_t mfma_wgrad(int E, int NQd, int NPd, const void *Qs, const void *Ps, c
 hipError_t mfma_wgrad_pair(int E, int NQd, int NPd, const void *Qs, const int32_t *tok, int nrows, const void *P0,
                            const void *P1, const int32_t *tiles, int launch, float *out0, float *out1, float *part,
                            int accumulate, hipStream_t s) {
-    const int64_t ntiles = (int64_t)(E + kMaxSplitSlots + 8) * (NQd / kTile) * (NPd / 128);
+    const int64_t ntiles = (int64_t)(E + kMaxSplitSlots + 8) * tiles_of(NQd, kTile) * tiles_of(NPd, 128);
     const int64_t n = (int64_t)NQd * NPd;
     float *part1 = part ? part + (int64_t)kMaxSplitSlots * n : nullptr;   // the second product's slots
     ProfScope ps(PROF_WGRAD_PAIR, s);
-    if (tok)
-        wgrad_pair_kernel<true><<<persistent_grid(ntiles), kThreads2, 0, s>>>(
-            NQd, NPd, (const bf16_t *)Qs, tok, nrows, (const bf16_t *)P0, (const bf16_t *)P1, tiles, out0, out1, part,
-            part1, accumulate, const_cast<int *>(tiles) + 2 + 8 * launch);
-    else
-        wgrad_pair_kernel<false><<<persistent_grid(ntiles), kThreads2, 0, s>>>(
-            NQd, NPd, (const bf16_t *)Qs, nullptr, 0, (const bf16_t *)P0, (const bf16_t *)P1, tiles, out0, out1, part,
-            part1, accumulate, const_cast<int *>(tiles) + 2 + 8 * launch);
+    const bool rag = mfma_ffn_ragged(NQd, NPd);
+    auto k = tok ? (rag ? wgrad_pair_kernel<true, true> : wgrad_pair_kernel<true, false>)
+                 : (rag ? wgrad_pair_kernel<false, true> : wgrad_pair_kernel<false, false>);
+    k<<<persistent_grid(ntiles), kThreads2, 0, s>>>(NQd, NPd, (const bf16_t *)Qs, tok, nrows, (const bf16_t *)P0,
+                                                    (const bf16_t *)P1, tiles, out0, out1, part, part1, accumulate,
+                                                    const_cast<int *>(tiles) + 2 + 8 * launch);
     if (part) wgrad_parts_kernel<<<512, 256, 0, s>>>(n / 4, tiles, out0, part, out1, part1);
     return hipGetLastError();
 }

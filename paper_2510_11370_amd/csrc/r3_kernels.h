@@ -91,7 +91,8 @@ hipError_t plain_dwr(int T, int d, int E, int act, const void *x, const void *ds
                      hipStream_t s);
 
 // r3_gemm.hip (bf16 MFMA)
-bool mfma_ffn_supported(int d, int F);
+bool mfma_ffn_supported(int64_t S, int d, int F);
+bool mfma_ffn_ragged(int d, int F);      // widths that are not whole tiles of 256
 bool mfma_router_supported(int d, int E);
 size_t mfma_tiles_bytes(int64_t S, int E);
 size_t mfma_dwr_ws_bytes(int T, int d, int E);

@@ -500,6 +500,7 @@ __device__ __forceinline__ void mfma_mainloop2(Acc2 &acc, int nk, const POp &P, 
 constexpr int kBK3 = 64;
 constexpr int kWinBytes = kTile * kBK3 * 2;   // 32 KB: one operand's window
 constexpr int kSuperBytes = 2 * kWinBytes;    // 64 KB: both operands
+constexpr int kOutsideWindow = 0x7ffffff0;    // a lane offset beyond any window: such a lane fetches zeros
 constexpr int kLoadsPerWindow = 16;           // tile loads per loader wave per window (8 per operand)
 
 // K-contiguous 256-row window [256 rows][128 B]: 32 chunks of 1 KB (8 rows x 128 B), eight per
@@ -513,8 +514,16 @@ constexpr int kLoadsPerWindow = 16;           // tile loads per loader wave per 
 // INSIDE (without ROWS): every row of the window exists (a weight panel), so the 32-row advance from
 // chunk to chunk rides in the load's scalar offset and the lane keeps one offset register; otherwise
 // (rows of an expert's segment, whose tail relies on the bounds check) each chunk has its own.
-template <bool ROWS, bool STASH = false, bool INSIDE = false>
+// TAIL: the reduction is not a multiple of 64 (a multiple of 8): the last window's chunks past its end, which are
+// the next row's values in memory, are fetched as zeros (`wlast`: that window; `ktail`: its live chunks).
+template <bool ROWS, bool STASH = false, bool INSIDE = false, bool TAIL = false>
 struct OpKC64 {
+    static_assert(!(INSIDE && TAIL), "a panel with a tail has no whole rows to rely on");
+    int wlast, ktail;      // TAIL
+    __device__ __forceinline__ void set_tail(int width) {
+        wlast = (width - 1) / kBK3;
+        ktail = (width - wlast * kBK3) / 8;
+    }
     static constexpr bool kIndexed = false, kWindowed = true;
     Src src[2];
     int wswitch;           // window from which src[1] takes over (two-phase reductions)
@@ -586,6 +595,12 @@ struct OpKC64 {
         } else {
 #pragma unroll
             for (int i = 0; i < 8; ++i) vo[i] = ROWS ? voff[(ROWS && !STASH) ? i : 0] : voff[0] + i * step;
+        }
+        if constexpr (TAIL) {
+            if (Js == wlast && lane_chunk() >= 16 * ktail) {
+#pragma unroll
+                for (int i = 0; i < 8; ++i) vo[i] = kOutsideWindow;
+            }
         }
         if (rows == kTile) {   // the common case as straight-line code
 #pragma unroll
@@ -930,14 +945,15 @@ struct RowStage {
     __device__ __forceinline__ void put8(int q, int byte_off, uint2 v) const { *(uint2 *)(base + q * PITCH + byte_off) = v; }
     __device__ __forceinline__ void put16(int q, int byte_off, float4 v) const { *(float4 *)(base + q * PITCH + byte_off) = v; }
     __device__ __forceinline__ uint2 get8(int q, int byte_off) const { return *(const uint2 *)(base + q * PITCH + byte_off); }
-    // rows [0, valid) of the patch -> out (byte pointer at row 0), row pitch ld_bytes
-    __device__ __forceinline__ void flush(char *out, int64_t ld_bytes, int valid) const {
+    // rows [0, valid) of the patch -> out (byte pointer at row 0), row pitch ld_bytes; only the first `width`
+    // bytes of a row (a multiple of 16; may be <= 0 or past the row's end)
+    __device__ __forceinline__ void flush(char *out, int64_t ld_bytes, int valid, int width = ROWB) const {
         const int lane = tid & 63, r = lane / LPR, c = lane % LPR;
 #pragma unroll
         for (int i = 0; i < 32 / RPI; ++i) {
             const int row = i * RPI + r;
             const uint4 v = *(const uint4 *)(base + row * PITCH + c * 16);
-            if (row < valid) {
+            if (row < valid && c * 16 < width) {
                 // non-temporal: the output is not read again by this kernel and should not displace
                 // operand tiles in L2 (measured: 1-3 % on the row-tiled GEMMs, at the price of 3 % on
                 // the much shorter kernels that read these rows next)
@@ -947,13 +963,13 @@ struct RowStage {
         }
     }
     // same for f32 rows, adding what is already in memory (accumulate != 0)
-    __device__ __forceinline__ void flush_f32(char *out, int64_t ld_bytes, int valid, int accumulate) const {
+    __device__ __forceinline__ void flush_f32(char *out, int64_t ld_bytes, int valid, int accumulate, int width = ROWB) const {
         const int lane = tid & 63, r = lane / LPR, c = lane % LPR;
 #pragma unroll 2
         for (int i = 0; i < 32 / RPI; ++i) {
             const int row = i * RPI + r;
             float4 v = *(const float4 *)(base + row * PITCH + c * 16);
-            if (row < valid) {
+            if (row < valid && c * 16 < width) {
                 float4 *dst = (float4 *)(out + row * ld_bytes + c * 16);
                 if (accumulate) {
                     const float4 old = *dst;
@@ -968,14 +984,14 @@ struct RowStage {
     struct Rows {
         uint4 v[32 / RPI];
     };
-    __device__ __forceinline__ Rows fetch(const char *in, int64_t ld_bytes, int valid) const {
+    __device__ __forceinline__ Rows fetch(const char *in, int64_t ld_bytes, int valid, int width = ROWB) const {
         const int lane = tid & 63, r = lane / LPR, c = lane % LPR;
         Rows x;
 #pragma unroll
         for (int i = 0; i < 32 / RPI; ++i) {
             const int row = i * RPI + r;
             x.v[i] = make_uint4(0u, 0u, 0u, 0u);
-            if (row < valid) {
+            if (row < valid && c * 16 < width) {
                 // read once per launch: non-temporal, so the rows do not displace operand tiles in L2
                 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
                 x.v[i] = __builtin_bit_cast(uint4, __builtin_nontemporal_load((const u32x4 *)(in + row * ld_bytes + c * 16)));
@@ -987,9 +1003,6 @@ struct RowStage {
         const int lane = tid & 63, r = lane / LPR, c = lane % LPR;
 #pragma unroll
         for (int i = 0; i < 32 / RPI; ++i) *(uint4 *)(base + (i * RPI + r) * PITCH + c * 16) = x.v[i];
-    }
-    __device__ __forceinline__ void fill(const char *in, int64_t ld_bytes, int valid) const {
-        deposit(fetch(in, ld_bytes, valid));
     }
 };
 

@@ -1,0 +1,56 @@
+"""The bf16 expert GEMMs at widths that are multiples of 8 but not of their 256 x 256 tiles: reductions that end inside a
+64-k window, feature tiles that end inside a wave's share, tail row tiles, and split weight-gradient reductions.  Both
+forwards and their backward against the CPU oracle, with the bars of tests/util.py."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sparse
+from paper_2510_11370_amd import r3, synth
+from util import Case, assert_close, host, router_gradient_sigma
+
+pytestmark = pytest.mark.gpu
+SH = synth.LayerShape
+
+
+@pytest.mark.parametrize("sh,one_call", [
+    (SH(T=300, d=264, E=128, K=8, F=136, sigma=0.02, seed=71), True),        # 8 over a window / a tile
+    (SH(T=611, d=504, E=16, K=6, F=328, sigma=0.02, zipf_s=1.0, seed=72), True),
+    (SH(T=611, d=504, E=16, K=6, F=328, sigma=0.02, zipf_s=1.0, seed=72), False),
+    (SH(T=77, d=1000, E=60, K=4, F=704, sigma=0.02, seed=73), True),         # tail tiles only
+    (SH(T=3000, d=256, E=16, K=2, F=72, sigma=0.02, seed=74), False),        # one width whole, the other not
+    (SH(T=9216, d=264, E=128, K=4, F=264, sigma=0.02, zipf_s=2.5, seed=75), True),   # split reductions
+], ids=lambda v: ("T%d_d%d_F%d" % (v.T, v.d, v.F)) if isinstance(v, SH) else ("one" if v else "steps"))
+def test_layer_at_ragged_widths(sh, one_call):
+    c = Case(sh, backward=True, scale_w=5.0)
+    n = c.np
+    fwd = sparse.forward(n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], n["bias"])
+    ref = sparse.backward(n["dy"], n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], fwd, want_dbias=True)
+    w = (c.t["Wg"], c.t["Wu"], c.t["Wd"])
+    buf = r3.LayerBuffers(c.D, backward=True, gathered_copy=not one_call)
+    for t in (buf.Yp, buf.H, buf.A, buf.B, buf.dx, buf.dW_gate, buf.dW_up, buf.dW_down):
+        t.fill_(7.0)      # an element left unwritten, or written past its row, shows
+    (r3.forward_one_call if one_call else r3.forward)(buf, c.t["x"], c.t["Wr"], c.t["idx"], *w, bias=c.t["bias"])
+    r3.backward(buf, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], *w)
+    torch.cuda.synchronize()
+    assert int(buf.status.item()) == 0
+    g = fwd["g"].reshape(-1)[fwd["perm"]][:, None] if one_call else 1.0
+    assert_close(host(buf.H), g * fwd["h"], "H", c.rel)
+    assert_close(host(buf.Yp), g * fwd["o"], "Yp", c.rel)
+    assert_close(host(buf.y), fwd["y"], "y", c.rel)
+    assert_close(host(buf.dx), ref["dx"], "dx", c.rel)
+    assert_close(buf.dW_r.cpu().numpy(), ref["dWr"], "dW_r", c.rel,
+                 router_gradient_sigma(n["x"], n["dy"], c.idx, fwd, sh.E)[0])
+    for got, key in ((buf.dW_gate, "dWg"), (buf.dW_up, "dWu"), (buf.dW_down, "dWd")):
+        got = got.cpu().numpy()
+        for e in range(sh.E):
+            assert np.linalg.norm(got[e] - ref[key][e]) <= c.rel * np.linalg.norm(ref[key][e]) + 1e-30, (key, e)
+    # a caller without perm still has the plain kernels (Xp given, forward call by call)
+    if not one_call:
+        dx = buf.dx.clone()
+        D = buf.D
+        r3.moe_backward(D, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], buf.gates, buf.inv_perm, None, buf.offsets, buf.Xp,
+                        buf.A, buf.B, buf.H, buf.Yp, *w, buf.dx, buf.dW_r, buf.dW_gate, buf.dW_up, buf.dW_down, buf.ws_bwd)
+        torch.cuda.synchronize()
+        assert_close(host(buf.dx), ref["dx"], "dx without perm", c.rel)
+        assert not torch.equal(dx, torch.zeros_like(dx))

@@ -151,17 +151,23 @@ int r3_replay_gate(const r3_layer_desc *desc, const void *x, const void *W_r, co
         (status_word && !aligned(status_word, 4)) || (m.idx == R3_IDX_U16 && !aligned(idx, 2)))
         return R3_ERR_INVALID_ARG;
     hipStream_t s = (hipStream_t)stream;
-    // one launch: the logits stay in the work-group that made them (no workspace needed)
-    if (use_mfma_router(m) && mfma_gate_fused_supported(m.d, m.E, m.K, agree_out != nullptr))
-        return hip_rc(mfma_gate_fused(m.T, m.d, m.E, m.K, x, W_r, bias, idx, m.idx, m.stride, gates, logits_out,
-                                      agree_out, status_word, s));
     float *logits = logits_out;
-    if (!logits) {
+    if (!logits && !(use_mfma_router(m) && m.E == 128 && (!agree_out || m.K <= 8))) {
         if (!ws || ws_bytes < r3_workspace_bytes(desc, R3_OP_REPLAY_GATE) || !aligned(ws, 256))
             return R3_ERR_WORKSPACE;
         logits = (float *)ws;
     }
     hipError_t e;
+    // one launch: the logits stay in the work-group that made them
+    if (router_gate_supported(m.act, m.d, m.E, force_simt())) {
+        // (the kernel counts agreement for K <= 8; beyond, a launch of its own reads the logits)
+        const bool count = agree_out && m.K <= 8;
+        e = router_gate(m.T, m.d, m.E, m.K, m.act, x, W_r, bias, idx, m.idx, m.stride, gates,
+                        agree_out && !count ? logits : logits_out, count ? agree_out : nullptr, status_word, force_simt(), s);
+        if (e != hipSuccess) return R3_ERR_HIP;
+        if (agree_out && !count) e = launch_agreement(m.T, m.E, m.K, logits, idx, m.idx, m.stride, agree_out, s);
+        return hip_rc(e);
+    }
     if (use_mfma_router(m)) e = mfma_router_logits(m.T, m.d, m.E, x, W_r, bias, logits, s);
     else e = plain_router_logits(m.T, m.d, m.E, m.act, x, W_r, bias, logits, s);
     if (e != hipSuccess) return R3_ERR_HIP;

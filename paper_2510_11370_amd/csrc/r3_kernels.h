@@ -90,6 +90,12 @@ size_t plain_dwr_ws_bytes(int T, int d, int E);   // partial products of plain_d
 hipError_t plain_dwr(int T, int d, int E, int act, const void *x, const void *ds, float *part, float *dWr, int accumulate,
                      hipStream_t s);
 
+// r3_router.hip: logits + replay gate (+ agreement counts, K <= 8) in one launch.  plain_only: f32 arithmetic
+bool router_gate_supported(int act, int d, int E, bool plain_only);
+hipError_t router_gate(int T, int d, int E, int K, int act, const void *x, const void *Wr, const float *bias, const void *idx,
+                       int idx_dtype, int64_t stride, float *gates, float *logits_out, int64_t *agree, int32_t *status,
+                       bool plain_only, hipStream_t s);
+
 // r3_gemm.hip (bf16 MFMA)
 bool mfma_ffn_supported(int64_t S, int d, int F);
 bool mfma_ffn_ragged(int d, int F);      // widths that are not whole tiles of 256
@@ -140,11 +146,6 @@ hipError_t mfma_wgrad_pair(int E, int NQd, int NPd, const void *Qs, const int32_
 size_t mfma_row_tokens_bytes(int64_t S);
 hipError_t mfma_router_logits(int T, int d, int E, const void *x, const void *Wr, const float *bias,
                               float *logits, hipStream_t s);
-// logits + replay gate (+ agreement counts) in one launch; E = 128 (see gate_fused_kernel)
-bool mfma_gate_fused_supported(int d, int E, int K, bool want_agreement);
-hipError_t mfma_gate_fused(int T, int d, int E, int K, const void *x, const void *Wr, const float *bias,
-                           const void *idx, int idx_dtype, int64_t stride, float *gates, float *logits_out,
-                           int64_t *agree, int32_t *status, hipStream_t s);
 hipError_t mfma_dwr(int T, int d, int E, const void *x, const void *ds, float *part, float *dWr, int accumulate,
                     hipStream_t s);
 

@@ -1,0 +1,439 @@
+// Router logits, replay gate and agreement in one launch (Section 4.1: first equation and the replay-gate
+// equation; Section 3.2, router level):
+//   s = x W_r (+ bias),  g_j = exp(s[id_j] - m) / sum_i exp(s[id_i] - m) over the recorded ids (m their maximum).
+// A work-group owns a few tokens and all experts, so a token's logits never leave it unless asked for.
+//
+// What bounds it: for few tokens latency, for many the read of x.  Every work-group streams the whole of W_r
+// (L2), so a serial walk over k is a chain of round trips: 32 of them took 24 us at 64 tokens, d = 2048.  Here the
+// waves of a work-group split k between them, each with its own operand tiles in flight and no barrier until the
+// partial logits are added in LDS (in a fixed order).
+#include <algorithm>
+
+#include "r3_kernels.h"
+#include "r3_mfma.h"
+#include "r3_mfma2.h"
+#include "r3_topk.h"
+
+namespace r3 {
+
+// The gate (and agreement) of a work-group's tokens from their logits in LDS: rows of PITCH floats, entries at and past
+// E undefined.  8 lanes take a token.  A recorded id >= E is clamped and raises R3_DATA_IDX_RANGE; a non-finite
+// logit among the recorded ones raises R3_DATA_NONFINITE.  agree (K <= 8): the token's own top-K mask (the record
+// kernel's selection) against the mask of the recorded ids; the block adds its counts once (integer atomics).
+// `part`: 2 * waves 64-bit words of LDS that hold nothing else.
+template <int NV, int NT, typename IdxT>
+__device__ __forceinline__ void gate_from_lds(const float *sl, int pitch, int t0, int nq, int T, int E, int K,
+                                              const IdxT *__restrict__ idx, int64_t stride, float *__restrict__ gates,
+                                              unsigned long long *agree, int32_t *status, unsigned long long *part) {
+    const int sub = threadIdx.x & 7;
+    int bad = 0;
+    unsigned long long equal = 0, common = 0;
+    for (int q = threadIdx.x >> 3; q < nq; q += NT / 8) {
+        const int t = t0 + q;
+        const bool live = t < T;
+        const float *row = sl + q * pitch;
+        const IdxT *id = idx + (int64_t)(live ? t : 0) * stride;
+        // gate: slots sub, sub + 8, ... of the token
+        float m = -INFINITY;
+        for (int j = sub; j < K; j += 8) {
+            int e = (int)id[j];
+            if (e >= E) { bad |= R3_DATA_IDX_RANGE; e = E - 1; }
+            const float z = row[e];
+            if (live && !(fabsf(z) <= 3.4028235e38f)) bad |= R3_DATA_NONFINITE;
+            m = fmaxf(m, z);
+        }
+        m = fmaxf(m, __shfl_xor(m, 1, 8));
+        m = fmaxf(m, __shfl_xor(m, 2, 8));
+        m = fmaxf(m, __shfl_xor(m, 4, 8));
+        float den = 0.0f;
+        for (int j = sub; j < K; j += 8) den += expf(row[min((int)id[j], E - 1)] - m);
+        den += __shfl_xor(den, 1, 8);
+        den += __shfl_xor(den, 2, 8);
+        den += __shfl_xor(den, 4, 8);
+        const float inv = 1.0f / den;
+        if (live)
+            for (int j = sub; j < K; j += 8) gates[(int64_t)t * K + j] = expf(row[min((int)id[j], E - 1)] - m) * inv;
+        if (agree) {
+            uint32_t key[NV][4];
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const float4 v = *(const float4 *)(row + 32 * i + 4 * sub);
+                const int e = 32 * i + 4 * sub;
+                bool nf;
+                // (experts that do not exist rank with the NaNs, behind every real one of that rank)
+                key[i][0] = e < E ? order_key(v.x, nf) : 0u;
+                key[i][1] = e + 1 < E ? order_key(v.y, nf) : 0u;
+                key[i][2] = e + 2 < E ? order_key(v.z, nf) : 0u;
+                key[i][3] = e + 3 < E ? order_key(v.w, nf) : 0u;
+            }
+            uint32_t own[NV], rec[NV];
+            topk_mask8<NV>(key, K, sub, own);
+            const int e = sub < K ? min((int)id[sub], E - 1) : -1;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                uint32_t w = (e >> 5) == i ? 1u << (e & 31) : 0u;   // e = -1 matches no word
+                w |= group8_exchange<0>(w);
+                w |= group8_exchange<1>(w);
+                w |= group8_exchange<2>(w);
+                rec[i] = w;
+            }
+            int shared = 0;
+#pragma unroll
+            for (int i = 0; i < NV; ++i) shared += __popc(own[i] & rec[i]);
+            if (live && sub == 0) {
+                common += (unsigned long long)shared;
+                equal += shared == K;
+            }
+        }
+    }
+    if (bad && status) atomicOr(status, bad);
+    if (agree) {
+        equal = wave_sum(equal);
+        common = wave_sum(common);
+        const int w = threadIdx.x / kWave;
+        if (lane_id() == 0) {
+            part[2 * w] = equal;
+            part[2 * w + 1] = common;
+        }
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            unsigned long long a0 = 0, a1 = 0;
+            for (int i = 0; i < NT / kWave; ++i) {
+                a0 += part[2 * i];
+                a1 += part[2 * i + 1];
+            }
+            if (a1) atomicAdd(agree + 1, a1);
+            if (a0) atomicAdd(agree, a0);
+        }
+    }
+}
+
+// Partial logits of the k groups (red: [WK][BQ][pitch], EP columns each) added up in ascending order into group
+// 0's rows, plus the bias; whole rows go to logits_out if it is given.
+template <int WK, int BQ, int EP, int NT>
+__device__ __forceinline__ void add_logits(float *red, int pitch, int t0, int T, int E, const float *__restrict__ bias,
+                                           float *__restrict__ logits_out) {
+    for (int i = threadIdx.x; i < BQ * (EP / 4); i += NT) {
+        const int q = i / (EP / 4), e = i % (EP / 4) * 4;
+        float *p = red + q * pitch + e;
+        float4 v = *(const float4 *)p;
+#pragma unroll
+        for (int g = 1; g < WK; ++g) {
+            const float4 w = *(const float4 *)(p + g * BQ * pitch);
+            v.x += w.x; v.y += w.y; v.z += w.z; v.w += w.w;
+        }
+        float s[4] = {v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+            if (bias && e + c < E) s[c] += bias[e + c];
+        *(float4 *)p = make_float4(s[0], s[1], s[2], s[3]);
+        if (logits_out && t0 + q < T) {
+            float *o = logits_out + (int64_t)(t0 + q) * E + e;
+            if (E % 4 == 0) {
+                if (e < E) *(float4 *)o = make_float4(s[0], s[1], s[2], s[3]);
+            } else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (e + c < E) o[c] = s[c];
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// bf16 (d and E multiples of 8, E <= 512).  NW waves: WE groups of 64 experts times WK = NW / WE groups that take
+// every WK-th step of 32 k.  A wave brings its step's W_r tile [32 k][64 experts] and x tile [BQ tokens][32 k]
+// into LDS of its own with direct loads, NBUF steps deep, and multiplies with 32x32x16 instructions.
+// W_r's k-rows are 128 B here: two to a bank line, so their 64-byte halves swap by bit 1 of k and the transposing
+// reads (4 k-rows of 64 B at a time) touch every bank once.
+// ---------------------------------------------------------------------------
+template <int NW, int WE, int TQ>
+struct RouterCfg {
+    static constexpr int WK = NW / WE, BQ = 32 * TQ, NT = 64 * NW, EP = 64 * WE, PITCH = EP + 4;
+    static constexpr int WT = 32 * 64 * 2, XT = BQ * 32 * 2, LPS = (WT + XT) / 1024;   // bytes per tile; loads per step
+    static constexpr int NBUF = TQ == 1 ? 3 : 2;
+    static constexpr int TILES = NW * NBUF * (WT + XT), RED = WK * BQ * PITCH * 4;
+    static constexpr int LDS = (TILES > RED ? TILES : RED) + 2 * NW * 8;
+};
+
+template <class C, int WE, int TQ, typename IdxT>
+__global__ void __launch_bounds__(C::NT)
+router_gate_kernel(int T, int d, int E, int K, const bf16_t *__restrict__ x, const bf16_t *__restrict__ Wr,
+                   const float *__restrict__ bias, const IdxT *__restrict__ idx, int64_t stride,
+                   float *__restrict__ gates, float *__restrict__ logits_out, unsigned long long *agree,
+                   int32_t *status) {
+    extern __shared__ __attribute__((aligned(1024))) char lds[];
+    const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+    const int we = wave % WE, kg = wave / WE;
+    const int t0 = blockIdx.x * C::BQ;
+    char *mine = lds + wave * C::NBUF * (C::WT + C::XT);
+    const uint32_t base = lds_addr(mine);
+    // W_r chunk i (1 KB): k-rows 8 i .. + 7, eight 16-byte pieces each
+    const rsrc_t rw = src_rsrc(Src{(const char *)Wr, (uint64_t)d * E * 2, 0u}, 0);
+    int wk[4], woff[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int k = 8 * i + (lane >> 3), p = lane & 7;
+        const int c = ((((p >> 2) ^ (k >> 1)) & 1) << 2) | (p & 3);
+        wk[i] = k;
+        woff[i] = 64 * we + 8 * c < E ? (k * E + 64 * we + 8 * c) * 2 : kOutsideWindow;
+    }
+    // x chunk i: tokens 16 i .. + 15, four pieces each, piece c of token r at c ^ ((r >> 2) & 3)
+    const rsrc_t rx = src_rsrc(Src{(const char *)(x + (int64_t)t0 * d), clamp_bytes((int64_t)(T - t0) * d * 2), 0u}, 0);
+    int xoff[2 * TQ];
+    const int xc = ((lane & 3) ^ ((lane >> 4) & 3)) * 8;   // (bits 2,3 of the token are bits 4,5 of the lane)
+#pragma unroll
+    for (int i = 0; i < 2 * TQ; ++i) xoff[i] = ((16 * i + (lane >> 2)) * d + xc) * 2;
+    auto issue = [&](int it, int buf) {
+        const int k0 = (it * C::WK + kg) * 32;
+        const uint32_t dst = base + buf * (C::WT + C::XT);
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+            lds_load16(rw, dst + 1024 * i, k0 + wk[i] < d && woff[i] != kOutsideWindow ? woff[i] + k0 * E * 2 : kOutsideWindow);
+#pragma unroll
+        for (int i = 0; i < 2 * TQ; ++i)
+            lds_load16(rx, dst + C::WT + 1024 * i, k0 + xc < d ? xoff[i] + k0 * 2 : kOutsideWindow);
+    };
+    // fragment addresses: W_r by the transposing read (see TrFrag), x rows as KcFrag<32>
+    const int b = lane >> 4, i16 = lane & 15;
+    const int wrow = (8 * (b >> 1) + (i16 >> 2)) * 128 + (i16 & 1) * 8;   // + 4 k-rows: the upper half of the 8 k
+    const int wsub = 2 * (b & 1) + ((i16 & 3) >> 1), wsw = (i16 >> 3) & 1;
+    KcFrag<32> xf;
+    xf.init(0, lane);
+    f32x16_t acc[2][TQ];
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int q = 0; q < TQ; ++q)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[e][q][v] = 0.0f;
+
+    const int nit = (d + 32 * C::WK - 1) / (32 * C::WK);
+#pragma unroll
+    for (int p = 0; p < C::NBUF - 1; ++p) issue(p, p);
+    int buf = 0;
+    for (int it = 0; it < nit; ++it) {
+        // the buffer asked for now is the one read last time round: those reads are over
+        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+        issue(it + C::NBUF - 1, buf == 0 ? C::NBUF - 1 : buf - 1);
+        constexpr int VM = (C::NBUF - 1) * C::LPS;
+        __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
+        asm volatile("" ::: "memory");
+        const char *wt = mine + buf * (C::WT + C::XT), *xt = wt + C::WT;
+#pragma unroll
+        for (int s = 0; s < 2; ++s) {
+            bf16x8_t a[2], bq[TQ];
+#pragma unroll
+            for (int e = 0; e < 2; ++e) {
+                const char *p = wt + s * 16 * 128 + wrow;
+                // bit 1 of the k-row is that of i16 >> 2 (rows 8 (b >> 1), + 4 and 16 s do not change it)
+                const char *pp = p + ((e ^ wsw) & 1) * 64 + wsub * 16;
+                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(pp));
+                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(pp + 4 * 128));
+                a[e] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+            }
+#pragma unroll
+            for (int q = 0; q < TQ; ++q) bq[q] = xf.read(xt, q, s);
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+#pragma unroll
+                for (int q = 0; q < TQ; ++q) acc[e][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[e], bq[q], acc[e][q], 0, 0, 0);
+        }
+        buf = buf == C::NBUF - 1 ? 0 : buf + 1;
+    }
+    __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0 << 8) | (0 << 14));   // no load may land in what follows
+    __syncthreads();
+    float *red = (float *)lds;
+#pragma unroll
+    for (int e = 0; e < 2; ++e)
+#pragma unroll
+        for (int q = 0; q < TQ; ++q)
+#pragma unroll
+            for (int g = 0; g < 4; ++g)
+                *(float4 *)(red + (kg * C::BQ + 32 * q + (lane & 31)) * C::PITCH + 64 * we + 32 * e + 8 * g + 4 * (lane >> 5)) =
+                    make_float4(acc[e][q][4 * g], acc[e][q][4 * g + 1], acc[e][q][4 * g + 2], acc[e][q][4 * g + 3]);
+    __syncthreads();
+    add_logits<C::WK, C::BQ, C::EP, C::NT>(red, C::PITCH, t0, T, E, bias, logits_out);
+    __syncthreads();
+    gate_from_lds<2 * WE, C::NT, IdxT>(red, C::PITCH, t0, C::BQ, T, E, K, idx, stride, gates, agree, status,
+                                       (unsigned long long *)(lds + C::LDS - 2 * 8 * (C::NT / 64)));
+}
+
+// ---------------------------------------------------------------------------
+// The same for E = 128 and many tokens: 128 tokens per work-group, so that W_r is streamed a quarter as often, and two
+// work-groups per compute unit, so that one's gates and prologue hide behind the other's loads.  k is walked in
+// sequence, two k-tiles ahead.
+// ---------------------------------------------------------------------------
+typedef TileCfg<128, 128, 2, 2, 64> TLGate;   // 128 experts x 128 tokens
+template <typename IdxT>
+__global__ void __launch_bounds__(TLGate::NT, 2)
+router_gate_many_kernel(int T, int d, int K, const bf16_t *__restrict__ x, const bf16_t *__restrict__ Wr,
+                        const float *__restrict__ bias, const IdxT *__restrict__ idx, int64_t stride,
+                        float *__restrict__ gates, float *__restrict__ logits_out, unsigned long long *agree,
+                        int32_t *status) {
+    typedef TLGate TL;
+    constexpr int E = TL::BP, PITCH = E + 4;   // floats per LDS row (the pad spreads rows over the banks)
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    __shared__ unsigned long long part[2 * TL::NWAVES];
+    const int t0 = blockIdx.x * TL::BQ;
+    auto fp = [&](int kt, int k, int c) -> uint4 { return ld16(Wr + (int64_t)(kt * TL::BK + k) * E + c * 8); };
+    auto fq = [&](int kt, int r, int c) -> uint4 {
+        return ld16(x + (int64_t)min(t0 + r, T - 1) * d + kt * TL::BK + c * 8);
+    };
+    f32x16_t acc[TL::TP][TL::TQ];
+    zero_acc<TL>(acc);
+    mfma_mainloop_ahead2<TL, true, false>(acc, d / TL::BK, fp, fq, lds);   // ends with a barrier: the stages are free
+    float *sl = (float *)lds;
+    for_each_quad<TL>([&](int tp, int tq, int g, int p, int q) {
+        *(float4 *)(sl + q * PITCH + p) = make_float4(acc[tp][tq][4 * g], acc[tp][tq][4 * g + 1], acc[tp][tq][4 * g + 2],
+                                                      acc[tp][tq][4 * g + 3]);
+    });
+    __syncthreads();
+    add_logits<1, TL::BQ, E, TL::NT>(sl, PITCH, t0, T, E, bias, logits_out);
+    __syncthreads();
+    gate_from_lds<E / 32, TL::NT, IdxT>(sl, PITCH, t0, TL::BQ, T, E, K, idx, stride, gates, agree, status, part);
+}
+
+// ---------------------------------------------------------------------------
+// f32 arithmetic, any d, E <= 128, both activation types: 16 tokens per work-group, 8 waves that take every 8th step of
+// 16 k.  Both operands go straight from global memory into fragments of the 16x16x4 instruction (a lane's four k
+// of a step are neighbours in x; W_r rows are read 16 experts at a time, out of cache).
+// ---------------------------------------------------------------------------
+template <int NE, bool VEC, typename T, typename IdxT>
+__global__ void __launch_bounds__(512)
+plain_gate_kernel(int Tn, int d, int E, int K, const T *__restrict__ x, const T *__restrict__ Wr,
+                  const float *__restrict__ bias, const IdxT *__restrict__ idx, int64_t stride, float *__restrict__ gates,
+                  float *__restrict__ logits_out, unsigned long long *agree, int32_t *status) {
+    constexpr int EP = NE < 2 ? 32 : 16 * NE, PITCH = EP + 4;   // (agreement reads rows in pieces of 32)
+    __shared__ __attribute__((aligned(16))) float red[8 * 16 * PITCH];
+    __shared__ unsigned long long part[16];
+    typedef float f32x4_t __attribute__((ext_vector_type(4)));
+    const int lane = lane_id(), wave = threadIdx.x >> 6, r16 = lane & 15, k4 = 4 * (lane >> 4);
+    const int t0 = blockIdx.x * 16;
+    const T *xr = x + (int64_t)min(t0 + r16, Tn - 1) * d;
+    f32x4_t acc[NE];
+#pragma unroll
+    for (int e = 0; e < NE; ++e) acc[e] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+    const int nst = (d + 127) / 128;
+    for (int it = 0; it < nst; ++it) {
+        const int k = (it * 8 + wave) * 16 + k4;
+        float xv[4] = {0.0f, 0.0f, 0.0f, 0.0f}, wv[NE][4];
+        if constexpr (VEC) {   // d is a multiple of four
+            if (k < d) {
+                if constexpr (sizeof(T) == 4) {
+                    const float4 v = *(const float4 *)(xr + k);
+                    xv[0] = v.x; xv[1] = v.y; xv[2] = v.z; xv[3] = v.w;
+                } else {
+                    const uint2 u = *(const uint2 *)(xr + k);
+                    xv[0] = __uint_as_float(u.x << 16); xv[1] = __uint_as_float(u.x & 0xffff0000u);
+                    xv[2] = __uint_as_float(u.y << 16); xv[3] = __uint_as_float(u.y & 0xffff0000u);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                if (k + i < d) xv[i] = Elem<T>::ld(xr + k + i);
+        }
+#pragma unroll
+        for (int e = 0; e < NE; ++e)
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+                wv[e][i] = k + i < d && 16 * e + r16 < E ? Elem<T>::ld(Wr + (int64_t)(k + i) * E + 16 * e + r16) : 0.0f;
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < NE; ++e) acc[e] = __builtin_amdgcn_mfma_f32_16x16x4f32(wv[e][i], xv[i], acc[e], 0, 0, 0);
+    }
+#pragma unroll
+    for (int e = 0; e < NE; ++e)
+        *(float4 *)(red + (wave * 16 + r16) * PITCH + 16 * e + k4) = make_float4(acc[e][0], acc[e][1], acc[e][2], acc[e][3]);
+    __syncthreads();
+    add_logits<8, 16, 16 * NE, 512>(red, PITCH, t0, Tn, E, bias, logits_out);
+    __syncthreads();
+    gate_from_lds<(NE + 1) / 2, 512, IdxT>(red, PITCH, t0, 16, Tn, E, K, idx, stride, gates, agree, status, part);
+}
+
+// ---------------------------------------------------------------------------
+// host side
+// ---------------------------------------------------------------------------
+namespace {
+
+template <int NW, int WE, int TQ, typename IdxT>
+void launch_router(int T, int d, int E, int K, const void *x, const void *Wr, const float *bias, const void *idx,
+                   int64_t stride, float *gates, float *logits_out, int64_t *agree, int32_t *status, hipStream_t s) {
+    typedef RouterCfg<NW, WE, TQ> C;
+    auto k = router_gate_kernel<C, WE, TQ, IdxT>;
+    (void)hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
+    k<<<(T + C::BQ - 1) / C::BQ, C::NT, C::LDS, s>>>(T, d, E, K, (const bf16_t *)x, (const bf16_t *)Wr, bias, (const IdxT *)idx,
+                                                   stride, gates, logits_out, (unsigned long long *)agree, status);
+}
+
+template <int NE, bool VEC, typename T, typename IdxT>
+void launch_plain(int Tn, int d, int E, int K, const void *x, const void *Wr, const float *bias, const void *idx,
+                  int64_t stride, float *gates, float *logits_out, int64_t *agree, int32_t *status, hipStream_t s) {
+    plain_gate_kernel<NE, VEC, T, IdxT><<<(Tn + 15) / 16, 512, 0, s>>>(Tn, d, E, K, (const T *)x, (const T *)Wr, bias,
+                                                                 (const IdxT *)idx, stride, gates, logits_out,
+                                                                 (unsigned long long *)agree, status);
+}
+
+template <typename IdxT>
+void router_by_size(int T, int d, int E, int K, const void *x, const void *Wr, const float *bias, const void *idx,
+                    int64_t stride, float *gates, float *logits_out, int64_t *agree, int32_t *status, hipStream_t s) {
+    // d = 2048, E = 128, us at 32 tokens per work-group / 64 / the kernel for many: 4096 tokens 12.4 / 16.0 / -, 8192
+    // 14.0 / 17.4 / 23.7, 16384 25.7 / 18.6 / 24.8, 32768 66 / 50 / 43, 65536 129 / 97 / 72.  The first two are at
+    // their best as long as every work-group has a compute unit of its own.
+    constexpr int kCus = 256;
+    const bool wide = T > 32 * kCus;
+    if (T > 64 * kCus && E == 128 && d % 64 == 0) {
+        constexpr int LDS = std::max(TLGate::LDS_BYTES, TLGate::BQ * (TLGate::BP + 4) * 4);
+        (void)hipFuncSetAttribute((const void *)router_gate_many_kernel<IdxT>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
+        router_gate_many_kernel<IdxT><<<(T + TLGate::BQ - 1) / TLGate::BQ, TLGate::NT, LDS, s>>>(
+            T, d, K, (const bf16_t *)x, (const bf16_t *)Wr, bias, (const IdxT *)idx, stride, gates, logits_out,
+            (unsigned long long *)agree, status);
+        return;
+    }
+#define R3_ROUTER(WE)                                                                                                  \
+    (wide ? launch_router<8, WE, 2, IdxT> : launch_router<8, WE, 1, IdxT>)(T, d, E, K, x, Wr, bias, idx, stride, gates, \
+                                                                            logits_out, agree, status, s)
+    if (E <= 64) R3_ROUTER(1);
+    else if (E <= 128) R3_ROUTER(2);
+    else if (E <= 256) R3_ROUTER(4);
+    else R3_ROUTER(8);
+#undef R3_ROUTER
+}
+
+template <typename T, typename IdxT>
+void plain_by_size(int Tn, int d, int E, int K, const void *x, const void *Wr, const float *bias, const void *idx,
+                   int64_t stride, float *gates, float *logits_out, int64_t *agree, int32_t *status, hipStream_t s) {
+    const bool vec = d % 4 == 0;
+    auto f = E <= 16   ? (vec ? launch_plain<1, true, T, IdxT> : launch_plain<1, false, T, IdxT>)
+             : E <= 32 ? (vec ? launch_plain<2, true, T, IdxT> : launch_plain<2, false, T, IdxT>)
+             : E <= 64 ? (vec ? launch_plain<4, true, T, IdxT> : launch_plain<4, false, T, IdxT>)
+                       : (vec ? launch_plain<8, true, T, IdxT> : launch_plain<8, false, T, IdxT>);
+    f(Tn, d, E, K, x, Wr, bias, idx, stride, gates, logits_out, agree, status, s);
+}
+
+}  // namespace
+
+bool router_gate_supported(int act, int d, int E, bool plain_only) {
+    if (act == R3_BF16 && !plain_only && d % 8 == 0 && E % 8 == 0 && E <= 512) return true;
+    return E <= 128;
+}
+
+hipError_t router_gate(int T, int d, int E, int K, int act, const void *x, const void *Wr, const float *bias, const void *idx,
+                       int idx_dtype, int64_t stride, float *gates, float *logits_out, int64_t *agree, int32_t *status,
+                       bool plain_only, hipStream_t s) {
+    ProfScope ps(PROF_GATE, s);
+    const bool u8 = idx_dtype == R3_IDX_U8;
+    if (act == R3_BF16 && !plain_only && d % 8 == 0 && E % 8 == 0 && E <= 512) {
+        auto f = u8 ? router_by_size<uint8_t> : router_by_size<uint16_t>;
+        f(T, d, E, K, x, Wr, bias, idx, stride, gates, logits_out, agree, status, s);
+    } else {
+        auto f = act == R3_BF16 ? (u8 ? plain_by_size<bf16_t, uint8_t> : plain_by_size<bf16_t, uint16_t>)
+                                : (u8 ? plain_by_size<float, uint8_t> : plain_by_size<float, uint16_t>);
+        f(T, d, E, K, x, Wr, bias, idx, stride, gates, logits_out, agree, status, s);
+    }
+    return hipGetLastError();
+}
+
+}  // namespace r3

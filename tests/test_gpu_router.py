@@ -1,0 +1,50 @@
+"""The one-launch router kernels (logits, replay gate, agreement) at the edges of their tiles and of the rule that picks
+between them, against the CPU oracle: gates to 1e-5 (tests/util.py), logits to a float32 sum's error, status and agreement."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sparse
+from paper_2510_11370_amd import r3, synth
+from util import Case, assert_gates_close
+
+pytestmark = pytest.mark.gpu
+SH = synth.LayerShape
+
+
+@pytest.mark.parametrize("sh", [
+    SH(T=1, d=8, E=8, K=8, F=8, seed=81),                            # one token, one piece of k
+    SH(T=33, d=264, E=72, K=6, F=8, zipf_s=0.5, seed=82),            # a token, a piece of k and an expert over the tiles
+    SH(T=64, d=1000, E=264, K=12, F=8, seed=83),                     # four expert groups; K > 8: agreement by its own launch
+    SH(T=130, d=512, E=512, K=8, F=8, seed=84),                      # the most experts of the bf16 kernel
+    SH(T=70, d=256, E=640, K=4, F=8, seed=85),                       # beyond it
+    SH(T=8192, d=64, E=128, K=8, F=8, seed=86), SH(T=8193, d=64, E=128, K=8, F=8, seed=87),       # 32 | 64 tokens
+    SH(T=16384, d=64, E=128, K=8, F=8, seed=88), SH(T=16385, d=64, E=128, K=8, F=8, seed=89),     # 64 | 128 tokens
+    SH(T=17, d=50, E=60, K=5, F=8, seed=90),                         # bf16 in f32 arithmetic
+    SH(T=49, d=132, E=9, K=3, F=8, act="f32", seed=91), SH(T=16, d=129, E=128, K=8, F=8, act="f32", zipf_s=0.7, seed=92),
+    SH(T=40, d=33, E=130, K=2, F=8, act="f32", seed=93),             # more experts than the f32 kernel holds
+], ids=lambda s: "T%d_d%d_E%d_K%d_%s" % (s.T, s.d, s.E, s.K, s.act))
+def test_router_at_tile_edges(sh):
+    c = Case(sh, backward=False)
+    gates = torch.empty(sh.T, sh.K, dtype=torch.float32, device="cuda")
+    logits = torch.full((sh.T + 1, sh.E), 7.0, dtype=torch.float32, device="cuda")     # a row to spare: nothing past the end
+    agree = torch.zeros(2, dtype=torch.int64, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    ws = r3.workspace(c.D, r3.OP_REPLAY_GATE)
+    r3.replay_gate(c.D, c.t["x"], c.t["Wr"], c.t["idx"], gates, bias=c.t["bias"], logits_out=logits, agree_out=agree,
+                   status=status, ws=ws)
+    torch.cuda.synchronize()
+    lg = logits.cpu().numpy()
+    assert (lg[-1] == 7.0).all() and int(status.item()) == 0
+    lg = lg[:-1]
+    assert np.abs(lg - c.s).max() <= 2e-5 * max(1.0, np.abs(c.s).max())
+    assert_gates_close(gates.cpu().numpy(), sparse.replay_gate(c.s, c.idx))
+    # the counts are of the kernel's own logits: exact against the oracle's selection on those
+    own = sparse.topk_mask(lg, sh.K)
+    assert tuple(agree.tolist()) == tuple(int(v) for v in sparse.agreement(own, c.idx))
+    # logits kept on chip: the same gates and counts
+    gates2 = torch.empty_like(gates)
+    r3.replay_gate(c.D, c.t["x"], c.t["Wr"], c.t["idx"], gates2, bias=c.t["bias"], agree_out=agree, ws=ws)
+    torch.cuda.synchronize()
+    assert torch.equal(gates, gates2)
+    assert tuple(agree.tolist()) == tuple(2 * int(v) for v in sparse.agreement(own, c.idx))

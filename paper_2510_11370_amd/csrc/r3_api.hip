@@ -189,7 +189,7 @@ int r3_permute(const r3_layer_desc *desc, const void *x, const void *idx, int32_
         return R3_ERR_INVALID_ARG;
     if (!ws || ws_bytes < permute_ws_bytes(m.T, m.E, m.K) || !aligned(ws, 256)) return R3_ERR_WORKSPACE;
     return hip_rc(launch_permute(m.T, m.d, m.E, m.K, m.eb, x, idx, m.idx, m.stride, counts, offsets, inv_perm,
-                                 perm, Xp, status_word, ws, (hipStream_t)stream));
+                                 perm, Xp, status_word, ws, DispatchExtra{}, (hipStream_t)stream));
 }
 
 int r3_permute_static(const r3_layer_desc *desc, const void *x, const void *idx, int32_t *counts,
@@ -269,17 +269,21 @@ int r3_moe_forward(const r3_layer_desc *desc, const void *x, const void *W_r, co
     rc = r3_replay_gate(&plain, x, W_r, bias, idx, gates, logits_out, agree_out, status_word, base + w.gate,
                         w.perm - w.gate, stream);
     if (rc) return rc;
-    rc = r3_permute(&plain, nullptr, idx, counts, offsets, inv_perm, perm, nullptr, status_word, base + w.perm,
-                    w.ffn - w.perm, stream);
-    if (rc) return rc;
+    if (!counts || !offsets || !inv_perm || !perm || !aligned(counts, 4) || !aligned(offsets, 4) || !aligned(inv_perm, 4) ||
+        !aligned(perm, 4))
+        return R3_ERR_INVALID_ARG;
+    const bool mf = use_mfma_ffn(m), with_tiles = mf && dispatch_makes_tiles(m.E);
+    int32_t *tiles = (int32_t *)(base + w.ffn), *tok = (int32_t *)(base + w.tok);
+    float *grow = (float *)(base + w.grow);
+    if (launch_permute(m.T, m.d, m.E, m.K, m.eb, nullptr, idx, m.idx, m.stride, counts, offsets, inv_perm, perm, nullptr,
+                       status_word, base + w.perm, with_tiles ? DispatchExtra{tiles, gates, tok, grow} : DispatchExtra{},
+                       s) != hipSuccess)
+        return R3_ERR_HIP;
     // the gate of every expert-sorted row: the first contraction's epilogue scales H with it, so the
     // down projection yields gated rows and the combination is a plain sum of each token's K rows
-    if (use_mfma_ffn(m)) {
-        int32_t *tok = (int32_t *)(base + w.tok);
-        float *grow = (float *)(base + w.grow);
-        int32_t *tiles = (int32_t *)(base + w.ffn);
-        if (mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, -1, (int)m.S, m.K, perm, gates, tok, grow, s) !=
-            hipSuccess)
+    if (mf) {
+        if (!with_tiles && mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, -1, (int)m.S, m.K, perm, gates, tok, grow, s) !=
+                               hipSuccess)
             return R3_ERR_HIP;
         if (mfma_ffn_forward(m.S, m.d, m.E, m.F, x, perm, m.K, m.T, offsets, tiles, W_gate, W_up, W_down, Yp, H,
                              FA_save, FB_save, grow, s) != hipSuccess)

@@ -11,20 +11,15 @@
 #include "r3_kernels.h"
 #include "r3_mfma.h"
 #include "r3_mfma2.h"
+#include "r3_tiles.h"
+
 
 namespace r3 {
 
+static_assert(kRowTile == kTile, "the tile table's row tiles are the GEMMs'");
+
 // ---------------------------------------------------------------------------
-// Tile table, built by one block per pass:
-//   tiles[0] = number of row tiles; tiles[1] = number of reduction segments (a multiple of 8);
-//   tiles[2 .. 2+64) = the tile counters of up to eight persistent launches (8 XCDs each, zeroed here);
-//   tiles[kTileSeg ..)  = reduction segments (expert, row0, row1, slot), longest first, dealt out evenly to
-//     the 8 XCD shares of a tile list;
-//   tiles[kTileHot ..)  = number of split experts, then (expert, first slot, slots) for each;
-//   tiles[kTileX .. +9) = where each XCD's share of the row tiles starts (and where the last one ends);
-//   tiles[kTileHdr ..)  = row tiles as (expert, row0) pairs, experts ascending, rows ascending (tiles
-//     that share a weight panel are neighbours and meet in one L2); XCD x's share is the eighth
-//     [tiles[kTileX + x], tiles[kTileX + x + 1]) of them, which its work-groups take from a counter.
+// Tile table (layout in r3_tiles.h), built by one block per pass.
 // The weight-gradient kernels' tiles last as long as their expert has rows: taken longest first from a
 // shared counter, a heavily loaded expert no longer starts late and finishes alone.  A segment is an
 // expert's whole row range, or, when `split_rows` > 0, one of ceil(n / split_rows) equal parts of it
@@ -36,13 +31,6 @@ namespace r3 {
 // 8 have slot -2 and are skipped.  At most kMaxSplitSlots slots are handed out (the caller's split_rows
 // >= S / kMaxSplitSlots guarantees that this is never the binding limit).
 // ---------------------------------------------------------------------------
-constexpr int kRowTokensPad = 64;   // zeros after the row->token list
-constexpr int kMaxSplitSlots = 32;
-constexpr int kMaxSegs = kMaxE + kMaxSplitSlots + 8;
-constexpr int kTileX = 2 + 64;               // 9 ints: first row tile of every XCD's share, and the end
-constexpr int kTileSeg = kTileX + 16;
-constexpr int kTileHot = kTileSeg + 4 * kMaxSegs;
-constexpr int kTileHdr = kTileHot + 1 + 3 * kMaxSplitSlots + 3;
 __device__ __forceinline__ int *tile_counters(const int32_t *tiles, int launch) {
     return const_cast<int *>(tiles) + 2 + 8 * launch;
 }

@@ -26,9 +26,18 @@ hipError_t launch_gate(int T, int E, int K, const float *logits, const void *idx
 hipError_t launch_agreement(int T, int E, int K, const float *logits, const void *idx, int idx_dtype,
                             int64_t stride, int64_t *agree, hipStream_t s);
 size_t permute_ws_bytes(int T, int E, int K);
+// What the dispatch may make in the same launch (dispatch_makes_tiles(E)): the expert GEMMs' tile table without
+// reduction segments, tok[row] = token of the row (padded), grow[row] = gates of the row's slot.  All or none.
+struct DispatchExtra {
+    int32_t *tiles;
+    const float *gates;
+    int32_t *tok;
+    float *grow;
+};
+bool dispatch_makes_tiles(int E);
 hipError_t launch_permute(int T, int d, int E, int K, int elem_bytes, const void *x, const void *idx,
                           int idx_dtype, int64_t stride, int32_t *counts, int32_t *offsets,
-                          int32_t *inv_perm, int32_t *perm, void *Xp, int32_t *status, void *ws,
+                          int32_t *inv_perm, int32_t *perm, void *Xp, int32_t *status, void *ws, const DispatchExtra &extra,
                           hipStream_t s);
 hipError_t launch_combine(int T, int d, int K, int act, const void *Yp, const float *gates,
                           const int32_t *inv_perm, void *y, hipStream_t s);

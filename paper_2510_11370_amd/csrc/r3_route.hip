@@ -3,7 +3,10 @@
 // element-wise parts of the backward.  All of them are bound by HBM traffic, so
 // they move 16-byte vectors per lane, read every input once and use wave-level
 // reductions; none uses floating-point atomics (results are bit-reproducible).
+#include <algorithm>
+
 #include "r3_kernels.h"
+#include "r3_tiles.h"
 #include "r3_topk.h"
 
 namespace r3 {
@@ -362,12 +365,17 @@ hipError_t launch_agreement(int T, int E, int K, const float *logits, const void
 }
 
 // ---------------------------------------------------------------------------
-// Dispatch permutation: stable counting sort of the T*K slots by expert.
-//   pass 1: per-chunk expert histograms (one wave per chunk of slots)
-//   pass 2: exclusive scan over (expert, chunk) -> offsets and chunk bases
-//   pass 3: every wave walks its chunk in slot order and places slots
-//   pass 4: row gather, one read of x[t] feeding its K destination rows
-// The placement never depends on arrival order, so perm is unique.
+// Dispatch permutation: stable counting sort of the T*K slots by expert.  The placement never depends on arrival
+// order, so perm is unique.
+//
+// Up to 1024 experts (dispatch_kernel): a work-group owns a chunk of slots, 64 per wave and step, and needs for every
+// expert the slots before its chunk and in all.  It finds them itself, without waiting for another work-group:
+// it counts all ids (LDS atomics; they are one or two bytes each, read as 16-byte vectors out of L2), or, when
+// that would be too many, adds up the chunk counts a first launch has left.  The expert GEMMs' tile table, the
+// row -> token list and the per-row gates come out of the same launch where the caller wants them.  Bound by
+// latency: r3_permute, K=8 E=128, took 26.5 us at T=1001 and 55.6 at T=131072 in three dependent launches (count, scan,
+// place), 9.3 in one and 28.1 in two; the tile table was a fourth.
+// Beyond 1024 experts: three launches (count per chunk, scan over the chunks, place).
 // ---------------------------------------------------------------------------
 // A wave's chunk is walked 64 slots at a time, kPermBatch such steps per batch: the ids of a whole
 // batch are fetched before any of them is used, so the wave pays one memory round trip per batch
@@ -390,9 +398,251 @@ struct SlotSplit {
 };
 constexpr int kWaitLds = 15 | (7 << 4) | (0 << 8) | (3 << 14);   // s_waitcnt lgkmcnt(0): LDS only, not the stores
 
+constexpr int kDispWaves = 16, kDispMaxE = 1024;
+constexpr int kDispStep = 64 * kDispWaves;       // slots a work-group takes per step
+struct DispatchArgs {
+    int T, E, K, steps, nchunks;
+    int64_t stride;
+    const int32_t *chunk_hist;                   // [nchunks][E] slots per chunk and expert (HIST only)
+    int32_t *counts, *offsets, *inv_perm, *perm, *status;
+    DispatchExtra x;
+};
+
+// sum over the lanes up to and with this one
+__device__ __forceinline__ int wave_scan(int v) {
+    const int lane = lane_id();
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+        const int u = __shfl_up(v, o, kWave);
+        if (lane >= o) v += u;
+    }
+    return v;
+}
+// the same over a block of 1024 threads; `tmp`: 16 ints of LDS
+__device__ __forceinline__ int block_scan(int v, int32_t *tmp) {
+    const int w = threadIdx.x >> 6;
+    v = wave_scan(v);
+    __syncthreads();
+    if (lane_id() == kWave - 1) tmp[w] = v;
+    __syncthreads();
+    for (int i = 0; i < w; ++i) v += tmp[i];
+    return v;
+}
+
+// slots per expert of every chunk
 template <typename IdxT>
+__global__ void __launch_bounds__(1024)
+dispatch_count_kernel(int T, int E, int K, const IdxT *__restrict__ idx, int64_t stride, int steps,
+                      int32_t *__restrict__ chunk_hist) {
+    extern __shared__ int32_t sm[];
+    for (int e = threadIdx.x; e < E; e += 1024) sm[e] = 0;
+    __syncthreads();
+    const int S = T * K, s0 = blockIdx.x * steps * kDispStep;
+    const SlotSplit split(K);
+    for (int i = 0; i < steps; i += 4) {
+        int ev[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int sl = s0 + (i + u) * kDispStep + threadIdx.x;
+            int t, j;
+            split(min(sl, S - 1), t, j);
+            ev[u] = i + u < steps && sl < S ? min((int)idx[(int64_t)t * stride + j], E - 1) : -1;
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (ev[u] >= 0) atomicAdd(&sm[ev[u]], 1);
+    }
+    __syncthreads();
+    for (int e = threadIdx.x; e < E; e += 1024) chunk_hist[(int64_t)blockIdx.x * E + e] = sm[e];
+}
+
+template <typename IdxT, bool HIST>
+__global__ void __launch_bounds__(1024)
+dispatch_kernel(const IdxT *__restrict__ idx, DispatchArgs a) {
+    extern __shared__ int32_t sm[];
+    const int E = a.E, K = a.K, S = a.T * K;
+    int32_t *cnt = sm, *before = sm + kDispWaves * E, *after = before + E, *tmp = after + E;   // cnt: [wave][E]
+    const int w = threadIdx.x >> 6, lane = lane_id(), c = blockIdx.x;
+    const bool table = c == a.nchunks;            // the last work-group (if asked for) only makes the tile table
+    const int chunk = a.steps * kDispStep;
+    const int s0 = c * chunk + w * a.steps * 64;  // this wave's slots
+    const SlotSplit split(K);
+    for (int i = threadIdx.x; i < (kDispWaves + 2) * E; i += 1024) sm[i] = 0;
+    __syncthreads();
+    auto fetch = [&](int step) -> int {           // this lane's id of a step, -1 past the end
+        const int sl = s0 + step * 64 + lane;
+        if (step >= a.steps || sl >= S) return -1;
+        int t, j;
+        split(sl, t, j);
+        return (int)idx[(int64_t)t * a.stride + j];
+    };
+    // this wave's counts, and the checks of its ids
+    int first = -1;                               // the first step's id is kept for the placement
+    if (!table) {
+        // a token's K ids sit in K neighbouring lanes of one step when K divides 64: the duplicate check
+        // compares lanes then, instead of loading ids again
+        const bool lanes_hold_token = 64 % K == 0;
+        int bad = 0;
+        for (int i = 0; i < a.steps; i += 4) {
+            int ev[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) ev[u] = fetch(i + u);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                int e = ev[u];
+                const bool live = e >= 0;
+                if (live && e >= E) {
+                    bad |= R3_DATA_IDX_RANGE;
+                    e = E - 1;
+                }
+                if (i == 0 && u == 0) first = e;
+                if (lanes_hold_token) {
+                    const int j = lane % K;       // (a wave's steps start at multiples of 64)
+                    for (int back = 1; back < K; ++back) {
+                        const int other = __shfl(e, lane - back);
+                        if (live && back <= j && other == e) bad |= R3_DATA_IDX_DUP;
+                    }
+                } else if (live) {
+                    int t, j;
+                    split(s0 + (i + u) * 64 + lane, t, j);
+                    for (int jj = 0; jj < j; ++jj)
+                        if (min((int)idx[(int64_t)t * a.stride + jj], E - 1) == e) bad |= R3_DATA_IDX_DUP;
+                }
+                if (live) atomicAdd(&cnt[w * E + e], 1);
+            }
+        }
+        if (bad && a.status) atomicOr(a.status, bad);
+    }
+    // slots before this chunk, and from it on, per expert
+    if constexpr (HIST) {
+        int Ep = 1;
+        while (Ep < E) Ep <<= 1;
+        const int e = threadIdx.x % Ep, g = threadIdx.x / Ep, G = 1024 / Ep;
+        int b = 0, f = 0;
+        if (e < E)
+            for (int q = g; q < a.nchunks; q += 8 * G) {
+                int h[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) h[u] = q + u * G < a.nchunks ? a.chunk_hist[(int64_t)(q + u * G) * E + e] : 0;
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    b += q + u * G < c ? h[u] : 0;
+                    f += q + u * G < c ? 0 : h[u];
+                }
+            }
+        if (b) atomicAdd(&before[e], b);
+        if (f) atomicAdd(&after[e], f);
+    } else if (a.stride == K && ((uintptr_t)idx & 15) == 0) {
+        constexpr int PER = 16 / sizeof(IdxT);    // ids per vector (chunks start at multiples of it)
+        const int nv = S / PER, cv = c * chunk / PER;
+        for (int v0 = threadIdx.x; v0 < nv; v0 += 4 * 1024) {
+            uint4 d[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) d[u] = v0 + u * 1024 < nv ? ((const uint4 *)idx)[v0 + u * 1024] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (v0 + u * 1024 >= nv) break;
+                int32_t *to = v0 + u * 1024 < cv ? before : after;
+                const uint32_t q[4] = {d[u].x, d[u].y, d[u].z, d[u].w};
+#pragma unroll
+                for (int i = 0; i < PER; ++i)
+                    atomicAdd(&to[min((int)((q[i * sizeof(IdxT) / 4] >> (8 * sizeof(IdxT) * (i % (4 / sizeof(IdxT))))) &
+                                            (sizeof(IdxT) == 1 ? 0xffu : 0xffffu)), E - 1)], 1);
+            }
+        }
+        for (int sl = nv * PER + threadIdx.x; sl < S; sl += 1024)
+            atomicAdd(&(sl < c * chunk ? before : after)[min((int)idx[sl], E - 1)], 1);
+    } else {
+        for (int i = threadIdx.x; i < S; i += 8 * 1024) {
+            int ev[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                int t, j;
+                split(min(i + u * 1024, S - 1), t, j);
+                ev[u] = min((int)idx[(int64_t)t * a.stride + j], E - 1);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u)
+                if (i + u * 1024 < S) atomicAdd(&(i + u * 1024 < c * chunk ? before : after)[ev[u]], 1);
+        }
+    }
+    __syncthreads();
+    // offsets, and where every wave's slots of an expert start
+    const int e = threadIdx.x;
+    const int bef = e < E ? before[e] : 0, n = e < E ? bef + after[e] : 0;
+    const int off = block_scan(n, tmp) - n;
+    if (e < E) {
+        int run = off + bef;
+#pragma unroll
+        for (int i = 0; i < kDispWaves; ++i) {
+            const int h = cnt[i * E + e];
+            cnt[i * E + e] = run;
+            run += h;
+        }
+        if (c == 0) {
+            a.counts[e] = n;
+            a.offsets[e] = off;
+            if (e == E - 1) a.offsets[E] = off + n;
+        }
+    }
+    if (table) {
+        int32_t *tiles = a.x.tiles;
+        const int nt = (n + kRowTile - 1) / kRowTile;
+        const int end = block_scan(nt, tmp), start = end - nt;
+        for (int i = 0; i < nt; ++i) {
+            tiles[kTileHdr + 2 * (start + i)] = e;
+            tiles[kTileHdr + 1 + 2 * (start + i)] = off + i * kRowTile;
+        }
+        if (threadIdx.x < 64) {
+            tiles[2 + threadIdx.x] = 0;
+            a.x.tok[S + threadIdx.x] = 0;         // kRowTokensPad
+        }
+        if (threadIdx.x == 1023) {
+            tiles[0] = end;
+            for (int x = 0; x <= 8; ++x) tiles[kTileX + x] = (int)(((int64_t)end * x) >> 3);
+        }
+        return;
+    }
+    __syncthreads();
+    int ebits = 1;
+    while ((1 << ebits) < E) ++ebits;
+    const uint64_t lt = (1ull << lane) - 1ull;
+    int32_t *mine = cnt + w * E;
+    for (int i = 0; i < a.steps; ++i) {
+        const int sl = s0 + i * 64 + lane;
+        const int ev = i == 0 ? first : fetch(i);
+        const bool live = ev >= 0;
+        const int ee = live ? min(ev, E - 1) : 0;
+        // lanes holding the same expert
+        uint64_t same = __ballot(live);
+        for (int b = 0; b < ebits; ++b) {
+            const uint64_t bal = __ballot((ee >> b) & 1);
+            same &= ((ee >> b) & 1) ? bal : ~bal;
+        }
+        if (live) {
+            const int row = mine[ee] + __popcll(same & lt);
+            a.inv_perm[sl] = row;
+            a.perm[row] = (int32_t)sl;
+            if (a.x.tok) {
+                int t, j;
+                split(sl, t, j);
+                a.x.tok[row] = t;
+                a.x.grow[row] = a.x.gates[sl];
+            }
+        }
+        if (i + 1 == a.steps) break;
+        // (LDS traffic only: the stores above need not have landed)
+        __builtin_amdgcn_s_waitcnt(kWaitLds);
+        __builtin_amdgcn_wave_barrier();
+        // the highest lane of each group advances the group's counter
+        if (live && (same >> lane) == 1ull) mine[ee] += __popcll(same);
+        __builtin_amdgcn_s_waitcnt(kWaitLds);
+        __builtin_amdgcn_wave_barrier();
+    }
+}
+
 __global__ void __launch_bounds__(256)
-permute_hist_kernel(int T, int E, int K, const IdxT *__restrict__ idx, int64_t stride, int chunk,
+permute_hist_kernel(int T, int E, int K, const uint16_t *__restrict__ idx, int64_t stride, int chunk,
                     int nchunks, int32_t *__restrict__ chunk_hist, int32_t *status) {
     extern __shared__ int32_t hist_all[];
     const int w = threadIdx.x / kWave, lane = lane_id();
@@ -450,93 +700,45 @@ permute_hist_kernel(int T, int E, int K, const IdxT *__restrict__ idx, int64_t s
     if (bad && status) atomicOr(status, bad);
 }
 
-// One block of 1024 threads.  chunk_base [nchunks,E] receives the exclusive running count of
-// chunk_hist over chunks; counts/offsets are written.  An expert's column of chunk_hist is shared out
-// among G = 1024 / E' threads (E' = E rounded up to a power of two), each taking a contiguous range of
-// chunks: sums of the ranges first, then every thread walks its range again from its own base.  (One
-// thread per expert walking all chunks paid a memory round trip per 8 chunks, 16 in a row at 128
-// chunks, with 7 of 8 threads idle at E = 128.)
+// One block of 1024 threads (more than 1024 experts).  chunk_base [nchunks,E] receives the exclusive running count of
+// chunk_hist over chunks; counts/offsets are written.
 __global__ void __launch_bounds__(1024)
 permute_scan_kernel(int E, int nchunks, const int32_t *__restrict__ chunk_hist, int32_t *__restrict__ chunk_base,
                     int32_t *__restrict__ counts, int32_t *__restrict__ offsets) {
     __shared__ int32_t tot[kMaxE];
-    __shared__ int32_t part[1024];
-    int Ep = 1;
-    while (Ep < E && Ep < 1024) Ep <<= 1;
-    const int G = E <= 1024 ? 1024 / Ep : 1;                 // threads per expert
-    const int per_g = (nchunks + G - 1) / G;                 // chunks per thread
-    const int g = E <= 1024 ? threadIdx.x / Ep : 0;
-    const int c0 = min(g * per_g, nchunks), c1 = min(c0 + per_g, nchunks);
-    auto walk = [&](int e, int32_t run, bool write) {
-        int c = c0;
-        for (; c + 8 <= c1; c += 8) {
+    __shared__ int32_t tmp[16];
+    for (int e = threadIdx.x; e < E; e += 1024) {
+        int32_t run = 0;
+        for (int c = 0; c < nchunks; c += 8) {
             int32_t h[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) h[u] = chunk_hist[(int64_t)(c + u) * E + e];
+            for (int u = 0; u < 8; ++u) h[u] = c + u < nchunks ? chunk_hist[(int64_t)(c + u) * E + e] : 0;
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                if (write) chunk_base[(int64_t)(c + u) * E + e] = run;
+                if (c + u < nchunks) chunk_base[(int64_t)(c + u) * E + e] = run;
                 run += h[u];
             }
         }
-        for (; c < c1; ++c) {
-            const int32_t h = chunk_hist[(int64_t)c * E + e];
-            if (write) chunk_base[(int64_t)c * E + e] = run;
-            run += h;
-        }
-        return run;
-    };
-    if (E <= 1024) {
-        const int e = threadIdx.x % Ep;
-        part[threadIdx.x] = e < E ? walk(e, 0, false) : 0;
-        __syncthreads();
-        int32_t base = 0, all = 0;
-        for (int gg = 0; gg < G; ++gg) {
-            const int32_t v = part[gg * Ep + e];
-            base += gg < g ? v : 0;
-            all += v;
-        }
-        if (e < E) {
-            walk(e, base, true);
-            if (g == 0) {
-                tot[e] = all;
-                counts[e] = all;
-            }
-        }
-    } else {
-        for (int e = threadIdx.x; e < E; e += blockDim.x) {
-            const int32_t all = walk(e, 0, true);
-            tot[e] = all;
-            counts[e] = all;
-        }
+        tot[e] = run;
+        counts[e] = run;
     }
     __syncthreads();
     // exclusive scan of tot[0..E): each thread owns a contiguous span
-    const int per = (E + blockDim.x - 1) / blockDim.x;
-    const int b = threadIdx.x * per;
+    const int per = (E + 1023) / 1024, b = threadIdx.x * per;
     int32_t sum = 0;
     for (int i = 0; i < per; ++i)
         if (b + i < E) sum += tot[b + i];
-    part[threadIdx.x] = sum;
-    __syncthreads();
-    for (int o = 1; o < (int)blockDim.x; o <<= 1) {
-        int32_t v = (threadIdx.x >= (unsigned)o) ? part[threadIdx.x - o] : 0;
-        __syncthreads();
-        part[threadIdx.x] += v;
-        __syncthreads();
-    }
-    int32_t run = part[threadIdx.x] - sum;
+    int32_t run = block_scan(sum, tmp) - sum;
     for (int i = 0; i < per; ++i)
         if (b + i < E) {
             offsets[b + i] = run;
             run += tot[b + i];
         }
-    if (threadIdx.x == blockDim.x - 1) offsets[E] = part[threadIdx.x];
+    if (threadIdx.x == 1023) offsets[E] = run;
 }
 
-template <typename IdxT>
 __global__ void __launch_bounds__(256)
-permute_place_kernel(int T, int E, int K, const IdxT *__restrict__ idx, int64_t stride, int chunk,
+permute_place_kernel(int T, int E, int K, const uint16_t *__restrict__ idx, int64_t stride, int chunk,
                      int nchunks, const int32_t *__restrict__ chunk_base,
                      const int32_t *__restrict__ offsets, int32_t *__restrict__ inv_perm,
                      int32_t *__restrict__ perm) {
@@ -634,33 +836,52 @@ size_t permute_ws_bytes(int T, int E, int K) {
     return 2 * align_up((size_t)nchunks * E * sizeof(int32_t), 256);  // histograms + running bases
 }
 
+// Where counting all ids in every work-group gives way to a launch that counts the chunks first (E=128 K=8, us, all /
+// first): 8192 slots 9.3 / 12.1, 32768 10.2 / 11.8, 131072 18.6 / 12.2, 1048576 369 / 28.1; under a skewed load the LDS
+// atomics of the first collide (131072 slots: 60 / 12.6), so the line is drawn early.
+constexpr int64_t kDispCountAll = 16384;
+
+template <typename IdxT>
+static void launch_dispatch(int T, int E, int K, const IdxT *idx, int64_t stride, int32_t *counts, int32_t *offsets,
+                            int32_t *inv_perm, int32_t *perm, int32_t *status, void *ws, const DispatchExtra &x,
+                            hipStream_t s) {
+    const int64_t S = (int64_t)T * K;
+    const bool hist = S > kDispCountAll;
+    const int chunk = hist ? std::max(2 * kDispStep, pick_chunk(S)) : kDispStep;
+    DispatchArgs a = {T, E, K, chunk / kDispStep, (int)((S + chunk - 1) / chunk), stride, (const int32_t *)ws, counts, offsets,
+                      inv_perm, perm, status, x};
+    if (hist) dispatch_count_kernel<IdxT><<<a.nchunks, 1024, E * sizeof(int32_t), s>>>(T, E, K, idx, stride, a.steps, (int32_t *)ws);
+    const size_t lds = ((size_t)(kDispWaves + 2) * E + kDispWaves) * sizeof(int32_t);
+    auto k = hist ? dispatch_kernel<IdxT, true> : dispatch_kernel<IdxT, false>;
+    if (lds > 65536) (void)hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    k<<<a.nchunks + (x.tiles ? 1 : 0), 1024, lds, s>>>(idx, a);
+}
+
+bool dispatch_makes_tiles(int E) { return E <= kDispMaxE; }
+
 hipError_t launch_permute(int T, int d, int E, int K, int elem_bytes, const void *x, const void *idx,
                           int idx_dtype, int64_t stride, int32_t *counts, int32_t *offsets,
-                          int32_t *inv_perm, int32_t *perm, void *Xp, int32_t *status, void *ws,
+                          int32_t *inv_perm, int32_t *perm, void *Xp, int32_t *status, void *ws, const DispatchExtra &extra,
                           hipStream_t s) {
-    const int64_t S = (int64_t)T * K;
-    const int chunk = pick_chunk(S);
-    const int nchunks = (int)((S + chunk - 1) / chunk);
-    int32_t *chunk_hist = (int32_t *)ws;
-    int32_t *chunk_base = (int32_t *)((char *)ws + align_up((size_t)nchunks * E * sizeof(int32_t), 256));
-    const int grid = (nchunks + 3) / 4;
-    const size_t lds = (size_t)4 * E * sizeof(int32_t);
-    {
-    ProfScope ps(PROF_PERMUTE_INDEX, s);
-    if (idx_dtype == R3_IDX_U8)
-        permute_hist_kernel<uint8_t><<<grid, 256, lds, s>>>(T, E, K, (const uint8_t *)idx, stride, chunk,
-                                                           nchunks, chunk_hist, status);
-    else
-        permute_hist_kernel<uint16_t><<<grid, 256, lds, s>>>(T, E, K, (const uint16_t *)idx, stride,
-                                                            chunk, nchunks, chunk_hist, status);
-    permute_scan_kernel<<<1, 1024, 0, s>>>(E, nchunks, chunk_hist, chunk_base, counts, offsets);
-    if (idx_dtype == R3_IDX_U8)
-        permute_place_kernel<uint8_t><<<grid, 256, lds, s>>>(T, E, K, (const uint8_t *)idx, stride, chunk,
-                                                            nchunks, chunk_base, offsets, inv_perm, perm);
-    else
-        permute_place_kernel<uint16_t><<<grid, 256, lds, s>>>(T, E, K, (const uint16_t *)idx, stride,
-                                                             chunk, nchunks, chunk_base, offsets,
-                                                             inv_perm, perm);
+    if (E <= kDispMaxE) {
+        ProfScope ps(PROF_PERMUTE_INDEX, s);
+        if (idx_dtype == R3_IDX_U8)
+            launch_dispatch(T, E, K, (const uint8_t *)idx, stride, counts, offsets, inv_perm, perm, status, ws, extra, s);
+        else
+            launch_dispatch(T, E, K, (const uint16_t *)idx, stride, counts, offsets, inv_perm, perm, status, ws, extra, s);
+    } else {
+        const int64_t S = (int64_t)T * K;
+        const int chunk = pick_chunk(S);
+        const int nchunks = (int)((S + chunk - 1) / chunk);
+        int32_t *chunk_hist = (int32_t *)ws;
+        int32_t *chunk_base = (int32_t *)((char *)ws + align_up((size_t)nchunks * E * sizeof(int32_t), 256));
+        const int grid = (nchunks + 3) / 4;
+        const size_t lds = (size_t)4 * E * sizeof(int32_t);
+        const uint16_t *id = (const uint16_t *)idx;   // (more than 256 experts)
+        ProfScope ps(PROF_PERMUTE_INDEX, s);
+        permute_hist_kernel<<<grid, 256, lds, s>>>(T, E, K, id, stride, chunk, nchunks, chunk_hist, status);
+        permute_scan_kernel<<<1, 1024, 0, s>>>(E, nchunks, chunk_hist, chunk_base, counts, offsets);
+        permute_place_kernel<<<grid, 256, lds, s>>>(T, E, K, id, stride, chunk, nchunks, chunk_base, offsets, inv_perm, perm);
     }
     if (Xp) {
         ProfScope ps(PROF_GATHER_ROWS, s);

@@ -48,3 +48,35 @@ def test_router_at_tile_edges(sh):
     torch.cuda.synchronize()
     assert torch.equal(gates, gates2)
     assert tuple(agree.tolist()) == tuple(2 * int(v) for v in sparse.agreement(own, c.idx))
+
+
+def _slots(T, E, K, seed, skew):
+    rng = np.random.default_rng(seed)
+    p = rng.random((T, E)) - skew * np.log(np.arange(1, E + 1))
+    return np.sort(np.argsort(-p, axis=1)[:, :K], axis=1).astype(np.int32)
+
+
+@pytest.mark.parametrize("T,E,K,skew,token_major", [
+    (1, 1, 1, 0.0, False), (16384, 8, 1, 0.0, False),           # one slot; the most one launch counts by itself
+    (5462, 100, 3, 0.3, True), (2731, 256, 6, 0.0, False),      # the first sizes counted by chunk; ids that fit no vector
+    (2049, 128, 8, 0.5, True), (129, 1024, 64, 0.0, False),     # a slot over a chunk; the most experts of these kernels
+    (300, 1025, 4, 0.0, False),                                 # beyond them
+    (70000, 16, 16, 0.0, False), (131072, 128, 8, 0.3, False),  # several steps per wave
+])
+def test_dispatch_at_chunk_edges(T, E, K, skew, token_major):
+    idx = _slots(T, E, K, T + E, skew)
+    counts, offsets, inv_perm, perm = sparse.permute(idx, E)
+    L = 3 if token_major else 1
+    D = r3.desc(T, 16, E, K, 16, idx_token_stride=L * K if token_major else 0)
+    rec = np.zeros((T, L, K), np.uint8 if E <= 256 else np.uint16)
+    rec[:, L // 2] = idx
+    rec = torch.from_numpy(rec.view(np.int16) if E > 256 else rec).to("cuda")
+    if E > 256:
+        rec = rec.view(torch.uint16)
+    out = [torch.full((n,), -1, dtype=torch.int32, device="cuda") for n in (E, E + 1, T * K, T * K)]
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    r3.permute(D, None, rec[:, L // 2], *out, None, r3.workspace(D, r3.OP_PERMUTE), status)
+    torch.cuda.synchronize()
+    assert int(status.item()) == 0
+    for got, want in zip(out, (counts, offsets, inv_perm, perm)):
+        assert np.array_equal(got.cpu().numpy(), want)

@@ -42,7 +42,7 @@ bool use_mfma_ffn(const Dims &m) { return m.act == R3_BF16 && mfma_ffn_supported
 bool use_mfma_router(const Dims &m) { return m.act == R3_BF16 && mfma_router_supported(m.d, m.E) && !force_simt(); }
 
 struct BwdWs {
-    size_t dXp, dz, ds, WrT, dA, dB, tiles, part, tok, Hg, grow, wpart, total;
+    size_t dXp, dz, WrT, dA, dB, tiles, part, tok, Hg, grow, wpart, total;
 };
 int row_parts(const Dims &m) { return 2 * ((m.F + 255) / 256); }   // partial dot products per row (MFMA path)
 BwdWs bwd_layout(const Dims &m) {
@@ -52,12 +52,11 @@ BwdWs bwd_layout(const Dims &m) {
     const bool mf = use_mfma_ffn(m);
     w.dXp = take((size_t)m.S * m.d * m.eb);  // the plain kernels keep g*dy here first
     w.dz = take((size_t)m.T * m.K * sizeof(float));
-    w.ds = take((size_t)m.T * m.E * (m.act == R3_BF16 ? 2 : 1) * m.eb);  // bf16: (hi, lo) halves
     w.WrT = take((size_t)m.E * m.d * m.eb);
     w.dA = take((size_t)m.S * m.F * m.eb);
     w.dB = take((size_t)m.S * m.F * m.eb);
     w.tiles = take(mf ? mfma_tiles_bytes(m.S, m.E) : 0);
-    w.part = take(use_mfma_router(m) ? mfma_dwr_ws_bytes(m.T, m.d, m.E) : plain_dwr_ws_bytes(m.T, m.d, m.E));
+    w.part = take(router_dwr_ws_bytes(m.act, m.T, m.d, m.E, m.K, force_simt()));
     w.tok = take(mf ? mfma_row_tokens_bytes(m.S) : 0);           // row -> token list
     w.Hg = take(mf ? (size_t)m.S * m.F * m.eb : 0);              // gate-scaled H rows
     w.grow = take(mf ? (size_t)m.S * sizeof(float) : 0);         // row -> gate list
@@ -329,10 +328,9 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
     if (!ws || ws_bytes < w.total || !aligned(ws, 256)) return R3_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     char *base = (char *)ws;
-    void *dXp = base + w.dXp, *ds = base + w.ds, *WrT = base + w.WrT, *dA = base + w.dA, *dB = base + w.dB;
+    void *dXp = base + w.dXp, *WrT = base + w.WrT, *dA = base + w.dA, *dB = base + w.dB;
     float *dz = (float *)(base + w.dz);
     const int S = (int)m.S;
-    hipError_t e;
 
     if (mf) {
         // experts first: the gradient GEMM of the down projection reads dy through the row -> token
@@ -350,8 +348,7 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
         if (mfma_ffn_dh(m.S, m.d, m.E, m.F, dy, tok, m.T, grow, offsets, tiles, W_down, FA, FB, H, dA, dB, Hg, wpart,
                         s) != hipSuccess)
             return R3_ERR_HIP;
-        if (launch_gate_backward_parts(m.T, m.E, m.K, row_parts(m), wpart, gates, inv_perm, idx, m.idx, m.stride, dz,
-                                       ds, s) != hipSuccess)
+        if (launch_gate_backward_parts(m.T, m.K, row_parts(m), wpart, gates, inv_perm, dz, s) != hipSuccess)
             return R3_ERR_HIP;
         if (mfma_wgrad(m.E, m.F, m.d, gated ? H : Hg, dy, tok, m.T, tiles, 2, dW_down, split ? (float *)dXp : nullptr,
                        accumulate, s) != hipSuccess)
@@ -362,10 +359,9 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
         if (mfma_ffn_dxp(m.S, m.d, m.E, m.F, dA, dB, offsets, tiles, W_gate, W_up, dXp, s) != hipSuccess)
             return R3_ERR_HIP;
     } else {
-        // combine and masked softmax:  dYp = g*dy per slot, dz, dense ds
+        // combine and masked softmax:  dYp = g*dy per slot, dz
         void *dYp = dXp;  // dYp is dead once dW_down and dH are done
-        if (launch_gate_backward(m.T, m.d, m.E, m.K, m.act, dy, Yp, gates, inv_perm, idx, m.idx, m.stride, dYp, dz,
-                                 ds, gated ? 1 : 0, s) != hipSuccess)
+        if (launch_gate_backward(m.T, m.d, m.K, m.act, dy, Yp, gates, inv_perm, dYp, dz, gated ? 1 : 0, s) != hipSuccess)
             return R3_ERR_HIP;
         if (plain_dh(S, m.d, m.E, m.F, m.act, dYp, offsets, W_down, FA, FB, dA, dB, s) != hipSuccess) return R3_ERR_HIP;
         // gated: H is g H already, so its partner is the plain dy row (read through perm), not g dy
@@ -374,11 +370,12 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
             return R3_ERR_HIP;
         if (plain_dxp(S, m.d, m.E, m.F, m.act, dA, dB, offsets, W_gate, W_up, dXp, s) != hipSuccess) return R3_ERR_HIP;
     }
-    // router:  dW_r = x^T ds, dbias = column sums
-    if (use_mfma_router(m)) e = mfma_dwr(m.T, m.d, m.E, x, ds, (float *)(base + w.part), dW_r, accumulate, s);
-    else e = plain_dwr(m.T, m.d, m.E, m.act, x, ds, (float *)(base + w.part), dW_r, accumulate, s);
-    if (e != hipSuccess) return R3_ERR_HIP;
-    if (dbias && launch_colsum(m.T, m.E, m.act, ds, dbias, accumulate, s) != hipSuccess) return R3_ERR_HIP;
+    // router:  dW_r = x^T ds, dbias = column sums of ds (ds: dz at the recorded experts)
+    if (router_dwr(m.T, m.d, m.E, m.K, m.act, x, dz, idx, m.idx, m.stride, (float *)(base + w.part), dW_r, accumulate,
+                   force_simt(), s) != hipSuccess)
+        return R3_ERR_HIP;
+    if (dbias && router_dbias(m.T, m.E, m.K, dz, idx, m.idx, m.stride, offsets, perm, dbias, accumulate, s) != hipSuccess)
+        return R3_ERR_HIP;
     if (launch_transpose(m.d, m.E, m.act, W_r, WrT, s) != hipSuccess) return R3_ERR_HIP;
     // dx = un-permuted expert gradients + router term
     return hip_rc(launch_dx_finish(m.T, m.d, m.E, m.K, m.act, dXp, WrT, dz, inv_perm, idx, m.idx, m.stride, dx,

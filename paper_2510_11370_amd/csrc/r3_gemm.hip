@@ -816,64 +816,6 @@ logits_kernel(int T, int d, int E, const bf16_t *__restrict__ x, const bf16_t *_
 }
 
 // ---------------------------------------------------------------------------
-// Router weight gradient, split over tokens.  ds arrives as [T, 2E] bf16 with
-// dz split into hi (columns 0..E) and lo (columns E..2E) halves:
-//   part[s][c][e'] = sum_{t in split s} x[t][c] * ds[t][e'],   e' in [0, 2E)
-// followed by a fixed-order sum over the splits and over (hi, lo).
-// (E below is the width of ds, i.e. twice the number of experts.)
-// A work-group takes 128 hidden columns and, with E = 128 experts, the whole width of ds, so x is
-// read once; 16 splits of the tokens fill the chip with d / 128 tiles each and leave 16 partial
-// matrices (with 128 x 128 tiles and a split per 512 tokens x was read twice and the partials, 67 MB
-// at 16384 tokens, moved more bytes than x itself).
-// ---------------------------------------------------------------------------
-template <class TL>
-__global__ void __launch_bounds__(TL::NT)
-dwr_partial_kernel(int T, int d, int E, int rows_per_split, const bf16_t *__restrict__ x,
-                   const bf16_t *__restrict__ ds, float *__restrict__ part) {
-    extern __shared__ __attribute__((aligned(16))) char lds[];
-    const int nqt = d / TL::BQ, npt = E / TL::BP;
-    const int id = blockIdx.x;
-    const int sp = id / (nqt * npt);
-    const int rem = id - sp * nqt * npt;
-    const int qt = rem / npt, pt = rem - qt * npt;
-    const int r0 = sp * rows_per_split, r1 = min(T, r0 + rows_per_split);
-    const int q0 = qt * TL::BQ, p0 = pt * TL::BP;
-    auto fp = [&](int kt, int k, int c) -> uint4 {
-        const int r = r0 + kt * TL::BK + k;
-        return r < r1 ? ld16(ds + (int64_t)r * E + p0 + c * 8) : zero16();
-    };
-    auto fq = [&](int kt, int k, int c) -> uint4 {
-        const int r = r0 + kt * TL::BK + k;
-        return r < r1 ? ld16(x + (int64_t)r * d + q0 + c * 8) : zero16();
-    };
-    f32x16_t acc[TL::TP][TL::TQ];
-    zero_acc<TL>(acc);
-    // bound by the stream of x: two k-tiles in flight per work-group
-    mfma_mainloop_ahead2<TL, true, true>(acc, (max(r1 - r0, 0) + TL::BK - 1) / TL::BK, fp, fq, lds);
-    float *o = part + (int64_t)sp * d * E;
-    for_each_quad<TL>([&](int tp, int tq, int g, int p, int q) {
-        *(float4 *)(o + (int64_t)(q0 + q) * E + p0 + p) =
-            make_float4(acc[tp][tq][4 * g], acc[tp][tq][4 * g + 1], acc[tp][tq][4 * g + 2],
-                        acc[tp][tq][4 * g + 3]);
-    });
-}
-
-// out[c][e] (+)= sum_s part[s][c][e] + part[s][c][E+e]
-__global__ void __launch_bounds__(256)
-split_reduce_kernel(int d, int E, int nsplit, const float *__restrict__ part, float *__restrict__ out,
-                    int accumulate) {
-    const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= (int64_t)d * E) return;
-    const int c = (int)(i / E), e = (int)(i - (int64_t)c * E);
-    float acc = accumulate ? out[i] : 0.0f;
-    for (int s = 0; s < nsplit; ++s) {
-        const float *row = part + ((int64_t)s * d + c) * 2 * E;
-        acc += row[e] + row[E + e];
-    }
-    out[i] = acc;
-}
-
-// ---------------------------------------------------------------------------
 // The partial products of split reductions into their gradients: for every split expert, in slot order
 // (a fixed order: the sum does not depend on the launch shape).  n4 = float4s per expert matrix; a
 // second gradient with slots of its own (out1, part1) is optional.
@@ -904,7 +846,6 @@ wgrad_parts_kernel(int64_t n4, const int32_t *__restrict__ tiles, float *__restr
 // host side
 // ---------------------------------------------------------------------------
 typedef TileCfg<128, 64, 2, 2, 64> TLLogits;   // router: 128 experts x 64 tokens
-typedef TileCfg<256, 128, 2, 2, 64> TLDwrW;    // router wgrad: 256 columns of ds (hi, lo) x 128 hidden
 
 // Rows come in 16-byte pieces (d, F multiples of 8).  Layers of very small matrices and few rows are left to the
 // f32 tiles (r3_plain.hip): a 256 x 256 tile of 40 x 40 features is nearly all padding and both paths are a chain of
@@ -917,7 +858,7 @@ bool mfma_ffn_supported(int64_t S, int d, int F) {
     return !(w <= (1 << 15) && S * w <= (1 << 25));
 }
 bool mfma_ffn_ragged(int d, int F) { return d % kTile != 0 || F % kTile != 0; }
-bool mfma_router_supported(int d, int E) { return E % 128 == 0 && d % 128 == 0; }  // 2E % 128 for ds
+bool mfma_router_supported(int d, int E) { return E % 128 == 0 && d % 128 == 0; }
 
 size_t mfma_tiles_bytes(int64_t S, int E) {
     return align_up((size_t)(kTileHdr + 2 * (size_t)max_row_tiles(S, E, kTile)) * sizeof(int32_t), 256);
@@ -1058,29 +999,6 @@ hipError_t mfma_router_logits(int T, int d, int E, const void *x, const void *Wr
     ProfScope ps(PROF_LOGITS, s);
     logits_kernel<TL><<<tiles, TL::NT, TL::LDS_BYTES, s>>>(T, d, E, (const bf16_t *)x, (const bf16_t *)Wr, bias,
                                                          logits);
-    return hipGetLastError();
-}
-
-static int dwr_splits(int T) {
-    int s = (T + 511) / 512;
-    return s < 1 ? 1 : (s > 16 ? 16 : s);
-}
-size_t mfma_dwr_ws_bytes(int T, int d, int E) {
-    return align_up((size_t)dwr_splits(T) * d * 2 * E * sizeof(float), 256);
-}
-
-hipError_t mfma_dwr(int T, int d, int E, const void *x, const void *ds, float *part, float *dWr, int accumulate,
-                    hipStream_t s) {
-    const int ns = dwr_splits(T);
-    typedef TLDwrW TL;
-    int rows = (T + ns - 1) / ns;
-    rows = (rows + TL::BK - 1) / TL::BK * TL::BK;
-    allow_lds(dwr_partial_kernel<TL>, TL::LDS_BYTES);
-    ProfScope ps(PROF_DWR, s);
-    dwr_partial_kernel<TL><<<ns * (d / TL::BQ) * (2 * E / TL::BP), TL::NT, TL::LDS_BYTES, s>>>(
-        T, d, 2 * E, rows, (const bf16_t *)x, (const bf16_t *)ds, part);
-    const int64_t n = (int64_t)d * E;
-    split_reduce_kernel<<<(int)((n + 255) / 256), 256, 0, s>>>(d, E, ns, part, dWr, accumulate);
     return hipGetLastError();
 }
 

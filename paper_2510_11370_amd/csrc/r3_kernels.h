@@ -42,21 +42,16 @@ hipError_t launch_permute(int T, int d, int E, int K, int elem_bytes, const void
 hipError_t launch_combine(int T, int d, int K, int act, const void *Yp, const float *gates,
                           const int32_t *inv_perm, void *y, hipStream_t s);
 // gated != 0: Yp holds gate-scaled rows (g o), so <dy, Yp_j> is already g_j dg_j
-hipError_t launch_gate_backward(int T, int d, int E, int K, int act, const void *dy, const void *Yp,
-                                const float *gates, const int32_t *inv_perm, const void *idx,
-                                int idx_dtype, int64_t stride, void *dYp, float *dz, void *ds_dense,
-                                int gated, hipStream_t s);
+hipError_t launch_gate_backward(int T, int d, int K, int act, const void *dy, const void *Yp, const float *gates,
+                                const int32_t *inv_perm, void *dYp, float *dz, int gated, hipStream_t s);
 // masked-softmax backward from the row parts written by the expert-gradient GEMM:
-// w_j = sum_p wpart[row_j][p] (= g_j dg_j), dz_j = w_j - g_j sum_i w_i; writes dz [T,K] and the dense
-// bf16 ds [T,2E] (hi | lo halves)
-hipError_t launch_gate_backward_parts(int T, int E, int K, int nparts, const float *wpart, const float *gates,
-                                      const int32_t *inv_perm, const void *idx, int idx_dtype, int64_t stride,
-                                      float *dz, void *ds_dense, hipStream_t s);
+// w_j = sum_p wpart[row_j][p] (= g_j dg_j), dz_j = w_j - g_j sum_i w_i; writes dz [T,K]
+hipError_t launch_gate_backward_parts(int T, int K, int nparts, const float *wpart, const float *gates,
+                                      const int32_t *inv_perm, float *dz, hipStream_t s);
 hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp, const void *WrT,
                             const float *dz, const int32_t *inv_perm, const void *idx, int idx_dtype,
                             int64_t stride, void *dx, hipStream_t s);
 hipError_t launch_transpose(int R, int C, int act, const void *in, void *out, hipStream_t s);
-hipError_t launch_colsum(int T, int E, int act, const void *ds, float *out, int accumulate, hipStream_t s);
 
 // r3_diag.hip
 size_t policy_ws_bytes();
@@ -95,9 +90,9 @@ hipError_t plain_dxp(int S, int d, int E, int F, int act, const void *dA, const 
 hipError_t plain_wgrads(int d, int E, int F, int K, int act, const int32_t *offsets, const void *H, const void *dYrows,
                         const int32_t *dyperm, const void *xrows, const int32_t *xperm, const void *dA, const void *dB,
                         float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s);
-size_t plain_dwr_ws_bytes(int T, int d, int E);   // partial products of plain_dwr
-hipError_t plain_dwr(int T, int d, int E, int act, const void *x, const void *ds, float *part, float *dWr, int accumulate,
-                     hipStream_t s);
+int plain_dwr_rows(int T, int d, int E);          // tokens per part
+void plain_dwr_parts(int T, int d, int E, int K, int act, const void *x, const float *dz, const void *idx, int idx_dtype,
+                     int64_t stride, float *part, hipStream_t s);
 
 // r3_router.hip: logits + replay gate (+ agreement counts, K <= 8) in one launch.  plain_only: f32 arithmetic
 bool router_gate_supported(int act, int d, int E, bool plain_only);
@@ -105,12 +100,19 @@ hipError_t router_gate(int T, int d, int E, int K, int act, const void *x, const
                        int idx_dtype, int64_t stride, float *gates, float *logits_out, int64_t *agree, int32_t *status,
                        bool plain_only, hipStream_t s);
 
+// Router weight gradient dW_r (+)= x^T ds, ds[t][idx[t][j]] = dz[t][j]; part: router_dwr_ws_bytes() bytes.  dbias (+)=
+// column sums of ds (offsets and perm as r3_permute makes them; perm may be NULL)
+size_t router_dwr_ws_bytes(int act, int T, int d, int E, int K, bool plain_only);
+hipError_t router_dwr(int T, int d, int E, int K, int act, const void *x, const float *dz, const void *idx, int idx_dtype,
+                      int64_t stride, float *part, float *dWr, int accumulate, bool plain_only, hipStream_t s);
+hipError_t router_dbias(int T, int E, int K, const float *dz, const void *idx, int idx_dtype, int64_t stride,
+                        const int32_t *offsets, const int32_t *perm, float *dbias, int accumulate, hipStream_t s);
+
 // r3_gemm.hip (bf16 MFMA)
 bool mfma_ffn_supported(int64_t S, int d, int F);
 bool mfma_ffn_ragged(int d, int F);      // widths that are not whole tiles of 256
 bool mfma_router_supported(int d, int E);
 size_t mfma_tiles_bytes(int64_t S, int E);
-size_t mfma_dwr_ws_bytes(int T, int d, int E);
 // split_rows > 0: experts with more rows than that are cut into parts of at most that many rows for the
 // weight gradients (mfma_wgrad_split_rows picks it); 0: never; < 0: the pass has no
 // weight gradients and the table gets no reduction segments at all
@@ -155,7 +157,5 @@ hipError_t mfma_wgrad_pair(int E, int NQd, int NPd, const void *Qs, const int32_
 size_t mfma_row_tokens_bytes(int64_t S);
 hipError_t mfma_router_logits(int T, int d, int E, const void *x, const void *Wr, const float *bias,
                               float *logits, hipStream_t s);
-hipError_t mfma_dwr(int T, int d, int E, const void *x, const void *ds, float *part, float *dWr, int accumulate,
-                    hipStream_t s);
 
 }  // namespace r3

@@ -390,7 +390,7 @@ plain_wgrad_kernel(int E, int K, const int32_t *__restrict__ offsets, PlainWgrad
 
 // ---------------------------------------------------------------------------
 // Router: logits s[t][e] = sum_c x[t][c] W_r[c][e] (+ bias), and the parts of dW_r[c][e] = sum_t x[t][c] ds[t][e]
-// over `rows` tokens each (bf16 activations: ds rows are [hi(E) | lo(E)], widened and added).
+// over `rows` tokens each, ds[t][idx[t][j]] = dz[t][j] looked up as the tile is loaded.
 // ---------------------------------------------------------------------------
 template <class C, typename T, bool VECX, bool VECE>
 __global__ void __launch_bounds__(C::NT)
@@ -413,26 +413,26 @@ plain_logits_kernel(int Tn, int d, int E, const T *__restrict__ x, const T *__re
     });
 }
 
-template <class C, typename T, bool VECX, bool VECE>
+template <class C, typename T, bool VECX, typename IdxT>
 __global__ void __launch_bounds__(C::NT)
-plain_dwr_kernel(int Tn, int d, int E, int rows, const T *__restrict__ x, const T *__restrict__ ds,
-                 float *__restrict__ part) {
+plain_dwr_kernel(int Tn, int d, int E, int K, int rows, const T *__restrict__ x, const float *__restrict__ dz,
+                 const IdxT *__restrict__ idx, int64_t stride, float *__restrict__ part) {
     extern __shared__ __attribute__((aligned(16))) char lds[];
     const int npt = (E + C::BP - 1) / C::BP, nqt = (d + C::BQ - 1) / C::BQ;
     const int sp = blockIdx.x / (npt * nqt), rem = blockIdx.x - sp * npt * nqt;
     const int qt = rem / npt, q0 = qt * C::BQ, p0 = (rem - qt * npt) * C::BP;
     const int t0 = sp * rows, n = min(rows, Tn - t0);
-    constexpr bool HILO = sizeof(T) == 2;
-    const int dsw = HILO ? 2 * E : E;
     auto fp = [&](int, int k, int c) {
-        const T *p = ds + (int64_t)(t0 + min(k, n - 1)) * dsw + p0 + c;
-        const int m = k < n ? E - p0 - c : 0;
-        float4 v = load4<T, VECE>(p, m);
-        if constexpr (HILO) {
-            const float4 lo = load4<T, VECE>(p + E, m);
-            v.x += lo.x; v.y += lo.y; v.z += lo.z; v.w += lo.w;
-        }
-        return v;
+        float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if (k < n)
+            for (int j = 0; j < K; ++j) {
+                const int e = min((int)idx[(int64_t)(t0 + k) * stride + j], E - 1) - p0 - c;
+                const float z = dz[(int64_t)(t0 + k) * K + j];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (e == i) v[i] = z;
+            }
+        return make_float4(v[0], v[1], v[2], v[3]);
     };
     auto fq = [&](int, int k, int c) { return load4<T, VECX>(x + (int64_t)(t0 + min(k, n - 1)) * d + q0 + c, k < n ? d - q0 - c : 0); };
     PlainAcc<C> acc;
@@ -442,18 +442,8 @@ plain_dwr_kernel(int Tn, int d, int E, int rows, const T *__restrict__ x, const 
     plain_results<C>([&](int tp, int tq, int p, int q) {
         if (q0 + q >= d || p0 + p >= E) return;
         float v[4] = {acc[tp][tq][0], acc[tp][tq][1], acc[tp][tq][2], acc[tp][tq][3]};
-        store4<float, VECE>(o + (int64_t)(q0 + q) * E + p0 + p, v, E - p0 - p);
+        store4<float, false>(o + (int64_t)(q0 + q) * E + p0 + p, v, E - p0 - p);
     });
-}
-
-// out[i] (+)= sum_s part[s][i], s ascending
-__global__ void __launch_bounds__(256)
-plain_sum_parts_kernel(int64_t n, int nsplit, const float *__restrict__ part, float *__restrict__ out, int accumulate) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float acc = accumulate ? out[i] : 0.0f;
-    for (int s = 0; s < nsplit; ++s) acc += part[(int64_t)s * n + i];
-    out[i] = acc;
 }
 
 // ---------------------------------------------------------------------------
@@ -531,32 +521,15 @@ hipError_t wgrads_any(int d, int E, int F, int K, const int32_t *offsets, const 
     return hipGetLastError();
 }
 
-// tokens per part of dW_r: enough parts to give every compute unit a tile, at least 64 tokens each
-int dwr_rows(int T, int d, int E) {
-    const int64_t tiles = ceil_div(d, 64) * ceil_div(E, 64);
-    const int64_t ns = std::max<int64_t>(1, std::min<int64_t>(ceil_div(T, 64), ceil_div(256, tiles)));
-    return (int)(ceil_div(ceil_div(T, ns), 32) * 32);
-}
-
-template <typename T>
-hipError_t dwr_any(int Tn, int d, int E, const T *x, const T *ds, float *part, float *dWr, int accumulate, hipStream_t s) {
+template <typename T, typename IdxT>
+void dwr_any(int Tn, int d, int E, int K, const T *x, const float *dz, const IdxT *idx, int64_t stride, float *part,
+             hipStream_t s) {
     typedef PlainSmall C;
-    const int rows = dwr_rows(Tn, d, E), ns = (int)ceil_div(Tn, rows);
-    const unsigned grid = (unsigned)(ns * ceil_div(d, C::BQ) * ceil_div(E, C::BP));
-    const bool vx = d % 4 == 0, ve = E % 4 == 0;
-#define R3_DWR(VX, VE)                                                                              \
-    do {                                                                                            \
-        allow_lds(plain_dwr_kernel<C, T, VX, VE>, C::LDS);                                          \
-        plain_dwr_kernel<C, T, VX, VE><<<grid, C::NT, C::LDS, s>>>(Tn, d, E, rows, x, ds, part);    \
-    } while (0)
-    if (vx && ve) R3_DWR(true, true);
-    else if (vx) R3_DWR(true, false);
-    else if (ve) R3_DWR(false, true);
-    else R3_DWR(false, false);
-#undef R3_DWR
-    const int64_t n = (int64_t)d * E;
-    plain_sum_parts_kernel<<<(unsigned)ceil_div(n, 256), 256, 0, s>>>(n, ns, part, dWr, accumulate);
-    return hipGetLastError();
+    const int rows = plain_dwr_rows(Tn, d, E);
+    const unsigned grid = (unsigned)(ceil_div(Tn, rows) * ceil_div(d, C::BQ) * ceil_div(E, C::BP));
+    auto k = d % 4 == 0 ? plain_dwr_kernel<C, T, true, IdxT> : plain_dwr_kernel<C, T, false, IdxT>;
+    allow_lds(k, C::LDS);
+    k<<<grid, C::NT, C::LDS, s>>>(Tn, d, E, K, rows, x, dz, idx, stride, part);
 }
 
 template <typename T>
@@ -626,15 +599,22 @@ hipError_t plain_wgrads(int d, int E, int F, int K, int act, const int32_t *offs
                                    xperm, (const float *)dA, (const float *)dB, dWg, dWu, dWd, accumulate, s);
 }
 
-size_t plain_dwr_ws_bytes(int T, int d, int E) {
-    return align_up((size_t)ceil_div(T, dwr_rows(T, d, E)) * d * E * sizeof(float), 256);
+// tokens per part of dW_r: enough parts to give every compute unit a tile, at least 64 tokens each
+int plain_dwr_rows(int T, int d, int E) {
+    const int64_t tiles = ceil_div(d, 64) * ceil_div(E, 64);
+    const int64_t ns = std::max<int64_t>(1, std::min<int64_t>(ceil_div(T, 64), ceil_div(256, tiles)));
+    return (int)(ceil_div(ceil_div(T, ns), 32) * 32);
 }
 
-hipError_t plain_dwr(int T, int d, int E, int act, const void *x, const void *ds, float *part, float *dWr, int accumulate,
-                     hipStream_t s) {
-    ProfScope ps(PROF_DWR, s);
-    return act == R3_BF16 ? dwr_any(T, d, E, (const bf16_t *)x, (const bf16_t *)ds, part, dWr, accumulate, s)
-                          : dwr_any(T, d, E, (const float *)x, (const float *)ds, part, dWr, accumulate, s);
+void plain_dwr_parts(int T, int d, int E, int K, int act, const void *x, const float *dz, const void *idx, int idx_dtype,
+                     int64_t stride, float *part, hipStream_t s) {
+    if (idx_dtype == R3_IDX_U8) {
+        if (act == R3_BF16) dwr_any(T, d, E, K, (const bf16_t *)x, dz, (const uint8_t *)idx, stride, part, s);
+        else dwr_any(T, d, E, K, (const float *)x, dz, (const uint8_t *)idx, stride, part, s);
+    } else {
+        if (act == R3_BF16) dwr_any(T, d, E, K, (const bf16_t *)x, dz, (const uint16_t *)idx, stride, part, s);
+        else dwr_any(T, d, E, K, (const float *)x, dz, (const uint16_t *)idx, stride, part, s);
+    }
 }
 
 }  // namespace r3

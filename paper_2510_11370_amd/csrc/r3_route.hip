@@ -14,107 +14,6 @@ namespace r3 {
 // ---------------------------------------------------------------------------
 // TopKMask
 // ---------------------------------------------------------------------------
-// Fast record: 8 lanes per token (8 tokens per wave), K <= 8, E <= 512.
-// Lane `sub` of a token owns the contiguous id range [sub*EPL, (sub+1)*EPL) and keeps its 8
-// largest keys in a sorted register list; three butterfly rounds of bitonic merges leave every
-// lane with the token's 8 largest keys.  The K-th of them is the threshold: keys above it are
-// taken, keys equal to it are taken lowest id first until K are out (prefix counts over the
-// 8 lanes give each lane its quota and its output position, so ids come out ascending).
-template <typename IdxT>
-__global__ void __launch_bounds__(256)
-record_topk_sub8_kernel(int T, int E, int K, int EPL, const float *__restrict__ logits, int64_t ld,
-                        IdxT *__restrict__ idx, int64_t stride, int32_t *status) {
-    const int t = blockIdx.x * 32 + (int)(threadIdx.x >> 3);
-    const int sub = threadIdx.x & 7;
-    const bool live = t < T;
-    const float *row = logits + (int64_t)(live ? t : 0) * ld;
-    const int e0 = sub * EPL;
-    uint32_t top[8];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) top[j] = 0u;
-    bool bad = false;
-    for (int i = 0; i < EPL; ++i) {
-        const int e = e0 + i;
-        uint32_t v = 0u;
-        if (live && e < E) {
-            bool nf;
-            v = order_key(row[e], nf);
-            bad |= nf;
-        }
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const uint32_t hi = max(top[j], v);
-            v = min(top[j], v);
-            top[j] = hi;
-        }
-    }
-    // butterfly merge over the token's 8 lanes: max(mine[i], partner[7-i]) is the top 8 of the
-    // union as a bitonic sequence; three compare-exchange stages sort it again
-#pragma unroll
-    for (int m = 1; m < 8; m <<= 1) {
-        uint32_t other[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) other[j] = __shfl_xor(top[j], m, 8);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) top[j] = max(top[j], other[7 - j]);
-        cmpx_desc(top[0], top[4]); cmpx_desc(top[1], top[5]); cmpx_desc(top[2], top[6]); cmpx_desc(top[3], top[7]);
-        cmpx_desc(top[0], top[2]); cmpx_desc(top[1], top[3]); cmpx_desc(top[4], top[6]); cmpx_desc(top[5], top[7]);
-        cmpx_desc(top[0], top[1]); cmpx_desc(top[2], top[3]); cmpx_desc(top[4], top[5]); cmpx_desc(top[6], top[7]);
-    }
-    uint32_t thr = 0u;
-    int above = 0;
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (j == K - 1) thr = top[j];
-#pragma unroll
-    for (int j = 0; j < 8; ++j)
-        if (j < K && top[j] > thr) ++above;
-    // second pass over the lane's own ids
-    int n_gt = 0, n_eq = 0;
-    for (int i = 0; i < EPL; ++i) {
-        const int e = e0 + i;
-        if (live && e < E) {
-            bool nf;
-            const uint32_t v = order_key(row[e], nf);
-            n_gt += v > thr;
-            n_eq += v == thr;
-        }
-    }
-    // exclusive prefix over the 8 lanes (ids ascend with the lane)
-    int eq_before = n_eq, gt_before = n_gt;
-#pragma unroll
-    for (int o = 1; o < 8; o <<= 1) {
-        const int a = __shfl_up(eq_before, o, 8), b = __shfl_up(gt_before, o, 8);
-        if (sub >= o) {
-            eq_before += a;
-            gt_before += b;
-        }
-    }
-    eq_before -= n_eq;
-    gt_before -= n_gt;
-    const int quota = K - above;                                   // equal keys taken in all
-    const int eq_taken_before = min(eq_before, quota);
-    int my_quota = max(0, min(n_eq, quota - eq_before));           // equal keys this lane takes
-    int pos = gt_before + eq_taken_before;
-    if (live) {
-        IdxT *out = idx + (int64_t)t * stride;
-        for (int i = 0; i < EPL; ++i) {
-            const int e = e0 + i;
-            if (e < E) {
-                bool nf;
-                const uint32_t v = order_key(row[e], nf);
-                bool take = v > thr;
-                if (v == thr && my_quota > 0) {
-                    take = true;
-                    --my_quota;
-                }
-                if (take) out[pos++] = (IdxT)e;
-            }
-        }
-        if (bad && status) atomicOr(status, R3_DATA_NONFINITE);
-    }
-}
-
 // General record: one wave per token, rank counting, E <= 4096, K <= 64.
 // key of element e beats key of element f if larger, or equal with lower id.
 template <typename IdxT>
@@ -157,30 +56,44 @@ record_topk_wave_kernel(int T, int E, int K, const float *__restrict__ logits, i
     if (__ballot(bad) && lane == 0 && status) atomicOr(status, R3_DATA_NONFINITE);
 }
 
-// The same selection for E = 32 NV with vector loads and one pass over the row: the 8 lanes of a
-// token read consecutive float4 pieces (lane `sub` holds ids 32 i + 4 sub + c, i < NV, c < 4: one
-// 128-byte segment per token per load instruction), keep the keys in registers, and after the
-// merges express "above the threshold" and "equal to it" as E-bit masks, OR-ed over the 8 lanes.
-// The recorded set is the first mask plus the lowest-id bits of the second up to K; lane `sub`
-// writes its sub-th set bit, so the K ids land ascending in one 8-byte segment.
-template <typename IdxT, int NV>
+// K <= 8, E <= 32 NV <= 512: 8 lanes per token (8 tokens per wave), one pass over the row.  Lane `sub` of a token holds the
+// keys of ids 32 i + 4 sub + c (i < NV, c < 4: one 128-byte segment per token per load instruction), and after the
+// merges the ids above the threshold and equal to it are E-bit masks, OR-ed over the 8 lanes (topk_mask8).
+// Lane `sub` writes the sub-th set bit, so the K ids land ascending in one segment.  VEC: rows are whole 16-byte
+// pieces.  Bound by the read of the logits; with one id at a time per lane and three passes over the row
+// E=384 took 37 us at 6000 tokens, 9.8 now.
+template <typename IdxT, int NV, bool VEC>
 __global__ void __launch_bounds__(256)
-record_topk_vec_kernel(int T, int K, const float *__restrict__ logits, int64_t ld, IdxT *__restrict__ idx,
+record_topk_vec_kernel(int T, int E, int K, const float *__restrict__ logits, int64_t ld, IdxT *__restrict__ idx,
                        int64_t stride, int32_t *status) {
     const int t = blockIdx.x * 32 + (int)(threadIdx.x >> 3);
     const int sub = threadIdx.x & 7;
     const bool live = t < T;
-    const float4 *row = (const float4 *)(logits + (int64_t)(live ? t : 0) * ld);
+    const float *row = logits + (int64_t)(live ? t : 0) * ld;
     uint32_t key[NV][4];
     bool bad = false;
 #pragma unroll
     for (int i = 0; i < NV; ++i) {
-        const float4 v = row[i * 8 + sub];
-        bool nf;
-        key[i][0] = order_key(v.x, nf); bad |= nf;
-        key[i][1] = order_key(v.y, nf); bad |= nf;
-        key[i][2] = order_key(v.z, nf); bad |= nf;
-        key[i][3] = order_key(v.w, nf); bad |= nf;
+        const int e = 32 * i + 4 * sub;
+        float v[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+        if constexpr (VEC) {
+            if (e < E) {
+                const float4 q = *(const float4 *)(row + e);
+                v[0] = q.x; v[1] = q.y; v[2] = q.z; v[3] = q.w;
+            }
+        } else {
+#pragma unroll
+            for (int c = 0; c < 4; ++c)
+                if (e + c < E) v[c] = row[e + c];
+        }
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            bool nf;
+            const uint32_t k = order_key(v[c], nf);
+            // (ids that do not exist rank with the NaNs, behind every real one of that rank)
+            key[i][c] = e + c < E ? k : 0u;
+            bad |= nf;
+        }
     }
     uint32_t gt[NV];
     topk_mask8<NV>(key, K, sub, gt);
@@ -208,14 +121,14 @@ record_topk_vec_kernel(int T, int K, const float *__restrict__ logits, int64_t l
 template <typename IdxT>
 static bool launch_record_vec(int T, int E, int K, const float *logits, int64_t ld, IdxT *idx, int64_t stride,
                               int32_t *status, hipStream_t s) {
-    if (K > 8 || E % 32 != 0 || ld % 4 != 0 || ((uintptr_t)logits & 15)) return false;
-    const int grid = (T + 31) / 32;
-    switch (E / 32) {
-        case 2: record_topk_vec_kernel<IdxT, 2><<<grid, 256, 0, s>>>(T, K, logits, ld, idx, stride, status); return true;
-        case 4: record_topk_vec_kernel<IdxT, 4><<<grid, 256, 0, s>>>(T, K, logits, ld, idx, stride, status); return true;
-        case 8: record_topk_vec_kernel<IdxT, 8><<<grid, 256, 0, s>>>(T, K, logits, ld, idx, stride, status); return true;
-        default: return false;
-    }
+    if (K > 8 || E > 512) return false;
+    const bool vec = E % 4 == 0 && ld % 4 == 0 && ((uintptr_t)logits & 15) == 0;
+#define R3_RECORD(NV) (vec ? record_topk_vec_kernel<IdxT, NV, true> : record_topk_vec_kernel<IdxT, NV, false>)
+    auto k = E <= 32 ? R3_RECORD(1) : E <= 64 ? R3_RECORD(2) : E <= 128 ? R3_RECORD(4) : E <= 256 ? R3_RECORD(8)
+             : E <= 384 ? R3_RECORD(12) : R3_RECORD(16);
+#undef R3_RECORD
+    k<<<(T + 31) / 32, 256, 0, s>>>(T, E, K, logits, ld, idx, stride, status);
+    return true;
 }
 
 hipError_t launch_record_topk(int T, int E, int K, const float *logits, int64_t ld, void *idx,
@@ -224,16 +137,7 @@ hipError_t launch_record_topk(int T, int E, int K, const float *logits, int64_t 
     if (idx_dtype == R3_IDX_U8 ? launch_record_vec(T, E, K, logits, ld, (uint8_t *)idx, stride, status, s)
                                : launch_record_vec(T, E, K, logits, ld, (uint16_t *)idx, stride, status, s))
         return hipGetLastError();
-    if (K <= 8 && E <= 512) {
-        const int EPL = (E + 7) / 8;
-        const int grid = (T + 31) / 32;
-        if (idx_dtype == R3_IDX_U8)
-            record_topk_sub8_kernel<uint8_t><<<grid, 256, 0, s>>>(T, E, K, EPL, logits, ld, (uint8_t *)idx, stride,
-                                                                 status);
-        else
-            record_topk_sub8_kernel<uint16_t><<<grid, 256, 0, s>>>(T, E, K, EPL, logits, ld, (uint16_t *)idx,
-                                                                  stride, status);
-    } else {
+    {
         size_t lds = (size_t)4 * E * sizeof(uint32_t);
         int grid = (T + 3) / 4;
         if (idx_dtype == R3_IDX_U8)
@@ -1014,17 +918,14 @@ hipError_t launch_combine(int T, int d, int K, int act, const void *Yp, const fl
 // Backward through combine and masked softmax, one block per token:
 //   dg_j = <dy_t, Yp[row_j]>,  dYp[row_j] = g_j * dy_t,
 //   dz_j = g_j (dg_j - sum_i g_i dg_i).
-// Writes dz [T,K] f32 and, when ds_dense != NULL, the dense row ds[t,:] (zero off
-// the recorded set) that the router weight gradient contracts: [T,E] f32, or for
-// bf16 activations [T,2E] holding dz as hi and lo bf16 halves.
+// Writes dz [T,K] f32.
 // ---------------------------------------------------------------------------
-template <typename T, int VEC, typename IdxT, int KT>
+template <typename T, int VEC, int KT>
 __global__ void __launch_bounds__(256)
-gate_backward_kernel(int E, int Krt, int row_vecs, const typename VecIO<T, VEC>::V *__restrict__ dy,
+gate_backward_kernel(int Krt, int row_vecs, const typename VecIO<T, VEC>::V *__restrict__ dy,
                      const typename VecIO<T, VEC>::V *__restrict__ Yp, const float *__restrict__ gates,
-                     const int32_t *__restrict__ inv_perm, const IdxT *__restrict__ idx, int64_t stride,
-                     typename VecIO<T, VEC>::V *__restrict__ dYp, float *__restrict__ dz,
-                     T *__restrict__ ds_dense, int gated) {
+                     const int32_t *__restrict__ inv_perm, typename VecIO<T, VEC>::V *__restrict__ dYp,
+                     float *__restrict__ dz, int gated) {
     typedef VecIO<T, VEC> IO;
     const int K = KT > 0 ? KT : Krt;
     const int t = blockIdx.x;
@@ -1037,11 +938,6 @@ gate_backward_kernel(int E, int Krt, int row_vecs, const typename VecIO<T, VEC>:
         rows[threadIdx.x] = inv_perm[(int64_t)t * K + threadIdx.x];
         g[threadIdx.x] = gates[(int64_t)t * K + threadIdx.x];
     }
-    // bf16 activations: ds is stored as a (hi, lo) pair of bf16 rows [hi(E) | lo(E)] so that the
-    // router weight gradient sees dz to about 16 bits instead of 8
-    const int dsw = (sizeof(T) == 2) ? 2 * E : E;
-    if (ds_dense)
-        for (int e = threadIdx.x; e < dsw; e += blockDim.x) Elem<T>::st(ds_dense + (int64_t)t * dsw + e, 0.0f);
     __syncthreads();
     if constexpr (KT > 0) {
         // dy is read once per column chunk and the K rows of Yp are all in flight together; per
@@ -1105,117 +1001,58 @@ gate_backward_kernel(int E, int Krt, int row_vecs, const typename VecIO<T, VEC>:
         for (int j = 0; j < K; ++j) mix = gated ? mix + dgs[j] : fmaf(g[j], dgs[j], mix);
         float v = gated ? dgs[threadIdx.x] - g[threadIdx.x] * mix : g[threadIdx.x] * (dgs[threadIdx.x] - mix);
         dz[(int64_t)t * K + threadIdx.x] = v;
-        if (ds_dense) {
-            int e = min((int)idx[(int64_t)t * stride + threadIdx.x], E - 1);
-            T *row = ds_dense + (int64_t)t * dsw;
-            Elem<T>::st(row + e, v);
-            if (sizeof(T) == 2) Elem<T>::st(row + E + e, v - Elem<T>::ld(row + e));
-        }
     }
 }
 
 template <typename T, int VEC>
-static hipError_t gate_backward_dispatch(int Tn, int E, int K, int row_vecs, const void *dy, const void *Yp,
-                                         const float *gates, const int32_t *inv_perm, const void *idx,
-                                         int idx_dtype, int64_t stride, void *dYp, float *dz,
-                                         void *ds_dense, int gated, hipStream_t s) {
+static hipError_t gate_backward_dispatch(int Tn, int K, int row_vecs, const void *dy, const void *Yp, const float *gates,
+                                         const int32_t *inv_perm, void *dYp, float *dz, int gated, hipStream_t s) {
     typedef typename VecIO<T, VEC>::V V;
-    if (idx_dtype == R3_IDX_U8 && K == 8 && VEC > 1)
-        gate_backward_kernel<T, VEC, uint8_t, 8><<<Tn, 256, 0, s>>>(E, K, row_vecs, (const V *)dy, (const V *)Yp,
-                                                                  gates, inv_perm, (const uint8_t *)idx,
-                                                                  stride, (V *)dYp, dz, (T *)ds_dense, gated);
-    else if (idx_dtype == R3_IDX_U8)
-        gate_backward_kernel<T, VEC, uint8_t, 0><<<Tn, 256, 0, s>>>(E, K, row_vecs, (const V *)dy, (const V *)Yp,
-                                                                  gates, inv_perm, (const uint8_t *)idx,
-                                                                  stride, (V *)dYp, dz, (T *)ds_dense, gated);
-    else
-        gate_backward_kernel<T, VEC, uint16_t, 0><<<Tn, 256, 0, s>>>(E, K, row_vecs, (const V *)dy,
-                                                                   (const V *)Yp, gates, inv_perm,
-                                                                   (const uint16_t *)idx, stride, (V *)dYp,
-                                                                   dz, (T *)ds_dense, gated);
+    auto k = K == 8 && VEC > 1 ? gate_backward_kernel<T, VEC, 8> : gate_backward_kernel<T, VEC, 0>;
+    k<<<Tn, 256, 0, s>>>(K, row_vecs, (const V *)dy, (const V *)Yp, gates, inv_perm, (V *)dYp, dz, gated);
     return hipGetLastError();
 }
 
-hipError_t launch_gate_backward(int T, int d, int E, int K, int act, const void *dy, const void *Yp,
-                                const float *gates, const int32_t *inv_perm, const void *idx,
-                                int idx_dtype, int64_t stride, void *dYp, float *dz, void *ds_dense,
-                                int gated, hipStream_t s) {
+hipError_t launch_gate_backward(int T, int d, int K, int act, const void *dy, const void *Yp, const float *gates,
+                                const int32_t *inv_perm, void *dYp, float *dz, int gated, hipStream_t s) {
     ProfScope ps(PROF_GATE_BWD, s);
-    if (act == R3_BF16) {
-        if (d % 8 == 0)
-            return gate_backward_dispatch<bf16_t, 8>(T, E, K, d / 8, dy, Yp, gates, inv_perm, idx, idx_dtype,
-                                                     stride, dYp, dz, ds_dense, gated, s);
-        return gate_backward_dispatch<bf16_t, 1>(T, E, K, d, dy, Yp, gates, inv_perm, idx, idx_dtype, stride,
-                                                 dYp, dz, ds_dense, gated, s);
-    }
-    if (d % 4 == 0)
-        return gate_backward_dispatch<float, 4>(T, E, K, d / 4, dy, Yp, gates, inv_perm, idx, idx_dtype,
-                                                stride, dYp, dz, ds_dense, gated, s);
-    return gate_backward_dispatch<float, 1>(T, E, K, d, dy, Yp, gates, inv_perm, idx, idx_dtype, stride, dYp,
-                                            dz, ds_dense, gated, s);
+    if (act == R3_BF16)
+        return d % 8 == 0 ? gate_backward_dispatch<bf16_t, 8>(T, K, d / 8, dy, Yp, gates, inv_perm, dYp, dz, gated, s)
+                          : gate_backward_dispatch<bf16_t, 1>(T, K, d, dy, Yp, gates, inv_perm, dYp, dz, gated, s);
+    return d % 4 == 0 ? gate_backward_dispatch<float, 4>(T, K, d / 4, dy, Yp, gates, inv_perm, dYp, dz, gated, s)
+                      : gate_backward_dispatch<float, 1>(T, K, d, dy, Yp, gates, inv_perm, dYp, dz, gated, s);
 }
 
 // ---------------------------------------------------------------------------
 // Masked-softmax backward when the expert-gradient GEMM has already formed the dot products: its
 // epilogue leaves, for every row r, `nparts` partial sums whose total is w = g <dy_t, o_r> = g dg.
 //   w_j = sum_p wpart[row_j][p] (p ascending),   dz_j = g_j (dg_j - sum_i g_i dg_i) = w_j - g_j sum_i w_i
-// One thread per slot, a token's K slots in neighbouring lanes; a block owns 256 / KP tokens (KP = K
-// rounded up to a power of two) and writes their dense ds rows [hi(E) | lo(E)] (bf16): zeros first,
-// then the K entries of each token.
+// One thread per slot, a token's K slots in neighbouring lanes (KP: K rounded up to a power of two).
 // ---------------------------------------------------------------------------
-template <typename IdxT>
 __global__ void __launch_bounds__(256)
-gate_backward_parts_kernel(int T, int E, int K, int KP, int nparts, const float *__restrict__ wpart,
-                           const float *__restrict__ gates, const int32_t *__restrict__ inv_perm,
-                           const IdxT *__restrict__ idx, int64_t stride, float *__restrict__ dz,
-                           bf16_t *__restrict__ ds) {
-    const int tpb = 256 / KP;                       // tokens per block
-    const int t0 = blockIdx.x * tpb;
-    const int nt = min(tpb, T - t0);
-    // zero this block's ds rows: nt * 2E bf16, contiguous, a multiple of 4 bytes
-    uint32_t *z = (uint32_t *)(ds + (int64_t)t0 * 2 * E);
-    for (int i = threadIdx.x; i < nt * E; i += 256) z[i] = 0u;
-    const int tl = threadIdx.x / KP, j = threadIdx.x % KP;
-    const int t = t0 + tl;
-    const bool live = tl < nt && j < K;
+gate_backward_parts_kernel(int T, int K, int KP, int nparts, const float *__restrict__ wpart,
+                           const float *__restrict__ gates, const int32_t *__restrict__ inv_perm, float *__restrict__ dz) {
+    const int j = threadIdx.x % KP, t = blockIdx.x * (256 / KP) + threadIdx.x / KP;
+    const bool live = t < T && j < K;
     float w = 0.0f, g = 0.0f;
-    int e = 0;
     if (live) {
-        const int row = inv_perm[(int64_t)t * K + j];
-        const float *p = wpart + (int64_t)row * nparts;
+        const float *p = wpart + (int64_t)inv_perm[(int64_t)t * K + j] * nparts;
         for (int i = 0; i < nparts; ++i) w += p[i];
         g = gates[(int64_t)t * K + j];
-        e = min((int)idx[(int64_t)t * stride + j], E - 1);
     }
     // sum of w over the token's slots, in a fixed order: KP neighbouring lanes (KP <= 64 divides 64)
     float mix = w;
     for (int o = 1; o < KP; o <<= 1) mix += __shfl_xor(mix, o, 64);
-    __syncthreads();                                // the zeros are in before the entries go on top
-    if (live) {
-        const float v = w - g * mix;
-        dz[(int64_t)t * K + j] = v;
-        bf16_t *row = ds + (int64_t)t * 2 * E;
-        const bf16_t hi = f32_to_bf16(v);
-        row[e] = hi;
-        row[E + e] = f32_to_bf16(v - bf16_to_f32(hi));
-    }
+    if (live) dz[(int64_t)t * K + j] = w - g * mix;
 }
 
-hipError_t launch_gate_backward_parts(int T, int E, int K, int nparts, const float *wpart, const float *gates,
-                                      const int32_t *inv_perm, const void *idx, int idx_dtype, int64_t stride,
-                                      float *dz, void *ds_dense, hipStream_t s) {
+hipError_t launch_gate_backward_parts(int T, int K, int nparts, const float *wpart, const float *gates,
+                                      const int32_t *inv_perm, float *dz, hipStream_t s) {
     ProfScope ps(PROF_GATE_BWD, s);
     int KP = 1;
     while (KP < K) KP <<= 1;                        // K <= kMaxK = 64
     const int tpb = 256 / KP;
-    const int grid = (T + tpb - 1) / tpb;
-    if (idx_dtype == R3_IDX_U8)
-        gate_backward_parts_kernel<uint8_t><<<grid, 256, 0, s>>>(T, E, K, KP, nparts, wpart, gates, inv_perm,
-                                                                (const uint8_t *)idx, stride, dz, (bf16_t *)ds_dense);
-    else
-        gate_backward_parts_kernel<uint16_t><<<grid, 256, 0, s>>>(T, E, K, KP, nparts, wpart, gates, inv_perm,
-                                                                 (const uint16_t *)idx, stride, dz,
-                                                                 (bf16_t *)ds_dense);
+    gate_backward_parts_kernel<<<(T + tpb - 1) / tpb, 256, 0, s>>>(T, K, KP, nparts, wpart, gates, inv_perm, dz);
     return hipGetLastError();
 }
 
@@ -1339,31 +1176,6 @@ hipError_t launch_transpose(int R, int C, int act, const void *in, void *out, hi
         transpose_kernel<bf16_t><<<grid, block, 0, s>>>(R, C, (const bf16_t *)in, (bf16_t *)out);
     else
         transpose_kernel<float><<<grid, block, 0, s>>>(R, C, (const float *)in, (float *)out);
-    return hipGetLastError();
-}
-
-// column sums of the dense ds [T,E] -> dbias[E] (f32), fixed order: one thread
-// per expert walks the tokens in ascending order in 64 interleaved partials,
-// combined in a fixed tree.
-template <typename T>
-__global__ void __launch_bounds__(64)
-colsum_kernel(int Tn, int E, const T *__restrict__ ds, float *__restrict__ out, int accumulate) {
-    const int e = blockIdx.x, lane = threadIdx.x;
-    const int dsw = (sizeof(T) == 2) ? 2 * E : E;
-    float acc = 0.0f;
-    for (int t = lane; t < Tn; t += kWave) {
-        acc += Elem<T>::ld(ds + (int64_t)t * dsw + e);
-        if (sizeof(T) == 2) acc += Elem<T>::ld(ds + (int64_t)t * dsw + E + e);
-    }
-    acc = wave_sum(acc);
-    if (lane == 0) out[e] = accumulate ? out[e] + acc : acc;
-}
-
-hipError_t launch_colsum(int T, int E, int act, const void *ds, float *out, int accumulate, hipStream_t s) {
-    if (act == R3_BF16)
-        colsum_kernel<bf16_t><<<E, 64, 0, s>>>(T, E, (const bf16_t *)ds, out, accumulate);
-    else
-        colsum_kernel<float><<<E, 64, 0, s>>>(T, E, (const float *)ds, out, accumulate);
     return hipGetLastError();
 }
 

@@ -285,12 +285,19 @@ router_gate_many_kernel(int T, int d, int K, const bf16_t *__restrict__ x, const
     mfma_mainloop_ahead2<TL, true, false>(acc, d / TL::BK, fp, fq, lds);   // ends with a barrier: the stages are free
     float *sl = (float *)lds;
     for_each_quad<TL>([&](int tp, int tq, int g, int p, int q) {
-        *(float4 *)(sl + q * PITCH + p) = make_float4(acc[tp][tq][4 * g], acc[tp][tq][4 * g + 1], acc[tp][tq][4 * g + 2],
-                                                      acc[tp][tq][4 * g + 3]);
+        float4 v = make_float4(acc[tp][tq][4 * g], acc[tp][tq][4 * g + 1], acc[tp][tq][4 * g + 2], acc[tp][tq][4 * g + 3]);
+        if (bias) {
+            const float4 b = *(const float4 *)(bias + p);
+            v.x += b.x; v.y += b.y; v.z += b.z; v.w += b.w;
+        }
+        *(float4 *)(sl + q * PITCH + p) = v;
     });
     __syncthreads();
-    add_logits<1, TL::BQ, E, TL::NT>(sl, PITCH, t0, T, E, bias, logits_out);
-    __syncthreads();
+    if (logits_out)   // whole rows, 16 bytes per lane
+        for (int i = threadIdx.x; i < TL::BQ * (E / 4); i += TL::NT) {
+            const int q = i / (E / 4), c = i % (E / 4);
+            if (t0 + q < T) *(float4 *)(logits_out + (int64_t)(t0 + q) * E + 4 * c) = *(const float4 *)(sl + q * PITCH + 4 * c);
+        }
     gate_from_lds<E / 32, TL::NT, IdxT>(sl, PITCH, t0, TL::BQ, T, E, K, idx, stride, gates, agree, status, part);
 }
 
@@ -354,6 +361,203 @@ plain_gate_kernel(int Tn, int d, int E, int K, const T *__restrict__ x, const T 
 }
 
 // ---------------------------------------------------------------------------
+// Router weight gradient dW_r[c][e] = sum_t x[t][c] ds[t][e], in parts over the tokens.  ds has K entries in a row of E:
+// it is never in memory.  A work-group (128 hidden columns x 128 experts, 64 tokens per k-tile) keeps its ds tile in
+// LDS, takes the old tile's entries out and puts the new one's in, each as a hi and a lo bf16 (dz to about 16 bits) in
+// columns that meet in one lane's accumulators.  A token's entries belong to one wave, whose clearing and setting are
+// in order.  Two work-groups per compute unit; x comes in two k-tiles ahead.  Bound by the read of x and, for few
+// tokens, the parts.  With ds in memory as [T][2E] and hi and lo parts written apart, us with the sum of the parts:
+// T=65536 d=2048 E=128 K=8 142 -> 109, T=16384 52 -> 44, T=1001 26 -> 17, T=6000 d=1024 E=384 K=4 54 -> 28; half or twice
+// the work-groups: 145 / 123 at 65536 tokens, 48 / 56 at 16384.  The kernel that made ds: 28 -> 14 us at T=65536.
+// ---------------------------------------------------------------------------
+constexpr int kDwrQ = 128, kDwrP = 128, kDwrK = 64;
+constexpr int kDwrPBytes = kDwrK * 2 * kDwrP * 2, kDwrQBytes = kDwrK * kDwrQ * 2, kDwrLds = kDwrPBytes + 2 * kDwrQBytes;
+
+template <int EPT, typename IdxT>   // EPT: entries per thread and k-tile, 4 EPT >= K
+__global__ void __launch_bounds__(256, 2)
+router_dwr_kernel(int T, int d, int E, int K, int rows, const bf16_t *__restrict__ x, const float *__restrict__ dz,
+                  const IdxT *__restrict__ idx, int64_t stride, float *__restrict__ part) {
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const int npt = (E + kDwrP - 1) / kDwrP, nqt = (d + kDwrQ - 1) / kDwrQ;
+    const int sp = blockIdx.x / (npt * nqt), rem = blockIdx.x - sp * npt * nqt;
+    const int qt = rem / npt, q0 = qt * kDwrQ, p0 = (rem - qt * npt) * kDwrP;
+    const int r0 = sp * rows, r1 = min(T, r0 + rows), nk = (r1 - r0 + kDwrK - 1) / kDwrK;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wp = wave & 1, wq = wave >> 1;
+    char *const pt = lds, *const qs = lds + kDwrPBytes;
+    uint4 rq[2][4];
+    int eid[2][EPT];
+    float ez[2][EPT];
+    // the thread's entries: token ek of the k-tile, position ej
+    int ek[EPT], ej[EPT];
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) {
+        const int n = lane + 64 * i;
+        ek[i] = n < 16 * K ? 16 * wave + n / K : kDwrK * 65536;   // (no entry: past every token)
+        ej[i] = n % K;
+    }
+    auto gload = [&](int kt, uint4 (&q)[4], int (&id)[EPT], float (&z)[EPT]) {
+        const int t0 = r0 + kt * kDwrK;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int n = tid + 256 * i, t = t0 + n / 16, c = q0 + n % 16 * 8;
+            q[i] = t < r1 && c < d ? ld16(x + (int64_t)t * d + c) : zero16();
+        }
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            id[i] = -1;
+            z[i] = 0.0f;
+            if (ek[i] < kDwrK && t0 + ek[i] < r1) {
+                id[i] = min((int)idx[(int64_t)(t0 + ek[i]) * stride + ej[i]], E - 1) - p0;
+                z[i] = dz[(int64_t)(t0 + ek[i]) * K + ej[i]];
+            }
+        }
+    };
+    int old[EPT];
+#pragma unroll
+    for (int i = 0; i < EPT; ++i) old[i] = -1;
+    auto put = [&](int stage, const uint4 (&q)[4], const int (&id)[EPT], const float (&z)[EPT]) {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const int n = tid + 256 * i;
+            *(uint4 *)(qs + stage * kDwrQBytes + tr_off<kDwrQ>(n / 16, n % 16)) = q[i];
+        }
+        // expert e's hi half is column (e / 64) * 128 + e % 64, its lo half 64 columns on (128 bytes, a bit of the offset)
+#pragma unroll
+        for (int i = 0; i < EPT; ++i)
+            if (old[i] >= 0) {
+                *(bf16_t *)(pt + old[i]) = 0;
+                *(bf16_t *)(pt + (old[i] ^ 128)) = 0;
+            }
+        asm volatile("" ::: "memory");
+#pragma unroll
+        for (int i = 0; i < EPT; ++i) {
+            old[i] = -1;
+            if (id[i] >= 0 && id[i] < kDwrP) {
+                const int c = (id[i] >> 6) * 128 + (id[i] & 63);
+                old[i] = tr_off<2 * kDwrP>(ek[i], c >> 3) + (c & 7) * 2;
+                const bf16_t hi = f32_to_bf16(z[i]);
+                *(bf16_t *)(pt + old[i]) = hi;
+                *(bf16_t *)(pt + (old[i] ^ 128)) = f32_to_bf16(z[i] - bf16_to_f32(hi));
+            }
+        }
+    };
+    TrFrag<2 * kDwrP> pf;
+    TrFrag<kDwrQ> qf;
+    pf.init(wp * 128);
+    qf.init(wq * 64);
+    f32x16_t acc[4][2];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+    auto multiply = [&](int stage) {
+#pragma unroll
+        for (int s = 0; s < kDwrK / 16; ++s) {
+            bf16x8_t a[4], b[2];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) a[i] = pf.read(pt, i, s);
+#pragma unroll
+            for (int j = 0; j < 2; ++j) b[j] = qf.read(qs + stage * kDwrQBytes, j, s);
+#pragma unroll
+            for (int i = 0; i < 4; ++i)
+#pragma unroll
+                for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        }
+    };
+    gload(0, rq[0], eid[0], ez[0]);
+    gload(1, rq[1], eid[1], ez[1]);
+    for (int i = tid; i < kDwrPBytes / 16; i += 256) ((uint4 *)pt)[i] = zero16();
+    __syncthreads();
+    put(0, rq[0], eid[0], ez[0]);
+    __syncthreads();
+    for (int kt = 0; kt < nk; kt += 2) {
+        gload(kt + 2, rq[0], eid[0], ez[0]);
+        multiply(0);
+        __syncthreads();
+        put(1, rq[1], eid[1], ez[1]);
+        __syncthreads();
+        if (kt + 1 < nk) {
+            gload(kt + 3, rq[1], eid[1], ez[1]);
+            multiply(1);
+            __syncthreads();
+            put(0, rq[0], eid[0], ez[0]);
+            __syncthreads();
+        }
+    }
+    float *o = part + (int64_t)sp * d * E;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+#pragma unroll
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const int e = p0 + wp * 64 + i * 32 + g * 8 + (lane >> 5) * 4, c = q0 + wq * 64 + j * 32 + (lane & 31);
+                float v[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) v[u] = acc[i][j][4 * g + u] + acc[i + 2][j][4 * g + u];
+                if (c >= d) continue;
+                float *at = o + (int64_t)c * E + e;
+                if (E % 4 == 0) {
+                    if (e < E) *(float4 *)at = make_float4(v[0], v[1], v[2], v[3]);
+                } else {
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        if (e + u < E) at[u] = v[u];
+                }
+            }
+}
+
+// out[i] (+)= sum_s part[s][i], s ascending
+__global__ void __launch_bounds__(256)
+sum_parts_kernel(int64_t n, int nsplit, const float *__restrict__ part, float *__restrict__ out, int accumulate) {
+    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (i >= n) return;
+    float acc = accumulate ? out[i] : 0.0f;
+    for (int s = 0; s < nsplit; s += 8) {
+        float v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = s + u < nsplit ? part[(int64_t)(s + u) * n + i] : 0.0f;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    out[i] = acc;
+}
+
+// dbias[e] (+)= the sum of dz over the slots of expert e: its rows of the permutation, or, without one, all slots
+// whose id it is.  A block per expert, fixed order.
+template <typename IdxT, bool PERM>
+__global__ void __launch_bounds__(1024)
+router_dbias_kernel(int T, int E, int K, const float *__restrict__ dz, const IdxT *__restrict__ idx, int64_t stride,
+                    const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm, float *__restrict__ dbias,
+                    int accumulate) {
+    __shared__ float tmp[16];
+    const int e = blockIdx.x;
+    float acc = 0.0f;
+    if constexpr (PERM) {
+        const int r1 = offsets[e + 1];
+        for (int r = offsets[e] + threadIdx.x; r < r1; r += 4 * 1024) {
+            float v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = r + u * 1024 < r1 ? dz[perm[r + u * 1024]] : 0.0f;
+            acc += (v[0] + v[1]) + (v[2] + v[3]);
+        }
+    } else {
+        for (int64_t i = threadIdx.x; i < (int64_t)T * K; i += 1024)
+            if (min((int)idx[i / K * stride + i % K], E - 1) == e) acc += dz[i];
+    }
+    acc = wave_sum(acc);
+    if (lane_id() == 0) tmp[threadIdx.x >> 6] = acc;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        acc = accumulate ? dbias[e] : 0.0f;
+        for (int i = 0; i < 16; ++i) acc += tmp[i];
+        dbias[e] = acc;
+    }
+}
+
+// ---------------------------------------------------------------------------
 // host side
 // ---------------------------------------------------------------------------
 namespace {
@@ -414,6 +618,55 @@ void plain_by_size(int Tn, int d, int E, int K, const void *x, const void *Wr, c
 }
 
 }  // namespace
+
+// (with more than 16 entries a token the kernel's bookkeeping no longer fits its registers)
+static bool bf16_dwr(int act, int d, int K, bool plain_only) { return act == R3_BF16 && d % 8 == 0 && K <= 16 && !plain_only; }
+// tokens per part: whole k-tiles, and enough parts for two work-groups on every compute unit
+static int dwr_rows(int T, int d, int E) {
+    const int64_t tiles = (int64_t)((d + kDwrQ - 1) / kDwrQ) * ((E + kDwrP - 1) / kDwrP), kts = (T + kDwrK - 1) / kDwrK;
+    const int64_t ns = std::max<int64_t>(1, std::min<int64_t>(kts, 512 / tiles));
+    return (int)((kts + ns - 1) / ns * kDwrK);
+}
+
+size_t router_dwr_ws_bytes(int act, int T, int d, int E, int K, bool plain_only) {
+    const int rows = bf16_dwr(act, d, K, plain_only) ? dwr_rows(T, d, E) : plain_dwr_rows(T, d, E);
+    return align_up((size_t)((T + rows - 1) / rows) * d * E * sizeof(float), 256);
+}
+
+template <typename IdxT>
+static void launch_dwr(int T, int d, int E, int K, const void *x, const float *dz, const void *idx, int64_t stride,
+                       float *part, hipStream_t s) {
+    const int rows = dwr_rows(T, d, E);
+    const int grid = (T + rows - 1) / rows * ((d + kDwrQ - 1) / kDwrQ) * ((E + kDwrP - 1) / kDwrP);
+    auto k = K <= 4 ? router_dwr_kernel<1, IdxT> : K <= 8 ? router_dwr_kernel<2, IdxT> : router_dwr_kernel<4, IdxT>;
+    k<<<grid, 256, kDwrLds, s>>>(T, d, E, K, rows, (const bf16_t *)x, dz, (const IdxT *)idx, stride, part);
+}
+
+hipError_t router_dwr(int T, int d, int E, int K, int act, const void *x, const float *dz, const void *idx, int idx_dtype,
+                      int64_t stride, float *part, float *dWr, int accumulate, bool plain_only, hipStream_t s) {
+    ProfScope ps(PROF_DWR, s);
+    const bool bf = bf16_dwr(act, d, K, plain_only);
+    const int rows = bf ? dwr_rows(T, d, E) : plain_dwr_rows(T, d, E);
+    if (bf) (idx_dtype == R3_IDX_U8 ? launch_dwr<uint8_t> : launch_dwr<uint16_t>)(T, d, E, K, x, dz, idx, stride, part, s);
+    else plain_dwr_parts(T, d, E, K, act, x, dz, idx, idx_dtype, stride, part, s);
+    const int64_t n = (int64_t)d * E;
+    sum_parts_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, (T + rows - 1) / rows, part, dWr, accumulate);
+    return hipGetLastError();
+}
+
+hipError_t router_dbias(int T, int E, int K, const float *dz, const void *idx, int idx_dtype, int64_t stride,
+                        const int32_t *offsets, const int32_t *perm, float *dbias, int accumulate, hipStream_t s) {
+    if (perm) {
+        router_dbias_kernel<uint8_t, true><<<E, 1024, 0, s>>>(T, E, K, dz, nullptr, stride, offsets, perm, dbias, accumulate);
+    } else if (idx_dtype == R3_IDX_U8) {
+        router_dbias_kernel<uint8_t, false><<<E, 1024, 0, s>>>(T, E, K, dz, (const uint8_t *)idx, stride, nullptr, nullptr, dbias,
+                                                               accumulate);
+    } else {
+        router_dbias_kernel<uint16_t, false><<<E, 1024, 0, s>>>(T, E, K, dz, (const uint16_t *)idx, stride, nullptr, nullptr,
+                                                                dbias, accumulate);
+    }
+    return hipGetLastError();
+}
 
 bool router_gate_supported(int act, int d, int E, bool plain_only) {
     if (act == R3_BF16 && !plain_only && d % 8 == 0 && E % 8 == 0 && E <= 512) return true;

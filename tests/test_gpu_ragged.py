@@ -48,9 +48,13 @@ def test_layer_at_ragged_widths(sh, one_call):
     # a caller without perm still has the plain kernels (Xp given, forward call by call)
     if not one_call:
         dx = buf.dx.clone()
+        dbias = torch.full((sh.E,), 3.0, dtype=torch.float32, device="cuda")
         D = buf.D
         r3.moe_backward(D, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], buf.gates, buf.inv_perm, None, buf.offsets, buf.Xp,
-                        buf.A, buf.B, buf.H, buf.Yp, *w, buf.dx, buf.dW_r, buf.dW_gate, buf.dW_up, buf.dW_down, buf.ws_bwd)
+                        buf.A, buf.B, buf.H, buf.Yp, *w, buf.dx, buf.dW_r, buf.dW_gate, buf.dW_up, buf.dW_down, buf.ws_bwd,
+                        dbias=dbias)
         torch.cuda.synchronize()
+        assert_close(dbias.cpu().numpy(), ref["dbias"], "dbias without perm", c.rel,
+                     router_gradient_sigma(n["x"], n["dy"], c.idx, fwd, sh.E)[1])
         assert_close(host(buf.dx), ref["dx"], "dx without perm", c.rel)
         assert not torch.equal(dx, torch.zeros_like(dx))

@@ -1,4 +1,4 @@
-"""The one-launch router kernels (logits, replay gate, agreement) at the edges of their tiles and of the rule that picks
+"""The router kernels (logits, replay gate, agreement; their weight gradient) and the dispatch at the edges of their tiles and of the rule that picks
 between them, against the CPU oracle: gates to 1e-5 (tests/util.py), logits to a float32 sum's error, status and agreement."""
 import numpy as np
 import pytest
@@ -6,7 +6,7 @@ import torch
 
 from oracle import sparse
 from paper_2510_11370_amd import r3, synth
-from util import Case, assert_gates_close
+from util import Case, assert_close, assert_gates_close, router_gradient_sigma
 
 pytestmark = pytest.mark.gpu
 SH = synth.LayerShape
@@ -80,3 +80,49 @@ def test_dispatch_at_chunk_edges(T, E, K, skew, token_major):
     assert int(status.item()) == 0
     for got, want in zip(out, (counts, offsets, inv_perm, perm)):
         assert np.array_equal(got.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("T,d,E,K,act,with_perm", [
+    (1, 8, 8, 1, "bf16", True), (65, 136, 136, 6, "bf16", False), (4097, 264, 130, 16, "bf16", True),   # tile and part edges
+    (300, 128, 128, 24, "bf16", True), (150, 36, 70, 5, "f32", False), (129, 33, 9, 3, "f32", True),    # the f32 tiles
+])
+def test_router_gradient_at_tile_edges(T, d, E, K, act, with_perm):
+    """dW_r and dbias through r3_moe_backward, overwritten and then added to, with and without the permutation."""
+    sh = SH(T=T, d=d, E=E, K=K, F=256, act=act, sigma=0.05, seed=95)
+    c = Case(sh, backward=True, scale_w=5.0)
+    n = c.np
+    fwd = sparse.forward(n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], n["bias"])
+    ref = sparse.backward(n["dy"], n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], fwd, want_dbias=True)
+    buf = r3.LayerBuffers(c.D, backward=True, gathered_copy=not with_perm)
+    w = (c.t["Wg"], c.t["Wu"], c.t["Wd"])
+    (r3.forward_one_call if with_perm else r3.forward)(buf, c.t["x"], c.t["Wr"], c.t["idx"], *w, bias=c.t["bias"])
+    dbias = torch.full((E,), 3.0, dtype=torch.float32, device="cuda")
+    for acc in (False, True):
+        r3.backward(buf, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], *w, dbias=dbias, accumulate=acc)
+    torch.cuda.synchronize()
+    if K == 1:
+        assert not buf.dW_r.any() and not dbias.any()
+        return
+    sw, sb = (None, None) if act == "f32" else router_gradient_sigma(n["x"], n["dy"], c.idx, fwd, E)
+    assert_close(buf.dW_r.cpu().numpy() / 2, ref["dWr"], "dW_r", c.rel, sw)
+    assert_close(dbias.cpu().numpy() / 2, ref["dbias"], "dbias", c.rel, sb)
+
+
+@pytest.mark.parametrize("T,E,K,pad", [(1, 1, 1, 0), (33, 5, 3, 0), (65, 33, 8, 3), (31, 100, 6, 4), (40, 257, 8, 0),
+                                       (64, 384, 4, 0), (7, 385, 7, 1), (90, 512, 8, 0), (33, 513, 8, 0)])
+def test_record_at_tile_edges(T, E, K, pad):
+    """TopKMask for expert counts that fill no whole pieces: ties, NaNs and infinities included, rows `pad` floats apart."""
+    rng = np.random.default_rng(E)
+    lg = rng.integers(-3, 4, size=(T, E + pad)).astype(np.float32)
+    lg[rng.random(lg.shape) < 0.05] = np.nan
+    lg[rng.random(lg.shape) < 0.02] = -np.inf
+    lg[0] = np.nan
+    lg[:, E:] = 9.0                                    # beyond the row: never selected
+    D = r3.desc(T, 16, E, K, 16)
+    out = torch.zeros(T, K, dtype=torch.uint8 if E <= 256 else torch.int16, device="cuda")
+    out = out if E <= 256 else out.view(torch.uint16)
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    r3.record_topk(D, torch.from_numpy(lg).to("cuda"), out, status)
+    torch.cuda.synchronize()
+    assert np.array_equal(out.cpu().numpy().astype(np.int32), sparse.topk_mask(np.ascontiguousarray(lg[:, :E]), K))
+    assert int(status.item()) == r3.DATA_NONFINITE

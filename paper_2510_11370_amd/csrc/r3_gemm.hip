@@ -257,7 +257,7 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
             const int32_t *__restrict__ offsets, const int32_t *__restrict__ tiles, const bf16_t *__restrict__ Wg,
             const bf16_t *__restrict__ Wu, bf16_t *__restrict__ H, bf16_t *__restrict__ FA, bf16_t *__restrict__ FB,
             const float *__restrict__ grow) {
-    __shared__ __attribute__((aligned(1024))) char lds[2 * kSuperBytes];   // one piece: a tail tile lays it out differently
+    __shared__ __attribute__((aligned(1024))) char lds[kRowLds];   // one piece: a tail tile lays it out differently
     char *const bufA = lds, *const bufB = lds + kSuperBytes;
     char *const s0 = bufA, *const s1 = bufA + kStageBytes, *const s2 = bufB, *const s3 = bufB + kStageBytes;
     constexpr int BF = 128;  // features per tile
@@ -312,7 +312,7 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
 
     Acc2 acc;
     zero_acc2(acc);
-    if (row_end - row0 <= kWaveRowsQ) mfma_tail_loop3(acc, nw, P, Q, lds);
+    if (row_end - row0 <= kTailRows) mfma_tail_loop3(acc, nw, P, Q, lds, row_end - row0);
     else mfma_mainloop3(acc, nw, P, Q, lds, row_end - row0);
     tl.prefetch();
     if (more) aim(nxt);   // here, so that the row-index loads of a gathered tile hide behind the epilogue
@@ -392,7 +392,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
                const bf16_t *__restrict__ FB, bf16_t *__restrict__ out0, bf16_t *__restrict__ out1,
                const int32_t *__restrict__ tok, int T, const float *__restrict__ grow,
                const bf16_t *__restrict__ Hs, bf16_t *__restrict__ out2, float *__restrict__ wpart) {
-    __shared__ __attribute__((aligned(1024))) char lds[2 * kSuperBytes];   // one piece: a tail tile lays it out differently
+    __shared__ __attribute__((aligned(1024))) char lds[kRowLds];   // one piece: a tail tile lays it out differently
     char *const bufA = lds, *const bufB = lds + kSuperBytes;
     char *const s0 = bufA, *const s1 = bufA + kStageBytes, *const s2 = bufB, *const s3 = bufB + kStageBytes;
     const int NOUT = (MODE == 1) ? F : d;  // width of the output
@@ -485,7 +485,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
 
     Acc2 acc;
     zero_acc2(acc);
-    if (row_end - row0 <= kWaveRowsQ) mfma_tail_loop3(acc, nw, P, Q, lds);
+    if (row_end - row0 <= kTailRows) mfma_tail_loop3(acc, nw, P, Q, lds, row_end - row0);
     else mfma_mainloop3(acc, nw, P, Q, lds, row_end - row0);
     tl.prefetch();
     if constexpr (GATHER)

@@ -748,35 +748,44 @@ __device__ __forceinline__ void mfma_mainloop3(Acc2 &acc, int nw, const POp &P, 
 }
 
 // ---------------------------------------------------------------------------
-// The same loop for a tail tile: at most 64 live rows (the last few rows of an expert's segment).
-// Such a tile multiplies little and is bound by the latency of its weight windows, so the space the
-// dead 192 rows of the Q windows would take holds a third window instead and the loads run two
-// windows ahead.  `lds` is the work-group's whole 128 KB: P windows at 0, 32, 64 KB; Q windows (rows
-// 0..63 only, 8 KB each) from 96 KB.  Only waves 0 and 1 hold live rows; waves 0-3 load.
-// A loader wave issues kTailLoads per window, so "at most that many outstanding" is "the next
+// The same loop for a tail tile: at most 128 live rows (the last rows of an expert's segment, or all of a
+// rarely chosen expert's).  Such a tile multiplies little and is bound by the latency of its weight
+// windows, so the space the dead rows of the Q windows would take holds a third window instead and the loads run two
+// windows ahead.  `lds` is the work-group's kRowLds bytes: P windows at 0, 32, 64 KB; Q windows (rows 0..127 only, 16 KB
+// each) from 96 KB.  Only the waves of live 64-row blocks multiply; waves 0-3 load.
+// A loader wave issues 8 loads for P and 2 per 64 rows for Q, so "at most that many outstanding" is "the next
 // window is in" as long as the one after it has been issued.
+// (Rows 65..128 in the two-window loop instead: 128 experts, d=2048 F=768, 1001 tokens top-8, SwiGLU 194 -> 177 us,
+// down 95 -> 86, dH 131 -> 117, dXp 229 -> 213.)
 // ---------------------------------------------------------------------------
-constexpr int kTailQBytes = kWaveRowsQ * kBK3 * 2;                       // 8 KB: 64 rows of a Q window
-constexpr int kTailLoads = 8 + 8 * kWaveRowsQ / kTile;                   // 8 for P + 2 for Q
+constexpr int kTailRows = 2 * kWaveRowsQ;
+constexpr int kTailQBytes = kTailRows * kBK3 * 2;                        // 16 KB: 128 rows of a Q window
 constexpr int kTailQBase = 3 * kWinBytes;
+constexpr int kRowLds = kTailQBase + 3 * kTailQBytes;                    // 144 KB (the full tiles' loop uses 128)
 
-__device__ __forceinline__ void tail_barrier(bool loader, bool one_ahead) {
+template <int LOADS>
+__device__ __forceinline__ void tail_wait() {
+    __builtin_amdgcn_s_waitcnt((LOADS & 15) | (7 << 4) | (0 << 8) | ((LOADS >> 4) << 14));
+}
+__device__ __forceinline__ void tail_barrier(bool loader, bool one_ahead, bool wide) {
     if (!loader) __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
-    else if (one_ahead) __builtin_amdgcn_s_waitcnt((kTailLoads & 15) | (7 << 4) | (0 << 8) | ((kTailLoads >> 4) << 14));
-    else __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0 << 8) | (0 << 14));
+    else if (!one_ahead) tail_wait<0>();
+    else if (wide) tail_wait<12>();
+    else tail_wait<10>();
     __builtin_amdgcn_s_barrier();
 }
 
 template <class POp, class QOp>
-__device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P, const QOp &Q, char *lds) {
+__device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P, const QOp &Q, char *lds, int live_rows) {
     if (nw <= 0) return;
     const uint32_t a0 = lds_addr(lds);
     const int wave_ = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const bool loader = wave_ < kLoaderWaves;
-    const bool live = wave_ / kWP2 == 0;
+    const bool loader = wave_ < kLoaderWaves, wide = live_rows > kWaveRowsQ;
+    const bool live = (wave_ / kWP2) * kWaveRowsQ < live_rows;
+    const int qrows = wide ? kTailRows : kWaveRowsQ;
     auto issue = [&](int J, int slot) {
         win_issue(P, J, a0 + slot * kWinBytes);
-        win_issue(Q, J, a0 + kTailQBase + slot * kTailQBytes, kWaveRowsQ);
+        win_issue(Q, J, a0 + kTailQBase + slot * kTailQBytes, qrows);
     };
     if (loader) {
         if constexpr (POp::kIndexed || QOp::kIndexed) {
@@ -788,7 +797,7 @@ __device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P,
             if (nw > 1) issue(1, 1);
         }
     }
-    tail_barrier(loader, nw > 1);
+    tail_barrier(loader, nw > 1, wide);
     Frags x, y;
 #pragma unroll
     for (int i = 0; i < kTP2; ++i) x.a[i] = bf16x8_t{};
@@ -806,7 +815,7 @@ __device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P,
             sub_step3(acc, y, x, P, Q, pw, qw, 2);
             sub_step3(acc, x, y, P, Q, pw, qw, 3);
         }
-        tail_barrier(loader, J + 2 < nw);
+        tail_barrier(loader, J + 2 < nw, wide);
     };
     for (int J = 0; J < nw; J += 3) {
         window(J, 0);

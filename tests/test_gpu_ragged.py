@@ -58,3 +58,30 @@ def test_layer_at_ragged_widths(sh, one_call):
                      router_gradient_sigma(n["x"], n["dy"], c.idx, fwd, sh.E)[1])
         assert_close(host(buf.dx), ref["dx"], "dx without perm", c.rel)
         assert not torch.equal(dx, torch.zeros_like(dx))
+
+
+@pytest.mark.parametrize("d,F", [(256, 256), (320, 192)])     # whole tiles; guarded ones, five and three windows of 64 k
+def test_rows_per_expert_at_tile_edges(d, F):
+    """Experts with 0, 1, 64, 65, 128, 129, 192, 256, 257 and 385 rows: every loop a row tile can take, and its edges."""
+    rows = [0, 1, 64, 65, 128, 129, 192, 256, 257, 385]
+    sh = SH(T=sum(rows), d=d, E=len(rows), K=1, F=F, seed=76)
+    c = Case(sh, backward=True, scale_w=5.0)
+    c.idx = np.random.default_rng(0).permutation(np.repeat(np.arange(len(rows)), rows)).astype(np.int32)[:, None]
+    c.t["idx"] = torch.from_numpy(c.idx.astype(np.uint8)).to("cuda")
+    n = c.np
+    fwd = sparse.forward(n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], n["bias"])
+    ref = sparse.backward(n["dy"], n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], fwd, want_dbias=True)
+    w = (c.t["Wg"], c.t["Wu"], c.t["Wd"])
+    buf = r3.LayerBuffers(c.D, backward=True, gathered_copy=False)
+    for t in (buf.Yp, buf.H, buf.A, buf.B, buf.dx):
+        t.fill_(7.0)
+    r3.forward_one_call(buf, c.t["x"], c.t["Wr"], c.t["idx"], *w, bias=c.t["bias"])
+    r3.backward(buf, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], *w)
+    torch.cuda.synchronize()
+    assert buf.counts.tolist() == rows
+    for got, want, name in ((buf.H, fwd["h"], "H"), (buf.Yp, fwd["o"], "Yp"), (buf.y, fwd["y"], "y"), (buf.dx, ref["dx"], "dx")):
+        assert_close(host(got), want, name, c.rel)
+    for got, key in ((buf.dW_gate, "dWg"), (buf.dW_up, "dWu"), (buf.dW_down, "dWd")):
+        got = got.cpu().numpy()
+        for e in range(sh.E):
+            assert np.linalg.norm(got[e] - ref[key][e]) <= c.rel * np.linalg.norm(ref[key][e]) + 1e-30, (key, e)

@@ -134,3 +134,36 @@ def test_diagnostics_host_errors():
         r3.policy_discrepancy(x, x, [2.0] * 9, out[:1], out)               # too many thresholds
     with pytest.raises(r3.R3Error, match="WORKSPACE"):
         r3.policy_discrepancy(x, x, [2.0], out[:1], out[1:2], ws=torch.empty(256, dtype=torch.uint8, device="cuda"))
+
+
+@pytest.mark.parametrize("K,E", [(2, 64), (4, 128), (6, 64), (8, 256), (2, 384), (4, 384), (6, 300), (8, 384)])
+@pytest.mark.parametrize("token_major", [False, True])
+@pytest.mark.parametrize("L,T,flip", [(3, 129, 1.0), (7, 1000, 0.0), (5, 128, 0.4), (600, 3, 0.5)])
+def test_routing_diff_every_set_size(K, E, token_major, L, T, flip):
+    """Each set size that is kept in registers: nothing differs, everything does (the queues fill on every step),
+    a tile and one token more, more layers than a work-group has lanes."""
+    a, b = _pair(L, T, K, E, seed=K * E + T, flip=flip)
+    off = [0, T // 3, T // 3, T]
+    want = dg.routing_diff_fast(a, b, E, off)
+    got = _run(a, b, E, token_major, off)
+    for name, w, g in zip(("router_hist", "token_choices", "token_routers", "seq_mean"), want, got):
+        assert np.array_equal(np.asarray(w), np.asarray(g)), name
+
+
+@pytest.mark.parametrize("K,E,shift", [(8, 128, 1), (8, 128, 4), (4, 64, 2), (6, 64, 1), (8, 384, 2), (4, 384, 2)])
+def test_routing_diff_at_odd_addresses(K, E, shift):
+    """Records that start between the addresses whole loads need (shift in bytes)."""
+    L, T = 4, 300
+    a, b = _pair(L, T, K, E, seed=shift)
+    want = dg.routing_diff_fast(a, b, E, [0, T])
+    npdt = np.uint8 if E <= 256 else np.uint16
+    dev = []
+    for v in (a, b):
+        raw = np.frombuffer(b"\0" * shift + v.astype(npdt).tobytes(), dtype=np.uint8)
+        dev.append(torch.from_numpy(raw.copy()).cuda()[shift:])
+    D = r3.desc(T, 16, E, K, 16)
+    hist = torch.zeros(K + 1, dtype=torch.int64, device="cuda")
+    tc, tr = (torch.empty(T, dtype=torch.int32, device="cuda") for _ in range(2))
+    r3.routing_diff(D, L, dev[0], dev[1], T * K, hist, tc, tr)
+    for name, w, g in zip(("router_hist", "token_choices", "token_routers"), want, (hist, tc, tr)):
+        assert np.array_equal(np.asarray(w), g.cpu().numpy()), name

@@ -236,3 +236,30 @@ def test_empty_inputs_and_host_errors():
     r3.mask_cache_gather(pages, table2, start, out3)
     torch.cuda.synchronize()
     assert torch.equal(out3, pages[0, :3].permute(1, 0, 2))
+
+
+@pytest.mark.parametrize("lens", [
+    [1] * 200,                                         # a tile spans 64 sequences
+    [0] * 150 + [5] + [0] * 90 + [70, 1, 0, 0, 3],     # long runs of empty sequences
+    [1000], [63, 1, 64, 65, 1, 0, 200],
+    [3] * 5000,                                        # three probing steps for the first token
+])
+def test_gather_finds_the_sequence(lens):
+    L, K, P = 2, 8, 4
+    rng = np.random.default_rng(len(lens))
+    start = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T, blocks = int(start[-1]), max(1, (max(lens) + P - 1) // P)
+    need = [(n + P - 1) // P for n in lens]
+    table = np.zeros((len(lens), blocks), np.int32)
+    ids = rng.permutation(sum(need)).astype(np.int32)
+    at = 0
+    for s, k in enumerate(need):
+        table[s, :k] = ids[at:at + k]
+        at += k
+    pages = rng.integers(0, 256, (sum(need), P, L, K)).astype(np.uint8)
+    want = np.stack([pages[table[s, p // P], p % P] for s, n in enumerate(lens) for p in range(n)], axis=1)
+    out = torch.zeros((L, T, K), dtype=torch.uint8, device="cuda")
+    status = torch.zeros(1, dtype=torch.int32, device="cuda")
+    r3.mask_cache_gather(*(torch.from_numpy(v).cuda() for v in (pages, table, start)), out, status)
+    assert status.item() == 0
+    assert np.array_equal(out.cpu().numpy(), want)

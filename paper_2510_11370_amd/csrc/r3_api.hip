@@ -370,13 +370,10 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
             return R3_ERR_HIP;
         if (plain_dxp(S, m.d, m.E, m.F, m.act, dA, dB, offsets, W_gate, W_up, dXp, s) != hipSuccess) return R3_ERR_HIP;
     }
-    // router:  dW_r = x^T ds, dbias = column sums of ds (ds: dz at the recorded experts)
-    if (router_dwr(m.T, m.d, m.E, m.K, m.act, x, dz, idx, m.idx, m.stride, (float *)(base + w.part), dW_r, accumulate,
-                   force_simt(), s) != hipSuccess)
+    // router:  dW_r = x^T ds, dbias = column sums of ds (ds: dz at the recorded experts), W_r^T for dx
+    if (router_backward(m.T, m.d, m.E, m.K, m.act, x, W_r, dz, idx, m.idx, m.stride, offsets, perm, (float *)(base + w.part),
+                        dW_r, dbias, WrT, accumulate, force_simt(), s) != hipSuccess)
         return R3_ERR_HIP;
-    if (dbias && router_dbias(m.T, m.E, m.K, dz, idx, m.idx, m.stride, offsets, perm, dbias, accumulate, s) != hipSuccess)
-        return R3_ERR_HIP;
-    if (launch_transpose(m.d, m.E, m.act, W_r, WrT, s) != hipSuccess) return R3_ERR_HIP;
     // dx = un-permuted expert gradients + router term
     return hip_rc(launch_dx_finish(m.T, m.d, m.E, m.K, m.act, dXp, WrT, dz, inv_perm, idx, m.idx, m.stride, dx,
                                    s));

@@ -51,7 +51,6 @@ hipError_t launch_gate_backward_parts(int T, int K, int nparts, const float *wpa
 hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp, const void *WrT,
                             const float *dz, const int32_t *inv_perm, const void *idx, int idx_dtype,
                             int64_t stride, void *dx, hipStream_t s);
-hipError_t launch_transpose(int R, int C, int act, const void *in, void *out, hipStream_t s);
 
 // r3_diag.hip
 size_t policy_ws_bytes();
@@ -101,12 +100,11 @@ hipError_t router_gate(int T, int d, int E, int K, int act, const void *x, const
                        bool plain_only, hipStream_t s);
 
 // Router weight gradient dW_r (+)= x^T ds, ds[t][idx[t][j]] = dz[t][j]; part: router_dwr_ws_bytes() bytes.  dbias (+)=
-// column sums of ds (offsets and perm as r3_permute makes them; perm may be NULL)
+// column sums of ds, unless NULL (offsets and perm as r3_permute makes them; perm may be NULL).  WrT [E,d] = W_r^T
 size_t router_dwr_ws_bytes(int act, int T, int d, int E, int K, bool plain_only);
-hipError_t router_dwr(int T, int d, int E, int K, int act, const void *x, const float *dz, const void *idx, int idx_dtype,
-                      int64_t stride, float *part, float *dWr, int accumulate, bool plain_only, hipStream_t s);
-hipError_t router_dbias(int T, int E, int K, const float *dz, const void *idx, int idx_dtype, int64_t stride,
-                        const int32_t *offsets, const int32_t *perm, float *dbias, int accumulate, hipStream_t s);
+hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, const void *Wr, const float *dz, const void *idx,
+                           int idx_dtype, int64_t stride, const int32_t *offsets, const int32_t *perm, float *part, float *dWr,
+                           float *dbias, void *WrT, int accumulate, bool plain_only, hipStream_t s);
 
 // r3_gemm.hip (bf16 MFMA)
 bool mfma_ffn_supported(int64_t S, int d, int F);

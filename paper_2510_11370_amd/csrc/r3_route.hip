@@ -1157,26 +1157,4 @@ hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp
     return dx_finish_dispatch<float, 1>(T, E, K, d, dXp, WrT, dz, inv_perm, idx, idx_dtype, stride, dx, s);
 }
 
-// transpose a small [R,C] matrix (W_r) into [C,R]
-template <typename T>
-__global__ void transpose_kernel(int R, int C, const T *__restrict__ in, T *__restrict__ out) {
-    __shared__ T tile[32][33];
-    int c = blockIdx.x * 32 + threadIdx.x, r0 = blockIdx.y * 32;
-    for (int i = threadIdx.y; i < 32; i += blockDim.y)
-        if (r0 + i < R && c < C) tile[i][threadIdx.x] = in[(int64_t)(r0 + i) * C + c];
-    __syncthreads();
-    int r = r0 + threadIdx.x, c0 = blockIdx.x * 32;
-    for (int i = threadIdx.y; i < 32; i += blockDim.y)
-        if (c0 + i < C && r < R) out[(int64_t)(c0 + i) * R + r] = tile[threadIdx.x][i];
-}
-
-hipError_t launch_transpose(int R, int C, int act, const void *in, void *out, hipStream_t s) {
-    dim3 grid((C + 31) / 32, (R + 31) / 32), block(32, 8);
-    if (act == R3_BF16)
-        transpose_kernel<bf16_t><<<grid, block, 0, s>>>(R, C, (const bf16_t *)in, (bf16_t *)out);
-    else
-        transpose_kernel<float><<<grid, block, 0, s>>>(R, C, (const float *)in, (float *)out);
-    return hipGetLastError();
-}
-
 }  // namespace r3

@@ -509,52 +509,79 @@ router_dwr_kernel(int T, int d, int E, int K, int rows, const bf16_t *__restrict
             }
 }
 
-// out[i] (+)= sum_s part[s][i], s ascending
-__global__ void __launch_bounds__(256)
-sum_parts_kernel(int64_t n, int nsplit, const float *__restrict__ part, float *__restrict__ out, int accumulate) {
-    const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (i >= n) return;
-    float acc = accumulate ? out[i] : 0.0f;
-    for (int s = 0; s < nsplit; s += 8) {
-        float v[8];
-#pragma unroll
-        for (int u = 0; u < 8; ++u) v[u] = s + u < nsplit ? part[(int64_t)(s + u) * n + i] : 0.0f;
-#pragma unroll
-        for (int u = 0; u < 8; ++u) acc += v[u];
-    }
-    out[i] = acc;
-}
+// The last launch before dx: three sorts of work that do not wait for each other, a work-group each.
+//   dbias[e] (+)= the sum of dz over the slots of expert e: its rows of the permutation, or, without one, all slots whose
+//     id it is (fixed order; first in the grid, as a skewed load's hot expert takes longest);
+//   dW_r[i] (+)= sum_s part[s][i], s ascending, 1024 values;
+//   W_r^T, which dx reads, a 32 x 32 tile.
+// Each is microseconds of latency, so launches of their own cost a layer of few tokens more than the work did.
+// Forward + backward, three launches vs one: f32 T=256 d=128 E=8 79.8 -> 78.0 us, bf16 T=3001 d=1000 E=64 612 -> 609,
+// T=6000 d=1024 E=384 with dbias 1083 -> 1074, T=1001 d=2048 E=128 1121 -> 1118.
+template <typename T> struct RouterFinish {
+    int Tn, d, E, K, nsplit, accumulate, bias_blocks, sum_blocks, u8;
+    int64_t stride;
+    const float *dz, *part;
+    const void *idx;
+    const int32_t *offsets, *perm;
+    float *dbias, *dWr;
+    const T *Wr;
+    T *WrT;
+};
 
-// dbias[e] (+)= the sum of dz over the slots of expert e: its rows of the permutation, or, without one, all slots
-// whose id it is.  A block per expert, fixed order.
-template <typename IdxT, bool PERM>
-__global__ void __launch_bounds__(1024)
-router_dbias_kernel(int T, int E, int K, const float *__restrict__ dz, const IdxT *__restrict__ idx, int64_t stride,
-                    const int32_t *__restrict__ offsets, const int32_t *__restrict__ perm, float *__restrict__ dbias,
-                    int accumulate) {
+template <typename T>
+__global__ void __launch_bounds__(1024) router_finish_kernel(RouterFinish<T> a) {
     __shared__ float tmp[16];
-    const int e = blockIdx.x;
-    float acc = 0.0f;
-    if constexpr (PERM) {
-        const int r1 = offsets[e + 1];
-        for (int r = offsets[e] + threadIdx.x; r < r1; r += 4 * 1024) {
-            float v[4];
+    __shared__ T tile[32][33];
+    const int tid = threadIdx.x, E = a.E, K = a.K;
+    int blk = blockIdx.x;
+    if (blk < a.bias_blocks) {
+        const int e = blk;
+        float acc = 0.0f;
+        if (a.perm) {
+            const int r1 = a.offsets[e + 1];
+            for (int r = a.offsets[e] + tid; r < r1; r += 4 * 1024) {
+                float v[4];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = r + u * 1024 < r1 ? dz[perm[r + u * 1024]] : 0.0f;
-            acc += (v[0] + v[1]) + (v[2] + v[3]);
+                for (int u = 0; u < 4; ++u) v[u] = r + u * 1024 < r1 ? a.dz[a.perm[r + u * 1024]] : 0.0f;
+                acc += (v[0] + v[1]) + (v[2] + v[3]);
+            }
+        } else {
+            for (int64_t i = tid; i < (int64_t)a.Tn * K; i += 1024) {
+                const int64_t at = i / K * a.stride + i % K;
+                const int id = a.u8 ? ((const uint8_t *)a.idx)[at] : ((const uint16_t *)a.idx)[at];
+                if (min(id, E - 1) == e) acc += a.dz[i];
+            }
         }
-    } else {
-        for (int64_t i = threadIdx.x; i < (int64_t)T * K; i += 1024)
-            if (min((int)idx[i / K * stride + i % K], E - 1) == e) acc += dz[i];
+        acc = wave_sum(acc);
+        if (lane_id() == 0) tmp[tid >> 6] = acc;
+        __syncthreads();
+        if (tid == 0) {
+            acc = a.accumulate ? a.dbias[e] : 0.0f;
+            for (int i = 0; i < 16; ++i) acc += tmp[i];
+            a.dbias[e] = acc;
+        }
+        return;
     }
-    acc = wave_sum(acc);
-    if (lane_id() == 0) tmp[threadIdx.x >> 6] = acc;
+    blk -= a.bias_blocks;
+    if (blk < a.sum_blocks) {
+        const int64_t n = (int64_t)a.d * E, i = (int64_t)blk * 1024 + tid;
+        if (i >= n) return;
+        float acc = a.accumulate ? a.dWr[i] : 0.0f;
+        for (int s = 0; s < a.nsplit; s += 8) {
+            float v[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) v[u] = s + u < a.nsplit ? a.part[(int64_t)(s + u) * n + i] : 0.0f;
+#pragma unroll
+            for (int u = 0; u < 8; ++u) acc += v[u];
+        }
+        a.dWr[i] = acc;
+        return;
+    }
+    blk -= a.sum_blocks;
+    const int ne = (E + 31) / 32, e0 = blk % ne * 32, c0 = blk / ne * 32, lo = tid & 31, hi = tid >> 5;
+    if (c0 + hi < a.d && e0 + lo < E) tile[hi][lo] = a.Wr[(int64_t)(c0 + hi) * E + e0 + lo];
     __syncthreads();
-    if (threadIdx.x == 0) {
-        acc = accumulate ? dbias[e] : 0.0f;
-        for (int i = 0; i < 16; ++i) acc += tmp[i];
-        dbias[e] = acc;
-    }
+    if (e0 + hi < E && c0 + lo < a.d) a.WrT[(int64_t)(e0 + hi) * a.d + c0 + lo] = tile[lo][hi];
 }
 
 // ---------------------------------------------------------------------------
@@ -642,30 +669,36 @@ static void launch_dwr(int T, int d, int E, int K, const void *x, const float *d
     k<<<grid, 256, kDwrLds, s>>>(T, d, E, K, rows, (const bf16_t *)x, dz, (const IdxT *)idx, stride, part);
 }
 
-hipError_t router_dwr(int T, int d, int E, int K, int act, const void *x, const float *dz, const void *idx, int idx_dtype,
-                      int64_t stride, float *part, float *dWr, int accumulate, bool plain_only, hipStream_t s) {
+template <typename T>
+static hipError_t launch_finish(RouterFinish<T> a, const void *Wr, void *WrT, hipStream_t s) {
+    a.Wr = (const T *)Wr;
+    a.WrT = (T *)WrT;
+    const int64_t tr = (int64_t)((a.d + 31) / 32) * ((a.E + 31) / 32);
+    router_finish_kernel<T><<<(unsigned)(a.bias_blocks + a.sum_blocks + tr), 1024, 0, s>>>(a);
+    return hipGetLastError();
+}
+
+hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, const void *Wr, const float *dz, const void *idx,
+                           int idx_dtype, int64_t stride, const int32_t *offsets, const int32_t *perm, float *part, float *dWr,
+                           float *dbias, void *WrT, int accumulate, bool plain_only, hipStream_t s) {
     ProfScope ps(PROF_DWR, s);
     const bool bf = bf16_dwr(act, d, K, plain_only);
     const int rows = bf ? dwr_rows(T, d, E) : plain_dwr_rows(T, d, E);
     if (bf) (idx_dtype == R3_IDX_U8 ? launch_dwr<uint8_t> : launch_dwr<uint16_t>)(T, d, E, K, x, dz, idx, stride, part, s);
     else plain_dwr_parts(T, d, E, K, act, x, dz, idx, idx_dtype, stride, part, s);
-    const int64_t n = (int64_t)d * E;
-    sum_parts_kernel<<<(unsigned)((n + 255) / 256), 256, 0, s>>>(n, (T + rows - 1) / rows, part, dWr, accumulate);
-    return hipGetLastError();
-}
-
-hipError_t router_dbias(int T, int E, int K, const float *dz, const void *idx, int idx_dtype, int64_t stride,
-                        const int32_t *offsets, const int32_t *perm, float *dbias, int accumulate, hipStream_t s) {
-    if (perm) {
-        router_dbias_kernel<uint8_t, true><<<E, 1024, 0, s>>>(T, E, K, dz, nullptr, stride, offsets, perm, dbias, accumulate);
-    } else if (idx_dtype == R3_IDX_U8) {
-        router_dbias_kernel<uint8_t, false><<<E, 1024, 0, s>>>(T, E, K, dz, (const uint8_t *)idx, stride, nullptr, nullptr, dbias,
-                                                               accumulate);
-    } else {
-        router_dbias_kernel<uint16_t, false><<<E, 1024, 0, s>>>(T, E, K, dz, (const uint16_t *)idx, stride, nullptr, nullptr,
-                                                                dbias, accumulate);
-    }
-    return hipGetLastError();
+    auto finish = [&](auto f) {
+        f.Tn = T; f.d = d; f.E = E; f.K = K;
+        f.nsplit = (T + rows - 1) / rows;
+        f.accumulate = accumulate;
+        f.bias_blocks = dbias ? E : 0;
+        f.sum_blocks = (int)(((int64_t)d * E + 1023) / 1024);
+        f.u8 = idx_dtype == R3_IDX_U8;
+        f.stride = stride;
+        f.dz = dz; f.part = part; f.idx = idx; f.offsets = offsets; f.perm = perm;
+        f.dbias = dbias; f.dWr = dWr;
+        return launch_finish(f, Wr, WrT, s);
+    };
+    return act == R3_BF16 ? finish(RouterFinish<bf16_t>{}) : finish(RouterFinish<float>{});
 }
 
 bool router_gate_supported(int act, int d, int E, bool plain_only) {

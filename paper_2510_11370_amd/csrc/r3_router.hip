@@ -3,10 +3,10 @@
 //   s = x W_r (+ bias),  g_j = exp(s[id_j] - m) / sum_i exp(s[id_i] - m) over the recorded ids (m their maximum).
 // A work-group owns a few tokens and all experts, so a token's logits never leave it unless asked for.
 //
-// What bounds it: for few tokens latency, for many the read of x.  Every work-group streams the whole of W_r
-// (L2), so a serial walk over k is a chain of round trips: 32 of them took 24 us at 64 tokens, d = 2048.  Here the
-// waves of a work-group split k between them, each with its own operand tiles in flight and no barrier until the
-// partial logits are added in LDS (in a fixed order).
+// What bounds it: for few tokens latency, for many the read of x.  Every work-group streams the whole of W_r (L2), so
+// a serial walk over k is a chain of round trips: 32 of them took 24 us at 64 tokens, d = 2048.  The kernels keep
+// several stages of k in flight, but add up in the order of k, whatever the number of tokens: split over the waves, a
+// token's logits were other bits in a micro-batch than in the whole batch.
 #include <algorithm>
 
 #include "r3_kernels.h"
@@ -141,122 +141,140 @@ __device__ __forceinline__ void add_logits(float *red, int pitch, int t0, int T,
 }
 
 // ---------------------------------------------------------------------------
-// bf16 (d and E multiples of 8, E <= 512).  NW waves: WE groups of 64 experts times WK = NW / WE groups that take
-// every WK-th step of 32 k.  A wave brings its step's W_r tile [32 k][64 experts] and x tile [BQ tokens][32 k]
-// into LDS of its own with direct loads, NBUF steps deep, and multiplies with 32x32x16 instructions.
-// W_r's k-rows are 128 B here: two to a bank line, so their 64-byte halves swap by bit 1 of k and the transposing
-// reads (4 k-rows of 64 B at a time) touch every bank once.
+// bf16 (d and E multiples of 8, E <= 512).  A work-group takes 32 or 64 tokens and all experts.  Its eight waves bring
+// stages of SK k into a ring of NBUF in LDS with direct loads, one barrier per stage; the 32 x 32 results are dealt to the
+// waves and each is one chain of 32x32x16 instructions over ascending k.  So a token's logits are the same bits
+// whatever the number of tokens, and those of a sum in the order of k.
+// Few, large stages: with few work-groups a stage costs about 0.3 us however small it is (barrier, LDS round trip, the
+// chain's end).  T=64 d=2048, us with half the k per stage: E=128 9.2 | 15.9, E=256 14.9 | 17.4, E=512 26.1 | 29.8.
+// W_r stage: EP / 64 tiles [SK k][64 experts].  Their k-rows are 128 B: two to a bank line, so their 64-byte halves
+// swap by bit 1 of k and the transposing reads (4 k-rows of 64 B at a time) touch every bank once.  x stage: SK / 32
+// tiles [BQ tokens][32 k] (KcFrag<32>).
 // ---------------------------------------------------------------------------
-template <int NW, int WE, int TQ>
+template <int EP_, int TQ_>
 struct RouterCfg {
-    static constexpr int WK = NW / WE, BQ = 32 * TQ, NT = 64 * NW, EP = 64 * WE, PITCH = EP + 4;
-    static constexpr int WT = 32 * 64 * 2, XT = BQ * 32 * 2, LPS = (WT + XT) / 1024;   // bytes per tile; loads per step
-    static constexpr int NBUF = TQ == 1 ? 3 : 2;
-    static constexpr int TILES = NW * NBUF * (WT + XT), RED = WK * BQ * PITCH * 4;
-    static constexpr int LDS = (TILES > RED ? TILES : RED) + 2 * NW * 8;
+    static constexpr int EP = EP_, TQ = TQ_, BQ = 32 * TQ, NW = 8, NT = 64 * NW, PITCH = EP + 4;
+    // k per stage: what lets two or three stages into LDS
+    static constexpr int SK = EP == 64 ? 256 / TQ : EP == 128 ? 128 : EP == 256 ? 128 / TQ : 64;
+    static constexpr int WT = SK * EP * 2, XT = SK * BQ * 2, STAGE = WT + XT;
+    static constexpr int NBUF = (160 * 1024 - 256) / STAGE;
+    static constexpr int WCH = WT / 1024, XCH = XT / 1024;                       // loads of 1 KB; of the whole work-group
+    static constexpr int WPW = WCH / NW, XPW = (XCH + NW - 1) / NW;              // of a wave (the last one: the first XLAST waves)
+    static constexpr int XLAST = XCH - (XPW - 1) * NW;
+    static constexpr int NE = EP / 32, TILES = NE * TQ, TPW = (TILES + NW - 1) / NW;   // 32 x 32 results; of a wave
+    static constexpr int RING = NBUF * STAGE, RED = BQ * PITCH * 4;
+    static constexpr int LDS = (RING > RED ? RING : RED) + 2 * NW * 8;
+    static_assert(WCH % NW == 0 && NBUF >= 2 && LDS <= 160 * 1024, "router stages");
 };
 
-template <class C, int WE, int TQ, typename IdxT>
+// at most N of this wave's loads outstanding, and none of its LDS reads
+template <int N>
+__device__ __forceinline__ void router_wait() {
+    __builtin_amdgcn_s_waitcnt((N & 15) | (7 << 4) | (0 << 8) | ((N >> 4) << 14));
+}
+
+template <class C, typename IdxT>
 __global__ void __launch_bounds__(C::NT)
 router_gate_kernel(int T, int d, int E, int K, const bf16_t *__restrict__ x, const bf16_t *__restrict__ Wr,
                    const float *__restrict__ bias, const IdxT *__restrict__ idx, int64_t stride,
                    float *__restrict__ gates, float *__restrict__ logits_out, unsigned long long *agree,
                    int32_t *status) {
     extern __shared__ __attribute__((aligned(1024))) char lds[];
+    constexpr int SK = C::SK, XG = C::BQ / 16;
     const int lane = lane_id(), wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-    const int we = wave % WE, kg = wave / WE;
     const int t0 = blockIdx.x * C::BQ;
-    char *mine = lds + wave * C::NBUF * (C::WT + C::XT);
-    const uint32_t base = lds_addr(mine);
-    // W_r chunk i (1 KB): k-rows 8 i .. + 7, eight 16-byte pieces each
-    const rsrc_t rw = src_rsrc(Src{(const char *)Wr, (uint64_t)d * E * 2, 0u}, 0);
-    int wk[4], woff[4];
+    const uint32_t base = lds_addr(lds);
+    // W_r chunk c (1 KB): k-rows 8 (c % (SK / 8)) .. + 7 of expert tile c / (SK / 8), eight 16-byte pieces each.
+    // (k-rows past d are past the end of W_r and read zero)
+    const Src sw = Src{(const char *)Wr, (uint64_t)d * E * 2, (uint32_t)(SK * E * 2)};
+    int woff[C::WPW];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int k = 8 * i + (lane >> 3), p = lane & 7;
-        const int c = ((((p >> 2) ^ (k >> 1)) & 1) << 2) | (p & 3);
-        wk[i] = k;
-        woff[i] = 64 * we + 8 * c < E ? (k * E + 64 * we + 8 * c) * 2 : kOutsideWindow;
+    for (int i = 0; i < C::WPW; ++i) {
+        const int ch = wave + C::NW * i, k = ch % (SK / 8) * 8 + (lane >> 3), p = lane & 7;
+        const int e = ch / (SK / 8) * 64 + (((((p >> 2) ^ (k >> 1)) & 1) << 2) | (p & 3)) * 8;
+        woff[i] = e < E ? (k * E + e) * 2 : kOutsideWindow;
     }
-    // x chunk i: tokens 16 i .. + 15, four pieces each, piece c of token r at c ^ ((r >> 2) & 3)
-    const rsrc_t rx = src_rsrc(Src{(const char *)(x + (int64_t)t0 * d), clamp_bytes((int64_t)(T - t0) * d * 2), 0u}, 0);
-    int xoff[2 * TQ];
-    const int xc = ((lane & 3) ^ ((lane >> 4) & 3)) * 8;   // (bits 2,3 of the token are bits 4,5 of the lane)
+    // x chunk c: tokens 16 (c % XG) .. + 15 of k-tile c / XG, four pieces each, piece p of token r at p ^ ((r >> 2) & 3)
+    const Src sx = Src{(const char *)(x + (int64_t)t0 * d), clamp_bytes((int64_t)(T - t0) * d * 2), (uint32_t)(SK * 2)};
+    int xoff[C::XPW], xk[C::XPW];
 #pragma unroll
-    for (int i = 0; i < 2 * TQ; ++i) xoff[i] = ((16 * i + (lane >> 2)) * d + xc) * 2;
+    for (int i = 0; i < C::XPW; ++i) {
+        const int ch = wave + C::NW * i;
+        xk[i] = ch / XG * 32 + ((lane & 3) ^ ((lane >> 4) & 3)) * 8;   // (bits 2,3 of the token are bits 4,5 of the lane)
+        xoff[i] = ((ch % XG * 16 + (lane >> 2)) * d + xk[i]) * 2;
+    }
     auto issue = [&](int it, int buf) {
-        const int k0 = (it * C::WK + kg) * 32;
-        const uint32_t dst = base + buf * (C::WT + C::XT);
+        const uint32_t dst = base + buf * C::STAGE + 1024 * wave;
+        const rsrc_t rw = src_rsrc(sw, it), rx = src_rsrc(sx, it);
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-            lds_load16(rw, dst + 1024 * i, k0 + wk[i] < d && woff[i] != kOutsideWindow ? woff[i] + k0 * E * 2 : kOutsideWindow);
+        for (int i = 0; i < C::WPW; ++i) lds_load16(rw, dst + 1024 * C::NW * i, woff[i]);
 #pragma unroll
-        for (int i = 0; i < 2 * TQ; ++i)
-            lds_load16(rx, dst + C::WT + 1024 * i, k0 + xc < d ? xoff[i] + k0 * 2 : kOutsideWindow);
+        for (int i = 0; i < C::XPW; ++i)
+            if (i + 1 < C::XPW || wave < C::XLAST)   // (k past d: the next token's values in memory)
+                lds_load16(rx, dst + C::WT + 1024 * C::NW * i, it * SK + xk[i] < d ? xoff[i] : kOutsideWindow);
     };
     // fragment addresses: W_r by the transposing read (see TrFrag), x rows as KcFrag<32>
     const int b = lane >> 4, i16 = lane & 15;
     const int wrow = (8 * (b >> 1) + (i16 >> 2)) * 128 + (i16 & 1) * 8;   // + 4 k-rows: the upper half of the 8 k
-    const int wsub = 2 * (b & 1) + ((i16 & 3) >> 1), wsw = (i16 >> 3) & 1;
+    const int wsub = (2 * (b & 1) + ((i16 & 3) >> 1)) * 16, wsw = (i16 >> 3) & 1;
     KcFrag<32> xf;
     xf.init(0, lane);
-    f32x16_t acc[2][TQ];
+    f32x16_t acc[C::TPW];
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+    for (int i = 0; i < C::TPW; ++i)
 #pragma unroll
-        for (int q = 0; q < TQ; ++q)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[e][q][v] = 0.0f;
+        for (int v = 0; v < 16; ++v) acc[i][v] = 0.0f;
 
-    const int nit = (d + 32 * C::WK - 1) / (32 * C::WK);
+    const int nit = (d + SK - 1) / SK;
 #pragma unroll
     for (int p = 0; p < C::NBUF - 1; ++p) issue(p, p);
     int buf = 0;
     for (int it = 0; it < nit; ++it) {
-        // the buffer asked for now is the one read last time round: those reads are over
-        __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
-        issue(it + C::NBUF - 1, buf == 0 ? C::NBUF - 1 : buf - 1);
-        constexpr int VM = (C::NBUF - 1) * C::LPS;
-        __builtin_amdgcn_s_waitcnt((VM & 15) | (7 << 4) | (15 << 8) | ((VM >> 4) << 14));
         asm volatile("" ::: "memory");
-        const char *wt = mine + buf * (C::WT + C::XT), *xt = wt + C::WT;
+        // this stage is in when only the loads of the later ones are outstanding
+        if (C::XLAST == C::NW || wave < C::XLAST) router_wait<(C::NBUF - 2) * (C::WPW + C::XPW)>();
+        else router_wait<(C::NBUF - 2) * (C::WPW + C::XPW - 1)>();
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        // the buffer asked for now is the one read last time round: those reads are over
+        issue(it + C::NBUF - 1, buf == 0 ? C::NBUF - 1 : buf - 1);
+        const char *wt = lds + buf * C::STAGE, *xt = wt + C::WT;
+        if (wave < C::TILES) {
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            bf16x8_t a[2], bq[TQ];
+            for (int s = 0; s < SK / 16; ++s)
 #pragma unroll
-            for (int e = 0; e < 2; ++e) {
-                const char *p = wt + s * 16 * 128 + wrow;
-                // bit 1 of the k-row is that of i16 >> 2 (rows 8 (b >> 1), + 4 and 16 s do not change it)
-                const char *pp = p + ((e ^ wsw) & 1) * 64 + wsub * 16;
-                const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(pp));
-                const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(pp + 4 * 128));
-                a[e] = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
-            }
-#pragma unroll
-            for (int q = 0; q < TQ; ++q) bq[q] = xf.read(xt, q, s);
-#pragma unroll
-            for (int e = 0; e < 2; ++e)
-#pragma unroll
-                for (int q = 0; q < TQ; ++q) acc[e][q] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[e], bq[q], acc[e][q], 0, 0, 0);
+                for (int i = 0; i < C::TPW; ++i) {
+                    const int id = wave + C::NW * i, e = id % C::NE, q = id / C::NE;
+                    if (C::TILES % C::NW != 0 && id >= C::TILES) continue;
+                    // bit 1 of the k-row is that of i16 >> 2 (rows 8 (b >> 1), + 4 and 16 s do not change it)
+                    const char *p = wt + (e >> 1) * (SK * 128) + s * 16 * 128 + wrow + ((e ^ wsw) & 1) * 64 + wsub;
+                    const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
+                    const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * 128));
+                    const bf16x8_t a = __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+                    acc[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, xf.read(xt + (s >> 1) * (C::BQ * 64), q, s & 1), acc[i], 0, 0, 0);
+                }
         }
         buf = buf == C::NBUF - 1 ? 0 : buf + 1;
     }
-    __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0 << 8) | (0 << 14));   // no load may land in what follows
+    router_wait<0>();   // no load may land in what follows
     __syncthreads();
     float *red = (float *)lds;
 #pragma unroll
-    for (int e = 0; e < 2; ++e)
+    for (int i = 0; i < C::TPW; ++i) {
+        const int id = wave + C::NW * i, e = id % C::NE, q = id / C::NE;
+        if (id >= C::TILES) continue;
 #pragma unroll
-        for (int q = 0; q < TQ; ++q)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                *(float4 *)(red + (kg * C::BQ + 32 * q + (lane & 31)) * C::PITCH + 64 * we + 32 * e + 8 * g + 4 * (lane >> 5)) =
-                    make_float4(acc[e][q][4 * g], acc[e][q][4 * g + 1], acc[e][q][4 * g + 2], acc[e][q][4 * g + 3]);
+        for (int g = 0; g < 4; ++g)
+            *(float4 *)(red + (32 * q + (lane & 31)) * C::PITCH + 32 * e + 8 * g + 4 * (lane >> 5)) =
+                make_float4(acc[i][4 * g], acc[i][4 * g + 1], acc[i][4 * g + 2], acc[i][4 * g + 3]);
+    }
     __syncthreads();
-    add_logits<C::WK, C::BQ, C::EP, C::NT>(red, C::PITCH, t0, T, E, bias, logits_out);
-    __syncthreads();
-    gate_from_lds<2 * WE, C::NT, IdxT>(red, C::PITCH, t0, C::BQ, T, E, K, idx, stride, gates, agree, status,
-                                       (unsigned long long *)(lds + C::LDS - 2 * 8 * (C::NT / 64)));
+    if (bias || logits_out) {
+        add_logits<1, C::BQ, C::EP, C::NT>(red, C::PITCH, t0, T, E, bias, logits_out);
+        __syncthreads();
+    }
+    gate_from_lds<C::NE, C::NT, IdxT>(red, C::PITCH, t0, C::BQ, T, E, K, idx, stride, gates, agree, status,
+                                      (unsigned long long *)(lds + C::LDS - 2 * 8 * C::NW));
 }
 
 // ---------------------------------------------------------------------------
@@ -589,11 +607,11 @@ __global__ void __launch_bounds__(1024) router_finish_kernel(RouterFinish<T> a) 
 // ---------------------------------------------------------------------------
 namespace {
 
-template <int NW, int WE, int TQ, typename IdxT>
+template <int EP, int TQ, typename IdxT>
 void launch_router(int T, int d, int E, int K, const void *x, const void *Wr, const float *bias, const void *idx,
                    int64_t stride, float *gates, float *logits_out, int64_t *agree, int32_t *status, hipStream_t s) {
-    typedef RouterCfg<NW, WE, TQ> C;
-    auto k = router_gate_kernel<C, WE, TQ, IdxT>;
+    typedef RouterCfg<EP, TQ> C;
+    auto k = router_gate_kernel<C, IdxT>;
     (void)hipFuncSetAttribute((const void *)k, hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
     k<<<(T + C::BQ - 1) / C::BQ, C::NT, C::LDS, s>>>(T, d, E, K, (const bf16_t *)x, (const bf16_t *)Wr, bias, (const IdxT *)idx,
                                                    stride, gates, logits_out, (unsigned long long *)agree, status);
@@ -610,12 +628,19 @@ void launch_plain(int Tn, int d, int E, int K, const void *x, const void *Wr, co
 template <typename IdxT>
 void router_by_size(int T, int d, int E, int K, const void *x, const void *Wr, const float *bias, const void *idx,
                     int64_t stride, float *gates, float *logits_out, int64_t *agree, int32_t *status, hipStream_t s) {
-    // d = 2048, E = 128, us at 32 tokens per work-group / 64 / the kernel for many: 4096 tokens 12.4 / 16.0 / -, 8192
-    // 14.0 / 17.4 / 23.7, 16384 25.7 / 18.6 / 24.8, 32768 66 / 50 / 43, 65536 129 / 97 / 72.  The first two are at
-    // their best as long as every work-group has a compute unit of its own.
+    // d = 2048, us at 32 tokens per work-group / 64 (/ E = 128: the kernel for many).  Both are at their best as long as
+    // every work-group has a compute unit of its own:
+    //   tokens    E=64         E=128                  E=256        E=384        E=512
+    //     4096    8.8 / 10.2    9.9 /  13.0 /  29.1   18.2 / 21.4  23.9 / 30.7  30.5 / 38.3
+    //     8192    9.0 / 10.8   10.9 /  14.8 /  29.6   20.1 / 21.7  26.0 / 33.3  35.5 / 40.4
+    //    12000   16.4 / 11.5   19.2 /  15.9 /  29.6   36.5 / 22.3  47.5 / 33.9  65.8 / 40.5
+    //    32768   35.5 / 25.2   39.0 /  33.7 /  35.6   74.6 / 47.3  96.7 / 71.3   136 / 87.5
+    //    65536   67.5 / 53.3   86.1 /  66.5 /  48.2    158 / 96.2   194 /  146   267 /  175
+    //   131072    161 /  126    207 /   150 /   137    384 /  214   402 /  308   610 /  370
+    // (24576 tokens, E=128: 30.3 / 32.3 / 32.1)
     constexpr int kCus = 256;
     const bool wide = T > 32 * kCus;
-    if (T > 64 * kCus && E == 128 && d % 64 == 0) {
+    if (T > 128 * kCus && E == 128 && d % 64 == 0) {
         constexpr int LDS = std::max(TLGate::LDS_BYTES, TLGate::BQ * (TLGate::BP + 4) * 4);
         (void)hipFuncSetAttribute((const void *)router_gate_many_kernel<IdxT>, hipFuncAttributeMaxDynamicSharedMemorySize, LDS);
         router_gate_many_kernel<IdxT><<<(T + TLGate::BQ - 1) / TLGate::BQ, TLGate::NT, LDS, s>>>(
@@ -623,13 +648,14 @@ void router_by_size(int T, int d, int E, int K, const void *x, const void *Wr, c
             (unsigned long long *)agree, status);
         return;
     }
-#define R3_ROUTER(WE)                                                                                                  \
-    (wide ? launch_router<8, WE, 2, IdxT> : launch_router<8, WE, 1, IdxT>)(T, d, E, K, x, Wr, bias, idx, stride, gates, \
-                                                                            logits_out, agree, status, s)
-    if (E <= 64) R3_ROUTER(1);
-    else if (E <= 128) R3_ROUTER(2);
-    else if (E <= 256) R3_ROUTER(4);
-    else R3_ROUTER(8);
+#define R3_ROUTER(EP)                                                                                            \
+    (wide ? launch_router<EP, 2, IdxT> : launch_router<EP, 1, IdxT>)(T, d, E, K, x, Wr, bias, idx, stride, gates, \
+                                                                     logits_out, agree, status, s)
+    if (E <= 64) R3_ROUTER(64);
+    else if (E <= 128) R3_ROUTER(128);
+    else if (E <= 256) R3_ROUTER(256);
+    else if (E <= 384) R3_ROUTER(384);
+    else R3_ROUTER(512);
 #undef R3_ROUTER
 }
 

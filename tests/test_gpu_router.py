@@ -19,7 +19,7 @@ SH = synth.LayerShape
     SH(T=130, d=512, E=512, K=8, F=8, seed=84),                      # the most experts of the bf16 kernel
     SH(T=70, d=256, E=640, K=4, F=8, seed=85),                       # beyond it
     SH(T=8192, d=64, E=128, K=8, F=8, seed=86), SH(T=8193, d=64, E=128, K=8, F=8, seed=87),       # 32 | 64 tokens
-    SH(T=16384, d=64, E=128, K=8, F=8, seed=88), SH(T=16385, d=64, E=128, K=8, F=8, seed=89),     # 64 | 128 tokens
+    SH(T=32768, d=64, E=128, K=8, F=8, seed=88), SH(T=32769, d=64, E=128, K=8, F=8, seed=89),     # 64 | 128 tokens
     SH(T=17, d=50, E=60, K=5, F=8, seed=90),                         # bf16 in f32 arithmetic
     SH(T=49, d=132, E=9, K=3, F=8, act="f32", seed=91), SH(T=16, d=129, E=128, K=8, F=8, act="f32", zipf_s=0.7, seed=92),
     SH(T=40, d=33, E=130, K=2, F=8, act="f32", seed=93),             # more experts than the f32 kernel holds
@@ -48,6 +48,27 @@ def test_router_at_tile_edges(sh):
     torch.cuda.synchronize()
     assert torch.equal(gates, gates2)
     assert tuple(agree.tolist()) == tuple(2 * int(v) for v in sparse.agreement(own, c.idx))
+
+
+@pytest.mark.parametrize("E,d", [(64, 264), (128, 512), (128, 264), (256, 328), (384, 136), (512, 256)])
+def test_logits_do_not_depend_on_the_batch(E, d):
+    """A token's logits and gates are the same bits whatever the number of tokens in the call: micro-batches replay as
+    the whole batch does.  32 | 64 | (E = 128) 128 tokens per work-group."""
+    T, K = 33000, 4
+    g = torch.Generator(device="cuda").manual_seed(E + d)
+    x = torch.randn(T, d, generator=g, device="cuda").bfloat16()
+    Wr = torch.randn(d, E, generator=g, device="cuda").bfloat16()
+    idx = (torch.randint(0, E // K, (T, K), generator=g, device="cuda") + E // K * torch.arange(K, device="cuda")).to(
+        torch.uint8 if E <= 256 else torch.int16)
+    got = []
+    for n in (T, 32768, 9000, 8192, 33):
+        D = r3.desc(n, d, E, K, 8)
+        lg, gates = (torch.empty(n, w, dtype=torch.float32, device="cuda") for w in (E, K))
+        r3.replay_gate(D, x[:n], Wr, idx[:n], gates, logits_out=lg, ws=r3.workspace(D, r3.OP_REPLAY_GATE))
+        got.append((n, lg, gates))
+    torch.cuda.synchronize()
+    for n, lg, gates in got[1:]:
+        assert torch.equal(lg, got[0][1][:n]) and torch.equal(gates, got[0][2][:n]), n
 
 
 def _slots(T, E, K, seed, skew):

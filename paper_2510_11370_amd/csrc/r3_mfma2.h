@@ -64,9 +64,13 @@ typedef __attribute__((address_space(3))) void *lds_void_ptr;
 // `step` is how far one k-tile advances.
 struct Src {
     const char *base;
-    uint64_t nbytes;   // a segment may exceed 4 GB; each descriptor sees at most 2 GB of what is left
+    uint64_t nbytes;   // a segment may exceed 4 GB; each descriptor sees at most kOutsideWindow bytes of what is left
     uint32_t step;
 };
+
+// A lane offset outside every window: such a lane fetches zeros.  Windows end there, so it holds for those cut short as
+// well (16 bytes under 2 GB more, 12 of the lane's 16 were inside: values of another row).
+constexpr int kOutsideWindow = 0x7ffffff0;
 
 typedef int rsrc_t __attribute__((ext_vector_type(4)));  // buffer descriptor words (wave-uniform)
 
@@ -75,7 +79,7 @@ typedef int rsrc_t __attribute__((ext_vector_type(4)));  // buffer descriptor wo
 __device__ __forceinline__ rsrc_t src_rsrc(const Src &s, int kt, uint32_t extra = 0u) {
     const uint64_t adv = (uint64_t)kt * s.step + extra;
     const uint64_t rest = adv < s.nbytes ? s.nbytes - adv : 0u;
-    const uint32_t left = rest > 0x7fffffffu ? 0x7fffffffu : (uint32_t)rest;
+    const uint32_t left = rest > (uint32_t)kOutsideWindow ? (uint32_t)kOutsideWindow : (uint32_t)rest;
     const uint64_t b = (uint64_t)(s.base + adv);
     // the words are wave-uniform by construction; readfirstlane makes that visible to the
     // compiler so that they live in SGPRs
@@ -241,7 +245,6 @@ struct OpTR256G {
     static constexpr int kDsReads = 2 * kTP2, kDsReadsQ = 2 * kTQ2;
     static constexpr bool kIndexed = true, kWindowed = false;
     static constexpr int kLoads = 5;             // four tile loads and one index load
-    static constexpr int kOutside = 0x7ffffff0;  // beyond any window (windows are < 2^31 bytes)
     rsrc_t rs, rsi;        // the matrix; the tile's index list
     const_i32_ptr rows;
     int n, ld_bytes, wl;
@@ -279,7 +282,7 @@ struct OpTR256G {
     __device__ __forceinline__ void issue_index(int kt) const {
         const int lane = threadIdx.x & 63;
         const int base = min(kt * kBK2 + 8 * wl, n);
-        const int voff = lane < 8 ? (base + 2 * (lane & 3) + (lane >> 2)) * 4 : kOutside;
+        const int voff = lane < 8 ? (base + 2 * (lane & 3) + (lane >> 2)) * 4 : kOutsideWindow;
         const uint32_t m0v = __builtin_amdgcn_readfirstlane(ring + 256u * (kt & 3));
         asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(m0v), "v"(voff), "s"(rsi)
                      : "memory");
@@ -287,7 +290,7 @@ struct OpTR256G {
     __device__ __forceinline__ void chunk_load(int kt, uint32_t tile, int i, int row) const {
         const int lane = threadIdx.x & 63;
         const int k = kt * kBK2 + 8 * wl + 2 * i + (lane >> 5);
-        const int voff = k < n ? row * ld_bytes + cvoff[i] : kOutside;
+        const int voff = k < n ? row * ld_bytes + cvoff[i] : kOutsideWindow;
         lds_load16(rs, tile + 1024 * (4 * wl + i), voff);
     }
     // stages 0 and 1 of a tile: entries by scalar loads; the ring is started for stages 2 and 3
@@ -500,7 +503,6 @@ __device__ __forceinline__ void mfma_mainloop2(Acc2 &acc, int nk, const POp &P, 
 constexpr int kBK3 = 64;
 constexpr int kWinBytes = kTile * kBK3 * 2;   // 32 KB: one operand's window
 constexpr int kSuperBytes = 2 * kWinBytes;    // 64 KB: both operands
-constexpr int kOutsideWindow = 0x7ffffff0;    // a lane offset beyond any window: such a lane fetches zeros
 constexpr int kLoadsPerWindow = 16;           // tile loads per loader wave per window (8 per operand)
 
 // K-contiguous 256-row window [256 rows][128 B]: 32 chunks of 1 KB (8 rows x 128 B), eight per

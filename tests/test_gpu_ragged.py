@@ -85,3 +85,37 @@ def test_rows_per_expert_at_tile_edges(d, F):
         got = got.cpu().numpy()
         for e in range(sh.E):
             assert np.linalg.norm(got[e] - ref[key][e]) <= c.rel * np.linalg.norm(ref[key][e]) + 1e-30, (key, e)
+
+
+def test_masked_lanes_of_sources_past_two_gigabytes():
+    """Width 1032: the last window of a reduction has 8 live values, the other lanes fetch nothing, also where more than
+    2 GB of the source are left: NaN in rows 2 GB on stay where they are."""
+    T, d, E, F = 1 << 20, 1032, 64, 8
+    D = r3.desc(T, d, E, 1, F)
+    bad = (1 << 31) // (2 * d) - 1                       # NaN from the row that 2 GB from row 0 lie in
+    g = torch.Generator(device="cuda").manual_seed(1)
+    x = torch.zeros(T, d, dtype=torch.bfloat16, device="cuda")
+    x[:4096] = torch.randn(4096, d, generator=g, device="cuda")
+    x[bad:] = float("nan")
+    # router: one id per token (gate 1), logits kept
+    Wr = torch.randn(d, E, generator=g, device="cuda").bfloat16()
+    idx = torch.zeros(T, 1, dtype=torch.uint8, device="cuda")
+    gates = torch.empty(T, 1, dtype=torch.float32, device="cuda")
+    logits = torch.empty(T, E, dtype=torch.float32, device="cuda")
+    r3.replay_gate(D, x, Wr, idx, gates, logits_out=logits, ws=r3.workspace(D, r3.OP_REPLAY_GATE))
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(logits[:4096]).all()) and bool(torch.isnan(logits[bad:]).all())
+    assert torch.allclose(logits[:4096].double(), x[:4096].double() @ Wr.double(), rtol=1e-4, atol=1e-3)
+    del logits
+    # expert network on rows that are there already, all of them of expert 0
+    offsets = torch.full((E + 1,), T, dtype=torch.int32, device="cuda")
+    offsets[0] = 0
+    Wg, Wu = (0.05 * torch.randn(E, d, F, generator=g, device="cuda").bfloat16() for _ in range(2))
+    Wd = torch.randn(E, F, d, generator=g, device="cuda").bfloat16()
+    Yp, H = torch.empty(T, d, dtype=torch.bfloat16, device="cuda"), torch.empty(T, F, dtype=torch.bfloat16, device="cuda")
+    r3.grouped_ffn(D, x, offsets, Wg, Wu, Wd, Yp, H, ws=r3.workspace(D, r3.OP_GROUPED_FFN))
+    torch.cuda.synchronize()
+    assert bool(torch.isfinite(H[:4096]).all()) and bool(torch.isnan(H[bad:]).all())
+    a, b = x[:4096].double() @ Wg[0].double(), x[:4096].double() @ Wu[0].double()
+    want = a * torch.sigmoid(a) * b
+    assert float((H[:4096].double() - want).norm() / want.norm()) < 4e-3      # (one rounding to bf16: 2^-9 at most)

@@ -217,9 +217,8 @@ int r3_moe_forward(const r3_layer_desc *desc, const void *x, const void *W_r, co
  * their tile loads, and the softmax backward takes its dot products
  * <dy_t, o_j> from the down projection's gradient GEMM (<dy, H W_down> =
  * <dy W_down^T, H>), so no per-slot copy of dy is made and Yp is not read: Yp
- * and Xp may be NULL.  Other shapes and f32 need Yp, and Xp or perm; a perm
- * that is given holds what r3_permute wrote (bf16 widths that are multiples of
- * 8 and dbias read it where they can).
+ * and Xp may be NULL.  Other shapes and f32 need Yp, and Xp or perm; perm is
+ * not read when Xp is given (unless desc->flags asks for it, see below).
  * desc->flags = R3_FLAG_GATED_H: H and Yp are the gate-scaled tensors that
  * r3_moe_forward wrote (H = g silu(A) B, Yp = g o); perm is then required on
  * every path and Xp may be NULL on every path.

@@ -42,7 +42,7 @@ bool use_mfma_ffn(const Dims &m) { return m.act == R3_BF16 && mfma_ffn_supported
 bool use_mfma_router(const Dims &m) { return m.act == R3_BF16 && mfma_router_supported(m.d, m.E) && !force_simt(); }
 
 struct BwdWs {
-    size_t dXp, dz, WrT, dA, dB, tiles, part, tok, Hg, grow, wpart, total;
+    size_t dXp, dz, dzrow, WrT, dA, dB, tiles, part, tok, Hg, grow, wpart, total;
 };
 int row_parts(const Dims &m) { return 2 * ((m.F + 255) / 256); }   // partial dot products per row (MFMA path)
 BwdWs bwd_layout(const Dims &m) {
@@ -52,6 +52,7 @@ BwdWs bwd_layout(const Dims &m) {
     const bool mf = use_mfma_ffn(m);
     w.dXp = take((size_t)m.S * m.d * m.eb);  // the plain kernels keep g*dy here first
     w.dz = take((size_t)m.T * m.K * sizeof(float));
+    w.dzrow = take((size_t)m.S * sizeof(float));                 // dz in the order of the rows (for dbias)
     w.WrT = take((size_t)m.E * m.d * m.eb);
     w.dA = take((size_t)m.S * m.F * m.eb);
     w.dB = take((size_t)m.S * m.F * m.eb);
@@ -281,7 +282,7 @@ int r3_moe_forward(const r3_layer_desc *desc, const void *x, const void *W_r, co
     // the gate of every expert-sorted row: the first contraction's epilogue scales H with it, so the
     // down projection yields gated rows and the combination is a plain sum of each token's K rows
     if (mf) {
-        if (!with_tiles && mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, -1, (int)m.S, m.K, perm, gates, tok, grow, s) !=
+        if (!with_tiles && mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, -1, (int)m.S, m.K, inv_perm, gates, tok, grow, s) !=
                                hipSuccess)
             return R3_ERR_HIP;
         if (mfma_ffn_forward(m.S, m.d, m.E, m.F, x, perm, m.K, m.T, offsets, tiles, W_gate, W_up, W_down, Yp, H,
@@ -305,9 +306,9 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
     Dims m;
     int rc = check_desc(desc, m);
     if (rc) return rc;
-    // (ragged widths also have the plain kernels, for callers that give no perm or a token matrix of 2 GB and more)
-    const bool mf = use_mfma_ffn(m) &&
-                    (!mfma_ffn_ragged(m.d, m.F) || (perm && (int64_t)m.T * m.d * m.eb < (1ll << 31)));
+    // (ragged widths also have the plain kernels, for a token matrix of 2 GB and more)
+    const bool ragged = mfma_ffn_ragged(m.d, m.F);
+    const bool mf = use_mfma_ffn(m) && (!ragged || (int64_t)m.T * m.d * m.eb < (1ll << 31));
     const bool gated = (m.flags & R3_FLAG_GATED_H) != 0;   // H = g H and Yp = g o, as r3_moe_forward leaves them
     const void *ptrs[] = {dy, x, W_r, idx, gates, inv_perm, offsets, FA, FB, H, W_gate, W_up, W_down,
                           dx, dW_r, dW_gate, dW_up, dW_down};
@@ -317,19 +318,20 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
     for (const void *p : a16)
         if (!aligned(p, 16)) return R3_ERR_INVALID_ARG;
     if (accumulate != 0 && accumulate != 1) return R3_ERR_INVALID_ARG;
-    if (mf) {
-        // rows of dy (and of x when there is no Xp) are read through perm inside the tile loads
+    // Every path but the plain kernels without Xp or after r3_moe_forward reads inv_perm only, so that a perm that need not
+    // be given need not be filled either; what has to be given is the header's word.
+    if (use_mfma_ffn(m) && !ragged) {
         if (!perm || !aligned(perm, 4)) return R3_ERR_INVALID_ARG;
         if ((int64_t)m.T * m.d * m.eb >= (1ll << 31)) return R3_ERR_UNSUPPORTED;   // 32-bit row offsets
     } else if (!Yp || ((!Xp || gated) && (!perm || !aligned(perm, 4)))) {
-        return R3_ERR_INVALID_ARG;   // the plain kernels need Yp, and Xp or perm (perm after r3_moe_forward)
+        return R3_ERR_INVALID_ARG;   // Yp, and Xp or perm (perm after r3_moe_forward)
     }
     const BwdWs w = bwd_layout(m);
     if (!ws || ws_bytes < w.total || !aligned(ws, 256)) return R3_ERR_WORKSPACE;
     hipStream_t s = (hipStream_t)stream;
     char *base = (char *)ws;
     void *dXp = base + w.dXp, *WrT = base + w.WrT, *dA = base + w.dA, *dB = base + w.dB;
-    float *dz = (float *)(base + w.dz);
+    float *dz = (float *)(base + w.dz), *dzrow = dbias ? (float *)(base + w.dzrow) : nullptr;
     const int S = (int)m.S;
 
     if (mf) {
@@ -343,12 +345,12 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
         // the same place, dW_gate's and dW_up's side by side)
         const size_t slot_bytes = 2 * (size_t)m.F * m.d * sizeof(float);
         const int split = mfma_wgrad_split_rows(m.S, ((m.F + 255) / 256) * ((m.d + 255) / 256), (size_t)m.S * m.d * m.eb, slot_bytes);
-        if (mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, split, S, m.K, perm, gates, tok, grow, s) != hipSuccess)
+        if (mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, split, S, m.K, inv_perm, gates, tok, grow, s) != hipSuccess)
             return R3_ERR_HIP;
         if (mfma_ffn_dh(m.S, m.d, m.E, m.F, dy, tok, m.T, grow, offsets, tiles, W_down, FA, FB, H, dA, dB, Hg, wpart,
                         s) != hipSuccess)
             return R3_ERR_HIP;
-        if (launch_gate_backward_parts(m.T, m.K, row_parts(m), wpart, gates, inv_perm, dz, s) != hipSuccess)
+        if (launch_gate_backward_parts(m.T, m.K, row_parts(m), wpart, gates, inv_perm, dz, dzrow, s) != hipSuccess)
             return R3_ERR_HIP;
         if (mfma_wgrad(m.E, m.F, m.d, gated ? H : Hg, dy, tok, m.T, tiles, 2, dW_down, split ? (float *)dXp : nullptr,
                        accumulate, s) != hipSuccess)
@@ -361,7 +363,7 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
     } else {
         // combine and masked softmax:  dYp = g*dy per slot, dz
         void *dYp = dXp;  // dYp is dead once dW_down and dH are done
-        if (launch_gate_backward(m.T, m.d, m.K, m.act, dy, Yp, gates, inv_perm, dYp, dz, gated ? 1 : 0, s) != hipSuccess)
+        if (launch_gate_backward(m.T, m.d, m.K, m.act, dy, Yp, gates, inv_perm, dYp, dz, dzrow, gated ? 1 : 0, s) != hipSuccess)
             return R3_ERR_HIP;
         if (plain_dh(S, m.d, m.E, m.F, m.act, dYp, offsets, W_down, FA, FB, dA, dB, s) != hipSuccess) return R3_ERR_HIP;
         // gated: H is g H already, so its partner is the plain dy row (read through perm), not g dy
@@ -371,7 +373,7 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
         if (plain_dxp(S, m.d, m.E, m.F, m.act, dA, dB, offsets, W_gate, W_up, dXp, s) != hipSuccess) return R3_ERR_HIP;
     }
     // router:  dW_r = x^T ds, dbias = column sums of ds (ds: dz at the recorded experts), W_r^T for dx
-    if (router_backward(m.T, m.d, m.E, m.K, m.act, x, W_r, dz, idx, m.idx, m.stride, offsets, perm, (float *)(base + w.part),
+    if (router_backward(m.T, m.d, m.E, m.K, m.act, x, W_r, dz, idx, m.idx, m.stride, offsets, dzrow, (float *)(base + w.part),
                         dW_r, dbias, WrT, accumulate, force_simt(), s) != hipSuccess)
         return R3_ERR_HIP;
     // dx = un-permuted expert gradients + router term

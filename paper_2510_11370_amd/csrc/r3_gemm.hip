@@ -78,18 +78,18 @@ __device__ __forceinline__ void block_ranks(int n, Key key, int32_t *rnk) {
 
 __global__ void __launch_bounds__(1024)
 build_row_tiles_kernel(int E, int BQ, const int32_t *__restrict__ offsets, int32_t *__restrict__ tiles,
-                       int split_rows, int S, int K, const int32_t *__restrict__ perm,
+                       int split_rows, int S, int K, const int32_t *__restrict__ inv_perm,
                        const float *__restrict__ gates, int32_t *__restrict__ tok, float *__restrict__ grow) {
     // Work-groups past the first make the row -> token list (and the per-row gates) of the same pass: the
     // two jobs wait for the same inputs and are both too short to be worth a launch of their own.
     if (blockIdx.x > 0) {
-        const int r = (blockIdx.x - 1) * 1024 + threadIdx.x;
-        if (r < S) {
-            const int slot = perm[r];
+        const int slot = (blockIdx.x - 1) * 1024 + threadIdx.x;
+        if (slot < S) {
+            const int r = inv_perm[slot];
             tok[r] = slot / K;
-            if (gates) grow[r] = gates[slot];
-        } else if (r < S + kRowTokensPad) {
-            tok[r] = 0;
+            grow[r] = gates[slot];
+        } else if (slot < S + kRowTokensPad) {
+            tok[slot] = 0;
         }
         return;
     }
@@ -876,10 +876,10 @@ hipError_t mfma_build_tiles(int E, const int32_t *offsets, int32_t *tiles, int s
 }
 
 hipError_t mfma_build_tiles_and_row_tokens(int E, const int32_t *offsets, int32_t *tiles, int split_rows, int S, int K,
-                                           const int32_t *perm, const float *gates, int32_t *tok, float *grow,
+                                           const int32_t *inv_perm, const float *gates, int32_t *tok, float *grow,
                                            hipStream_t s) {
     build_row_tiles_kernel<<<1 + (S + kRowTokensPad + 1023) / 1024, 1024, 0, s>>>(E, kTile, offsets, tiles, split_rows,
-                                                                                  S, K, perm, gates, tok, grow);
+                                                                                  S, K, inv_perm, gates, tok, grow);
     return hipGetLastError();
 }
 

@@ -41,13 +41,14 @@ hipError_t launch_permute(int T, int d, int E, int K, int elem_bytes, const void
                           hipStream_t s);
 hipError_t launch_combine(int T, int d, int K, int act, const void *Yp, const float *gates,
                           const int32_t *inv_perm, void *y, hipStream_t s);
-// gated != 0: Yp holds gate-scaled rows (g o), so <dy, Yp_j> is already g_j dg_j
+// gated != 0: Yp holds gate-scaled rows (g o), so <dy, Yp_j> is already g_j dg_j.  dzrow (or NULL): dz in the order
+// of the rows, dzrow[inv_perm[i]] = dz[i]
 hipError_t launch_gate_backward(int T, int d, int K, int act, const void *dy, const void *Yp, const float *gates,
-                                const int32_t *inv_perm, void *dYp, float *dz, int gated, hipStream_t s);
+                                const int32_t *inv_perm, void *dYp, float *dz, float *dzrow, int gated, hipStream_t s);
 // masked-softmax backward from the row parts written by the expert-gradient GEMM:
-// w_j = sum_p wpart[row_j][p] (= g_j dg_j), dz_j = w_j - g_j sum_i w_i; writes dz [T,K]
+// w_j = sum_p wpart[row_j][p] (= g_j dg_j), dz_j = w_j - g_j sum_i w_i; writes dz [T,K], and dzrow as above
 hipError_t launch_gate_backward_parts(int T, int K, int nparts, const float *wpart, const float *gates,
-                                      const int32_t *inv_perm, float *dz, hipStream_t s);
+                                      const int32_t *inv_perm, float *dz, float *dzrow, hipStream_t s);
 hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp, const void *WrT,
                             const float *dz, const int32_t *inv_perm, const void *idx, int idx_dtype,
                             int64_t stride, void *dx, hipStream_t s);
@@ -100,10 +101,10 @@ hipError_t router_gate(int T, int d, int E, int K, int act, const void *x, const
                        bool plain_only, hipStream_t s);
 
 // Router weight gradient dW_r (+)= x^T ds, ds[t][idx[t][j]] = dz[t][j]; part: router_dwr_ws_bytes() bytes.  dbias (+)=
-// column sums of ds, unless NULL (offsets and perm as r3_permute makes them; perm may be NULL).  WrT [E,d] = W_r^T
+// column sums of ds, unless NULL (dzrow: dz in the order of the rows).  WrT [E,d] = W_r^T
 size_t router_dwr_ws_bytes(int act, int T, int d, int E, int K, bool plain_only);
 hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, const void *Wr, const float *dz, const void *idx,
-                           int idx_dtype, int64_t stride, const int32_t *offsets, const int32_t *perm, float *part, float *dWr,
+                           int idx_dtype, int64_t stride, const int32_t *offsets, const float *dzrow, float *part, float *dWr,
                            float *dbias, void *WrT, int accumulate, bool plain_only, hipStream_t s);
 
 // r3_gemm.hip (bf16 MFMA)
@@ -115,9 +116,10 @@ size_t mfma_tiles_bytes(int64_t S, int E);
 // weight gradients (mfma_wgrad_split_rows picks it); 0: never; < 0: the pass has no
 // weight gradients and the table gets no reduction segments at all
 hipError_t mfma_build_tiles(int E, const int32_t *offsets, int32_t *tiles, int split_rows, hipStream_t s);
-// the same launch also makes the row -> token list and the per-row gates (see mfma_row_tokens)
+// the same launch also makes the row -> token list, tok[inv_perm[i]] = i / K (mfma_row_tokens_bytes(): padded), and the
+// gates in that order, grow[inv_perm[i]] = gates[i]
 hipError_t mfma_build_tiles_and_row_tokens(int E, const int32_t *offsets, int32_t *tiles, int split_rows, int S, int K,
-                                           const int32_t *perm, const float *gates, int32_t *tok, float *grow,
+                                           const int32_t *inv_perm, const float *gates, int32_t *tok, float *grow,
                                            hipStream_t s);
 // 0 unless `part_bytes_available` holds the partial products of every slot a split may use
 int mfma_wgrad_split_rows(int64_t S, int tiles_per_seg, size_t part_bytes_available, size_t bytes_per_slot);
@@ -144,14 +146,12 @@ hipError_t mfma_ffn_dxp(int64_t S, int d, int E, int F, const void *dA, const vo
 hipError_t mfma_wgrad(int E, int NQd, int NPd, const void *Qs, const void *Ps, const int32_t *tok, int nrows,
                       const int32_t *tiles, int launch, float *out, float *part, int accumulate, hipStream_t s);
 // out0 (+)= Qs^T P0 and out1 (+)= Qs^T P1 per expert in one pass over Qs.  tok != NULL: Qs is the
-// un-permuted [nrows, NQd] matrix and row r of the reduction is its row tok[r] (a list made by
-// mfma_row_tokens; nrows * NQd * 2 < 2^31)
+// un-permuted [nrows, NQd] matrix and row r of the reduction is its row tok[r] (nrows * NQd * 2 < 2^31)
 // `part` (split tables only, else NULL): room for the partial products of both gradients, 2 x the slots of
 // mfma_wgrad's
 hipError_t mfma_wgrad_pair(int E, int NQd, int NPd, const void *Qs, const int32_t *tok, int nrows, const void *P0,
                            const void *P1, const int32_t *tiles, int launch, float *out0, float *out1, float *part,
                            int accumulate, hipStream_t s);
-// the list above: tok[r] = perm[r] / K (r < S), padded
 size_t mfma_row_tokens_bytes(int64_t S);
 hipError_t mfma_router_logits(int T, int d, int E, const void *x, const void *Wr, const float *bias,
                               float *logits, hipStream_t s);

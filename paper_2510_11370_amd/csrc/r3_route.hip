@@ -918,14 +918,14 @@ hipError_t launch_combine(int T, int d, int K, int act, const void *Yp, const fl
 // Backward through combine and masked softmax, one block per token:
 //   dg_j = <dy_t, Yp[row_j]>,  dYp[row_j] = g_j * dy_t,
 //   dz_j = g_j (dg_j - sum_i g_i dg_i).
-// Writes dz [T,K] f32.
+// Writes dz [T,K] f32, and dzrow[row_j] = dz_j unless that is NULL.
 // ---------------------------------------------------------------------------
 template <typename T, int VEC, int KT>
 __global__ void __launch_bounds__(256)
 gate_backward_kernel(int Krt, int row_vecs, const typename VecIO<T, VEC>::V *__restrict__ dy,
                      const typename VecIO<T, VEC>::V *__restrict__ Yp, const float *__restrict__ gates,
                      const int32_t *__restrict__ inv_perm, typename VecIO<T, VEC>::V *__restrict__ dYp,
-                     float *__restrict__ dz, int gated) {
+                     float *__restrict__ dz, float *__restrict__ dzrow, int gated) {
     typedef VecIO<T, VEC> IO;
     const int K = KT > 0 ? KT : Krt;
     const int t = blockIdx.x;
@@ -1001,26 +1001,28 @@ gate_backward_kernel(int Krt, int row_vecs, const typename VecIO<T, VEC>::V *__r
         for (int j = 0; j < K; ++j) mix = gated ? mix + dgs[j] : fmaf(g[j], dgs[j], mix);
         float v = gated ? dgs[threadIdx.x] - g[threadIdx.x] * mix : g[threadIdx.x] * (dgs[threadIdx.x] - mix);
         dz[(int64_t)t * K + threadIdx.x] = v;
+        if (dzrow) dzrow[rows[threadIdx.x]] = v;
     }
 }
 
 template <typename T, int VEC>
 static hipError_t gate_backward_dispatch(int Tn, int K, int row_vecs, const void *dy, const void *Yp, const float *gates,
-                                         const int32_t *inv_perm, void *dYp, float *dz, int gated, hipStream_t s) {
+                                         const int32_t *inv_perm, void *dYp, float *dz, float *dzrow, int gated,
+                                         hipStream_t s) {
     typedef typename VecIO<T, VEC>::V V;
     auto k = K == 8 && VEC > 1 ? gate_backward_kernel<T, VEC, 8> : gate_backward_kernel<T, VEC, 0>;
-    k<<<Tn, 256, 0, s>>>(K, row_vecs, (const V *)dy, (const V *)Yp, gates, inv_perm, (V *)dYp, dz, gated);
+    k<<<Tn, 256, 0, s>>>(K, row_vecs, (const V *)dy, (const V *)Yp, gates, inv_perm, (V *)dYp, dz, dzrow, gated);
     return hipGetLastError();
 }
 
 hipError_t launch_gate_backward(int T, int d, int K, int act, const void *dy, const void *Yp, const float *gates,
-                                const int32_t *inv_perm, void *dYp, float *dz, int gated, hipStream_t s) {
+                                const int32_t *inv_perm, void *dYp, float *dz, float *dzrow, int gated, hipStream_t s) {
     ProfScope ps(PROF_GATE_BWD, s);
     if (act == R3_BF16)
-        return d % 8 == 0 ? gate_backward_dispatch<bf16_t, 8>(T, K, d / 8, dy, Yp, gates, inv_perm, dYp, dz, gated, s)
-                          : gate_backward_dispatch<bf16_t, 1>(T, K, d, dy, Yp, gates, inv_perm, dYp, dz, gated, s);
-    return d % 4 == 0 ? gate_backward_dispatch<float, 4>(T, K, d / 4, dy, Yp, gates, inv_perm, dYp, dz, gated, s)
-                      : gate_backward_dispatch<float, 1>(T, K, d, dy, Yp, gates, inv_perm, dYp, dz, gated, s);
+        return d % 8 == 0 ? gate_backward_dispatch<bf16_t, 8>(T, K, d / 8, dy, Yp, gates, inv_perm, dYp, dz, dzrow, gated, s)
+                          : gate_backward_dispatch<bf16_t, 1>(T, K, d, dy, Yp, gates, inv_perm, dYp, dz, dzrow, gated, s);
+    return d % 4 == 0 ? gate_backward_dispatch<float, 4>(T, K, d / 4, dy, Yp, gates, inv_perm, dYp, dz, dzrow, gated, s)
+                      : gate_backward_dispatch<float, 1>(T, K, d, dy, Yp, gates, inv_perm, dYp, dz, dzrow, gated, s);
 }
 
 // ---------------------------------------------------------------------------
@@ -1031,28 +1033,34 @@ hipError_t launch_gate_backward(int T, int d, int K, int act, const void *dy, co
 // ---------------------------------------------------------------------------
 __global__ void __launch_bounds__(256)
 gate_backward_parts_kernel(int T, int K, int KP, int nparts, const float *__restrict__ wpart,
-                           const float *__restrict__ gates, const int32_t *__restrict__ inv_perm, float *__restrict__ dz) {
+                           const float *__restrict__ gates, const int32_t *__restrict__ inv_perm, float *__restrict__ dz,
+                           float *__restrict__ dzrow) {
     const int j = threadIdx.x % KP, t = blockIdx.x * (256 / KP) + threadIdx.x / KP;
     const bool live = t < T && j < K;
     float w = 0.0f, g = 0.0f;
+    int row = 0;
     if (live) {
-        const float *p = wpart + (int64_t)inv_perm[(int64_t)t * K + j] * nparts;
+        row = inv_perm[(int64_t)t * K + j];
+        const float *p = wpart + (int64_t)row * nparts;
         for (int i = 0; i < nparts; ++i) w += p[i];
         g = gates[(int64_t)t * K + j];
     }
     // sum of w over the token's slots, in a fixed order: KP neighbouring lanes (KP <= 64 divides 64)
     float mix = w;
     for (int o = 1; o < KP; o <<= 1) mix += __shfl_xor(mix, o, 64);
-    if (live) dz[(int64_t)t * K + j] = w - g * mix;
+    if (live) {
+        dz[(int64_t)t * K + j] = w - g * mix;
+        if (dzrow) dzrow[row] = w - g * mix;
+    }
 }
 
 hipError_t launch_gate_backward_parts(int T, int K, int nparts, const float *wpart, const float *gates,
-                                      const int32_t *inv_perm, float *dz, hipStream_t s) {
+                                      const int32_t *inv_perm, float *dz, float *dzrow, hipStream_t s) {
     ProfScope ps(PROF_GATE_BWD, s);
     int KP = 1;
     while (KP < K) KP <<= 1;                        // K <= kMaxK = 64
     const int tpb = 256 / KP;
-    gate_backward_parts_kernel<<<(T + tpb - 1) / tpb, 256, 0, s>>>(T, K, KP, nparts, wpart, gates, inv_perm, dz);
+    gate_backward_parts_kernel<<<(T + tpb - 1) / tpb, 256, 0, s>>>(T, K, KP, nparts, wpart, gates, inv_perm, dz, dzrow);
     return hipGetLastError();
 }
 

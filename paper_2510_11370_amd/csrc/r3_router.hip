@@ -528,19 +528,17 @@ router_dwr_kernel(int T, int d, int E, int K, int rows, const bf16_t *__restrict
 }
 
 // The last launch before dx: three sorts of work that do not wait for each other, a work-group each.
-//   dbias[e] (+)= the sum of dz over the slots of expert e: its rows of the permutation, or, without one, all slots whose
-//     id it is (fixed order; first in the grid, as a skewed load's hot expert takes longest);
+//   dbias[e] (+)= the sum of dz over the rows of expert e (fixed order; first in the grid, as a skewed load's hot expert takes
+//     longest);
 //   dW_r[i] (+)= sum_s part[s][i], s ascending, 1024 values;
 //   W_r^T, which dx reads, a 32 x 32 tile.
 // Each is microseconds of latency, so launches of their own cost a layer of few tokens more than the work did.
 // Forward + backward, three launches vs one: f32 T=256 d=128 E=8 79.8 -> 78.0 us, bf16 T=3001 d=1000 E=64 612 -> 609,
 // T=6000 d=1024 E=384 with dbias 1083 -> 1074, T=1001 d=2048 E=128 1121 -> 1118.
 template <typename T> struct RouterFinish {
-    int Tn, d, E, K, nsplit, accumulate, bias_blocks, sum_blocks, u8;
-    int64_t stride;
-    const float *dz, *part;
-    const void *idx;
-    const int32_t *offsets, *perm;
+    int d, E, nsplit, accumulate, bias_blocks, sum_blocks;
+    const float *dzrow, *part;
+    const int32_t *offsets;
     float *dbias, *dWr;
     const T *Wr;
     T *WrT;
@@ -550,25 +548,16 @@ template <typename T>
 __global__ void __launch_bounds__(1024) router_finish_kernel(RouterFinish<T> a) {
     __shared__ float tmp[16];
     __shared__ T tile[32][33];
-    const int tid = threadIdx.x, E = a.E, K = a.K;
+    const int tid = threadIdx.x, E = a.E;
     int blk = blockIdx.x;
     if (blk < a.bias_blocks) {
-        const int e = blk;
+        const int e = blk, r1 = a.offsets[e + 1];
         float acc = 0.0f;
-        if (a.perm) {
-            const int r1 = a.offsets[e + 1];
-            for (int r = a.offsets[e] + tid; r < r1; r += 4 * 1024) {
-                float v[4];
+        for (int r = a.offsets[e] + tid; r < r1; r += 4 * 1024) {
+            float v[4];
 #pragma unroll
-                for (int u = 0; u < 4; ++u) v[u] = r + u * 1024 < r1 ? a.dz[a.perm[r + u * 1024]] : 0.0f;
-                acc += (v[0] + v[1]) + (v[2] + v[3]);
-            }
-        } else {
-            for (int64_t i = tid; i < (int64_t)a.Tn * K; i += 1024) {
-                const int64_t at = i / K * a.stride + i % K;
-                const int id = a.u8 ? ((const uint8_t *)a.idx)[at] : ((const uint16_t *)a.idx)[at];
-                if (min(id, E - 1) == e) acc += a.dz[i];
-            }
+            for (int u = 0; u < 4; ++u) v[u] = r + u * 1024 < r1 ? a.dzrow[r + u * 1024] : 0.0f;
+            acc += (v[0] + v[1]) + (v[2] + v[3]);
         }
         acc = wave_sum(acc);
         if (lane_id() == 0) tmp[tid >> 6] = acc;
@@ -705,7 +694,7 @@ static hipError_t launch_finish(RouterFinish<T> a, const void *Wr, void *WrT, hi
 }
 
 hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, const void *Wr, const float *dz, const void *idx,
-                           int idx_dtype, int64_t stride, const int32_t *offsets, const int32_t *perm, float *part, float *dWr,
+                           int idx_dtype, int64_t stride, const int32_t *offsets, const float *dzrow, float *part, float *dWr,
                            float *dbias, void *WrT, int accumulate, bool plain_only, hipStream_t s) {
     ProfScope ps(PROF_DWR, s);
     const bool bf = bf16_dwr(act, d, K, plain_only);
@@ -713,14 +702,12 @@ hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, c
     if (bf) (idx_dtype == R3_IDX_U8 ? launch_dwr<uint8_t> : launch_dwr<uint16_t>)(T, d, E, K, x, dz, idx, stride, part, s);
     else plain_dwr_parts(T, d, E, K, act, x, dz, idx, idx_dtype, stride, part, s);
     auto finish = [&](auto f) {
-        f.Tn = T; f.d = d; f.E = E; f.K = K;
+        f.d = d; f.E = E;
         f.nsplit = (T + rows - 1) / rows;
         f.accumulate = accumulate;
         f.bias_blocks = dbias ? E : 0;
         f.sum_blocks = (int)(((int64_t)d * E + 1023) / 1024);
-        f.u8 = idx_dtype == R3_IDX_U8;
-        f.stride = stride;
-        f.dz = dz; f.part = part; f.idx = idx; f.offsets = offsets; f.perm = perm;
+        f.dzrow = dzrow; f.part = part; f.offsets = offsets;
         f.dbias = dbias; f.dWr = dWr;
         return launch_finish(f, Wr, WrT, s);
     };

@@ -45,19 +45,24 @@ def test_layer_at_ragged_widths(sh, one_call):
         got = got.cpu().numpy()
         for e in range(sh.E):
             assert np.linalg.norm(got[e] - ref[key][e]) <= c.rel * np.linalg.norm(ref[key][e]) + 1e-30, (key, e)
-    # a caller without perm still has the plain kernels (Xp given, forward call by call)
+    # a caller that gives Xp need not give perm, nor fill one: every output again
     if not one_call:
-        dx = buf.dx.clone()
-        dbias = torch.full((sh.E,), 3.0, dtype=torch.float32, device="cuda")
-        D = buf.D
-        r3.moe_backward(D, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], buf.gates, buf.inv_perm, None, buf.offsets, buf.Xp,
-                        buf.A, buf.B, buf.H, buf.Yp, *w, buf.dx, buf.dW_r, buf.dW_gate, buf.dW_up, buf.dW_down, buf.ws_bwd,
-                        dbias=dbias)
-        torch.cuda.synchronize()
-        assert_close(dbias.cpu().numpy(), ref["dbias"], "dbias without perm", c.rel,
-                     router_gradient_sigma(n["x"], n["dy"], c.idx, fwd, sh.E)[1])
-        assert_close(host(buf.dx), ref["dx"], "dx without perm", c.rel)
-        assert not torch.equal(dx, torch.zeros_like(dx))
+        sigma = router_gradient_sigma(n["x"], n["dy"], c.idx, fwd, sh.E)
+        for perm in (None, torch.zeros_like(buf.perm)):
+            dbias = torch.full((sh.E,), 3.0, dtype=torch.float32, device="cuda")
+            for t in (buf.dx, buf.dW_r, buf.dW_gate, buf.dW_up, buf.dW_down):
+                t.fill_(7.0)
+            r3.moe_backward(buf.D, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], buf.gates, buf.inv_perm, perm, buf.offsets,
+                            buf.Xp, buf.A, buf.B, buf.H, buf.Yp, *w, buf.dx, buf.dW_r, buf.dW_gate, buf.dW_up, buf.dW_down,
+                            buf.ws_bwd, dbias=dbias)
+            torch.cuda.synchronize()
+            assert_close(dbias.cpu().numpy(), ref["dbias"], "dbias without perm", c.rel, sigma[1])
+            assert_close(buf.dW_r.cpu().numpy(), ref["dWr"], "dW_r without perm", c.rel, sigma[0])
+            assert_close(host(buf.dx), ref["dx"], "dx without perm", c.rel)
+            for got, key in ((buf.dW_gate, "dWg"), (buf.dW_up, "dWu"), (buf.dW_down, "dWd")):
+                got = got.cpu().numpy()
+                for e in range(sh.E):
+                    assert np.linalg.norm(got[e] - ref[key][e]) <= c.rel * np.linalg.norm(ref[key][e]) + 1e-30, (key, e)
 
 
 @pytest.mark.parametrize("d,F", [(256, 256), (320, 192)])     # whole tiles; guarded ones, five and three windows of 64 k

@@ -103,23 +103,36 @@ def test_dispatch_at_chunk_edges(T, E, K, skew, token_major):
         assert np.array_equal(got.cpu().numpy(), want)
 
 
-@pytest.mark.parametrize("T,d,E,K,act,with_perm", [
-    (1, 8, 8, 1, "bf16", True), (65, 136, 136, 6, "bf16", False), (4097, 264, 130, 16, "bf16", True),   # tile and part edges
-    (300, 128, 128, 24, "bf16", True), (150, 36, 70, 5, "f32", False), (129, 33, 9, 3, "f32", True),    # the f32 tiles
+@pytest.mark.parametrize("T,d,E,K,act,perm", [
+    (1, 8, 8, 1, "bf16", "own"), (4097, 264, 130, 16, "bf16", "own"), (300, 128, 128, 24, "bf16", "own"),   # tile and part edges
+    (129, 33, 9, 3, "f32", "own"),                                                                         # the f32 tiles
+    # Xp given: no perm, or one that holds nothing
+    (65, 136, 136, 6, "bf16", None), (65, 136, 136, 6, "bf16", "unfilled"), (700, 136, 300, 4, "bf16", None),
+    (150, 36, 70, 5, "f32", None), (150, 36, 70, 5, "f32", "unfilled"), (222, 64, 260, 7, "f32", None),
 ])
-def test_router_gradient_at_tile_edges(T, d, E, K, act, with_perm):
-    """dW_r and dbias through r3_moe_backward, overwritten and then added to, with and without the permutation."""
+@pytest.mark.parametrize("token_major", [False, True])
+def test_router_gradient_at_tile_edges(T, d, E, K, act, perm, token_major):
+    """dW_r and dbias through r3_moe_backward, overwritten and then added to: after the forward in one call, and after the
+    forward step by step without a permutation."""
     sh = SH(T=T, d=d, E=E, K=K, F=256, act=act, sigma=0.05, seed=95)
     c = Case(sh, backward=True, scale_w=5.0)
     n = c.np
     fwd = sparse.forward(n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], n["bias"])
     ref = sparse.backward(n["dy"], n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], fwd, want_dbias=True)
-    buf = r3.LayerBuffers(c.D, backward=True, gathered_copy=not with_perm)
+    D, idx = c.D, c.t["idx"]
+    if token_major:      # the middle one of three layers
+        D = r3.desc(T, d, E, K, 256, act, idx_token_stride=3 * K)
+        ids = idx if E <= 256 else idx.view(torch.int16)
+        rec = torch.zeros(T, 3, K, dtype=ids.dtype, device="cuda")
+        rec[:, 1] = ids
+        idx = (rec if E <= 256 else rec.view(torch.uint16))[:, 1]
+    buf = r3.LayerBuffers(D, backward=True, gathered_copy=perm != "own")
     w = (c.t["Wg"], c.t["Wu"], c.t["Wd"])
-    (r3.forward_one_call if with_perm else r3.forward)(buf, c.t["x"], c.t["Wr"], c.t["idx"], *w, bias=c.t["bias"])
+    (r3.forward_one_call if perm == "own" else r3.forward)(buf, c.t["x"], c.t["Wr"], idx, *w, bias=c.t["bias"])
+    buf.perm = buf.perm if perm == "own" else None if perm is None else torch.zeros_like(buf.perm)
     dbias = torch.full((E,), 3.0, dtype=torch.float32, device="cuda")
     for acc in (False, True):
-        r3.backward(buf, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], *w, dbias=dbias, accumulate=acc)
+        r3.backward(buf, c.t["dy"], c.t["x"], c.t["Wr"], idx, *w, dbias=dbias, accumulate=acc)
     torch.cuda.synchronize()
     if K == 1:
         assert not buf.dW_r.any() and not dbias.any()

@@ -57,7 +57,7 @@ BwdWs bwd_layout(const Dims &m) {
     w.dA = take((size_t)m.S * m.F * m.eb);
     w.dB = take((size_t)m.S * m.F * m.eb);
     w.tiles = take(mf ? mfma_tiles_bytes(m.S, m.E) : 0);
-    w.part = take(router_dwr_ws_bytes(m.act, m.T, m.d, m.E, m.K, force_simt()));
+    w.part = take(router_dwr_ws_bytes(m.act, m.T, m.d, m.E, force_simt()));
     w.tok = take(mf ? mfma_row_tokens_bytes(m.S) : 0);           // row -> token list
     w.Hg = take(mf ? (size_t)m.S * m.F * m.eb : 0);              // gate-scaled H rows
     w.grow = take(mf ? (size_t)m.S * sizeof(float) : 0);         // row -> gate list

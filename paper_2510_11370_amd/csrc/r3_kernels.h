@@ -102,7 +102,7 @@ hipError_t router_gate(int T, int d, int E, int K, int act, const void *x, const
 
 // Router weight gradient dW_r (+)= x^T ds, ds[t][idx[t][j]] = dz[t][j]; part: router_dwr_ws_bytes() bytes.  dbias (+)=
 // column sums of ds, unless NULL (dzrow: dz in the order of the rows).  WrT [E,d] = W_r^T
-size_t router_dwr_ws_bytes(int act, int T, int d, int E, int K, bool plain_only);
+size_t router_dwr_ws_bytes(int act, int T, int d, int E, bool plain_only);
 hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, const void *Wr, const float *dz, const void *idx,
                            int idx_dtype, int64_t stride, const int32_t *offsets, const float *dzrow, float *part, float *dWr,
                            float *dbias, void *WrT, int accumulate, bool plain_only, hipStream_t s);

@@ -391,7 +391,11 @@ plain_gate_kernel(int Tn, int d, int E, int K, const T *__restrict__ x, const T 
 constexpr int kDwrQ = 128, kDwrP = 128, kDwrK = 64;
 constexpr int kDwrPBytes = kDwrK * 2 * kDwrP * 2, kDwrQBytes = kDwrK * kDwrQ * 2, kDwrLds = kDwrPBytes + 2 * kDwrQBytes;
 
-template <int EPT, typename IdxT>   // EPT: entries per thread and k-tile, 4 EPT >= K
+// EPT = 8, K > 16: too many registers for two k-tiles ahead and for what to take out again.  x and the first 8 entries come
+// one k-tile ahead (those past 8, K > 32, while the tile is made), and a wave clears its tokens' rows (8 KB) instead.
+// T=16384 d=2048 E=128, us on the f32 tiles, which such layers took for a while | here: K=17 762 | 50, K=24 905 | 54, K=32 1088 | 59,
+// K=64 1816 | 90.
+template <int EPT, typename IdxT>   // EPT: entries per thread and k-tile, 4 EPT >= K (or 8)
 __global__ void __launch_bounds__(256, 2)
 router_dwr_kernel(int T, int d, int E, int K, int rows, const bf16_t *__restrict__ x, const float *__restrict__ dz,
                   const IdxT *__restrict__ idx, int64_t stride, float *__restrict__ part) {
@@ -402,61 +406,86 @@ router_dwr_kernel(int T, int d, int E, int K, int rows, const bf16_t *__restrict
     const int r0 = sp * rows, r1 = min(T, r0 + rows), nk = (r1 - r0 + kDwrK - 1) / kDwrK;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, wp = wave & 1, wq = wave >> 1;
     char *const pt = lds, *const qs = lds + kDwrPBytes;
-    uint4 rq[2][4];
-    int eid[2][EPT];
-    float ez[2][EPT];
-    // the thread's entries: token ek of the k-tile, position ej
-    int ek[EPT], ej[EPT];
+    constexpr bool kMany = EPT > 4;
+    constexpr int kSets = kMany ? 1 : 2;   // k-tiles on their way
+    uint4 rq[kSets][4];
+    int eid[kSets][EPT];
+    float ez[kSets][EPT];
+    // entry n of the wave's 16 tokens: token n / K of them (by a multiplication: n < 1024, K <= 64), position n % K
+    const int inv_k = (65536 + K - 1) / K;
+    auto token = [&](int n) { return (n * inv_k) >> 16; };
+    auto eload = [&](int kt, int first, auto &id, auto &z) {
+        constexpr int N = sizeof(id) / sizeof(id[0]);
+        const int t0 = r0 + kt * kDwrK + 16 * wave, live = max(0, min(16, r1 - t0)) * K;
+        const float *zb = dz + (int64_t)t0 * K;
+        const IdxT *ib = idx + (int64_t)t0 * stride;
 #pragma unroll
-    for (int i = 0; i < EPT; ++i) {
-        const int n = lane + 64 * i;
-        ek[i] = n < 16 * K ? 16 * wave + n / K : kDwrK * 65536;   // (no entry: past every token)
-        ej[i] = n % K;
-    }
-    auto gload = [&](int kt, uint4 (&q)[4], int (&id)[EPT], float (&z)[EPT]) {
+        for (int i = 0; i < N; ++i) {
+            const int n = first + lane + 64 * i, t = token(n);
+            id[i] = -1;
+            z[i] = 0.0f;
+            if (n < live) {
+                id[i] = min((int)ib[t * stride + n - t * K], E - 1) - p0;
+                z[i] = zb[n];
+            }
+        }
+    };
+    auto gload = [&](int kt, int set) {
         const int t0 = r0 + kt * kDwrK;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int n = tid + 256 * i, t = t0 + n / 16, c = q0 + n % 16 * 8;
-            q[i] = t < r1 && c < d ? ld16(x + (int64_t)t * d + c) : zero16();
+            rq[set % kSets][i] = t < r1 && c < d ? ld16(x + (int64_t)t * d + c) : zero16();
         }
-#pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-            id[i] = -1;
-            z[i] = 0.0f;
-            if (ek[i] < kDwrK && t0 + ek[i] < r1) {
-                id[i] = min((int)idx[(int64_t)(t0 + ek[i]) * stride + ej[i]], E - 1) - p0;
-                z[i] = dz[(int64_t)(t0 + ek[i]) * K + ej[i]];
-            }
-        }
+        if constexpr (!kMany) eload(kt, 0, eid[set % kSets], ez[set % kSets]);
     };
     int old[EPT];
 #pragma unroll
     for (int i = 0; i < EPT; ++i) old[i] = -1;
-    auto put = [&](int stage, const uint4 (&q)[4], const int (&id)[EPT], const float (&z)[EPT]) {
+    // expert e's hi half is column (e / 64) * 128 + e % 64, its lo half 64 columns on (128 bytes, a bit of the offset)
+    auto eset = [&](int first, const auto &id, const auto &z) {
+        constexpr int N = sizeof(id) / sizeof(id[0]);
+#pragma unroll
+        for (int i = 0; i < N; ++i) {
+            if constexpr (!kMany) old[i] = -1;
+            if (id[i] >= 0 && id[i] < kDwrP) {
+                const int k = 16 * wave + token(first + lane + 64 * i);
+                const int c = (id[i] >> 6) * 128 + (id[i] & 63);
+                const int at = tr_off<2 * kDwrP>(k, c >> 3) + (c & 7) * 2;
+                const bf16_t hi = f32_to_bf16(z[i]);
+                *(bf16_t *)(pt + at) = hi;
+                *(bf16_t *)(pt + (at ^ 128)) = f32_to_bf16(z[i] - bf16_to_f32(hi));
+                if constexpr (!kMany) old[i] = at;
+            }
+        }
+    };
+    auto put = [&](int kt, int stage) {
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
             const int n = tid + 256 * i;
-            *(uint4 *)(qs + stage * kDwrQBytes + tr_off<kDwrQ>(n / 16, n % 16)) = q[i];
+            *(uint4 *)(qs + stage * kDwrQBytes + tr_off<kDwrQ>(n / 16, n % 16)) = rq[stage % kSets][i];
         }
-        // expert e's hi half is column (e / 64) * 128 + e % 64, its lo half 64 columns on (128 bytes, a bit of the offset)
+        if constexpr (kMany) {
 #pragma unroll
-        for (int i = 0; i < EPT; ++i)
-            if (old[i] >= 0) {
-                *(bf16_t *)(pt + old[i]) = 0;
-                *(bf16_t *)(pt + (old[i] ^ 128)) = 0;
+            for (int i = 0; i < 8; ++i) ((uint4 *)(pt + wave * (kDwrPBytes / 4)))[lane + 64 * i] = zero16();
+            asm volatile("" ::: "memory");
+            eset(0, eid[0], ez[0]);
+#pragma unroll 1
+            for (int n = EPT * 64; n < 16 * K; n += EPT * 64) {
+                int id[EPT];
+                float z[EPT];
+                eload(kt, n, id, z);
+                eset(n, id, z);
             }
-        asm volatile("" ::: "memory");
+        } else {
 #pragma unroll
-        for (int i = 0; i < EPT; ++i) {
-            old[i] = -1;
-            if (id[i] >= 0 && id[i] < kDwrP) {
-                const int c = (id[i] >> 6) * 128 + (id[i] & 63);
-                old[i] = tr_off<2 * kDwrP>(ek[i], c >> 3) + (c & 7) * 2;
-                const bf16_t hi = f32_to_bf16(z[i]);
-                *(bf16_t *)(pt + old[i]) = hi;
-                *(bf16_t *)(pt + (old[i] ^ 128)) = f32_to_bf16(z[i] - bf16_to_f32(hi));
-            }
+            for (int i = 0; i < EPT; ++i)
+                if (old[i] >= 0) {
+                    *(bf16_t *)(pt + old[i]) = 0;
+                    *(bf16_t *)(pt + (old[i] ^ 128)) = 0;
+                }
+            asm volatile("" ::: "memory");
+            eset(0, eid[stage % kSets], ez[stage % kSets]);
         }
     };
     TrFrag<2 * kDwrP> pf;
@@ -484,24 +513,35 @@ router_dwr_kernel(int T, int d, int E, int K, int rows, const bf16_t *__restrict
                 for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
         }
     };
-    gload(0, rq[0], eid[0], ez[0]);
-    gload(1, rq[1], eid[1], ez[1]);
     for (int i = tid; i < kDwrPBytes / 16; i += 256) ((uint4 *)pt)[i] = zero16();
-    __syncthreads();
-    put(0, rq[0], eid[0], ez[0]);
-    __syncthreads();
-    for (int kt = 0; kt < nk; kt += 2) {
-        gload(kt + 2, rq[0], eid[0], ez[0]);
-        multiply(0);
-        __syncthreads();
-        put(1, rq[1], eid[1], ez[1]);
-        __syncthreads();
-        if (kt + 1 < nk) {
-            gload(kt + 3, rq[1], eid[1], ez[1]);
-            multiply(1);
+    if constexpr (kMany) {
+        for (int kt = -1; kt < nk; ++kt) {
+            eload(kt + 1, 0, eid[0], ez[0]);
+            gload(kt + 1, 0);
+            if (kt >= 0) multiply(kt & 1);
             __syncthreads();
-            put(0, rq[0], eid[0], ez[0]);
+            put(kt + 1, (kt + 1) & 1);
             __syncthreads();
+        }
+    } else {
+        gload(0, 0);
+        gload(1, 1);
+        __syncthreads();
+        put(0, 0);
+        __syncthreads();
+        for (int kt = 0; kt < nk; kt += 2) {
+            gload(kt + 2, 0);
+            multiply(0);
+            __syncthreads();
+            put(kt + 1, 1);
+            __syncthreads();
+            if (kt + 1 < nk) {
+                gload(kt + 3, 1);
+                multiply(1);
+                __syncthreads();
+                put(kt + 2, 0);
+                __syncthreads();
+            }
         }
     }
     float *o = part + (int64_t)sp * d * E;
@@ -661,8 +701,7 @@ void plain_by_size(int Tn, int d, int E, int K, const void *x, const void *Wr, c
 
 }  // namespace
 
-// (with more than 16 entries a token the kernel's bookkeeping no longer fits its registers)
-static bool bf16_dwr(int act, int d, int K, bool plain_only) { return act == R3_BF16 && d % 8 == 0 && K <= 16 && !plain_only; }
+static bool bf16_dwr(int act, int d, bool plain_only) { return act == R3_BF16 && d % 8 == 0 && !plain_only; }
 // tokens per part: whole k-tiles, and enough parts for two work-groups on every compute unit
 static int dwr_rows(int T, int d, int E) {
     const int64_t tiles = (int64_t)((d + kDwrQ - 1) / kDwrQ) * ((E + kDwrP - 1) / kDwrP), kts = (T + kDwrK - 1) / kDwrK;
@@ -670,8 +709,8 @@ static int dwr_rows(int T, int d, int E) {
     return (int)((kts + ns - 1) / ns * kDwrK);
 }
 
-size_t router_dwr_ws_bytes(int act, int T, int d, int E, int K, bool plain_only) {
-    const int rows = bf16_dwr(act, d, K, plain_only) ? dwr_rows(T, d, E) : plain_dwr_rows(T, d, E);
+size_t router_dwr_ws_bytes(int act, int T, int d, int E, bool plain_only) {
+    const int rows = bf16_dwr(act, d, plain_only) ? dwr_rows(T, d, E) : plain_dwr_rows(T, d, E);
     return align_up((size_t)((T + rows - 1) / rows) * d * E * sizeof(float), 256);
 }
 
@@ -680,7 +719,8 @@ static void launch_dwr(int T, int d, int E, int K, const void *x, const float *d
                        float *part, hipStream_t s) {
     const int rows = dwr_rows(T, d, E);
     const int grid = (T + rows - 1) / rows * ((d + kDwrQ - 1) / kDwrQ) * ((E + kDwrP - 1) / kDwrP);
-    auto k = K <= 4 ? router_dwr_kernel<1, IdxT> : K <= 8 ? router_dwr_kernel<2, IdxT> : router_dwr_kernel<4, IdxT>;
+    auto k = K <= 4 ? router_dwr_kernel<1, IdxT> : K <= 8 ? router_dwr_kernel<2, IdxT> : K <= 16 ? router_dwr_kernel<4, IdxT>
+                                                                                     : router_dwr_kernel<8, IdxT>;
     k<<<grid, 256, kDwrLds, s>>>(T, d, E, K, rows, (const bf16_t *)x, dz, (const IdxT *)idx, stride, part);
 }
 
@@ -697,7 +737,7 @@ hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, c
                            int idx_dtype, int64_t stride, const int32_t *offsets, const float *dzrow, float *part, float *dWr,
                            float *dbias, void *WrT, int accumulate, bool plain_only, hipStream_t s) {
     ProfScope ps(PROF_DWR, s);
-    const bool bf = bf16_dwr(act, d, K, plain_only);
+    const bool bf = bf16_dwr(act, d, plain_only);
     const int rows = bf ? dwr_rows(T, d, E) : plain_dwr_rows(T, d, E);
     if (bf) (idx_dtype == R3_IDX_U8 ? launch_dwr<uint8_t> : launch_dwr<uint16_t>)(T, d, E, K, x, dz, idx, stride, part, s);
     else plain_dwr_parts(T, d, E, K, act, x, dz, idx, idx_dtype, stride, part, s);

@@ -613,15 +613,21 @@ permute_scan_kernel(int E, int nchunks, const int32_t *__restrict__ chunk_hist, 
     __shared__ int32_t tmp[16];
     for (int e = threadIdx.x; e < E; e += 1024) {
         int32_t run = 0;
-        for (int c = 0; c < nchunks; c += 8) {
+        int c = 0;
+        for (; c + 8 <= nchunks; c += 8) {   // (guards in here took 7 % of the whole call: E=2048 T=131072 K=8 173 us, 159 without)
             int32_t h[8];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) h[u] = c + u < nchunks ? chunk_hist[(int64_t)(c + u) * E + e] : 0;
+            for (int u = 0; u < 8; ++u) h[u] = chunk_hist[(int64_t)(c + u) * E + e];
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
-                if (c + u < nchunks) chunk_base[(int64_t)(c + u) * E + e] = run;
+                chunk_base[(int64_t)(c + u) * E + e] = run;
                 run += h[u];
             }
+        }
+        for (; c < nchunks; ++c) {
+            const int32_t h = chunk_hist[(int64_t)c * E + e];
+            chunk_base[(int64_t)c * E + e] = run;
+            run += h;
         }
         tot[e] = run;
         counts[e] = run;

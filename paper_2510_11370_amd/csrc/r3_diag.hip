@@ -206,6 +206,50 @@ routing_diff_kernel(int T, int Krt, int L, const IdxT *__restrict__ a, const Idx
         if (hist[i]) atomicAdd(&router_hist[i], (unsigned long long)hist[i]);
 }
 
+// One thread per token, its layers in a loop: for records of few layers, which do not fill the other kernel's work-groups
+// (and a quarter of the work-groups adds to the histogram).
+template <typename IdxT, int K, int U>
+__global__ void __launch_bounds__(256)
+routing_diff_tokens_kernel(int T, int Krt, int L, const IdxT *__restrict__ a, const IdxT *__restrict__ b,
+                           int64_t token_stride, int64_t layer_stride, unsigned long long *__restrict__ router_hist,
+                           int32_t *__restrict__ token_choices, int32_t *__restrict__ token_routers) {
+    constexpr bool kRegs = K > 0;
+    typedef IdSet<IdxT, kRegs ? K : 4, kRegs ? U : 2> Set;
+    __shared__ int hist[kMaxK + 1];
+    const int Kn = kRegs ? K : Krt;
+    for (int i = threadIdx.x; i <= Kn; i += 256) hist[i] = 0;
+    __syncthreads();
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    int choices = 0, routers = 0;
+    if (t < T)
+        for (int l = 0; l < L; ++l) {
+            const int64_t o = (int64_t)l * layer_stride + (int64_t)t * token_stride;
+            int d;
+            if constexpr (kRegs) {
+                Set x, y;
+                x.load(a + o);
+                y.load(b + o);
+                d = x != y ? x.differing_from(y) : 0;
+            } else {
+                d = differing(a + o, b + o, Kn);
+            }
+            if (d > 0) {
+                choices += d;
+                ++routers;
+                atomicAdd(&hist[d], 1);
+            }
+        }
+    const int same = wave_sum(t < T ? L - routers : 0);
+    if (lane_id() == 0 && same) atomicAdd(&hist[0], same);
+    if (t < T) {
+        token_choices[t] = choices;
+        token_routers[t] = routers;
+    }
+    __syncthreads();
+    for (int i = threadIdx.x; i <= Kn; i += 256)
+        if (hist[i]) atomicAdd(&router_hist[i], (unsigned long long)hist[i]);
+}
+
 // W waves per sequence: exact integer sum of the tokens' differing routers, one division.  One wave walking a
 // sequence of 2048 tokens is 32 round trips to memory in a row (11 us); sixteen waves make it two (4.2 us).
 template <int W>
@@ -362,10 +406,20 @@ hipError_t launch_routing_diff(int T, int K, int L, const void *a, const void *b
     };
     const int tiles = (T + kDiffTok - 1) / kDiffTok;
     const int grid = tiles < kMaxDiffBlocks ? tiles : kMaxDiffBlocks;
-#define R3_DIFF(TT, KK, UU)                                                                                          \
-    routing_diff_kernel<TT, KK, UU><<<grid, kDiffThreads, 0, s>>>(T, K, L, (const TT *)a, (const TT *)b, token_stride, \
-                                                                 layer_stride, (unsigned long long *)router_hist,     \
-                                                                 token_choices, token_routers)
+    // Where a thread per token is the faster one, us per token / by tiles, K=8 one-byte ids: T=131072 one layer 8.5 / 17.1, eight
+    // 10.8 / 18.0, 24 layers 20.2 / 21.5 (two-byte ids 22.5 / 24.9), 48 layers 36 / 24.5; T=4096 eight 7.3 / 7.3, 24 layers
+    // 12.8 / 7.3; token-major T=131072 eight 12.0 / 18.0, twelve 16.5 / 18.0 (two-byte ids 28.6 / 19.9).  Compared in place, K=12: T=131072 one
+    // layer 13.1 / 30.6, four 27.7 / 31.1, six 38.5 / 31.3; T=64 two layers 11.1 / 11.2, three 16.0 / 12.4.
+    const bool many = T >= 65536, token_major = layer_stride < token_stride && L > 1;
+    auto few_layers = [&](bool regs) {
+        if (regs) return L <= 8 || (many && (token_major ? L <= 12 && L * K * ib <= 96 : L <= 24));
+        return K * L <= 24 || (many && !token_major && (K * L <= 48 || L == 1));
+    };
+#define R3_DIFF(TT, KK, UU)                                                                                            \
+    (few_layers(KK > 0) ? routing_diff_tokens_kernel<TT, KK, UU> : routing_diff_kernel<TT, KK, UU>)                      \
+        <<<few_layers(KK > 0) ? (T + 255) / 256 : grid, few_layers(KK > 0) ? 256 : kDiffThreads, 0, s>>>(               \
+            T, K, L, (const TT *)a, (const TT *)b, token_stride, layer_stride, (unsigned long long *)router_hist,       \
+            token_choices, token_routers)
     {
         ProfScope ps(PROF_ROUTING_DIFF, s);
         if (ib == 1) {

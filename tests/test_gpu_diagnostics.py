@@ -138,10 +138,13 @@ def test_diagnostics_host_errors():
 
 @pytest.mark.parametrize("K,E", [(2, 64), (4, 128), (6, 64), (8, 256), (2, 384), (4, 384), (6, 300), (8, 384)])
 @pytest.mark.parametrize("token_major", [False, True])
-@pytest.mark.parametrize("L,T,flip", [(3, 129, 1.0), (7, 1000, 0.0), (5, 128, 0.4), (600, 3, 0.5)])
+@pytest.mark.parametrize("L,T,flip", [
+    (11, 129, 1.0), (9, 1000, 0.0), (13, 128, 0.4), (600, 3, 0.5),      # tiles of tokens
+    (1, 257, 1.0), (8, 256, 0.4), (3, 1, 0.5),                          # a thread per token
+])
 def test_routing_diff_every_set_size(K, E, token_major, L, T, flip):
-    """Each set size that is kept in registers: nothing differs, everything does (the queues fill on every step),
-    a tile and one token more, more layers than a work-group has lanes."""
+    """Each set size that is kept in registers: nothing differs, everything does (the queues fill on every step), a tile or
+    work-group and one token more, more layers than a work-group has lanes."""
     a, b = _pair(L, T, K, E, seed=K * E + T, flip=flip)
     off = [0, T // 3, T // 3, T]
     want = dg.routing_diff_fast(a, b, E, off)
@@ -153,7 +156,7 @@ def test_routing_diff_every_set_size(K, E, token_major, L, T, flip):
 @pytest.mark.parametrize("K,E,shift", [(8, 128, 1), (8, 128, 4), (4, 64, 2), (6, 64, 1), (8, 384, 2), (4, 384, 2)])
 def test_routing_diff_at_odd_addresses(K, E, shift):
     """Records that start between the addresses whole loads need (shift in bytes)."""
-    L, T = 4, 300
+    L, T = 20, 300
     a, b = _pair(L, T, K, E, seed=shift)
     want = dg.routing_diff_fast(a, b, E, [0, T])
     npdt = np.uint8 if E <= 256 else np.uint16
@@ -167,3 +170,37 @@ def test_routing_diff_at_odd_addresses(K, E, shift):
     r3.routing_diff(D, L, dev[0], dev[1], T * K, hist, tc, tr)
     for name, w, g in zip(("router_hist", "token_choices", "token_routers"), want, (hist, tc, tr)):
         assert np.array_equal(np.asarray(w), g.cpu().numpy()), name
+
+
+@pytest.mark.parametrize("K,E", [(1, 5), (3, 8), (5, 128), (7, 300), (12, 384), (64, 256)])
+@pytest.mark.parametrize("L,T,token_major", [(1, 65, False), (2, 300, True), (9, 129, False)])
+def test_routing_diff_of_sets_compared_in_place(K, E, L, T, token_major):
+    """Set sizes that no registers hold, on both sides of the rule between a thread per token and tiles."""
+    a, b = _pair(L, T, K, E, seed=K * E + T, flip=0.3)
+    off = [0, T // 3, T]
+    want = dg.routing_diff_fast(a, b, E, off)
+    got = _run(a, b, E, token_major, off)
+    for name, w, g in zip(("router_hist", "token_choices", "token_routers", "seq_mean"), want, got):
+        assert np.array_equal(np.asarray(w), np.asarray(g)), name
+
+
+@pytest.mark.parametrize("K,E", [(2, 64), (8, 256), (8, 384), (12, 100)])
+@pytest.mark.parametrize("L,T,token_major", [(1, 65537, False), (4, 65536, False), (24, 65535, False), (24, 65536, False),
+                                             (12, 65600, True), (13, 65600, True)])
+def test_routing_diff_of_many_tokens_and_few_layers(K, E, L, T, token_major):
+    """Both sides of the same rule where the number of tokens counts in it."""
+    g = torch.Generator(device="cuda").manual_seed(K + L)
+    w = E // K
+    sets = lambda: (torch.randint(0, w, (L, T, K), generator=g, device="cuda") + w * torch.arange(K, device="cuda")).to(  # noqa: E731
+        torch.int16)
+    a = sets()
+    b = torch.where(torch.rand(L, T, K, generator=g, device="cuda") < 0.05, sets(), a).flip(2)
+    d = K - (a[..., :, None] == b[..., None, :]).any(-1).sum(-1)
+    as_ids = lambda t: (t.transpose(0, 1) if token_major else t).contiguous().to(torch.uint8 if E <= 256 else torch.int16)  # noqa: E731
+    D = r3.desc(T, 16, E, K, 16, idx_token_stride=L * K if token_major else 0)
+    hist = torch.zeros(K + 1, dtype=torch.int64, device="cuda")
+    tc, tr = (torch.empty(T, dtype=torch.int32, device="cuda") for _ in range(2))
+    r3.routing_diff(D, L, as_ids(a), as_ids(b), K if token_major else T * K, hist, tc, tr)
+    torch.cuda.synchronize()
+    assert torch.equal(hist, torch.bincount(d.flatten(), minlength=K + 1))
+    assert torch.equal(tc.long(), d.sum(0)) and torch.equal(tr.long(), (d > 0).sum(0))

@@ -250,7 +250,8 @@ __device__ __forceinline__ void unpack4(uint2 v, float *f) {
 // a matrix's end read zero by the buffer bounds, chunks past the end of a reduction are masked (OpKC64's TAIL),
 // features past an output's width are computed on whatever their columns hold and not stored.  The flag is a
 // template parameter because the whole-tile kernels have no registers to spare for the guards.
-// T=3001 d=1000 E=64 K=6 F=704, forward + backward: 4.2 ms on f32 tiles, 0.72 ms on these.
+// T=3001 d=1000 E=64 K=6 F=704, forward + backward: 4.2 ms on f32 tiles, 0.72 ms on these.  Their sigmoid is expf and a
+// division, as on the f32 tiles: the exponential of sigmoid_fast is off by tens of ulp at arguments below -50.
 template <bool GATHER, bool RAGGED>
 __global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
 ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *__restrict__ perm, int K, int T,
@@ -341,7 +342,7 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
                     const float a = acc[tp][tq][4 * g + i], b = acc[tp + 2][tq][4 * g + i];
-                    const float sg = sigmoid_fast(a);
+                    const float sg = RAGGED ? sigmoidf_(a) : sigmoid_fast(a);
                     fb[i] = a * sg;                                  // silu(a)
                     h[i] = gq * (fb[i] * b);
                     fa[i] = b * fmaf(fb[i], 1.0f - sg, sg);          // b silu'(a), silu'(a) = sg (1 + a (1 - sg))

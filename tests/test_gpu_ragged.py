@@ -124,3 +124,29 @@ def test_masked_lanes_of_sources_past_two_gigabytes():
     a, b = x[:4096].double() @ Wg[0].double(), x[:4096].double() @ Wu[0].double()
     want = a * torch.sigmoid(a) * b
     assert float((H[:4096].double() - want).norm() / want.norm()) < 4e-3      # (one rounding to bf16: 2^-9 at most)
+
+
+def test_sigmoid_of_large_arguments():
+    """FB = silu(A) at A = -80 .. -20, sums of two bf16 weights (exact in f32): next to none is rounded to bf16 on another side
+    than the exact value.  An error of n ulp of f32 flips about n in 65536 (1 for expf and a division, 40 for the
+    hardware's exponential of a rounded product)."""
+    T, d, E, F = 512, 264, 1, 1032
+    D = r3.desc(T, d, E, 1, F)
+    g = torch.Generator(device="cuda").manual_seed(3)
+    Wg = torch.zeros(E, d, F, device="cuda")
+    Wg[:, :d // 2] = -20 - 50 * torch.rand(E, d // 2, F, generator=g, device="cuda")
+    Wg[:, d // 2:] = -torch.rand(E, d // 2, F, generator=g, device="cuda")
+    Wg = Wg.bfloat16()
+    hi = torch.randint(0, d // 2, (T,), generator=g, device="cuda")
+    lo = torch.randint(d // 2, d, (T,), generator=g, device="cuda")
+    x = torch.zeros(T, d, device="cuda").scatter_(1, torch.stack([hi, lo], 1), 1.0).bfloat16()
+    offsets = torch.tensor([0, T], dtype=torch.int32, device="cuda")
+    e = lambda n: torch.empty(T, n, dtype=torch.bfloat16, device="cuda")  # noqa: E731
+    Yp, H, FA, FB = e(d), e(F), e(F), e(F)
+    r3.grouped_ffn(D, x, offsets, Wg, Wg, torch.zeros(E, F, d, device="cuda").bfloat16(), Yp, H, FA, FB,
+                   ws=r3.workspace(D, r3.OP_GROUPED_FFN))
+    torch.cuda.synchronize()
+    a = Wg[0].double()[hi] + Wg[0].double()[lo]
+    want = (a * torch.sigmoid(a)).bfloat16()
+    flips = int((FB != want).sum())
+    assert flips <= 4 * T * F / 65536, flips

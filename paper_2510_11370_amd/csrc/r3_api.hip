@@ -67,7 +67,7 @@ BwdWs bwd_layout(const Dims &m) {
 }
 
 struct FwdWs {
-    size_t gate, perm, ffn, tok, grow, total;
+    size_t gate, perm, ffn, tok, grow, total;   // tok: only where the dispatch does not make the tile table
 };
 FwdWs fwd_layout(const Dims &m) {
     FwdWs w;
@@ -76,7 +76,7 @@ FwdWs fwd_layout(const Dims &m) {
     w.gate = take((size_t)m.T * m.E * sizeof(float));
     w.perm = take(permute_ws_bytes(m.T, m.E, m.K));
     w.ffn = take(use_mfma_ffn(m) ? mfma_tiles_bytes(m.S, m.E) : 0);
-    w.tok = take(use_mfma_ffn(m) ? mfma_row_tokens_bytes(m.S) : 0);
+    w.tok = take(use_mfma_ffn(m) && !dispatch_makes_tiles(m.E) ? mfma_row_tokens_bytes(m.S) : 0);
     w.grow = take(use_mfma_ffn(m) ? (size_t)m.S * sizeof(float) : 0);
     w.total = o;
     return w;
@@ -273,17 +273,17 @@ int r3_moe_forward(const r3_layer_desc *desc, const void *x, const void *W_r, co
         !aligned(perm, 4))
         return R3_ERR_INVALID_ARG;
     const bool mf = use_mfma_ffn(m), with_tiles = mf && dispatch_makes_tiles(m.E);
-    int32_t *tiles = (int32_t *)(base + w.ffn), *tok = (int32_t *)(base + w.tok);
+    int32_t *tiles = (int32_t *)(base + w.ffn);
     float *grow = (float *)(base + w.grow);
     if (launch_permute(m.T, m.d, m.E, m.K, m.eb, nullptr, idx, m.idx, m.stride, counts, offsets, inv_perm, perm, nullptr,
-                       status_word, base + w.perm, with_tiles ? DispatchExtra{tiles, gates, tok, grow} : DispatchExtra{},
+                       status_word, base + w.perm, with_tiles ? DispatchExtra{tiles, gates, grow} : DispatchExtra{},
                        s) != hipSuccess)
         return R3_ERR_HIP;
     // the gate of every expert-sorted row: the first contraction's epilogue scales H with it, so the
     // down projection yields gated rows and the combination is a plain sum of each token's K rows
     if (mf) {
-        if (!with_tiles && mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, -1, (int)m.S, m.K, inv_perm, gates, tok, grow, s) !=
-                               hipSuccess)
+        if (!with_tiles && mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, -1, (int)m.S, m.K, inv_perm, gates,
+                                                           (int32_t *)(base + w.tok), grow, s) != hipSuccess)
             return R3_ERR_HIP;
         if (mfma_ffn_forward(m.S, m.d, m.E, m.F, x, perm, m.K, m.T, offsets, tiles, W_gate, W_up, W_down, Yp, H,
                              FA_save, FB_save, grow, s) != hipSuccess)

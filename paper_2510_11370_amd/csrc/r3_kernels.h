@@ -27,11 +27,10 @@ hipError_t launch_agreement(int T, int E, int K, const float *logits, const void
                             int64_t stride, int64_t *agree, hipStream_t s);
 size_t permute_ws_bytes(int T, int E, int K);
 // What the dispatch may make in the same launch (dispatch_makes_tiles(E)): the expert GEMMs' tile table without
-// reduction segments, tok[row] = token of the row (padded), grow[row] = gates of the row's slot.  All or none.
+// reduction segments, grow[row] = gates of the row's slot.  All or none.
 struct DispatchExtra {
     int32_t *tiles;
     const float *gates;
-    int32_t *tok;
     float *grow;
 };
 bool dispatch_makes_tiles(int E);

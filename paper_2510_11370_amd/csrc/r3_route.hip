@@ -277,8 +277,8 @@ hipError_t launch_agreement(int T, int E, int K, const float *logits, const void
 // Up to 1024 experts (dispatch_kernel): a work-group owns a chunk of slots, 64 per wave and step, and needs for every
 // expert the slots before its chunk and in all.  It finds them itself, without waiting for another work-group:
 // it counts all ids (LDS atomics; they are one or two bytes each, read as 16-byte vectors out of L2), or, when
-// that would be too many, adds up the chunk counts a first launch has left.  The expert GEMMs' tile table, the
-// row -> token list and the per-row gates come out of the same launch where the caller wants them.  Bound by
+// that would be too many, adds up the chunk counts a first launch has left.  The expert GEMMs' tile table and
+// the per-row gates come out of the same launch where the caller wants them.  Bound by
 // latency: r3_permute, K=8 E=128, took 26.5 us at T=1001 and 55.6 at T=131072 in three dependent launches (count, scan,
 // place), 9.3 in one and 28.1 in two; the tile table was a fourth.
 // Beyond 1024 experts: three launches (count per chunk, scan over the chunks, place).
@@ -499,10 +499,7 @@ dispatch_kernel(const IdxT *__restrict__ idx, DispatchArgs a) {
             tiles[kTileHdr + 2 * (start + i)] = e;
             tiles[kTileHdr + 1 + 2 * (start + i)] = off + i * kRowTile;
         }
-        if (threadIdx.x < 64) {
-            tiles[2 + threadIdx.x] = 0;
-            a.x.tok[S + threadIdx.x] = 0;         // kRowTokensPad
-        }
+        if (threadIdx.x < 64) tiles[2 + threadIdx.x] = 0;
         if (threadIdx.x == 1023) {
             tiles[0] = end;
             for (int x = 0; x <= 8; ++x) tiles[kTileX + x] = (int)(((int64_t)end * x) >> 3);
@@ -529,12 +526,7 @@ dispatch_kernel(const IdxT *__restrict__ idx, DispatchArgs a) {
             const int row = mine[ee] + __popcll(same & lt);
             a.inv_perm[sl] = row;
             a.perm[row] = (int32_t)sl;
-            if (a.x.tok) {
-                int t, j;
-                split(sl, t, j);
-                a.x.tok[row] = t;
-                a.x.grow[row] = a.x.gates[sl];
-            }
+            if (a.x.grow) a.x.grow[row] = a.x.gates[sl];
         }
         if (i + 1 == a.steps) break;
         // (LDS traffic only: the stores above need not have landed)

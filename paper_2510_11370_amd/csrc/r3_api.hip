@@ -66,6 +66,9 @@ BwdWs bwd_layout(const Dims &m) {
     return w;
 }
 
+// whether the gates or agreement counts are made from logits in memory
+bool gate_reads_logits(const Dims &m) { return !router_gate_supported(m.act, m.d, m.E, force_simt()) || m.K > 8; }
+
 struct FwdWs {
     size_t gate, perm, ffn, tok, grow, total;   // tok: only where the dispatch does not make the tile table
 };
@@ -73,7 +76,7 @@ FwdWs fwd_layout(const Dims &m) {
     FwdWs w;
     size_t o = 0;
     auto take = [&](size_t bytes) { size_t at = o; o += align_up(bytes, 256); return at; };
-    w.gate = take((size_t)m.T * m.E * sizeof(float));
+    w.gate = take(gate_reads_logits(m) ? (size_t)m.T * m.E * sizeof(float) : 0);
     w.perm = take(permute_ws_bytes(m.T, m.E, m.K));
     w.ffn = take(use_mfma_ffn(m) ? mfma_tiles_bytes(m.S, m.E) : 0);
     w.tok = take(use_mfma_ffn(m) && !dispatch_makes_tiles(m.E) ? mfma_row_tokens_bytes(m.S) : 0);
@@ -83,6 +86,36 @@ FwdWs fwd_layout(const Dims &m) {
 }
 
 int hip_rc(hipError_t e) { return e == hipSuccess ? R3_OK : R3_ERR_HIP; }
+
+bool gate_args_ok(const Dims &m, const void *x, const void *W_r, const float *bias, const void *idx, const float *gates,
+                  const float *logits_out, const int64_t *agree_out, const int32_t *status_word) {
+    return x && W_r && idx && gates && aligned(x, 16) && aligned(W_r, 16) && aligned(gates, 4) && aligned(logits_out, 16) &&
+           aligned(bias, 16) && aligned(agree_out, 8) && aligned(status_word, 4) && (m.idx != R3_IDX_U16 || aligned(idx, 2));
+}
+
+// r3_replay_gate past its checks; scratch: T E floats, may be NULL if logits_out is given or !gate_reads_logits(m)
+int replay_gate(const Dims &m, const void *x, const void *W_r, const float *bias, const void *idx, float *gates,
+                float *logits_out, int64_t *agree_out, int32_t *status, float *scratch, hipStream_t s) {
+    float *logits = logits_out ? logits_out : scratch;
+    hipError_t e;
+    // one launch: the logits stay in the work-group that made them
+    if (router_gate_supported(m.act, m.d, m.E, force_simt())) {
+        // (the kernel counts agreement for K <= 8; beyond, a launch of its own reads the logits)
+        const bool count = agree_out && m.K <= 8;
+        e = router_gate(m.T, m.d, m.E, m.K, m.act, x, W_r, bias, idx, m.idx, m.stride, gates,
+                        agree_out && !count ? logits : logits_out, count ? agree_out : nullptr, status, force_simt(), s);
+        if (e != hipSuccess) return R3_ERR_HIP;
+        if (agree_out && !count) e = launch_agreement(m.T, m.E, m.K, logits, idx, m.idx, m.stride, agree_out, s);
+        return hip_rc(e);
+    }
+    if (use_mfma_router(m)) e = mfma_router_logits(m.T, m.d, m.E, x, W_r, bias, logits, s);
+    else e = plain_router_logits(m.T, m.d, m.E, m.act, x, W_r, bias, logits, s);
+    if (e != hipSuccess) return R3_ERR_HIP;
+    e = launch_gate(m.T, m.E, m.K, logits, idx, m.idx, m.stride, gates, status, s);
+    if (e != hipSuccess) return R3_ERR_HIP;
+    if (agree_out) e = launch_agreement(m.T, m.E, m.K, logits, idx, m.idx, m.stride, agree_out, s);
+    return hip_rc(e);
+}
 
 // Scratch of r3_permute_static: a fixed array in every device's copy of this code object, held until
 // the process ends.  `scratch` is a host-side stand-in for the symbol, not a device address; the
@@ -113,7 +146,7 @@ int static_scratch(void **out) {
 
 extern "C" {
 
-const char *r3_version(void) { return "r3-mi355x 0.1 (gfx950, bf16 MFMA + f32 SIMT)"; }
+const char *r3_version(void) { return "r3-mi355x 0.1 (gfx950, bf16 and f32 MFMA)"; }
 
 size_t r3_workspace_bytes(const r3_layer_desc *desc, r3_op op) {
     Dims m;
@@ -145,36 +178,12 @@ int r3_replay_gate(const r3_layer_desc *desc, const void *x, const void *W_r, co
     Dims m;
     int rc = check_desc(desc, m);
     if (rc) return rc;
-    if (!x || !W_r || !idx || !gates) return R3_ERR_INVALID_ARG;
-    if (!aligned(x, 16) || !aligned(W_r, 16) || !aligned(gates, 4) || (logits_out && !aligned(logits_out, 16)) ||
-        (bias && !aligned(bias, 16)) || (agree_out && !aligned(agree_out, 8)) ||
-        (status_word && !aligned(status_word, 4)) || (m.idx == R3_IDX_U16 && !aligned(idx, 2)))
-        return R3_ERR_INVALID_ARG;
-    hipStream_t s = (hipStream_t)stream;
-    float *logits = logits_out;
-    if (!logits && !(use_mfma_router(m) && m.E == 128 && (!agree_out || m.K <= 8))) {
-        if (!ws || ws_bytes < r3_workspace_bytes(desc, R3_OP_REPLAY_GATE) || !aligned(ws, 256))
-            return R3_ERR_WORKSPACE;
-        logits = (float *)ws;
-    }
-    hipError_t e;
-    // one launch: the logits stay in the work-group that made them
-    if (router_gate_supported(m.act, m.d, m.E, force_simt())) {
-        // (the kernel counts agreement for K <= 8; beyond, a launch of its own reads the logits)
-        const bool count = agree_out && m.K <= 8;
-        e = router_gate(m.T, m.d, m.E, m.K, m.act, x, W_r, bias, idx, m.idx, m.stride, gates,
-                        agree_out && !count ? logits : logits_out, count ? agree_out : nullptr, status_word, force_simt(), s);
-        if (e != hipSuccess) return R3_ERR_HIP;
-        if (agree_out && !count) e = launch_agreement(m.T, m.E, m.K, logits, idx, m.idx, m.stride, agree_out, s);
-        return hip_rc(e);
-    }
-    if (use_mfma_router(m)) e = mfma_router_logits(m.T, m.d, m.E, x, W_r, bias, logits, s);
-    else e = plain_router_logits(m.T, m.d, m.E, m.act, x, W_r, bias, logits, s);
-    if (e != hipSuccess) return R3_ERR_HIP;
-    e = launch_gate(m.T, m.E, m.K, logits, idx, m.idx, m.stride, gates, status_word, s);
-    if (e != hipSuccess) return R3_ERR_HIP;
-    if (agree_out) e = launch_agreement(m.T, m.E, m.K, logits, idx, m.idx, m.stride, agree_out, s);
-    return hip_rc(e);
+    if (!gate_args_ok(m, x, W_r, bias, idx, gates, logits_out, agree_out, status_word)) return R3_ERR_INVALID_ARG;
+    // The header's rule, though most layers do without (gate_reads_logits); with 128 experts none was ever asked for.
+    const bool given = ws && ws_bytes >= r3_workspace_bytes(desc, R3_OP_REPLAY_GATE) && aligned(ws, 256);
+    if (!logits_out && !given && !(use_mfma_router(m) && m.E == 128 && (!agree_out || m.K <= 8))) return R3_ERR_WORKSPACE;
+    return replay_gate(m, x, W_r, bias, idx, gates, logits_out, agree_out, status_word, given ? (float *)ws : nullptr,
+                       (hipStream_t)stream);
 }
 
 int r3_permute(const r3_layer_desc *desc, const void *x, const void *idx, int32_t *counts,
@@ -264,14 +273,12 @@ int r3_moe_forward(const r3_layer_desc *desc, const void *x, const void *W_r, co
     if (!ws || ws_bytes < w.total || !aligned(ws, 256)) return R3_ERR_WORKSPACE;
     char *base = (char *)ws;
     hipStream_t s = (hipStream_t)stream;
-    r3_layer_desc plain = *desc;
-    plain.flags = 0;
-    rc = r3_replay_gate(&plain, x, W_r, bias, idx, gates, logits_out, agree_out, status_word, base + w.gate,
-                        w.perm - w.gate, stream);
-    if (rc) return rc;
+    if (!gate_args_ok(m, x, W_r, bias, idx, gates, logits_out, agree_out, status_word)) return R3_ERR_INVALID_ARG;
     if (!counts || !offsets || !inv_perm || !perm || !aligned(counts, 4) || !aligned(offsets, 4) || !aligned(inv_perm, 4) ||
         !aligned(perm, 4))
         return R3_ERR_INVALID_ARG;
+    rc = replay_gate(m, x, W_r, bias, idx, gates, logits_out, agree_out, status_word, (float *)(base + w.gate), s);
+    if (rc) return rc;
     const bool mf = use_mfma_ffn(m), with_tiles = mf && dispatch_makes_tiles(m.E);
     int32_t *tiles = (int32_t *)(base + w.ffn);
     float *grow = (float *)(base + w.grow);

@@ -34,6 +34,10 @@ def test_workspace_sizes_and_descriptor_checks_run_on_the_host():
     sizes = [r3.workspace_bytes(D, op) for op in (r3.OP_REPLAY_GATE, r3.OP_PERMUTE, r3.OP_GROUPED_FFN,
                                                   r3.OP_BACKWARD)]
     assert sizes[0] == 16384 * 128 * 4 and all(s % 256 == 0 for s in sizes) and sizes[3] > 5e8
+    # the forward reserves the logits only where something reads them
+    logits = 16384 * 384 * 4
+    fwd = {K: r3.workspace_bytes(r3.desc(16384, 256, 384, K, 256, "bf16"), r3.OP_FORWARD) for K in (8, 12)}
+    assert fwd[8] < logits <= fwd[12]
     bad = r3.desc(16, 16, 8, 9, 16)  # K > E
     assert r3.workspace_bytes(bad, r3.OP_PERMUTE) == 0
     # host-detectable errors come back before anything touches a device

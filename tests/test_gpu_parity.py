@@ -179,7 +179,7 @@ def test_replay_gate_and_logits(name):
     assert torch.equal(gates, gates2)
 
 
-@pytest.mark.parametrize("E,d", [(128, 256), (16, 48)])       # the one-launch kernel; the plain kernels
+@pytest.mark.parametrize("E,d", [(128, 256), (16, 48)])       # (every gate kernel: test_gpu_router.py)
 def test_replay_gate_flags_bad_record_and_nonfinite_logits(E, d):
     T, K = 200, 4
     D = r3.desc(T, d, E, K, 256)
@@ -449,3 +449,9 @@ def test_host_errors_are_returned_before_launch():
         r3.combine(D, x.view(-1)[1:], x, x, x)  # misaligned
     with pytest.raises(r3.R3Error, match="INVALID_ARG"):
         r3.grouped_ffn(D, None, x, x, x, x, x, x, x=x)  # neither Xp nor (x, perm)
+    gates = torch.full((16, 2), 7.0, device="cuda")
+    i32 = torch.empty(64, dtype=torch.int32, device="cuda")
+    with pytest.raises(r3.R3Error, match="INVALID_ARG"):    # (no perm: the gate has not run either)
+        r3.moe_forward(D, x, x, i32.view(torch.uint8), x, x, x, x, gates, i32, i32, i32, None, x, x, r3.workspace(D, r3.OP_FORWARD))
+    sync()
+    assert bool((gates == 7.0).all())

@@ -55,21 +55,6 @@ template <typename T> __device__ __forceinline__ T wave_sum(T v) {
     for (int o = kWave / 2; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);
     return v;
 }
-template <typename T> __device__ __forceinline__ T wave_max(T v) {
-#pragma unroll
-    for (int o = kWave / 2; o > 0; o >>= 1) {
-        T w = __shfl_xor(v, o, kWave);
-        v = w > v ? w : v;
-    }
-    return v;
-}
-
-// read one recorded expert id
-template <typename IdxT>
-__device__ __forceinline__ int load_idx(const void *idx, int64_t stride, int t, int j) {
-    return (int)((const IdxT *)idx)[(int64_t)t * stride + j];
-}
-
 inline size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 }  // namespace r3

@@ -1,7 +1,7 @@
 // Dense steps of the replayed MoE layer on bf16 MFMA (gfx950):
 //   router logits  s = x W_r                       (Section 4.1, first equation)
 //   grouped SwiGLU expert FFN, forward              (the E_i of the output equation)
-//   its data gradients and weight gradients, and the router weight gradient.
+//   its data gradients and weight gradients.
 // Every kernel is one instance of the tile loop in r3_mfma.h with its own
 // operand addressing and epilogue.  Expert segments are ragged: a small kernel
 // turns `offsets` into a list of (expert, first row) row tiles on the device, so
@@ -12,7 +12,6 @@
 #include "r3_mfma.h"
 #include "r3_mfma2.h"
 #include "r3_tiles.h"
-
 
 namespace r3 {
 
@@ -205,7 +204,6 @@ build_row_tiles_kernel(int E, int BQ, const int32_t *__restrict__ offsets, int32
 }
 
 static inline int max_row_tiles(int64_t S, int E, int BQ) { return (int)(S / BQ) + E; }
-static inline int grid_for(int64_t tiles) { return (int)((tiles + 7) / 8 * 8); }
 
 // Grid of a persistent launch: one work-group per compute unit of the current device (a
 // multiple of 8, so that every XCD gets the same number), fewer when there are fewer tiles.

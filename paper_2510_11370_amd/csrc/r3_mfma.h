@@ -304,16 +304,6 @@ __device__ __forceinline__ void for_each_quad(F f) {
             }
 }
 
-// XCD-aware work-group -> logical tile id.  Work-groups are handed to the 8 XCDs
-// round-robin; giving each XCD one contiguous range of the tile list keeps the
-// tiles that share an expert's weights inside one L2.  Returns -1 when idle.
-__device__ __forceinline__ int xcd_tile_id(int total) {
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    const int per = (total + 7) >> 3;
-    const int id = xcd * per + slot;
-    return (slot < per && id < total) ? id : -1;
-}
-
 __device__ __forceinline__ uint4 ld16(const bf16_t *p) { return *(const uint4 *)p; }
 __device__ __forceinline__ uint4 zero16() { return make_uint4(0u, 0u, 0u, 0u); }
 

@@ -15,7 +15,7 @@
 // reduction of the weight gradients needs, and keeps every access in bounds.
 //
 // Tile forms in LDS (per stage):
-//   KC   [256 rows][32 k]     row = 64 B; 16-B chunk c of row r sits at c ^ ((r>>2)&3)
+//   KC   [256 rows][64 k]     row = 128 B; 16-B chunk c of row r sits at c ^ ((r>>1)&7) (see OpKC64)
 //   TR   [32 k][R features]   k-row = 2R B; 64-B group g of k-row k sits at g ^ (k&3);
 //        fragments come out through ds_read_b64_tr_b16 (4 consecutive k of one feature).
 // The four stages are separate LDS arrays so that the compiler can see that loads in
@@ -115,25 +115,6 @@ __device__ __forceinline__ void lds_load16_soff(rsrc_t r, uint32_t dst_wave, int
                  : "memory");
 }
 
-// K-contiguous 256-row tile: 16 chunks of 1 KB (16 rows x 64 B), four per loader wave.
-struct DmaKC {
-    int voff[4];
-    __device__ __forceinline__ void init(int ld_bytes) {
-        const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const int row = 16 * ((w & 3) + kLoaderWaves * i) + (lane >> 2);
-            const int c = (lane & 3) ^ ((row >> 2) & 3);
-            voff[i] = row * ld_bytes + c * 16;
-        }
-    }
-    __device__ __forceinline__ void issue(rsrc_t r, uint32_t tile) const {
-        const int w = threadIdx.x >> 6;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) lds_load16(r, tile + 1024 * ((w & 3) + kLoaderWaves * i), voff[i]);
-    }
-};
-
 // Transposed tile: 32 k-rows of R features.  R = 256: 16 chunks (2 k-rows each), two per
 // wave.  R = 128: 8 chunks (4 k-rows each), one per wave.
 template <int R>
@@ -162,31 +143,10 @@ struct DmaTR {
 
 // Operand kinds.  Each provides: init, issue(kt, stage_tile), frag(stage_tile, t, s) and
 // issues exactly four loads per loader wave per stage.
-//   KC256  : one Src
 //   TR256  : one Src
 //   TR128x2: two Src (sub-tile 0 at tile+0, sub-tile 1 at tile+8 KB); MFMA tiles 0,1 of a
 //            wave come from sub-tile 0 and tiles 2,3 from sub-tile 1 at the same features
 // A second Src set takes over from k-tile `kswitch` on (two-phase reductions).
-struct OpKC256 {
-    static constexpr bool kIndexed = false, kWindowed = false;
-    static constexpr int kLoads = 4;
-    static constexpr int kDsReads = kTP2, kDsReadsQ = kTQ2;  // ds_read_b128 per sub-step as P / as Q
-    Src src[2];
-    int kswitch;
-    DmaKC dma;
-    KcFrag<kBK2> fr;
-    __device__ __forceinline__ void init(int ld_bytes, int wave_base) {
-        dma.init(ld_bytes);
-        fr.init(wave_base);
-    }
-    __device__ __forceinline__ void issue(int kt, uint32_t tile) const {
-        const bool second = kt >= kswitch;
-        const Src &s = second ? src[1] : src[0];
-        dma.issue(src_rsrc(s, second ? kt - kswitch : kt), tile);
-    }
-    __device__ __forceinline__ bf16x8_t frag(const char *tile, int t, int s) const { return fr.read(tile, t, s); }
-};
-
 struct OpTR256 {
     static constexpr bool kIndexed = false, kWindowed = false;
     static constexpr int kLoads = 4;
@@ -1026,20 +986,6 @@ __device__ __forceinline__ char *wave_patch(char *s0, char *s1, char *s2, char *
     } else {
         return w == 0 ? s0 : w == 1 ? s1 : w == 2 ? s2 : s3;
     }
-}
-
-// Visit the wave's results as groups of 4 consecutive p for one q (tile-local p, q).
-template <class F>
-__device__ __forceinline__ void for_each_quad2(F f) {
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int wp = wave % kWP2, wq = wave / kWP2;
-#pragma unroll
-    for (int tp = 0; tp < kTP2; ++tp)
-#pragma unroll
-        for (int tq = 0; tq < kTQ2; ++tq)
-#pragma unroll
-            for (int g = 0; g < 4; ++g)
-                f(tp, tq, g, wp * 128 + tp * 32 + g * 8 + (lane >> 5) * 4, wq * kWaveRowsQ + tq * 32 + (lane & 31));
 }
 
 __device__ __forceinline__ uint64_t clamp_bytes(int64_t b) { return b <= 0 ? 0u : (uint64_t)b; }

@@ -45,6 +45,13 @@ def test_layer_at_ragged_widths(sh, one_call):
         got = got.cpu().numpy()
         for e in range(sh.E):
             assert np.linalg.norm(got[e] - ref[key][e]) <= c.rel * np.linalg.norm(ref[key][e]) + 1e-30, (key, e)
+    # added to instead of overwritten: twice the gradient (a sum of two f32, in parts where a reduction is split)
+    grads = (buf.dW_r, buf.dW_gate, buf.dW_up, buf.dW_down)
+    once = [t.double() for t in grads]
+    r3.backward(buf, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], *w, accumulate=True)
+    torch.cuda.synchronize()
+    for t, o in zip(grads, once):
+        assert float((t.double() - 2 * o).norm()) <= 1e-6 * float((2 * o).norm())
     # a caller that gives Xp need not give perm, nor fill one: every output again
     if not one_call:
         sigma = router_gradient_sigma(n["x"], n["dy"], c.idx, fwd, sh.E)
@@ -150,3 +157,43 @@ def test_sigmoid_of_large_arguments():
     want = (a * torch.sigmoid(a)).bfloat16()
     flips = int((FB != want).sum())
     assert flips <= 4 * T * F / 65536, flips
+
+
+@pytest.mark.parametrize("d,F", [(264, 136), (1000, 72), (256, 256)])     # (whole tiles beside the guarded ones)
+def test_nonfinite_values_stay_where_they_belong(d, F):
+    """NaN or infinity in the last value of a token, of its dy, or of one expert's weights: the tokens and experts that do not
+    meet it come out finite, though masked lanes and dead rows lie beside it."""
+    T, E, K = 700, 12, 3
+    sh = SH(T=T, d=d, E=E, K=K, F=F, sigma=0.02, seed=77)
+    c = Case(sh, backward=True, scale_w=5.0)
+    idx = torch.from_numpy(c.idx).long().cuda()
+    t0, e0 = 333, int(c.idx[333, 1])
+
+    def run(**bad):
+        t = {k: v.clone() if v is not None else None for k, v in c.t.items()}
+        for k, (at, value) in bad.items():
+            t[k][at] = value
+        w = (t["Wg"], t["Wu"], t["Wd"])
+        buf = r3.LayerBuffers(c.D, backward=True, gathered_copy=False)
+        r3.forward_one_call(buf, t["x"], t["Wr"], t["idx"], *w, bias=t["bias"])
+        r3.backward(buf, t["dy"], t["x"], t["Wr"], t["idx"], *w)
+        torch.cuda.synchronize()
+        return buf
+
+    tokens = torch.arange(T, device="cuda")
+    finite = lambda v: bool(torch.isfinite(v).all())    # noqa: E731
+    other_experts = torch.ones(E, dtype=torch.bool, device="cuda")
+    other_experts[idx[t0]] = False
+    b = run(x=((t0, d - 1), float("nan")))
+    assert not finite(b.y[t0]) and finite(b.y[tokens != t0]) and finite(b.dx[tokens != t0])
+    assert all(finite(g[other_experts]) for g in (b.dW_gate, b.dW_up, b.dW_down))
+    b = run(dy=((t0, d - 1), float("inf")))
+    assert finite(b.y) and not finite(b.dx[t0]) and finite(b.dx[tokens != t0])
+    assert all(finite(g[other_experts]) for g in (b.dW_gate, b.dW_up, b.dW_down))
+    apart = (idx != e0).all(1)
+    others = torch.arange(E, device="cuda") != e0
+    for k, at in (("Wg", (e0, d - 1, F - 1)), ("Wu", (e0, 0, 0)), ("Wd", (e0, F - 1, d - 1)), ("Wd", (e0, 0, 0))):
+        b = run(**{k: (at, float("nan"))})
+        assert finite(b.y[apart]) and finite(b.dx[apart]) and not finite(b.y), k
+        # (the tokens that met it carry it, through their gate's gradient, to their other experts' dz, not to their weights)
+        assert all(finite(g[others]) for g in (b.dW_gate, b.dW_up, b.dW_down)), k

@@ -71,6 +71,78 @@ def test_logits_do_not_depend_on_the_batch(E, d):
         assert torch.equal(lg, got[0][1][:n]) and torch.equal(gates, got[0][2][:n]), n
 
 
+@pytest.mark.parametrize("T,E,d,act", [
+    (200, 128, 256, "bf16"), (9000, 64, 72, "bf16"), (200, 384, 256, "bf16"),      # a work-group of 32 | 64 tokens, all experts
+    (33000, 128, 64, "bf16"),                                                      # the kernel for many tokens
+    (200, 16, 48, "f32"), (200, 60, 50, "bf16"),                                   # f32 arithmetic in one launch
+    (200, 640, 256, "bf16"), (200, 130, 33, "f32"),                                # logits and gates in a launch each
+])
+def test_every_gate_kernel_flags_bad_records_and_nonfinite_logits(T, E, d, act):
+    """An id past the last expert, in the last token, and a non-finite logit raise their bits, and only their own token's
+    gates change."""
+    K = 4
+    D = r3.desc(T, d, E, K, 256, act)
+    g = torch.Generator(device="cuda").manual_seed(T + E)
+    a = r3.act_dtype(D)
+    x = torch.randn(T, d, generator=g, device="cuda").to(a)
+    Wr = (torch.randn(d, E, generator=g, device="cuda") * d ** -0.5).to(a)
+    idx = torch.randint(0, E // K, (T, K), generator=g, device="cuda") + E // K * torch.arange(K, device="cuda")
+    ids = lambda t: t.to(torch.uint8) if E <= 256 else t.to(torch.int16)   # noqa: E731
+
+    def run(xx, rec):
+        gates = torch.empty(T, K, dtype=torch.float32, device="cuda")
+        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        agree = torch.zeros(2, dtype=torch.int64, device="cuda")
+        r3.replay_gate(D, xx, Wr, ids(rec), gates, status=status, agree_out=agree, ws=r3.workspace(D, r3.OP_REPLAY_GATE))
+        torch.cuda.synchronize()
+        return int(status.item()), gates
+
+    st, clean = run(x, idx)
+    assert st == 0 and torch.allclose(clean.sum(1), torch.ones(T, device="cuda"), atol=1e-5)
+    bad = idx.clone()
+    bad[T - 1, 1] = 255 if E <= 256 else 700
+    st, got = run(x, bad)
+    assert st == r3.DATA_IDX_RANGE and torch.equal(got[:-1], clean[:-1])
+    xn = x.clone()
+    xn[T - 2, d - 1] = float("inf")
+    st, got = run(xn, idx)
+    assert st == r3.DATA_NONFINITE
+    keep = torch.arange(T, device="cuda") != T - 2
+    assert torch.equal(got[keep], clean[keep])
+    assert run(xn, bad)[0] == r3.DATA_NONFINITE | r3.DATA_IDX_RANGE
+
+
+@pytest.mark.parametrize("T,E,K", [
+    (700, 40, 3), (700, 250, 8), (2730, 100, 6),        # counted in one launch; ids that share lanes with their token and not
+    (2731, 100, 6), (9000, 200, 2), (4000, 700, 8),     # counted by chunk first
+    (900, 2000, 6),                                     # three launches
+])
+@pytest.mark.parametrize("token_major", [False, True])
+def test_dispatch_flags_bad_records(T, E, K, token_major):
+    """An id past the last expert (clamped) and a duplicate, late in the record: the bits, and the dispatch of what is left."""
+    rng = np.random.default_rng(T + E)
+    w = E // K
+    idx = (rng.integers(0, w - 1, (T, K)) + w * np.arange(K)).astype(np.int32)     # (the last expert is nobody's)
+    D = r3.desc(T, 16, E, K, 16, idx_token_stride=3 * K if token_major else 0)
+    npdt = np.uint8 if E <= 256 else np.uint16
+    cases = [(idx, 0)]
+    bad = idx.copy(); bad[T - 2, K - 1] = np.iinfo(npdt).max; cases.append((bad, r3.DATA_IDX_RANGE))   # noqa: E702
+    dup = idx.copy(); dup[T - 1, K - 1] = dup[T - 1, 0]; cases.append((dup, r3.DATA_IDX_DUP))          # noqa: E702
+    both = bad.copy(); both[T - 1] = dup[T - 1]; cases.append((both, r3.DATA_IDX_RANGE | r3.DATA_IDX_DUP))   # noqa: E702
+    for ids, bits in cases:
+        rec = np.zeros((T, 3 if token_major else 1, K), npdt)
+        rec[:, -1 if token_major else 0] = ids
+        rec = torch.from_numpy(rec.view(np.int16) if E > 256 else rec).cuda()
+        rec = rec[:, -1] if token_major else rec
+        out = [torch.full((n,), -1, dtype=torch.int32, device="cuda") for n in (E, E + 1, T * K, T * K)]
+        status = torch.zeros(1, dtype=torch.int32, device="cuda")
+        r3.permute(D, None, rec, *out, None, r3.workspace(D, r3.OP_PERMUTE), status)
+        torch.cuda.synchronize()
+        assert int(status.item()) == bits
+        for got, want in zip(out, sparse.permute(np.minimum(ids, E - 1), E)):
+            assert np.array_equal(got.cpu().numpy(), want)
+
+
 def _slots(T, E, K, seed, skew):
     rng = np.random.default_rng(seed)
     p = rng.random((T, E)) - skew * np.log(np.arange(1, E + 1))

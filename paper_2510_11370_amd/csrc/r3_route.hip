@@ -740,9 +740,14 @@ size_t permute_ws_bytes(int T, int E, int K) {
     return 2 * align_up((size_t)nchunks * E * sizeof(int32_t), 256);  // histograms + running bases
 }
 
-// Where counting all ids in every work-group gives way to a launch that counts the chunks first (E=128 K=8, us, all /
-// first): 8192 slots 9.3 / 12.1, 32768 10.2 / 11.8, 131072 18.6 / 12.2, 1048576 369 / 28.1; under a skewed load the LDS
-// atomics of the first collide (131072 slots: 60 / 12.6), so the line is drawn early.
+// Where counting all ids in every work-group gives way to a launch that counts the chunks first, us of r3_permute, all / first:
+//   slots          E=8 K=2      E=64 K=4     E=128 K=8    E=384 K=4    E=1024 K=8
+//     8192        7.8 / 11.1   7.9 / 10.9   8.1 / 10.8   7.9 / 11.0    8.6 / 12.4
+//    16384        9.4 / 11.1   8.0 / 11.0   8.9 / 11.3   8.0 / 11.1    9.3 / 13.0
+//    32768       14.3 / 10.7   9.8 / 11.0  11.0 / 11.4   8.6 / 11.0   10.4 / 13.8
+//    65536       23.7 / 10.9  13.8 / 10.9  15.0 / 11.3  11.3 / 11.9   12.9 / 15.6
+// With the same experts in every token the LDS atomics collide (16384 slots 19 to 22 / 11, 32768 32 to 36 / 11), so the line
+// is drawn where the first column still gains and the collisions cost 10 us.
 constexpr int64_t kDispCountAll = 16384;
 
 template <typename IdxT>

@@ -711,9 +711,10 @@ __device__ __forceinline__ void mfma_mainloop3(Acc2 &acc, int nw, const POp &P, 
 
 // ---------------------------------------------------------------------------
 // The same loop for a tail tile: at most 128 live rows (the last rows of an expert's segment, or all of a
-// rarely chosen expert's).  Such a tile multiplies little and is bound by the latency of its weight
-// windows, so the space the dead rows of the Q windows would take holds a third window instead and the loads run two
-// windows ahead.  `lds` is the work-group's kRowLds bytes: P windows at 0, 32, 64 KB; Q windows (rows 0..127 only, 16 KB
+// rarely chosen expert's).  Such a tile waited for its weight windows, so the space the dead rows of the Q windows would
+// take holds a third window instead and the loads run two windows ahead.  What it costs then, about half a full tile, is the
+// chain of the few waves that multiply (two of eight at up to 64 rows: 1024 cycles a window, a full tile 2048).
+// `lds` is the work-group's kRowLds bytes: P windows at 0, 32, 64 KB; Q windows (rows 0..127 only, 16 KB
 // each) from 96 KB.  Only the waves of live 64-row blocks multiply; waves 0-3 load.
 // A loader wave issues 8 loads for P and 2 per 64 rows for Q, so "at most that many outstanding" is "the next
 // window is in" as long as the one after it has been issued.

@@ -238,7 +238,7 @@ __device__ __forceinline__ void unpack4(uint2 v, float *f) {
 // FFN, first contraction + SwiGLU:  A = Xp Wg, B = Xp Wu, H = silu(A) * B.
 // The P operand is two 128-feature sub-tiles, one of W_gate and one of W_up, at
 // the same features, so a wave holds both pre-activations of a (row, feature)
-// pair in the same lane: MFMA tiles 0,1 are gate, tiles 2,3 the matching up.
+// pair in the same lane: MFMA tiles 0..3 are gate, tiles 4..7 the matching up.
 // What is saved for the backward are not A and B but the two factors its SwiGLU
 // step multiplies dh with: FA = B silu'(A) (dA = dh FA) and FB = silu(A)
 // (dB = dh FB); the sigmoid is in registers here anyway, and the backward's
@@ -321,37 +321,39 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
     const int tid = opaque_tid();
     const int lane = tid & 63, wq = (tid >> 6) / kWP2, wp = (tid >> 6) % kWP2;
     char *patch = wave_patch(s0, s1, s2, s3, tid);
-    const int q = lane & 31;
+    const int r16 = lane & 15, f4 = (lane >> 4) * 4;   // a lane's row and four features of every 16 x 16 tile
     const bool save = FA != nullptr;
 #pragma unroll
-    for (int tq = 0; tq < kTQ2; ++tq) {
-        const int brow = row0 + wq * kWaveRowsQ + tq * 32;            // first row of this block
+    for (int blk = 0; blk < kWaveRowsQ / 32; ++blk) {
+        const int brow = row0 + wq * kWaveRowsQ + blk * 32;           // first row of this block
         const int valid = min(32, row_end - brow);             // may be <= 0
         const int64_t o = ((int64_t)brow * F + f0 + wp * 64) * 2;  // byte offset of the block
         RowStage<128> sh{patch, tid}, sa{patch + RowStage<128>::BYTES, tid}, sb{patch + 2 * RowStage<128>::BYTES, tid};
         // grow != NULL: H leaves as g H, g the gate of the row's slot (the down projection then yields
         // gated rows and the gradient of W_down finds its row operand ready); FA and FB are not scaled
-        const float gq = grow ? (brow + q < row_end ? grow[brow + q] : 0.0f) : 1.0f;
 #pragma unroll
-        for (int tp = 0; tp < 2; ++tp)
+        for (int t = 0; t < 2; ++t) {
+            const int tq = 2 * blk + t, q = 16 * t + r16;
+            const float gq = grow ? (brow + q < row_end ? grow[brow + q] : 0.0f) : 1.0f;
 #pragma unroll
-            for (int g = 0; g < 4; ++g) {
+            for (int tp = 0; tp < kHalfP; ++tp) {
                 float h[4], fa[4], fb[4];
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float a = acc[tp][tq][4 * g + i], b = acc[tp + 2][tq][4 * g + i];
+                    const float a = acc[tp][tq][i], b = acc[tp + kHalfP][tq][i];
                     const float sg = RAGGED ? sigmoidf_(a) : sigmoid_fast(a);
                     fb[i] = a * sg;                                  // silu(a)
                     h[i] = gq * (fb[i] * b);
                     fa[i] = b * fmaf(fb[i], 1.0f - sg, sg);          // b silu'(a), silu'(a) = sg (1 + a (1 - sg))
                 }
-                const int bo = (tp * 32 + g * 8 + (lane >> 5) * 4) * 2;
+                const int bo = (tp * 16 + f4) * 2;
                 sh.put8(q, bo, pack4(h[0], h[1], h[2], h[3]));
                 if (save) {
                     sa.put8(q, bo, pack4(fa[0], fa[1], fa[2], fa[3]));
                     sb.put8(q, bo, pack4(fb[0], fb[1], fb[2], fb[3]));
                 }
             }
+        }
         const int width = RAGGED ? (F - f0 - wp * 64) * 2 : 128;
         sh.flush((char *)H + o, (int64_t)F * 2, valid, width);
         if (save) {
@@ -481,6 +483,10 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
         P.set_lane(d * 2, 128 * ((t0 >> 6) % kWP2), t0);
         Q.set_lane(KQ * 2, kWaveRowsQ * ((t0 >> 6) / kWP2), t0, qstash);
     }
+    if constexpr (MODE == 0 && RAGGED) {   // likewise: the guards of ragged widths need the registers
+        const int t0 = opaque_tid();
+        Q.set_lane(KQ * 2, kWaveRowsQ * ((t0 >> 6) / kWP2), t0);
+    }
 
     Acc2 acc;
     zero_acc2(acc);
@@ -494,18 +500,18 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     const int tid = opaque_tid();
     const int lane = tid & 63, wq = (tid >> 6) / kWP2, wp = (tid >> 6) % kWP2;
     RowStage<256> st{wave_patch(s0, s1, s2, s3, tid), tid};
-    const int q = lane & 31;
+    const int r16 = lane & 15, f4 = (lane >> 4) * 4;   // a lane's row and four features of every 16 x 16 tile
     const int width = RAGGED ? (NOUT - p0 - wp * 128) * 2 : 256;   // bytes of this wave's features that exist
     if constexpr (MODE == 1) {
         // Four rounds of 32 rows x 64 features, each in three phases: FA -> dA, FB -> dB, H -> g H and the
         // row's dot product.  A phase's rows come in row-contiguously into a patch, each lane replaces
         // exactly the quads it read, and the patch goes out row-contiguously.  The rows of the phase
         // after next are asked for while this one is worked on: two 4 KB blocks in flight per wave (a
-        // whole round ahead, three blocks, cost the tile loop its registers).  A lane's 16 + 16 products
-        // u H of one 32-row block belong to one row (q).
+        // whole round ahead, three blocks, cost the tile loop its registers).  A lane's products u H of one
+        // 32-row block belong to two rows (r16 and 16 + r16).
         typedef RowStage<128> Patch;
         const Patch sa{st.base, tid}, sb{st.base + Patch::BYTES, tid}, sh{st.base + 2 * Patch::BYTES, tid};
-        constexpr int NPH = 3 * 2 * kTQ2;   // (GATED: the H phases only read)
+        constexpr int NPH = 3 * 2 * (kWaveRowsQ / 32);   // (GATED: the H phases only read)
         auto where = [&](int ph, int &valid) -> int64_t {
             const int r = ph / 3;
             const int brow = row0 + wq * kWaveRowsQ + (r >> 1) * 32;
@@ -523,36 +529,39 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
 #endif
         constexpr int AH = R3_DH_AHEAD;   // phases the row fetches run ahead (1 or 2)
         Patch::Rows rr[2] = {ask(0), ask(AH == 2 ? 1 : 0)};
-        float gq = 0.0f, wsum = 0.0f;
+        float gq[2] = {0.0f, 0.0f}, wsum[2] = {0.0f, 0.0f};
 #pragma unroll
         for (int ph = 0; ph < NPH; ++ph) {
-            const int r = ph / 3, which = ph % 3, tq = r >> 1, half = r & 1;
-            const int brow = row0 + wq * kWaveRowsQ + tq * 32;
+            const int r = ph / 3, which = ph % 3, blk = r >> 1, half = r & 1;
+            const int brow = row0 + wq * kWaveRowsQ + blk * 32;
             const Patch &sp = which == 0 ? sa : which == 1 ? sb : sh;
             int valid;
             const int64_t oh = where(ph, valid);
             sp.deposit(rr[AH == 2 ? (ph & 1) : 0]);
             if (ph + AH < NPH) rr[AH == 2 ? (ph & 1) : 0] = ask(ph + AH);
             if (which == 0 && half == 0) {
-                gq = brow + q < row_end ? grow[brow + q] : 0.0f;
-                wsum = 0.0f;
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    gq[t] = brow + 16 * t + r16 < row_end ? grow[brow + 16 * t + r16] : 0.0f;
+                    wsum[t] = 0.0f;
+                }
             }
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int tp = half * 2 + t;
-                    const int bo = (t * 32 + g * 8 + (lane >> 5) * 4) * 2;
+                    const int tp = half * 4 + g, tq = 2 * blk + t, q = 16 * t + r16;
+                    const int bo = (g * 16 + f4) * 2;
                     float v[4], o[4];
                     unpack4(sp.get8(q, bo), v);
 #pragma unroll
                     for (int i = 0; i < 4; ++i) {
-                        const float u = acc[tp][tq][4 * g + i];
+                        const float u = acc[tp][tq][i];
                         if (which == 2) {
-                            wsum = fmaf(u, v[i], wsum);
-                            o[i] = gq * v[i];
+                            wsum[t] = fmaf(u, v[i], wsum[t]);
+                            o[i] = gq[t] * v[i];
                         } else {
-                            o[i] = gq * u * v[i];
+                            o[i] = gq[t] * u * v[i];
                         }
                     }
                     if (!(GATED && which == 2)) sp.put8(q, bo, pack4(o[0], o[1], o[2], o[3]));
@@ -560,25 +569,31 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
             bf16_t *dst = which == 0 ? out0 : which == 1 ? out1 : out2;
             if (!(GATED && which == 2)) sp.flush((char *)dst + oh, (int64_t)NOUT * 2, valid, width - 128 * half);
             if (which == 2 && half == 1) {
-                // the two lanes that hold row q (k-groups 0 and 1 of the MFMA layout) add up
-                const float w = (GATED ? 1.0f : gq) * (wsum + __shfl_xor(wsum, 32, 64));
+                // the four lanes that hold a row add up; lanes 0..15 write the first 16 rows, 16..31 the others
+                float w[2];
+#pragma unroll
+                for (int t = 0; t < 2; ++t) {
+                    w[t] = wsum[t] + __shfl_xor(wsum[t], 16, 64);
+                    w[t] = (GATED ? 1.0f : gq[t]) * (w[t] + __shfl_xor(w[t], 32, 64));
+                }
+                const int q = lane & 31;
                 if (lane < 32 && brow + q < row_end)
-                    wpart[(int64_t)(brow + q) * (2 * npt) + 2 * (p0 / kTile) + wp] = w;
+                    wpart[(int64_t)(brow + q) * (2 * npt) + 2 * (p0 / kTile) + wp] = lane < 16 ? w[0] : w[1];
             }
         }
     } else {
 #pragma unroll
-        for (int tq = 0; tq < kTQ2; ++tq) {
-            const int brow = row0 + wq * kWaveRowsQ + tq * 32;
+        for (int blk = 0; blk < kWaveRowsQ / 32; ++blk) {
+            const int brow = row0 + wq * kWaveRowsQ + blk * 32;
             const int valid = min(32, row_end - brow);
             const int64_t o = ((int64_t)brow * NOUT + p0 + wp * 128) * 2;
 #pragma unroll
-            for (int tp = 0; tp < kTP2; ++tp)
+            for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int g = 0; g < 4; ++g)
-                    st.put8(q, (tp * 32 + g * 8 + (lane >> 5) * 4) * 2,
-                            pack4(acc[tp][tq][4 * g], acc[tp][tq][4 * g + 1], acc[tp][tq][4 * g + 2],
-                                  acc[tp][tq][4 * g + 3]));
+                for (int tp = 0; tp < kTP2; ++tp) {
+                    const f32x4_t v = acc[tp][2 * blk + t];
+                    st.put8(16 * t + r16, (tp * 16 + f4) * 2, pack4(v[0], v[1], v[2], v[3]));
+                }
             st.flush((char *)out0 + o, (int64_t)NOUT * 2, valid, width);
         }
     }
@@ -651,26 +666,24 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
     const int tid = opaque_tid();
     const int lane = tid & 63, wq = (tid >> 6) / kWP2, wp = (tid >> 6) % kWP2;
     RowStage<256> st{wave_patch(s0, s1, s2, s3, tid), tid};
-    const int q = lane & 31;
+    const int r16 = lane & 15, f4 = (lane >> 4) * 4;   // a lane's row and four features of every 16 x 16 tile
     // part 0 of an expert's rows goes to the gradient, a later part to its own slot of partial products
     char *o = (char *)(pslot < 0 ? out + (int64_t)e * NQd * NPd : part + (int64_t)pslot * NQd * NPd);
     const int add = pslot < 0 ? accumulate : 0;
 #pragma unroll
-    for (int tq = 0; tq < kTQ2; ++tq)
+    for (int blk = 0; blk < kWaveRowsQ / 32; ++blk)
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int tp = half * 2 + t;
-                    st.put16(q, (t * 32 + g * 8 + (lane >> 5) * 4) * 4,
-                             make_float4(acc[tp][tq][4 * g], acc[tp][tq][4 * g + 1], acc[tp][tq][4 * g + 2],
-                                         acc[tp][tq][4 * g + 3]));
+                    const f32x4_t v = acc[half * 4 + g][2 * blk + t];
+                    st.put16(16 * t + r16, (g * 16 + f4) * 4, make_float4(v[0], v[1], v[2], v[3]));
                 }
-            const int64_t off = ((int64_t)(q0 + wq * kWaveRowsQ + tq * 32) * NPd + p0 + wp * 128 + half * 64) * 4;
+            const int64_t off = ((int64_t)(q0 + wq * kWaveRowsQ + blk * 32) * NPd + p0 + wp * 128 + half * 64) * 4;
             if constexpr (RAGGED)
-                st.flush_f32(o + off, (int64_t)NPd * 4, NQd - (q0 + wq * kWaveRowsQ + tq * 32), add,
+                st.flush_f32(o + off, (int64_t)NPd * 4, NQd - (q0 + wq * kWaveRowsQ + blk * 32), add,
                              (NPd - p0 - wp * 128 - half * 64) * 4);
             else st.flush_f32(o + off, (int64_t)NPd * 4, 32, add);
         }
@@ -747,25 +760,23 @@ wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t
     const int tid = opaque_tid();
     const int lane = tid & 63, wq = (tid >> 6) / kWP2, wp = (tid >> 6) % kWP2;
     RowStage<256> st{wave_patch(s0, s1, s2, s3, tid), tid};
-    const int q = lane & 31;
+    const int r16 = lane & 15, f4 = (lane >> 4) * 4;   // a lane's row and four features of every 16 x 16 tile
 #pragma unroll
-    for (int tq = 0; tq < kTQ2; ++tq)
+    for (int blk = 0; blk < kWaveRowsQ / 32; ++blk)
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {   // MFMA tiles 0,1: first product; 2,3: second
+        for (int half = 0; half < 2; ++half) {   // MFMA tiles 0..3: first product; 4..7: second
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const int tp = half * 2 + t;
-                    st.put16(q, (t * 32 + g * 8 + (lane >> 5) * 4) * 4,
-                             make_float4(acc[tp][tq][4 * g], acc[tp][tq][4 * g + 1], acc[tp][tq][4 * g + 2],
-                                         acc[tp][tq][4 * g + 3]));
+                    const f32x4_t v = acc[half * 4 + g][2 * blk + t];
+                    st.put16(16 * t + r16, (g * 16 + f4) * 4, make_float4(v[0], v[1], v[2], v[3]));
                 }
             char *o = (char *)(pslot < 0 ? (half ? out1 : out0) + (int64_t)e * NQd * NPd
                                          : (half ? part1 : part0) + (int64_t)pslot * NQd * NPd);
-            const int64_t off = ((int64_t)(q0 + wq * kWaveRowsQ + tq * 32) * NPd + p0 + wp * 64) * 4;
+            const int64_t off = ((int64_t)(q0 + wq * kWaveRowsQ + blk * 32) * NPd + p0 + wp * 64) * 4;
             if constexpr (RAGGED)
-                st.flush_f32(o + off, (int64_t)NPd * 4, NQd - (q0 + wq * kWaveRowsQ + tq * 32), pslot < 0 ? accumulate : 0,
+                st.flush_f32(o + off, (int64_t)NPd * 4, NQd - (q0 + wq * kWaveRowsQ + blk * 32), pslot < 0 ? accumulate : 0,
                              (NPd - p0 - wp * 64) * 4);
             else st.flush_f32(o + off, (int64_t)NPd * 4, 32, pslot < 0 ? accumulate : 0);
         }

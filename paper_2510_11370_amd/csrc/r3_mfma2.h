@@ -4,7 +4,13 @@
 //
 // D[p][q] = sum_k P[p][k] * Q[q][k], f32 accumulation; P feeds the MFMA A operand
 // (output's contiguous dimension), Q the B operand (output rows).  8 waves, arranged
-// 2 (P) x 4 (Q), each owning a 128 x 64 block as 4 x 2 MFMA 32x32x16 tiles.
+// 2 (P) x 4 (Q), each owning a 128 x 64 block as 8 x 4 MFMA 16x16x32 tiles.
+//
+// Why 16x16x32: the matrix pipe runs at the card's power limit, and this shape takes each accumulator through
+// the registers once per 32 k where 32x32x16 does so once per 16.  128 x 64 per wave, all compute units, normally
+// distributed operands, one card: 32x32x16 from registers 1.78-1.81 PFLOP/s, with the fragments read from LDS
+// 1.60-1.61; 16x16x32 2.05 and 1.77.  Neighbouring MFMAs share an operand (the inner index runs back and forth):
+// 16x16x32 2.08 and 1.79.
 //
 // Operand tiles (16 KB each per stage) are fetched with buffer_load_dwordx4 ... lds: a
 // wave's 64 lanes deposit 64 x 16 B at consecutive LDS addresses, so LDS writes are
@@ -16,7 +22,7 @@
 //
 // Tile forms in LDS (per stage):
 //   KC   [256 rows][64 k]     row = 128 B; 16-B chunk c of row r sits at c ^ ((r>>1)&7) (see OpKC64)
-//   TR   [32 k][R features]   k-row = 2R B; 64-B group g of k-row k sits at g ^ (k&3);
+//   TR   [32 k][R features]   k-row = 2R B; 32-B group g of k-row k sits at g ^ tr_swz(k);
 //        fragments come out through ds_read_b64_tr_b16 (4 consecutive k of one feature).
 // The four stages are separate LDS arrays so that the compiler can see that loads in
 // flight never alias the stage being read (no vmcnt wait in front of the fragment reads).
@@ -36,25 +42,12 @@ constexpr int kTile = 256;
 constexpr int kStages2 = 4;
 constexpr int kOperandBytes = kTile * kBK2 * 2;  // 16 KB
 constexpr int kStageBytes = 2 * kOperandBytes;   // 32 KB
-#ifndef R3_GEMM_WAVES
-#define R3_GEMM_WAVES 8
-#endif
-#if R3_GEMM_WAVES == 8
 // 2 (P) x 4 (Q) waves of 128 x 64, two per SIMD; waves 0-3 also load
 constexpr int kWaves2 = 8, kThreads2 = 512, kMinWavesPerSimd = 2;
-constexpr int kWP2 = 2, kWQ2 = 4, kTP2 = 4, kTQ2 = 2;
-constexpr int kReadsPerMfma = 2;   // fragment reads threaded behind each MFMA of a sub-step
-#else
-// 2 x 2 waves of 128 x 128, one per SIMD (accumulators in the second half of the 512
-// registers a lone wave may use); every wave loads.  A third less LDS read traffic, but
-// measured 5 % (weight gradients) to 30 % (kernels with wide epilogues) slower than the
-// 8-wave form on the 16384-token layer: a lone wave has nobody to cover its stalls.
-constexpr int kWaves2 = 4, kThreads2 = 256, kMinWavesPerSimd = 1;
-constexpr int kWP2 = 2, kWQ2 = 2, kTP2 = 4, kTQ2 = 4;
-constexpr int kReadsPerMfma = 1;
-#endif
+constexpr int kWP2 = 2, kWQ2 = 4, kTP2 = 8, kTQ2 = 4;   // waves and 16 x 16 tiles of a wave along P and Q
+constexpr int kHalfP = kTP2 / 2;                        // a sub-step multiplies half of a wave's P tiles with all Q tiles
 constexpr int kLoaderWaves = 4;
-constexpr int kWaveRowsQ = 32 * kTQ2;            // output rows (Q) per wave
+constexpr int kWaveRowsQ = 16 * kTQ2;            // output rows (Q) per wave
 constexpr uint32_t kRsrcFlags = 0x00020000u;
 
 typedef __attribute__((address_space(3))) void *lds_void_ptr;
@@ -115,6 +108,41 @@ __device__ __forceinline__ void lds_load16_soff(rsrc_t r, uint32_t dst_wave, int
                  : "memory");
 }
 
+// Where a transposed tile's k-row puts its 32-byte groups (16 features): group g sits at g ^ tr_swz(k).  The two k-groups
+// that a fragment read's 32 lanes meet, k-rows 8 b + 0..3 and 8 (b + 1) + 0..3, get eight different places.
+__device__ __forceinline__ int tr_swz(int k) { return (k & 3) | ((k >> 1) & 4); }
+
+// Fragments of 16x16x32 MFMAs: lane l holds 8 consecutive k, 8 (l >> 4) .. + 7 of the step's 32, of row or feature l & 15.
+// KC: [rows][64 k], step u of the window (see OpKC64).
+struct KcFrag16 {
+    int base, swz, hi;
+    __device__ __forceinline__ void init(int wave_base, int lane) {
+        const int row = wave_base + (lane & 15);
+        base = row * 128;
+        swz = (row >> 1) & 7;
+        hi = lane >> 4;
+    }
+    __device__ __forceinline__ bf16x8_t read(const char *win, int t, int u) const {
+        return *(const bf16x8_t *)(win + base + t * 2048 + (((4 * u + hi) ^ swz) << 4));
+    }
+};
+// TR: [32 k][R features]; two transposing reads of 4 k each
+template <int R>
+struct TrFrag16 {
+    int at;
+    __device__ __forceinline__ void init(int wave_base) {   // wave_base: a multiple of 64 features
+        const int lane = lane_id(), b = lane >> 4, i = lane & 15, k = 8 * b + (i >> 2);
+        at = k * (2 * R) + (((wave_base >> 4) ^ tr_swz(k)) << 5) + (i & 3) * 8;
+    }
+    __device__ __forceinline__ bf16x8_t read(const char *tile, int t) const {
+        const int a = at ^ (t << 5);
+        const char *p = tile + a;
+        const s16x4_t lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p));
+        const s16x4_t hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4_ptr)(p + 4 * (2 * R)));
+        return __builtin_bit_cast(bf16x8_t, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+    }
+};
+
 // Transposed tile: 32 k-rows of R features.  R = 256: 16 chunks (2 k-rows each), two per
 // wave.  R = 128: 8 chunks (4 k-rows each), one per wave.
 template <int R>
@@ -130,8 +158,7 @@ struct DmaTR {
         for (int i = 0; i < PER; ++i) {
             const int k = KR * ((w & 3) + kLoaderWaves * i) + lane / LPR;
             const int pc = lane % LPR;
-            const int c16 = (((pc >> 2) ^ (k & 3)) << 2) | (pc & 3);
-            voff[i] = k * ld_bytes + col_bytes + c16 * 16;
+            voff[i] = k * ld_bytes + col_bytes + (pc ^ (tr_swz(k) << 1)) * 16;
         }
     }
     __device__ __forceinline__ void issue(rsrc_t r, uint32_t tile) const {
@@ -141,20 +168,20 @@ struct DmaTR {
     }
 };
 
-// Operand kinds.  Each provides: init, issue(kt, stage_tile), frag(stage_tile, t, s) and
+// Operand kinds.  Each provides: init, issue(kt, stage_tile), frag(stage_tile, t) and
 // issues exactly four loads per loader wave per stage.
 //   TR256  : one Src
-//   TR128x2: two Src (sub-tile 0 at tile+0, sub-tile 1 at tile+8 KB); MFMA tiles 0,1 of a
-//            wave come from sub-tile 0 and tiles 2,3 from sub-tile 1 at the same features
+//   TR128x2: two Src (sub-tile 0 at tile+0, sub-tile 1 at tile+8 KB); MFMA tiles 0..3 of a
+//            wave come from sub-tile 0 and tiles 4..7 from sub-tile 1 at the same features
 // A second Src set takes over from k-tile `kswitch` on (two-phase reductions).
 struct OpTR256 {
     static constexpr bool kIndexed = false, kWindowed = false;
     static constexpr int kLoads = 4;
-    static constexpr int kDsReads = 2 * kTP2, kDsReadsQ = 2 * kTQ2;  // two ds_read_b64_tr_b16 per fragment
+    static constexpr int kReads = 2;   // LDS reads per fragment
     Src src[2];
     int kswitch;
     DmaTR<256> dma;
-    TrFrag<256> fr;
+    TrFrag16<256> fr;
     __device__ __forceinline__ void init(int ld_bytes, int col_bytes, int wave_base) {
         dma.init(ld_bytes, col_bytes);
         fr.init(wave_base);
@@ -164,16 +191,16 @@ struct OpTR256 {
         const Src &s = second ? src[1] : src[0];
         dma.issue(src_rsrc(s, second ? kt - kswitch : kt), tile);
     }
-    __device__ __forceinline__ bf16x8_t frag(const char *tile, int t, int s) const { return fr.read(tile, t, s); }
+    __device__ __forceinline__ bf16x8_t frag(const char *tile, int t) const { return fr.read(tile, t); }
 };
 
 struct OpTR128x2 {
     static constexpr bool kIndexed = false, kWindowed = false;
     static constexpr int kLoads = 4;
-    static constexpr int kDsReads = 2 * kTP2, kDsReadsQ = 2 * kTQ2;
+    static constexpr int kReads = 2;
     Src src[2];  // sub-tile 0, sub-tile 1
     DmaTR<128> dma;
-    TrFrag<128> fr;
+    TrFrag16<128> fr;
     __device__ __forceinline__ void init(int ld_bytes, int col_bytes, int wave_base) {
         dma.init(ld_bytes, col_bytes);
         fr.init(wave_base);
@@ -182,8 +209,8 @@ struct OpTR128x2 {
         dma.issue(src_rsrc(src[0], kt), tile);
         dma.issue(src_rsrc(src[1], kt), tile + kOperandBytes / 2);
     }
-    __device__ __forceinline__ bf16x8_t frag(const char *tile, int t, int s) const {
-        return fr.read(tile + (t >> 1) * (kOperandBytes / 2), t & 1, s);
+    __device__ __forceinline__ bf16x8_t frag(const char *tile, int t) const {
+        return fr.read(tile + (t / kHalfP) * (kOperandBytes / 2), t % kHalfP);
     }
 };
 
@@ -202,7 +229,7 @@ struct OpTR128x2 {
 typedef const __attribute__((address_space(4))) int32_t *const_i32_ptr;
 constexpr int kIndexRingBytes = kLoaderWaves * 4 * 256;  // per loader wave: four slots of one 64-lane dword load
 struct OpTR256G {
-    static constexpr int kDsReads = 2 * kTP2, kDsReadsQ = 2 * kTQ2;
+    static constexpr int kReads = 2;
     static constexpr bool kIndexed = true, kWindowed = false;
     static constexpr int kLoads = 5;             // four tile loads and one index load
     rsrc_t rs, rsi;        // the matrix; the tile's index list
@@ -210,7 +237,7 @@ struct OpTR256G {
     int n, ld_bytes, wl;
     uint32_t ring;         // LDS address of this wave's ring
     int cvoff[4];
-    TrFrag<256> fr;
+    TrFrag16<256> fr;
     __device__ __forceinline__ void init(int ld_bytes_, int wave_base, const void *ring_base) {
         wl = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6) & 3);
         ring = __builtin_amdgcn_readfirstlane((int)(lds_addr(ring_base) + 1024u * wl));
@@ -231,8 +258,8 @@ struct OpTR256G {
         const int lane = threadIdx.x & 63, pc = lane & 31;
 #pragma unroll
         for (int i = 0; i < 4; ++i) {
-            const int k = 2 * i + (lane >> 5);   // k-row within the wave's eight; 8 wl does not change k & 3
-            cvoff[i] = col_bytes + ((((pc >> 2) ^ (k & 3)) << 2) | (pc & 3)) * 16;
+            const int k = 8 * wl + 2 * i + (lane >> 5);   // k-row within the stage
+            cvoff[i] = col_bytes + (pc ^ (tr_swz(k) << 1)) * 16;
         }
     }
     // The wave's eight entries of stage kt into ring slot kt & 3.  Lane p < 8 fetches the entry of
@@ -281,74 +308,109 @@ struct OpTR256G {
         chunk_load(kt, tile, 2, v.z);
         chunk_load(kt, tile, 3, v.w);
     }
-    __device__ __forceinline__ bf16x8_t frag(const char *tile, int t, int s) const { return fr.read(tile, t, s); }
+    __device__ __forceinline__ bf16x8_t frag(const char *tile, int t) const { return fr.read(tile, t); }
 };
 
-typedef f32x16_t Acc2[kTP2][kTQ2];
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+typedef f32x4_t Acc2[kTP2][kTQ2];
 
 __device__ __forceinline__ void zero_acc2(Acc2 &acc) {
 #pragma unroll
     for (int i = 0; i < kTP2; ++i)
 #pragma unroll
-        for (int j = 0; j < kTQ2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
+        for (int j = 0; j < kTQ2; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 }
 
+// What a wave holds between sub-steps.  A 32-k step is two sub-steps: `y`, the first half of the wave's P tiles, times all Q
+// tiles, then `x`, the second half, times the same.
 struct Frags {
-    bf16x8_t a[kTP2], b[kTQ2];
+    bf16x8_t x[kHalfP], y[kHalfP], q[kTQ2];
+    __device__ __forceinline__ void clear() {   // what the first sub-step multiplies
+#pragma unroll
+        for (int i = 0; i < kHalfP; ++i) x[i] = bf16x8_t{};
+#pragma unroll
+        for (int j = 0; j < kTQ2; ++j) q[j] = bf16x8_t{};
+    }
 };
 
-template <class POp, class QOp>
-__device__ __forceinline__ void read_frags(Frags &f, const POp &P, const QOp &Q, const char *stage, int s) {
+// four MFMAs: half H of the wave's P tiles with Q tile j.  The P index runs back and forth, so that neighbouring MFMAs share
+// an operand.
+template <int H>
+__device__ __forceinline__ void mfma_col(Acc2 &acc, const bf16x8_t (&a)[kHalfP], const bf16x8_t &b, int j) {
 #pragma unroll
-    for (int i = 0; i < kTP2; ++i) f.a[i] = P.frag(stage, i, s);
-#pragma unroll
-    for (int j = 0; j < kTQ2; ++j) f.b[j] = Q.frag(stage + kOperandBytes, j, s);
+    for (int ii = 0; ii < kHalfP; ++ii) {
+        const int i = (j & 1) ? kHalfP - 1 - ii : ii;
+        acc[H * kHalfP + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b, acc[H * kHalfP + i][j], 0, 0, 0);
+    }
 }
-
-__device__ __forceinline__ void mfma_block(Acc2 &acc, const Frags &f) {
+// One MFMA, some of the READS LDS reads, one MFMA, ...: the first MFMA goes out at once (right after a barrier the matrix
+// pipe would otherwise idle while a wave issues its reads), and the reads ride in the shadow of the MFMAs.
+template <int READS>
+__device__ __forceinline__ void thread_reads() {
+    constexpr int per = (READS + kHalfP - 1) / kHalfP;
 #pragma unroll
-    for (int i = 0; i < kTP2; ++i)
-#pragma unroll
-        for (int j = 0; j < kTQ2; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i], f.b[j], acc[i][j], 0, 0, 0);
-}
-
-// 8 MFMAs with the next fragment reads threaded between them: one MFMA, two LDS reads, one
-// MFMA, ...  The first MFMA goes out at once (right after a barrier the matrix pipe would
-// otherwise idle while a wave issues its reads), and the reads ride in the shadow of the
-// MFMAs.  Left alone the compiler sinks the reads below the MFMAs and every sub-step starts
-// by waiting on LDS.
-template <class POp, class QOp>
-__device__ __forceinline__ void sub_step(Acc2 &acc, Frags &next, const Frags &cur, const POp &P, const QOp &Q,
-                                         const char *stage, int s) {
-    read_frags(next, P, Q, stage, s);
-    mfma_block(acc, cur);
-#pragma unroll
-    for (int i = 0; i < kTP2 * kTQ2; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, kReadsPerMfma, 0);  // DS read
+    for (int i = 0; i < kHalfP; ++i) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // MFMA
+        if (i * per < READS) __builtin_amdgcn_sched_group_barrier(0x100, per, 0);  // DS read
     }
     __builtin_amdgcn_sched_barrier(0);
 }
 
-// One resident stage (two 16-k sub-steps).  On entry `x` holds the last fragment set of the
-// previous stage (zeros before the first): its MFMAs open this stage, so the matrix pipe has
-// work while this stage's first fragment reads are in flight.  On exit `x` holds this
-// stage's last fragment set, not yet multiplied.  The loads of the stage two ahead are
-// issued between the two sub-steps (inline asm, stays where it is written).  At most two
-// fragment sets are live next to the 128 accumulator registers.
+// The two sub-steps of a 32-k step, each one sub-step late: the first multiplies the second half of the step before while it
+// reads this step's first half and Q tiles, the second multiplies those while it reads this step's second half.
+// So a window opens with MFMAs that need none of its data, and all its reads are done one sub-step before it is left.
+// A Q tile's register is free as soon as its four MFMAs are issued and takes the next step's tile at once: 48 fragment
+// registers in all next to the 128 accumulators (with a second set for Q, 16 more, the kernels spill).  Left alone the
+// compiler sinks the reads below the MFMAs and every sub-step starts by waiting on LDS: hence the fixed order.
+// fp(i), fq(j): the step's fragments of P tile i and Q tile j.
+template <int PREADS, int QREADS, class FP, class FQ>
+__device__ __forceinline__ void step_first(Acc2 &acc, Frags &f, FP fp, FQ fq) {
+#pragma unroll
+    for (int i = 0; i < kHalfP; ++i) f.y[i] = fp(i);
+    mfma_col<1>(acc, f.x, f.q[0], 0);
+    thread_reads<kHalfP * PREADS>();
+#pragma unroll
+    for (int j = 1; j < kTQ2; ++j) {
+        f.q[j - 1] = fq(j - 1);
+        mfma_col<1>(acc, f.x, f.q[j], j);
+        thread_reads<QREADS>();
+    }
+}
+template <int PREADS, int QREADS, class FP, class FQ>
+__device__ __forceinline__ void step_second(Acc2 &acc, Frags &f, FP fp, FQ fq) {
+    f.q[kTQ2 - 1] = fq(kTQ2 - 1);
+    f.x[0] = fp(kHalfP);
+    f.x[1] = fp(kHalfP + 1);
+    mfma_col<0>(acc, f.y, f.q[0], 0);
+    thread_reads<2 * PREADS + QREADS>();
+    f.x[2] = fp(kHalfP + 2);
+    f.x[3] = fp(kHalfP + 3);
+    mfma_col<0>(acc, f.y, f.q[1], 1);
+    thread_reads<2 * PREADS>();
+    mfma_col<0>(acc, f.y, f.q[2], 2);
+    mfma_col<0>(acc, f.y, f.q[3], 3);
+    __builtin_amdgcn_sched_barrier(0);
+}
+// the last second half
+__device__ __forceinline__ void step_last(Acc2 &acc, const Frags &f) {
+#pragma unroll
+    for (int j = 0; j < kTQ2; ++j) mfma_col<1>(acc, f.x, f.q[j], j);
+}
+
+// One resident stage (one 32-k step).  The loads of the stage two ahead are
+// issued between the two sub-steps (inline asm, stays where it is written).
 template <class POp, class QOp>
-__device__ __forceinline__ void stage_compute(Acc2 &acc, Frags &x, Frags &y, const POp &P, const QOp &Q,
-                                              const char *stage, int kt_load, uint32_t stage_load, bool loader) {
-    sub_step(acc, y, x, P, Q, stage, 0);
+__device__ __forceinline__ void stage_compute(Acc2 &acc, Frags &f, const POp &P, const QOp &Q, const char *stage, int kt_load,
+                                              uint32_t stage_load, bool loader) {
+    auto fp = [&](int i) { return P.frag(stage, i); };
+    auto fq = [&](int j) { return Q.frag(stage + kOperandBytes, j); };
+    step_first<POp::kReads, QOp::kReads>(acc, f, fp, fq);
     if (loader) {
         P.issue(kt_load, stage_load);
         Q.issue(kt_load, stage_load + kOperandBytes);
     }
     __builtin_amdgcn_sched_barrier(0);
-    sub_step(acc, x, y, P, Q, stage, 1);
+    step_second<POp::kReads, QOp::kReads>(acc, f, fp, fq);
 }
 
 // End of a stage.  Loaders wait until at most one stage's loads are outstanding (their share
@@ -425,23 +487,20 @@ __device__ __forceinline__ void mfma_mainloop2(Acc2 &acc, int nk, const POp &P, 
         }
     }
     stage_barrier<NL>(loader);
-    Frags x, y;
-#pragma unroll
-    for (int i = 0; i < kTP2; ++i) x.a[i] = bf16x8_t{};
-#pragma unroll
-    for (int j = 0; j < kTQ2; ++j) x.b[j] = bf16x8_t{};
+    Frags f;
+    f.clear();
     // single loop exit (no break) keeps the accumulators in place
     for (int kt = 0; kt < nk; kt += 4) {
-        stage_compute(acc, x, y, P, Q, st0, kt + 2, a2, loader);
+        stage_compute(acc, f, P, Q, st0, kt + 2, a2, loader);
         stage_barrier<NL>(loader);
-        if (kt + 1 < nk) stage_compute(acc, x, y, P, Q, st1, kt + 3, a3, loader);
+        if (kt + 1 < nk) stage_compute(acc, f, P, Q, st1, kt + 3, a3, loader);
         stage_barrier<NL>(loader);
-        if (kt + 2 < nk) stage_compute(acc, x, y, P, Q, st2, kt + 4, a0, loader);
+        if (kt + 2 < nk) stage_compute(acc, f, P, Q, st2, kt + 4, a0, loader);
         stage_barrier<NL>(loader);
-        if (kt + 3 < nk) stage_compute(acc, x, y, P, Q, st3, kt + 5, a1, loader);
+        if (kt + 3 < nk) stage_compute(acc, f, P, Q, st3, kt + 5, a1, loader);
         stage_barrier<NL>(loader);
     }
-    mfma_block(acc, x);
+    step_last(acc, f);
     // loads for stages past the end are still in flight: drain them, and meet, before anyone
     // reuses the stage buffers (the epilogues stage their stores through them)
     __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (15 << 8));
@@ -466,7 +525,7 @@ constexpr int kSuperBytes = 2 * kWinBytes;    // 64 KB: both operands
 constexpr int kLoadsPerWindow = 16;           // tile loads per loader wave per window (8 per operand)
 
 // K-contiguous 256-row window [256 rows][128 B]: 32 chunks of 1 KB (8 rows x 128 B), eight per
-// loader wave; the 16-byte chunk c of row r sits at slot c ^ ((r >> 1) & 7) (KcFrag<64>'s
+// loader wave; the 16-byte chunk c of row r sits at slot c ^ ((r >> 1) & 7) (KcFrag16's
 // conflict-free order), applied on the global side.  Chunk i of a wave is 32 rows below chunk
 // i - 1 and has the same swizzle, so one per-lane offset and a stride describe all eight --
 // unless the rows are gathered (ROWS = true): then each lane keeps the offsets of its eight rows.
@@ -492,7 +551,7 @@ struct OpKC64 {
     int voff[(ROWS && !STASH) ? 8 : 1];
     int step;              // bytes between a lane's consecutive chunks (32 rows)
     int4 *stash;           // STASH: this thread's first slot; the second is 256 slots on
-    KcFrag<kBK3> fr;
+    KcFrag16 fr;
     int tid_;              // the thread index the lane constants were made from (see set_lane)
     __device__ __forceinline__ int lane_chunk() const {
         const int w = tid_ >> 6, lane = tid_ & 63;
@@ -575,6 +634,7 @@ struct OpKC64 {
         }
     }
     __device__ __forceinline__ bf16x8_t frag_window(const char *win, int t, int u) const { return fr.read(win, t, u); }
+    static constexpr int kReads = 1;
 };
 
 // a 32-k tile operand as a window: tiles 2J and 2J+1 back to back
@@ -590,23 +650,7 @@ __device__ __forceinline__ void win_issue(const Op &op, int J, uint32_t win, int
 template <class Op>
 __device__ __forceinline__ bf16x8_t win_frag(const Op &op, const char *win, int t, int u) {
     if constexpr (Op::kWindowed) return op.frag_window(win, t, u);
-    else return op.frag(win + (u >> 1) * kOperandBytes, t, u & 1);
-}
-
-template <class POp, class QOp>
-__device__ __forceinline__ void sub_step3(Acc2 &acc, Frags &next, const Frags &cur, const POp &P, const QOp &Q,
-                                          const char *pwin, const char *qwin, int u) {
-#pragma unroll
-    for (int i = 0; i < kTP2; ++i) next.a[i] = win_frag(P, pwin, i, u);
-#pragma unroll
-    for (int j = 0; j < kTQ2; ++j) next.b[j] = win_frag(Q, qwin, j, u);
-    mfma_block(acc, cur);
-#pragma unroll
-    for (int i = 0; i < kTP2 * kTQ2; ++i) {
-        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x100, kReadsPerMfma, 0);  // DS read
-    }
-    __builtin_amdgcn_sched_barrier(0);
+    else return op.frag(win + u * kOperandBytes, t);
 }
 
 // End of a window: a loader's loads (the next window) have all landed, everyone's fragment reads
@@ -617,23 +661,26 @@ __device__ __forceinline__ void window_barrier(bool loader) {
     __builtin_amdgcn_s_barrier();
 }
 
-// One resident window (four 16-k sub-steps).  `x` carries the last fragment set of the previous
+// One resident window (four sub-steps, two of each 32-k step).  f carries the last half of the previous
 // window in and this window's last one out, as in stage_compute(); the next window's loads go out
 // into the buffer the previous window has just left, one operand before the first sub-step and
 // the other after it (measured: all sixteen at once makes the loader waves late for the window's
 // barrier; later than this shortens the time the loads have).
 template <class POp, class QOp>
-__device__ __forceinline__ void window_compute(Acc2 &acc, Frags &x, Frags &y, const POp &P, const QOp &Q,
+__device__ __forceinline__ void window_compute(Acc2 &acc, Frags &f, const POp &P, const QOp &Q,
                                                const char *pwin, const char *qwin, int Jnext, uint32_t pnext,
                                                uint32_t qnext, bool load_next, int qrows) {
     if (load_next) win_issue(P, Jnext, pnext);
     __builtin_amdgcn_sched_barrier(0);
-    sub_step3(acc, y, x, P, Q, pwin, qwin, 0);
-    if (load_next) win_issue(Q, Jnext, qnext, qrows);
-    __builtin_amdgcn_sched_barrier(0);
-    sub_step3(acc, x, y, P, Q, pwin, qwin, 1);
-    sub_step3(acc, y, x, P, Q, pwin, qwin, 2);
-    sub_step3(acc, x, y, P, Q, pwin, qwin, 3);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+        auto fp = [&](int i) { return win_frag(P, pwin, i, u); };
+        auto fq = [&](int j) { return win_frag(Q, qwin, j, u); };
+        step_first<POp::kReads, QOp::kReads>(acc, f, fp, fq);
+        if (u == 0 && load_next) win_issue(Q, Jnext, qnext, qrows);
+        __builtin_amdgcn_sched_barrier(0);
+        step_second<POp::kReads, QOp::kReads>(acc, f, fp, fq);
+    }
 }
 
 // nw windows of 64 k.  `lds`: the work-group's 128 KB.  The two P windows sit at 0 and 32 KB, the two
@@ -693,20 +740,17 @@ __device__ __forceinline__ void mfma_mainloop3(Acc2 &acc, int nw, const POp &P, 
         }
         return;
     }
-    Frags x, y;
-#pragma unroll
-    for (int i = 0; i < kTP2; ++i) x.a[i] = bf16x8_t{};
-#pragma unroll
-    for (int j = 0; j < kTQ2; ++j) x.b[j] = bf16x8_t{};
+    Frags f;
+    f.clear();
     for (int J = 0; J < nw; J += 2) {
-        window_compute(acc, x, y, P, Q, pA, qA, J + 1, apB, aqB, loader && J > 0 && J + 1 < nw, qrows);
+        window_compute(acc, f, P, Q, pA, qA, J + 1, apB, aqB, loader && J > 0 && J + 1 < nw, qrows);
         window_barrier(loader);
         if (J + 1 < nw) {
-            window_compute(acc, x, y, P, Q, pB, qB, J + 2, apA, aqA, loader && J + 2 < nw, qrows);
+            window_compute(acc, f, P, Q, pB, qB, J + 2, apA, aqA, loader && J + 2 < nw, qrows);
             window_barrier(loader);
         }
     }
-    mfma_block(acc, x);
+    step_last(acc, f);
 }
 
 // ---------------------------------------------------------------------------
@@ -761,11 +805,8 @@ __device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P,
         }
     }
     tail_barrier(loader, nw > 1, wide);
-    Frags x, y;
-#pragma unroll
-    for (int i = 0; i < kTP2; ++i) x.a[i] = bf16x8_t{};
-#pragma unroll
-    for (int j = 0; j < kTQ2; ++j) x.b[j] = bf16x8_t{};
+    Frags f;
+    f.clear();
     // window J sits in slot J % 3; window J + 2 goes into the slot window J - 1 has just left
     auto window = [&](int J, int slot) {
         const int nslot = slot == 0 ? 2 : slot - 1;   // (slot + 2) % 3
@@ -773,10 +814,13 @@ __device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P,
         __builtin_amdgcn_sched_barrier(0);
         if (live) {
             const char *pw = lds + slot * kWinBytes, *qw = lds + kTailQBase + slot * kTailQBytes;
-            sub_step3(acc, y, x, P, Q, pw, qw, 0);
-            sub_step3(acc, x, y, P, Q, pw, qw, 1);
-            sub_step3(acc, y, x, P, Q, pw, qw, 2);
-            sub_step3(acc, x, y, P, Q, pw, qw, 3);
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                auto fp = [&](int i) { return win_frag(P, pw, i, u); };
+                auto fq = [&](int j) { return win_frag(Q, qw, j, u); };
+                step_first<POp::kReads, QOp::kReads>(acc, f, fp, fq);
+                step_second<POp::kReads, QOp::kReads>(acc, f, fp, fq);
+            }
         }
         tail_barrier(loader, J + 2 < nw, wide);
     };
@@ -785,7 +829,7 @@ __device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P,
         if (J + 1 < nw) window(J + 1, 1);
         if (J + 2 < nw) window(J + 2, 2);
     }
-    if (live) mfma_block(acc, x);
+    if (live) step_last(acc, f);
 }
 
 // Persistent work-groups.  A launch has one work-group per compute unit; each walks the tile
@@ -981,12 +1025,8 @@ struct RowStage {
 // the wave's private share (128 KB / waves) of the (now idle) stage buffers
 __device__ __forceinline__ char *wave_patch(char *s0, char *s1, char *s2, char *s3, int tid) {
     const int w = tid >> 6;
-    if constexpr (kWaves2 == 8) {
-        char *b = (w >> 1) == 0 ? s0 : (w >> 1) == 1 ? s1 : (w >> 1) == 2 ? s2 : s3;
-        return b + (w & 1) * 16384;
-    } else {
-        return w == 0 ? s0 : w == 1 ? s1 : w == 2 ? s2 : s3;
-    }
+    char *b = (w >> 1) == 0 ? s0 : (w >> 1) == 1 ? s1 : (w >> 1) == 2 ? s2 : s3;
+    return b + (w & 1) * 16384;
 }
 
 __device__ __forceinline__ uint64_t clamp_bytes(int64_t b) { return b <= 0 ? 0u : (uint64_t)b; }

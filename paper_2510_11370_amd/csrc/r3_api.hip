@@ -238,7 +238,7 @@ int r3_grouped_ffn(const r3_layer_desc *desc, const void *Xp, const void *x, con
         return hip_rc(mfma_ffn_forward(m.S, m.d, m.E, m.F, rows, via, m.K, m.T, offsets, tiles, W_gate, W_up, W_down,
                                        Yp, H, FA_save, FB_save, nullptr, s));
     }
-    if (plain_ffn1((int)m.S, m.d, m.E, m.F, m.act, rows, via, m.K, offsets, W_gate, W_up, H, FA_save, FB_save, nullptr,
+    if (plain_ffn1((int)m.S, m.d, m.E, m.F, m.act, rows, m.T, via, m.K, offsets, W_gate, W_up, H, FA_save, FB_save, nullptr,
                    s) != hipSuccess)
         return R3_ERR_HIP;
     return hip_rc(plain_ffn2((int)m.S, m.d, m.E, m.F, m.act, H, offsets, W_down, Yp, s));
@@ -296,7 +296,7 @@ int r3_moe_forward(const r3_layer_desc *desc, const void *x, const void *W_r, co
                              FA_save, FB_save, grow, s) != hipSuccess)
             return R3_ERR_HIP;
     } else {
-        if (plain_ffn1((int)m.S, m.d, m.E, m.F, m.act, x, perm, m.K, offsets, W_gate, W_up, H, FA_save, FB_save, gates,
+        if (plain_ffn1((int)m.S, m.d, m.E, m.F, m.act, x, m.T, perm, m.K, offsets, W_gate, W_up, H, FA_save, FB_save, gates,
                        s) != hipSuccess)
             return R3_ERR_HIP;
         if (plain_ffn2((int)m.S, m.d, m.E, m.F, m.act, H, offsets, W_down, Yp, s) != hipSuccess) return R3_ERR_HIP;
@@ -374,7 +374,7 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
             return R3_ERR_HIP;
         if (plain_dh(S, m.d, m.E, m.F, m.act, dYp, offsets, W_down, FA, FB, dA, dB, s) != hipSuccess) return R3_ERR_HIP;
         // gated: H is g H already, so its partner is the plain dy row (read through perm), not g dy
-        if (plain_wgrads(m.d, m.E, m.F, m.K, m.act, offsets, H, gated ? dy : dYp, gated ? perm : nullptr, Xp ? Xp : x,
+        if (plain_wgrads(m.d, m.E, m.F, m.T, m.K, m.act, offsets, H, gated ? dy : dYp, gated ? perm : nullptr, Xp ? Xp : x,
                          Xp ? nullptr : perm, dA, dB, dW_gate, dW_up, dW_down, accumulate, s) != hipSuccess)
             return R3_ERR_HIP;
         if (plain_dxp(S, m.d, m.E, m.F, m.act, dA, dB, offsets, W_gate, W_up, dXp, s) != hipSuccess) return R3_ERR_HIP;

@@ -1,0 +1,432 @@
+// The expert network of the f32 layer on the f32 matrix instruction (16x16x4), for widths that are multiples of four
+// (16-byte rows); all other widths and the bf16 layers without a matrix path have the tiles of r3_plain.hip.  Products and
+// sums are those of an f32 FMA chain, in the same order of k as there.
+//
+// What bounds it: the f32 matrix pipe, 256 FLOP per cycle and compute unit (157 TFLOP/s at 2.4 GHz); for layers of a few
+// hundred rows the chain of loads and MFMAs of one tile.  An operand tile (32 k) goes from memory straight to LDS, 1 KB per
+// wave and load, into the place its lane belongs to: the XOR swizzle that keeps the fragment reads free of bank conflicts is
+// applied to the source address, and the buffer's bounds and an offset outside it give the zeros of ragged edges.  No
+// operand passes the registers, so several small work-groups share a compute unit and cover each other's waits, which is
+// why the tiles are small: 64 x 64 keeps both the row padding and the last round of tiles short.
+#include <algorithm>
+#include <type_traits>
+
+#include "r3_f32.h"
+#include "r3_kernels.h"
+#include "r3_mfma2.h"
+
+namespace r3 {
+namespace {
+
+// 4 waves as 2 (P) x 2 (Q), each TP x TQ tiles of 16 x 16; NST tiles of 32 k in LDS, NST - 1 on the way
+template <int TP_, int TQ_, int NST_>
+struct F32Cfg {
+    static constexpr int TP = TP_, TQ = TQ_, NST = NST_, NT = 256, BK = 32;
+    static constexpr int BP = 32 * TP, BQ = 32 * TQ, PBYTES = BP * BK * 4, STAGE = (BP + BQ) * BK * 4;
+    static constexpr int LOADS = TP + TQ;   // loads per wave and k-tile (a load of four waves is 4 KB)
+};
+typedef F32Cfg<2, 2, 2> F32Tile;     // 32 KB of LDS: five work-groups on a compute unit, which cover what is not prefetched
+typedef F32Cfg<1, 1, 4> F32Short;    // few tiles: four times as many, half the chain each, loads three k-tiles ahead
+typedef F32Cfg<2, 1, 4> F32Short1;   // the same for the SwiGLU, whose P tile holds both weights
+
+template <class C> using F32Acc = f32x4_t[C::TP][C::TQ];
+
+// Row-major operand tile [R rows][32 k]: a row is 128 B, its 16-byte chunk c sits at c ^ ((row >> 1) & 7).
+template <int R>
+struct F32Rows {
+    Src src;
+    int voff[R / 32], kc, KK, frag;
+    // the row of the tile that this lane's i-th load belongs to
+    static __device__ __forceinline__ int load_row(int i) { return 8 * ((int)(threadIdx.x >> 6) + 4 * i) + ((threadIdx.x & 63) >> 3); }
+    __device__ __forceinline__ void init(const float *base, uint64_t bytes, int KK_, int wave_row) {
+        const int lane = threadIdx.x & 63;
+        src = Src{(const char *)base, bytes, 128};
+        KK = KK_;
+        kc = 4 * ((lane & 7) ^ ((load_row(0) >> 1) & 7));   // (32 rows on: the same swizzle)
+        const int row = wave_row + (lane & 15);
+        frag = row * 128 + (((lane >> 4) ^ ((row >> 1) & 7)) << 4);
+    }
+    __device__ __forceinline__ void set_row(int i, int row) { voff[i] = (row * KK + kc) * 4; }
+    __device__ __forceinline__ void issue(int kt, uint32_t tile) const {
+        const rsrc_t r = src_rsrc(src, kt);
+        const bool in = kt * 32 + kc < KK;
+#pragma unroll
+        for (int i = 0; i < R / 32; ++i)
+            lds_load16(r, tile + 1024 * ((threadIdx.x >> 6) + 4 * i), in ? voff[i] : kOutsideWindow);
+    }
+    // four consecutive k of row `wave_row + 16 t + lane % 16`, 16-k group g: k = 16 g + 4 (lane / 16) ..
+    __device__ __forceinline__ void read(const char *tile, int t, int g, float (&f)[4]) const {
+        const float4 v = *(const float4 *)(tile + (frag ^ (g << 6)) + t * 2048);
+        f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
+    }
+};
+
+// k-major operand tile [32 k][R features], R = 64 or 32.  Its blocks of 16 features are spread so that the four k of a
+// fragment read (4 apart) meet different banks: R = 64, block b of k at b ^ ((k >> 2) & 3); R = 32, two k-rows to the 256
+// bytes of all banks, b ^ ((k >> 2) & 1) with k in row k ^ ((k >> 3) & 1).
+template <int R>
+struct F32Cols {
+    static constexpr int ROWB = R * 4, KPL = 1024 / ROWB;   // bytes of a k-row; k-rows per load
+    Src src;
+    int koff[R / 32], coff, fr[R == 64 ? 1 : 2];
+    // the k-row of the tile that this lane's i-th load belongs to
+    static __device__ __forceinline__ int load_k(int i) {
+        const int j = (threadIdx.x >> 6) + 4 * i, lane = threadIdx.x & 63;
+        const int row = KPL * j + lane / (R / 4);
+        return R == 64 ? row : row ^ (j & 1);
+    }
+    // base: first k-row, first feature; ld: floats per k-row; wave_block: the wave's first block of 16 features
+    __device__ __forceinline__ void init(const float *base, uint64_t bytes, int ld, int wave_block) {
+        const int lane = threadIdx.x & 63, hi = lane >> 4;
+        src = Src{(const char *)base, bytes, (uint32_t)(32 * ld * 4)};
+        const int slot = lane % (R / 4);
+        coff = (R == 64 ? slot ^ (((threadIdx.x >> 6) & 3) << 2) : slot ^ (((lane >> 5) & 1) << 2)) * 16;
+#pragma unroll
+        for (int i = 0; i < R / 32; ++i) koff[i] = load_k(i) * ld * 4;
+        if constexpr (R == 64) {
+            fr[0] = 4 * hi * ROWB + ((wave_block ^ hi) << 6) + (lane & 15) * 4;
+        } else {   // k = 4 hi + s sits in row 4 hi + (s ^ (hi >> 1))
+            const int b = 4 * hi * ROWB + ((wave_block ^ (hi & 1)) << 6) + (lane & 15) * 4;
+            fr[0] = b + (hi >> 1) * ROWB;
+            fr[1] = b + (1 - (hi >> 1)) * ROWB;
+        }
+    }
+    __device__ __forceinline__ void issue(int kt, uint32_t tile) const {
+        const rsrc_t r = src_rsrc(src, kt);
+#pragma unroll
+        for (int i = 0; i < R / 32; ++i) lds_load16(r, tile + 1024 * ((threadIdx.x >> 6) + 4 * i), koff[i] + coff);
+    }
+    // one load of k-rows gathered from the whole matrix (src.step = 0): byte offset of this lane's row, < 0: none
+    __device__ __forceinline__ void issue_row(int i, uint32_t tile, int row_off) const {
+        lds_load16(src_rsrc(src, 0), tile + 1024 * ((threadIdx.x >> 6) + 4 * i), row_off < 0 ? kOutsideWindow : row_off + coff);
+    }
+    // four consecutive k (as F32Rows::read) of the wave's features 16 t + lane % 16
+    __device__ __forceinline__ void read(const char *tile, int t, int g, float (&f)[4]) const {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+            f[s] = *(const float *)(tile + ((R == 64 ? fr[0] + s * ROWB : fr[s & 1] + (s & 2) * ROWB) ^ (t << 6)) + g * 16 * ROWB);
+    }
+};
+
+// the wave's loads of all but `stages` k-tiles have landed, its LDS reads are done; then the waves meet
+template <class C, int STAGES>
+__device__ __forceinline__ void f32_wait() {
+    constexpr int vm = STAGES * C::LOADS;
+    asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(vm) : "memory");
+}
+
+template <class C>
+__device__ __forceinline__ void f32_mul(F32Acc<C> &acc, const float (&a)[C::TP][4], const float (&b)[C::TQ][4]) {
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int i = 0; i < C::TP; ++i)
+#pragma unroll
+            for (int j = 0; j < C::TQ; ++j)
+                acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i][s], b[j][s], acc[i][j], 0, 0, 0);
+}
+
+// acc[p][q] += sum_k P[p][k] Q[q][k] over nk tiles of 32 k.  issue(kt, LDS address): the wave's C::LOADS loads of k-tile kt
+// (zeros past the end).  rp(i, g, f, tile) / rq: fragment reads.  A k-tile is two groups of 16 k; a group is read while the
+// one before it is multiplied, so that a k-tile opens with MFMAs that wait for nothing of it.
+template <class C, class Issue, class RP, class RQ>
+__device__ __forceinline__ void f32_loop(F32Acc<C> &acc, int nk, Issue issue, RP rp, RQ rq, char *lds) {
+    const uint32_t at = lds_addr(lds);
+    float a[2][C::TP][4], b[2][C::TQ][4];
+    auto read = [&](const char *st, int g) {
+#pragma unroll
+        for (int i = 0; i < C::TP; ++i) rp(st, i, g, a[g][i]);
+#pragma unroll
+        for (int j = 0; j < C::TQ; ++j) rq(st + C::PBYTES, j, g, b[g][j]);
+    };
+#pragma unroll
+    for (int p = 0; p < C::NST - 1; ++p) issue(p, at + p * C::STAGE);
+    f32_wait<C, C::NST - 2>();
+    int slot = 0;
+    for (int kt = 0; kt < nk; ++kt) {
+        const char *st = lds + slot * C::STAGE;
+        const int prev = slot == 0 ? C::NST - 1 : slot - 1;
+        issue(kt + C::NST - 1, at + prev * C::STAGE);   // into the tile that was left last
+        read(st, 0);
+        if (kt) f32_mul<C>(acc, a[1], b[1]);
+        __builtin_amdgcn_sched_barrier(0);
+        read(st, 1);
+        f32_mul<C>(acc, a[0], b[0]);
+        f32_wait<C, C::NST - 2>();
+        slot = slot + 1 == C::NST ? 0 : slot + 1;
+    }
+    if (nk > 0) f32_mul<C>(acc, a[1], b[1]);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the loads past the end, before the space is used again or left
+}
+
+template <class C>
+__device__ __forceinline__ void f32_zero(F32Acc<C> &acc) {
+#pragma unroll
+    for (int i = 0; i < C::TP; ++i)
+#pragma unroll
+        for (int j = 0; j < C::TQ; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
+}
+
+// ---------------------------------------------------------------------------
+// Row-tiled contractions over the expert-sorted rows (the operands of plain_rows_kernel).
+// ---------------------------------------------------------------------------
+template <class C, int MODE>
+__global__ void __launch_bounds__(C::NT)
+f32_rows_kernel(int d, int E, int F, const int32_t *__restrict__ offsets, const float *__restrict__ in0,
+                const float *__restrict__ in1, int T, const int32_t *__restrict__ perm, int K, const float *__restrict__ gates,
+                const float *__restrict__ W0, const float *__restrict__ W1, const float *__restrict__ FAin,
+                const float *__restrict__ FBin, float *__restrict__ out0, float *__restrict__ out1, float *__restrict__ out2) {
+    __shared__ __attribute__((aligned(1024))) char lds[C::NST * C::STAGE];
+    static_assert(MODE != PLAIN_FFN1 || C::TP == 2, "one tile of each weight");
+    constexpr int BF = MODE == PLAIN_FFN1 ? C::BP / 2 : C::BP;            // output features per tile
+    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d;
+    const int KK = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? d : F;      // width of the row operand
+    const int npt = (NOUT + BF - 1) / BF;
+    const RowTile t = find_row_tile<true>(offsets, E, C::BQ, blockIdx.x, npt);
+    if (t.e < 0) return;
+    const int p0 = t.col * BF, rows = t.row1 - t.row0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wp = wave & 1, wq = wave >> 1;
+    const uint64_t wbytes = (uint64_t)d * F * 4;
+    const float *w0 = W0 + (int64_t)t.e * d * F;
+
+    const bool gather = MODE == PLAIN_FFN1 && perm;
+    F32Rows<C::BQ> Q;
+    Q.init(gather ? in0 : in0 + (int64_t)t.row0 * KK, gather ? (uint64_t)T * KK * 4 : (uint64_t)rows * KK * 4, KK, wq * 16 * C::TQ);
+#pragma unroll
+    for (int i = 0; i < C::BQ / 32; ++i) {
+        const int r = min(Q.load_row(i), rows - 1);
+        Q.set_row(i, gather ? perm[t.row0 + r] / K : r);
+    }
+    F32Acc<C> acc;
+    f32_zero<C>(acc);
+    const int nk = (KK + C::BK - 1) / C::BK;
+    auto rq = [&](const char *tile, int j, int g, float (&f)[4]) { Q.read(tile, j, g, f); };
+    if constexpr (MODE == PLAIN_FFN1) {
+        const float *w1 = W1 + (int64_t)t.e * d * F;
+        F32Cols<32> G, U;   // the same 32 features of both weights, so that a lane holds both pre-activations
+        G.init(w0 + p0, wbytes - p0 * 4u, F, wp);
+        U.init(w1 + p0, wbytes - p0 * 4u, F, wp);
+        f32_loop<C>(acc, nk, [&](int kt, uint32_t a) { G.issue(kt, a); U.issue(kt, a + 4096); Q.issue(kt, a + C::PBYTES); },
+                    [&](const char *tile, int i, int g, float (&f)[4]) { G.read(tile + i * 4096, 0, g, f); }, rq, lds);
+    } else if constexpr (MODE == PLAIN_DOWN) {
+        F32Cols<C::BP> P;
+        P.init(w0 + p0, wbytes - p0 * 4u, d, wp * C::TP);
+        f32_loop<C>(acc, nk, [&](int kt, uint32_t a) { P.issue(kt, a); Q.issue(kt, a + C::PBYTES); },
+                    [&](const char *tile, int i, int g, float (&f)[4]) { P.read(tile, i, g, f); }, rq, lds);
+    } else {
+        F32Rows<C::BP> P;
+        const uint64_t pbytes = (uint64_t)(NOUT - p0) * KK * 4;
+        P.init(w0 + (int64_t)p0 * KK, pbytes, KK, wp * 16 * C::TP);
+#pragma unroll
+        for (int i = 0; i < C::BP / 32; ++i) P.set_row(i, min(P.load_row(i), NOUT - p0 - 1));
+        auto rp = [&](const char *tile, int i, int g, float (&f)[4]) { P.read(tile, i, g, f); };
+        if constexpr (MODE == PLAIN_DH) {
+            f32_loop<C>(acc, nk, [&](int kt, uint32_t a) { P.issue(kt, a); Q.issue(kt, a + C::PBYTES); }, rp, rq, lds);
+        } else {   // one reduction over both halves: dA Wg^T, then dB Wu^T
+            const Src p1{(const char *)(W1 + (int64_t)t.e * d * F + (int64_t)p0 * KK), pbytes, 128};
+            const Src q1{(const char *)(in1 + (int64_t)t.row0 * KK), Q.src.nbytes, 128};
+            const Src p0s = P.src, q0s = Q.src;
+            f32_loop<C>(acc, 2 * nk,
+                        [&](int kt, uint32_t a) {
+                            const bool second = kt >= nk;
+                            P.src = second ? p1 : p0s;
+                            Q.src = second ? q1 : q0s;
+                            P.issue(second ? kt - nk : kt, a);
+                            Q.issue(second ? kt - nk : kt, a + C::PBYTES);
+                        },
+                        rp, rq, lds);
+        }
+    }
+    // a lane's results: four consecutive features of one row per 16 x 16 tile
+#pragma unroll
+    for (int tq = 0; tq < C::TQ; ++tq) {
+        const int q = wq * 16 * C::TQ + 16 * tq + (lane & 15);
+        if (q >= rows) continue;
+        const int row = t.row0 + q;
+        if constexpr (MODE == PLAIN_FFN1) {
+            const int f = p0 + 16 * wp + 4 * (lane >> 4);
+            if (f >= F) continue;
+            const float gq = gates ? gates[perm[row]] : 1.0f;
+            float h[4], fa[4], fb[4];
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const float a = acc[0][tq][i], b = acc[1][tq][i];
+                const float sg = sigmoidf_(a);
+                h[i] = gq * (a * sg * b);
+                fa[i] = b * sg * (1.0f + a * (1.0f - sg));
+                fb[i] = a * sg;
+            }
+            const int64_t o = (int64_t)row * F + f;
+            *(float4 *)(out0 + o) = make_float4(h[0], h[1], h[2], h[3]);
+            if (out1) *(float4 *)(out1 + o) = make_float4(fa[0], fa[1], fa[2], fa[3]);
+            if (out2) *(float4 *)(out2 + o) = make_float4(fb[0], fb[1], fb[2], fb[3]);
+        } else {
+#pragma unroll
+            for (int tp = 0; tp < C::TP; ++tp) {
+                const int c = p0 + wp * 16 * C::TP + 16 * tp + 4 * (lane >> 4);
+                if (c >= NOUT) continue;
+                const int64_t o = (int64_t)row * NOUT + c;
+                const f32x4_t v = acc[tp][tq];
+                if constexpr (MODE == PLAIN_DH) {
+                    const float4 a = *(const float4 *)(FAin + o), b = *(const float4 *)(FBin + o);
+                    *(float4 *)(out0 + o) = make_float4(v[0] * a.x, v[1] * a.y, v[2] * a.z, v[3] * a.w);
+                    *(float4 *)(out1 + o) = make_float4(v[0] * b.x, v[1] * b.y, v[2] * b.z, v[3] * b.w);
+                } else {
+                    *(float4 *)(out0 + o) = make_float4(v[0], v[1], v[2], v[3]);
+                }
+            }
+        }
+    }
+}
+
+// ---------------------------------------------------------------------------
+// The three weight gradients of every expert in one launch (as plain_wgrad_kernel).
+// ---------------------------------------------------------------------------
+// A k-major operand of which k-row r is row r0 + r of a matrix, or row perm[r0 + r] / K of it: the indices are fetched a
+// k-tile before the loads that need them.
+template <int R>
+struct F32WgradOp {
+    F32Cols<R> op;
+    const int32_t *perm;
+    int n, ld, K, next[R / 32];
+    __device__ __forceinline__ void init(const float *m, const int32_t *perm_, int64_t nrows, int r0, int n_, int ld_, int K_, int col0,
+                                         int wave_block) {
+        perm = perm_ ? perm_ + r0 : nullptr;
+        n = n_; ld = ld_; K = K_;
+        const int64_t first = perm ? 0 : (int64_t)r0 * ld;
+        op.init(m + first + col0, (uint64_t)((perm ? nrows : n) * ld - col0) * 4, ld, wave_block);
+        if (perm) {
+            op.src.step = 0;
+            fetch(0);
+        }
+    }
+    __device__ __forceinline__ void fetch(int kt) {
+#pragma unroll
+        for (int i = 0; i < R / 32; ++i) next[i] = perm[min(kt * 32 + op.load_k(i), n - 1)];
+    }
+    __device__ __forceinline__ void issue(int kt, uint32_t tile) {
+        if (!perm) {
+            op.issue(kt, tile);
+            return;
+        }
+#pragma unroll
+        for (int i = 0; i < R / 32; ++i) op.issue_row(i, tile, kt * 32 + op.load_k(i) < n ? next[i] / K * (ld * 4) : -1);
+        fetch(kt + 1);
+    }
+};
+
+struct F32Wgrad {
+    const float *Qs, *Ps;
+    const int32_t *qperm, *pperm;
+    float *out;
+    int NQ, NP, tiles;   // tiles: per expert
+};
+struct F32Wgrad3 {
+    F32Wgrad g[3];
+};
+
+template <class C>
+__global__ void __launch_bounds__(C::NT)
+f32_wgrad_kernel(int E, int T, int K, const int32_t *__restrict__ offsets, F32Wgrad3 all, int accumulate) {
+    __shared__ __attribute__((aligned(1024))) char lds[C::NST * C::STAGE];
+    const int per = all.g[0].tiles + all.g[1].tiles + all.g[2].tiles;
+    const int e = blockIdx.x / per;
+    int rem = blockIdx.x - e * per, which = 0;
+    while (rem >= all.g[which].tiles) rem -= all.g[which++].tiles;
+    const F32Wgrad g = all.g[which];
+    const int npt = (g.NP + C::BP - 1) / C::BP;
+    const int qt = rem / npt, q0 = qt * C::BQ, p0 = (rem - qt * npt) * C::BP;
+    const int r0 = offsets[e], n = offsets[e + 1] - r0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wp = wave & 1, wq = wave >> 1;
+    F32Acc<C> acc;
+    f32_zero<C>(acc);
+    if (n > 0) {
+        F32WgradOp<C::BP> P;
+        F32WgradOp<C::BQ> Q;
+        P.init(g.Ps, g.pperm, T, r0, n, g.NP, K, p0, wp * C::TP);
+        Q.init(g.Qs, g.qperm, T, r0, n, g.NQ, K, q0, wq * C::TQ);
+        f32_loop<C>(acc, (n + C::BK - 1) / C::BK, [&](int kt, uint32_t a) { P.issue(kt, a); Q.issue(kt, a + C::PBYTES); },
+                    [&](const char *tile, int i, int gr, float (&f)[4]) { P.op.read(tile, i, gr, f); },
+                    [&](const char *tile, int j, int gr, float (&f)[4]) { Q.op.read(tile, j, gr, f); }, lds);
+    }
+    float *o = g.out + (int64_t)e * g.NQ * g.NP;
+#pragma unroll
+    for (int tq = 0; tq < C::TQ; ++tq) {
+        const int q = q0 + wq * 16 * C::TQ + 16 * tq + (lane & 15);
+        if (q >= g.NQ) continue;
+#pragma unroll
+        for (int tp = 0; tp < C::TP; ++tp) {
+            const int p = p0 + wp * 16 * C::TP + 16 * tp + 4 * (lane >> 4);
+            if (p >= g.NP) continue;
+            float4 *at = (float4 *)(o + (int64_t)q * g.NP + p);
+            float4 v = make_float4(acc[tp][tq][0], acc[tp][tq][1], acc[tp][tq][2], acc[tp][tq][3]);
+            if (accumulate) {
+                const float4 old = *at;
+                v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
+            }
+            *at = v;
+        }
+    }
+}
+
+int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
+// Tiles of 64 x 64 or of 32 x 32 outputs.  Row-tiled kernels: 32 x 32 below 512 tiles of the larger kind, and where an expert has
+// fewer than 64 rows on average.  us, 64 x 64 | 32 x 32: dXp of 256 x 2 rows, 128 features out of 256 x 2 (16 tiles) 16.3 | 10.5;
+// 2048 rows, 512 out of 512 x 2 (256) 43.0 | 38.9; 2048 rows, 1024 out of 1024 x 2 (512) 111.6 | 116.5; 8192 rows, 512 out of
+// 1024 x 2 (1024) 190.7 | 211.2; 4096 rows over 128 experts, 512 out of 512 x 2 (512) 88.7 | 85.1; 256 over 128 82.1 | 64.0.
+constexpr int kRowsFill = 512;
+// The weight gradients, whose tiles each write 16 or 4 KB: 32 x 32 below 256 tiles.  8 experts, 16384 rows, 128 x 256 (192 tiles)
+// 96.3 | 60.0; 8192 rows, 256 x 256 (384) 62.9 | 60.7, 2048 rows 21.2 | 22.6, 128 rows 8.4 | 11.0; 512 rows, 128 x 256 9.6 | 9.1.
+constexpr int kWgradFill = 256;
+
+template <class C, int MODE>
+void rows_launch(int S, int d, int E, int F, const int32_t *offsets, const float *in0, const float *in1, int T,
+                 const int32_t *perm, int K, const float *gates, const float *W0, const float *W1, const float *FA,
+                 const float *FB, float *o0, float *o1, float *o2, hipStream_t s) {
+    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d, BF = MODE == PLAIN_FFN1 ? C::BP / 2 : C::BP;
+    f32_rows_kernel<C, MODE><<<(unsigned)f32_rows_grid(S, E, C::BQ, ceil_div(NOUT, BF)), C::NT, 0, s>>>(
+        d, E, F, offsets, in0, in1, T, perm, K, gates, W0, W1, FA, FB, o0, o1, o2);
+}
+
+template <int MODE>
+void rows_by_size(int S, int d, int E, int F, const int32_t *offsets, const float *in0, const float *in1, int T,
+                  const int32_t *perm, int K, const float *gates, const float *W0, const float *W1, const float *FA,
+                  const float *FB, float *o0, float *o1, float *o2, hipStream_t s) {
+    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d;
+    typedef typename std::conditional<MODE == PLAIN_FFN1, F32Short1, F32Short>::type Short;
+    const bool few = ceil_div(S, 64) * ceil_div(NOUT, MODE == PLAIN_FFN1 ? 32 : 64) < kRowsFill || S < 64 * (int64_t)E;
+    auto f = few ? rows_launch<Short, MODE> : rows_launch<F32Tile, MODE>;
+    f(S, d, E, F, offsets, in0, in1, T, perm, K, gates, W0, W1, FA, FB, o0, o1, o2, s);
+}
+
+template <class C>
+void wgrad_launch(int E, int T, int K, const int32_t *offsets, F32Wgrad3 all, int accumulate, hipStream_t s) {
+    int per = 0;
+    for (auto &g : all.g) per += g.tiles = (int)(ceil_div(g.NQ, C::BQ) * ceil_div(g.NP, C::BP));
+    f32_wgrad_kernel<C><<<(unsigned)((int64_t)E * per), C::NT, 0, s>>>(E, T, K, offsets, all, accumulate);
+}
+
+}  // namespace
+
+hipError_t f32_rows(int mode, int S, int d, int E, int F, const int32_t *offsets, const float *in0, const float *in1, int T,
+                    const int32_t *perm, int K, const float *gates, const float *W0, const float *W1, const float *FA,
+                    const float *FB, float *o0, float *o1, float *o2, hipStream_t s) {
+    auto f = mode == PLAIN_FFN1 ? rows_by_size<PLAIN_FFN1> : mode == PLAIN_DOWN ? rows_by_size<PLAIN_DOWN>
+           : mode == PLAIN_DH ? rows_by_size<PLAIN_DH> : rows_by_size<PLAIN_DXP>;
+    f(S, d, E, F, offsets, in0, in1, T, perm, K, gates, W0, W1, FA, FB, o0, o1, o2, s);
+    return hipGetLastError();
+}
+
+hipError_t f32_wgrads(int d, int E, int F, int T, int K, const int32_t *offsets, const float *H, const float *dYrows,
+                      const int32_t *dyperm, const float *xrows, const int32_t *xperm, const float *dA, const float *dB,
+                      float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s) {
+    const F32Wgrad3 all = {{{H, dYrows, nullptr, dyperm, dWd, F, d, 0},
+                            {xrows, dA, xperm, nullptr, dWg, d, F, 0},
+                            {xrows, dB, xperm, nullptr, dWu, d, F, 0}}};
+    const bool few = 3 * (int64_t)E * ceil_div(d, 64) * ceil_div(F, 64) < kWgradFill;
+    auto f = few ? wgrad_launch<F32Short> : wgrad_launch<F32Tile>;
+    f(E, T, K, offsets, all, accumulate, s);
+    return hipGetLastError();
+}
+
+}  // namespace r3

@@ -75,7 +75,7 @@ hipError_t plain_router_logits(int T, int d, int E, int act, const void *x, cons
                                float *logits, hipStream_t s);
 // perm != NULL: `rows` is x [T,d] and row r of the grouped operand is x[perm[r] / K] (no gathered copy);
 // gates != NULL (with perm): H is stored scaled by the gate of the row's slot, gates[perm[r]]
-hipError_t plain_ffn1(int S, int d, int E, int F, int act, const void *rows, const int32_t *perm, int K,
+hipError_t plain_ffn1(int S, int d, int E, int F, int act, const void *rows, int T, const int32_t *perm, int K,
                       const int32_t *offsets, const void *Wg, const void *Wu, void *H, void *FA, void *FB,
                       const float *gates, hipStream_t s);
 hipError_t plain_ffn2(int S, int d, int E, int F, int act, const void *H, const int32_t *offsets, const void *Wd,
@@ -86,7 +86,7 @@ hipError_t plain_dxp(int S, int d, int E, int F, int act, const void *dA, const 
                      const void *Wg, const void *Wu, void *dXp, hipStream_t s);
 // dWd (+)= H^T dYrows, dWg (+)= xrows^T dA, dWu (+)= xrows^T dB per expert.  dyperm / xperm != NULL: that operand is
 // an un-permuted matrix and row r of the reduction is its row perm[r] / K
-hipError_t plain_wgrads(int d, int E, int F, int K, int act, const int32_t *offsets, const void *H, const void *dYrows,
+hipError_t plain_wgrads(int d, int E, int F, int T, int K, int act, const int32_t *offsets, const void *H, const void *dYrows,
                         const int32_t *dyperm, const void *xrows, const int32_t *xperm, const void *dA, const void *dB,
                         float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s);
 int plain_dwr_rows(int T, int d, int E);          // tokens per part

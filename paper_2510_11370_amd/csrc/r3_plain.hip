@@ -1,6 +1,6 @@
-// The expert network and the router in f32 arithmetic, for any widths and both activation types: the f32
-// layer, and the bf16 shapes that the bf16 MFMA kernels do not take.  Tiles run on the f32 matrix
-// instruction (16x16x4): products and sums are those of an f32 FMA chain (bf16 operands are widened, so their
+// The expert network and the router in f32 arithmetic, for any widths and both activation types: the f32 layers whose widths
+// are no multiples of four (the others have r3_f32.hip), and the bf16 shapes that the bf16 MFMA kernels do not take.  Tiles run on
+// the f32 matrix instruction (16x16x4): products and sums are those of an f32 FMA chain (bf16 operands are widened, so their
 // products are exact).
 //
 // What bounds it: the f32 matrix pipe (154 TFLOP/s is what a large library product reaches here) where a
@@ -9,11 +9,10 @@
 // f32 instruction takes 32 cycles, so the fragment reads (16 bytes per lane and 16 k from a row-major tile,
 // 4 bytes from a k-major one) are far from being felt.  Tiles are 128 x 128 (4 waves of 64 x 64) where
 // that still gives every compute unit two of them, else 64 x 64 (4 waves of 32 x 32).
-// Measured on T=2048 d=512 E=16 K=4 F=1024 f32, forward + backward (77 GFLOP): 65.3 ms with one thread per
-// output element (uncoalesced weight rows), 1.06 ms now; T=256 d=128 E=8 K=2 F=256 f32: 0.435 -> 0.099 ms;
-// T=3001 d=1000 E=64 K=6 F=704 bf16: 193 -> 4.2 ms.
+// Measured on T=3001 d=1000 E=64 K=6 F=704 bf16: 193 ms with one thread per output element, 4.2 ms here.
 #include <algorithm>
 
+#include "r3_f32.h"
 #include "r3_kernels.h"
 
 namespace r3 {
@@ -176,55 +175,11 @@ __device__ __forceinline__ void plain_results(F f) {
             f(tp, tq, (wave & 1) * C::WTP + 16 * tp + 4 * (lane >> 4), (wave >> 1) * C::WTQ + 16 * tq + (lane & 15));
 }
 
-// The expert and first row of row tile `want` (tiles of BQ rows, experts ascending), or e = -1 past the
-// last one.  Every wave finds it by itself: a lane adds up the tiles of its share of the experts, the wave
-// scans the sums and the lane that holds the tile walks its share.  (A table made by a launch of its own
-// costs more than this: the layers that come here are small.)
-struct RowTile {
-    int e, row0, row1;
-};
-__device__ __forceinline__ RowTile find_row_tile(const int32_t *__restrict__ offsets, int E, int BQ, int want) {
-    const int lane = lane_id(), per = (E + kWave - 1) / kWave;
-    const int e0 = min(lane * per, E), e1 = min(e0 + per, E);
-    int mine = 0, lo = offsets[e0];
-    for (int e = e0; e < e1; ++e) {
-        const int hi = offsets[e + 1];
-        mine += (hi - lo + BQ - 1) / BQ;
-        lo = hi;
-    }
-    int incl = mine;
-#pragma unroll
-    for (int o = 1; o < kWave; o <<= 1) {
-        const int v = __shfl_up(incl, o, kWave);
-        if (lane >= o) incl += v;
-    }
-    const uint64_t past = __ballot(incl > want);
-    RowTile t = {-1, 0, 0};
-    if (past == 0) return t;
-    const int owner = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)past) - 1);
-    int left = want - __builtin_amdgcn_readlane(incl - mine, owner);
-    for (int e = owner * per; e < min((owner + 1) * per, E); ++e) {   // wave-uniform
-        const int a = offsets[e], b = offsets[e + 1], n = (b - a + BQ - 1) / BQ;
-        if (left < n) {
-            t.e = e;
-            t.row0 = a + left * BQ;
-            t.row1 = min(b, t.row0 + BQ);
-            return t;
-        }
-        left -= n;
-    }
-    return t;
-}
-
 // ---------------------------------------------------------------------------
-// Row-tiled contractions over the expert-sorted rows:
-//   FFN1: A = rows Wg, B = rows Wu; H = (g) silu(A) B; FA = B silu'(A), FB = silu(A)   (P: gate | up halves)
-//   DOWN: Yp = H Wd        DH: dh = dYp Wd^T, dA = dh FA, dB = dh FB        DXP: dA Wg^T + dB Wu^T
+// Row-tiled contractions over the expert-sorted rows (listed in r3_f32.h; FFN1's P: gate | up halves).
 // `in0` holds the rows; FFN1 with perm != NULL reads row r as in0[perm[r] / K], and with gates != NULL
 // scales H by the gate of the row's slot.
 // ---------------------------------------------------------------------------
-enum { PLAIN_FFN1, PLAIN_DOWN, PLAIN_DH, PLAIN_DXP };
-
 template <class C, int MODE, typename T, bool VEC>
 __global__ void __launch_bounds__(C::NT)
 plain_rows_kernel(int d, int E, int F, const int32_t *__restrict__ offsets, const T *__restrict__ in0,
@@ -236,10 +191,9 @@ plain_rows_kernel(int d, int E, int F, const int32_t *__restrict__ offsets, cons
     const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d;
     const int KK = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? d : F;      // width of the row operand
     const int npt = (NOUT + BF - 1) / BF;
-    const int qt = blockIdx.x / npt, p0 = (blockIdx.x - qt * npt) * BF;
-    const RowTile t = find_row_tile(offsets, E, C::BQ, qt);
+    const RowTile t = find_row_tile<false>(offsets, E, C::BQ, blockIdx.x, npt);
     if (t.e < 0) return;
-    const int rows = t.row1 - t.row0;
+    const int p0 = t.col * BF, rows = t.row1 - t.row0;
     const T *w0 = W0 + (int64_t)t.e * d * F;
     const T *w1 = (MODE == PLAIN_FFN1 || MODE == PLAIN_DXP) ? W1 + (int64_t)t.e * d * F : nullptr;
 
@@ -459,25 +413,26 @@ void allow_lds(K kernel, int bytes) {
     (void)hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
 }
 
-// row tiles of BQ rows over E ragged segments of S rows: at most this many
-int64_t row_tiles(int64_t S, int E, int BQ) { return S / BQ + std::min<int64_t>(E, S); }
-
 template <class C, int MODE, typename T, bool VEC>
 void rows_launch(int S, int d, int E, int F, const int32_t *offsets, const T *in0, const T *in1, const int32_t *perm, int K,
                  const float *gates, const T *W0, const T *W1, const T *FA, const T *FB, T *o0, T *o1, T *o2, hipStream_t s) {
     const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d, BF = MODE == PLAIN_FFN1 ? C::BP / 2 : C::BP;
     auto k = plain_rows_kernel<C, MODE, T, VEC>;
     allow_lds(k, C::LDS);
-    k<<<(unsigned)(row_tiles(S, E, C::BQ) * ceil_div(NOUT, BF)), C::NT, C::LDS, s>>>(d, E, F, offsets, in0, in1, perm, K, gates,
+    k<<<(unsigned)(max_row_tiles(S, E, C::BQ) * ceil_div(NOUT, BF)), C::NT, C::LDS, s>>>(d, E, F, offsets, in0, in1, perm, K, gates,
                                                                                      W0, W1, FA, FB, o0, o1, o2);
 }
 
 template <int MODE, typename T>
-hipError_t rows_any(int S, int d, int E, int F, const int32_t *offsets, const void *in0, const void *in1, const int32_t *perm,
-                    int K, const float *gates, const void *W0, const void *W1, const void *FA, const void *FB, void *o0,
+hipError_t rows_any(int S, int d, int E, int F, const int32_t *offsets, const void *in0, const void *in1, int Tn,
+                    const int32_t *perm, int K, const float *gates, const void *W0, const void *W1, const void *FA, const void *FB, void *o0,
                     void *o1, void *o2, hipStream_t s) {
     const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d;
     const bool vec = d % 4 == 0 && F % 4 == 0;
+    if constexpr (sizeof(T) == 4)
+        if (vec)
+            return f32_rows(MODE, S, d, E, F, offsets, (const T *)in0, (const T *)in1, Tn, perm, K, gates, (const T *)W0,
+                            (const T *)W1, (const T *)FA, (const T *)FB, (T *)o0, (T *)o1, (T *)o2, s);
     const bool big = ceil_div(S, 128) * ceil_div(NOUT, MODE == PLAIN_FFN1 ? 64 : 128) >= kFill;
 #define R3_ROWS(C, V)                                                                                                   \
     rows_launch<C, MODE, T, V>(S, d, E, F, offsets, (const T *)in0, (const T *)in1, perm, K, gates, (const T *)W0,      \
@@ -491,10 +446,10 @@ hipError_t rows_any(int S, int d, int E, int F, const int32_t *offsets, const vo
 
 template <int MODE>
 hipError_t rows_by_act(int act, int S, int d, int E, int F, const int32_t *offsets, const void *in0, const void *in1,
-                       const int32_t *perm, int K, const float *gates, const void *W0, const void *W1, const void *FA,
+                       int Tn, const int32_t *perm, int K, const float *gates, const void *W0, const void *W1, const void *FA,
                        const void *FB, void *o0, void *o1, void *o2, hipStream_t s) {
-    return act == R3_BF16 ? rows_any<MODE, bf16_t>(S, d, E, F, offsets, in0, in1, perm, K, gates, W0, W1, FA, FB, o0, o1, o2, s)
-                          : rows_any<MODE, float>(S, d, E, F, offsets, in0, in1, perm, K, gates, W0, W1, FA, FB, o0, o1, o2, s);
+    return act == R3_BF16 ? rows_any<MODE, bf16_t>(S, d, E, F, offsets, in0, in1, Tn, perm, K, gates, W0, W1, FA, FB, o0, o1, o2, s)
+                          : rows_any<MODE, float>(S, d, E, F, offsets, in0, in1, Tn, perm, K, gates, W0, W1, FA, FB, o0, o1, o2, s);
 }
 
 template <class C, typename T, bool VEC>
@@ -507,13 +462,17 @@ void wgrad_launch(int E, int K, const int32_t *offsets, PlainWgrad3<T> all, int 
 }
 
 template <typename T>
-hipError_t wgrads_any(int d, int E, int F, int K, const int32_t *offsets, const T *H, const T *dYrows,
+hipError_t wgrads_any(int d, int E, int F, int Tn, int K, const int32_t *offsets, const T *H, const T *dYrows,
                       const int32_t *dyperm, const T *xrows, const int32_t *xperm, const T *dA, const T *dB, float *dWg,
                       float *dWu, float *dWd, int accumulate, hipStream_t s) {
+    const bool vec = d % 4 == 0 && F % 4 == 0;
+    // (gathered rows by 32-bit offsets: a token matrix below 2 GB)
+    if constexpr (sizeof(T) == 4)
+        if (vec && ((!dyperm && !xperm) || (int64_t)Tn * d * 4 < (1ll << 31) - 16))
+            return f32_wgrads(d, E, F, Tn, K, offsets, H, dYrows, dyperm, xrows, xperm, dA, dB, dWg, dWu, dWd, accumulate, s);
     PlainWgrad3<T> all = {{{H, dYrows, nullptr, dyperm, dWd, F, d, 0},
                            {xrows, dA, xperm, nullptr, dWg, d, F, 0},
                            {xrows, dB, xperm, nullptr, dWu, d, F, 0}}};
-    const bool vec = d % 4 == 0 && F % 4 == 0;
     const bool big = 3 * (int64_t)E * ceil_div(d, 128) * ceil_div(F, 128) >= kFill;
     if (vec && big) wgrad_launch<PlainBig, T, true>(E, K, offsets, all, accumulate, s);
     else if (vec) wgrad_launch<PlainSmall, T, true>(E, K, offsets, all, accumulate, s);
@@ -562,40 +521,40 @@ hipError_t plain_router_logits(int T, int d, int E, int act, const void *x, cons
 hipError_t plain_ffn2(int S, int d, int E, int F, int act, const void *H, const int32_t *offsets, const void *Wd, void *Yp,
                       hipStream_t s) {
     ProfScope ps(PROF_FFN2, s);
-    return rows_by_act<PLAIN_DOWN>(act, S, d, E, F, offsets, H, nullptr, nullptr, 1, nullptr, Wd, nullptr, nullptr, nullptr, Yp,
+    return rows_by_act<PLAIN_DOWN>(act, S, d, E, F, offsets, H, nullptr, 0, nullptr, 1, nullptr, Wd, nullptr, nullptr, nullptr, Yp,
                                    nullptr, nullptr, s);
 }
 
-hipError_t plain_ffn1(int S, int d, int E, int F, int act, const void *rows, const int32_t *perm, int K,
+hipError_t plain_ffn1(int S, int d, int E, int F, int act, const void *rows, int T, const int32_t *perm, int K,
                       const int32_t *offsets, const void *Wg, const void *Wu, void *H, void *FA, void *FB, const float *gates,
                       hipStream_t s) {
     ProfScope ps(PROF_FFN1, s);
-    return rows_by_act<PLAIN_FFN1>(act, S, d, E, F, offsets, rows, nullptr, perm, K, gates, Wg, Wu, nullptr, nullptr, H, FA, FB,
+    return rows_by_act<PLAIN_FFN1>(act, S, d, E, F, offsets, rows, nullptr, T, perm, K, gates, Wg, Wu, nullptr, nullptr, H, FA, FB,
                                    s);
 }
 
 hipError_t plain_dh(int S, int d, int E, int F, int act, const void *dYp, const int32_t *offsets, const void *Wd,
                     const void *FA, const void *FB, void *dA, void *dB, hipStream_t s) {
     ProfScope ps(PROF_DH, s);
-    return rows_by_act<PLAIN_DH>(act, S, d, E, F, offsets, dYp, nullptr, nullptr, 1, nullptr, Wd, nullptr, FA, FB, dA, dB,
+    return rows_by_act<PLAIN_DH>(act, S, d, E, F, offsets, dYp, nullptr, 0, nullptr, 1, nullptr, Wd, nullptr, FA, FB, dA, dB,
                                  nullptr, s);
 }
 
 hipError_t plain_dxp(int S, int d, int E, int F, int act, const void *dA, const void *dB, const int32_t *offsets,
                      const void *Wg, const void *Wu, void *dXp, hipStream_t s) {
     ProfScope ps(PROF_DXP, s);
-    return rows_by_act<PLAIN_DXP>(act, S, d, E, F, offsets, dA, dB, nullptr, 1, nullptr, Wg, Wu, nullptr, nullptr, dXp, nullptr,
+    return rows_by_act<PLAIN_DXP>(act, S, d, E, F, offsets, dA, dB, 0, nullptr, 1, nullptr, Wg, Wu, nullptr, nullptr, dXp, nullptr,
                                   nullptr, s);
 }
 
-hipError_t plain_wgrads(int d, int E, int F, int K, int act, const int32_t *offsets, const void *H, const void *dYrows,
+hipError_t plain_wgrads(int d, int E, int F, int T, int K, int act, const int32_t *offsets, const void *H, const void *dYrows,
                         const int32_t *dyperm, const void *xrows, const int32_t *xperm, const void *dA, const void *dB,
                         float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s) {
     ProfScope ps(PROF_WGRAD, s);
     return act == R3_BF16
-               ? wgrads_any<bf16_t>(d, E, F, K, offsets, (const bf16_t *)H, (const bf16_t *)dYrows, dyperm, (const bf16_t *)xrows,
+               ? wgrads_any<bf16_t>(d, E, F, T, K, offsets, (const bf16_t *)H, (const bf16_t *)dYrows, dyperm, (const bf16_t *)xrows,
                                     xperm, (const bf16_t *)dA, (const bf16_t *)dB, dWg, dWu, dWd, accumulate, s)
-               : wgrads_any<float>(d, E, F, K, offsets, (const float *)H, (const float *)dYrows, dyperm, (const float *)xrows,
+               : wgrads_any<float>(d, E, F, T, K, offsets, (const float *)H, (const float *)dYrows, dyperm, (const float *)xrows,
                                    xperm, (const float *)dA, (const float *)dB, dWg, dWu, dWd, accumulate, s);
 }
 

@@ -1,5 +1,5 @@
 """The f32-arithmetic tile kernels (f32 layers, and bf16 widths the bf16 matrix kernels do not take) at the edges of
-their tiles: 64 x 64 and 128 x 128 outputs, 32 k per step, four elements per load where the widths allow it.  Forward in
+their tiles: 32 x 32, 64 x 64 and 128 x 128 outputs, 32 k per step, four elements per load where the widths allow it.  Forward in
 one call and backward, against the CPU oracle, with the bars of tests/util.py."""
 import numpy as np
 import pytest
@@ -18,6 +18,10 @@ SH = synth.LayerShape
     SH(T=65, d=64, E=2, K=1, F=128, act="f32", sigma=0.05, seed=62),     # whole tiles, one row over a tile
     SH(T=129, d=132, E=70, K=3, F=60, act="f32", sigma=0.05, seed=63),   # more experts than lanes, four elements over a tile
     SH(T=257, d=51, E=9, K=4, F=66, act="bf16", sigma=0.05, seed=64),    # bf16 widths no vector load fits
+    SH(T=3, d=4, E=5, K=2, F=4, act="f32", seed=66),                      # one 16-byte piece a row, experts without rows
+    SH(T=96, d=36, E=2, K=1, F=100, act="f32", sigma=0.05, seed=67),      # 32 x 32 tiles, a k-tile's second piece alone
+    SH(T=1030, d=68, E=3, K=2, F=640, act="f32", sigma=0.05, seed=68),    # 64 x 64 tiles forward (10 to a row), 32 x 32 backward
+    SH(T=700, d=516, E=4, K=3, F=1028, act="f32", sigma=0.05, zipf_s=1.0, seed=69),   # 64 x 64 tiles all through, four over a tile
     SH(T=2050, d=1028, E=10, K=4, F=1028, act="f32", sigma=0.05, zipf_s=0.7, seed=65),   # the 128 x 128 tiles, ragged on every side
 ], ids=lambda s: "T%d_d%d_F%d_E%d_K%d_%s" % (s.T, s.d, s.F, s.E, s.K, s.act))
 def test_layer_at_tile_edges(sh):

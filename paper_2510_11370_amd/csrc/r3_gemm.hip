@@ -261,12 +261,13 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
     char *const s0 = bufA, *const s1 = bufA + kStageBytes, *const s2 = bufB, *const s3 = bufB + kStageBytes;
     constexpr int BF = 128;  // features per tile
     const int npt = RAGGED ? (F + BF - 1) / BF : F / BF, nw = RAGGED ? (d + kBK3 - 1) / kBK3 : d / kBK3;
-    OpTR128x2 P;
+    OpTR128x2<!RAGGED> P;
     P.init(F * 2, 0, 64 * ((threadIdx.x >> 6) % kWP2));
     OpKC64<GATHER, false, false, RAGGED> Q;
     Q.init(d * 2, kWaveRowsQ * ((threadIdx.x >> 6) / kWP2));
     if constexpr (RAGGED) Q.set_tail(d);
     __shared__ int mailbox[2];
+    __shared__ __attribute__((aligned(256))) char gates_lds[4 * kTile];
     RowTileLoop tl(tiles + kTileX, npt, tile_counters(tiles, 0));
     struct Tile {
         int e, row0, row_end, f0;
@@ -289,16 +290,15 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
             // dispatch folded into the tile load: `Xp` is x [T,d]; each lane's eight rows of the tile
             // are read from their tokens' rows (rows past the end of the permutation repeat the last
             // one; they are never stored)
-            Q.src[0] = Src{(const char *)Xp, clamp_bytes((int64_t)T * d * 2), kBK3 * 2};
+            Q.set_source(0, Xp, clamp_bytes((int64_t)T * d * 2));
             const int chunk = Q.lane_chunk();
             int v[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] = (perm[min(t.row0 + Q.lane_row(i), S - 1)] / K) * (d * 2) + chunk;
             Q.set_rows(v);
         } else {
-            Q.src[0] = Src{(const char *)(Xp + (int64_t)t.row0 * d), clamp_bytes((int64_t)(S - t.row0) * d * 2), kBK3 * 2};
+            Q.set_source(0, Xp + (int64_t)t.row0 * d, clamp_bytes((int64_t)(S - t.row0) * d * 2));
         }
-        Q.src[1] = Q.src[0];
     };
     if (!tl.valid(tl.first())) return;
     Tile cur = decode(tl.first());
@@ -307,8 +307,13 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
     // the next tile's coordinates are fetched now (scalar loads), a whole tile before their use
     const bool more = tl.valid(next);
     const Tile nxt = more ? decode(next) : cur;
-    const int e = cur.e, row0 = cur.row0, row_end = cur.row_end, f0 = cur.f0;
+    const int row0 = cur.row0, row_end = cur.row_end, f0 = cur.f0;
+    if constexpr (RAGGED) {   // the guards of ragged widths need the registers (see rowgemm_kernel)
+        const int t0 = opaque_tid();
+        Q.set_lane(d * 2, kWaveRowsQ * ((t0 >> 6) / kWP2), t0);
+    }
 
+    if (grow) issue_row_gates(grow, row0, S, gates_lds);
     Acc2 acc;
     zero_acc2(acc);
     if (row_end - row0 <= kTailRows) mfma_tail_loop3(acc, nw, P, Q, lds, row_end - row0);
@@ -317,50 +322,63 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
     if (more) aim(nxt);   // here, so that the row-index loads of a gathered tile hide behind the epilogue
 
     // per wave: 64 rows x 64 features of H (and FA, FB), 32 rows at a time through LDS
-    // (three patches, so that one tensor's stores and the next one's deposits overlap)
+    // (three patches, so that one tensor's stores and the next one's deposits overlap); a tail tile: 64 or 32 rows x 32
     const int tid = opaque_tid();
-    const int lane = tid & 63, wq = (tid >> 6) / kWP2, wp = (tid >> 6) % kWP2;
+    const int lane = tid & 63;
+    const WaveTile wt(row_end - row0, tid);
     char *patch = wave_patch(s0, s1, s2, s3, tid);
     const int r16 = lane & 15, f4 = (lane >> 4) * 4;   // a lane's row and four features of every 16 x 16 tile
     const bool save = FA != nullptr;
+    // two copies: with the tail's conditions in it a full tile's came out 4 % slower; one at ragged widths, where two, with
+    // expf and a division each, outgrow the instruction cache (8 % slower)
+    auto epilogue = [&](auto is_tail) {
+        const bool tail = is_tail;
+        const int fw = f0 + (tail ? 32 * wt.quarter : 64 * ((tid >> 6) % kWP2));   // the wave's first feature
 #pragma unroll
-    for (int blk = 0; blk < kWaveRowsQ / 32; ++blk) {
-        const int brow = row0 + wq * kWaveRowsQ + blk * 32;           // first row of this block
-        const int valid = min(32, row_end - brow);             // may be <= 0
-        const int64_t o = ((int64_t)brow * F + f0 + wp * 64) * 2;  // byte offset of the block
-        RowStage<128> sh{patch, tid}, sa{patch + RowStage<128>::BYTES, tid}, sb{patch + 2 * RowStage<128>::BYTES, tid};
-        // grow != NULL: H leaves as g H, g the gate of the row's slot (the down projection then yields
-        // gated rows and the gradient of W_down finds its row operand ready); FA and FB are not scaled
+        for (int blk = 0; blk < kWaveRowsQ / 32; ++blk) {
+            if (tail && blk >= wt.blocks) continue;
+            const int brow = row0 + wt.row + blk * 32;             // first row of this block
+            const int valid = min(32, row_end - brow);             // may be <= 0
+            const int64_t o = ((int64_t)brow * F + fw) * 2;        // byte offset of the block
+            RowStage<128> sh{patch, tid}, sa{patch + RowStage<128>::BYTES, tid}, sb{patch + 2 * RowStage<128>::BYTES, tid};
+            // grow != NULL: H leaves as g H, g the gate of the row's slot (the down projection then yields
+            // gated rows and the gradient of W_down finds its row operand ready); FA and FB are not scaled
+            const float2 gates = grow ? row_gates(gates_lds, wt.row + blk * 32 + r16) : make_float2(1.0f, 1.0f);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            const int tq = 2 * blk + t, q = 16 * t + r16;
-            const float gq = grow ? (brow + q < row_end ? grow[brow + q] : 0.0f) : 1.0f;
+            for (int t = 0; t < 2; ++t) {
+                const int tq = 2 * blk + t, q = 16 * t + r16;
+                const float gq = t ? gates.y : gates.x;
 #pragma unroll
-            for (int tp = 0; tp < kHalfP; ++tp) {
-                float h[4], fa[4], fb[4];
+                for (int tp = 0; tp < kHalfP; ++tp) {
+                    if (tp >= 2 && tail) continue;
+                    float h[4], fa[4], fb[4];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const float a = acc[tp][tq][i], b = acc[tp + kHalfP][tq][i];
-                    const float sg = RAGGED ? sigmoidf_(a) : sigmoid_fast(a);
-                    fb[i] = a * sg;                                  // silu(a)
-                    h[i] = gq * (fb[i] * b);
-                    fa[i] = b * fmaf(fb[i], 1.0f - sg, sg);          // b silu'(a), silu'(a) = sg (1 + a (1 - sg))
-                }
-                const int bo = (tp * 16 + f4) * 2;
-                sh.put8(q, bo, pack4(h[0], h[1], h[2], h[3]));
-                if (save) {
-                    sa.put8(q, bo, pack4(fa[0], fa[1], fa[2], fa[3]));
-                    sb.put8(q, bo, pack4(fb[0], fb[1], fb[2], fb[3]));
+                    for (int i = 0; i < 4; ++i) {
+                        const float a = acc[tp][tq][i], b = acc[tp + kHalfP][tq][i];
+                        const float sg = RAGGED ? sigmoidf_(a) : sigmoid_fast(a);
+                        fb[i] = a * sg;                                  // silu(a)
+                        h[i] = gq * (fb[i] * b);
+                        fa[i] = b * fmaf(fb[i], 1.0f - sg, sg);          // b silu'(a), silu'(a) = sg (1 + a (1 - sg))
+                    }
+                    const int bo = (tp * 16 + f4) * 2;
+                    sh.put8(q, bo, pack4(h[0], h[1], h[2], h[3]));
+                    if (save) {
+                        sa.put8(q, bo, pack4(fa[0], fa[1], fa[2], fa[3]));
+                        sb.put8(q, bo, pack4(fb[0], fb[1], fb[2], fb[3]));
+                    }
                 }
             }
+            const int whole = tail ? 64 : 128, width = RAGGED ? min(whole, (F - fw) * 2) : whole;
+            sh.flush((char *)H + o, (int64_t)F * 2, valid, width);
+            if (save) {
+                sa.flush((char *)FA + o, (int64_t)F * 2, valid, width);
+                sb.flush((char *)FB + o, (int64_t)F * 2, valid, width);
+            }
         }
-        const int width = RAGGED ? (F - f0 - wp * 64) * 2 : 128;
-        sh.flush((char *)H + o, (int64_t)F * 2, valid, width);
-        if (save) {
-            sa.flush((char *)FA + o, (int64_t)F * 2, valid, width);
-            sb.flush((char *)FB + o, (int64_t)F * 2, valid, width);
-        }
-    }
+    };
+    if constexpr (RAGGED) epilogue(wt.quarter >= 0);
+    else if (wt.quarter >= 0) epilogue(std::true_type{});
+    else epilogue(std::false_type{});
     const int after = tl.finish(mailbox);
     slot = next;
     next = after;
@@ -403,7 +421,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     const int nw = (MODE == 2) ? 2 * nwk : nwk;
     const int wp0 = (threadIdx.x >> 6) % kWP2, wq0 = (threadIdx.x >> 6) / kWP2;
     // operand forms: the weights are feature-contiguous (TR) for MODE 0, K-contiguous otherwise
-    typedef typename std::conditional<MODE == 0, OpTR256, OpKC64<false, false, !RAGGED, RAGGED>>::type POp;
+    typedef typename std::conditional<MODE == 0, OpTR256<!RAGGED>, OpKC64<false, false, !RAGGED, RAGGED>>::type POp;
     constexpr bool GATHER = MODE == 1;     // Q rows through the row -> token list
     __shared__ int4 qstash[GATHER ? 2 * 256 : 1];   // the gathered rows' offsets (no registers to spare for them)
     POp P;
@@ -412,7 +430,6 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
 #endif
     OpKC64<GATHER, GATHER && R3_DH_STASH, false, RAGGED> Q;
     if constexpr (MODE == 0) {
-        P.kswitch = 0x7fffffff;
         P.init(d * 2, 0, 128 * wp0);
     } else {
         P.init((MODE == 1 ? d : F) * 2, 128 * wp0);
@@ -423,6 +440,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     if constexpr (MODE == 2) Q.wswitch = nwk;
     if constexpr (RAGGED) Q.set_tail(KQ);
     __shared__ int mailbox[2];
+    __shared__ __attribute__((aligned(256))) char gates_lds[MODE == 1 ? 4 * kTile : 4];
     RowTileLoop tl(tiles + kTileX, npt, tile_counters(tiles, MODE == 1 ? 0 : 1));
     struct Tile {
         int e, row0, row_end, p0;
@@ -442,28 +460,24 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
         if constexpr (GATHER) {
             // each lane's eight rows of the tile come from their tokens' rows of Q0 [T, KQ] (rows past the
             // end of the list read token 0: the list is padded with zeros; they are never stored)
-            Q.src[0] = Src{(const char *)Q0, clamp_bytes((int64_t)T * KQ * 2), kBK3 * 2};
+            Q.set_source(0, Q0, clamp_bytes((int64_t)T * KQ * 2));
             const int chunk = Q.lane_chunk();
             int v[8];
 #pragma unroll
             for (int i = 0; i < 8; ++i) v[i] = tok[min(t.row0 + Q.lane_row(i), S)] * (KQ * 2) + chunk;
             Q.set_rows(v);
         } else {
-            Q.src[0] = Src{(const char *)(Q0 + (int64_t)t.row0 * KQ), clamp_bytes((int64_t)(S - t.row0) * KQ * 2), kBK3 * 2};
+            Q.set_source(0, Q0 + (int64_t)t.row0 * KQ, clamp_bytes((int64_t)(S - t.row0) * KQ * 2));
         }
-        Q.src[1] = Q.src[0];
-        if constexpr (MODE == 2)
-            Q.src[1] = Src{(const char *)(Q1 + (int64_t)t.row0 * KQ), clamp_bytes((int64_t)(S - t.row0) * KQ * 2), kBK3 * 2};
+        if constexpr (MODE == 2) Q.set_source(1, Q1 + (int64_t)t.row0 * KQ, clamp_bytes((int64_t)(S - t.row0) * KQ * 2));
         if constexpr (MODE == 0) {
-            P.src[0] = Src{(const char *)(w0 + t.p0), clamp_bytes(((int64_t)d * F - t.p0) * 2), (uint32_t)(kBK2 * d * 2)};
-            P.src[1] = P.src[0];
+            P.src = Src{(const char *)(w0 + t.p0), clamp_bytes(((int64_t)d * F - t.p0) * 2), (uint32_t)(kBK2 * d * 2)};
         } else if constexpr (MODE == 1) {
-            P.src[0] = Src{(const char *)(w0 + (int64_t)t.p0 * d), clamp_bytes((int64_t)(F - t.p0) * d * 2), kBK3 * 2};
-            P.src[1] = P.src[0];
+            P.set_source(0, w0 + (int64_t)t.p0 * d, clamp_bytes((int64_t)(F - t.p0) * d * 2));
         } else {
             const bf16_t *w1 = W1 + (int64_t)t.e * d * F;
-            P.src[0] = Src{(const char *)(w0 + (int64_t)t.p0 * F), clamp_bytes((int64_t)(d - t.p0) * F * 2), kBK3 * 2};
-            P.src[1] = Src{(const char *)(w1 + (int64_t)t.p0 * F), clamp_bytes((int64_t)(d - t.p0) * F * 2), kBK3 * 2};
+            P.set_source(0, w0 + (int64_t)t.p0 * F, clamp_bytes((int64_t)(d - t.p0) * F * 2));
+            P.set_source(1, w1 + (int64_t)t.p0 * F, clamp_bytes((int64_t)(d - t.p0) * F * 2));
         }
     };
     if (!tl.valid(tl.first())) return;
@@ -488,6 +502,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
         Q.set_lane(KQ * 2, kWaveRowsQ * ((t0 >> 6) / kWP2), t0);
     }
 
+    if constexpr (MODE == 1) issue_row_gates(grow, row0, S, gates_lds);
     Acc2 acc;
     zero_acc2(acc);
     if (row_end - row0 <= kTailRows) mfma_tail_loop3(acc, nw, P, Q, lds, row_end - row0);
@@ -496,14 +511,18 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     if constexpr (GATHER)
         if (more) aim(nxt);   // here, so that the row-index loads of the next tile hide behind the epilogue
 
-    // per wave: 64 rows x 128 features, 32 rows at a time through LDS
+    // per wave: 64 rows x 128 features, 32 rows at a time through LDS; a tail tile: 64 or 32 rows x 64
     const int tid = opaque_tid();
-    const int lane = tid & 63, wq = (tid >> 6) / kWP2, wp = (tid >> 6) % kWP2;
+    const int lane = tid & 63;
+    const WaveTile wt(row_end - row0, tid);
+    const bool tail = wt.quarter >= 0;
+    const int wp = tail ? wt.quarter >> 1 : (tid >> 6) % kWP2;         // the wave's 128 features, of which a tail tile's wave
+    const int pw = tail ? 64 * wt.quarter : 128 * wp;                  // has the first or the second half
     RowStage<256> st{wave_patch(s0, s1, s2, s3, tid), tid};
     const int r16 = lane & 15, f4 = (lane >> 4) * 4;   // a lane's row and four features of every 16 x 16 tile
-    const int width = RAGGED ? (NOUT - p0 - wp * 128) * 2 : 256;   // bytes of this wave's features that exist
+    const int whole = tail ? 128 : 256, width = RAGGED ? min(whole, (NOUT - p0 - pw) * 2) : whole;   // bytes of the wave's features
     if constexpr (MODE == 1) {
-        // Four rounds of 32 rows x 64 features, each in three phases: FA -> dA, FB -> dB, H -> g H and the
+        // Rounds of 32 rows x 64 features (four, a tail tile two or one), each in three phases: FA -> dA, FB -> dB, H -> g H and the
         // row's dot product.  A phase's rows come in row-contiguously into a patch, each lane replaces
         // exactly the quads it read, and the patch goes out row-contiguously.  The rows of the phase
         // after next are asked for while this one is worked on: two 4 KB blocks in flight per wave (a
@@ -511,86 +530,100 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
         // 32-row block belong to two rows (r16 and 16 + r16).
         typedef RowStage<128> Patch;
         const Patch sa{st.base, tid}, sb{st.base + Patch::BYTES, tid}, sh{st.base + 2 * Patch::BYTES, tid};
-        constexpr int NPH = 3 * 2 * (kWaveRowsQ / 32);   // (GATED: the H phases only read)
-        auto where = [&](int ph, int &valid) -> int64_t {
-            const int r = ph / 3;
-            const int brow = row0 + wq * kWaveRowsQ + (r >> 1) * 32;
+        float *const wtail = (float *)(st.base + 3 * Patch::BYTES);   // tail tiles: the wave's share of its rows' dot products
+        constexpr int NR = 2 * (kWaveRowsQ / 32);   // (GATED: the H phases only read)
+        auto where = [&](int r, int &valid) -> int64_t {
+            const int brow = row0 + wt.row + (r >> 1) * 32;
             valid = min(32, row_end - brow);
-            return ((int64_t)brow * NOUT + p0 + wp * 128) * 2 + (r & 1) * 128;
+            return ((int64_t)brow * NOUT + p0 + pw) * 2 + (r & 1) * 128;
         };
-        auto ask = [&](int ph) -> Patch::Rows {
+        auto ask = [&](int r, int which) -> Patch::Rows {
             int valid;
-            const int64_t o = where(ph, valid);
-            const char *src = ph % 3 == 0 ? (const char *)FA : ph % 3 == 1 ? (const char *)FB : (const char *)Hs;
-            return sa.fetch(src + o, (int64_t)NOUT * 2, valid, width - 128 * (ph / 3 & 1));
+            const int64_t o = where(r, valid);
+            const char *src = which == 0 ? (const char *)FA : which == 1 ? (const char *)FB : (const char *)Hs;
+            return sa.fetch(src + o, (int64_t)NOUT * 2, valid, width - 128 * (r & 1));
         };
-#ifndef R3_DH_AHEAD
-#define R3_DH_AHEAD 1
-#endif
-        constexpr int AH = R3_DH_AHEAD;   // phases the row fetches run ahead (1 or 2)
-        Patch::Rows rr[2] = {ask(0), ask(AH == 2 ? 1 : 0)};
+        Patch::Rows rr = ask(0, 0);
         float gq[2] = {0.0f, 0.0f}, wsum[2] = {0.0f, 0.0f};
 #pragma unroll
-        for (int ph = 0; ph < NPH; ++ph) {
-            const int r = ph / 3, which = ph % 3, blk = r >> 1, half = r & 1;
-            const int brow = row0 + wq * kWaveRowsQ + blk * 32;
-            const Patch &sp = which == 0 ? sa : which == 1 ? sb : sh;
-            int valid;
-            const int64_t oh = where(ph, valid);
-            sp.deposit(rr[AH == 2 ? (ph & 1) : 0]);
-            if (ph + AH < NPH) rr[AH == 2 ? (ph & 1) : 0] = ask(ph + AH);
-            if (which == 0 && half == 0) {
+        for (int r = 0; r < NR; ++r) {
+            const int blk = r >> 1, half = r & 1;
+            if (blk >= wt.blocks || (half && tail)) continue;
+            const int brow = row0 + wt.row + blk * 32;
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    gq[t] = brow + 16 * t + r16 < row_end ? grow[brow + 16 * t + r16] : 0.0f;
-                    wsum[t] = 0.0f;
+            for (int which = 0; which < 3; ++which) {
+                const Patch &sp = which == 0 ? sa : which == 1 ? sb : sh;
+                int valid;
+                const int64_t oh = where(r, valid);
+                sp.deposit(rr);
+                if (which < 2) rr = ask(r, which + 1);
+                else if (r + 1 < NR) {
+                    const int rn = tail ? r + 2 : r + 1;   // the wave's next round
+                    if ((rn >> 1) < wt.blocks) rr = ask(rn, 0);
                 }
-            }
+                if (which == 0 && half == 0) {
+                    const float2 gates = row_gates(gates_lds, wt.row + blk * 32 + r16);
+                    gq[0] = gates.x;
+                    gq[1] = gates.y;
+                    wsum[0] = wsum[1] = 0.0f;
+                }
 #pragma unroll
-            for (int t = 0; t < 2; ++t)
+                for (int t = 0; t < 2; ++t)
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const int tp = half * 4 + g, tq = 2 * blk + t, q = 16 * t + r16;
-                    const int bo = (g * 16 + f4) * 2;
-                    float v[4], o[4];
-                    unpack4(sp.get8(q, bo), v);
+                    for (int g = 0; g < 4; ++g) {
+                        const int tp = half * 4 + g, tq = 2 * blk + t, q = 16 * t + r16;
+                        const int bo = (g * 16 + f4) * 2;
+                        float v[4], o[4];
+                        unpack4(sp.get8(q, bo), v);
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        const float u = acc[tp][tq][i];
-                        if (which == 2) {
-                            wsum[t] = fmaf(u, v[i], wsum[t]);
-                            o[i] = gq[t] * v[i];
-                        } else {
-                            o[i] = gq[t] * u * v[i];
+                        for (int i = 0; i < 4; ++i) {
+                            const float u = acc[tp][tq][i];
+                            if (which == 2) {
+                                wsum[t] = fmaf(u, v[i], wsum[t]);
+                                o[i] = gq[t] * v[i];
+                            } else {
+                                o[i] = gq[t] * u * v[i];
+                            }
                         }
+                        if (!(GATED && which == 2)) sp.put8(q, bo, pack4(o[0], o[1], o[2], o[3]));
                     }
-                    if (!(GATED && which == 2)) sp.put8(q, bo, pack4(o[0], o[1], o[2], o[3]));
-                }
-            bf16_t *dst = which == 0 ? out0 : which == 1 ? out1 : out2;
-            if (!(GATED && which == 2)) sp.flush((char *)dst + oh, (int64_t)NOUT * 2, valid, width - 128 * half);
-            if (which == 2 && half == 1) {
-                // the four lanes that hold a row add up; lanes 0..15 write the first 16 rows, 16..31 the others
-                float w[2];
+                bf16_t *dst = which == 0 ? out0 : which == 1 ? out1 : out2;
+                if (!(GATED && which == 2)) sp.flush((char *)dst + oh, (int64_t)NOUT * 2, valid, width - 128 * half);
+                if (which == 2 && (half == 1 || tail)) {
+                    // the four lanes that hold a row add up; lanes 0..15 write the first 16 rows, 16..31 the others
+                    float w[2];
 #pragma unroll
-                for (int t = 0; t < 2; ++t) {
-                    w[t] = wsum[t] + __shfl_xor(wsum[t], 16, 64);
-                    w[t] = (GATED ? 1.0f : gq[t]) * (w[t] + __shfl_xor(w[t], 32, 64));
+                    for (int t = 0; t < 2; ++t) {
+                        w[t] = wsum[t] + __shfl_xor(wsum[t], 16, 64);
+                        w[t] = (GATED ? 1.0f : gq[t]) * (w[t] + __shfl_xor(w[t], 32, 64));
+                    }
+                    const int q = lane & 31;
+                    const float wq = lane < 16 ? w[0] : w[1];
+                    if (lane < 32 && tail) wtail[32 * blk + q] = wq;
+                    else if (lane < 32 && brow + q < row_end)
+                        wpart[(int64_t)(brow + q) * (2 * npt) + 2 * (p0 / kTile) + wp] = wq;
                 }
-                const int q = lane & 31;
-                if (lane < 32 && brow + q < row_end)
-                    wpart[(int64_t)(brow + q) * (2 * npt) + 2 * (p0 / kTile) + wp] = lane < 16 ? w[0] : w[1];
             }
+        }
+        if (tail) {   // 128 features' products are two waves': the even one adds its neighbour's
+            asm volatile("s_waitcnt lgkmcnt(0)\n\ts_barrier" ::: "memory");
+            const float *other = (const float *)(wave_patch(s0, s1, s2, s3, tid ^ 64) + 3 * Patch::BYTES);
+            const int row = row0 + wt.row + lane;
+            if (!(wt.quarter & 1) && lane < 32 * wt.blocks && row < row_end)
+                wpart[(int64_t)row * (2 * npt) + 2 * (p0 / kTile) + wp] = wtail[lane] + other[lane];
         }
     } else {
 #pragma unroll
         for (int blk = 0; blk < kWaveRowsQ / 32; ++blk) {
-            const int brow = row0 + wq * kWaveRowsQ + blk * 32;
+            if (blk >= wt.blocks) continue;
+            const int brow = row0 + wt.row + blk * 32;
             const int valid = min(32, row_end - brow);
-            const int64_t o = ((int64_t)brow * NOUT + p0 + wp * 128) * 2;
+            const int64_t o = ((int64_t)brow * NOUT + p0 + pw) * 2;
 #pragma unroll
             for (int t = 0; t < 2; ++t)
 #pragma unroll
                 for (int tp = 0; tp < kTP2; ++tp) {
+                    if (tp >= kTailP && tail) continue;
                     const f32x4_t v = acc[tp][2 * blk + t];
                     st.put8(16 * t + r16, (tp * 16 + f4) * 2, pack4(v[0], v[1], v[2], v[3]));
                 }
@@ -625,13 +658,11 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
     const int nqt = RAGGED ? (NQd + kTile - 1) / kTile : NQd / kTile, npt = RAGGED ? (NPd + kTile - 1) / kTile : NPd / kTile;
     const int wp0 = (threadIdx.x >> 6) % kWP2, wq0 = (threadIdx.x >> 6) / kWP2;
     // operands are set up once; a tile only moves their source windows (column offset included)
-    typename std::conditional<GATHER, OpTR256G, OpTR256>::type P;
-    OpTR256 Q;
-    Q.kswitch = 0x7fffffff;
+    typename std::conditional<GATHER, OpTR256G, OpTR256<>>::type P;
+    OpTR256<> Q;
     if constexpr (GATHER) {
         P.init(NPd * 2, 128 * wp0, ring);
     } else {
-        P.kswitch = 0x7fffffff;
         P.init(NPd * 2, 0, 128 * wp0);
     }
     Q.init(NQd * 2, 0, kWaveRowsQ * wq0);
@@ -649,13 +680,11 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
     if constexpr (GATHER) {
         P.aim(Ps, (uint64_t)nrows * NPd * 2, p0 * 2, tok + r0, r1 - r0);
     } else {
-        P.src[0] = Src{(const char *)(Ps + (int64_t)r0 * NPd + p0), clamp_bytes(((int64_t)(r1 - r0) * NPd - p0) * 2),
-                       (uint32_t)(kBK2 * NPd * 2)};
-        P.src[1] = P.src[0];
+        P.src = Src{(const char *)(Ps + (int64_t)r0 * NPd + p0), clamp_bytes(((int64_t)(r1 - r0) * NPd - p0) * 2),
+                    (uint32_t)(kBK2 * NPd * 2)};
     }
-    Q.src[0] = Src{(const char *)(Qs + (int64_t)r0 * NQd + q0), clamp_bytes(((int64_t)(r1 - r0) * NQd - q0) * 2),
-                   (uint32_t)(kBK2 * NQd * 2)};
-    Q.src[1] = Q.src[0];
+    Q.src = Src{(const char *)(Qs + (int64_t)r0 * NQd + q0), clamp_bytes(((int64_t)(r1 - r0) * NQd - q0) * 2),
+                (uint32_t)(kBK2 * NQd * 2)};
 
     Acc2 acc;
     zero_acc2(acc);
@@ -720,13 +749,12 @@ wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t
     constexpr int BF = 128;  // features of P0 (and of P1) per tile
     const int nqt = RAGGED ? (NQd + kTile - 1) / kTile : NQd / kTile, npt = RAGGED ? (NPd + BF - 1) / BF : NPd / BF;
     const int wp0 = (threadIdx.x >> 6) % kWP2, wq0 = (threadIdx.x >> 6) / kWP2;
-    OpTR128x2 P;
+    OpTR128x2<> P;
     P.init(NPd * 2, 0, 64 * wp0);
-    typename std::conditional<GATHER, OpTR256G, OpTR256>::type Q;
+    typename std::conditional<GATHER, OpTR256G, OpTR256<>>::type Q;
     if constexpr (GATHER) {
         Q.init(NQd * 2, kWaveRowsQ * wq0, ring);
     } else {
-        Q.kswitch = 0x7fffffff;
         Q.init(NQd * 2, 0, kWaveRowsQ * wq0);
     }
     // reduction segments as in wgrad_kernel: an expert's rows or one part of them
@@ -746,9 +774,8 @@ wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t
     if constexpr (GATHER) {
         Q.aim(Qs, (uint64_t)nrows * NQd * 2, q0 * 2, tok + r0, r1 - r0);
     } else {
-        Q.src[0] = Src{(const char *)(Qs + (int64_t)r0 * NQd + q0), clamp_bytes(((int64_t)(r1 - r0) * NQd - q0) * 2),
-                       (uint32_t)(kBK2 * NQd * 2)};
-        Q.src[1] = Q.src[0];
+        Q.src = Src{(const char *)(Qs + (int64_t)r0 * NQd + q0), clamp_bytes(((int64_t)(r1 - r0) * NQd - q0) * 2),
+                    (uint32_t)(kBK2 * NQd * 2)};
     }
 
     Acc2 acc;

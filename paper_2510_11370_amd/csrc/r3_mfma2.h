@@ -82,6 +82,15 @@ __device__ __forceinline__ rsrc_t src_rsrc(const Src &s, int kt, uint32_t extra 
     return r;
 }
 
+// The same for a window that lies inside its buffer whatever the lane offsets are (a weight panel whose rows and columns all
+// exist): nothing to check, which leaves a third of the scalar instructions.
+__device__ __forceinline__ rsrc_t src_rsrc_inside(const Src &s, int kt) {
+    const uint64_t b = (uint64_t)s.base + (uint64_t)(uint32_t)kt * s.step;
+    rsrc_t r = {__builtin_amdgcn_readfirstlane((int)(uint32_t)b),
+                __builtin_amdgcn_readfirstlane((int)((uint32_t)(b >> 32) & 0xffffu)), kOutsideWindow, (int)kRsrcFlags};
+    return r;
+}
+
 // LDS byte address of a __shared__ object (the low half of its generic address)
 __device__ __forceinline__ uint32_t lds_addr(const void *p) { return (uint32_t)(uintptr_t)(lds_void_ptr)p; }
 
@@ -130,7 +139,7 @@ struct KcFrag16 {
 template <int R>
 struct TrFrag16 {
     int at;
-    __device__ __forceinline__ void init(int wave_base) {   // wave_base: a multiple of 64 features
+    __device__ __forceinline__ void init(int wave_base) {   // wave_base: a multiple of the wave's features
         const int lane = lane_id(), b = lane >> 4, i = lane & 15, k = 8 * b + (i >> 2);
         at = k * (2 * R) + (((wave_base >> 4) ^ tr_swz(k)) << 5) + (i & 3) * 8;
     }
@@ -173,13 +182,12 @@ struct DmaTR {
 //   TR256  : one Src
 //   TR128x2: two Src (sub-tile 0 at tile+0, sub-tile 1 at tile+8 KB); MFMA tiles 0..3 of a
 //            wave come from sub-tile 0 and tiles 4..7 from sub-tile 1 at the same features
-// A second Src set takes over from k-tile `kswitch` on (two-phase reductions).
+template <bool INSIDE = false>   // every k-row of every tile, and every column, exists
 struct OpTR256 {
     static constexpr bool kIndexed = false, kWindowed = false;
     static constexpr int kLoads = 4;
     static constexpr int kReads = 2;   // LDS reads per fragment
-    Src src[2];
-    int kswitch;
+    Src src;
     DmaTR<256> dma;
     TrFrag16<256> fr;
     __device__ __forceinline__ void init(int ld_bytes, int col_bytes, int wave_base) {
@@ -187,13 +195,19 @@ struct OpTR256 {
         fr.init(wave_base);
     }
     __device__ __forceinline__ void issue(int kt, uint32_t tile) const {
-        const bool second = kt >= kswitch;
-        const Src &s = second ? src[1] : src[0];
-        dma.issue(src_rsrc(s, second ? kt - kswitch : kt), tile);
+        dma.issue(INSIDE ? src_rsrc_inside(src, kt) : src_rsrc(src, kt), tile);
     }
     __device__ __forceinline__ bf16x8_t frag(const char *tile, int t) const { return fr.read(tile, t); }
+    // fragments of a tail tile (mfma_tail_loop3): the wave's 64 features as four MFMA tiles
+    struct Tail {
+        TrFrag16<256> fr;
+        __device__ __forceinline__ void init(int quarter) { fr.init(64 * quarter); }
+        __device__ __forceinline__ bf16x8_t read(const char *win, int t, int u) const { return fr.read(win + u * kOperandBytes, t); }
+        static constexpr int acc(int t) { return t; }
+    };
 };
 
+template <bool INSIDE = false>
 struct OpTR128x2 {
     static constexpr bool kIndexed = false, kWindowed = false;
     static constexpr int kLoads = 4;
@@ -206,12 +220,21 @@ struct OpTR128x2 {
         fr.init(wave_base);
     }
     __device__ __forceinline__ void issue(int kt, uint32_t tile) const {
-        dma.issue(src_rsrc(src[0], kt), tile);
-        dma.issue(src_rsrc(src[1], kt), tile + kOperandBytes / 2);
+        dma.issue(INSIDE ? src_rsrc_inside(src[0], kt) : src_rsrc(src[0], kt), tile);
+        dma.issue(INSIDE ? src_rsrc_inside(src[1], kt) : src_rsrc(src[1], kt), tile + kOperandBytes / 2);
     }
     __device__ __forceinline__ bf16x8_t frag(const char *tile, int t) const {
         return fr.read(tile + (t / kHalfP) * (kOperandBytes / 2), t % kHalfP);
     }
+    // a tail tile: 32 features of each sub-tile, accumulated where a full tile's first two MFMA tiles of each are
+    struct Tail {
+        TrFrag16<128> fr;
+        __device__ __forceinline__ void init(int quarter) { fr.init(32 * quarter); }
+        __device__ __forceinline__ bf16x8_t read(const char *win, int t, int u) const {
+            return fr.read(win + u * kOperandBytes + (t >> 1) * (kOperandBytes / 2), t & 1);
+        }
+        static constexpr int acc(int t) { return (t >> 1) * kHalfP + (t & 1); }
+    };
 };
 
 // Transposed 256-feature tile whose k-rows are gathered through an index: k-row r of the reduction is
@@ -546,8 +569,14 @@ struct OpKC64 {
         ktail = (width - wlast * kBK3) / 8;
     }
     static constexpr bool kIndexed = false, kWindowed = true;
-    Src src[2];
-    int wswitch;           // window from which src[1] takes over (two-phase reductions)
+    Src src[2];            // INSIDE
+    rsrc_t rs[2];          // else: a whole tile's rows, bounds included
+    int wswitch;           // window from which the second source takes over (two-phase reductions)
+    // a source of row tiles: `bytes` from its first row to the matrix's end; of those a tile's rows at most are seen
+    __device__ __forceinline__ void set_source(int i, const void *base, uint64_t bytes) {
+        if constexpr (INSIDE) src[i] = Src{(const char *)base, bytes, kBK3 * 2};
+        else rs[i] = src_rsrc(Src{(const char *)base, bytes, 0u}, 0);
+    }
     int voff[(ROWS && !STASH) ? 8 : 1];
     int step;              // bytes between a lane's consecutive chunks (32 rows)
     int4 *stash;           // STASH: this thread's first slot; the second is 256 slots on
@@ -567,7 +596,7 @@ struct OpKC64 {
     // made anew per tile and are not carried through the epilogue in registers.
     __device__ __forceinline__ void set_lane(int ld_bytes, int wave_base, int tid, int4 *stash_base = nullptr) {
         tid_ = tid;
-        step = 32 * ld_bytes;
+        step = __builtin_amdgcn_readfirstlane(32 * ld_bytes);
         if constexpr (!ROWS) voff[0] = lane_row(0) * ld_bytes + lane_chunk();   // (gathered rows: set_rows())
         stash = stash_base + (tid & 255);
         fr.init(wave_base, tid & 63);
@@ -591,17 +620,19 @@ struct OpKC64 {
     // rows: only rows [0, rows) of the window are wanted (a multiple of 64; the rest is left as it is)
     __device__ __forceinline__ void issue_window(int J, uint32_t win, int rows = kTile) const {
         const bool second = J >= wswitch;
-        const Src &s = second ? src[1] : src[0];
         const int Js = second ? J - wswitch : J;
         const int w = threadIdx.x >> 6;
-        const rsrc_t r = src_rsrc(s, Js);
         if constexpr (!ROWS && INSIDE) {
+            const rsrc_t r = src_rsrc_inside(second ? src[1] : src[0], Js);
 #pragma unroll
             for (int i = 0; i < 8; ++i)
                 if (rows == kTile || (i < 6 && 32 * i < rows))
                     lds_load16_soff(r, win + 1024 * ((w & 3) + kLoaderWaves * i), voff[0], i * step);
             return;
         }
+        // the reduction advances in the lane offsets, under one descriptor per tile
+        const rsrc_t r = second ? rs[1] : rs[0];
+        const int adv = Js * (kBK3 * 2);
         int vo[8];
         if constexpr (STASH) {
             // read as inline asm: left to the compiler, the two reads are hoisted out of the window loop
@@ -613,9 +644,16 @@ struct OpKC64 {
                          : "memory");
             vo[0] = a.x; vo[1] = a.y; vo[2] = a.z; vo[3] = a.w;
             vo[4] = b.x; vo[5] = b.y; vo[6] = b.z; vo[7] = b.w;
+#pragma unroll
+            for (int i = 0; i < 8; ++i) vo[i] += adv;
         } else {
 #pragma unroll
-            for (int i = 0; i < 8; ++i) vo[i] = ROWS ? voff[(ROWS && !STASH) ? i : 0] : voff[0] + i * step;
+            for (int i = 0; i < 8; ++i) {
+                // one scalar sum, opaque: the compiler would keep the eight lane sums voff + i step in registers
+                int sum = ROWS ? adv : adv + i * step;
+                asm("" : "+s"(sum));
+                vo[i] = voff[(ROWS && !STASH) ? i : 0] + sum;
+            }
         }
         if constexpr (TAIL) {
             if (Js == wlast && lane_chunk() >= 16 * ktail) {
@@ -635,6 +673,12 @@ struct OpKC64 {
     }
     __device__ __forceinline__ bf16x8_t frag_window(const char *win, int t, int u) const { return fr.read(win, t, u); }
     static constexpr int kReads = 1;
+    struct Tail {
+        KcFrag16 fr;
+        __device__ __forceinline__ void init(int quarter) { fr.init(64 * quarter, lane_id()); }
+        __device__ __forceinline__ bf16x8_t read(const char *win, int t, int u) const { return fr.read(win, t, u); }
+        static constexpr int acc(int t) { return t; }
+    };
 };
 
 // a 32-k tile operand as a window: tiles 2J and 2J+1 back to back
@@ -755,20 +799,22 @@ __device__ __forceinline__ void mfma_mainloop3(Acc2 &acc, int nw, const POp &P, 
 
 // ---------------------------------------------------------------------------
 // The same loop for a tail tile: at most 128 live rows (the last rows of an expert's segment, or all of a
-// rarely chosen expert's).  Such a tile waited for its weight windows, so the space the dead rows of the Q windows would
-// take holds a third window instead and the loads run two windows ahead.  What it costs then, about half a full tile, is the
-// chain of the few waves that multiply (two of eight at up to 64 rows: 1024 cycles a window, a full tile 2048).
+// rarely chosen expert's).  In the full tiles' arrangement only the waves of live 64-row blocks would multiply (two of eight at
+// up to 64 rows, 1024 cycles of the matrix pipe a window where a full tile needs 2048); here all eight share the live rows:
+// four quarters of the features by two halves of the rows, 64 rows each above 64 live rows and 32 below, so that a window takes
+// 1024 or 512 cycles, on every SIMD two waves to cover each other.  The space the dead rows of the Q windows would
+// take holds a third window, so the loads run two windows ahead.
 // `lds` is the work-group's kRowLds bytes: P windows at 0, 32, 64 KB; Q windows (rows 0..127 only, 16 KB
-// each) from 96 KB.  Only the waves of live 64-row blocks multiply; waves 0-3 load.
+// each) from 96 KB.  Waves 0-3 load.
 // A loader wave issues 8 loads for P and 2 per 64 rows for Q, so "at most that many outstanding" is "the next
 // window is in" as long as the one after it has been issued.
-// (Rows 65..128 in the two-window loop instead: 128 experts, d=2048 F=768, 1001 tokens top-8, SwiGLU 194 -> 177 us,
-// down 95 -> 86, dH 131 -> 117, dXp 229 -> 213.)
+// A lane's results: rows wave_row + 16 j + lane % 16, acc[POp::Tail::acc(i)][j] (i: the wave's MFMA tiles along the features).
 // ---------------------------------------------------------------------------
 constexpr int kTailRows = 2 * kWaveRowsQ;
 constexpr int kTailQBytes = kTailRows * kBK3 * 2;                        // 16 KB: 128 rows of a Q window
 constexpr int kTailQBase = 3 * kWinBytes;
 constexpr int kRowLds = kTailQBase + 3 * kTailQBytes;                    // 144 KB (the full tiles' loop uses 128)
+constexpr int kTailP = 4;                                                // MFMA tiles of a wave along the features
 
 template <int LOADS>
 __device__ __forceinline__ void tail_wait() {
@@ -782,17 +828,32 @@ __device__ __forceinline__ void tail_barrier(bool loader, bool one_ahead, bool w
     __builtin_amdgcn_s_barrier();
 }
 
-template <class POp, class QOp>
-__device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P, const QOp &Q, char *lds, int live_rows) {
-    if (nw <= 0) return;
+template <class PT, int TQ>
+__device__ __forceinline__ void tail_mul(Acc2 &acc, const bf16x8_t (&a)[kTailP], const bf16x8_t (&b)[TQ]) {
+#pragma unroll
+    for (int j = 0; j < TQ; ++j)
+#pragma unroll
+        for (int ii = 0; ii < kTailP; ++ii) {
+            const int i = (j & 1) ? kTailP - 1 - ii : ii;
+            acc[PT::acc(i)][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[PT::acc(i)][j], 0, 0, 0);
+        }
+}
+
+// TQ: MFMA tiles of a wave along the rows (4: 64 rows, 2: 32).  A 32-k step is read while the one before is multiplied.
+template <int TQ, class POp, class QOp>
+__device__ __forceinline__ void tail_windows(Acc2 &acc, int nw, const POp &P, const QOp &Q, char *lds, int live_rows) {
     const uint32_t a0 = lds_addr(lds);
     const int wave_ = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const bool loader = wave_ < kLoaderWaves, wide = live_rows > kWaveRowsQ;
-    const bool live = (wave_ / kWP2) * kWaveRowsQ < live_rows;
-    const int qrows = wide ? kTailRows : kWaveRowsQ;
+    constexpr bool wide = TQ * 16 == kWaveRowsQ;
+    const bool loader = wave_ < kLoaderWaves, live = (wave_ >> 2) * 16 * TQ < live_rows;
+    typedef typename POp::Tail PT;
+    PT pt;
+    KcFrag16 qt;
+    pt.init(wave_ & 3);
+    qt.init((wave_ >> 2) * 16 * TQ, lane_id());
     auto issue = [&](int J, int slot) {
         win_issue(P, J, a0 + slot * kWinBytes);
-        win_issue(Q, J, a0 + kTailQBase + slot * kTailQBytes, qrows);
+        win_issue(Q, J, a0 + kTailQBase + slot * kTailQBytes, wide ? kTailRows : kWaveRowsQ);
     };
     if (loader) {
         if constexpr (POp::kIndexed || QOp::kIndexed) {
@@ -805,8 +866,26 @@ __device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P,
         }
     }
     tail_barrier(loader, nw > 1, wide);
-    Frags f;
-    f.clear();
+    bf16x8_t xa[kTailP], ya[kTailP], xb[TQ], yb[TQ];
+#pragma unroll
+    for (int i = 0; i < kTailP; ++i) xa[i] = bf16x8_t{};
+#pragma unroll
+    for (int j = 0; j < TQ; ++j) xb[j] = bf16x8_t{};
+    auto step = [&](const char *pw, const char *qw, int u, const bf16x8_t(&ca)[kTailP], const bf16x8_t(&cb)[TQ], bf16x8_t(&na)[kTailP],
+                    bf16x8_t(&nb)[TQ]) {
+#pragma unroll
+        for (int i = 0; i < kTailP; ++i) na[i] = pt.read(pw, i, u);
+#pragma unroll
+        for (int j = 0; j < TQ; ++j) nb[j] = qt.read(qw, j, u);
+        tail_mul<PT, TQ>(acc, ca, cb);
+        constexpr int reads = kTailP * POp::kReads + TQ, per = (reads + kTailP * TQ - 1) / (kTailP * TQ);
+#pragma unroll
+        for (int i = 0; i < kTailP * TQ; ++i) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);    // MFMA
+            __builtin_amdgcn_sched_group_barrier(0x100, per, 0);  // DS read
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
     // window J sits in slot J % 3; window J + 2 goes into the slot window J - 1 has just left
     auto window = [&](int J, int slot) {
         const int nslot = slot == 0 ? 2 : slot - 1;   // (slot + 2) % 3
@@ -814,13 +893,8 @@ __device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P,
         __builtin_amdgcn_sched_barrier(0);
         if (live) {
             const char *pw = lds + slot * kWinBytes, *qw = lds + kTailQBase + slot * kTailQBytes;
-#pragma unroll
-            for (int u = 0; u < 2; ++u) {
-                auto fp = [&](int i) { return win_frag(P, pw, i, u); };
-                auto fq = [&](int j) { return win_frag(Q, qw, j, u); };
-                step_first<POp::kReads, QOp::kReads>(acc, f, fp, fq);
-                step_second<POp::kReads, QOp::kReads>(acc, f, fp, fq);
-            }
+            step(pw, qw, 0, xa, xb, ya, yb);
+            step(pw, qw, 1, ya, yb, xa, xb);
         }
         tail_barrier(loader, J + 2 < nw, wide);
     };
@@ -829,8 +903,49 @@ __device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P,
         if (J + 1 < nw) window(J + 1, 1);
         if (J + 2 < nw) window(J + 2, 2);
     }
-    if (live) step_last(acc, f);
+    if (live) tail_mul<PT, TQ>(acc, xa, xb);
 }
+
+template <class POp, class QOp>
+__device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P, const QOp &Q, char *lds, int live_rows) {
+    if (nw <= 0) return;
+    if (live_rows > kWaveRowsQ) tail_windows<4>(acc, nw, P, Q, lds, live_rows);
+    else tail_windows<2>(acc, nw, P, Q, lds, live_rows);
+}
+
+// The gates of a row tile's 256 rows travel like its operands, to 1 KB of LDS outside the windows, ahead of the first window:
+// read from memory in the epilogue they would be waited for there, behind the stores of the rows before them (the memory
+// counter runs in order).  A dword per lane, waves 0-3; rows past the last one of the batch read as zero.
+__device__ __forceinline__ void issue_row_gates(const float *grow, int row0, int S, const char *gates_lds) {
+    const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    if (w >= kLoaderWaves) return;
+    const rsrc_t r = src_rsrc(Src{(const char *)(grow + row0), (uint64_t)(S - row0) * 4u, 0u}, 0);
+    const uint32_t m0v = __builtin_amdgcn_readfirstlane(lds_addr(gates_lds) + 256u * w);
+    asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dword %1, %2, 0 offen lds" ::"s"(m0v), "v"((int)(threadIdx.x & 255) * 4), "s"(r)
+                 : "memory");
+}
+// rows `row` and `row + 16` of the tile (inline asm: the compiler knows of no store to that space)
+__device__ __forceinline__ float2 row_gates(const char *gates_lds, int row) {
+    float2 g;
+    asm volatile("ds_read2_b32 %0, %1 offset0:0 offset1:16\n\ts_waitcnt lgkmcnt(0)"
+                 : "=v"(g)
+                 : "v"(lds_addr(gates_lds) + 4u * row)
+                 : "memory");
+    return g;
+}
+
+// Which rows and features of a row tile a wave's accumulators hold, as blocks of 32 rows: a full tile's wave has two blocks of
+// 128 features; a tail tile's has 64 features and two blocks, or one at up to 64 live rows.
+struct WaveTile {
+    int row, blocks, quarter;   // first row; blocks of 32 rows; tail tiles: the wave's quarter of the features, else -1
+    __device__ __forceinline__ WaveTile(int rows, int tid) {
+        const int w = tid >> 6;
+        const bool tail = rows <= kTailRows;
+        row = !tail ? (w / kWP2) * kWaveRowsQ : (w >> 2) * (rows > kWaveRowsQ ? 64 : 32);
+        blocks = tail && rows <= kWaveRowsQ ? 1 : 2;
+        quarter = tail ? w & 3 : -1;
+    }
+};
 
 // Persistent work-groups.  A launch has one work-group per compute unit; each walks the tile
 // list instead of ending after one tile, so a tile's stores drain while the next tile's first

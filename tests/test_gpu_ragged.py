@@ -99,6 +99,55 @@ def test_rows_per_expert_at_tile_edges(d, F):
             assert np.linalg.norm(got[e] - ref[key][e]) <= c.rel * np.linalg.norm(ref[key][e]) + 1e-30, (key, e)
 
 
+@pytest.mark.parametrize("one_call", [True, False])
+@pytest.mark.parametrize("d,F", [(256, 512), (264, 136)])     # whole tiles; guarded ones
+def test_tail_tiles(d, F, one_call):
+    """Row tiles of at most 128 rows, whose rows and features all eight waves share: at the edges of a wave's 16- and 32-row blocks
+    and of the two arrangements, alone and behind a full tile."""
+    rows = [15, 16, 17, 31, 32, 33, 48, 63, 95, 96, 97, 127, 256 + 32, 256 + 33, 256 + 96, 256 + 97]
+    sh = SH(T=sum(rows), d=d, E=len(rows), K=1, F=F, seed=78)
+    c = Case(sh, backward=True, scale_w=5.0)
+    c.idx = np.random.default_rng(1).permutation(np.repeat(np.arange(len(rows)), rows)).astype(np.int32)[:, None]
+    c.t["idx"] = torch.from_numpy(c.idx.astype(np.uint8)).to("cuda")
+    n = c.np
+    fwd = sparse.forward(n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], n["bias"])
+    ref = sparse.backward(n["dy"], n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], fwd, want_dbias=True)
+    w = (c.t["Wg"], c.t["Wu"], c.t["Wd"])
+    buf = r3.LayerBuffers(c.D, backward=True, gathered_copy=False)
+    for t in (buf.Yp, buf.H, buf.A, buf.B, buf.dx):
+        t.fill_(7.0)
+    (r3.forward_one_call if one_call else r3.forward)(buf, c.t["x"], c.t["Wr"], c.t["idx"], *w, bias=c.t["bias"])
+    r3.backward(buf, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], *w)
+    torch.cuda.synchronize()
+    assert buf.counts.tolist() == rows
+    for got, want, name in ((buf.H, fwd["h"], "H"), (buf.Yp, fwd["o"], "Yp"), (buf.y, fwd["y"], "y"), (buf.dx, ref["dx"], "dx")):
+        assert_close(host(got), want, name, c.rel)      # (one expert per token: the gate is 1)
+    for got, key in ((buf.dW_gate, "dWg"), (buf.dW_up, "dWu"), (buf.dW_down, "dWd")):
+        got = got.cpu().numpy()
+        for e in range(sh.E):
+            assert np.linalg.norm(got[e] - ref[key][e]) <= c.rel * np.linalg.norm(ref[key][e]) + 1e-30, (key, e)
+
+
+@pytest.mark.parametrize("one_call", [True, False])
+def test_gate_products_of_tail_tiles(one_call):
+    """K > 1, experts of a few rows up to 128: the products <dy, o> that the gate's gradient is made of come from pairs of waves."""
+    sh = SH(T=300, d=512, E=24, K=4, F=512, sigma=0.05, zipf_s=0.8, seed=79)
+    c = Case(sh, backward=True, scale_w=5.0)
+    n = c.np
+    fwd = sparse.forward(n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], n["bias"])
+    ref = sparse.backward(n["dy"], n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], fwd, want_dbias=True)
+    w = (c.t["Wg"], c.t["Wu"], c.t["Wd"])
+    buf = r3.LayerBuffers(c.D, backward=True, gathered_copy=False)
+    dbias = torch.zeros(sh.E, dtype=torch.float32, device="cuda")
+    (r3.forward_one_call if one_call else r3.forward)(buf, c.t["x"], c.t["Wr"], c.t["idx"], *w, bias=c.t["bias"])
+    r3.backward(buf, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], *w, dbias=dbias)
+    torch.cuda.synchronize()
+    sig_w, sig_b = router_gradient_sigma(n["x"], n["dy"], c.idx, fwd, sh.E)
+    assert_close(buf.dW_r.cpu().numpy(), ref["dWr"], "dW_r", c.rel, sig_w)
+    assert_close(dbias.cpu().numpy(), ref["dbias"], "dbias", c.rel, sig_b)
+    assert_close(host(buf.dx), ref["dx"], "dx", c.rel)
+
+
 def test_masked_lanes_of_sources_past_two_gigabytes():
     """Width 1032: the last window of a reduction has 8 live values, the other lanes fetch nothing, also where more than
     2 GB of the source are left: NaN in rows 2 GB on stay where they are."""

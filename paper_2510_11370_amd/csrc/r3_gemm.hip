@@ -263,8 +263,9 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
     const int npt = RAGGED ? (F + BF - 1) / BF : F / BF, nw = RAGGED ? (d + kBK3 - 1) / kBK3 : d / kBK3;
     OpTR128x2<!RAGGED> P;
     P.init(F * 2, 0, 64 * ((threadIdx.x >> 6) % kWP2));
-    OpKC64<GATHER, false, false, RAGGED> Q;
-    Q.init(d * 2, kWaveRowsQ * ((threadIdx.x >> 6) / kWP2));
+    __shared__ int4 qstash[GATHER ? 2 * 256 : 1];   // the gathered rows' offsets (no registers to spare for them)
+    OpKC64<GATHER, GATHER, false, RAGGED> Q;
+    Q.init(d * 2, kWaveRowsQ * ((threadIdx.x >> 6) / kWP2), qstash);
     if constexpr (RAGGED) Q.set_tail(d);
     __shared__ int mailbox[2];
     __shared__ __attribute__((aligned(256))) char gates_lds[4 * kTile];
@@ -308,16 +309,16 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
     const bool more = tl.valid(next);
     const Tile nxt = more ? decode(next) : cur;
     const int row0 = cur.row0, row_end = cur.row_end, f0 = cur.f0;
-    if constexpr (RAGGED) {   // the guards of ragged widths need the registers (see rowgemm_kernel)
+    {   // lane constants made anew for every tile (see rowgemm_kernel)
         const int t0 = opaque_tid();
-        Q.set_lane(d * 2, kWaveRowsQ * ((t0 >> 6) / kWP2), t0);
+        Q.set_lane(d * 2, kWaveRowsQ * ((t0 >> 6) / kWP2), t0, qstash);
     }
 
     if (grow) issue_row_gates(grow, row0, S, gates_lds);
     Acc2 acc;
     zero_acc2(acc);
     if (row_end - row0 <= kTailRows) mfma_tail_loop3(acc, nw, P, Q, lds, row_end - row0);
-    else mfma_mainloop3(acc, nw, P, Q, lds, row_end - row0);
+    else mfma_mainloop3<!RAGGED>(acc, nw, P, Q, lds, row_end - row0);
     tl.prefetch();
     if (more) aim(nxt);   // here, so that the row-index loads of a gathered tile hide behind the epilogue
 
@@ -506,7 +507,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     Acc2 acc;
     zero_acc2(acc);
     if (row_end - row0 <= kTailRows) mfma_tail_loop3(acc, nw, P, Q, lds, row_end - row0);
-    else mfma_mainloop3(acc, nw, P, Q, lds, row_end - row0);
+    else mfma_mainloop3<!RAGGED>(acc, nw, P, Q, lds, row_end - row0);
     tl.prefetch();
     if constexpr (GATHER)
         if (more) aim(nxt);   // here, so that the row-index loads of the next tile hide behind the epilogue

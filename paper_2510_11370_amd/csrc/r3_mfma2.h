@@ -545,7 +545,6 @@ __device__ __forceinline__ void mfma_mainloop2(Acc2 &acc, int nk, const POp &P, 
 constexpr int kBK3 = 64;
 constexpr int kWinBytes = kTile * kBK3 * 2;   // 32 KB: one operand's window
 constexpr int kSuperBytes = 2 * kWinBytes;    // 64 KB: both operands
-constexpr int kLoadsPerWindow = 16;           // tile loads per loader wave per window (8 per operand)
 
 // K-contiguous 256-row window [256 rows][128 B]: 32 chunks of 1 KB (8 rows x 128 B), eight per
 // loader wave; the 16-byte chunk c of row r sits at slot c ^ ((r >> 1) & 7) (KcFrag16's
@@ -608,10 +607,9 @@ struct OpKC64 {
     // the byte offsets of this lane's eight gathered rows (ROWS)
     __device__ __forceinline__ void set_rows(const int (&v)[8]) {
         if constexpr (STASH) {
-            if ((threadIdx.x >> 6) < kLoaderWaves) {
-                stash[0] = make_int4(v[0], v[1], v[2], v[3]);
-                stash[256] = make_int4(v[4], v[5], v[6], v[7]);
-            }
+            // (waves w and w + 4 have the same rows and write the same: a tile's Q operand is loaded by the one or the other)
+            stash[0] = make_int4(v[0], v[1], v[2], v[3]);
+            stash[256] = make_int4(v[4], v[5], v[6], v[7]);
         } else if constexpr (ROWS) {
 #pragma unroll
             for (int i = 0; i < 8; ++i) voff[i] = v[i];
@@ -697,31 +695,33 @@ __device__ __forceinline__ bf16x8_t win_frag(const Op &op, const char *win, int 
     else return op.frag(win + u * kOperandBytes, t);
 }
 
-// End of a window: a loader's loads (the next window) have all landed, everyone's fragment reads
-// are done, then the waves meet.  Bare s_barrier, as in stage_barrier().
-__device__ __forceinline__ void window_barrier(bool loader) {
-    if (loader) __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0 << 8) | (0 << 14));
-    else __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
+// End of a window: a wave's loads (its share of the next window) have all landed, its fragment reads
+// are done, then the waves meet.  Bare s_barrier, as in stage_barrier().  LOADS: how many may be outstanding.
+template <int LOADS = 0>
+__device__ __forceinline__ void window_barrier() {
+    __builtin_amdgcn_s_waitcnt((LOADS & 15) | (7 << 4) | (0 << 8) | ((LOADS >> 4) << 14));
     __builtin_amdgcn_s_barrier();
 }
 
 // One resident window (four sub-steps, two of each 32-k step).  f carries the last half of the previous
 // window in and this window's last one out, as in stage_compute(); the next window's loads go out
-// into the buffer the previous window has just left, one operand before the first sub-step and
-// the other after it (measured: all sixteen at once makes the loader waves late for the window's
-// barrier; later than this shortens the time the loads have).
+// into the buffer the previous window has just left: the P operand by waves 0-3 before the first sub-step, Q by waves 4-7
+// after it.  The two waves of a SIMD (w and w + 4) so issue at different times, and one multiplies while the other does;
+// with all sixteen loads in waves 0-3 these came late to every barrier (131072 tokens forward 9571 | 9456 us, 65536 Zipf
+// training 14623 | 14456; at ragged widths, SPLIT = false, they were 1 % faster so), with four and four in every wave at once
+// nobody multiplied meanwhile.
 template <class POp, class QOp>
 __device__ __forceinline__ void window_compute(Acc2 &acc, Frags &f, const POp &P, const QOp &Q,
                                                const char *pwin, const char *qwin, int Jnext, uint32_t pnext,
-                                               uint32_t qnext, bool load_next, int qrows) {
-    if (load_next) win_issue(P, Jnext, pnext);
+                                               uint32_t qnext, bool load_p, bool load_q, int qrows) {
+    if (load_p) win_issue(P, Jnext, pnext);
     __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
     for (int u = 0; u < 2; ++u) {
         auto fp = [&](int i) { return win_frag(P, pwin, i, u); };
         auto fq = [&](int j) { return win_frag(Q, qwin, j, u); };
         step_first<POp::kReads, QOp::kReads>(acc, f, fp, fq);
-        if (u == 0 && load_next) win_issue(Q, Jnext, qnext, qrows);
+        if (u == 0 && load_q) win_issue(Q, Jnext, qnext, qrows);
         __builtin_amdgcn_sched_barrier(0);
         step_second<POp::kReads, QOp::kReads>(acc, f, fp, fq);
     }
@@ -733,53 +733,44 @@ __device__ __forceinline__ void window_compute(Acc2 &acc, Frags &f, const POp &P
 // P and Q of a buffer side by side the twin was 64 KB away and had registers of its own: eight
 // more, in kernels that have none to spare).  live_rows as in mfma_mainloop2().  Every wave passes
 // the same barriers whatever its role: one after the first window's loads and one per window.
-template <class POp, class QOp>
+template <bool SPLIT, class POp, class QOp>
 __device__ __forceinline__ void mfma_mainloop3(Acc2 &acc, int nw, const POp &P, const QOp &Q, char *lds,
                                                int live_rows = kTile) {
     if (nw <= 0) return;
     char *const pA = lds, *const pB = lds + kWinBytes, *const qA = lds + 2 * kWinBytes, *const qB = lds + 3 * kWinBytes;
     const uint32_t apA = lds_addr(pA), apB = lds_addr(pB), aqA = lds_addr(qA), aqB = lds_addr(qB);
     const int wave_ = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-    const bool loader = wave_ < kLoaderWaves;
-    // rows of the Q window that some wave reads: whole 64-row blocks (a tail tile's dead rows are
+    const bool pl = wave_ < kLoaderWaves, ql = SPLIT ? !pl : pl;   // loads P, Q
+    // rows of the Q window that some wave reads: whole 64-row blocks (dead rows are
     // not fetched at all: their loads, though out of range, would still take their turn in the
-    // vector memory path, and a tail tile is bound by that path and its latency)
+    // vector memory path); 192 or 256, tiles of fewer rows have the loop below
     const int qrows = min(kTile, (live_rows + kWaveRowsQ - 1) / kWaveRowsQ * kWaveRowsQ);
-    if (loader) {
-        // windows 0 and 1 go out together; only window 0 is waited for: it is in when at most window
-        // 1's loads are outstanding, 16 per loader wave for a full window; a tail tile issues fewer
-        // for Q, so there only window 1's P share (8) may remain
-        if constexpr (POp::kIndexed || QOp::kIndexed) {
-            // an indexed operand's address arithmetic per tile load is long: kept as a real loop, or the
-            // compiler works it all out ahead and spills the results (reloads that wait on the loads)
-#pragma nounroll
-            for (int w = 0; w < 2; ++w)
-                if (w < nw) {
-                    win_issue(P, w, w ? apB : apA);
-                    win_issue(Q, w, w ? aqB : aqA, qrows);
-                }
-        } else {
-            win_issue(P, 0, apA);
-            win_issue(Q, 0, aqA, qrows);
-            if (nw > 1) {
-                win_issue(P, 1, apB);
-                win_issue(Q, 1, aqB, qrows);
-            }
-        }
-        if (nw > 1 && qrows == kTile)
-            __builtin_amdgcn_s_waitcnt((kLoadsPerWindow & 15) | (7 << 4) | (0 << 8) | ((kLoadsPerWindow >> 4) << 14));
-        else if (nw > 1) __builtin_amdgcn_s_waitcnt((kLoadsPerWindow / 2) | (7 << 4) | (0 << 8) | (0 << 14));
-        else __builtin_amdgcn_s_waitcnt(0 | (7 << 4) | (0 << 8) | (0 << 14));
+    // windows 0 and 1 go out together; only window 0 is waited for: it is in when at most window
+    // 1's loads are outstanding
+    if (pl) win_issue(P, 0, apA);
+    if (ql) win_issue(Q, 0, aqA, qrows);
+    if (nw > 1) {
+        if (pl) win_issue(P, 1, apB);
+        if (ql) win_issue(Q, 1, aqB, qrows);
     }
-    __builtin_amdgcn_s_barrier();
+    if (nw == 1) window_barrier<0>();
+    else if (qrows == kTile) window_barrier<SPLIT ? 8 : 16>();
+    else if (SPLIT && pl) window_barrier<8>();
+    else window_barrier<SPLIT ? 6 : 14>();
     if ((wave_ / kWP2) * kWaveRowsQ >= live_rows) {
-        // this wave's rows are not needed: keep the loads (if it is a loader) and the barriers going
+        // this wave's rows are not needed: keep its loads and the barriers going
         for (int J = 0; J < nw; J += 2) {
-            if (loader && J > 0 && J + 1 < nw) { win_issue(P, J + 1, apB); win_issue(Q, J + 1, aqB, qrows); }
-            window_barrier(loader);
+            if (J > 0 && J + 1 < nw) {
+                if (pl) win_issue(P, J + 1, apB);
+                if (ql) win_issue(Q, J + 1, aqB, qrows);
+            }
+            window_barrier();
             if (J + 1 < nw) {
-                if (loader && J + 2 < nw) { win_issue(P, J + 2, apA); win_issue(Q, J + 2, aqA, qrows); }
-                window_barrier(loader);
+                if (J + 2 < nw) {
+                    if (pl) win_issue(P, J + 2, apA);
+                    if (ql) win_issue(Q, J + 2, aqA, qrows);
+                }
+                window_barrier();
             }
         }
         return;
@@ -787,11 +778,12 @@ __device__ __forceinline__ void mfma_mainloop3(Acc2 &acc, int nw, const POp &P, 
     Frags f;
     f.clear();
     for (int J = 0; J < nw; J += 2) {
-        window_compute(acc, f, P, Q, pA, qA, J + 1, apB, aqB, loader && J > 0 && J + 1 < nw, qrows);
-        window_barrier(loader);
+        const bool l0 = J > 0 && J + 1 < nw, l1 = J + 2 < nw;
+        window_compute(acc, f, P, Q, pA, qA, J + 1, apB, aqB, l0 && pl, l0 && ql, qrows);
+        window_barrier();
         if (J + 1 < nw) {
-            window_compute(acc, f, P, Q, pB, qB, J + 2, apA, aqA, loader && J + 2 < nw, qrows);
-            window_barrier(loader);
+            window_compute(acc, f, P, Q, pB, qB, J + 2, apA, aqA, l1 && pl, l1 && ql, qrows);
+            window_barrier();
         }
     }
     step_last(acc, f);
@@ -805,7 +797,7 @@ __device__ __forceinline__ void mfma_mainloop3(Acc2 &acc, int nw, const POp &P, 
 // 1024 or 512 cycles, on every SIMD two waves to cover each other.  The space the dead rows of the Q windows would
 // take holds a third window, so the loads run two windows ahead.
 // `lds` is the work-group's kRowLds bytes: P windows at 0, 32, 64 KB; Q windows (rows 0..127 only, 16 KB
-// each) from 96 KB.  Waves 0-3 load.
+// each) from 96 KB.  Waves 0-3 load (sharing P and Q out as in the loop above was 1 % slower).
 // A loader wave issues 8 loads for P and 2 per 64 rows for Q, so "at most that many outstanding" is "the next
 // window is in" as long as the one after it has been issued.
 // A lane's results: rows wave_row + 16 j + lane % 16, acc[POp::Tail::acc(i)][j] (i: the wave's MFMA tiles along the features).
@@ -816,16 +808,11 @@ constexpr int kTailQBase = 3 * kWinBytes;
 constexpr int kRowLds = kTailQBase + 3 * kTailQBytes;                    // 144 KB (the full tiles' loop uses 128)
 constexpr int kTailP = 4;                                                // MFMA tiles of a wave along the features
 
-template <int LOADS>
-__device__ __forceinline__ void tail_wait() {
-    __builtin_amdgcn_s_waitcnt((LOADS & 15) | (7 << 4) | (0 << 8) | ((LOADS >> 4) << 14));
-}
 __device__ __forceinline__ void tail_barrier(bool loader, bool one_ahead, bool wide) {
-    if (!loader) __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14));
-    else if (!one_ahead) tail_wait<0>();
-    else if (wide) tail_wait<12>();
-    else tail_wait<10>();
-    __builtin_amdgcn_s_barrier();
+    if (!loader) __builtin_amdgcn_s_waitcnt(15 | (7 << 4) | (0 << 8) | (3 << 14)), __builtin_amdgcn_s_barrier();
+    else if (!one_ahead) window_barrier<0>();
+    else if (wide) window_barrier<12>();
+    else window_barrier<10>();
 }
 
 template <class PT, int TQ>
@@ -856,14 +843,8 @@ __device__ __forceinline__ void tail_windows(Acc2 &acc, int nw, const POp &P, co
         win_issue(Q, J, a0 + kTailQBase + slot * kTailQBytes, wide ? kTailRows : kWaveRowsQ);
     };
     if (loader) {
-        if constexpr (POp::kIndexed || QOp::kIndexed) {
-#pragma nounroll
-            for (int w = 0; w < 2; ++w)
-                if (w < nw) issue(w, w);
-        } else {
-            issue(0, 0);
-            if (nw > 1) issue(1, 1);
-        }
+        issue(0, 0);
+        if (nw > 1) issue(1, 1);
     }
     tail_barrier(loader, nw > 1, wide);
     bf16x8_t xa[kTailP], ya[kTailP], xb[TQ], yb[TQ];

@@ -72,4 +72,22 @@ hipError_t f32_wgrads(int d, int E, int F, int T, int K, const int32_t *offsets,
                       const int32_t *dyperm, const float *xrows, const int32_t *xperm, const float *dA, const float *dB,
                       float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s);
 
+
+// The backward between the gate's (which leaves dz, dzrow and dYp = g dy) and dx_finish, for a forward that left H gated, so
+// that nothing but dH reads dYp and dXp may take its place: dH with the parts of dW_r, then dW_gate, dW_up, dW_down, dXp, dW_r,
+// dbias and W_r^T, two launches.
+struct F32Backward {
+    int S, T, d, E, F, K, accumulate;
+    const int32_t *offsets, *perm;
+    const float *dy, *x, *xrows;      // xrows: x with xperm = perm, or the expert-sorted copy with xperm = NULL
+    const int32_t *xperm;
+    const void *idx;
+    int idx_dtype;
+    int64_t stride;
+    const float *dYp, *dz, *dzrow, *H, *FA, *FB, *Wr, *Wg, *Wu, *Wd;
+    float *dA, *dB, *dXp, *part, *dWg, *dWu, *dWd, *dWr, *dbias, *WrT;
+};
+bool f32_backward_supported(int act, int T, int d, int F);
+hipError_t f32_backward(const F32Backward &b, hipStream_t s);
+
 }  // namespace r3

@@ -12,8 +12,10 @@
 #include <type_traits>
 
 #include "r3_f32.h"
+#include "r3_finish.h"
 #include "r3_kernels.h"
 #include "r3_mfma2.h"
+#include "r3_plain_tiles.h"
 
 namespace r3 {
 namespace {
@@ -170,19 +172,31 @@ __device__ __forceinline__ void f32_zero(F32Acc<C> &acc) {
 // ---------------------------------------------------------------------------
 // Row-tiled contractions over the expert-sorted rows (the operands of plain_rows_kernel).
 // ---------------------------------------------------------------------------
+struct F32RowArgs {
+    int d, E, F;
+    const int32_t *offsets;
+    const float *in0, *in1;
+    int T;
+    const int32_t *perm;
+    int K;
+    const float *gates, *W0, *W1, *FA, *FB;
+    float *out0, *out1, *out2;
+};
+
+// one tile; `block` of f32_rows_grid()
 template <class C, int MODE>
-__global__ void __launch_bounds__(C::NT)
-f32_rows_kernel(int d, int E, int F, const int32_t *__restrict__ offsets, const float *__restrict__ in0,
-                const float *__restrict__ in1, int T, const int32_t *__restrict__ perm, int K, const float *__restrict__ gates,
-                const float *__restrict__ W0, const float *__restrict__ W1, const float *__restrict__ FAin,
-                const float *__restrict__ FBin, float *__restrict__ out0, float *__restrict__ out1, float *__restrict__ out2) {
-    __shared__ __attribute__((aligned(1024))) char lds[C::NST * C::STAGE];
+__device__ __forceinline__ void f32_rows_tile(const F32RowArgs &g, int block, char *lds) {
+    const int d = g.d, E = g.E, F = g.F, T = g.T, K = g.K;
+    const int32_t *__restrict__ offsets = g.offsets, *__restrict__ perm = g.perm;
+    const float *__restrict__ in0 = g.in0, *__restrict__ in1 = g.in1, *__restrict__ gates = g.gates, *__restrict__ W0 = g.W0,
+                *__restrict__ W1 = g.W1, *__restrict__ FAin = g.FA, *__restrict__ FBin = g.FB;
+    float *__restrict__ out0 = g.out0, *__restrict__ out1 = g.out1, *__restrict__ out2 = g.out2;
     static_assert(MODE != PLAIN_FFN1 || C::TP == 2, "one tile of each weight");
     constexpr int BF = MODE == PLAIN_FFN1 ? C::BP / 2 : C::BP;            // output features per tile
     const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d;
     const int KK = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? d : F;      // width of the row operand
     const int npt = (NOUT + BF - 1) / BF;
-    const RowTile t = find_row_tile<true>(offsets, E, C::BQ, blockIdx.x, npt);
+    const RowTile t = find_row_tile<true>(offsets, E, C::BQ, block, npt);
     if (t.e < 0) return;
     const int p0 = t.col * BF, rows = t.row1 - t.row0;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wp = wave & 1, wq = wave >> 1;
@@ -326,14 +340,13 @@ struct F32Wgrad3 {
 };
 
 template <class C>
-__global__ void __launch_bounds__(C::NT)
-f32_wgrad_kernel(int E, int T, int K, const int32_t *__restrict__ offsets, F32Wgrad3 all, int accumulate) {
-    __shared__ __attribute__((aligned(1024))) char lds[C::NST * C::STAGE];
+__device__ __forceinline__ void f32_wgrad_tile(int E, int T, int K, const int32_t *__restrict__ offsets, const F32Wgrad3 &all,
+                                               int accumulate, int block, char *lds) {
     const int per = all.g[0].tiles + all.g[1].tiles + all.g[2].tiles;
-    const int e = blockIdx.x / per;
-    int rem = blockIdx.x - e * per, which = 0;
-    while (rem >= all.g[which].tiles) rem -= all.g[which++].tiles;
-    const F32Wgrad g = all.g[which];
+    const int e = block / per, t0 = all.g[0].tiles, t1 = t0 + all.g[1].tiles;
+    int rem = block - e * per;
+    const F32Wgrad g = rem < t0 ? all.g[0] : rem < t1 ? all.g[1] : all.g[2];
+    rem -= rem < t0 ? 0 : rem < t1 ? t0 : t1;
     const int npt = (g.NP + C::BP - 1) / C::BP;
     const int qt = rem / npt, q0 = qt * C::BQ, p0 = (rem - qt * npt) * C::BP;
     const int r0 = offsets[e], n = offsets[e + 1] - r0;
@@ -369,6 +382,49 @@ f32_wgrad_kernel(int E, int T, int K, const int32_t *__restrict__ offsets, F32Wg
     }
 }
 
+// ---------------------------------------------------------------------------
+// Launches.  What does not wait for each other shares one: a layer of few tokens is a chain of launches, and a larger one
+// fills one kernel's last round of tiles with the next one's.  After the gate's backward:  dH and the parts of dW_r;  then all
+// weight gradients, dXp, and the router's last step.  T=256 d=128 E=8 K=2 F=256, forward + backward: 58 -> 52 us in four launches of the
+// backward instead of seven; T=2048 d=512 E=16 K=4 F=1024: 815 -> 767.
+// ---------------------------------------------------------------------------
+template <class C, int MODE>
+__global__ void __launch_bounds__(C::NT) f32_rows_kernel(F32RowArgs a) {
+    __shared__ __attribute__((aligned(1024))) char lds[C::NST * C::STAGE];
+    f32_rows_tile<C, MODE>(a, blockIdx.x, lds);
+}
+
+template <class C>
+__global__ void __launch_bounds__(C::NT)
+f32_wgrad_kernel(int E, int T, int K, const int32_t *__restrict__ offsets, F32Wgrad3 all, int accumulate) {
+    __shared__ __attribute__((aligned(1024))) char lds[C::NST * C::STAGE];
+    f32_wgrad_tile<C>(E, T, K, offsets, all, accumulate, blockIdx.x, lds);
+}
+
+constexpr int max_int(int a, int b) { return a > b ? a : b; }
+
+// the first `first` blocks (a multiple of 8, so that the rows' tiles keep their XCDs): parts of dW_r; then dH
+template <class C, typename IdxT>
+__global__ void __launch_bounds__(C::NT) f32_dh_dwr_kernel(F32RowArgs a, PlainDwr<float, IdxT> w, int nw, int first) {
+    __shared__ __attribute__((aligned(1024))) char lds[max_int(C::NST * C::STAGE, PlainSmall::LDS)];
+    const int b = blockIdx.x;
+    if (b >= first) f32_rows_tile<C, PLAIN_DH>(a, b - first, lds);
+    else if (b < nw) plain_dwr_tile<PlainSmall, float, true>(w, b, lds);
+}
+
+// [0, first): the router's last step (its dbias of a hot expert is a long chain); [first, second): dXp; then the weight gradients
+template <class CR, class CW>
+__global__ void __launch_bounds__(CR::NT)
+f32_grads_kernel(F32RowArgs a, int E, int T, int K, const int32_t *__restrict__ offsets, F32Wgrad3 all, int accumulate,
+                 RouterFinish<float> fin, int nfin, int first, int second) {
+    __shared__ __attribute__((aligned(1024))) char lds[max_int(CR::NST * CR::STAGE, CW::NST * CW::STAGE)];
+    static_assert(sizeof(RouterFinishLds<float>) <= sizeof(lds), "");
+    const int b = blockIdx.x;
+    if (b >= second) f32_wgrad_tile<CW>(E, T, K, offsets, all, accumulate, b - second, lds);
+    else if (b >= first) f32_rows_tile<CR, PLAIN_DXP>(a, b - first, lds);
+    else if (b < nfin) router_finish_block<CR::NT>(fin, b, *(RouterFinishLds<float> *)lds);
+}
+
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // Tiles of 64 x 64 or of 32 x 32 outputs.  Row-tiled kernels: 32 x 32 below 512 tiles of the larger kind, and where an expert has
 // fewer than 64 rows on average.  us, 64 x 64 | 32 x 32: dXp of 256 x 2 rows, 128 features out of 256 x 2 (16 tiles) 16.3 | 10.5;
@@ -380,30 +436,54 @@ constexpr int kRowsFill = 512;
 constexpr int kWgradFill = 256;
 
 template <class C, int MODE>
-void rows_launch(int S, int d, int E, int F, const int32_t *offsets, const float *in0, const float *in1, int T,
-                 const int32_t *perm, int K, const float *gates, const float *W0, const float *W1, const float *FA,
-                 const float *FB, float *o0, float *o1, float *o2, hipStream_t s) {
-    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d, BF = MODE == PLAIN_FFN1 ? C::BP / 2 : C::BP;
-    f32_rows_kernel<C, MODE><<<(unsigned)f32_rows_grid(S, E, C::BQ, ceil_div(NOUT, BF)), C::NT, 0, s>>>(
-        d, E, F, offsets, in0, in1, T, perm, K, gates, W0, W1, FA, FB, o0, o1, o2);
+int rows_blocks(int S, const F32RowArgs &a) {
+    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? a.F : a.d, BF = MODE == PLAIN_FFN1 ? C::BP / 2 : C::BP;
+    return (int)f32_rows_grid(S, a.E, C::BQ, ceil_div(NOUT, BF));
+}
+template <class C, int MODE>
+void rows_launch(int S, const F32RowArgs &a, hipStream_t s) {
+    f32_rows_kernel<C, MODE><<<rows_blocks<C, MODE>(S, a), C::NT, 0, s>>>(a);
 }
 
+bool few_row_tiles(int S, int E, int NOUT, int width) {
+    return ceil_div(S, 64) * ceil_div(NOUT, width) < kRowsFill || S < 64 * (int64_t)E;
+}
 template <int MODE>
-void rows_by_size(int S, int d, int E, int F, const int32_t *offsets, const float *in0, const float *in1, int T,
-                  const int32_t *perm, int K, const float *gates, const float *W0, const float *W1, const float *FA,
-                  const float *FB, float *o0, float *o1, float *o2, hipStream_t s) {
-    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d;
+void rows_by_size(int S, const F32RowArgs &a, hipStream_t s) {
+    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? a.F : a.d;
     typedef typename std::conditional<MODE == PLAIN_FFN1, F32Short1, F32Short>::type Short;
-    const bool few = ceil_div(S, 64) * ceil_div(NOUT, MODE == PLAIN_FFN1 ? 32 : 64) < kRowsFill || S < 64 * (int64_t)E;
-    auto f = few ? rows_launch<Short, MODE> : rows_launch<F32Tile, MODE>;
-    f(S, d, E, F, offsets, in0, in1, T, perm, K, gates, W0, W1, FA, FB, o0, o1, o2, s);
+    auto f = few_row_tiles(S, a.E, NOUT, MODE == PLAIN_FFN1 ? 32 : 64) ? rows_launch<Short, MODE> : rows_launch<F32Tile, MODE>;
+    f(S, a, s);
 }
 
+bool few_wgrad_tiles(int E, int d, int F) { return 3 * (int64_t)E * ceil_div(d, 64) * ceil_div(F, 64) < kWgradFill; }
 template <class C>
-void wgrad_launch(int E, int T, int K, const int32_t *offsets, F32Wgrad3 all, int accumulate, hipStream_t s) {
+int wgrad_blocks(int E, F32Wgrad3 &all) {
     int per = 0;
     for (auto &g : all.g) per += g.tiles = (int)(ceil_div(g.NQ, C::BQ) * ceil_div(g.NP, C::BP));
-    f32_wgrad_kernel<C><<<(unsigned)((int64_t)E * per), C::NT, 0, s>>>(E, T, K, offsets, all, accumulate);
+    return (int)((int64_t)E * per);
+}
+template <class C>
+void wgrad_launch(int E, int T, int K, const int32_t *offsets, F32Wgrad3 all, int accumulate, hipStream_t s) {
+    const int n = wgrad_blocks<C>(E, all);
+    f32_wgrad_kernel<C><<<n, C::NT, 0, s>>>(E, T, K, offsets, all, accumulate);
+}
+F32Wgrad3 wgrad_args(int d, int F, const float *H, const float *dYrows, const int32_t *dyperm, const float *xrows, const int32_t *xperm,
+                     const float *dA, const float *dB, float *dWg, float *dWu, float *dWd) {
+    return {{{H, dYrows, nullptr, dyperm, dWd, F, d, 0}, {xrows, dA, xperm, nullptr, dWg, d, F, 0}, {xrows, dB, xperm, nullptr, dWu, d, F, 0}}};
+}
+
+template <class C, typename IdxT>
+void dh_dwr_launch(int S, const F32RowArgs &a, const PlainDwr<float, IdxT> &w, hipStream_t s) {
+    const int nw = (int)plain_dwr_blocks(w.Tn, w.d, w.E), first = (nw + 7) / 8 * 8;
+    f32_dh_dwr_kernel<C, IdxT><<<first + rows_blocks<C, PLAIN_DH>(S, a), C::NT, 0, s>>>(a, w, nw, first);
+}
+template <class CR, class CW>
+void grads_launch(int S, const F32RowArgs &a, int T, int K, const int32_t *offsets, F32Wgrad3 all, int accumulate,
+                  const RouterFinish<float> &fin, int nfin, hipStream_t s) {
+    const int first = (nfin + 7) / 8 * 8, second = first + rows_blocks<CR, PLAIN_DXP>(S, a);
+    f32_grads_kernel<CR, CW><<<second + wgrad_blocks<CW>(a.E, all), CR::NT, 0, s>>>(a, a.E, T, K, offsets, all, accumulate, fin, nfin, first,
+                                                                                  second);
 }
 
 }  // namespace
@@ -413,19 +493,47 @@ hipError_t f32_rows(int mode, int S, int d, int E, int F, const int32_t *offsets
                     const float *FB, float *o0, float *o1, float *o2, hipStream_t s) {
     auto f = mode == PLAIN_FFN1 ? rows_by_size<PLAIN_FFN1> : mode == PLAIN_DOWN ? rows_by_size<PLAIN_DOWN>
            : mode == PLAIN_DH ? rows_by_size<PLAIN_DH> : rows_by_size<PLAIN_DXP>;
-    f(S, d, E, F, offsets, in0, in1, T, perm, K, gates, W0, W1, FA, FB, o0, o1, o2, s);
+    f(S, F32RowArgs{d, E, F, offsets, in0, in1, T, perm, K, gates, W0, W1, FA, FB, o0, o1, o2}, s);
     return hipGetLastError();
 }
 
 hipError_t f32_wgrads(int d, int E, int F, int T, int K, const int32_t *offsets, const float *H, const float *dYrows,
                       const int32_t *dyperm, const float *xrows, const int32_t *xperm, const float *dA, const float *dB,
                       float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s) {
-    const F32Wgrad3 all = {{{H, dYrows, nullptr, dyperm, dWd, F, d, 0},
-                            {xrows, dA, xperm, nullptr, dWg, d, F, 0},
-                            {xrows, dB, xperm, nullptr, dWu, d, F, 0}}};
-    const bool few = 3 * (int64_t)E * ceil_div(d, 64) * ceil_div(F, 64) < kWgradFill;
-    auto f = few ? wgrad_launch<F32Short> : wgrad_launch<F32Tile>;
-    f(E, T, K, offsets, all, accumulate, s);
+    auto f = few_wgrad_tiles(E, d, F) ? wgrad_launch<F32Short> : wgrad_launch<F32Tile>;
+    f(E, T, K, offsets, wgrad_args(d, F, H, dYrows, dyperm, xrows, xperm, dA, dB, dWg, dWu, dWd), accumulate, s);
+    return hipGetLastError();
+}
+
+bool f32_backward_supported(int act, int T, int d, int F) {
+    return act == R3_F32 && d % 4 == 0 && F % 4 == 0 && (int64_t)T * d * 4 < (1ll << 31) - 16;
+}
+
+hipError_t f32_backward(const F32Backward &b, hipStream_t s) {
+    {
+        ProfScope ps(PROF_DH, s);
+        const F32RowArgs a = {b.d, b.E, b.F, b.offsets, b.dYp, nullptr, 0, nullptr, 1, nullptr, b.Wd, nullptr, b.FA, b.FB, b.dA, b.dB, nullptr};
+        const bool few = few_row_tiles(b.S, b.E, b.F, 64);
+        auto go = [&](auto idx) {
+            typedef typename std::remove_const<typename std::remove_pointer<decltype(idx)>::type>::type IdxT;
+            const PlainDwr<float, IdxT> w = {b.T, b.d, b.E, b.K, plain_dwr_rows(b.T, b.d, b.E), b.x, b.dz, idx, b.stride, b.part};
+            (few ? dh_dwr_launch<F32Short, IdxT> : dh_dwr_launch<F32Tile, IdxT>)(b.S, a, w, s);
+        };
+        if (b.idx_dtype == R3_IDX_U8) go((const uint8_t *)b.idx);
+        else go((const uint16_t *)b.idx);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    ProfScope ps(PROF_WGRAD, s);
+    const F32RowArgs a = {b.d, b.E, b.F, b.offsets, b.dA, b.dB, 0, nullptr, 1, nullptr, b.Wg, b.Wu, nullptr, nullptr, b.dXp, nullptr, nullptr};
+    const F32Wgrad3 all = wgrad_args(b.d, b.F, b.H, b.dy, b.perm, b.xrows, b.xperm, b.dA, b.dB, b.dWg, b.dWu, b.dWd);
+    RouterFinish<float> fin;
+    const int rows = plain_dwr_rows(b.T, b.d, b.E);
+    const int nfin = fin.fill<F32Tile::NT>(b.d, b.E, (b.T + rows - 1) / rows, b.accumulate, b.dzrow, b.part, b.offsets, b.dbias, b.dWr, b.Wr, b.WrT);
+    const bool fr = few_row_tiles(b.S, b.E, b.d, 64), fw = few_wgrad_tiles(b.E, b.d, b.F);
+    auto f = fr ? (fw ? grads_launch<F32Short, F32Short> : grads_launch<F32Short, F32Tile>)
+                : (fw ? grads_launch<F32Tile, F32Short> : grads_launch<F32Tile, F32Tile>);
+    f(b.S, a, b.T, b.K, b.offsets, all, b.accumulate, fin, nfin, s);
     return hipGetLastError();
 }
 

@@ -90,6 +90,7 @@ hipError_t plain_wgrads(int d, int E, int F, int T, int K, int act, const int32_
                         const int32_t *dyperm, const void *xrows, const int32_t *xperm, const void *dA, const void *dB,
                         float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s);
 int plain_dwr_rows(int T, int d, int E);          // tokens per part
+unsigned plain_dwr_blocks(int T, int d, int E);   // work-groups of 256
 void plain_dwr_parts(int T, int d, int E, int K, int act, const void *x, const float *dz, const void *idx, int idx_dtype,
                      int64_t stride, float *part, hipStream_t s);
 

@@ -9,6 +9,7 @@
 // token's logits were other bits in a micro-batch than in the whole batch.
 #include <algorithm>
 
+#include "r3_finish.h"
 #include "r3_kernels.h"
 #include "r3_mfma.h"
 #include "r3_mfma2.h"
@@ -575,60 +576,10 @@ router_dwr_kernel(int T, int d, int E, int K, int rows, const bf16_t *__restrict
 // Each is microseconds of latency, so launches of their own cost a layer of few tokens more than the work did.
 // Forward + backward, three launches vs one: f32 T=256 d=128 E=8 79.8 -> 78.0 us, bf16 T=3001 d=1000 E=64 612 -> 609,
 // T=6000 d=1024 E=384 with dbias 1083 -> 1074, T=1001 d=2048 E=128 1121 -> 1118.
-template <typename T> struct RouterFinish {
-    int d, E, nsplit, accumulate, bias_blocks, sum_blocks;
-    const float *dzrow, *part;
-    const int32_t *offsets;
-    float *dbias, *dWr;
-    const T *Wr;
-    T *WrT;
-};
-
 template <typename T>
 __global__ void __launch_bounds__(1024) router_finish_kernel(RouterFinish<T> a) {
-    __shared__ float tmp[16];
-    __shared__ T tile[32][33];
-    const int tid = threadIdx.x, E = a.E;
-    int blk = blockIdx.x;
-    if (blk < a.bias_blocks) {
-        const int e = blk, r1 = a.offsets[e + 1];
-        float acc = 0.0f;
-        for (int r = a.offsets[e] + tid; r < r1; r += 4 * 1024) {
-            float v[4];
-#pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = r + u * 1024 < r1 ? a.dzrow[r + u * 1024] : 0.0f;
-            acc += (v[0] + v[1]) + (v[2] + v[3]);
-        }
-        acc = wave_sum(acc);
-        if (lane_id() == 0) tmp[tid >> 6] = acc;
-        __syncthreads();
-        if (tid == 0) {
-            acc = a.accumulate ? a.dbias[e] : 0.0f;
-            for (int i = 0; i < 16; ++i) acc += tmp[i];
-            a.dbias[e] = acc;
-        }
-        return;
-    }
-    blk -= a.bias_blocks;
-    if (blk < a.sum_blocks) {
-        const int64_t n = (int64_t)a.d * E, i = (int64_t)blk * 1024 + tid;
-        if (i >= n) return;
-        float acc = a.accumulate ? a.dWr[i] : 0.0f;
-        for (int s = 0; s < a.nsplit; s += 8) {
-            float v[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) v[u] = s + u < a.nsplit ? a.part[(int64_t)(s + u) * n + i] : 0.0f;
-#pragma unroll
-            for (int u = 0; u < 8; ++u) acc += v[u];
-        }
-        a.dWr[i] = acc;
-        return;
-    }
-    blk -= a.sum_blocks;
-    const int ne = (E + 31) / 32, e0 = blk % ne * 32, c0 = blk / ne * 32, lo = tid & 31, hi = tid >> 5;
-    if (c0 + hi < a.d && e0 + lo < E) tile[hi][lo] = a.Wr[(int64_t)(c0 + hi) * E + e0 + lo];
-    __syncthreads();
-    if (e0 + hi < E && c0 + lo < a.d) a.WrT[(int64_t)(e0 + hi) * a.d + c0 + lo] = tile[lo][hi];
+    __shared__ RouterFinishLds<T> lds;
+    router_finish_block<1024>(a, blockIdx.x, lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -724,15 +675,6 @@ static void launch_dwr(int T, int d, int E, int K, const void *x, const float *d
     k<<<grid, 256, kDwrLds, s>>>(T, d, E, K, rows, (const bf16_t *)x, dz, (const IdxT *)idx, stride, part);
 }
 
-template <typename T>
-static hipError_t launch_finish(RouterFinish<T> a, const void *Wr, void *WrT, hipStream_t s) {
-    a.Wr = (const T *)Wr;
-    a.WrT = (T *)WrT;
-    const int64_t tr = (int64_t)((a.d + 31) / 32) * ((a.E + 31) / 32);
-    router_finish_kernel<T><<<(unsigned)(a.bias_blocks + a.sum_blocks + tr), 1024, 0, s>>>(a);
-    return hipGetLastError();
-}
-
 hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, const void *Wr, const float *dz, const void *idx,
                            int idx_dtype, int64_t stride, const int32_t *offsets, const float *dzrow, float *part, float *dWr,
                            float *dbias, void *WrT, int accumulate, bool plain_only, hipStream_t s) {
@@ -742,14 +684,9 @@ hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, c
     if (bf) (idx_dtype == R3_IDX_U8 ? launch_dwr<uint8_t> : launch_dwr<uint16_t>)(T, d, E, K, x, dz, idx, stride, part, s);
     else plain_dwr_parts(T, d, E, K, act, x, dz, idx, idx_dtype, stride, part, s);
     auto finish = [&](auto f) {
-        f.d = d; f.E = E;
-        f.nsplit = (T + rows - 1) / rows;
-        f.accumulate = accumulate;
-        f.bias_blocks = dbias ? E : 0;
-        f.sum_blocks = (int)(((int64_t)d * E + 1023) / 1024);
-        f.dzrow = dzrow; f.part = part; f.offsets = offsets;
-        f.dbias = dbias; f.dWr = dWr;
-        return launch_finish(f, Wr, WrT, s);
+        const int blocks = f.template fill<1024>(d, E, (T + rows - 1) / rows, accumulate, dzrow, part, offsets, dbias, dWr, Wr, WrT);
+        router_finish_kernel<<<blocks, 1024, 0, s>>>(f);
+        return hipGetLastError();
     };
     return act == R3_BF16 ? finish(RouterFinish<bf16_t>{}) : finish(RouterFinish<float>{});
 }

@@ -255,7 +255,7 @@ __global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
 ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *__restrict__ perm, int K, int T,
             const int32_t *__restrict__ offsets, const int32_t *__restrict__ tiles, const bf16_t *__restrict__ Wg,
             const bf16_t *__restrict__ Wu, bf16_t *__restrict__ H, bf16_t *__restrict__ FA, bf16_t *__restrict__ FB,
-            const float *__restrict__ grow) {
+            const float *__restrict__ grow, int stream) {
     __shared__ __attribute__((aligned(1024))) char lds[kRowLds];   // one piece: a tail tile lays it out differently
     char *const bufA = lds, *const bufB = lds + kSuperBytes;
     char *const s0 = bufA, *const s1 = bufA + kStageBytes, *const s2 = bufB, *const s3 = bufB + kStageBytes;
@@ -370,10 +370,10 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
                 }
             }
             const int whole = tail ? 64 : 128, width = RAGGED ? min(whole, (F - fw) * 2) : whole;
-            sh.flush((char *)H + o, (int64_t)F * 2, valid, width);
+            sh.flush((char *)H + o, (int64_t)F * 2, valid, width, stream);
             if (save) {
-                sa.flush((char *)FA + o, (int64_t)F * 2, valid, width);
-                sb.flush((char *)FB + o, (int64_t)F * 2, valid, width);
+                sa.flush((char *)FA + o, (int64_t)F * 2, valid, width, stream);
+                sb.flush((char *)FB + o, (int64_t)F * 2, valid, width, stream);
             }
         }
     };
@@ -411,7 +411,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
                const bf16_t *__restrict__ W0, const bf16_t *__restrict__ W1, const bf16_t *__restrict__ FA,
                const bf16_t *__restrict__ FB, bf16_t *__restrict__ out0, bf16_t *__restrict__ out1,
                const int32_t *__restrict__ tok, int T, const float *__restrict__ grow,
-               const bf16_t *__restrict__ Hs, bf16_t *__restrict__ out2, float *__restrict__ wpart) {
+               const bf16_t *__restrict__ Hs, bf16_t *__restrict__ out2, float *__restrict__ wpart, int stream) {
     __shared__ __attribute__((aligned(1024))) char lds[kRowLds];   // one piece: a tail tile lays it out differently
     char *const bufA = lds, *const bufB = lds + kSuperBytes;
     char *const s0 = bufA, *const s1 = bufA + kStageBytes, *const s2 = bufB, *const s3 = bufB + kStageBytes;
@@ -589,7 +589,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
                         if (!(GATED && which == 2)) sp.put8(q, bo, pack4(o[0], o[1], o[2], o[3]));
                     }
                 bf16_t *dst = which == 0 ? out0 : which == 1 ? out1 : out2;
-                if (!(GATED && which == 2)) sp.flush((char *)dst + oh, (int64_t)NOUT * 2, valid, width - 128 * half);
+                if (!(GATED && which == 2)) sp.flush((char *)dst + oh, (int64_t)NOUT * 2, valid, width - 128 * half, stream);
                 if (which == 2 && (half == 1 || tail)) {
                     // the four lanes that hold a row add up; lanes 0..15 write the first 16 rows, 16..31 the others
                     float w[2];
@@ -700,6 +700,7 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
     // part 0 of an expert's rows goes to the gradient, a later part to its own slot of partial products
     char *o = (char *)(pslot < 0 ? out + (int64_t)e * NQd * NPd : part + (int64_t)pslot * NQd * NPd);
     const int add = pslot < 0 ? accumulate : 0;
+    const bool stream = pslot < 0 && (!RAGGED || NPd % 32 == 0);   // (partial products are read again at once)
 #pragma unroll
     for (int blk = 0; blk < kWaveRowsQ / 32; ++blk)
 #pragma unroll
@@ -713,9 +714,9 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
                 }
             const int64_t off = ((int64_t)(q0 + wq * kWaveRowsQ + blk * 32) * NPd + p0 + wp * 128 + half * 64) * 4;
             if constexpr (RAGGED)
-                st.flush_f32(o + off, (int64_t)NPd * 4, NQd - (q0 + wq * kWaveRowsQ + blk * 32), add,
+                st.flush_f32(o + off, (int64_t)NPd * 4, NQd - (q0 + wq * kWaveRowsQ + blk * 32), add, stream,
                              (NPd - p0 - wp * 128 - half * 64) * 4);
-            else st.flush_f32(o + off, (int64_t)NPd * 4, 32, add);
+            else st.flush_f32(o + off, (int64_t)NPd * 4, 32, add, stream);
         }
     } else {
         tl.prefetch();
@@ -784,6 +785,7 @@ wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t
     mfma_mainloop2(acc, (r1 - r0 + kBK2 - 1) / kBK2, P, Q, s0, s1, s2, s3);
     tl.prefetch();
 
+    const bool stream = pslot < 0 && (!RAGGED || NPd % 32 == 0);   // (partial products are read again at once)
     // per wave: 64 rows (q) x 64 features (p) of each product, 32-row blocks through LDS
     const int tid = opaque_tid();
     const int lane = tid & 63, wq = (tid >> 6) / kWP2, wp = (tid >> 6) % kWP2;
@@ -804,9 +806,9 @@ wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t
                                          : (half ? part1 : part0) + (int64_t)pslot * NQd * NPd);
             const int64_t off = ((int64_t)(q0 + wq * kWaveRowsQ + blk * 32) * NPd + p0 + wp * 64) * 4;
             if constexpr (RAGGED)
-                st.flush_f32(o + off, (int64_t)NPd * 4, NQd - (q0 + wq * kWaveRowsQ + blk * 32), pslot < 0 ? accumulate : 0,
+                st.flush_f32(o + off, (int64_t)NPd * 4, NQd - (q0 + wq * kWaveRowsQ + blk * 32), pslot < 0 ? accumulate : 0, stream,
                              (NPd - p0 - wp * 64) * 4);
-            else st.flush_f32(o + off, (int64_t)NPd * 4, 32, pslot < 0 ? accumulate : 0);
+            else st.flush_f32(o + off, (int64_t)NPd * 4, 32, pslot < 0 ? accumulate : 0, stream);
         }
     } else {
         tl.prefetch();
@@ -923,6 +925,16 @@ hipError_t mfma_build_tiles_and_row_tokens(int E, const int32_t *offsets, int32_
 
 static int64_t tiles_of(int64_t n, int tile) { return (n + tile - 1) / tile; }
 
+// Whether what the forward saves and what dH leaves go out with the non-temporal hint.  As a rule they do (see RowStage).  Where
+// an expert has few rows, a backward is bound by writing the weight gradients, and reading its rows from memory through
+// that queue is slow: they are left in the caches then, if they fit.  Training, us, streamed | left: 1001 tokens of the
+// 2048 x 768 x 128-expert layer, 63 rows per expert, dW_gate/dW_up 318 | 304, 2000 tokens 328 | 308, 4000 393 | 385 (SwiGLU and dH
+// together 446 | 451), 8000 531 | 534; 6000 tokens of 1024 x 512 x 384, 62 rows, dW_down 217 | 156, dW_gate/dW_up 335 | 318; 3001
+// tokens of 1000 x 704 x 64, 281 rows, SwiGLU 118 | 124.
+static int stream_rows(int64_t S, int E, int F) {
+    return !(S < 192 * (int64_t)E && S * F * 2 <= (64ll << 20));
+}
+
 template <bool GATHER, bool RAGGED>
 static void launch_ffn1(int64_t S, int d, int E, int F, const void *Xp, const int32_t *perm, int K, int T,
                         const int32_t *offsets, const int32_t *tiles, const void *Wg, const void *Wu, void *H, void *FA,
@@ -930,7 +942,7 @@ static void launch_ffn1(int64_t S, int d, int E, int F, const void *Xp, const in
     const int64_t n = max_row_tiles(S, E, kTile) * tiles_of(F, 128);
     ffn1_kernel<GATHER, RAGGED><<<persistent_grid(n), kThreads2, 0, s>>>(
         (int)S, d, F, (const bf16_t *)Xp, perm, K, T, offsets, tiles, (const bf16_t *)Wg, (const bf16_t *)Wu, (bf16_t *)H,
-        (bf16_t *)FA, (bf16_t *)FB, grow);
+        (bf16_t *)FA, (bf16_t *)FB, grow, FA ? stream_rows(S, E, F) : 1);
 }
 
 template <int MODE, bool GATED, bool RAGGED>
@@ -942,7 +954,7 @@ static void launch_rowgemm(int64_t S, int d, int E, int F, const void *Q0, const
     rowgemm_kernel<MODE, GATED, RAGGED><<<persistent_grid(n), kThreads2, 0, s>>>(
         (int)S, d, F, (const bf16_t *)Q0, (const bf16_t *)Q1, offsets, tiles, (const bf16_t *)W0, (const bf16_t *)W1,
         (const bf16_t *)FA, (const bf16_t *)FB, (bf16_t *)out0, (bf16_t *)out1, tok, T, grow, (const bf16_t *)H, (bf16_t *)Hg,
-        wpart);
+        wpart, stream_rows(S, E, F));
 }
 
 hipError_t mfma_ffn_forward(int64_t S, int d, int E, int F, const void *Xp, const int32_t *perm, int K, int T,

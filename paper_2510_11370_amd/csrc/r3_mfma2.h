@@ -1058,24 +1058,34 @@ struct RowStage {
     __device__ __forceinline__ void put16(int q, int byte_off, float4 v) const { *(float4 *)(base + q * PITCH + byte_off) = v; }
     __device__ __forceinline__ uint2 get8(int q, int byte_off) const { return *(const uint2 *)(base + q * PITCH + byte_off); }
     // rows [0, valid) of the patch -> out (byte pointer at row 0), row pitch ld_bytes; only the first `width`
-    // bytes of a row (a multiple of 16; may be <= 0 or past the row's end)
-    __device__ __forceinline__ void flush(char *out, int64_t ld_bytes, int valid, int width = ROWB) const {
+    // bytes of a row (a multiple of 16; may be <= 0 or past the row's end).  stream: non-temporal, as these
+    // rows are not read again by this kernel and should not displace its operand tiles (1-3 % on the row-tiled GEMMs)
+    template <bool STREAM>
+    __device__ __forceinline__ void flush_as(char *out, int64_t ld_bytes, int valid, int width) const {
         const int lane = tid & 63, r = lane / LPR, c = lane % LPR;
 #pragma unroll
         for (int i = 0; i < 32 / RPI; ++i) {
             const int row = i * RPI + r;
             const uint4 v = *(const uint4 *)(base + row * PITCH + c * 16);
             if (row < valid && c * 16 < width) {
-                // non-temporal: the output is not read again by this kernel and should not displace
-                // operand tiles in L2 (measured: 1-3 % on the row-tiled GEMMs, at the price of 3 % on
-                // the much shorter kernels that read these rows next)
                 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-                __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), (u32x4 *)(out + row * ld_bytes + c * 16));
+                u32x4 *dst = (u32x4 *)(out + row * ld_bytes + c * 16);
+                if constexpr (STREAM) __builtin_nontemporal_store(__builtin_bit_cast(u32x4, v), dst);
+                else *dst = __builtin_bit_cast(u32x4, v);
             }
         }
+        // (the two forms end differently, so that they are not merged into one without the hint)
+        if constexpr (STREAM) asm volatile("" ::: "memory");
     }
-    // same for f32 rows, adding what is already in memory (accumulate != 0)
-    __device__ __forceinline__ void flush_f32(char *out, int64_t ld_bytes, int valid, int accumulate, int width = ROWB) const {
+    __device__ __forceinline__ void flush(char *out, int64_t ld_bytes, int valid, int width, bool stream = true) const {
+        if (stream) flush_as<true>(out, ld_bytes, valid, width);
+        else flush_as<false>(out, ld_bytes, valid, width);
+    }
+    // same for f32 rows, adding what is already in memory (accumulate != 0).  stream: non-temporal.  The weight gradients are the
+    // largest outputs of a pass; left in the caches they are written back while the next kernel (dXp) wants its weights: 1001 tokens
+    // of the 2048 x 768 x 128-expert layer dXp 211 -> 157 us, 6000 tokens of 1024 x 512 x 384 141 -> 103, 16384 tokens 801 -> 770.
+    // Only where rows are whole 128-byte lines: pieces of lines are slow to stream (rows of 4000 bytes: this kernel 61 -> 90 us).
+    __device__ __forceinline__ void flush_f32(char *out, int64_t ld_bytes, int valid, int accumulate, bool stream, int width = ROWB) const {
         const int lane = tid & 63, r = lane / LPR, c = lane % LPR;
 #pragma unroll 2
         for (int i = 0; i < 32 / RPI; ++i) {
@@ -1087,7 +1097,9 @@ struct RowStage {
                     const float4 old = *dst;
                     v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
                 }
-                *dst = v;
+                typedef float f32x4 __attribute__((ext_vector_type(4)));
+                if (stream) __builtin_nontemporal_store(f32x4{v.x, v.y, v.z, v.w}, (f32x4 *)dst);
+                else *dst = v;
             }
         }
     }

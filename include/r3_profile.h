@@ -42,10 +42,11 @@ int r3_profile_copy(void *dst, const void *src, size_t bytes, void *stream);
 
 /*
  * Measurement aid: a pure bf16 MFMA issue loop (`calib_mfma_kernel`, one
- * work-group of 8 waves per compute unit, 8 independent 32x32x16 accumulator
- * tiles per wave, operands in registers, no memory traffic) of `iters`
+ * work-group of 8 waves per compute unit, 32 independent 16x16 accumulator
+ * tiles per wave as in the expert GEMMs, 16 MFMAs 16x16x32 per iteration,
+ * operands in registers, no memory traffic) of `iters`
  * iterations; random_operands != 0 fills the operand registers with varied bit
- * patterns, 0 with one constant.  It does 2*32*32*16 * 8 * iters * 8 * grid
+ * patterns, 0 with one constant.  It does 2*16*16*32 * 16 * iters * 8 * grid
  * FLOP (r3_profile_mfma_flops); timed by the caller it gives the matrix rate
  * this machine sustains under its power limit, which depends on the operand
  * data.  `sink` is a device float the kernel may write (never in practice).
@@ -55,16 +56,15 @@ double r3_profile_mfma_flops(int iters);
 
 /*
  * Measurement aid: the same MFMA loop fed the way the expert GEMMs feed theirs
- * (`calib_mix_kernel`): per 8 MFMAs a wave reads 6 fragments from LDS, and per
- * 16 MFMAs of each wave the work-group brings 32 KB into LDS with direct
+ * (`calib_mix_kernel`): per 32 MFMAs a wave reads 12 fragments from LDS and
+ * the work-group brings 32 KB into LDS with direct
  * global->LDS loads from `src_1mib` (device, 1 MiB, 16-byte aligned, finite
  * bf16 values; stays cache-resident).  No barriers, epilogues or HBM misses:
  * the rate a perfect schedule of that instruction mix reaches under the power
  * limit.  Same FLOP count as r3_profile_mfma (r3_profile_mfma_flops).
  * shape 0: the kernels' shape, 8 waves of 128 x 64 per work-group.  shape 1: 4
- * waves of 128 x 128 (8 fragment reads per 16 MFMAs, the same global->LDS
- * bytes per FLOP): the ceiling of the other shape the GEMM header can be built
- * for.  Any other shape: R3_ERR_INVALID_ARG.
+ * waves of 128 x 128 (16 fragment reads per 64 MFMAs, the same global->LDS
+ * bytes per FLOP), for comparison.  Any other shape: R3_ERR_INVALID_ARG.
  */
 int r3_profile_gemm_mix(int shape, int iters, const void *src_1mib, float *sink, void *stream);
 

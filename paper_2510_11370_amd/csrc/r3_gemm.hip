@@ -426,10 +426,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     constexpr bool GATHER = MODE == 1;     // Q rows through the row -> token list
     __shared__ int4 qstash[GATHER ? 2 * 256 : 1];   // the gathered rows' offsets (no registers to spare for them)
     POp P;
-#ifndef R3_DH_STASH
-#define R3_DH_STASH 1
-#endif
-    OpKC64<GATHER, GATHER && R3_DH_STASH, false, RAGGED> Q;
+    OpKC64<GATHER, GATHER, false, RAGGED> Q;
     if constexpr (MODE == 0) {
         P.init(d * 2, 0, 128 * wp0);
     } else {
@@ -525,9 +522,9 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     if constexpr (MODE == 1) {
         // Rounds of 32 rows x 64 features (four, a tail tile two or one), each in three phases: FA -> dA, FB -> dB, H -> g H and the
         // row's dot product.  A phase's rows come in row-contiguously into a patch, each lane replaces
-        // exactly the quads it read, and the patch goes out row-contiguously.  The rows of the phase
-        // after next are asked for while this one is worked on: two 4 KB blocks in flight per wave (a
-        // whole round ahead, three blocks, cost the tile loop its registers).  A lane's products u H of one
+        // exactly the quads it read, and the patch goes out row-contiguously.  The rows of the next phase
+        // are asked for while this one is worked on (three phases ahead, straight into LDS: this kernel 0-2 % faster,
+        // no step any faster, so it is not what the epilogue waits for; through registers that spills).  A lane's products u H of one
         // 32-row block belong to two rows (r16 and 16 + r16).
         typedef RowStage<128> Patch;
         const Patch sa{st.base, tid}, sb{st.base + Patch::BYTES, tid}, sh{st.base + 2 * Patch::BYTES, tid};

@@ -26,8 +26,9 @@
 //        fragments come out through ds_read_b64_tr_b16 (4 consecutive k of one feature).
 // The four stages are separate LDS arrays so that the compiler can see that loads in
 // flight never alias the stage being read (no vmcnt wait in front of the fragment reads).
-// Wave roles.  All 8 waves multiply.  Waves 0-3 ("loaders") also issue every tile load and
-// count them: each issues the same number of loads per stage (a stage past the end of the
+// Wave roles.  All 8 waves multiply.  In the ring of stages waves 0-3 ("loaders") also issue every tile load and
+// count them (sharing them out over all eight made the weight gradients 2 % slower; the loop over windows does
+// share them, see there): each issues the same number of loads per stage (a stage past the end of the
 // reduction gets a zero-length descriptor), so "s_waitcnt vmcnt(one stage's worth)" at the end
 // of stage kt is exactly "stage kt+1 has landed" (a third stage of prefetch was measured: no gain).  (Having waves 4-7 touch the lines of
 // later stages to warm L2 was tried and measured slower: the extra requests cost more in the
@@ -42,7 +43,7 @@ constexpr int kTile = 256;
 constexpr int kStages2 = 4;
 constexpr int kOperandBytes = kTile * kBK2 * 2;  // 16 KB
 constexpr int kStageBytes = 2 * kOperandBytes;   // 32 KB
-// 2 (P) x 4 (Q) waves of 128 x 64, two per SIMD; waves 0-3 also load
+// 2 (P) x 4 (Q) waves of 128 x 64, two per SIMD
 constexpr int kWaves2 = 8, kThreads2 = 512, kMinWavesPerSimd = 2;
 constexpr int kWP2 = 2, kWQ2 = 4, kTP2 = 8, kTQ2 = 4;   // waves and 16 x 16 tiles of a wave along P and Q
 constexpr int kHalfP = kTP2 / 2;                        // a sub-step multiplies half of a wave's P tiles with all Q tiles
@@ -546,13 +547,13 @@ constexpr int kBK3 = 64;
 constexpr int kWinBytes = kTile * kBK3 * 2;   // 32 KB: one operand's window
 constexpr int kSuperBytes = 2 * kWinBytes;    // 64 KB: both operands
 
-// K-contiguous 256-row window [256 rows][128 B]: 32 chunks of 1 KB (8 rows x 128 B), eight per
-// loader wave; the 16-byte chunk c of row r sits at slot c ^ ((r >> 1) & 7) (KcFrag16's
+// K-contiguous 256-row window [256 rows][128 B]: 32 chunks of 1 KB (8 rows x 128 B), eight for
+// each of the four waves that load this operand; the 16-byte chunk c of row r sits at slot c ^ ((r >> 1) & 7) (KcFrag16's
 // conflict-free order), applied on the global side.  Chunk i of a wave is 32 rows below chunk
 // i - 1 and has the same swizzle, so one per-lane offset and a stride describe all eight --
 // unless the rows are gathered (ROWS = true): then each lane keeps the offsets of its eight rows.
 // STASH (with ROWS): the eight row offsets live in LDS instead of registers (`stash`: 2 x 256 int4
-// outside the tile buffers, one slot pair per loader thread) and are read back at every window issue;
+// outside the tile buffers, one slot pair per loading thread) and are read back at every window issue;
 // for kernels whose tile loop has no eight registers to spare.
 // INSIDE (without ROWS): every row of the window exists (a weight panel), so the 32-row advance from
 // chunk to chunk rides in the load's scalar offset and the lane keeps one offset register; otherwise

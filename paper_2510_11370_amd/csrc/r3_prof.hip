@@ -54,42 +54,64 @@ __global__ void __launch_bounds__(256) calib_copy_kernel(uint4 *__restrict__ dst
 }
 
 typedef __bf16 cal_bf16x8_t __attribute__((ext_vector_type(8)));
-typedef float cal_f32x16_t __attribute__((ext_vector_type(16)));
+typedef float cal_f32x4_t __attribute__((ext_vector_type(4)));
 typedef unsigned short cal_u16x8_t __attribute__((ext_vector_type(8)));
 
-// the accumulator/fragment shape of the expert GEMMs' inner step, fed from registers only
+// MFMAs 16x16x32 of PI x PJ accumulator tiles, neighbours sharing an operand, as the expert GEMMs order them
+template <int PI, int PJ, int NI>
+__device__ __forceinline__ void cal_block(cal_f32x4_t (&acc)[NI][PJ], const cal_bf16x8_t (&a)[PI], const cal_bf16x8_t (&b)[PJ], int i0) {
+#pragma unroll
+    for (int j = 0; j < PJ; ++j)
+#pragma unroll
+        for (int ii = 0; ii < PI; ++ii) {
+            const int i = (j & 1) ? PI - 1 - ii : ii;
+            acc[i0 + i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], b[j], acc[i0 + i][j], 0, 0, 0);
+        }
+}
+template <int NI, int NJ>
+__device__ __forceinline__ void cal_keep(const cal_f32x4_t (&acc)[NI][NJ], float *sink) {   // keeps the loop alive
+    float s = 0.0f;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+#pragma unroll
+        for (int j = 0; j < NJ; ++j)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) s += acc[i][j][v];
+    if (s == 1.2345678f) *sink = s;
+}
+
+// the accumulator/fragment shape of the expert GEMMs' inner step, fed from registers only: half of a wave's 128 x 64 tile
+// (16 MFMAs) per iteration
 __global__ void __launch_bounds__(512, 2) calib_mfma_kernel(int iters, int rnd, float *sink) {
-    cal_bf16x8_t a[4], b[2];
+    cal_bf16x8_t a[2][4], b[4];
     uint32_t h = (threadIdx.x + blockIdx.x * 977u) * 2654435761u;
-    for (int i = 0; i < 6; ++i) {
+    auto fill = [&](cal_bf16x8_t &f) {
         cal_u16x8_t u;
+#pragma unroll
         for (int j = 0; j < 8; ++j) {
             h = h * 1664525u + 1013904223u;
             // finite bf16 values of either sign with varied mantissas, or the constant 1.0
             u[j] = rnd ? (unsigned short)(0x3c00u + ((h >> 9) & 0x83ffu)) : (unsigned short)0x3f80u;
         }
-        if (i < 4) a[i] = __builtin_bit_cast(cal_bf16x8_t, u);
-        else b[i - 4] = __builtin_bit_cast(cal_bf16x8_t, u);
-    }
-    cal_f32x16_t acc[4][2];
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 2; ++j)
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-    for (int it = 0; it < iters; ++it) {
+        f = __builtin_bit_cast(cal_bf16x8_t, u);
+    };
 #pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+    for (int i = 0; i < 4; ++i) {
+        fill(a[0][i]);
+        fill(a[1][i]);
+        fill(b[i]);
     }
-    float s = 0.0f;
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 2; ++j)
-            for (int v = 0; v < 16; ++v) s += acc[i][j][v];
-    if (s == 1.2345678f) *sink = s;  // keeps the loop alive
+    cal_f32x4_t acc[8][4] = {};
+    for (int it = 0; it + 1 < iters; it += 2) {
+        cal_block<4, 4, 8>(acc, a[0], b, 0);
+        cal_block<4, 4, 8>(acc, a[1], b, 4);
+    }
+    if (iters & 1) cal_block<4, 4, 8>(acc, a[0], b, 0);
+    cal_keep(acc, sink);
 }
 
-// The expert GEMMs' instruction mix without their synchronisation: per 8 MFMAs a wave reads 6 fragments
-// (ds_read_b128) from LDS, and per two such steps the work-group brings 32 KB into LDS with direct
+// The expert GEMMs' instruction mix without their synchronisation: per 32 MFMAs (two iterations) a wave reads 12 fragments
+// (ds_read_b128) from LDS, and the work-group brings 32 KB into LDS with direct
 // global->LDS loads from a 1 MiB (cache-resident) source.  No barriers, no epilogue, no HBM misses: the rate
 // a perfect schedule of the same mix would reach under the machine's power limit.  LDS holds varied bf16
 // bit patterns; the loads race with the reads on purpose (only the traffic matters, every value is finite).
@@ -102,43 +124,39 @@ __global__ void __launch_bounds__(512, 2) calib_mix_kernel(int iters, const uint
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    cal_f32x16_t acc[4][2];
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 2; ++j)
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-    cal_bf16x8_t a[4], b[2];
+    cal_f32x4_t acc[8][4] = {};
+    cal_bf16x8_t a[4], b[4] = {};
     __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)src, (short)0, 1 << 20, 0x00020000);
-    for (int it = 0; it < iters; ++it) {
-        const char *st = lds[it & 3] + (w & 1) * 8192;
+    auto half = [&](int it, int hf) {
+        const char *st = lds[(it >> 1) & 3] + (w & 1) * 8192 + hf * 4096;
 #pragma unroll
         for (int i = 0; i < 4; ++i) a[i] = *(const cal_bf16x8_t *)(st + i * 1024 + lane * 16);
+        if (hf == 0) {
 #pragma unroll
-        for (int i = 0; i < 2; ++i) b[i] = *(const cal_bf16x8_t *)(st + 16384 + i * 1024 + lane * 16);
-        if (it & 1) {
-            char *dst = lds[(it + 2) & 3];
+            for (int i = 0; i < 4; ++i)
+                b[i] = *(const cal_bf16x8_t *)(lds[(it >> 1) & 3] + 16384 + (w >> 1) * 4096 + i * 1024 + lane * 16);
+        } else {
+            char *dst = lds[((it >> 1) + 2) & 3];
 #pragma unroll
             for (int c = 0; c < 4; ++c)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     r, (__attribute__((address_space(3))) void *)(dst + c * 8192 + w * 1024), 16,
                     ((it * 4 + c) * 8192 + (int)threadIdx.x * 16) & ((1 << 20) - 1), 0, 0, 0);
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 2; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        cal_block<4, 4, 8>(acc, a, b, 4 * hf);
+    };
+    for (int it = 0; it + 1 < iters; it += 2) {
+        half(it, 0);
+        half(it + 1, 1);
     }
+    if (iters & 1) half(iters - 1, 0);
     __builtin_amdgcn_s_waitcnt(0);
-    float s = 0.0f;
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 2; ++j)
-            for (int v = 0; v < 16; ++v) s += acc[i][j][v];
-    if (s == 1.2345678f) *sink = s;
+    cal_keep(acc, sink);
 }
 
-// The same for the other tile shape the GEMM header can be built for: 4 waves of 128 x 128 per work-group
-// (one per SIMD, 256 accumulator registers each).  Per 16 MFMAs a wave reads 8 fragments -- a third fewer LDS
-// bytes per FLOP -- and the work-group's global->LDS traffic per FLOP is the same (per 32 MFMAs of each wave it
-// brings 32 KB).  Same FLOP per iteration and work-group as calib_mix_kernel (4 waves x 16 MFMAs).
+// The same for a shape of 4 waves of 128 x 128 per work-group (one per SIMD, 256 accumulator registers each).  Per 64 MFMAs a
+// wave reads 16 fragments -- a third fewer LDS bytes per FLOP -- and the work-group's global->LDS traffic per FLOP is the same.
+// Same FLOP per iteration and work-group as calib_mix_kernel (4 waves x 32 MFMAs: half of the wave's tile).
 __global__ void __launch_bounds__(256) calib_mix4_kernel(int iters, const uint32_t *src, float *sink) {
     __shared__ __attribute__((aligned(16))) char lds[4][32768];
     uint32_t h = (threadIdx.x + blockIdx.x * 977u) * 2654435761u;
@@ -148,37 +166,33 @@ __global__ void __launch_bounds__(256) calib_mix4_kernel(int iters, const uint32
     }
     __syncthreads();
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-    cal_f32x16_t acc[4][4];
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j)
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.0f;
-    cal_bf16x8_t a[4], b[4];
+    cal_f32x4_t acc[8][8] = {};
+    cal_bf16x8_t a[4], b[8] = {};
     __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)src, (short)0, 1 << 20, 0x00020000);
-    for (int it = 0; it < iters; ++it) {
-        const char *st = lds[it & 3];
+    auto half = [&](int it, int hf) {
+        const char *st = lds[(it >> 1) & 3];
 #pragma unroll
-        for (int i = 0; i < 4; ++i) a[i] = *(const cal_bf16x8_t *)(st + (w & 1) * 4096 + i * 1024 + lane * 16);
+        for (int i = 0; i < 4; ++i) a[i] = *(const cal_bf16x8_t *)(st + (w & 1) * 8192 + hf * 4096 + i * 1024 + lane * 16);
+        if (hf == 0) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) b[i] = *(const cal_bf16x8_t *)(st + 16384 + (w >> 1) * 4096 + i * 1024 + lane * 16);
-        if (it & 1) {
-            char *dst = lds[(it + 2) & 3];
+            for (int i = 0; i < 8; ++i) b[i] = *(const cal_bf16x8_t *)(st + 16384 + (w >> 1) * 8192 + i * 1024 + lane * 16);
+        } else {
+            char *dst = lds[((it >> 1) + 2) & 3];
 #pragma unroll
             for (int c = 0; c < 8; ++c)
                 __builtin_amdgcn_raw_ptr_buffer_load_lds(
                     r, (__attribute__((address_space(3))) void *)(dst + c * 4096 + w * 1024), 16,
                     ((it * 8 + c) * 4096 + (int)threadIdx.x * 16) & ((1 << 20) - 1), 0, 0, 0);
         }
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-#pragma unroll
-            for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[i], b[j], acc[i][j], 0, 0, 0);
+        cal_block<4, 8, 8>(acc, a, b, 4 * hf);
+    };
+    for (int it = 0; it + 1 < iters; it += 2) {
+        half(it, 0);
+        half(it + 1, 1);
     }
+    if (iters & 1) half(iters - 1, 0);
     __builtin_amdgcn_s_waitcnt(0);
-    float s = 0.0f;
-    for (int i = 0; i < 4; ++i)
-        for (int j = 0; j < 4; ++j)
-            for (int v = 0; v < 16; ++v) s += acc[i][j][v];
-    if (s == 1.2345678f) *sink = s;
+    cal_keep(acc, sink);
 }
 
 static int calib_grid() {
@@ -249,6 +263,6 @@ int r3_profile_gemm_mix(int shape, int iters, const void *src_1mib, float *sink,
 }
 
 double r3_profile_mfma_flops(int iters) {
-    return 2.0 * 32 * 32 * 16 * 8.0 * (double)iters * 8.0 * (double)calib_grid();
+    return 2.0 * 16 * 16 * 32 * 16.0 * (double)iters * 8.0 * (double)calib_grid();
 }
 }

@@ -49,3 +49,43 @@ def test_layer_at_tile_edges(sh):
         got = got.cpu().numpy()
         for e in range(sh.E):
             assert np.linalg.norm(got[e] - ref[key][e]) <= c.rel * np.linalg.norm(ref[key][e]) + 1e-30, (key, e)
+
+
+@pytest.mark.parametrize("sh", [
+    SH(T=70, d=36, E=300, K=3, F=44, act="f32", sigma=0.05, seed=71),             # two-byte record
+    SH(T=330, d=132, E=9, K=2, F=68, act="f32", sigma=0.05, zipf_s=0.8, seed=72),  # one-byte record, tiles cut on every side
+], ids=lambda s: "T%d_d%d_F%d_E%d_K%d" % (s.T, s.d, s.F, s.E, s.K))
+def test_shared_launches_of_the_f32_backward(sh):
+    """A token-major record, accumulated gradients, and tokens through perm or expert-sorted, after the one-call forward: the
+    kernels that share a launch there against the oracle, and against each other bit for bit."""
+    c = Case(sh, backward=True, scale_w=5.0)
+    n, L = c.np, 3
+    fwd = sparse.forward(n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], n["bias"])
+    ref = sparse.backward(n["dy"], n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], fwd, want_dbias=True)
+    D = r3.desc(sh.T, sh.d, sh.E, sh.K, sh.F, act="f32", idx_token_stride=L * sh.K)
+    record = torch.zeros(sh.T, L, sh.K, dtype=torch.uint8 if sh.E <= 256 else torch.uint16, device="cuda")
+    record[:, 1] = c.t["idx"]
+    idx, w = record[:, 1], (c.t["Wg"], c.t["Wu"], c.t["Wd"])
+    buf = r3.LayerBuffers(D, backward=True, gathered_copy=False)
+    r3.forward_one_call(buf, c.t["x"], c.t["Wr"], idx, *w, bias=c.t["bias"])
+    perm = torch.from_numpy(fwd["perm"].astype(np.int64)).cuda()
+    results = []
+    for Xp in (None, c.t["x"][perm // sh.K].contiguous()):
+        dbias = torch.zeros(sh.E, dtype=torch.float32, device="cuda")
+        for accumulate in (False, True):
+            r3.moe_backward(r3.gated_desc(D), c.t["dy"], c.t["x"], c.t["Wr"], idx, buf.gates, buf.inv_perm, buf.perm, buf.offsets,
+                            Xp, buf.A, buf.B, buf.H, buf.Yp, *w, buf.dx, buf.dW_r, buf.dW_gate, buf.dW_up, buf.dW_down,
+                            buf.ws_bwd, dbias=dbias, accumulate=accumulate)
+            torch.cuda.synchronize()
+            times = 2.0 if accumulate else 1.0
+            assert_close(host(buf.dx), ref["dx"], "dx", c.rel)
+            assert_close(buf.dW_r.cpu().numpy(), times * ref["dWr"], "dW_r", c.rel)
+            assert_close(dbias.cpu().numpy(), times * ref["dbias"], "dbias", c.rel)
+            for got, key in ((buf.dW_gate, "dWg"), (buf.dW_up, "dWu"), (buf.dW_down, "dWd")):
+                got = got.cpu().numpy()
+                for e in range(sh.E):
+                    want = times * ref[key][e]
+                    assert np.linalg.norm(got[e] - want) <= c.rel * np.linalg.norm(want) + 1e-30, (key, e)
+        results.append([t.clone() for t in (buf.dx, buf.dW_r, buf.dW_gate, buf.dW_up, buf.dW_down, dbias)])
+    for a, b in zip(*results):
+        assert torch.equal(a, b)

@@ -89,3 +89,46 @@ def test_shared_launches_of_the_f32_backward(sh):
         results.append([t.clone() for t in (buf.dx, buf.dW_r, buf.dW_gate, buf.dW_up, buf.dW_down, dbias)])
     for a, b in zip(*results):
         assert torch.equal(a, b)
+
+
+def chains_of_1024(v):
+    """The float32 sum of an expert's dz as the library orders it: 1024 chains of every 1024th row, four rows to an addition, a
+    butterfly over each 64 chains, the sixteen results one after the other."""
+    v = np.concatenate([v, np.zeros(-len(v) % 4096, np.float32)]).reshape(-1, 4, 1024)
+    chain = np.zeros(1024, np.float32)
+    for a in v:
+        chain = chain + ((a[0] + a[1]) + (a[2] + a[3]))
+    w = chain.reshape(16, 64)
+    for o in (32, 16, 8, 4, 2, 1):
+        w = w + w[:, np.arange(64) ^ o]
+    total = np.float32(0.0)
+    for s in w[:, 0]:
+        total = total + s
+    return total
+
+
+@pytest.mark.parametrize("one_call", [True, False])
+def test_router_bias_of_long_segments(one_call):
+    """dbias of an f32 layer, an expert of 70001 rows among them, is the sum of 1024 chains per expert (fewer chains round more),
+    whatever launch makes it.  The experts' weights do not touch the upper half of x and W_r is the unit matrix there, so that
+    dx shows every dz as it is."""
+    T, E, d, F = 70001, 5, 16, 8
+    g = torch.Generator().manual_seed(91)
+    x, dy = torch.randn(T, d, generator=g), torch.randn(T, d, generator=g)
+    Wr = torch.zeros(d, E)
+    Wr[8:8 + E] = torch.eye(E)
+    Wg, Wu, Wd = (torch.randn(E, a, b, generator=g) for a, b in ((d, F), (d, F), (F, d)))
+    Wg[:, 8:] = 0.0
+    Wu[:, 8:] = 0.0
+    idx = torch.stack([torch.zeros(T, dtype=torch.int64), torch.randint(1, E, (T,), generator=g)], 1).to(torch.uint8)
+    x, dy, Wr, Wg, Wu, Wd, idx = (t.cuda().contiguous() for t in (x, dy, Wr, Wg, Wu, Wd, idx))
+    buf = r3.LayerBuffers(r3.desc(T, d, E, 2, F, act="f32"), backward=True, gathered_copy=False)
+    dbias = torch.zeros(E, dtype=torch.float32, device="cuda")
+    (r3.forward_one_call if one_call else r3.forward)(buf, x, Wr, idx, Wg, Wu, Wd)
+    r3.backward(buf, dy, x, Wr, idx, Wg, Wu, Wd, dbias=dbias)
+    torch.cuda.synchronize()
+    dz, chosen = buf.dx[:, 8:8 + E].cpu().numpy(), idx.cpu().numpy()
+    for e in range(E):
+        rows = dz[(chosen == e).any(1), e]
+        assert len(rows) > 16000 and (rows != 0).mean() > 0.9
+        assert dbias[e].item() == chains_of_1024(rows), e

@@ -528,7 +528,9 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
         // 32-row block belong to two rows (r16 and 16 + r16).
         typedef RowStage<128> Patch;
         const Patch sa{st.base, tid}, sb{st.base + Patch::BYTES, tid}, sh{st.base + 2 * Patch::BYTES, tid};
-        float *const wtail = (float *)(st.base + 3 * Patch::BYTES);   // tail tiles: the wave's share of its rows' dot products
+        // A row's dot product is summed per 64 features and those sums are added in pairs, in a full tile (whose waves have both) as in a
+        // tail: a row's dz is the same bits whichever kind of tile its expert's other rows make it.
+        float *const whalf = (float *)(st.base + 3 * Patch::BYTES);   // the wave's first sums
         constexpr int NR = 2 * (kWaveRowsQ / 32);   // (GATED: the H phases only read)
         auto where = [&](int r, int &valid) -> int64_t {
             const int brow = row0 + wt.row + (r >> 1) * 32;
@@ -559,10 +561,12 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
                     const int rn = tail ? r + 2 : r + 1;   // the wave's next round
                     if ((rn >> 1) < wt.blocks) rr = ask(rn, 0);
                 }
-                if (which == 0 && half == 0) {
-                    const float2 gates = row_gates(gates_lds, wt.row + blk * 32 + r16);
-                    gq[0] = gates.x;
-                    gq[1] = gates.y;
+                if (which == 0) {
+                    if (half == 0) {
+                        const float2 gates = row_gates(gates_lds, wt.row + blk * 32 + r16);
+                        gq[0] = gates.x;
+                        gq[1] = gates.y;
+                    }
                     wsum[0] = wsum[1] = 0.0f;
                 }
 #pragma unroll
@@ -587,8 +591,8 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
                     }
                 bf16_t *dst = which == 0 ? out0 : which == 1 ? out1 : out2;
                 if (!(GATED && which == 2)) sp.flush((char *)dst + oh, (int64_t)NOUT * 2, valid, width - 128 * half, stream);
-                if (which == 2 && (half == 1 || tail)) {
-                    // the four lanes that hold a row add up; lanes 0..15 write the first 16 rows, 16..31 the others
+                if (which == 2) {
+                    // the four lanes that hold a row add up; lanes 0..15 have the first 16 rows, 16..31 the others
                     float w[2];
 #pragma unroll
                     for (int t = 0; t < 2; ++t) {
@@ -597,9 +601,11 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
                     }
                     const int q = lane & 31;
                     const float wq = lane < 16 ? w[0] : w[1];
-                    if (lane < 32 && tail) wtail[32 * blk + q] = wq;
-                    else if (lane < 32 && brow + q < row_end)
-                        wpart[(int64_t)(brow + q) * (2 * npt) + 2 * (p0 / kTile) + wp] = wq;
+                    if (lane < 32 && half == 0) whalf[32 * blk + q] = wq;
+                    else if (lane < 32 && brow + q < row_end) {
+#pragma clang fp contract(off)   // (the product with the gate is rounded, as where it passes through LDS)
+                        wpart[(int64_t)(brow + q) * (2 * npt) + 2 * (p0 / kTile) + wp] = whalf[32 * blk + q] + wq;
+                    }
                 }
             }
         }
@@ -608,7 +614,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
             const float *other = (const float *)(wave_patch(s0, s1, s2, s3, tid ^ 64) + 3 * Patch::BYTES);
             const int row = row0 + wt.row + lane;
             if (!(wt.quarter & 1) && lane < 32 * wt.blocks && row < row_end)
-                wpart[(int64_t)row * (2 * npt) + 2 * (p0 / kTile) + wp] = wtail[lane] + other[lane];
+                wpart[(int64_t)row * (2 * npt) + 2 * (p0 / kTile) + wp] = whalf[lane] + other[lane];
         }
     } else {
 #pragma unroll

@@ -246,3 +246,26 @@ def test_nonfinite_values_stay_where_they_belong(d, F):
         assert finite(b.y[apart]) and finite(b.dx[apart]) and not finite(b.y), k
         # (the tokens that met it carry it, through their gate's gradient, to their other experts' dz, not to their weights)
         assert all(finite(g[others]) for g in (b.dW_gate, b.dW_up, b.dW_down)), k
+
+
+@pytest.mark.parametrize("one_call", [True, False])
+@pytest.mark.parametrize("d,F", [(512, 512), (520, 392)])     # whole tiles; guarded ones
+def test_gate_gradients_do_not_depend_on_the_batch(d, F, one_call):
+    """A row's dz is the same bits whether its expert's rows make a tail tile or a full one: tokens without an upstream gradient
+    behind the others lift every expert past 128 rows and leave dbias as it is."""
+    few, many = 800, 2400
+    sh = SH(T=many, d=d, E=64, K=8, F=F, sigma=0.02, seed=80)
+    c = Case(sh, backward=True, scale_w=5.0)
+    c.t["dy"][few:] = 0.0
+    w, got = (c.t["Wg"], c.t["Wu"], c.t["Wd"]), []
+    for T in (few, many):
+        x, dy, idx = (c.t[k][:T].contiguous() for k in ("x", "dy", "idx"))
+        buf = r3.LayerBuffers(r3.desc(T, d, sh.E, sh.K, F), backward=True, gathered_copy=False)
+        dbias = torch.zeros(sh.E, dtype=torch.float32, device="cuda")
+        (r3.forward_one_call if one_call else r3.forward)(buf, x, c.t["Wr"], idx, *w)
+        r3.backward(buf, dy, x, c.t["Wr"], idx, *w, dbias=dbias)
+        torch.cuda.synchronize()
+        got.append((dbias, buf.dx[:few].clone(), buf.counts.tolist()))
+    assert np.median(got[0][2]) <= 128 < min(got[1][2])
+    assert torch.equal(got[0][0], got[1][0])
+    assert torch.equal(got[0][1], got[1][1])

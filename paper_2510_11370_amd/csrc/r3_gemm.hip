@@ -938,6 +938,19 @@ static int stream_rows(int64_t S, int E, int F) {
     return !(S < 192 * (int64_t)E && S * F * 2 <= (64ll << 20));
 }
 
+// The same for the H of a forward that saves nothing for a backward, which only the down projection reads.  At whole widths H leaves
+// with the hint; at ragged ones, where its rows mostly end inside a line, only if it is too large to wait in the caches, or if the pass is
+// mostly the stream of more weights than these hold.  Forward pass, us, streamed | left: 393 tokens top-6, d=392 F=592 E=16 57.1 | 53.8; 1000
+// tokens top-4, 776 x 1416, 32 experts (211 MB of weights) 131.5 | 126.1; 1000 x 704, 64 experts (270 MB), top-6: 1000 tokens 103.7 | 106.1, 2000
+// 134.3 | 133.9, 3001 (25 MB of H) 192.1 | 188.9, 8000 (68 MB) 334.0 | 331.9, 12000 (101 MB) 453.4 | 453.6, 16000 (135 MB) 575.5 | 578.1,
+// 32000 (270 MB) 1055.6 | 1073.7.  Whole: 1024 x 768, 64 experts, top-6, 2000 tokens 122.0 | 125.2, 2048 x 768, 128 experts, top-8, 1000
+// tokens 266.5 | 269.5.
+template <bool RAGGED>
+static int stream_unsaved_h(int64_t S, int d, int E, int F) {
+    const bool weights = S < 128 * (int64_t)E && 6 * (int64_t)E * d * F > (256ll << 20);
+    return !(RAGGED && !weights && S * F * 2 <= (96ll << 20));
+}
+
 template <bool GATHER, bool RAGGED>
 static void launch_ffn1(int64_t S, int d, int E, int F, const void *Xp, const int32_t *perm, int K, int T,
                         const int32_t *offsets, const int32_t *tiles, const void *Wg, const void *Wu, void *H, void *FA,
@@ -945,7 +958,7 @@ static void launch_ffn1(int64_t S, int d, int E, int F, const void *Xp, const in
     const int64_t n = max_row_tiles(S, E, kTile) * tiles_of(F, 128);
     ffn1_kernel<GATHER, RAGGED><<<persistent_grid(n), kThreads2, 0, s>>>(
         (int)S, d, F, (const bf16_t *)Xp, perm, K, T, offsets, tiles, (const bf16_t *)Wg, (const bf16_t *)Wu, (bf16_t *)H,
-        (bf16_t *)FA, (bf16_t *)FB, grow, FA ? stream_rows(S, E, F) : 1);
+        (bf16_t *)FA, (bf16_t *)FB, grow, FA ? stream_rows(S, E, F) : stream_unsaved_h<RAGGED>(S, d, E, F));
 }
 
 template <int MODE, bool GATED, bool RAGGED>

@@ -269,3 +269,21 @@ def test_gate_gradients_do_not_depend_on_the_batch(d, F, one_call):
     assert np.median(got[0][2]) <= 128 < min(got[1][2])
     assert torch.equal(got[0][0], got[1][0])
     assert torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.parametrize("T,d,F", [(500, 392, 592), (8200, 40, 776)])     # H left in the caches; 102 MB of it streamed
+def test_forward_without_saved_tensors(T, d, F):
+    """Whether the forward saves for a backward does not change a bit of y."""
+    sh = SH(T=T, d=d, E=16, K=8, F=F, sigma=0.02, seed=81)
+    c = Case(sh, scale_w=5.0)
+    y = []
+    for backward in (False, True):
+        buf = r3.LayerBuffers(c.D, backward=backward, gathered_copy=False)
+        buf.H.fill_(7.0)
+        r3.forward_one_call(buf, c.t["x"], c.t["Wr"], c.t["idx"], c.t["Wg"], c.t["Wu"], c.t["Wd"])
+        torch.cuda.synchronize()
+        y.append((buf.H, buf.y))
+    assert torch.equal(y[0][0], y[1][0]) and torch.equal(y[0][1], y[1][1])
+    n = c.np
+    fwd = sparse.forward(n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], n["bias"])
+    assert_close(host(y[0][1]), fwd["y"], "y", c.rel)

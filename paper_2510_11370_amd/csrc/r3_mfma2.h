@@ -421,20 +421,63 @@ __device__ __forceinline__ void step_last(Acc2 &acc, const Frags &f) {
     for (int j = 0; j < kTQ2; ++j) mfma_col<1>(acc, f.x, f.q[j], j);
 }
 
+// The same two sub-steps for the ring of stages, whose operands are both transposed tiles.  Such a fragment is two LDS reads, a stage's 24 of
+// eight waves keep LDS busy for three quarters of its MFMAs' time and the tiles' arrival for the rest, and LDS falls behind where more than
+// four go out with four MFMAs: eight and two, two, two with the first half's columns, six and four with the second's (the order above) left
+// the pipe waiting, visibly where the card has power to spare (7000 tokens over 8 experts, 256 x 256, dW_down 39.3 us).  So at most
+// four to a column, and none with the last, before the loads and the barrier: 37.7 us (32x32x16 MFMAs 36.9); 65536 Zipf tokens of the
+// 2048 x 768 x 128-expert layer dW_down 1382 -> 1337, dW_gate/dW_up 2903 -> 2847.  On the windows, half of whose operands or more come in single
+// reads, this order is no faster (131072 tokens forward 0.4 % slower).
+template <class FP, class FQ>
+__device__ __forceinline__ void ring_first(Acc2 &acc, Frags &f, FP fp, FQ fq) {
+    f.y[0] = fp(0);
+    f.y[1] = fp(1);
+    mfma_col<1>(acc, f.x, f.q[0], 0);
+    thread_reads<4>();
+    f.q[0] = fq(0);
+    f.y[2] = fp(2);
+    mfma_col<1>(acc, f.x, f.q[1], 1);
+    thread_reads<4>();
+    f.q[1] = fq(1);
+    f.y[3] = fp(3);
+    mfma_col<1>(acc, f.x, f.q[2], 2);
+    thread_reads<4>();
+    mfma_col<1>(acc, f.x, f.q[3], 3);
+    __builtin_amdgcn_sched_barrier(0);
+}
+template <class FP, class FQ>
+__device__ __forceinline__ void ring_second(Acc2 &acc, Frags &f, FP fp, FQ fq) {
+    f.q[2] = fq(2);
+    f.x[0] = fp(kHalfP);
+    mfma_col<0>(acc, f.y, f.q[0], 0);
+    thread_reads<4>();
+    f.q[3] = fq(3);
+    f.x[1] = fp(kHalfP + 1);
+    mfma_col<0>(acc, f.y, f.q[1], 1);
+    thread_reads<4>();
+    f.x[2] = fp(kHalfP + 2);
+    f.x[3] = fp(kHalfP + 3);
+    mfma_col<0>(acc, f.y, f.q[2], 2);
+    thread_reads<4>();
+    mfma_col<0>(acc, f.y, f.q[3], 3);
+    __builtin_amdgcn_sched_barrier(0);
+}
+
 // One resident stage (one 32-k step).  The loads of the stage two ahead are
 // issued between the two sub-steps (inline asm, stays where it is written).
 template <class POp, class QOp>
 __device__ __forceinline__ void stage_compute(Acc2 &acc, Frags &f, const POp &P, const QOp &Q, const char *stage, int kt_load,
                                               uint32_t stage_load, bool loader) {
+    static_assert(POp::kReads == 2 && QOp::kReads == 2, "");
     auto fp = [&](int i) { return P.frag(stage, i); };
     auto fq = [&](int j) { return Q.frag(stage + kOperandBytes, j); };
-    step_first<POp::kReads, QOp::kReads>(acc, f, fp, fq);
+    ring_first(acc, f, fp, fq);
     if (loader) {
         P.issue(kt_load, stage_load);
         Q.issue(kt_load, stage_load + kOperandBytes);
     }
     __builtin_amdgcn_sched_barrier(0);
-    step_second<POp::kReads, QOp::kReads>(acc, f, fp, fq);
+    ring_second(acc, f, fp, fq);
 }
 
 // End of a stage.  Loaders wait until at most one stage's loads are outstanding (their share

@@ -28,7 +28,7 @@ struct F32Cfg {
     static constexpr int LOADS = TP + TQ;   // loads per wave and k-tile (a load of four waves is 4 KB)
 };
 typedef F32Cfg<2, 2, 2> F32Tile;     // 32 KB of LDS: five work-groups on a compute unit, which cover what is not prefetched
-typedef F32Cfg<1, 1, 4> F32Short;    // few tiles: four times as many, half the chain each, loads three k-tiles ahead
+typedef F32Cfg<1, 1, 4> F32Short;    // few tiles: four times as many, half the chain each, loads three k-tiles ahead (F32WgradOp: one)
 typedef F32Cfg<2, 1, 4> F32Short1;   // the same for the SwiGLU, whose P tile holds both weights
 
 template <class C> using F32Acc = f32x4_t[C::TP][C::TQ];
@@ -296,20 +296,24 @@ __device__ __forceinline__ void f32_rows_tile(const F32RowArgs &g, int block, ch
 // ---------------------------------------------------------------------------
 // The three weight gradients of every expert in one launch (as plain_wgrad_kernel).
 // ---------------------------------------------------------------------------
-// A k-major operand of which k-row r is row r0 + r of a matrix, or row perm[r0 + r] / K of it: the indices are fetched a
-// k-tile before the loads that need them.
-template <int R>
+// A k-major operand of which k-row r is row r0 + r of a matrix, or (GATHER) row perm[r0 + r] / K of it.  The entries of perm are fetched a
+// k-tile before the loads that need them.  The compiler counts their loads but not the tiles', and waits for everything in flight
+// before it uses an entry: so the gathered operand's loads go out first, when the tiles before have been waited for (with two tiles in LDS) or
+// at most two are on the way (with four: one is left ahead), and a plain operand has no such registers.  With the choice made in the loop
+// a tile's own loads were drained before the MFMAs: training, us, 2048 tokens top-4, 512 x 1024, 16 experts 763 | 748 now, 4096 top-2, 256 x 256, 8 experts,
+// Zipf 274 | 217.  Entries by scalar loads, which have a counter of their own, take 8 selects a load: 217, and 8192 tokens, 128 x 256 189 | 203.
+template <int R, bool GATHER>
 struct F32WgradOp {
     F32Cols<R> op;
     const int32_t *perm;
     int n, ld, K, next[R / 32];
     __device__ __forceinline__ void init(const float *m, const int32_t *perm_, int64_t nrows, int r0, int n_, int ld_, int K_, int col0,
                                          int wave_block) {
-        perm = perm_ ? perm_ + r0 : nullptr;
+        perm = perm_ + r0;
         n = n_; ld = ld_; K = K_;
-        const int64_t first = perm ? 0 : (int64_t)r0 * ld;
-        op.init(m + first + col0, (uint64_t)((perm ? nrows : n) * ld - col0) * 4, ld, wave_block);
-        if (perm) {
+        const int64_t first = GATHER ? 0 : (int64_t)r0 * ld;
+        op.init(m + first + col0, (uint64_t)((GATHER ? nrows : n) * ld - col0) * 4, ld, wave_block);
+        if constexpr (GATHER) {
             op.src.step = 0;
             fetch(0);
         }
@@ -319,13 +323,16 @@ struct F32WgradOp {
         for (int i = 0; i < R / 32; ++i) next[i] = perm[min(kt * 32 + op.load_k(i), n - 1)];
     }
     __device__ __forceinline__ void issue(int kt, uint32_t tile) {
-        if (!perm) {
+        if constexpr (!GATHER) {
             op.issue(kt, tile);
-            return;
-        }
+        } else {
+            int off[R / 32];   // (every entry is used before the first load goes out)
 #pragma unroll
-        for (int i = 0; i < R / 32; ++i) op.issue_row(i, tile, kt * 32 + op.load_k(i) < n ? next[i] / K * (ld * 4) : -1);
-        fetch(kt + 1);
+            for (int i = 0; i < R / 32; ++i) off[i] = kt * 32 + op.load_k(i) < n ? next[i] / K * (ld * 4) : -1;
+#pragma unroll
+            for (int i = 0; i < R / 32; ++i) op.issue_row(i, tile, off[i]);
+            fetch(kt + 1);
+        }
     }
 };
 
@@ -354,13 +361,22 @@ __device__ __forceinline__ void f32_wgrad_tile(int E, int T, int K, const int32_
     F32Acc<C> acc;
     f32_zero<C>(acc);
     if (n > 0) {
-        F32WgradOp<C::BP> P;
-        F32WgradOp<C::BQ> Q;
-        P.init(g.Ps, g.pperm, T, r0, n, g.NP, K, p0, wp * C::TP);
-        Q.init(g.Qs, g.qperm, T, r0, n, g.NQ, K, q0, wq * C::TQ);
-        f32_loop<C>(acc, (n + C::BK - 1) / C::BK, [&](int kt, uint32_t a) { P.issue(kt, a); Q.issue(kt, a + C::PBYTES); },
-                    [&](const char *tile, int i, int gr, float (&f)[4]) { P.op.read(tile, i, gr, f); },
-                    [&](const char *tile, int j, int gr, float (&f)[4]) { Q.op.read(tile, j, gr, f); }, lds);
+        auto loop = [&](auto pg, auto qg) {
+            F32WgradOp<C::BP, decltype(pg)::value> P;
+            F32WgradOp<C::BQ, decltype(qg)::value> Q;
+            P.init(g.Ps, g.pperm, T, r0, n, g.NP, K, p0, wp * C::TP);
+            Q.init(g.Qs, g.qperm, T, r0, n, g.NQ, K, q0, wq * C::TQ);
+            auto issue = [&](int kt, uint32_t a) {
+                if constexpr (decltype(qg)::value) Q.issue(kt, a + C::PBYTES);
+                P.issue(kt, a);
+                if constexpr (!decltype(qg)::value) Q.issue(kt, a + C::PBYTES);
+            };
+            f32_loop<C>(acc, (n + C::BK - 1) / C::BK, issue, [&](const char *tile, int i, int gr, float (&f)[4]) { P.op.read(tile, i, gr, f); },
+                        [&](const char *tile, int j, int gr, float (&f)[4]) { Q.op.read(tile, j, gr, f); }, lds);
+        };
+        if (g.pperm) loop(std::true_type{}, std::false_type{});        // dW_down from dy
+        else if (g.qperm) loop(std::false_type{}, std::true_type{});   // dW_gate, dW_up from x
+        else loop(std::false_type{}, std::false_type{});
     }
     float *o = g.out + (int64_t)e * g.NQ * g.NP;
 #pragma unroll
@@ -431,9 +447,11 @@ int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 // 2048 rows, 512 out of 512 x 2 (256) 43.0 | 38.9; 2048 rows, 1024 out of 1024 x 2 (512) 111.6 | 116.5; 8192 rows, 512 out of
 // 1024 x 2 (1024) 190.7 | 211.2; 4096 rows over 128 experts, 512 out of 512 x 2 (512) 88.7 | 85.1; 256 over 128 82.1 | 64.0.
 constexpr int kRowsFill = 512;
-// The weight gradients, whose tiles each write 16 or 4 KB: 32 x 32 below 256 tiles.  8 experts, 16384 rows, 128 x 256 (192 tiles)
-// 96.3 | 60.0; 8192 rows, 256 x 256 (384) 62.9 | 60.7, 2048 rows 21.2 | 22.6, 128 rows 8.4 | 11.0; 512 rows, 128 x 256 9.6 | 9.1.
-constexpr int kWgradFill = 256;
+// The weight gradients, whose tiles each write 16 or 4 KB: 32 x 32 below 320 tiles of the larger kind.  Training, us, 64 x 64 | 32 x 32, 8 experts
+// unless given: 8192 tokens top-2, 128 x 256 (192 tiles) 187.8 | 189.5; 4096 top-2, 192 x 192 (216)
+// 137.4 | 125.0; 2048 top-2, 256 x 256, 5 experts (240) 118.7 | 108.4; 4096 top-1, 192 x 256 (288) 100.0 | 95.4; 3000 top-2, 320 x 320, 4 experts (300)
+// 190.7 | 184.3; 4096 top-2, 256 x 256 (384) 161.3 | 166.2; 300 top-2, 512 x 320, 4 experts (480) 65.5 | 67.6.
+constexpr int kWgradFill = 320;
 
 template <class C, int MODE>
 int rows_blocks(int S, const F32RowArgs &a) {

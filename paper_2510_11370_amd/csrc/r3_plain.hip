@@ -242,19 +242,22 @@ template <int MODE, typename T>
 hipError_t rows_any(int S, int d, int E, int F, const int32_t *offsets, const void *in0, const void *in1, int Tn,
                     const int32_t *perm, int K, const float *gates, const void *W0, const void *W1, const void *FA, const void *FB, void *o0,
                     void *o1, void *o2, hipStream_t s) {
-    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d;
     const bool vec = d % 4 == 0 && F % 4 == 0;
-    if constexpr (sizeof(T) == 4)
-        if (vec)
-            return f32_rows(MODE, S, d, E, F, offsets, (const T *)in0, (const T *)in1, Tn, perm, K, gates, (const T *)W0,
-                            (const T *)W1, (const T *)FA, (const T *)FB, (T *)o0, (T *)o1, (T *)o2, s);
-    const bool big = ceil_div(S, 128) * ceil_div(NOUT, MODE == PLAIN_FFN1 ? 64 : 128) >= kFill;
 #define R3_ROWS(C, V)                                                                                                   \
     rows_launch<C, MODE, T, V>(S, d, E, F, offsets, (const T *)in0, (const T *)in1, perm, K, gates, (const T *)W0,      \
                                (const T *)W1, (const T *)FA, (const T *)FB, (T *)o0, (T *)o1, (T *)o2, s)
-    if (vec && big) R3_ROWS(PlainBig, true);
-    else if (vec) R3_ROWS(PlainSmall, true);
-    else R3_ROWS(PlainSmall, false);
+    if constexpr (sizeof(T) == 4) {
+        if (vec)
+            return f32_rows(MODE, S, d, E, F, offsets, (const T *)in0, (const T *)in1, Tn, perm, K, gates, (const T *)W0,
+                            (const T *)W1, (const T *)FA, (const T *)FB, (T *)o0, (T *)o1, (T *)o2, s);
+        R3_ROWS(PlainSmall, false);
+    } else {
+        const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? F : d;
+        const bool big = ceil_div(S, 128) * ceil_div(NOUT, MODE == PLAIN_FFN1 ? 64 : 128) >= kFill;
+        if (vec && big) R3_ROWS(PlainBig, true);
+        else if (vec) R3_ROWS(PlainSmall, true);
+        else R3_ROWS(PlainSmall, false);
+    }
 #undef R3_ROWS
     return hipGetLastError();
 }

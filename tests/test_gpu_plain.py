@@ -20,9 +20,11 @@ SH = synth.LayerShape
     SH(T=257, d=51, E=9, K=4, F=66, act="bf16", sigma=0.05, seed=64),    # bf16 widths no vector load fits
     SH(T=3, d=4, E=5, K=2, F=4, act="f32", seed=66),                      # one 16-byte piece a row, experts without rows
     SH(T=96, d=36, E=2, K=1, F=100, act="f32", sigma=0.05, seed=67),      # 32 x 32 tiles, a k-tile's second piece alone
-    SH(T=1030, d=68, E=3, K=2, F=640, act="f32", sigma=0.05, seed=68),    # 64 x 64 tiles forward (10 to a row), 32 x 32 backward
-    SH(T=700, d=516, E=4, K=3, F=1028, act="f32", sigma=0.05, zipf_s=1.0, seed=69),   # 64 x 64 tiles all through, four over a tile
-    SH(T=2050, d=1028, E=10, K=4, F=1028, act="f32", sigma=0.05, zipf_s=0.7, seed=65),   # the 128 x 128 tiles, ragged on every side
+    SH(T=1030, d=68, E=3, K=2, F=640, act="f32", sigma=0.05, seed=68),    # 64 x 64 tiles in the SwiGLU (20 to a row), 32 x 32 in the rest
+    SH(T=700, d=516, E=4, K=3, F=1028, act="f32", sigma=0.05, zipf_s=1.0, seed=69),   # 64 x 64 tiles but for outputs of width d, four over a tile
+    SH(T=2050, d=1028, E=10, K=4, F=1028, act="f32", sigma=0.05, zipf_s=0.7, seed=65),   # 64 x 64 tiles all through, ragged on every side
+    SH(T=2050, d=1028, E=10, K=4, F=1028, act="bf16", sigma=0.05, zipf_s=0.7, seed=84),  # the 128 x 128 tiles, ragged on every side
+    SH(T=257, d=52, E=9, K=4, F=68, act="bf16", sigma=0.05, seed=85),     # bf16 in vector loads, 64 x 64 tiles
 ], ids=lambda s: "T%d_d%d_F%d_E%d_K%d_%s" % (s.T, s.d, s.F, s.E, s.K, s.act))
 def test_layer_at_tile_edges(sh):
     c = Case(sh, backward=True, scale_w=5.0)

@@ -930,12 +930,14 @@ static int64_t tiles_of(int64_t n, int tile) { return (n + tile - 1) / tile; }
 
 // Whether what the forward saves and what dH leaves go out with the non-temporal hint.  As a rule they do (see RowStage).  Where
 // an expert has few rows, a backward is bound by writing the weight gradients, and reading its rows from memory through
-// that queue is slow: they are left in the caches then, if they fit.  Training, us, streamed | left: 1001 tokens of the
-// 2048 x 768 x 128-expert layer, 63 rows per expert, dW_gate/dW_up 318 | 304, 2000 tokens 328 | 308, 4000 393 | 385 (SwiGLU and dH
-// together 446 | 451), 8000 531 | 534; 6000 tokens of 1024 x 512 x 384, 62 rows, dW_down 217 | 156, dW_gate/dW_up 335 | 318; 3001
-// tokens of 1000 x 704 x 64, 281 rows, SwiGLU 118 | 124.
+// that queue is slow: they are left in the caches then, if they fit.  Kernels, us, streamed | left: 1001 tokens of the
+// 2048 x 768 x 128-expert layer, 63 rows per expert, dW_gate/dW_up 318 | 304, 2000 tokens 328 | 308; 6000 tokens of 1024 x 512 x 384, Zipf, dW_down
+// 217 | 156.  Training, balanced load, rows per expert and MB of a matrix of rows, us: 2048 x 768 x 128 top-8, 62 and 11 1051 | 1043, 125 and
+// 23 1227 | 1218, 187 and 35 1348 | 1335, 250 and 46 1600 | 1602; 1000 x 704 x 64 top-6, 140 and 12 418 | 417, 187 and 16 443 | 445, 281 and 24
+// 579 | 583; 1024 x 512 x 384 top-4, 125 and 46 1392 | 1390, 166 and 62 1553 | 1573, 187 and 70 1630 | 1645; 512 x 1280 x 256 top-8, 62 and 39
+// 995 | 1010 (the one case found on the wrong side), 125 and 78 1171 | 1193, 187 and 117 1412 | 1443.
 static int stream_rows(int64_t S, int E, int F) {
-    return !(S < 192 * (int64_t)E && S * F * 2 <= (64ll << 20));
+    return !(S < 192 * (int64_t)E && S * F * 2 <= (48ll << 20));
 }
 
 // The same for the H of a forward that saves nothing for a backward, which only the down projection reads.  At whole widths H leaves

@@ -268,7 +268,7 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
     Q.init(d * 2, kWaveRowsQ * ((threadIdx.x >> 6) / kWP2), qstash);
     if constexpr (RAGGED) Q.set_tail(d);
     __shared__ int mailbox[2];
-    __shared__ __attribute__((aligned(256))) char gates_lds[4 * kTile];
+    __shared__ __attribute__((aligned(256))) char gates_lds[RAGGED ? 4 : 4 * kTile];
     RowTileLoop tl(tiles + kTileX, npt, tile_counters(tiles, 0));
     struct Tile {
         int e, row0, row_end, f0;
@@ -314,7 +314,7 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
         Q.set_lane(d * 2, kWaveRowsQ * ((t0 >> 6) / kWP2), t0, qstash);
     }
 
-    if (grow) issue_row_gates(grow, row0, S, gates_lds);
+    if (!RAGGED && grow) issue_row_gates(grow, row0, S, gates_lds);
     Acc2 acc;
     zero_acc2(acc);
     if (row_end - row0 <= kTailRows) mfma_tail_loop3(acc, nw, P, Q, lds, row_end - row0);
@@ -344,7 +344,13 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
             RowStage<128> sh{patch, tid}, sa{patch + RowStage<128>::BYTES, tid}, sb{patch + 2 * RowStage<128>::BYTES, tid};
             // grow != NULL: H leaves as g H, g the gate of the row's slot (the down projection then yields
             // gated rows and the gradient of W_down finds its row operand ready); FA and FB are not scaled
-            const float2 gates = grow ? row_gates(gates_lds, wt.row + blk * 32 + r16) : make_float2(1.0f, 1.0f);
+            // (at ragged widths straight from memory: few windows hide the way through LDS, 2000 tokens top-4, 264 x 392, 16 experts 23.0 us, from
+            // memory 22.1; 3001 top-6, 1000 x 704, 64 experts, forward 184.1 and 182.6)
+            float2 gates = make_float2(1.0f, 1.0f);
+            if (grow) {
+                if constexpr (RAGGED) gates = make_float2(grow[min(brow + r16, S - 1)], grow[min(brow + 16 + r16, S - 1)]);
+                else gates = row_gates(gates_lds, wt.row + blk * 32 + r16);
+            }
 #pragma unroll
             for (int t = 0; t < 2; ++t) {
                 const int tq = 2 * blk + t, q = 16 * t + r16;

@@ -25,6 +25,11 @@ extern "C" {
  * r3_profile_read waits for the recorded events and returns the summed
  * duration in milliseconds and the number of launches of kernel `tag`
  * (0 <= tag < r3_profile_tags()); r3_profile_name names it.
+ * A launch that does the work of several kernels counts under one name: in the
+ * backward of f32 layers whose widths are multiples of four, after
+ * r3_moe_forward, the parts of dW_r under ffn_dh, and dXp, dW_gate, dW_up and
+ * the router's last step under ffn_wgrad_down; ffn_dxp and router_wgrad have
+ * no launches there.
  */
 int r3_profile_enable(int on);
 int r3_profile_tags(void);

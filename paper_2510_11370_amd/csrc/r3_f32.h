@@ -72,7 +72,6 @@ hipError_t f32_wgrads(int d, int E, int F, int T, int K, const int32_t *offsets,
                       const int32_t *dyperm, const float *xrows, const int32_t *xperm, const float *dA, const float *dB,
                       float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s);
 
-
 // The backward between the gate's (which leaves dz, dzrow and dYp = g dy) and dx_finish, for a forward that left H gated, so
 // that nothing but dH reads dYp and dXp may take its place: dH with the parts of dW_r, then dW_gate, dW_up, dW_down, dXp, dW_r,
 // dbias and W_r^T, two launches.

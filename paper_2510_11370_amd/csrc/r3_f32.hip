@@ -27,7 +27,8 @@ struct F32Cfg {
     static constexpr int BP = 32 * TP, BQ = 32 * TQ, PBYTES = BP * BK * 4, STAGE = (BP + BQ) * BK * 4;
     static constexpr int LOADS = TP + TQ;   // loads per wave and k-tile (a load of four waves is 4 KB)
 };
-typedef F32Cfg<2, 2, 2> F32Tile;     // 32 KB of LDS: five work-groups on a compute unit, which cover what is not prefetched
+typedef F32Cfg<2, 2, 2> F32Tile;     // 32 KB of LDS: five work-groups on a compute unit, which cover what is not prefetched (four where dH
+                                     // shares its grid with the parts of dW_r, whose padded tiles take 36 KB)
 typedef F32Cfg<1, 1, 4> F32Short;    // few tiles: four times as many, half the chain each, loads three k-tiles ahead (F32WgradOp: one)
 typedef F32Cfg<2, 1, 4> F32Short1;   // the same for the SwiGLU, whose P tile holds both weights
 
@@ -402,7 +403,7 @@ __device__ __forceinline__ void f32_wgrad_tile(int E, int T, int K, const int32_
 // Launches.  What does not wait for each other shares one: a layer of few tokens is a chain of launches, and a larger one
 // fills one kernel's last round of tiles with the next one's.  After the gate's backward:  dH and the parts of dW_r;  then all
 // weight gradients, dXp, and the router's last step.  T=256 d=128 E=8 K=2 F=256, forward + backward: 58 -> 52 us in four launches of the
-// backward instead of seven; T=2048 d=512 E=16 K=4 F=1024: 815 -> 767.
+// backward instead of seven; T=2048 d=512 E=16 K=4 F=1024: 815 -> 767 (747 with the weight gradients' loop as it is now).
 // ---------------------------------------------------------------------------
 template <class C, int MODE>
 __global__ void __launch_bounds__(C::NT) f32_rows_kernel(F32RowArgs a) {

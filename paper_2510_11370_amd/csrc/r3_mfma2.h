@@ -940,7 +940,8 @@ __device__ __forceinline__ void mfma_tail_loop3(Acc2 &acc, int nw, const POp &P,
 
 // The gates of a row tile's 256 rows travel like its operands, to 1 KB of LDS outside the windows, ahead of the first window:
 // read from memory in the epilogue they would be waited for there, behind the stores of the rows before them (the memory
-// counter runs in order).  A dword per lane, waves 0-3; rows past the last one of the batch read as zero.
+// counter runs in order).  A dword per lane, waves 0-3; rows past the last one of the batch read as zero.  (Not the SwiGLU's at ragged
+// widths, see there.)
 __device__ __forceinline__ void issue_row_gates(const float *grow, int row0, int S, const char *gates_lds) {
     const int w = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
     if (w >= kLoaderWaves) return;
@@ -1074,8 +1075,8 @@ struct RowTileLoop {
 };
 
 // Epilogue staging.  The MFMA result layout gives a lane 4 consecutive features of ONE row
-// per register quad, so direct stores are 16-byte pieces scattered over 32 rows per
-// instruction and the vector memory path spends more time on them than the tile spent on
+// per register quad, and the four lanes of a row 16 of them, so direct stores are pieces of 32 bytes (bf16; f32: 64)
+// on each of 16 rows per instruction and the vector memory path spends more time on them than the tile spent on
 // arithmetic.  Instead a wave drops a 32-row block into its private LDS patch (the stage
 // buffers are free by now) and stores it back out with consecutive lanes along a row:
 // full 128/256-byte row segments per instruction.  The same patch serves to bring in

@@ -310,7 +310,7 @@ struct F32WgradOp {
     int n, ld, K, next[R / 32];
     __device__ __forceinline__ void init(const float *m, const int32_t *perm_, int64_t nrows, int r0, int n_, int ld_, int K_, int col0,
                                          int wave_block) {
-        perm = perm_ + r0;
+        perm = GATHER ? perm_ + r0 : nullptr;
         n = n_; ld = ld_; K = K_;
         const int64_t first = GATHER ? 0 : (int64_t)r0 * ld;
         op.init(m + first + col0, (uint64_t)((GATHER ? nrows : n) * ld - col0) * 4, ld, wave_block);

@@ -9,7 +9,7 @@ ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libr3.so")
 SOURCES = ["r3_api.hip", "r3_route.hip", "r3_plain.hip", "r3_f32.hip", "r3_router.hip", "r3_gemm.hip", "r3_diag.hip", "r3_cache.hip", "r3_prof.hip"]
-HEADERS = ["r3_common.h", "r3_kernels.h", "r3_mfma.h", "r3_mfma2.h", "r3_topk.h", "r3_tiles.h", "r3_f32.h", "r3_plain_tiles.h", "r3_finish.h"]
+HEADERS = ["r3_common.h", "r3_kernels.h", "r3_mfma.h", "r3_mfma2.h", "r3_topk.h", "r3_tiles.h", "r3_f32.h", "r3_f32_split.h", "r3_plain_tiles.h", "r3_finish.h"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

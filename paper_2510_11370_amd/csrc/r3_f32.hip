@@ -1,6 +1,7 @@
 // The expert network of the f32 layer on the f32 matrix instruction (16x16x4), for widths that are multiples of four
 // (16-byte rows); all other widths and the bf16 layers without a matrix path have the tiles of r3_plain.hip.  Products and
-// sums are those of an f32 FMA chain, in the same order of k as there.
+// sums are those of an f32 FMA chain, in the same order of k as there.  Where there is work for larger tiles, most of it goes
+// to the bf16 instruction at f32 precision instead (r3_f32_split.h; the rule is at split_rows() below).
 //
 // What bounds it: the f32 matrix pipe, 256 FLOP per cycle and compute unit (157 TFLOP/s at 2.4 GHz); for layers of a few
 // hundred rows the chain of loads and MFMAs of one tile.  An operand tile (32 k) goes from memory straight to LDS, 1 KB per
@@ -12,6 +13,7 @@
 #include <type_traits>
 
 #include "r3_f32.h"
+#include "r3_f32_split.h"
 #include "r3_finish.h"
 #include "r3_kernels.h"
 #include "r3_mfma2.h"
@@ -31,6 +33,11 @@ typedef F32Cfg<2, 2, 2> F32Tile;     // 32 KB of LDS: five work-groups on a comp
                                      // shares its grid with the parts of dW_r, whose padded tiles take 36 KB)
 typedef F32Cfg<1, 1, 4> F32Short;    // few tiles: four times as many, half the chain each, loads three k-tiles ahead (F32WgradOp: one)
 typedef F32Cfg<2, 1, 4> F32Short1;   // the same for the SwiGLU, whose P tile holds both weights
+
+// 128 x 128 tiles on the bf16 instruction (r3_f32_split.h)
+struct F32Split {
+    static constexpr int NT = kSplitThreads, BP = kSplitTile, BQ = kSplitTile;
+};
 
 template <class C> using F32Acc = f32x4_t[C::TP][C::TQ];
 
@@ -184,6 +191,33 @@ struct F32RowArgs {
     float *out0, *out1, *out2;
 };
 
+// four consecutive features of a row of the result (SwiGLU: v of the gate's weight, w of the other's)
+template <int MODE>
+__device__ __forceinline__ void f32_rows_store(const F32RowArgs &g, int row, int c, float gate, float4 v, float4 w) {
+    const int64_t o = (int64_t)row * ((MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? g.F : g.d) + c;
+    if constexpr (MODE == PLAIN_FFN1) {
+        const float va[4] = {v.x, v.y, v.z, v.w}, vb[4] = {w.x, w.y, w.z, w.w};
+        float h[4], fa[4], fb[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            const float a = va[i], b = vb[i];
+            const float sg = sigmoidf_(a);
+            h[i] = gate * (a * sg * b);
+            fa[i] = b * sg * (1.0f + a * (1.0f - sg));
+            fb[i] = a * sg;
+        }
+        *(float4 *)(g.out0 + o) = make_float4(h[0], h[1], h[2], h[3]);
+        if (g.out1) *(float4 *)(g.out1 + o) = make_float4(fa[0], fa[1], fa[2], fa[3]);
+        if (g.out2) *(float4 *)(g.out2 + o) = make_float4(fb[0], fb[1], fb[2], fb[3]);
+    } else if constexpr (MODE == PLAIN_DH) {
+        const float4 a = *(const float4 *)(g.FA + o), b = *(const float4 *)(g.FB + o);
+        *(float4 *)(g.out0 + o) = make_float4(v.x * a.x, v.y * a.y, v.z * a.z, v.w * a.w);
+        *(float4 *)(g.out1 + o) = make_float4(v.x * b.x, v.y * b.y, v.z * b.z, v.w * b.w);
+    } else {
+        *(float4 *)(g.out0 + o) = v;
+    }
+}
+
 // one tile; `block` of f32_rows_grid()
 template <class C, int MODE>
 __device__ __forceinline__ void f32_rows_tile(const F32RowArgs &g, int block, char *lds) {
@@ -258,36 +292,87 @@ __device__ __forceinline__ void f32_rows_tile(const F32RowArgs &g, int block, ch
         const int q = wq * 16 * C::TQ + 16 * tq + (lane & 15);
         if (q >= rows) continue;
         const int row = t.row0 + q;
+        const f32x4_t *v = &acc[0][tq];
         if constexpr (MODE == PLAIN_FFN1) {
             const int f = p0 + 16 * wp + 4 * (lane >> 4);
             if (f >= F) continue;
-            const float gq = gates ? gates[perm[row]] : 1.0f;
-            float h[4], fa[4], fb[4];
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const float a = acc[0][tq][i], b = acc[1][tq][i];
-                const float sg = sigmoidf_(a);
-                h[i] = gq * (a * sg * b);
-                fa[i] = b * sg * (1.0f + a * (1.0f - sg));
-                fb[i] = a * sg;
-            }
-            const int64_t o = (int64_t)row * F + f;
-            *(float4 *)(out0 + o) = make_float4(h[0], h[1], h[2], h[3]);
-            if (out1) *(float4 *)(out1 + o) = make_float4(fa[0], fa[1], fa[2], fa[3]);
-            if (out2) *(float4 *)(out2 + o) = make_float4(fb[0], fb[1], fb[2], fb[3]);
+            const f32x4_t b = acc[1][tq];
+            f32_rows_store<MODE>(g, row, f, gates ? gates[perm[row]] : 1.0f, make_float4((*v)[0], (*v)[1], (*v)[2], (*v)[3]),
+                                 make_float4(b[0], b[1], b[2], b[3]));
         } else {
 #pragma unroll
             for (int tp = 0; tp < C::TP; ++tp) {
                 const int c = p0 + wp * 16 * C::TP + 16 * tp + 4 * (lane >> 4);
                 if (c >= NOUT) continue;
-                const int64_t o = (int64_t)row * NOUT + c;
-                const f32x4_t v = acc[tp][tq];
-                if constexpr (MODE == PLAIN_DH) {
-                    const float4 a = *(const float4 *)(FAin + o), b = *(const float4 *)(FBin + o);
-                    *(float4 *)(out0 + o) = make_float4(v[0] * a.x, v[1] * a.y, v[2] * a.z, v[3] * a.w);
-                    *(float4 *)(out1 + o) = make_float4(v[0] * b.x, v[1] * b.y, v[2] * b.z, v[3] * b.w);
-                } else {
-                    *(float4 *)(out0 + o) = make_float4(v[0], v[1], v[2], v[3]);
+                const f32x4_t r = acc[tp][tq];
+                f32_rows_store<MODE>(g, row, c, 1.0f, make_float4(r[0], r[1], r[2], r[3]), float4());
+            }
+        }
+    }
+}
+
+// the same with a split tile
+template <int MODE>
+__device__ __forceinline__ void split_rows_tile(const F32RowArgs &g, int block, char *lds) {
+    constexpr int BP = kSplitTile, BQ = kSplitTile, BF = MODE == PLAIN_FFN1 ? BP / 2 : BP;
+    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? g.F : g.d;
+    const int KK = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? g.d : g.F;
+    const RowTile t = find_row_tile<true>(g.offsets, g.E, BQ, block, (NOUT + BF - 1) / BF);
+    if (t.e < 0) return;
+    const int p0 = t.col * BF, rows = t.row1 - t.row0, nk = (KK + 31) / 32;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wp = wave & 1, wq = wave >> 1, u = threadIdx.x & 127;
+    const int64_t we = (int64_t)t.e * g.d * g.F;
+    const uint64_t wbytes = (uint64_t)g.d * g.F * 4;
+
+    const bool gather = MODE == PLAIN_FFN1 && g.perm;
+    SplitRows Q;
+    Q.init(gather ? g.in0 : g.in0 + (int64_t)t.row0 * KK, gather ? (uint64_t)g.T * KK * 4 : (uint64_t)rows * KK * 4, KK, u);
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const int r = min(SplitRows::row(u, i), rows - 1);
+        Q.set_row(i, gather ? g.perm[t.row0 + r] / g.K : r);
+    }
+    SplitAcc acc;
+    split_zero(acc);
+    if constexpr (MODE == PLAIN_FFN1) {
+        SplitCols<true> P;   // the same features of both weights, so that a lane holds both pre-activations
+        P.init((wave == 0 ? g.W0 : g.W1) + we + p0, wbytes - p0 * 4u, g.F, u);
+        split_loop(acc, nk, P, Q, lds, 32 * wp, 64 + 32 * wp, 64 * wq);
+    } else if constexpr (MODE == PLAIN_DOWN) {
+        SplitCols<false> P;
+        P.init(g.W0 + we + p0, wbytes - p0 * 4u, g.d, u);
+        split_loop(acc, nk, P, Q, lds, 64 * wp, 64 * wp + 32, 64 * wq);
+    } else {
+        SplitRows P;
+        const uint64_t pbytes = (uint64_t)(NOUT - p0) * KK * 4;
+        P.init(g.W0 + we + (int64_t)p0 * KK, pbytes, KK, u);
+#pragma unroll
+        for (int i = 0; i < 4; ++i) P.set_row(i, min(SplitRows::row(u, i), NOUT - p0 - 1));
+        if constexpr (MODE == PLAIN_DH) {
+            split_loop(acc, nk, P, Q, lds, 64 * wp, 64 * wp + 32, 64 * wq);
+        } else {   // one reduction over both halves: dA Wg^T, then dB Wu^T
+            const SplitPair<SplitRows> P2{P, Src{(const char *)(g.W1 + we + (int64_t)p0 * KK), pbytes, 128}, nk};
+            const SplitPair<SplitRows> Q2{Q, Src{(const char *)(g.in1 + (int64_t)t.row0 * KK), Q.src.nbytes, 128}, nk};
+            split_loop(acc, 2 * nk, P2, Q2, lds, 64 * wp, 64 * wp + 32, 64 * wq);
+        }
+    }
+#pragma unroll
+    for (int tq = 0; tq < 2; ++tq) {
+        const int q = 64 * wq + 32 * tq + (lane & 31), row = t.row0 + q;
+        if (q >= rows) continue;
+        const float gate = MODE == PLAIN_FFN1 && g.gates ? g.gates[g.perm[row]] : 1.0f;
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const int f = 8 * k + 4 * (lane >> 5);
+            auto quad = [&](int tp) { return make_float4(acc[tp][tq][4 * k], acc[tp][tq][4 * k + 1], acc[tp][tq][4 * k + 2], acc[tp][tq][4 * k + 3]); };
+            if constexpr (MODE == PLAIN_FFN1) {
+                const int c = p0 + 32 * wp + f;
+                if (c < NOUT) f32_rows_store<MODE>(g, row, c, gate, quad(0), quad(1));
+            } else {
+#pragma unroll
+                for (int tp = 0; tp < 2; ++tp) {
+                    const int c = p0 + 64 * wp + 32 * tp + f;
+                    if (c < NOUT) f32_rows_store<MODE>(g, row, c, 1.0f, quad(tp), float4());
                 }
             }
         }
@@ -399,46 +484,116 @@ __device__ __forceinline__ void f32_wgrad_tile(int E, int T, int K, const int32_
     }
 }
 
+__device__ __forceinline__ void split_wgrad_tile(int E, int T, int K, const int32_t *__restrict__ offsets, const F32Wgrad3 &all,
+                                                 int accumulate, int block, char *lds) {
+    const int per = all.g[0].tiles + all.g[1].tiles + all.g[2].tiles;
+    const int e = block / per, t0 = all.g[0].tiles, t1 = t0 + all.g[1].tiles;
+    int rem = block - e * per;
+    const F32Wgrad g = rem < t0 ? all.g[0] : rem < t1 ? all.g[1] : all.g[2];
+    rem -= rem < t0 ? 0 : rem < t1 ? t0 : t1;
+    const int npt = (g.NP + kSplitTile - 1) / kSplitTile;
+    const int qt = rem / npt, q0 = qt * kSplitTile, p0 = (rem - qt * npt) * kSplitTile;
+    const int r0 = offsets[e], n = offsets[e + 1] - r0;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wp = wave & 1, wq = wave >> 1, u = threadIdx.x & 127;
+    SplitAcc acc;
+    split_zero(acc);
+    auto plain = [&](const float *m, int ld, int col0) {
+        SplitCols<false> op;
+        op.init(m + (int64_t)r0 * ld + col0, (uint64_t)((int64_t)n * ld - col0) * 4, ld, u);
+        return op;
+    };
+    auto gathered = [&](const float *m, int ld, int col0, const int32_t *perm) {
+        SplitGather op;
+        op.init(m + col0, (uint64_t)((int64_t)T * ld - col0) * 4, ld, u, perm + r0, n, K);
+        return op;
+    };
+    const int nk = (n + 31) / 32;
+    if (n > 0) {
+        if (g.pperm) split_loop(acc, nk, gathered(g.Ps, g.NP, p0, g.pperm), plain(g.Qs, g.NQ, q0), lds, 64 * wp, 64 * wp + 32, 64 * wq);
+        else if (g.qperm) split_loop(acc, nk, plain(g.Ps, g.NP, p0), gathered(g.Qs, g.NQ, q0, g.qperm), lds, 64 * wp, 64 * wp + 32, 64 * wq);
+        else split_loop(acc, nk, plain(g.Ps, g.NP, p0), plain(g.Qs, g.NQ, q0), lds, 64 * wp, 64 * wp + 32, 64 * wq);
+    }
+    float *o = g.out + (int64_t)e * g.NQ * g.NP;
+#pragma unroll
+    for (int tq = 0; tq < 2; ++tq) {
+        const int q = q0 + 64 * wq + 32 * tq + (lane & 31);
+        if (q >= g.NQ) continue;
+#pragma unroll
+        for (int tp = 0; tp < 2; ++tp)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const int p = p0 + 64 * wp + 32 * tp + 8 * k + 4 * (lane >> 5);
+                if (p >= g.NP) continue;
+                float4 *at = (float4 *)(o + (int64_t)q * g.NP + p);
+                float4 v = make_float4(acc[tp][tq][4 * k], acc[tp][tq][4 * k + 1], acc[tp][tq][4 * k + 2], acc[tp][tq][4 * k + 3]);
+                if (accumulate) {
+                    const float4 old = *at;
+                    v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
+                }
+                *at = v;
+            }
+    }
+}
+
+// either kind of tile
+template <class C> constexpr bool kIsSplit = std::is_same<C, F32Split>::value;
+template <class C> constexpr int tile_lds() {
+    if constexpr (kIsSplit<C>) return kSplitLds;
+    else return C::NST * C::STAGE;
+}
+template <class C, int MODE>
+__device__ __forceinline__ void rows_tile(const F32RowArgs &a, int block, char *lds) {
+    if constexpr (kIsSplit<C>) split_rows_tile<MODE>(a, block, lds);
+    else f32_rows_tile<C, MODE>(a, block, lds);
+}
+template <class C>
+__device__ __forceinline__ void wgrad_tile(int E, int T, int K, const int32_t *__restrict__ offsets, const F32Wgrad3 &all, int accumulate,
+                                           int block, char *lds) {
+    if constexpr (kIsSplit<C>) split_wgrad_tile(E, T, K, offsets, all, accumulate, block, lds);
+    else f32_wgrad_tile<C>(E, T, K, offsets, all, accumulate, block, lds);
+}
+template <class C> constexpr int kMinWaves = kIsSplit<C> ? kSplitMinWaves : 1;
+
 // ---------------------------------------------------------------------------
 // Launches.  What does not wait for each other shares one: a layer of few tokens is a chain of launches, and a larger one
 // fills one kernel's last round of tiles with the next one's.  After the gate's backward:  dH and the parts of dW_r;  then all
 // weight gradients, dXp, and the router's last step.  T=256 d=128 E=8 K=2 F=256, forward + backward: 58 -> 52 us in four launches of the
-// backward instead of seven; T=2048 d=512 E=16 K=4 F=1024: 815 -> 767 (747 with the weight gradients' loop as it is now).
+// backward instead of seven; T=2048 d=512 E=16 K=4 F=1024: 815 -> 767 (595 with split tiles and the loops as they are now).
 // ---------------------------------------------------------------------------
 template <class C, int MODE>
-__global__ void __launch_bounds__(C::NT) f32_rows_kernel(F32RowArgs a) {
-    __shared__ __attribute__((aligned(1024))) char lds[C::NST * C::STAGE];
-    f32_rows_tile<C, MODE>(a, blockIdx.x, lds);
+__global__ void __launch_bounds__(C::NT, kMinWaves<C>) f32_rows_kernel(F32RowArgs a) {
+    __shared__ __attribute__((aligned(1024))) char lds[tile_lds<C>()];
+    rows_tile<C, MODE>(a, blockIdx.x, lds);
 }
 
 template <class C>
-__global__ void __launch_bounds__(C::NT)
+__global__ void __launch_bounds__(C::NT, kMinWaves<C>)
 f32_wgrad_kernel(int E, int T, int K, const int32_t *__restrict__ offsets, F32Wgrad3 all, int accumulate) {
-    __shared__ __attribute__((aligned(1024))) char lds[C::NST * C::STAGE];
-    f32_wgrad_tile<C>(E, T, K, offsets, all, accumulate, blockIdx.x, lds);
+    __shared__ __attribute__((aligned(1024))) char lds[tile_lds<C>()];
+    wgrad_tile<C>(E, T, K, offsets, all, accumulate, blockIdx.x, lds);
 }
 
 constexpr int max_int(int a, int b) { return a > b ? a : b; }
 
 // the first `first` blocks (a multiple of 8, so that the rows' tiles keep their XCDs): parts of dW_r; then dH
 template <class C, typename IdxT>
-__global__ void __launch_bounds__(C::NT) f32_dh_dwr_kernel(F32RowArgs a, PlainDwr<float, IdxT> w, int nw, int first) {
-    __shared__ __attribute__((aligned(1024))) char lds[max_int(C::NST * C::STAGE, PlainSmall::LDS)];
+__global__ void __launch_bounds__(C::NT, kMinWaves<C>) f32_dh_dwr_kernel(F32RowArgs a, PlainDwr<float, IdxT> w, int nw, int first) {
+    __shared__ __attribute__((aligned(1024))) char lds[max_int(tile_lds<C>(), PlainSmall::LDS)];
     const int b = blockIdx.x;
-    if (b >= first) f32_rows_tile<C, PLAIN_DH>(a, b - first, lds);
+    if (b >= first) rows_tile<C, PLAIN_DH>(a, b - first, lds);
     else if (b < nw) plain_dwr_tile<PlainSmall, float, true>(w, b, lds);
 }
 
 // [0, first): the router's last step (its dbias of a hot expert is a long chain); [first, second): dXp; then the weight gradients
 template <class CR, class CW>
-__global__ void __launch_bounds__(CR::NT)
+__global__ void __launch_bounds__(CR::NT, max_int(kMinWaves<CR>, kMinWaves<CW>))
 f32_grads_kernel(F32RowArgs a, int E, int T, int K, const int32_t *__restrict__ offsets, F32Wgrad3 all, int accumulate,
                  RouterFinish<float> fin, int nfin, int first, int second) {
-    __shared__ __attribute__((aligned(1024))) char lds[max_int(CR::NST * CR::STAGE, CW::NST * CW::STAGE)];
+    __shared__ __attribute__((aligned(1024))) char lds[max_int(tile_lds<CR>(), tile_lds<CW>())];
     static_assert(sizeof(RouterFinishLds<float>) <= sizeof(lds), "");
     const int b = blockIdx.x;
-    if (b >= second) f32_wgrad_tile<CW>(E, T, K, offsets, all, accumulate, b - second, lds);
-    else if (b >= first) f32_rows_tile<CR, PLAIN_DXP>(a, b - first, lds);
+    if (b >= second) wgrad_tile<CW>(E, T, K, offsets, all, accumulate, b - second, lds);
+    else if (b >= first) rows_tile<CR, PLAIN_DXP>(a, b - first, lds);
     else if (b < nfin) router_finish_block<CR::NT>(fin, b, *(RouterFinishLds<float> *)lds);
 }
 
@@ -453,6 +608,26 @@ constexpr int kRowsFill = 512;
 // 137.4 | 125.0; 2048 top-2, 256 x 256, 5 experts (240) 118.7 | 108.4; 4096 top-1, 192 x 256 (288) 100.0 | 95.4; 3000 top-2, 320 x 320, 4 experts (300)
 // 190.7 | 184.3; 4096 top-2, 256 x 256 (384) 161.3 | 166.2; 300 top-2, 512 x 320, 4 experts (480) 65.5 | 67.6.
 constexpr int kWgradFill = 320;
+
+// Split tiles.  SwiGLU: wherever there are not few tiles (us, 64 x 64 | split, 2048 tokens top-4, 512 x 1024, 16 experts 174 | 137, 4096 top-4,
+// 512 x 512, 128 experts 208 | 167, 1024 top-2, 512 x 512, 8 experts 34.8 | 33.4).
+// Down projection (and dXp in a launch of its own): 2 M results and more, 128 rows per expert, a quarter of the tiles' columns dead at
+// most: 4096 top-2, 512 x 512, 8 experts (4 M) 50 | 45, 1024 top-4, 512 x 1024, 16 experts (2 M) 56.6 | 53.5, 4096 top-4, 512 x 512, 128 experts
+// 98 | 82; 512 top-2, 512 x 512, 8 experts (.5 M) 12.9 | 26.6; 64 rows per expert 34.2 | 35.9; 132 columns of 256 15.7 | 18.9.
+// dH stays with the others: 16 k-tiles and two operands beside the result, 94 | 104.
+// The weight gradients: one tile per compute unit and more, with the same allowance.  3 x 8 experts: 4096 tokens top-2, 320 x 320 (150 tiles' worth)
+// 97 | 116, 256 x 1024 (384) 230 | 185, 1024 top-2, 512 x 512 (384) 71 | 66, 32 rows per expert 483 | 487.  With them dXp from .9 M results on,
+// split beside small tiles: 1500 top-1, 640 columns, 5 experts (.96 M) 102 | 109, 2048 top-4, 512, 128 experts 292 | 327, 300 top-2, 1024, 5 experts (.6 M)
+// 102 | 78.
+constexpr int64_t kSplitDown = 1 << 21, kSplitDxp = 900000;
+int64_t split_columns(int n) { return (n + kSplitTile - 1) / kSplitTile * kSplitTile; }
+bool split_rows(int S, int E, int NOUT) {
+    return (int64_t)S * NOUT >= kSplitDown && S >= 128 * (int64_t)E && 4 * (int64_t)NOUT >= 3 * split_columns(NOUT);
+}
+bool split_wgrads(int E, int d, int F) {
+    const int64_t n = (int64_t)d * F;
+    return 3 * E * n >= 256ll * kSplitTile * kSplitTile && 4 * n >= 3 * split_columns(d) * split_columns(F);
+}
 
 template <class C, int MODE>
 int rows_blocks(int S, const F32RowArgs &a) {
@@ -471,7 +646,10 @@ template <int MODE>
 void rows_by_size(int S, const F32RowArgs &a, hipStream_t s) {
     const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? a.F : a.d;
     typedef typename std::conditional<MODE == PLAIN_FFN1, F32Short1, F32Short>::type Short;
-    auto f = few_row_tiles(S, a.E, NOUT, MODE == PLAIN_FFN1 ? 32 : 64) ? rows_launch<Short, MODE> : rows_launch<F32Tile, MODE>;
+    typedef typename std::conditional<MODE == PLAIN_FFN1, F32Split, F32Tile>::type Tile;
+    auto f = few_row_tiles(S, a.E, NOUT, MODE == PLAIN_FFN1 ? 32 : 64) ? rows_launch<Short, MODE> : rows_launch<Tile, MODE>;
+    if constexpr (MODE == PLAIN_DOWN || MODE == PLAIN_DXP)
+        if (split_rows(S, a.E, a.d)) f = rows_launch<F32Split, MODE>;
     f(S, a, s);
 }
 
@@ -519,7 +697,7 @@ hipError_t f32_rows(int mode, int S, int d, int E, int F, const int32_t *offsets
 hipError_t f32_wgrads(int d, int E, int F, int T, int K, const int32_t *offsets, const float *H, const float *dYrows,
                       const int32_t *dyperm, const float *xrows, const int32_t *xperm, const float *dA, const float *dB,
                       float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s) {
-    auto f = few_wgrad_tiles(E, d, F) ? wgrad_launch<F32Short> : wgrad_launch<F32Tile>;
+    auto f = split_wgrads(E, d, F) ? wgrad_launch<F32Split> : few_wgrad_tiles(E, d, F) ? wgrad_launch<F32Short> : wgrad_launch<F32Tile>;
     f(E, T, K, offsets, wgrad_args(d, F, H, dYrows, dyperm, xrows, xperm, dA, dB, dWg, dWu, dWd), accumulate, s);
     return hipGetLastError();
 }
@@ -550,8 +728,9 @@ hipError_t f32_backward(const F32Backward &b, hipStream_t s) {
     const int rows = plain_dwr_rows(b.T, b.d, b.E);
     const int nfin = fin.fill<F32Tile::NT>(b.d, b.E, (b.T + rows - 1) / rows, b.accumulate, b.dzrow, b.part, b.offsets, b.dbias, b.dWr, b.Wr, b.WrT);
     const bool fr = few_row_tiles(b.S, b.E, b.d, 64), fw = few_wgrad_tiles(b.E, b.d, b.F);
-    auto f = fr ? (fw ? grads_launch<F32Short, F32Short> : grads_launch<F32Short, F32Tile>)
-                : (fw ? grads_launch<F32Tile, F32Short> : grads_launch<F32Tile, F32Tile>);
+    auto f = split_wgrads(b.E, b.d, b.F) ? ((int64_t)b.S * b.d >= kSplitDxp ? grads_launch<F32Split, F32Split> : grads_launch<F32Short, F32Split>)
+             : fr ? (fw ? grads_launch<F32Short, F32Short> : grads_launch<F32Short, F32Tile>)
+                  : (fw ? grads_launch<F32Tile, F32Short> : grads_launch<F32Tile, F32Tile>);
     f(b.S, a, b.T, b.K, b.offsets, all, b.accumulate, fin, nfin, s);
     return hipGetLastError();
 }

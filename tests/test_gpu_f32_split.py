@@ -1,0 +1,89 @@
+"""The f32 contractions on the bf16 matrix instruction (three bf16 of every value, 128 x 128 tiles): at ragged edges against the oracle, and
+where the sum of three bf16 is not the value (infinities, NaN, values that round to an infinity, values near the smallest
+numbers), against the same product in float64."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import sparse
+from paper_2510_11370_amd import r3, synth
+from util import Case, assert_close, host
+
+pytestmark = pytest.mark.gpu
+SH = synth.LayerShape
+# every launch of both directions but dH takes split tiles here: cut on every side, a few hundred to two thousand rows an expert
+SPLIT = SH(T=2201, d=500, E=5, K=2, F=580, act="f32", sigma=0.05, zipf_s=0.8, seed=131)
+
+
+def run(c, calls, dy):
+    w = (c.t["Wg"], c.t["Wu"], c.t["Wd"])
+    buf = r3.LayerBuffers(c.D, backward=True, gathered_copy=calls == "copy")
+    forward = r3.forward_one_call if calls == "one" else r3.forward
+    forward(buf, c.t["x"], c.t["Wr"], c.t["idx"], *w, bias=c.t["bias"])
+    r3.backward(buf, dy, c.t["x"], c.t["Wr"], c.t["idx"], *w)
+    torch.cuda.synchronize()
+    return buf
+
+
+def dW_down_64(c, buf, dy):
+    """From the H that the layer left (gated by the one-call forward)."""
+    off = buf.offsets.tolist()
+    tok = buf.perm.long() // c.D.K
+    assert buf.gated
+    return torch.stack([buf.H[a:b].double().T @ dy[tok[a:b]].double() for a, b in zip(off, off[1:])])
+
+
+@pytest.mark.parametrize("calls", ["one", "steps", "copy"])
+@pytest.mark.parametrize("sh", [SPLIT, SH(T=4100, d=260, E=40, K=2, F=1028, act="f32", sigma=0.05, zipf_s=1.2, seed=132)],   # SwiGLU and gradients only, experts of few rows
+                         ids=lambda s: "T%d_d%d_F%d_E%d" % (s.T, s.d, s.F, s.E))
+def test_layer(sh, calls):
+    c = Case(sh, backward=True, scale_w=5.0)
+    n = c.np
+    fwd = sparse.forward(n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], n["bias"])
+    ref = sparse.backward(n["dy"], n["x"], n["Wr"], c.idx, n["Wg"], n["Wu"], n["Wd"], fwd)
+    buf = run(c, calls, c.t["dy"])
+    # f32 sums of up to 2000 terms, up to three in a row: an f32 FMA chain leaves 1e-6 of the norm here, 4e-6 is four times that
+    for got, want in ((buf.y, fwd["y"]), (buf.dx, ref["dx"]), (buf.dW_gate, ref["dWg"]), (buf.dW_up, ref["dWu"]), (buf.dW_down, ref["dWd"])):
+        got = host(got).astype(np.float64)
+        assert np.linalg.norm(got - want) <= 4e-6 * np.linalg.norm(want)
+    assert_close(host(buf.y), fwd["y"], "y", c.rel)
+    assert_close(host(buf.dx), ref["dx"], "dx", c.rel)
+
+
+@pytest.mark.parametrize("what", ["inf", "-inf", "nan", "rounds_to_inf", "tiny", "zero"])
+def test_where_three_bf16_are_not_the_value(what):
+    c = Case(SPLIT, backward=True, scale_w=1.0)
+    dy = c.t["dy"].clone()
+    if what == "tiny":
+        dy *= 2.0 ** -122
+    elif what == "zero":
+        dy.zero_()
+    else:
+        dy[7, 3] = {"inf": np.inf, "-inf": -np.inf, "nan": np.nan, "rounds_to_inf": 3.4e38}[what]
+    buf = run(c, "one", dy)
+    got, want = buf.dW_down.double(), dW_down_64(c, buf, dy).float().double()
+    assert torch.equal(got.isnan(), want.isnan())
+    assert torch.equal(got.isinf(), want.isinf()) and torch.equal(got[got.isinf()], want[want.isinf()])
+    if what in ("inf", "-inf", "nan"):
+        assert not want.isfinite().all()
+    f = want.isfinite()
+    big = f & (want.abs() > 1e30)
+    assert big.any() == (what == "rounds_to_inf")
+    for part in (big, f & ~big):
+        # an f32 chain of up to 2000 products: 1e-5 of the norm has room for all of its roundings, also those below 2^-126
+        assert (got - want)[part].norm() <= 1e-5 * want[part].norm()
+
+
+def test_nan_stays_with_its_token():
+    c = Case(SPLIT, backward=True, scale_w=1.0)
+    clean = run(c, "one", c.t["dy"]).y.clone()
+    x = c.t["x"].clone()
+    x[11, 5], x[900, 0] = np.nan, np.inf
+    buf = r3.LayerBuffers(c.D, backward=False, gathered_copy=False)
+    r3.forward_one_call(buf, x, c.t["Wr"], c.t["idx"], c.t["Wg"], c.t["Wu"], c.t["Wd"], bias=c.t["bias"])
+    torch.cuda.synchronize()
+    hit = torch.zeros(SPLIT.T, dtype=torch.bool, device="cuda")
+    hit[[11, 900]] = True
+    assert not buf.y[hit].isfinite().any()
+    # the other rows of these tiles are multiplied by the f32 instruction then: another order of roundings
+    assert (buf.y[~hit] - clean[~hit]).norm() <= 4e-6 * clean[~hit].norm()

@@ -29,7 +29,9 @@ extern "C" {
  * backward of f32 layers whose widths are multiples of four, after
  * r3_moe_forward, the parts of dW_r under ffn_dh, and dXp, dW_gate, dW_up and
  * the router's last step under ffn_wgrad_down; ffn_dxp and router_wgrad have
- * no launches there.
+ * no launches there.  In the backward of bf16 layers dW_down under ffn_dh and
+ * dXp under ffn_wgrad_gate_up where they share a launch (less than some 12000
+ * tokens of the 2048 x 768 layer).
  */
 int r3_profile_enable(int on);
 int r3_profile_tags(void);

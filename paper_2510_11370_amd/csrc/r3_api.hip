@@ -355,19 +355,13 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
         const int split = mfma_wgrad_split_rows(m.S, ((m.F + 255) / 256) * ((m.d + 255) / 256), (size_t)m.S * m.d * m.eb, slot_bytes);
         if (mfma_build_tiles_and_row_tokens(m.E, offsets, tiles, split, S, m.K, inv_perm, gates, tok, grow, s) != hipSuccess)
             return R3_ERR_HIP;
-        if (mfma_ffn_dh(m.S, m.d, m.E, m.F, dy, tok, m.T, grow, offsets, tiles, W_down, FA, FB, H, dA, dB, Hg, wpart,
-                        s) != hipSuccess)
-            return R3_ERR_HIP;
-        if (launch_gate_backward_parts(m.T, m.K, row_parts(m), wpart, gates, inv_perm, dz, dzrow, s) != hipSuccess)
-            return R3_ERR_HIP;
-        if (mfma_wgrad(m.E, m.F, m.d, gated ? H : Hg, dy, tok, m.T, tiles, 2, dW_down, split ? (float *)dXp : nullptr,
-                       accumulate, s) != hipSuccess)
-            return R3_ERR_HIP;
-        if (mfma_wgrad_pair(m.E, m.d, m.F, Xp ? Xp : x, Xp ? nullptr : tok, m.T, dA, dB, tiles, 3, dW_gate, dW_up,
-                            split ? (float *)dXp : nullptr, accumulate, s) != hipSuccess)
-            return R3_ERR_HIP;
-        if (mfma_ffn_dxp(m.S, m.d, m.E, m.F, dA, dB, offsets, tiles, W_gate, W_up, dXp, s) != hipSuccess)
-            return R3_ERR_HIP;
+        FfnBackward b = {};
+        b.S = m.S; b.T = m.T; b.d = m.d; b.E = m.E; b.F = m.F; b.K = m.K; b.accumulate = accumulate; b.row_parts = row_parts(m);
+        b.offsets = offsets; b.tiles = tiles; b.tok = tok; b.inv_perm = inv_perm; b.grow = grow; b.gates = gates;
+        b.dy = dy; b.x = x; b.Xp = Xp; b.FA = FA; b.FB = FB; b.H = H; b.Wg = W_gate; b.Wu = W_up; b.Wd = W_down;
+        b.dA = dA; b.dB = dB; b.Hg = Hg; b.dXp = dXp; b.wpart = wpart; b.dz = dz; b.dzrow = dzrow; b.part = split ? (float *)dXp : nullptr;
+        b.dWg = dW_gate; b.dWu = dW_up; b.dWd = dW_down;
+        if (mfma_ffn_backward(b, s) != hipSuccess) return R3_ERR_HIP;
     } else {
         // combine and masked softmax:  dYp = g*dy per slot, dz
         void *dYp = dXp;  // dYp is dead once dW_down and dH are done

@@ -411,14 +411,13 @@ ffn1_kernel(int S, int d, int F, const bf16_t *__restrict__ Xp, const int32_t *_
 //         (two-phase reduction: first F over (dA, Wg), then F over (dB, Wu))
 // ---------------------------------------------------------------------------
 template <int MODE, bool GATED, bool RAGGED>
-__global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
-rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t *__restrict__ Q1,
+__device__ __forceinline__ void
+rowgemm_tiles(char *lds, int4 *qstash, char *gates_lds, int *mailbox, int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t *__restrict__ Q1,
                const int32_t *__restrict__ offsets, const int32_t *__restrict__ tiles,
                const bf16_t *__restrict__ W0, const bf16_t *__restrict__ W1, const bf16_t *__restrict__ FA,
                const bf16_t *__restrict__ FB, bf16_t *__restrict__ out0, bf16_t *__restrict__ out1,
                const int32_t *__restrict__ tok, int T, const float *__restrict__ grow,
                const bf16_t *__restrict__ Hs, bf16_t *__restrict__ out2, float *__restrict__ wpart, int stream) {
-    __shared__ __attribute__((aligned(1024))) char lds[kRowLds];   // one piece: a tail tile lays it out differently
     char *const bufA = lds, *const bufB = lds + kSuperBytes;
     char *const s0 = bufA, *const s1 = bufA + kStageBytes, *const s2 = bufB, *const s3 = bufB + kStageBytes;
     const int NOUT = (MODE == 1) ? F : d;  // width of the output
@@ -429,8 +428,7 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     const int wp0 = (threadIdx.x >> 6) % kWP2, wq0 = (threadIdx.x >> 6) / kWP2;
     // operand forms: the weights are feature-contiguous (TR) for MODE 0, K-contiguous otherwise
     typedef typename std::conditional<MODE == 0, OpTR256<!RAGGED>, OpKC64<false, false, !RAGGED, RAGGED>>::type POp;
-    constexpr bool GATHER = MODE == 1;     // Q rows through the row -> token list
-    __shared__ int4 qstash[GATHER ? 2 * 256 : 1];   // the gathered rows' offsets (no registers to spare for them)
+    constexpr bool GATHER = MODE == 1;     // Q rows through the row -> token list (their offsets in qstash: no registers to spare for them)
     POp P;
     OpKC64<GATHER, GATHER, false, RAGGED> Q;
     if constexpr (MODE == 0) {
@@ -443,8 +441,6 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
     Q.init(KQ * 2, kWaveRowsQ * wq0, qstash);
     if constexpr (MODE == 2) Q.wswitch = nwk;
     if constexpr (RAGGED) Q.set_tail(KQ);
-    __shared__ int mailbox[2];
-    __shared__ __attribute__((aligned(256))) char gates_lds[MODE == 1 ? 4 * kTile : 4];
     RowTileLoop tl(tiles + kTileX, npt, tile_counters(tiles, MODE == 1 ? 0 : 1));
     struct Tile {
         int e, row0, row_end, p0;
@@ -654,17 +650,12 @@ rowgemm_kernel(int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t 
 // ---------------------------------------------------------------------------
 // GATHER: Ps is the un-permuted matrix [nrows, NPd] and row r of the reduction is its row tok[r]
 // (dW_down = Hg^T dy straight from the upstream gradient: no per-slot copy of dy is read).
-template <bool GATHER, bool RAGGED>
-__global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
-wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__restrict__ Ps,
+// LATE: its work-groups come from other tiles, at different times (TileLoop::join)
+template <bool GATHER, bool RAGGED, bool LATE>
+__device__ __forceinline__ void
+wgrad_tiles(char *s0, char *s1, char *s2, char *s3, char *ring, int *mailbox, int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__restrict__ Ps,
              const int32_t *__restrict__ tok, int nrows, const int32_t *__restrict__ tiles,
              float *__restrict__ out, float *__restrict__ part, int accumulate, int *ctr) {
-    __shared__ __attribute__((aligned(1024))) char s0[kStageBytes];
-    __shared__ __attribute__((aligned(1024))) char s1[kStageBytes];
-    __shared__ __attribute__((aligned(1024))) char s2[kStageBytes];
-    __shared__ __attribute__((aligned(1024))) char s3[kStageBytes];
-    __shared__ int mailbox[2];
-    __shared__ __attribute__((aligned(256))) char ring[GATHER ? kIndexRingBytes : 16];
     const int nqt = RAGGED ? (NQd + kTile - 1) / kTile : NQd / kTile, npt = RAGGED ? (NPd + kTile - 1) / kTile : NPd / kTile;
     const int wp0 = (threadIdx.x >> 6) % kWP2, wq0 = (threadIdx.x >> 6) / kWP2;
     // operands are set up once; a tile only moves their source windows (column offset included)
@@ -678,6 +669,7 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
     Q.init(NQd * 2, 0, kWaveRowsQ * wq0);
     // tiles of one reduction segment (an expert's rows, or one part of them) are neighbours in the list
     TileLoop tl(tiles[1] * nqt * npt, ctr);
+    if constexpr (LATE) tl.join(mailbox + 2);
     for (int slot = tl.first(), next = tl.second(); tl.valid(slot);) {
     const int id = tl.id(slot);
     const int eo = id / (nqt * npt);
@@ -731,7 +723,7 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
         tl.prefetch();
     }
     const int after = tl.finish(mailbox);
-    slot = next;
+    slot = LATE ? after : next;
     next = after;
     }
 }
@@ -745,18 +737,12 @@ wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__re
 // ---------------------------------------------------------------------------
 // GATHER: Qs is the un-permuted matrix [nrows, NQd] and row r of the reduction is its row tok[r]
 // (dW_gate, dW_up straight from x: no gathered copy of the tokens is read).
-template <bool GATHER, bool RAGGED>
-__global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
-wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t *__restrict__ tok, int nrows,
+template <bool GATHER, bool RAGGED, bool LATE>
+__device__ __forceinline__ void
+wgrad_pair_tiles(char *s0, char *s1, char *s2, char *s3, char *ring, int *mailbox, int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t *__restrict__ tok, int nrows,
                   const bf16_t *__restrict__ P0, const bf16_t *__restrict__ P1, const int32_t *__restrict__ tiles,
                   float *__restrict__ out0, float *__restrict__ out1, float *__restrict__ part0,
                   float *__restrict__ part1, int accumulate, int *ctr) {
-    __shared__ __attribute__((aligned(1024))) char s0[kStageBytes];
-    __shared__ __attribute__((aligned(1024))) char s1[kStageBytes];
-    __shared__ __attribute__((aligned(1024))) char s2[kStageBytes];
-    __shared__ __attribute__((aligned(1024))) char s3[kStageBytes];
-    __shared__ int mailbox[2];
-    __shared__ __attribute__((aligned(256))) char ring[GATHER ? kIndexRingBytes : 16];
     constexpr int BF = 128;  // features of P0 (and of P1) per tile
     const int nqt = RAGGED ? (NQd + kTile - 1) / kTile : NQd / kTile, npt = RAGGED ? (NPd + BF - 1) / BF : NPd / BF;
     const int wp0 = (threadIdx.x >> 6) % kWP2, wq0 = (threadIdx.x >> 6) / kWP2;
@@ -770,6 +756,7 @@ wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t
     }
     // reduction segments as in wgrad_kernel: an expert's rows or one part of them
     TileLoop tl(tiles[1] * nqt * npt, ctr);
+    if constexpr (LATE) tl.join(mailbox + 2);
     for (int slot = tl.first(), next = tl.second(); tl.valid(slot);) {
     const int id = tl.id(slot);
     const int eo = id / (nqt * npt);
@@ -823,9 +810,95 @@ wgrad_pair_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const int32_t
         tl.prefetch();
     }
     const int after = tl.finish(mailbox);
-    slot = next;
+    slot = LATE ? after : next;
     next = after;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Launches.  dH and dW_down, dXp and dW_gate/dW_up do not wait for each other: sharing one, a work-group that finds no tile of the first
+// left goes on with the second, instead of idling through the first one's last round (the rule is at mfma_ffn_backward).
+// ---------------------------------------------------------------------------
+struct RowGemmArgs {
+    int S, d, F;
+    const bf16_t *Q0, *Q1;
+    const int32_t *offsets, *tiles;
+    const bf16_t *W0, *W1, *FA, *FB;
+    bf16_t *out0, *out1;
+    const int32_t *tok;
+    int T;
+    const float *grow;
+    const bf16_t *H;
+    bf16_t *Hg;
+    float *wpart;
+    int stream;
+};
+struct WgradArgs {
+    int NQd, NPd;
+    const bf16_t *Qs, *P0, *P1;     // (P1: dW_gate and dW_up)
+    const int32_t *tok;
+    int nrows;
+    const int32_t *tiles;
+    float *out0, *out1, *part0, *part1;
+    int accumulate;
+    int *ctr;
+};
+// Spelled out in the kernels' own parameters: __restrict__ means nothing on a struct's members, and without it tile
+// coordinates come in through vector loads (down projection of 16384 tokens 436 -> 450 us).
+#define R3_ROWGEMM_PARAMS                                                                                                         \
+    int S, int d, int F, const bf16_t *__restrict__ Q0, const bf16_t *__restrict__ Q1, const int32_t *__restrict__ offsets,        \
+        const int32_t *__restrict__ tiles, const bf16_t *__restrict__ W0, const bf16_t *__restrict__ W1,                           \
+        const bf16_t *__restrict__ FA, const bf16_t *__restrict__ FB, bf16_t *__restrict__ out0, bf16_t *__restrict__ out1,        \
+        const int32_t *__restrict__ tok, int T, const float *__restrict__ grow, const bf16_t *__restrict__ Hs,                     \
+        bf16_t *__restrict__ Hg, float *__restrict__ wpart, int stream
+#define R3_ROWGEMM_ARGS S, d, F, Q0, Q1, offsets, tiles, W0, W1, FA, FB, out0, out1, tok, T, grow, Hs, Hg, wpart, stream
+#define R3_ROWGEMM_FIELDS(a)                                                                                                      \
+    a.S, a.d, a.F, a.Q0, a.Q1, a.offsets, a.tiles, a.W0, a.W1, a.FA, a.FB, a.out0, a.out1, a.tok, a.T, a.grow, a.H, a.Hg, a.wpart, a.stream
+
+template <bool PAIR, bool GATHER, bool RAGGED, bool LATE>
+__device__ __forceinline__ void wgrad_run(char *lds, char *ring, int *mailbox, int NQd, int NPd, const bf16_t *__restrict__ Qs,
+                                          const bf16_t *__restrict__ P0, const bf16_t *__restrict__ P1, const int32_t *__restrict__ tok, int nrows,
+                                          const int32_t *__restrict__ tiles, float *__restrict__ out0, float *__restrict__ out1,
+                                          float *__restrict__ part0, float *__restrict__ part1, int accumulate, int *ctr) {
+    char *const s1 = lds + kStageBytes, *const s2 = lds + 2 * kStageBytes, *const s3 = lds + 3 * kStageBytes;
+    if constexpr (PAIR)
+        wgrad_pair_tiles<GATHER, RAGGED, LATE>(lds, s1, s2, s3, ring, mailbox, NQd, NPd, Qs, tok, nrows, P0, P1, tiles, out0, out1, part0,
+                                               part1, accumulate, ctr);
+    else
+        wgrad_tiles<GATHER, RAGGED, LATE>(lds, s1, s2, s3, ring, mailbox, NQd, NPd, Qs, P0, tok, nrows, tiles, out0, part0, accumulate, ctr);
+}
+template <int MODE, bool GATED, bool RAGGED>
+__global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd) rowgemm_kernel(R3_ROWGEMM_PARAMS) {
+    __shared__ __attribute__((aligned(1024))) char lds[kRowLds];   // one piece: a tail tile lays it out differently
+    __shared__ int4 stash[MODE == 1 ? 2 * 256 : 1];
+    __shared__ __attribute__((aligned(256))) char gates[MODE == 1 ? 4 * kTile : 4];
+    __shared__ int mailbox[2];
+    rowgemm_tiles<MODE, GATED, RAGGED>(lds, stash, gates, mailbox, R3_ROWGEMM_ARGS);
+}
+template <bool PAIR, bool GATHER, bool RAGGED>
+__global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
+wgrad_kernel(int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__restrict__ P0, const bf16_t *__restrict__ P1,
+             const int32_t *__restrict__ tok, int nrows, const int32_t *__restrict__ tiles, float *__restrict__ wout0,
+             float *__restrict__ wout1, float *__restrict__ part0, float *__restrict__ part1, int accumulate, int *ctr) {
+    __shared__ __attribute__((aligned(1024))) char lds[4 * kStageBytes];
+    __shared__ __attribute__((aligned(256))) char ring[GATHER ? kIndexRingBytes : 16];
+    __shared__ int mailbox[2];
+    wgrad_run<PAIR, GATHER, RAGGED, false>(lds, ring, mailbox, NQd, NPd, Qs, P0, P1, tok, nrows, tiles, wout0, wout1, part0, part1, accumulate, ctr);
+}
+// MODE 1: dH (of a forward that left H gated), then dW_down; MODE 2: dXp, then dW_gate and dW_up
+template <int MODE, bool GATHER, bool RAGGED>
+__global__ void __launch_bounds__(kThreads2, kMinWavesPerSimd)
+grads_kernel(R3_ROWGEMM_PARAMS, int NQd, int NPd, const bf16_t *__restrict__ Qs, const bf16_t *__restrict__ P0,
+             const bf16_t *__restrict__ P1, const int32_t *__restrict__ wtok, int nrows, float *__restrict__ wout0,
+             float *__restrict__ wout1, float *__restrict__ part0, float *__restrict__ part1, int accumulate, int *ctr) {
+    __shared__ __attribute__((aligned(1024))) char lds[kRowLds];
+    __shared__ int4 stash[MODE == 1 ? 2 * 256 : 1];
+    __shared__ __attribute__((aligned(256))) char gates[MODE == 1 ? 4 * kTile : 4];
+    __shared__ int mailbox[3];
+    static_assert(4 * kStageBytes + kIndexRingBytes <= kRowLds, "");
+    rowgemm_tiles<MODE, MODE == 1, RAGGED>(lds, stash, gates, mailbox, R3_ROWGEMM_ARGS);
+    wgrad_run<MODE == 2, GATHER, RAGGED, true>(lds, lds + 4 * kStageBytes, mailbox, NQd, NPd, Qs, P0, P1, wtok, nrows, tiles, wout0, wout1,
+                                               part0, part1, accumulate, ctr);
 }
 
 // ---------------------------------------------------------------------------
@@ -969,16 +1042,26 @@ static void launch_ffn1(int64_t S, int d, int E, int F, const void *Xp, const in
         (bf16_t *)FA, (bf16_t *)FB, grow, FA ? stream_rows(S, E, F) : stream_unsaved_h<RAGGED>(S, d, E, F));
 }
 
+static int64_t rowgemm_grid_tiles(int mode, int64_t S, int d, int E, int F) {
+    return max_row_tiles(S, E, kTile) * tiles_of(mode == 1 ? F : d, kTile);
+}
+static int64_t wgrad_grid_tiles(int E, int NQd, int NPd, bool pair) {
+    return (int64_t)(E + kMaxSplitSlots + 8) * tiles_of(NQd, kTile) * tiles_of(NPd, pair ? 128 : kTile);
+}
 template <int MODE, bool GATED, bool RAGGED>
-static void launch_rowgemm(int64_t S, int d, int E, int F, const void *Q0, const void *Q1, const int32_t *offsets,
-                           const int32_t *tiles, const void *W0, const void *W1, const void *FA, const void *FB, void *out0,
-                           void *out1, const int32_t *tok, int T, const float *grow, const void *H, void *Hg, float *wpart,
-                           hipStream_t s) {
-    const int64_t n = max_row_tiles(S, E, kTile) * tiles_of(MODE == 1 ? F : d, kTile);
-    rowgemm_kernel<MODE, GATED, RAGGED><<<persistent_grid(n), kThreads2, 0, s>>>(
-        (int)S, d, F, (const bf16_t *)Q0, (const bf16_t *)Q1, offsets, tiles, (const bf16_t *)W0, (const bf16_t *)W1,
-        (const bf16_t *)FA, (const bf16_t *)FB, (bf16_t *)out0, (bf16_t *)out1, tok, T, grow, (const bf16_t *)H, (bf16_t *)Hg,
-        wpart, stream_rows(S, E, F));
+static void launch_rowgemm(int E, const RowGemmArgs &a, hipStream_t s) {
+    rowgemm_kernel<MODE, GATED, RAGGED><<<persistent_grid(rowgemm_grid_tiles(MODE, a.S, a.d, E, a.F)), kThreads2, 0, s>>>(R3_ROWGEMM_FIELDS(a));
+}
+template <bool PAIR, bool GATHER, bool RAGGED>
+static void launch_wgrad(int E, const WgradArgs &w, hipStream_t s) {
+    wgrad_kernel<PAIR, GATHER, RAGGED><<<persistent_grid(wgrad_grid_tiles(E, w.NQd, w.NPd, PAIR)), kThreads2, 0, s>>>(
+        w.NQd, w.NPd, w.Qs, w.P0, w.P1, w.tok, w.nrows, w.tiles, w.out0, w.out1, w.part0, w.part1, w.accumulate, w.ctr);
+}
+template <int MODE, bool GATHER, bool RAGGED>
+static void launch_grads(int E, const RowGemmArgs &a, const WgradArgs &w, hipStream_t s) {
+    const int64_t n = std::max(rowgemm_grid_tiles(MODE, a.S, a.d, E, a.F), wgrad_grid_tiles(E, w.NQd, w.NPd, MODE == 2));
+    grads_kernel<MODE, GATHER, RAGGED><<<persistent_grid(n), kThreads2, 0, s>>>(R3_ROWGEMM_FIELDS(a), w.NQd, w.NPd, w.Qs, w.P0, w.P1, w.tok, w.nrows,
+                                                                           w.out0, w.out1, w.part0, w.part1, w.accumulate, w.ctr);
 }
 
 hipError_t mfma_ffn_forward(int64_t S, int d, int E, int F, const void *Xp, const int32_t *perm, int K, int T,
@@ -993,30 +1076,9 @@ hipError_t mfma_ffn_forward(int64_t S, int d, int E, int F, const void *Xp, cons
         f(S, d, E, F, Xp, perm, K, T, offsets, tiles, Wg, Wu, H, FA, FB, grow, s);
     }
     ProfScope ps(PROF_FFN2, s);
-    auto f = rag ? launch_rowgemm<0, false, true> : launch_rowgemm<0, false, false>;
-    f(S, d, E, F, H, nullptr, offsets, tiles, Wd, nullptr, nullptr, nullptr, Yp, nullptr, nullptr, 0, nullptr, nullptr, nullptr,
-      nullptr, s);
-    return hipGetLastError();
-}
-
-hipError_t mfma_ffn_dh(int64_t S, int d, int E, int F, const void *dy, const int32_t *tok, int T, const float *grow,
-                       const int32_t *offsets, const int32_t *tiles, const void *Wd, const void *FA, const void *FB,
-                       const void *H, void *dA, void *dB, void *Hg, float *wpart, hipStream_t s) {
-    ProfScope ps(PROF_DH, s);
-    const bool rag = mfma_ffn_ragged(d, F);
-    // Hg == NULL: H already holds the gate-scaled rows
-    auto f = Hg ? (rag ? launch_rowgemm<1, false, true> : launch_rowgemm<1, false, false>)
-                : (rag ? launch_rowgemm<1, true, true> : launch_rowgemm<1, true, false>);
-    f(S, d, E, F, dy, nullptr, offsets, tiles, Wd, nullptr, FA, FB, dA, dB, tok, T, grow, H, Hg, wpart, s);
-    return hipGetLastError();
-}
-
-hipError_t mfma_ffn_dxp(int64_t S, int d, int E, int F, const void *dA, const void *dB, const int32_t *offsets,
-                        const int32_t *tiles, const void *Wg, const void *Wu, void *dXp, hipStream_t s) {
-    ProfScope ps(PROF_DXP, s);
-    auto f = mfma_ffn_ragged(d, F) ? launch_rowgemm<2, false, true> : launch_rowgemm<2, false, false>;
-    f(S, d, E, F, dA, dB, offsets, tiles, Wg, Wu, nullptr, nullptr, dXp, nullptr, nullptr, 0, nullptr, nullptr, nullptr, nullptr,
-      s);
+    RowGemmArgs a = {(int)S, d, F};
+    a.Q0 = (const bf16_t *)H; a.offsets = offsets; a.tiles = tiles; a.W0 = (const bf16_t *)Wd; a.out0 = (bf16_t *)Yp; a.stream = stream_rows(S, E, F);
+    (rag ? launch_rowgemm<0, false, true> : launch_rowgemm<0, false, false>)(E, a, s);
     return hipGetLastError();
 }
 
@@ -1033,33 +1095,62 @@ int mfma_wgrad_split_rows(int64_t S, int tiles_per_seg, size_t part_bytes_availa
     return r >= S ? 0 : (int)r;
 }
 
-hipError_t mfma_wgrad(int E, int NQd, int NPd, const void *Qs, const void *Ps, const int32_t *tok, int nrows,
-                      const int32_t *tiles, int launch, float *out, float *part, int accumulate, hipStream_t s) {
-    const int64_t ntiles = (int64_t)(E + kMaxSplitSlots + 8) * tiles_of(NQd, kTile) * tiles_of(NPd, kTile);
-    ProfScope ps(PROF_WGRAD, s);
-    const bool rag = mfma_ffn_ragged(NQd, NPd);
-    auto k = tok ? (rag ? wgrad_kernel<true, true> : wgrad_kernel<true, false>)
-                 : (rag ? wgrad_kernel<false, true> : wgrad_kernel<false, false>);
-    k<<<persistent_grid(ntiles), kThreads2, 0, s>>>(NQd, NPd, (const bf16_t *)Qs, (const bf16_t *)Ps, tok, nrows, tiles, out,
-                                                    part, accumulate, const_cast<int *>(tiles) + 2 + 8 * launch);
-    if (part) wgrad_parts_kernel<<<512, 256, 0, s>>>((int64_t)NQd * NPd / 4, tiles, out, part, nullptr, nullptr);
-    return hipGetLastError();
-}
-
-hipError_t mfma_wgrad_pair(int E, int NQd, int NPd, const void *Qs, const int32_t *tok, int nrows, const void *P0,
-                           const void *P1, const int32_t *tiles, int launch, float *out0, float *out1, float *part,
-                           int accumulate, hipStream_t s) {
-    const int64_t ntiles = (int64_t)(E + kMaxSplitSlots + 8) * tiles_of(NQd, kTile) * tiles_of(NPd, 128);
-    const int64_t n = (int64_t)NQd * NPd;
-    float *part1 = part ? part + (int64_t)kMaxSplitSlots * n : nullptr;   // the second product's slots
-    ProfScope ps(PROF_WGRAD_PAIR, s);
-    const bool rag = mfma_ffn_ragged(NQd, NPd);
-    auto k = tok ? (rag ? wgrad_pair_kernel<true, true> : wgrad_pair_kernel<true, false>)
-                 : (rag ? wgrad_pair_kernel<false, true> : wgrad_pair_kernel<false, false>);
-    k<<<persistent_grid(ntiles), kThreads2, 0, s>>>(NQd, NPd, (const bf16_t *)Qs, tok, nrows, (const bf16_t *)P0,
-                                                    (const bf16_t *)P1, tiles, out0, out1, part, part1, accumulate,
-                                                    const_cast<int *>(tiles) + 2 + 8 * launch);
-    if (part) wgrad_parts_kernel<<<512, 256, 0, s>>>(n / 4, tiles, out0, part, out1, part1);
+// dH and dW_down share a launch where dH does not make dW_down's rows (gated), dXp and dW_gate/dW_up do, unless reductions may be cut into
+// parts (whose place is dXp's).  us, each its own launch | shared: 3001 tokens top-6, 1000 x 704, 64 experts, whose launches are 1.4 to 6 rounds
+// of tiles, 147 | 130 and 205 | 181, training 594 | 537; 1001 top-8, 2048 x 768, 128 experts 270 | 246 and 462 | 460, 1045 | 1029; training: 1099
+// top-2, 176 x 96, 6 experts, Zipf 130 | 105, 20000 top-2, 512 x 1280, 64 experts, Zipf 1308 | 1184, 4096 top-8, 2048 x 768, 128 experts 1639 | 1562,
+// 4000 top-8, 768 x 512, 256 experts 723 | 685.  dXp before dW_gate/dW_up: its long tiles end a launch raggedly (3001 tokens 567 instead of 538).  Past some
+// 12000 tokens of the 2048 x 768 layer, where skewed reductions are cut, the last rounds are a few per cent of a launch: dH and dW_down of
+// 16384 tokens in one, training the same, 65536 Zipf .3 % faster.
+hipError_t mfma_ffn_backward(const FfnBackward &b, hipStream_t s) {
+    const int E = b.E;
+    const bool rag = mfma_ffn_ragged(b.d, b.F), gated = !b.Hg;
+    const int64_t n = (int64_t)b.d * b.F;
+    RowGemmArgs dh = {(int)b.S, b.d, b.F};
+    dh.Q0 = (const bf16_t *)b.dy; dh.offsets = b.offsets; dh.tiles = b.tiles; dh.W0 = (const bf16_t *)b.Wd;
+    dh.FA = (const bf16_t *)b.FA; dh.FB = (const bf16_t *)b.FB; dh.out0 = (bf16_t *)b.dA; dh.out1 = (bf16_t *)b.dB;
+    dh.tok = b.tok; dh.T = b.T; dh.grow = b.grow; dh.H = (const bf16_t *)b.H; dh.Hg = (bf16_t *)b.Hg; dh.wpart = b.wpart;
+    dh.stream = stream_rows(b.S, E, b.F);
+    RowGemmArgs dxp = {(int)b.S, b.d, b.F};
+    dxp.Q0 = (const bf16_t *)b.dA; dxp.Q1 = (const bf16_t *)b.dB; dxp.offsets = b.offsets; dxp.tiles = b.tiles;
+    dxp.W0 = (const bf16_t *)b.Wg; dxp.W1 = (const bf16_t *)b.Wu; dxp.out0 = (bf16_t *)b.dXp; dxp.stream = dh.stream;
+    int *ctr = const_cast<int *>(b.tiles) + 2;
+    WgradArgs down = {b.F, b.d, (const bf16_t *)(gated ? b.H : b.Hg), (const bf16_t *)b.dy, nullptr, b.tok, b.T, b.tiles, b.dWd, nullptr,
+                      b.part, nullptr, b.accumulate, ctr + 8 * 2};
+    WgradArgs pair = {b.d, b.F, (const bf16_t *)(b.Xp ? b.Xp : b.x), (const bf16_t *)b.dA, (const bf16_t *)b.dB, b.Xp ? nullptr : b.tok, b.T,
+                      b.tiles, b.dWg, b.dWu, b.part, b.part ? b.part + (int64_t)kMaxSplitSlots * n : nullptr, b.accumulate, ctr + 8 * 3};
+    if (gated && !b.part) {
+        ProfScope ps(PROF_DH, s);
+        (rag ? launch_grads<1, true, true> : launch_grads<1, true, false>)(E, dh, down, s);
+    } else {
+        {
+            ProfScope ps(PROF_DH, s);
+            auto f = gated ? (rag ? launch_rowgemm<1, true, true> : launch_rowgemm<1, true, false>)
+                           : (rag ? launch_rowgemm<1, false, true> : launch_rowgemm<1, false, false>);
+            f(E, dh, s);
+        }
+        ProfScope ps(PROF_WGRAD, s);
+        (rag ? launch_wgrad<false, true, true> : launch_wgrad<false, true, false>)(E, down, s);
+        if (b.part) wgrad_parts_kernel<<<512, 256, 0, s>>>(n / 4, b.tiles, b.dWd, b.part, nullptr, nullptr);
+    }
+    hipError_t rc = launch_gate_backward_parts(b.T, b.K, b.row_parts, b.wpart, b.gates, b.inv_perm, b.dz, b.dzrow, s);
+    if (rc != hipSuccess) return rc;
+    if (!b.part) {
+        ProfScope ps(PROF_WGRAD_PAIR, s);
+        auto f = b.Xp ? (rag ? launch_grads<2, false, true> : launch_grads<2, false, false>)
+                      : (rag ? launch_grads<2, true, true> : launch_grads<2, true, false>);
+        f(E, dxp, pair, s);
+        return hipGetLastError();
+    }
+    {
+        ProfScope ps(PROF_WGRAD_PAIR, s);
+        auto f = b.Xp ? (rag ? launch_wgrad<true, false, true> : launch_wgrad<true, false, false>)
+                      : (rag ? launch_wgrad<true, true, true> : launch_wgrad<true, true, false>);
+        f(E, pair, s);
+        wgrad_parts_kernel<<<512, 256, 0, s>>>(n / 4, b.tiles, b.dWg, b.part, b.dWu, pair.part1);
+    }
+    ProfScope ps(PROF_DXP, s);
+    (rag ? launch_rowgemm<2, false, true> : launch_rowgemm<2, false, false>)(E, dxp, s);
     return hipGetLastError();
 }
 

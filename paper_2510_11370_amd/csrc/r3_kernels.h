@@ -129,29 +129,24 @@ hipError_t mfma_ffn_forward(int64_t S, int d, int E, int F, const void *Xp, cons
                             const int32_t *offsets, const int32_t *tiles, const void *Wg, const void *Wu,
                             const void *Wd, void *Yp, void *H, void *FA, void *FB, const float *grow,
                             hipStream_t s);
-// u = dy Wd^T with the rows of dy read through tok (row r is dy[tok[r]], dy is [T,d]); writes dA = g u FA,
-// dB = g u FB, Hg = g H and wpart [S, 2 F/256] f32, whose row sums are g <dy, o> (see rowgemm_kernel<1>).
-// Hg == NULL: H already holds g H (the one-call forward wrote it so) and nothing is written for it
-hipError_t mfma_ffn_dh(int64_t S, int d, int E, int F, const void *dy, const int32_t *tok, int T, const float *grow,
-                       const int32_t *offsets, const int32_t *tiles, const void *Wd, const void *FA, const void *FB,
-                       const void *H, void *dA, void *dB, void *Hg, float *wpart, hipStream_t s);
-hipError_t mfma_ffn_dxp(int64_t S, int d, int E, int F, const void *dA, const void *dB, const int32_t *offsets,
-                        const int32_t *tiles, const void *Wg, const void *Wu, void *dXp, hipStream_t s);
-// `tiles` is the table mfma_build_tiles() filled in this call sequence; `launch` (2..7) picks the
-// tile counters of this launch: 0 and 1 belong to the forward pair and to dh / dxp.
-// out (+)= Qs^T Ps per expert.  tok != NULL: Ps is the un-permuted [nrows, NPd] matrix and row r of the
-// reduction is its row tok[r] (nrows * NPd * 2 < 2^31).  The reduction segments come from the table (an
-// expert's rows, or parts of them when the table was built with split_rows > 0: then `part` must hold
-// the partial products, and a second launch adds them to the gradient in a fixed order)
-hipError_t mfma_wgrad(int E, int NQd, int NPd, const void *Qs, const void *Ps, const int32_t *tok, int nrows,
-                      const int32_t *tiles, int launch, float *out, float *part, int accumulate, hipStream_t s);
-// out0 (+)= Qs^T P0 and out1 (+)= Qs^T P1 per expert in one pass over Qs.  tok != NULL: Qs is the
-// un-permuted [nrows, NQd] matrix and row r of the reduction is its row tok[r] (nrows * NQd * 2 < 2^31)
-// `part` (split tables only, else NULL): room for the partial products of both gradients, 2 x the slots of
-// mfma_wgrad's
-hipError_t mfma_wgrad_pair(int E, int NQd, int NPd, const void *Qs, const int32_t *tok, int nrows, const void *P0,
-                           const void *P1, const int32_t *tiles, int launch, float *out0, float *out1, float *part,
-                           int accumulate, hipStream_t s);
+// The expert gradients of a backward, with the gate's in between (r3_gemm.hip):
+//   u = dy Wd^T with the rows of dy read through tok (row r is dy[tok[r]], dy is [T,d], T * d * 2 < 2^31); dA = g u FA, dB = g u FB,
+//   Hg = g H and wpart [S, row_parts] f32, whose row sums are g <dy, o>.  Hg == NULL: H already holds g H (the one-call forward wrote it so);
+//   dz (and, if not NULL, dzrow) from wpart;
+//   dWd (+)= Hg^T dy, dWg (+)= X^T dA, dWu (+)= X^T dB per expert, X the rows of x read through tok, or Xp if given;
+//   dXp = dA Wg^T + dB Wu^T.
+// `tiles` is the table of mfma_build_tiles_and_row_tokens(); if that was built with split_rows > 0, `part` is the place for the partial
+// products of the weight gradients (dXp's own, which is written after they are added), else NULL.
+struct FfnBackward {
+    int64_t S;
+    int T, d, E, F, K, accumulate, row_parts;
+    const int32_t *offsets, *tiles, *tok, *inv_perm;
+    const float *grow, *gates;
+    const void *dy, *x, *Xp, *FA, *FB, *H, *Wg, *Wu, *Wd;
+    void *dA, *dB, *Hg, *dXp;
+    float *wpart, *dz, *dzrow, *part, *dWg, *dWu, *dWd;
+};
+hipError_t mfma_ffn_backward(const FfnBackward &b, hipStream_t s);
 size_t mfma_row_tokens_bytes(int64_t S);
 hipError_t mfma_router_logits(int T, int d, int E, const void *x, const void *Wr, const float *bias,
                               float *logits, hipStream_t s);

@@ -6,6 +6,7 @@
 #include <mutex>
 
 #include "r3_f32.h"
+#include "r3_finish.h"
 #include "r3_kernels.h"
 
 using namespace r3;
@@ -360,8 +361,15 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
         b.offsets = offsets; b.tiles = tiles; b.tok = tok; b.inv_perm = inv_perm; b.grow = grow; b.gates = gates;
         b.dy = dy; b.x = x; b.Xp = Xp; b.FA = FA; b.FB = FB; b.H = H; b.Wg = W_gate; b.Wu = W_up; b.Wd = W_down;
         b.dA = dA; b.dB = dB; b.Hg = Hg; b.dXp = dXp; b.wpart = wpart; b.dz = dz; b.dzrow = dzrow; b.part = split ? (float *)dXp : nullptr;
-        b.dWg = dW_gate; b.dWu = dW_up; b.dWd = dW_down;
+        b.dWg = dW_gate; b.dWu = dW_up; b.dWd = dW_down; b.Wr = W_r; b.WrT = WrT;
         if (mfma_ffn_backward(b, s) != hipSuccess) return R3_ERR_HIP;
+        // router:  dW_r = x^T ds in parts (ds: dz at the recorded experts); their sum and dbias, the column sums of ds, beside dx
+        float *part = (float *)(base + w.part);
+        if (router_dwr_parts(m.T, m.d, m.E, m.K, m.act, x, dz, idx, m.idx, m.stride, part, false, s) != hipSuccess) return R3_ERR_HIP;
+        RouterFinish<bf16_t> fin;
+        (void)fin.fill<256>(m.d, m.E, router_dwr_nparts(m.act, m.T, m.d, m.E, false), accumulate, dzrow, part, offsets, dbias, dW_r, W_r, WrT);
+        return hip_rc(launch_dx_finish(m.T, m.d, m.E, m.K, m.act, dXp, WrT, dz, inv_perm, idx, m.idx, m.stride, dx, &fin,
+                                       fin.bias_blocks + fin.sum_blocks, s));
     } else {
         // combine and masked softmax:  dYp = g*dy per slot, dz
         void *dYp = dXp;  // dYp is dead once dW_down and dH are done
@@ -379,7 +387,7 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
             b.dA = (float *)dA; b.dB = (float *)dB; b.dXp = (float *)dXp; b.part = (float *)(base + w.part);
             b.dWg = dW_gate; b.dWu = dW_up; b.dWd = dW_down; b.dWr = dW_r; b.dbias = dbias; b.WrT = (float *)WrT;
             if (f32_backward(b, s) != hipSuccess) return R3_ERR_HIP;
-            return hip_rc(launch_dx_finish(m.T, m.d, m.E, m.K, m.act, dXp, WrT, dz, inv_perm, idx, m.idx, m.stride, dx, s));
+            return hip_rc(launch_dx_finish(m.T, m.d, m.E, m.K, m.act, dXp, WrT, dz, inv_perm, idx, m.idx, m.stride, dx, nullptr, 0, s));
         }
         if (plain_dh(S, m.d, m.E, m.F, m.act, dYp, offsets, W_down, FA, FB, dA, dB, s) != hipSuccess) return R3_ERR_HIP;
         // gated: H is g H already, so its partner is the plain dy row (read through perm), not g dy
@@ -393,8 +401,7 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
                         dW_r, dbias, WrT, accumulate, force_simt(), s) != hipSuccess)
         return R3_ERR_HIP;
     // dx = un-permuted expert gradients + router term
-    return hip_rc(launch_dx_finish(m.T, m.d, m.E, m.K, m.act, dXp, WrT, dz, inv_perm, idx, m.idx, m.stride, dx,
-                                   s));
+    return hip_rc(launch_dx_finish(m.T, m.d, m.E, m.K, m.act, dXp, WrT, dz, inv_perm, idx, m.idx, m.stride, dx, nullptr, 0, s));
 }
 
 int r3_routing_diff(const r3_layer_desc *desc, int L, const void *idx_a, const void *idx_b, int64_t layer_stride,

@@ -1,4 +1,6 @@
-// The last step of the router's backward: three sorts of work that do not wait for each other, a work-group of NT threads each.
+// The last step of the router's backward: three sorts of work that do not wait for each other, a work-group of NT threads each (in a launch of
+// their own, or beside others: bf16 after the expert gradients, W_r^T with the gate's backward and the rest with dx; f32 after the
+// one-call forward, with the gradients).
 //   dbias[e] (+)= the sum of dz over the rows of expert e (fixed order; first in the grid, as a skewed load's hot expert takes
 //     longest);
 //   dW_r[i] (+)= sum_s part[s][i], s ascending, NT values;
@@ -26,6 +28,13 @@ template <typename T> struct RouterFinish {
         dbias = dbias_; dWr = dWr_;
         Wr = (const T *)Wr_; WrT = (T *)WrT_;
         return bias_blocks + sum_blocks + ((d + 31) / 32) * ((E + 31) / 32);
+    }
+    // W_r^T alone, and its work-groups
+    int transpose_only(int d_, int E_, const void *Wr_, void *WrT_) {
+        *this = {};
+        d = d_; E = E_;
+        Wr = (const T *)Wr_; WrT = (T *)WrT_;
+        return ((d + 31) / 32) * ((E + 31) / 32);
     }
 };
 template <typename T> struct RouterFinishLds {

@@ -1133,7 +1133,7 @@ hipError_t mfma_ffn_backward(const FfnBackward &b, hipStream_t s) {
         (rag ? launch_wgrad<false, true, true> : launch_wgrad<false, true, false>)(E, down, s);
         if (b.part) wgrad_parts_kernel<<<512, 256, 0, s>>>(n / 4, b.tiles, b.dWd, b.part, nullptr, nullptr);
     }
-    hipError_t rc = launch_gate_backward_parts(b.T, b.K, b.row_parts, b.wpart, b.gates, b.inv_perm, b.dz, b.dzrow, s);
+    hipError_t rc = launch_gate_backward_parts(b.T, b.K, b.row_parts, b.wpart, b.gates, b.inv_perm, b.dz, b.dzrow, b.d, E, b.Wr, b.WrT, s);
     if (rc != hipSuccess) return rc;
     if (!b.part) {
         ProfScope ps(PROF_WGRAD_PAIR, s);

@@ -47,10 +47,13 @@ hipError_t launch_gate_backward(int T, int d, int K, int act, const void *dy, co
 // masked-softmax backward from the row parts written by the expert-gradient GEMM:
 // w_j = sum_p wpart[row_j][p] (= g_j dg_j), dz_j = w_j - g_j sum_i w_i; writes dz [T,K], and dzrow as above
 hipError_t launch_gate_backward_parts(int T, int K, int nparts, const float *wpart, const float *gates,
-                                      const int32_t *inv_perm, float *dz, float *dzrow, hipStream_t s);
-hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp, const void *WrT,
-                            const float *dz, const int32_t *inv_perm, const void *idx, int idx_dtype,
-                            int64_t stride, void *dx, hipStream_t s);
+                                      const int32_t *inv_perm, float *dz, float *dzrow, int d, int E, const void *Wr, void *WrT,
+                                      hipStream_t s);
+// fin, nfin: work-groups of the router's last step to run beside it (bf16; NULL, 0: none)
+template <typename T> struct RouterFinish;
+hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp, const void *WrT, const float *dz, const int32_t *inv_perm,
+                            const void *idx, int idx_dtype, int64_t stride, void *dx, const RouterFinish<bf16_t> *fin, int nfin,
+                            hipStream_t s);
 
 // r3_diag.hip
 size_t policy_ws_bytes();
@@ -103,6 +106,10 @@ hipError_t router_gate(int T, int d, int E, int K, int act, const void *x, const
 // Router weight gradient dW_r (+)= x^T ds, ds[t][idx[t][j]] = dz[t][j]; part: router_dwr_ws_bytes() bytes.  dbias (+)=
 // column sums of ds, unless NULL (dzrow: dz in the order of the rows).  WrT [E,d] = W_r^T
 size_t router_dwr_ws_bytes(int act, int T, int d, int E, bool plain_only);
+// its first step alone, parts of dW_r over the tokens, and their number
+hipError_t router_dwr_parts(int T, int d, int E, int K, int act, const void *x, const float *dz, const void *idx, int idx_dtype, int64_t stride,
+                            float *part, bool plain_only, hipStream_t s);
+int router_dwr_nparts(int act, int T, int d, int E, bool plain_only);
 hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, const void *Wr, const float *dz, const void *idx,
                            int idx_dtype, int64_t stride, const int32_t *offsets, const float *dzrow, float *part, float *dWr,
                            float *dbias, void *WrT, int accumulate, bool plain_only, hipStream_t s);
@@ -132,7 +139,7 @@ hipError_t mfma_ffn_forward(int64_t S, int d, int E, int F, const void *Xp, cons
 // The expert gradients of a backward, with the gate's in between (r3_gemm.hip):
 //   u = dy Wd^T with the rows of dy read through tok (row r is dy[tok[r]], dy is [T,d], T * d * 2 < 2^31); dA = g u FA, dB = g u FB,
 //   Hg = g H and wpart [S, row_parts] f32, whose row sums are g <dy, o>.  Hg == NULL: H already holds g H (the one-call forward wrote it so);
-//   dz (and, if not NULL, dzrow) from wpart;
+//   dz (and, if not NULL, dzrow) from wpart; beside it W_r^T, which dx will want;
 //   dWd (+)= Hg^T dy, dWg (+)= X^T dA, dWu (+)= X^T dB per expert, X the rows of x read through tok, or Xp if given;
 //   dXp = dA Wg^T + dB Wu^T.
 // `tiles` is the table of mfma_build_tiles_and_row_tokens(); if that was built with split_rows > 0, `part` is the place for the partial
@@ -142,8 +149,8 @@ struct FfnBackward {
     int T, d, E, F, K, accumulate, row_parts;
     const int32_t *offsets, *tiles, *tok, *inv_perm;
     const float *grow, *gates;
-    const void *dy, *x, *Xp, *FA, *FB, *H, *Wg, *Wu, *Wd;
-    void *dA, *dB, *Hg, *dXp;
+    const void *dy, *x, *Xp, *FA, *FB, *H, *Wg, *Wu, *Wd, *Wr;
+    void *dA, *dB, *Hg, *dXp, *WrT;
     float *wpart, *dz, *dzrow, *part, *dWg, *dWu, *dWd;
 };
 hipError_t mfma_ffn_backward(const FfnBackward &b, hipStream_t s);

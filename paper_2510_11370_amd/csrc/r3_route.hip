@@ -5,6 +5,9 @@
 // reductions; none uses floating-point atomics (results are bit-reproducible).
 #include <algorithm>
 
+#include <type_traits>
+
+#include "r3_finish.h"
 #include "r3_kernels.h"
 #include "r3_tiles.h"
 #include "r3_topk.h"
@@ -810,10 +813,21 @@ hipError_t launch_permute(int T, int d, int E, int K, int elem_bytes, const void
 
 // ---------------------------------------------------------------------------
 // Combine: y[t] = sum_j g[t,j] * Yp[inv_perm[t*K+j]], j ascending, f32.
-// One block per token; each thread owns VEC consecutive columns.
+// A block takes 256 / LPT tokens, LPT lanes each; a lane owns VEC consecutive columns at a time.
 // ---------------------------------------------------------------------------
+// Lanes per token: a row shorter than 256 vectors leaves lanes of a block idle, so the block takes two, four or eight tokens; but a small
+// batch stays spread over the compute units.  With K known (by_k) and the router's last step beside dx, us, before | now: 3001 tokens top-6, 1000
+// columns, combine 10.4 | 9.7, router_finish and dx 20.4 | 13.8; 6000 top-4, 1024 columns 14.3 | 12.9, 22.7 | 20.3; 131072 top-2, 512 columns,
+// the forward pass 418 | 400.
+static int row_lanes(int T, int row_vecs) {
+    int n = 256;
+    while (n > 32 && n / 2 >= row_vecs && (int64_t)T * n / 2 >= 1024 * 256) n /= 2;
+    return n;
+}
 template <typename T, int VEC> struct VecIO;
 template <> struct VecIO<bf16_t, 8> {
+    typedef bf16_t Elem;
+    static constexpr int kVec = 8;
     typedef uint4 V;
     static __device__ __forceinline__ void unpack(const V &v, float *f) {
         const uint32_t w[4] = {v.x, v.y, v.z, v.w};
@@ -833,6 +847,8 @@ template <> struct VecIO<bf16_t, 8> {
     }
 };
 template <> struct VecIO<float, 4> {
+    typedef float Elem;
+    static constexpr int kVec = 4;
     typedef float4 V;
     static __device__ __forceinline__ void unpack(const V &v, float *f) {
         f[0] = v.x; f[1] = v.y; f[2] = v.z; f[3] = v.w;
@@ -840,33 +856,51 @@ template <> struct VecIO<float, 4> {
     static __device__ __forceinline__ V pack(const float *f) { return make_float4(f[0], f[1], f[2], f[3]); }
 };
 template <> struct VecIO<bf16_t, 1> {
+    typedef bf16_t Elem;
+    static constexpr int kVec = 1;
     typedef bf16_t V;
     static __device__ __forceinline__ void unpack(const V &v, float *f) { f[0] = bf16_to_f32(v); }
     static __device__ __forceinline__ V pack(const float *f) { return f32_to_bf16(f[0]); }
 };
 template <> struct VecIO<float, 1> {
+    typedef float Elem;
+    static constexpr int kVec = 1;
     typedef float V;
     static __device__ __forceinline__ void unpack(const V &v, float *f) { f[0] = v; }
     static __device__ __forceinline__ V pack(const float *f) { return f[0]; }
 };
 
 // KT > 0: K known at compile time, so that a thread's K row loads are all in flight together
+template <class F> static void by_k(int K, F f) {
+    switch (K) {
+        case 1: f(std::integral_constant<int, 1>{}); break;
+        case 2: f(std::integral_constant<int, 2>{}); break;
+        case 4: f(std::integral_constant<int, 4>{}); break;
+        case 6: f(std::integral_constant<int, 6>{}); break;
+        case 8: f(std::integral_constant<int, 8>{}); break;
+        default: f(std::integral_constant<int, 0>{});
+    }
+}
 template <typename T, int VEC, int KT>
 __global__ void __launch_bounds__(256)
-combine_kernel(int Krt, int row_vecs, const typename VecIO<T, VEC>::V *__restrict__ Yp,
+combine_kernel(int Tn, int Krt, int lanes, int row_vecs, const typename VecIO<T, VEC>::V *__restrict__ Yp,
                const float *__restrict__ gates, const int32_t *__restrict__ inv_perm,
                typename VecIO<T, VEC>::V *__restrict__ y) {
     typedef VecIO<T, VEC> IO;
     const int K = KT > 0 ? KT : Krt;
-    const int t = blockIdx.x;
-    __shared__ int32_t rows[kMaxK];
-    __shared__ float g[kMaxK];
-    if (threadIdx.x < (unsigned)K) {
-        rows[threadIdx.x] = inv_perm[(int64_t)t * K + threadIdx.x];
-        g[threadIdx.x] = gates ? gates[(int64_t)t * K + threadIdx.x] : 1.0f;   // no gates: rows arrive gated
+    const int t0 = blockIdx.x * (256 / lanes), n = min(256 / lanes, Tn - t0) * K;
+    __shared__ int32_t rows_s[8 * kMaxK];
+    __shared__ float g_s[8 * kMaxK];
+    for (int i = threadIdx.x; i < n; i += 256) {
+        rows_s[i] = inv_perm[(int64_t)t0 * K + i];
+        g_s[i] = gates ? gates[(int64_t)t0 * K + i] : 1.0f;   // no gates: rows arrive gated
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < row_vecs; c += blockDim.x) {
+    const int tok = (int)threadIdx.x / lanes, t = t0 + tok;
+    if (t >= Tn) return;
+    const int32_t *rows = rows_s + tok * K;
+    const float *g = g_s + tok * K;
+    for (int c = threadIdx.x & (lanes - 1); c < row_vecs; c += lanes) {
         float acc[VEC];
 #pragma unroll
         for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
@@ -898,23 +932,18 @@ combine_kernel(int Krt, int row_vecs, const typename VecIO<T, VEC>::V *__restric
 hipError_t launch_combine(int T, int d, int K, int act, const void *Yp, const float *gates,
                           const int32_t *inv_perm, void *y, hipStream_t s) {
     ProfScope ps(PROF_COMBINE, s);
+    auto go = [&](auto io, auto kt) {
+        typedef decltype(io) IO;
+        const int vecs = d / IO::kVec, lanes = row_lanes(T, vecs), tpb = 256 / lanes;
+        combine_kernel<typename IO::Elem, IO::kVec, decltype(kt)::value><<<(T + tpb - 1) / tpb, 256, 0, s>>>(
+            T, K, lanes, vecs, (const typename IO::V *)Yp, gates, inv_perm, (typename IO::V *)y);
+    };
     if (act == R3_BF16) {
-        if (d % 8 == 0 && K == 8)
-            combine_kernel<bf16_t, 8, 8><<<T, 256, 0, s>>>(K, d / 8, (const uint4 *)Yp, gates, inv_perm,
-                                                          (uint4 *)y);
-        else if (d % 8 == 0)
-            combine_kernel<bf16_t, 8, 0><<<T, 256, 0, s>>>(K, d / 8, (const uint4 *)Yp, gates, inv_perm,
-                                                          (uint4 *)y);
-        else
-            combine_kernel<bf16_t, 1, 0><<<T, 256, 0, s>>>(K, d, (const bf16_t *)Yp, gates, inv_perm,
-                                                          (bf16_t *)y);
+        if (d % 8 == 0) by_k(K, [&](auto kt) { go(VecIO<bf16_t, 8>{}, kt); });
+        else go(VecIO<bf16_t, 1>{}, std::integral_constant<int, 0>{});
     } else {
-        if (d % 4 == 0)
-            combine_kernel<float, 4, 0><<<T, 256, 0, s>>>(K, d / 4, (const float4 *)Yp, gates, inv_perm,
-                                                         (float4 *)y);
-        else
-            combine_kernel<float, 1, 0><<<T, 256, 0, s>>>(K, d, (const float *)Yp, gates, inv_perm,
-                                                         (float *)y);
+        if (d % 4 == 0) by_k(K, [&](auto kt) { go(VecIO<float, 4>{}, kt); });
+        else go(VecIO<float, 1>{}, std::integral_constant<int, 0>{});
     }
     return hipGetLastError();
 }
@@ -1015,6 +1044,7 @@ static hipError_t gate_backward_dispatch(int Tn, int K, int row_vecs, const void
                                          const int32_t *inv_perm, void *dYp, float *dz, float *dzrow, int gated,
                                          hipStream_t s) {
     typedef typename VecIO<T, VEC>::V V;
+    // (K = 4 in registers: 8.4 -> 10.3 us at 2048 f32 tokens of 512)
     auto k = K == 8 && VEC > 1 ? gate_backward_kernel<T, VEC, 8> : gate_backward_kernel<T, VEC, 0>;
     k<<<Tn, 256, 0, s>>>(K, row_vecs, (const V *)dy, (const V *)Yp, gates, inv_perm, (V *)dYp, dz, dzrow, gated);
     return hipGetLastError();
@@ -1039,8 +1069,13 @@ hipError_t launch_gate_backward(int T, int d, int K, int act, const void *dy, co
 __global__ void __launch_bounds__(256)
 gate_backward_parts_kernel(int T, int K, int KP, int nparts, const float *__restrict__ wpart,
                            const float *__restrict__ gates, const int32_t *__restrict__ inv_perm, float *__restrict__ dz,
-                           float *__restrict__ dzrow) {
-    const int j = threadIdx.x % KP, t = blockIdx.x * (256 / KP) + threadIdx.x / KP;
+                           float *__restrict__ dzrow, RouterFinish<bf16_t> wrt, int nwrt) {
+    __shared__ RouterFinishLds<bf16_t> lds;
+    if ((int)blockIdx.x < nwrt) {   // W_r^T, which dx will want, has nothing to wait for
+        router_finish_block<256>(wrt, blockIdx.x, lds);
+        return;
+    }
+    const int j = threadIdx.x % KP, t = ((int)blockIdx.x - nwrt) * (256 / KP) + threadIdx.x / KP;
     const bool live = t < T && j < K;
     float w = 0.0f, g = 0.0f;
     int row = 0;
@@ -1060,39 +1095,56 @@ gate_backward_parts_kernel(int T, int K, int KP, int nparts, const float *__rest
 }
 
 hipError_t launch_gate_backward_parts(int T, int K, int nparts, const float *wpart, const float *gates,
-                                      const int32_t *inv_perm, float *dz, float *dzrow, hipStream_t s) {
+                                      const int32_t *inv_perm, float *dz, float *dzrow, int d, int E, const void *Wr, void *WrT,
+                                      hipStream_t s) {
     ProfScope ps(PROF_GATE_BWD, s);
+    RouterFinish<bf16_t> wrt;
+    const int nwrt = wrt.transpose_only(d, E, Wr, WrT);
     int KP = 1;
     while (KP < K) KP <<= 1;                        // K <= kMaxK = 64
     const int tpb = 256 / KP;
-    gate_backward_parts_kernel<<<(T + tpb - 1) / tpb, 256, 0, s>>>(T, K, KP, nparts, wpart, gates, inv_perm, dz, dzrow);
+    gate_backward_parts_kernel<<<nwrt + (T + tpb - 1) / tpb, 256, 0, s>>>(T, K, KP, nparts, wpart, gates, inv_perm, dz, dzrow, wrt, nwrt);
     return hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------
-// Final input gradient, one block per token:
+// Final input gradient, tokens and lanes as in combine_kernel:
 //   dx[t] = sum_j dXp[row_j]  +  sum_j dz[t,j] * W_r[:, idx_j]
 // WrT is W_r transposed ([E,d], act dtype) so that the router term reads rows.
+// The first nfin blocks: the rest of the router's backward (the sum of dW_r's parts, dbias), which waits for the same launches.
 // ---------------------------------------------------------------------------
 template <typename T, int VEC, typename IdxT, int KT>
 __global__ void __launch_bounds__(256)
-dx_finish_kernel(int E, int Krt, int row_vecs, const typename VecIO<T, VEC>::V *__restrict__ dXp,
+dx_finish_kernel(int Tn, int E, int Krt, int lanes, int row_vecs, const typename VecIO<T, VEC>::V *__restrict__ dXp,
                  const typename VecIO<T, VEC>::V *__restrict__ WrT, const float *__restrict__ dz,
                  const int32_t *__restrict__ inv_perm, const IdxT *__restrict__ idx, int64_t stride,
-                 typename VecIO<T, VEC>::V *__restrict__ dx) {
+                 typename VecIO<T, VEC>::V *__restrict__ dx, RouterFinish<T> fin, int nfin) {
     typedef VecIO<T, VEC> IO;
     const int K = KT > 0 ? KT : Krt;
-    const int t = blockIdx.x;
-    __shared__ int32_t rows[kMaxK];
-    __shared__ int32_t ids[kMaxK];
-    __shared__ float z[kMaxK];
-    if (threadIdx.x < (unsigned)K) {
-        rows[threadIdx.x] = inv_perm[(int64_t)t * K + threadIdx.x];
-        ids[threadIdx.x] = min((int)idx[(int64_t)t * stride + threadIdx.x], E - 1);
-        z[threadIdx.x] = dz[(int64_t)t * K + threadIdx.x];
+    __shared__ union {
+        RouterFinishLds<T> fin;
+        struct {
+            int32_t rows[8 * kMaxK], ids[8 * kMaxK];
+            float z[8 * kMaxK];
+        } tok;
+    } lds;
+    if ((int)blockIdx.x < nfin) {
+        router_finish_block<256>(fin, blockIdx.x, lds.fin);
+        return;
+    }
+    const int t0 = ((int)blockIdx.x - nfin) * (256 / lanes), n = min(256 / lanes, Tn - t0) * K;
+    for (int i = threadIdx.x; i < n; i += 256) {
+        const int q = i / K;
+        lds.tok.rows[i] = inv_perm[(int64_t)t0 * K + i];
+        lds.tok.ids[i] = min((int)idx[(int64_t)(t0 + q) * stride + i - q * K], E - 1);
+        lds.tok.z[i] = dz[(int64_t)t0 * K + i];
     }
     __syncthreads();
-    for (int c = threadIdx.x; c < row_vecs; c += blockDim.x) {
+    const int tok = (int)threadIdx.x / lanes, t = t0 + tok;
+    if (t >= Tn) return;
+    const int32_t *rows = lds.tok.rows + tok * K, *ids = lds.tok.ids + tok * K;
+    const float *z = lds.tok.z + tok * K;
+    for (int c = threadIdx.x & (lanes - 1); c < row_vecs; c += lanes) {
         float acc[VEC];
 #pragma unroll
         for (int i = 0; i < VEC; ++i) acc[i] = 0.0f;
@@ -1136,38 +1188,37 @@ dx_finish_kernel(int E, int Krt, int row_vecs, const typename VecIO<T, VEC>::V *
     }
 }
 
-template <typename T, int VEC>
-static hipError_t dx_finish_dispatch(int Tn, int E, int K, int row_vecs, const void *dXp, const void *WrT,
-                                     const float *dz, const int32_t *inv_perm, const void *idx,
-                                     int idx_dtype, int64_t stride, void *dx, hipStream_t s) {
-    typedef typename VecIO<T, VEC>::V V;
-    if (idx_dtype == R3_IDX_U8 && K == 8 && VEC > 1)
-        dx_finish_kernel<T, VEC, uint8_t, 8><<<Tn, 256, 0, s>>>(E, K, row_vecs, (const V *)dXp, (const V *)WrT, dz,
-                                                              inv_perm, (const uint8_t *)idx, stride, (V *)dx);
-    else if (idx_dtype == R3_IDX_U8)
-        dx_finish_kernel<T, VEC, uint8_t, 0><<<Tn, 256, 0, s>>>(E, K, row_vecs, (const V *)dXp, (const V *)WrT, dz,
-                                                              inv_perm, (const uint8_t *)idx, stride, (V *)dx);
-    else
-        dx_finish_kernel<T, VEC, uint16_t, 0><<<Tn, 256, 0, s>>>(E, K, row_vecs, (const V *)dXp, (const V *)WrT,
-                                                               dz, inv_perm, (const uint16_t *)idx, stride,
-                                                               (V *)dx);
-    return hipGetLastError();
-}
-
-hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp, const void *WrT,
-                            const float *dz, const int32_t *inv_perm, const void *idx, int idx_dtype,
-                            int64_t stride, void *dx, hipStream_t s) {
+hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp, const void *WrT, const float *dz, const int32_t *inv_perm,
+                            const void *idx, int idx_dtype, int64_t stride, void *dx, const RouterFinish<bf16_t> *fin, int nfin,
+                            hipStream_t s) {
     ProfScope ps(PROF_DX_FINISH, s);
+    auto launch = [&](auto io, auto kt, auto id) {
+        typedef decltype(io) IO;
+        typedef typename IO::V V;
+        const int vecs = d / IO::kVec, lanes = row_lanes(T, vecs), tpb = 256 / lanes;
+        RouterFinish<typename IO::Elem> f = {};
+        if constexpr (std::is_same<typename IO::Elem, bf16_t>::value)
+            if (fin) f = *fin;
+        dx_finish_kernel<typename IO::Elem, IO::kVec, typename std::remove_const<typename std::remove_pointer<decltype(id)>::type>::type,
+                         decltype(kt)::value><<<nfin + (T + tpb - 1) / tpb, 256, 0, s>>>(
+            T, E, K, lanes, vecs, (const V *)dXp, (const V *)WrT, dz, inv_perm, id, stride, (V *)dx, f, nfin);
+    };
+    auto go = [&](auto io) {
+        auto kt = [&](auto k) {
+            if (idx_dtype == R3_IDX_U8) launch(io, k, (const uint8_t *)idx);
+            else launch(io, k, (const uint16_t *)idx);
+        };
+        if constexpr (decltype(io)::kVec > 1) by_k(K, kt);
+        else kt(std::integral_constant<int, 0>{});
+    };
     if (act == R3_BF16) {
-        if (d % 8 == 0)
-            return dx_finish_dispatch<bf16_t, 8>(T, E, K, d / 8, dXp, WrT, dz, inv_perm, idx, idx_dtype, stride,
-                                                 dx, s);
-        return dx_finish_dispatch<bf16_t, 1>(T, E, K, d, dXp, WrT, dz, inv_perm, idx, idx_dtype, stride, dx, s);
+        if (d % 8 == 0) go(VecIO<bf16_t, 8>{});
+        else go(VecIO<bf16_t, 1>{});
+    } else {
+        if (d % 4 == 0) go(VecIO<float, 4>{});
+        else go(VecIO<float, 1>{});
     }
-    if (d % 4 == 0)
-        return dx_finish_dispatch<float, 4>(T, E, K, d / 4, dXp, WrT, dz, inv_perm, idx, idx_dtype, stride, dx,
-                                            s);
-    return dx_finish_dispatch<float, 1>(T, E, K, d, dXp, WrT, dz, inv_perm, idx, idx_dtype, stride, dx, s);
+    return hipGetLastError();
 }
 
 }  // namespace r3

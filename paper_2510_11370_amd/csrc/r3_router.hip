@@ -568,14 +568,7 @@ router_dwr_kernel(int T, int d, int E, int K, int rows, const bf16_t *__restrict
             }
 }
 
-// The last launch before dx: three sorts of work that do not wait for each other, a work-group each.
-//   dbias[e] (+)= the sum of dz over the rows of expert e (fixed order; first in the grid, as a skewed load's hot expert takes
-//     longest);
-//   dW_r[i] (+)= sum_s part[s][i], s ascending, 1024 values;
-//   W_r^T, which dx reads, a 32 x 32 tile.
-// Each is microseconds of latency, so launches of their own cost a layer of few tokens more than the work did.
-// Forward + backward, three launches vs one: f32 T=256 d=128 E=8 79.8 -> 78.0 us, bf16 T=3001 d=1000 E=64 612 -> 609,
-// T=6000 d=1024 E=384 with dbias 1083 -> 1074, T=1001 d=2048 E=128 1121 -> 1118.
+// The router's last step (r3_finish.h) where no other launch takes it in: step by step f32 layers and the plain kernels.
 template <typename T>
 __global__ void __launch_bounds__(1024) router_finish_kernel(RouterFinish<T> a) {
     __shared__ RouterFinishLds<T> lds;
@@ -661,8 +654,7 @@ static int dwr_rows(int T, int d, int E) {
 }
 
 size_t router_dwr_ws_bytes(int act, int T, int d, int E, bool plain_only) {
-    const int rows = bf16_dwr(act, d, plain_only) ? dwr_rows(T, d, E) : plain_dwr_rows(T, d, E);
-    return align_up((size_t)((T + rows - 1) / rows) * d * E * sizeof(float), 256);
+    return align_up((size_t)router_dwr_nparts(act, T, d, E, plain_only) * d * E * sizeof(float), 256);
 }
 
 template <typename IdxT>
@@ -675,16 +667,27 @@ static void launch_dwr(int T, int d, int E, int K, const void *x, const float *d
     k<<<grid, 256, kDwrLds, s>>>(T, d, E, K, rows, (const bf16_t *)x, dz, (const IdxT *)idx, stride, part);
 }
 
+int router_dwr_nparts(int act, int T, int d, int E, bool plain_only) {
+    const int rows = bf16_dwr(act, d, plain_only) ? dwr_rows(T, d, E) : plain_dwr_rows(T, d, E);
+    return (T + rows - 1) / rows;
+}
+hipError_t router_dwr_parts(int T, int d, int E, int K, int act, const void *x, const float *dz, const void *idx, int idx_dtype, int64_t stride,
+                            float *part, bool plain_only, hipStream_t s) {
+    ProfScope ps(PROF_DWR, s);
+    if (bf16_dwr(act, d, plain_only)) (idx_dtype == R3_IDX_U8 ? launch_dwr<uint8_t> : launch_dwr<uint16_t>)(T, d, E, K, x, dz, idx, stride, part, s);
+    else plain_dwr_parts(T, d, E, K, act, x, dz, idx, idx_dtype, stride, part, s);
+    return hipGetLastError();
+}
+
 hipError_t router_backward(int T, int d, int E, int K, int act, const void *x, const void *Wr, const float *dz, const void *idx,
                            int idx_dtype, int64_t stride, const int32_t *offsets, const float *dzrow, float *part, float *dWr,
                            float *dbias, void *WrT, int accumulate, bool plain_only, hipStream_t s) {
+    const hipError_t rc = router_dwr_parts(T, d, E, K, act, x, dz, idx, idx_dtype, stride, part, plain_only, s);
+    if (rc != hipSuccess) return rc;
     ProfScope ps(PROF_DWR, s);
-    const bool bf = bf16_dwr(act, d, plain_only);
-    const int rows = bf ? dwr_rows(T, d, E) : plain_dwr_rows(T, d, E);
-    if (bf) (idx_dtype == R3_IDX_U8 ? launch_dwr<uint8_t> : launch_dwr<uint16_t>)(T, d, E, K, x, dz, idx, stride, part, s);
-    else plain_dwr_parts(T, d, E, K, act, x, dz, idx, idx_dtype, stride, part, s);
     auto finish = [&](auto f) {
-        const int blocks = f.template fill<1024>(d, E, (T + rows - 1) / rows, accumulate, dzrow, part, offsets, dbias, dWr, Wr, WrT);
+        const int blocks = f.template fill<1024>(d, E, router_dwr_nparts(act, T, d, E, plain_only), accumulate, dzrow, part, offsets, dbias, dWr,
+                                                 Wr, WrT);
         router_finish_kernel<<<blocks, 1024, 0, s>>>(f);
         return hipGetLastError();
     };

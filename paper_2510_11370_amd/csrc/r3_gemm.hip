@@ -39,38 +39,42 @@ __device__ __forceinline__ int dealt_position(int rank, int n) {
     const int j = rank >> 3, c = rank & 7;
     return ((j & 1) ? 7 - c : c) * (n >> 3) + j;
 }
-// rnk[i] = number of items that come before item i when the n items are sorted by descending key, ties
+// rnk[i] = number of items that come before item i when the n items (a multiple of 8) are sorted by descending key, ties
 // by index.  A block of 1024 threads; an item's comparisons are shared out among 1024 / n' threads (n' = n
 // rounded up to a power of two) and added up in LDS.  (One thread per item walking all n keys is a
-// chain of n dependent LDS reads: 6 us at n = 128.)
-template <class Key>
-__device__ __forceinline__ void block_ranks(int n, Key key, int32_t *rnk) {
+// chain of n dependent LDS reads: 6 us at n = 128.)  Bound by the comparisons: four keys a read, and as the items of a wave are neighbours,
+// ties matter one way before them and the other way after, so that a comparison is two instructions but for their own.  With the index compared
+// every time this kernel took 18.4 us at 384 experts, 11.0 at 256, 9.5 at 128; now 11.9, 8.6 and 8.8.
+// keys: 16-byte aligned.
+__device__ __forceinline__ int ranked_before(const int32_t *keys, int o0, int o1, int i) {
+    const int k = keys[i], w0 = __builtin_amdgcn_readfirstlane(i & ~(kWave - 1));
+    int r = 0;
+    auto count = [&](int from, int to, auto below) {
+        for (int o = from; o < to; o += 4) {
+            const int4 m = *(const int4 *)(keys + o);
+            r += (m.x > below(o)) + (m.y > below(o + 1)) + (m.z > below(o + 2)) + (m.w > below(o + 3));
+        }
+    };
+    const int a = max(o0, min(o1, w0)), b = max(a, min(o1, w0 + kWave));
+    count(o0, a, [&](int) { return k - 1; });
+    count(a, b, [&](int o) { return o < i ? k - 1 : k; });
+    count(b, o1, [&](int) { return k; });
+    return r;
+}
+__device__ __forceinline__ void block_ranks(int n, const int32_t *keys, int32_t *rnk) {
     for (int i = threadIdx.x; i < n; i += 1024) rnk[i] = 0;
     __syncthreads();
     if (n <= 1024) {
-        int np2 = 1;
+        int np2 = kWave;   // (whole waves share a part)
         while (np2 < n) np2 <<= 1;
         const int sub = 1024 / np2, i = threadIdx.x % np2, part = threadIdx.x / np2;
-        const int per = (n + sub - 1) / sub, o0 = min(n, part * per), o1 = min(n, o0 + per);
+        const int per = ((n + sub - 1) / sub + 3) & ~3, o0 = min(n, part * per), o1 = min(n, o0 + per);
         if (i < n) {
-            const int k = key(i);
-            int r = 0;
-            for (int o = o0; o < o1; ++o) {
-                const int m = key(o);
-                r += (m > k) || (m == k && o < i);
-            }
+            const int r = ranked_before(keys, o0, o1, i);
             if (r) atomicAdd(&rnk[i], r);
         }
     } else {
-        for (int i = threadIdx.x; i < n; i += 1024) {
-            const int k = key(i);
-            int r = 0;
-            for (int o = 0; o < n; ++o) {
-                const int m = key(o);
-                r += (m > k) || (m == k && o < i);
-            }
-            rnk[i] = r;
-        }
+        for (int i = threadIdx.x; i < n; i += 1024) rnk[i] = ranked_before(keys, 0, n, i);
     }
     __syncthreads();
 }
@@ -95,7 +99,7 @@ build_row_tiles_kernel(int E, int BQ, const int32_t *__restrict__ offsets, int32
     __shared__ int32_t start[kMaxE + 1];
     __shared__ int32_t off[kMaxE + 1];
     __shared__ int32_t seg0[kMaxE + 1];     // first segment of expert e
-    __shared__ int32_t seglen[kMaxSegs];    // rows of every segment (-1: padding)
+    __shared__ __attribute__((aligned(16))) int32_t seglen[kMaxSegs];    // rows of every segment (-1: padding)
     __shared__ int32_t rnk[kMaxSegs];
     __shared__ int32_t nseg_s;
     // the offsets come in once, in parallel (read one by one by a single thread they cost a memory
@@ -182,7 +186,7 @@ build_row_tiles_kernel(int E, int BQ, const int32_t *__restrict__ offsets, int32
     for (int i = seg0[E] + threadIdx.x; i < nseg; i += blockDim.x) seglen[i] = -1;
     __syncthreads();
     // rank every segment by length (ties by position) and write it where it is dealt to
-    block_ranks(nseg, [&](int i) { return seglen[i]; }, rnk);
+    block_ranks(nseg, seglen, rnk);
     for (int e = threadIdx.x; e < E; e += blockDim.x) {
         const int n = off[e + 1] - off[e], parts = seg0[e + 1] - seg0[e];
         const int len = parts > 1 ? ((n + parts - 1) / parts + 31) & ~31 : n;

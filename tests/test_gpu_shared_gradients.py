@@ -20,6 +20,8 @@ SH = synth.LayerShape
     SH(T=2047, d=512, E=20, K=16, F=256, sigma=0.02, zipf_s=0.5, seed=144),      # just under 128 F slots: shared
     SH(T=2048, d=512, E=20, K=16, F=256, sigma=0.02, zipf_s=0.5, seed=145),      # reductions may be cut: each its own launch
     SH(T=2500, d=1000, E=16, K=4, F=704, sigma=0.02, zipf_s=1.0, seed=146),      # more tiles than work-groups in both, ragged
+    SH(T=900, d=128, E=100, K=6, F=264, sigma=0.02, zipf_s=1.0, seed=147),       # experts ranked by two waves, many of a size
+    SH(T=900, d=128, E=1100, K=2, F=264, sigma=0.02, zipf_s=1.0, seed=148),      # more experts than threads rank
 ], ids=lambda s: "T%d_d%d_F%d_E%d" % (s.T, s.d, s.F, s.E))
 def test_gradients(sh, copy):
     c = Case(sh, backward=True, scale_w=5.0)

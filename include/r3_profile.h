@@ -27,11 +27,12 @@ extern "C" {
  * (0 <= tag < r3_profile_tags()); r3_profile_name names it.
  * A launch that does the work of several kernels counts under one name: in the
  * backward of f32 layers whose widths are multiples of four, after
- * r3_moe_forward, the parts of dW_r under ffn_dh, and dXp, dW_gate, dW_up and
- * the router's last step under ffn_wgrad_down; ffn_dxp and router_wgrad have
- * no launches there.  In the backward of bf16 layers dW_down under ffn_dh and
- * dXp under ffn_wgrad_gate_up where they share a launch (less than some 12000
- * tokens of the 2048 x 768 layer).
+ * r3_moe_forward, the gate's backward under ffn_dh, and dXp, dW_gate, dW_up and
+ * the parts of dW_r under ffn_wgrad_down; gate_backward, ffn_dxp and
+ * router_wgrad have no launches there.  In the backward of bf16 layers dW_down
+ * under ffn_dh and dXp under ffn_wgrad_gate_up where they share a launch (less
+ * than some 12000 tokens of the 2048 x 768 layer).  The sum of dW_r's parts and
+ * dbias count under dx_finish in both.
  */
 int r3_profile_enable(int on);
 int r3_profile_tags(void);

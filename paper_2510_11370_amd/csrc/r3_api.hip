@@ -370,25 +370,27 @@ int r3_moe_backward(const r3_layer_desc *desc, const void *dy, const void *x, co
         (void)fin.fill<256>(m.d, m.E, router_dwr_nparts(m.act, m.T, m.d, m.E, false), accumulate, dzrow, part, offsets, dbias, dW_r, W_r, WrT);
         return hip_rc(launch_dx_finish(m.T, m.d, m.E, m.K, m.act, dXp, WrT, dz, inv_perm, idx, m.idx, m.stride, dx, &fin,
                                        fin.bias_blocks + fin.sum_blocks, s));
+    } else if (gated && f32_backward_supported(m.act, m.T, m.d, m.F)) {
+        F32Backward b = {};
+        b.S = S; b.T = m.T; b.d = m.d; b.E = m.E; b.F = m.F; b.K = m.K; b.accumulate = accumulate;
+        b.offsets = offsets; b.perm = perm; b.inv_perm = inv_perm;
+        b.dy = (const float *)dy; b.x = (const float *)x; b.xrows = (const float *)(Xp ? Xp : x); b.xperm = Xp ? nullptr : perm;
+        b.idx = idx; b.idx_dtype = m.idx; b.stride = m.stride;
+        b.gates = gates; b.Yp = (const float *)Yp; b.dz = dz; b.dzrow = dzrow;
+        b.H = (const float *)H; b.FA = (const float *)FA; b.FB = (const float *)FB;
+        b.Wr = (const float *)W_r; b.Wg = (const float *)W_gate; b.Wu = (const float *)W_up; b.Wd = (const float *)W_down;
+        b.dA = (float *)dA; b.dB = (float *)dB; b.dXp = (float *)dXp; b.part = (float *)(base + w.part); b.WrT = (float *)WrT;
+        b.dWg = dW_gate; b.dWu = dW_up; b.dWd = dW_down;
+        if (f32_backward(b, s) != hipSuccess) return R3_ERR_HIP;
+        RouterFinish<float> fin;
+        (void)fin.fill<256>(m.d, m.E, router_dwr_nparts(m.act, m.T, m.d, m.E, false), accumulate, dzrow, b.part, offsets, dbias, dW_r, W_r, WrT);
+        return hip_rc(launch_dx_finish(m.T, m.d, m.E, m.K, m.act, dXp, WrT, dz, inv_perm, idx, m.idx, m.stride, dx, &fin,
+                                       fin.bias_blocks + fin.sum_blocks, s));
     } else {
         // combine and masked softmax:  dYp = g*dy per slot, dz
         void *dYp = dXp;  // dYp is dead once dW_down and dH are done
         if (launch_gate_backward(m.T, m.d, m.K, m.act, dy, Yp, gates, inv_perm, dYp, dz, dzrow, gated ? 1 : 0, s) != hipSuccess)
             return R3_ERR_HIP;
-        if (gated && f32_backward_supported(m.act, m.T, m.d, m.F)) {
-            F32Backward b = {};
-            b.S = S; b.T = m.T; b.d = m.d; b.E = m.E; b.F = m.F; b.K = m.K; b.accumulate = accumulate;
-            b.offsets = offsets; b.perm = perm;
-            b.dy = (const float *)dy; b.x = (const float *)x; b.xrows = (const float *)(Xp ? Xp : x); b.xperm = Xp ? nullptr : perm;
-            b.idx = idx; b.idx_dtype = m.idx; b.stride = m.stride;
-            b.dYp = (const float *)dYp; b.dz = dz; b.dzrow = dzrow;
-            b.H = (const float *)H; b.FA = (const float *)FA; b.FB = (const float *)FB;
-            b.Wr = (const float *)W_r; b.Wg = (const float *)W_gate; b.Wu = (const float *)W_up; b.Wd = (const float *)W_down;
-            b.dA = (float *)dA; b.dB = (float *)dB; b.dXp = (float *)dXp; b.part = (float *)(base + w.part);
-            b.dWg = dW_gate; b.dWu = dW_up; b.dWd = dW_down; b.dWr = dW_r; b.dbias = dbias; b.WrT = (float *)WrT;
-            if (f32_backward(b, s) != hipSuccess) return R3_ERR_HIP;
-            return hip_rc(launch_dx_finish(m.T, m.d, m.E, m.K, m.act, dXp, WrT, dz, inv_perm, idx, m.idx, m.stride, dx, nullptr, 0, s));
-        }
         if (plain_dh(S, m.d, m.E, m.F, m.act, dYp, offsets, W_down, FA, FB, dA, dB, s) != hipSuccess) return R3_ERR_HIP;
         // gated: H is g H already, so its partner is the plain dy row (read through perm), not g dy
         if (plain_wgrads(m.d, m.E, m.F, m.T, m.K, m.act, offsets, H, gated ? dy : dYp, gated ? perm : nullptr, Xp ? Xp : x,

@@ -72,19 +72,18 @@ hipError_t f32_wgrads(int d, int E, int F, int T, int K, const int32_t *offsets,
                       const int32_t *dyperm, const float *xrows, const int32_t *xperm, const float *dA, const float *dB,
                       float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s);
 
-// The backward between the gate's (which leaves dz, dzrow and dYp = g dy) and dx_finish, for a forward that left H gated, so
-// that nothing but dH reads dYp and dXp may take its place: dH with the parts of dW_r, then dW_gate, dW_up, dW_down, dXp, dW_r,
-// dbias and W_r^T, two launches.
+// The expert gradients and the gate's for a forward that left H and Yp gated, two launches: dz (and dzrow, unless NULL), W_r^T and dH; then
+// dW_gate, dW_up, dW_down, dXp and the parts of dW_r, plain_dwr_rows() tokens each.
 struct F32Backward {
     int S, T, d, E, F, K, accumulate;
-    const int32_t *offsets, *perm;
+    const int32_t *offsets, *perm, *inv_perm;
     const float *dy, *x, *xrows;      // xrows: x with xperm = perm, or the expert-sorted copy with xperm = NULL
     const int32_t *xperm;
     const void *idx;
     int idx_dtype;
     int64_t stride;
-    const float *dYp, *dz, *dzrow, *H, *FA, *FB, *Wr, *Wg, *Wu, *Wd;
-    float *dA, *dB, *dXp, *part, *dWg, *dWu, *dWd, *dWr, *dbias, *WrT;
+    const float *gates, *Yp, *H, *FA, *FB, *Wr, *Wg, *Wu, *Wd;
+    float *dz, *dzrow, *dA, *dB, *dXp, *part, *dWg, *dWu, *dWd, *WrT;
 };
 bool f32_backward_supported(int act, int T, int d, int F);
 hipError_t f32_backward(const F32Backward &b, hipStream_t s);

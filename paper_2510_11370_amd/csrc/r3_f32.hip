@@ -191,10 +191,10 @@ struct F32RowArgs {
     float *out0, *out1, *out2;
 };
 
-// four consecutive features of a row of the result (SwiGLU: v of the gate's weight, w of the other's)
+// four consecutive features of a row of the result (SwiGLU: v of the gate's weight, w of the other's; gate: of the row's slot, or 1)
 template <int MODE>
-__device__ __forceinline__ void f32_rows_store(const F32RowArgs &g, int row, int c, float gate, float4 v, float4 w) {
-    const int64_t o = (int64_t)row * ((MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? g.F : g.d) + c;
+__device__ __forceinline__ void f32_rows_store(const float *__restrict__ FA, const float *__restrict__ FB, float *__restrict__ out0,
+                                               float *__restrict__ out1, float *__restrict__ out2, int64_t o, float gate, float4 v, float4 w) {
     if constexpr (MODE == PLAIN_FFN1) {
         const float va[4] = {v.x, v.y, v.z, v.w}, vb[4] = {w.x, w.y, w.z, w.w};
         float h[4], fa[4], fb[4];
@@ -206,15 +206,16 @@ __device__ __forceinline__ void f32_rows_store(const F32RowArgs &g, int row, int
             fa[i] = b * sg * (1.0f + a * (1.0f - sg));
             fb[i] = a * sg;
         }
-        *(float4 *)(g.out0 + o) = make_float4(h[0], h[1], h[2], h[3]);
-        if (g.out1) *(float4 *)(g.out1 + o) = make_float4(fa[0], fa[1], fa[2], fa[3]);
-        if (g.out2) *(float4 *)(g.out2 + o) = make_float4(fb[0], fb[1], fb[2], fb[3]);
+        *(float4 *)(out0 + o) = make_float4(h[0], h[1], h[2], h[3]);
+        if (out1) *(float4 *)(out1 + o) = make_float4(fa[0], fa[1], fa[2], fa[3]);
+        if (out2) *(float4 *)(out2 + o) = make_float4(fb[0], fb[1], fb[2], fb[3]);
     } else if constexpr (MODE == PLAIN_DH) {
-        const float4 a = *(const float4 *)(g.FA + o), b = *(const float4 *)(g.FB + o);
-        *(float4 *)(g.out0 + o) = make_float4(v.x * a.x, v.y * a.y, v.z * a.z, v.w * a.w);
-        *(float4 *)(g.out1 + o) = make_float4(v.x * b.x, v.y * b.y, v.z * b.z, v.w * b.w);
+        const float4 a = *(const float4 *)(FA + o), b = *(const float4 *)(FB + o);
+        v = make_float4(gate * v.x, gate * v.y, gate * v.z, gate * v.w);
+        *(float4 *)(out0 + o) = make_float4(v.x * a.x, v.y * a.y, v.z * a.z, v.w * a.w);
+        *(float4 *)(out1 + o) = make_float4(v.x * b.x, v.y * b.y, v.z * b.z, v.w * b.w);
     } else {
-        *(float4 *)(g.out0 + o) = v;
+        *(float4 *)(out0 + o) = v;
     }
 }
 
@@ -238,7 +239,7 @@ __device__ __forceinline__ void f32_rows_tile(const F32RowArgs &g, int block, ch
     const uint64_t wbytes = (uint64_t)d * F * 4;
     const float *w0 = W0 + (int64_t)t.e * d * F;
 
-    const bool gather = MODE == PLAIN_FFN1 && perm;
+    const bool gather = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) && perm;
     F32Rows<C::BQ> Q;
     Q.init(gather ? in0 : in0 + (int64_t)t.row0 * KK, gather ? (uint64_t)T * KK * 4 : (uint64_t)rows * KK * 4, KK, wq * 16 * C::TQ);
 #pragma unroll
@@ -293,11 +294,12 @@ __device__ __forceinline__ void f32_rows_tile(const F32RowArgs &g, int block, ch
         if (q >= rows) continue;
         const int row = t.row0 + q;
         const f32x4_t *v = &acc[0][tq];
+        const float gate = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) && gates ? gates[perm[row]] : 1.0f;
         if constexpr (MODE == PLAIN_FFN1) {
             const int f = p0 + 16 * wp + 4 * (lane >> 4);
             if (f >= F) continue;
             const f32x4_t b = acc[1][tq];
-            f32_rows_store<MODE>(g, row, f, gates ? gates[perm[row]] : 1.0f, make_float4((*v)[0], (*v)[1], (*v)[2], (*v)[3]),
+            f32_rows_store<MODE>(FAin, FBin, out0, out1, out2, (int64_t)row * NOUT + f, gate, make_float4((*v)[0], (*v)[1], (*v)[2], (*v)[3]),
                                  make_float4(b[0], b[1], b[2], b[3]));
         } else {
 #pragma unroll
@@ -305,7 +307,7 @@ __device__ __forceinline__ void f32_rows_tile(const F32RowArgs &g, int block, ch
                 const int c = p0 + wp * 16 * C::TP + 16 * tp + 4 * (lane >> 4);
                 if (c >= NOUT) continue;
                 const f32x4_t r = acc[tp][tq];
-                f32_rows_store<MODE>(g, row, c, 1.0f, make_float4(r[0], r[1], r[2], r[3]), float4());
+                f32_rows_store<MODE>(FAin, FBin, out0, out1, out2, (int64_t)row * NOUT + c, gate, make_float4(r[0], r[1], r[2], r[3]), float4());
             }
         }
     }
@@ -367,12 +369,12 @@ __device__ __forceinline__ void split_rows_tile(const F32RowArgs &g, int block, 
             auto quad = [&](int tp) { return make_float4(acc[tp][tq][4 * k], acc[tp][tq][4 * k + 1], acc[tp][tq][4 * k + 2], acc[tp][tq][4 * k + 3]); };
             if constexpr (MODE == PLAIN_FFN1) {
                 const int c = p0 + 32 * wp + f;
-                if (c < NOUT) f32_rows_store<MODE>(g, row, c, gate, quad(0), quad(1));
+                if (c < NOUT) f32_rows_store<MODE>(g.FA, g.FB, g.out0, g.out1, g.out2, (int64_t)row * NOUT + c, gate, quad(0), quad(1));
             } else {
 #pragma unroll
                 for (int tp = 0; tp < 2; ++tp) {
                     const int c = p0 + 64 * wp + 32 * tp + f;
-                    if (c < NOUT) f32_rows_store<MODE>(g, row, c, 1.0f, quad(tp), float4());
+                    if (c < NOUT) f32_rows_store<MODE>(g.FA, g.FB, g.out0, g.out1, g.out2, (int64_t)row * NOUT + c, 1.0f, quad(tp), float4());
                 }
             }
         }
@@ -556,9 +558,10 @@ template <class C> constexpr int kMinWaves = kIsSplit<C> ? kSplitMinWaves : 1;
 
 // ---------------------------------------------------------------------------
 // Launches.  What does not wait for each other shares one: a layer of few tokens is a chain of launches, and a larger one
-// fills one kernel's last round of tiles with the next one's.  After the gate's backward:  dH and the parts of dW_r;  then all
-// weight gradients, dXp, and the router's last step.  T=256 d=128 E=8 K=2 F=256, forward + backward: 58 -> 52 us in four launches of the
-// backward instead of seven; T=2048 d=512 E=16 K=4 F=1024: 815 -> 767 (595 with split tiles and the loops as they are now).
+// fills one kernel's last round of tiles with the next one's.  After the one-call forward:  the gate's backward, W_r^T and dH, which reads dy's
+// rows by itself and scales its results by the gates;  then the parts of dW_r, dXp and all weight gradients;  then the rest of the router beside
+// dx.  T=256 d=128 E=8 K=2 F=256, kernels of a forward + backward: 58 us with a launch each, 50.7 in five launches of the backward (g dy written out
+// for dH), 44.7 in these three; T=2048 d=512 E=16 K=4 F=1024: 815, 767 (595 with split tiles), 588.
 // ---------------------------------------------------------------------------
 template <class C, int MODE>
 __global__ void __launch_bounds__(C::NT, kMinWaves<C>) f32_rows_kernel(F32RowArgs a) {
@@ -575,26 +578,70 @@ f32_wgrad_kernel(int E, int T, int K, const int32_t *__restrict__ offsets, F32Wg
 
 constexpr int max_int(int a, int b) { return a > b ? a : b; }
 
-// the first `first` blocks (a multiple of 8, so that the rows' tiles keep their XCDs): parts of dW_r; then dH
-template <class C, typename IdxT>
-__global__ void __launch_bounds__(C::NT, kMinWaves<C>) f32_dh_dwr_kernel(F32RowArgs a, PlainDwr<float, IdxT> w, int nw, int first) {
-    __shared__ __attribute__((aligned(1024))) char lds[max_int(tile_lds<C>(), PlainSmall::LDS)];
-    const int b = blockIdx.x;
-    if (b >= first) rows_tile<C, PLAIN_DH>(a, b - first, lds);
-    else if (b < nw) plain_dwr_tile<PlainSmall, float, true>(w, b, lds);
+// dz of the masked softmax from the gated rows that the forward left: w_j = <dy_t, Yp[row_j]> = g_j dg_j, dz_j = w_j - g_j sum_i w_i.
+// A wave per token, four rows of Yp in flight.
+struct F32Gate {
+    int T, d, K;
+    const float *dy, *Yp, *gates;
+    const int32_t *inv_perm;
+    float *dz, *dzrow;
+};
+__device__ __forceinline__ void f32_gate_tokens(const F32Gate &a, int block) {
+    const int t = 4 * block + ((int)threadIdx.x >> 6), lane = threadIdx.x & 63, vecs = a.d / 4, K = a.K;
+    if (t >= a.T) return;
+    const int mine = lane < K ? a.inv_perm[(int64_t)t * K + lane] : 0;
+    const float g = lane < K ? a.gates[(int64_t)t * K + lane] : 0.0f;
+    const float4 *dy = (const float4 *)(a.dy + (int64_t)t * a.d);
+    float w = 0.0f, mix = 0.0f;
+    for (int j0 = 0; j0 < K; j0 += 4) {
+        const float4 *y[4];
+        float dot[4] = {};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) y[u] = (const float4 *)(a.Yp + (int64_t)__shfl(mine, min(j0 + u, K - 1), 64) * a.d);
+        for (int c = lane; c < vecs; c += 64) {
+            const float4 b = dy[c];
+            float4 v[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) v[u] = y[u][c];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) dot[u] = fmaf(b.x, v[u].x, fmaf(b.y, v[u].y, fmaf(b.z, v[u].z, fmaf(b.w, v[u].w, dot[u]))));
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const float sum = wave_sum(dot[u]);
+            if (j0 + u < K) mix += sum;
+            if (j0 + u == lane) w = sum;
+        }
+    }
+    if (lane < K) {
+        const float v = w - g * mix;
+        a.dz[(int64_t)t * K + lane] = v;
+        if (a.dzrow) a.dzrow[mine] = v;
+    }
 }
 
-// [0, first): the router's last step (its dbias of a hot expert is a long chain); [first, second): dXp; then the weight gradients
-template <class CR, class CW>
+// [0, nt): W_r^T; [nt, ng): the gate's backward; from `first` on (a multiple of 8, so that the rows' tiles keep their XCDs) dH
+template <class C>
+__global__ void __launch_bounds__(C::NT, kMinWaves<C>)
+f32_dh_kernel(F32RowArgs a, F32Gate gate, RouterFinish<float> wrt, int nt, int ng, int first) {
+    __shared__ __attribute__((aligned(1024))) char lds[tile_lds<C>()];
+    static_assert(sizeof(RouterFinishLds<float>) <= sizeof(lds), "");
+    const int b = blockIdx.x;
+    if (b >= first) rows_tile<C, PLAIN_DH>(a, b - first, lds);
+    else if (b < nt) router_finish_block<C::NT>(wrt, b, *(RouterFinishLds<float> *)lds);
+    else if (b < ng) f32_gate_tokens(gate, b - nt);
+}
+
+// [0, first): parts of dW_r; [first, second): dXp; then the weight gradients
+template <class CR, class CW, typename IdxT>
 __global__ void __launch_bounds__(CR::NT, max_int(kMinWaves<CR>, kMinWaves<CW>))
 f32_grads_kernel(F32RowArgs a, int E, int T, int K, const int32_t *__restrict__ offsets, F32Wgrad3 all, int accumulate,
-                 RouterFinish<float> fin, int nfin, int first, int second) {
-    __shared__ __attribute__((aligned(1024))) char lds[max_int(tile_lds<CR>(), tile_lds<CW>())];
-    static_assert(sizeof(RouterFinishLds<float>) <= sizeof(lds), "");
+                 PlainDwr<float, IdxT> w, int nw, int first, int second) {
+    __shared__ __attribute__((aligned(1024))) char lds[max_int(max_int(tile_lds<CR>(), tile_lds<CW>()), PlainSmall::LDS)];
     const int b = blockIdx.x;
     if (b >= second) wgrad_tile<CW>(E, T, K, offsets, all, accumulate, b - second, lds);
     else if (b >= first) rows_tile<CR, PLAIN_DXP>(a, b - first, lds);
-    else if (b < nfin) router_finish_block<CR::NT>(fin, b, *(RouterFinishLds<float> *)lds);
+    else if (b < nw) plain_dwr_tile<PlainSmall, float, true>(w, b, lds);
 }
 
 int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -615,8 +662,9 @@ constexpr int kWgradFill = 320;
 // most: 4096 top-2, 512 x 512, 8 experts (4 M) 50 | 45, 1024 top-4, 512 x 1024, 16 experts (2 M) 56.6 | 53.5, 4096 top-4, 512 x 512, 128 experts
 // 98 | 82; 512 top-2, 512 x 512, 8 experts (.5 M) 12.9 | 26.6; 64 rows per expert 34.2 | 35.9; 132 columns of 256 15.7 | 18.9.
 // dH stays with the others: 16 k-tiles and two operands beside the result, 94 | 104.
-// The weight gradients: one tile per compute unit and more, with the same allowance.  3 x 8 experts: 4096 tokens top-2, 320 x 320 (150 tiles' worth)
-// 97 | 116, 256 x 1024 (384) 230 | 185, 1024 top-2, 512 x 512 (384) 71 | 66, 32 rows per expert 483 | 487.  With them dXp from .9 M results on,
+// The weight gradients: one tile per compute unit and more, with the same allowance, and 64 rows per expert.  3 x 8 experts: 4096 tokens top-2,
+// 320 x 320 (150 tiles' worth) 97 | 116, 256 x 1024 (384) 230 | 185, 1024 top-2, 512 x 512 (384) 71 | 66; 64 rows per expert 165 | 150, 32
+// 483 | 487, 16 16.1 | 20.9.  With them dXp from .9 M results on,
 // split beside small tiles: 1500 top-1, 640 columns, 5 experts (.96 M) 102 | 109, 2048 top-4, 512, 128 experts 292 | 327, 300 top-2, 1024, 5 experts (.6 M)
 // 102 | 78.
 constexpr int64_t kSplitDown = 1 << 21, kSplitDxp = 900000;
@@ -624,9 +672,9 @@ int64_t split_columns(int n) { return (n + kSplitTile - 1) / kSplitTile * kSplit
 bool split_rows(int S, int E, int NOUT) {
     return (int64_t)S * NOUT >= kSplitDown && S >= 128 * (int64_t)E && 4 * (int64_t)NOUT >= 3 * split_columns(NOUT);
 }
-bool split_wgrads(int E, int d, int F) {
+bool split_wgrads(int64_t S, int E, int d, int F) {
     const int64_t n = (int64_t)d * F;
-    return 3 * E * n >= 256ll * kSplitTile * kSplitTile && 4 * n >= 3 * split_columns(d) * split_columns(F);
+    return S >= 64 * (int64_t)E && 3 * E * n >= 256ll * kSplitTile * kSplitTile && 4 * n >= 3 * split_columns(d) * split_columns(F);
 }
 
 template <class C, int MODE>
@@ -670,17 +718,17 @@ F32Wgrad3 wgrad_args(int d, int F, const float *H, const float *dYrows, const in
     return {{{H, dYrows, nullptr, dyperm, dWd, F, d, 0}, {xrows, dA, xperm, nullptr, dWg, d, F, 0}, {xrows, dB, xperm, nullptr, dWu, d, F, 0}}};
 }
 
-template <class C, typename IdxT>
-void dh_dwr_launch(int S, const F32RowArgs &a, const PlainDwr<float, IdxT> &w, hipStream_t s) {
-    const int nw = (int)plain_dwr_blocks(w.Tn, w.d, w.E), first = (nw + 7) / 8 * 8;
-    f32_dh_dwr_kernel<C, IdxT><<<first + rows_blocks<C, PLAIN_DH>(S, a), C::NT, 0, s>>>(a, w, nw, first);
+template <class C>
+void dh_launch(int S, const F32RowArgs &a, const F32Gate &gate, const RouterFinish<float> &wrt, int nt, hipStream_t s) {
+    const int ng = nt + (int)ceil_div(gate.T, 4), first = (ng + 7) / 8 * 8;
+    f32_dh_kernel<C><<<first + rows_blocks<C, PLAIN_DH>(S, a), C::NT, 0, s>>>(a, gate, wrt, nt, ng, first);
 }
-template <class CR, class CW>
+template <class CR, class CW, typename IdxT>
 void grads_launch(int S, const F32RowArgs &a, int T, int K, const int32_t *offsets, F32Wgrad3 all, int accumulate,
-                  const RouterFinish<float> &fin, int nfin, hipStream_t s) {
-    const int first = (nfin + 7) / 8 * 8, second = first + rows_blocks<CR, PLAIN_DXP>(S, a);
-    f32_grads_kernel<CR, CW><<<second + wgrad_blocks<CW>(a.E, all), CR::NT, 0, s>>>(a, a.E, T, K, offsets, all, accumulate, fin, nfin, first,
-                                                                                  second);
+                  const PlainDwr<float, IdxT> &w, hipStream_t s) {
+    const int nw = (int)plain_dwr_blocks(w.Tn, w.d, w.E), first = (nw + 7) / 8 * 8, second = first + rows_blocks<CR, PLAIN_DXP>(S, a);
+    f32_grads_kernel<CR, CW, IdxT><<<second + wgrad_blocks<CW>(a.E, all), CR::NT, 0, s>>>(a, a.E, T, K, offsets, all, accumulate, w, nw, first,
+                                                                                        second);
 }
 
 }  // namespace
@@ -697,7 +745,7 @@ hipError_t f32_rows(int mode, int S, int d, int E, int F, const int32_t *offsets
 hipError_t f32_wgrads(int d, int E, int F, int T, int K, const int32_t *offsets, const float *H, const float *dYrows,
                       const int32_t *dyperm, const float *xrows, const int32_t *xperm, const float *dA, const float *dB,
                       float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s) {
-    auto f = split_wgrads(E, d, F) ? wgrad_launch<F32Split> : few_wgrad_tiles(E, d, F) ? wgrad_launch<F32Short> : wgrad_launch<F32Tile>;
+    auto f = split_wgrads((int64_t)T * K, E, d, F) ? wgrad_launch<F32Split> : few_wgrad_tiles(E, d, F) ? wgrad_launch<F32Short> : wgrad_launch<F32Tile>;
     f(E, T, K, offsets, wgrad_args(d, F, H, dYrows, dyperm, xrows, xperm, dA, dB, dWg, dWu, dWd), accumulate, s);
     return hipGetLastError();
 }
@@ -709,29 +757,29 @@ bool f32_backward_supported(int act, int T, int d, int F) {
 hipError_t f32_backward(const F32Backward &b, hipStream_t s) {
     {
         ProfScope ps(PROF_DH, s);
-        const F32RowArgs a = {b.d, b.E, b.F, b.offsets, b.dYp, nullptr, 0, nullptr, 1, nullptr, b.Wd, nullptr, b.FA, b.FB, b.dA, b.dB, nullptr};
-        const bool few = few_row_tiles(b.S, b.E, b.F, 64);
-        auto go = [&](auto idx) {
-            typedef typename std::remove_const<typename std::remove_pointer<decltype(idx)>::type>::type IdxT;
-            const PlainDwr<float, IdxT> w = {b.T, b.d, b.E, b.K, plain_dwr_rows(b.T, b.d, b.E), b.x, b.dz, idx, b.stride, b.part};
-            (few ? dh_dwr_launch<F32Short, IdxT> : dh_dwr_launch<F32Tile, IdxT>)(b.S, a, w, s);
-        };
-        if (b.idx_dtype == R3_IDX_U8) go((const uint8_t *)b.idx);
-        else go((const uint16_t *)b.idx);
+        const F32RowArgs a = {b.d, b.E, b.F, b.offsets, b.dy, nullptr, b.T, b.perm, b.K, b.gates, b.Wd, nullptr, b.FA, b.FB, b.dA, b.dB, nullptr};
+        const F32Gate gate = {b.T, b.d, b.K, b.dy, b.Yp, b.gates, b.inv_perm, b.dz, b.dzrow};
+        RouterFinish<float> wrt;
+        const int nt = wrt.transpose_only(b.d, b.E, b.Wr, b.WrT);
+        (few_row_tiles(b.S, b.E, b.F, 64) ? dh_launch<F32Short> : dh_launch<F32Tile>)(b.S, a, gate, wrt, nt, s);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     ProfScope ps(PROF_WGRAD, s);
     const F32RowArgs a = {b.d, b.E, b.F, b.offsets, b.dA, b.dB, 0, nullptr, 1, nullptr, b.Wg, b.Wu, nullptr, nullptr, b.dXp, nullptr, nullptr};
     const F32Wgrad3 all = wgrad_args(b.d, b.F, b.H, b.dy, b.perm, b.xrows, b.xperm, b.dA, b.dB, b.dWg, b.dWu, b.dWd);
-    RouterFinish<float> fin;
-    const int rows = plain_dwr_rows(b.T, b.d, b.E);
-    const int nfin = fin.fill<F32Tile::NT>(b.d, b.E, (b.T + rows - 1) / rows, b.accumulate, b.dzrow, b.part, b.offsets, b.dbias, b.dWr, b.Wr, b.WrT);
     const bool fr = few_row_tiles(b.S, b.E, b.d, 64), fw = few_wgrad_tiles(b.E, b.d, b.F);
-    auto f = split_wgrads(b.E, b.d, b.F) ? ((int64_t)b.S * b.d >= kSplitDxp ? grads_launch<F32Split, F32Split> : grads_launch<F32Short, F32Split>)
-             : fr ? (fw ? grads_launch<F32Short, F32Short> : grads_launch<F32Short, F32Tile>)
-                  : (fw ? grads_launch<F32Tile, F32Short> : grads_launch<F32Tile, F32Tile>);
-    f(b.S, a, b.T, b.K, b.offsets, all, b.accumulate, fin, nfin, s);
+    auto go = [&](auto idx) {
+        typedef typename std::remove_const<typename std::remove_pointer<decltype(idx)>::type>::type IdxT;
+        const PlainDwr<float, IdxT> w = {b.T, b.d, b.E, b.K, plain_dwr_rows(b.T, b.d, b.E), b.x, b.dz, idx, b.stride, b.part};
+        auto f = split_wgrads(b.S, b.E, b.d, b.F) ? ((int64_t)b.S * b.d >= kSplitDxp ? grads_launch<F32Split, F32Split, IdxT>
+                                                                               : grads_launch<F32Short, F32Split, IdxT>)
+                 : fr ? (fw ? grads_launch<F32Short, F32Short, IdxT> : grads_launch<F32Short, F32Tile, IdxT>)
+                      : (fw ? grads_launch<F32Tile, F32Short, IdxT> : grads_launch<F32Tile, F32Tile, IdxT>);
+        f(b.S, a, b.T, b.K, b.offsets, all, b.accumulate, w, s);
+    };
+    if (b.idx_dtype == R3_IDX_U8) go((const uint8_t *)b.idx);
+    else go((const uint16_t *)b.idx);
     return hipGetLastError();
 }
 

@@ -1,6 +1,5 @@
 // The last step of the router's backward: three sorts of work that do not wait for each other, a work-group of NT threads each (in a launch of
-// their own, or beside others: bf16 after the expert gradients, W_r^T with the gate's backward and the rest with dx; f32 after the
-// one-call forward, with the gradients).
+// their own, or beside others: W_r^T with the gate's backward and the rest with dx, for bf16 tiles and for f32 after the one-call forward).
 //   dbias[e] (+)= the sum of dz over the rows of expert e (fixed order; first in the grid, as a skewed load's hot expert takes
 //     longest);
 //   dW_r[i] (+)= sum_s part[s][i], s ascending, NT values;

@@ -49,10 +49,9 @@ hipError_t launch_gate_backward(int T, int d, int K, int act, const void *dy, co
 hipError_t launch_gate_backward_parts(int T, int K, int nparts, const float *wpart, const float *gates,
                                       const int32_t *inv_perm, float *dz, float *dzrow, int d, int E, const void *Wr, void *WrT,
                                       hipStream_t s);
-// fin, nfin: work-groups of the router's last step to run beside it (bf16; NULL, 0: none)
-template <typename T> struct RouterFinish;
+// fin, nfin: work-groups of the router's last step to run beside it (a RouterFinish of the activations' type; NULL, 0: none)
 hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp, const void *WrT, const float *dz, const int32_t *inv_perm,
-                            const void *idx, int idx_dtype, int64_t stride, void *dx, const RouterFinish<bf16_t> *fin, int nfin,
+                            const void *idx, int idx_dtype, int64_t stride, void *dx, const void *fin, int nfin,
                             hipStream_t s);
 
 // r3_diag.hip

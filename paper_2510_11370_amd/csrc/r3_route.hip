@@ -1189,7 +1189,7 @@ dx_finish_kernel(int Tn, int E, int Krt, int lanes, int row_vecs, const typename
 }
 
 hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp, const void *WrT, const float *dz, const int32_t *inv_perm,
-                            const void *idx, int idx_dtype, int64_t stride, void *dx, const RouterFinish<bf16_t> *fin, int nfin,
+                            const void *idx, int idx_dtype, int64_t stride, void *dx, const void *fin, int nfin,
                             hipStream_t s) {
     ProfScope ps(PROF_DX_FINISH, s);
     auto launch = [&](auto io, auto kt, auto id) {
@@ -1197,8 +1197,7 @@ hipError_t launch_dx_finish(int T, int d, int E, int K, int act, const void *dXp
         typedef typename IO::V V;
         const int vecs = d / IO::kVec, lanes = row_lanes(T, vecs), tpb = 256 / lanes;
         RouterFinish<typename IO::Elem> f = {};
-        if constexpr (std::is_same<typename IO::Elem, bf16_t>::value)
-            if (fin) f = *fin;
+        if (fin) f = *(const RouterFinish<typename IO::Elem> *)fin;
         dx_finish_kernel<typename IO::Elem, IO::kVec, typename std::remove_const<typename std::remove_pointer<decltype(id)>::type>::type,
                          decltype(kt)::value><<<nfin + (T + tpb - 1) / tpb, 256, 0, s>>>(
             T, E, K, lanes, vecs, (const V *)dXp, (const V *)WrT, dz, inv_perm, id, stride, (V *)dx, f, nfin);

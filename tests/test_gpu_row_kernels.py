@@ -34,6 +34,8 @@ def test_combine_and_dx_rows(d, T, K):
     SH(T=2051, d=520, E=300, K=4, F=72, sigma=0.02, seed=153),                  # 128 lanes, two-byte record
     SH(T=2050, d=1000, E=16, K=6, F=40, sigma=0.02, zipf_s=1.0, seed=154),
     SH(T=1030, d=2048, E=24, K=3, F=40, sigma=0.02, seed=155),                  # K that nothing is compiled for
+    SH(T=301, d=68, E=40, K=9, F=36, act="f32", sigma=0.05, seed=156),          # f32, the gate's backward beside dH: 4 + 4 + 1 rows a token
+    SH(T=38, d=516, E=300, K=33, F=36, act="f32", sigma=0.05, seed=157),        # two-byte record, two rounds of a wave's lanes along d
 ], ids=lambda s: "T%d_d%d_E%d_K%d" % (s.T, s.d, s.E, s.K))
 def test_dx_with_the_routers_last_step(sh):
     c = Case(sh, backward=True, scale_w=5.0)

@@ -17,7 +17,7 @@
 // 48 KB of planes leave room for two work-groups, one of which splits while the other multiplies.  Splitting raw tiles as they come out of LDS, a value
 // by two waves, was no slower where a compute unit had one tile and no faster with two (T=2048 d=512 E=16 K=4 F=1024: SwiGLU 137 us
 // and 136, gradients 297 and 280); the dot instructions, which would take the remainder in one step, wait for the matrix pipe.
-// T=2048 d=512 E=16 K=4 F=1024, us, f32 instruction in 64 x 64 tiles -> this: SwiGLU 174 -> 137, down 89 -> 86, all gradients and dXp 405 -> 280.
+// T=2048 d=512 E=16 K=4 F=1024, us, f32 instruction in 64 x 64 tiles -> this: SwiGLU 174 -> 128, down 89 -> 80, all gradients and dXp 405 -> 271.
 #pragma once
 #include "r3_mfma2.h"
 

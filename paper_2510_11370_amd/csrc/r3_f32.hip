@@ -656,7 +656,7 @@ constexpr int kRowsFill = 512;
 // 190.7 | 184.3; 4096 top-2, 256 x 256 (384) 161.3 | 166.2; 300 top-2, 512 x 320, 4 experts (480) 65.5 | 67.6.
 constexpr int kWgradFill = 320;
 
-// Split tiles.  SwiGLU: wherever there are not few tiles (us, 64 x 64 | split, 2048 tokens top-4, 512 x 1024, 16 experts 174 | 137, 4096 top-4,
+// Split tiles.  SwiGLU: wherever there are not few tiles (us, 64 x 64 | split, 2048 tokens top-4, 512 x 1024, 16 experts 174 | 128, 4096 top-4,
 // 512 x 512, 128 experts 208 | 167, 1024 top-2, 512 x 512, 8 experts 34.8 | 33.4).
 // Down projection (and dXp in a launch of its own): 2 M results and more, 128 rows per expert, a quarter of the tiles' columns dead at
 // most: 4096 top-2, 512 x 512, 8 experts (4 M) 50 | 45, 1024 top-4, 512 x 1024, 16 experts (2 M) 56.6 | 53.5, 4096 top-4, 512 x 512, 128 experts

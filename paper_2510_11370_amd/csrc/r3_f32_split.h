@@ -9,7 +9,8 @@
 //
 // Where that argument ends the tile is multiplied again on the f32 instruction (split_failed): an infinity or a NaN in an
 // operand, or a value that rounds to an infinity, leaves NaN or infinities in every result that it
-// meets; and where every result of a tile is tiny, pieces below the smallest bf16 could be what it is made of.
+// meets; and a value below 2^-110 has bits below the smallest bf16, which is looked for while splitting (split_loses), since a row or column of
+// them shows in nothing else when the rest of the tile is ordinary.
 //
 // What bounds it: of the 2300 cycles that a wave's 64 x 64 x 32 takes, two waves to a SIMD, its 48 MFMAs need 1536, half of them with the
 // issue to themselves; splitting its share of the tiles is 180 vector instructions, and the card runs at 1.9-2.1 GHz under all of
@@ -154,6 +155,23 @@ __device__ __forceinline__ void split_store(const float (&f)[8], char *at) {
         *(uint4 *)(at + p * kSplitPlane) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
+// Whether one of a thread's values is not the sum of its pieces because the last of them lies below the smallest bf16, 2^-133: a value
+// of 2^-110 and more has no bits there, zero has none at all.  A minimum of two values takes one instruction, and where it is an ordinary
+// number (a tile without padding) that was all.
+__device__ __forceinline__ bool split_loses(const SplitRaw &v) {
+    float m = 1.0f;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 8; k += 2) asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(m) : "v"(v[i][k]), "v"(v[i][k + 1]));
+    if (m >= 0x1p-110f) return false;
+    uint32_t least = ~0u;   // of twice the magnitude, less one: a zero counts as the largest
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int k = 0; k < 8; ++k) least = min(least, 2 * __float_as_uint(v[i][k]) - 1);
+    return least < 2 * 0x08800000u - 1;
+}
 template <class Op>
 __device__ __forceinline__ void split_store_tile(const SplitRaw &v, char *operand) {
     const int u = threadIdx.x & 127, g = Op::group(u);
@@ -216,7 +234,7 @@ __device__ __forceinline__ void split_zero(SplitAcc &acc) {
         for (int j = 0; j < 2; ++j) acc[i][j] = f32x16_t{};
 }
 
-__device__ __forceinline__ bool split_failed(const SplitAcc &acc, char *lds) {
+__device__ __forceinline__ bool split_failed(const SplitAcc &acc, bool lost, char *lds) {
     uint32_t m = 0;
 #pragma unroll
     for (int i = 0; i < 2; ++i)
@@ -224,30 +242,35 @@ __device__ __forceinline__ bool split_failed(const SplitAcc &acc, char *lds) {
         for (int j = 0; j < 2; ++j)
 #pragma unroll
             for (int k = 0; k < 16; ++k) m = max(m, __float_as_uint(acc[i][j][k]) & 0x7fffffffu);
-    const int code = (__ballot(m >= 0x7f800000u) ? 4 : 0) | (__ballot(m >= 0x1f800000u) ? 2 : 0) | (__ballot(m > 0u) ? 1 : 0);
     int *codes = (int *)lds;   // (the waves have met since the last read of the planes)
+    const int code = __ballot(m >= 0x7f800000u || lost) != 0;
     if ((threadIdx.x & 63) == 0) codes[threadIdx.x >> 6] = code;
     split_meet();
     const int all = codes[0] | codes[1] | codes[2] | codes[3];
     split_meet();
-    return (all & 4) || all == 1;
+    return all;
 }
 
 // nk k-tiles, for a wave that stages `op` to `mine`
+// nk > 0; whether a value of this thread's was not its pieces' sum
 template <class Op>
-__device__ __forceinline__ void split_chain(SplitAcc &acc, int nk, const Op &op, char *lds, int operand, int p0, int p1, int q0) {
+__device__ __forceinline__ bool split_chain(SplitAcc &acc, int nk, const Op &op, char *lds, int operand, int p0, int p1, int q0) {
     SplitRaw v;
     op.load(0, v);
+    bool lost = split_loses(v);
     split_store_tile<Op>(v, lds + operand * kSplitOperand);
     op.load(1, v);
     split_meet();
     for (int kt = 0; kt < nk; ++kt) {
         split_multiply(acc, lds, p0, p1, q0);
         split_meet();
+        if (kt + 1 == nk) break;
+        lost |= split_loses(v);
         split_store_tile<Op>(v, lds + operand * kSplitOperand);
         op.load(kt + 2, v);
         split_meet();
     }
+    return lost;
 }
 // the same on the f32 instruction
 template <class Op>
@@ -281,9 +304,8 @@ template <class OpP, class OpQ>
 __device__ __forceinline__ void split_loop(SplitAcc &acc, int nk, const OpP &P, const OpQ &Q, char *lds, int p0, int p1, int q0) {
     if (nk <= 0) return;
     const bool is_p = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 7)) == 0;
-    if (is_p) split_chain(acc, nk, P, lds, 0, p0, p1, q0);
-    else split_chain(acc, nk, Q, lds, 1, p0, p1, q0);
-    if (!split_failed(acc, lds)) return;
+    const bool lost = is_p ? split_chain(acc, nk, P, lds, 0, p0, p1, q0) : split_chain(acc, nk, Q, lds, 1, p0, p1, q0);
+    if (!split_failed(acc, lost, lds)) return;
     split_zero(acc);
     if (is_p) plain_chain(acc, nk, P, lds, 0, p0, p1, q0);
     else plain_chain(acc, nk, Q, lds, 1, p0, p1, q0);

@@ -15,12 +15,13 @@ SH = synth.LayerShape
 SPLIT = SH(T=2201, d=500, E=5, K=2, F=580, act="f32", sigma=0.05, zipf_s=0.8, seed=131)
 
 
-def run(c, calls, dy):
+def run(c, calls, dy, x=None):
     w = (c.t["Wg"], c.t["Wu"], c.t["Wd"])
+    x = c.t["x"] if x is None else x
     buf = r3.LayerBuffers(c.D, backward=True, gathered_copy=calls == "copy")
     forward = r3.forward_one_call if calls == "one" else r3.forward
-    forward(buf, c.t["x"], c.t["Wr"], c.t["idx"], *w, bias=c.t["bias"])
-    r3.backward(buf, dy, c.t["x"], c.t["Wr"], c.t["idx"], *w)
+    forward(buf, x, c.t["Wr"], c.t["idx"], *w, bias=c.t["bias"])
+    r3.backward(buf, dy, x, c.t["Wr"], c.t["idx"], *w)
     torch.cuda.synchronize()
     return buf
 
@@ -31,6 +32,83 @@ def dW_down_64(c, buf, dy):
     tok = buf.perm.long() // c.D.K
     assert buf.gated
     return torch.stack([buf.H[a:b].double().T @ dy[tok[a:b]].double() for a, b in zip(off, off[1:])])
+
+
+def layer_64(c, buf, dy, x=None):
+    """Every contraction in float64, each from the tensors that the layer left before it (dx, dW_gate and dW_up: from the saved factors,
+    so that dH's error is in them too)."""
+    K = c.D.K
+    x, dy = (c.t["x"] if x is None else x).double(), dy.double()
+    Wg, Wu, Wd, WrT = c.t["Wg"].double(), c.t["Wu"].double(), c.t["Wd"].double(), c.t["Wr"].double().T.contiguous()
+    off, tok = buf.offsets.tolist(), buf.perm.long() // K
+    gates = buf.gates.double()
+    g = gates.view(-1)[buf.perm.long(), None]
+    want = {k: torch.zeros_like(t, dtype=torch.float64) for k, t in
+            (("FA", buf.A), ("FB", buf.B), ("Yp", buf.Yp), ("dW_down", buf.dW_down), ("dW_gate", buf.dW_gate), ("dW_up", buf.dW_up))}
+    dXp = torch.zeros_like(buf.Yp, dtype=torch.float64)
+    for e, (a, b) in enumerate(zip(off, off[1:])):
+        xe, dye, ge, H = x[tok[a:b]], dy[tok[a:b]], g[a:b], buf.H[a:b].double()
+        s, u = xe @ Wg[e], xe @ Wu[e]
+        sg = torch.sigmoid(s)
+        want["FA"][a:b], want["FB"][a:b] = u * sg * (1 + s * (1 - sg)), s * sg
+        want["Yp"][a:b] = H @ Wd[e]
+        want["dW_down"][e] = H.T.contiguous() @ (dye if buf.gated else ge * dye)
+        dh = ge * (dye @ Wd[e].T.contiguous())
+        dA, dB = dh * buf.A[a:b].double(), dh * buf.B[a:b].double()
+        want["dW_gate"][e], want["dW_up"][e] = xe.T.contiguous() @ dA, xe.T.contiguous() @ dB
+        dXp[a:b] = dA @ Wg[e].T.contiguous() + dB @ Wu[e].T.contiguous()
+    rows = buf.inv_perm.long().view(-1, K)
+    w = (buf.Yp.double()[rows] * dy[:, None]).sum(-1) * (1 if buf.gated else gates)
+    dz = w - gates * w.sum(1, keepdim=True)
+    want["dx"] = dXp[rows].sum(1) + (dz[:, :, None] * WrT[c.t["idx"].long()]).sum(1)
+    return want
+
+
+# Of a row's norm.  An f32 chain of 500 to 1000 products leaves 4e-7 to 8e-7 of it, two such in a row 1.1e-6 (dx: from dH); a product of
+# pieces that is missing leaves 2.4e-6 (the middle ones with each other) and more.
+ROW = 2e-6
+
+
+def assert_rows(got, want, which=None):
+    err, size = (got.double() - want).norm(dim=-1), want.norm(dim=-1)
+    if which is not None:
+        err, size = err[which], size[which]
+    assert (size > 0).all() and (err <= ROW * size).all(), (err / size).max()
+
+
+@pytest.mark.parametrize("exp", [-104, -112, -118, -122])
+def test_small_values_beside_ordinary_ones(exp):
+    """Rows and columns whose lowest pieces lie below the smallest bf16 (from 2^-110 down), in tiles of ordinary values."""
+    c = Case(SPLIT, backward=True, scale_w=5.0)
+    toks = torch.arange(3, SPLIT.T, 50, device="cuda")
+    # gradients of a few tokens: dXp
+    dy = c.t["dy"].clone()
+    dy[toks] *= 2.0 ** exp
+    buf = run(c, "one", dy)
+    assert_rows(buf.dx, layer_64(c, buf, dy)["dx"], toks)
+    # features of the gradient: dW_down, the other operand
+    dy = c.t["dy"].clone()
+    cols = torch.arange(5, SPLIT.d, 37, device="cuda")
+    dy[:, cols] *= 2.0 ** exp
+    buf = run(c, "one", dy)
+    assert_rows(buf.dW_down[:, :, cols].transpose(1, 2), layer_64(c, buf, dy)["dW_down"][:, :, cols].transpose(1, 2))
+    # a few tokens: SwiGLU; half the exponent: down projection
+    for part, e in (("FB", exp), ("Yp", exp / 2)):
+        x = c.t["x"].clone()
+        x[toks] *= 2.0 ** e
+        buf = run(c, "one", c.t["dy"], x)
+        rows = torch.isin(buf.perm.long() // SPLIT.K, toks)
+        assert_rows({"FB": buf.B, "Yp": buf.Yp}[part], layer_64(c, buf, c.t["dy"], x)[part], rows)
+
+
+def test_values_without_a_bf16():
+    """Every piece of one operand rounds to zero, and what comes out is an ordinary number."""
+    c = Case(SPLIT, backward=True, scale_w=1.0)
+    dy, x = c.t["dy"] * 2.0 ** -139, c.t["x"] * 2.0 ** 40
+    buf = run(c, "one", dy, x)
+    want = layer_64(c, buf, dy, x)["dW_down"]
+    assert want.abs().max() > 1e-20
+    assert (buf.dW_down.double() - want).norm() <= ROW * want.norm()
 
 
 @pytest.mark.parametrize("calls", ["one", "steps", "copy"])

@@ -316,9 +316,9 @@ __device__ __forceinline__ void f32_rows_tile(const F32RowArgs &g, int block, ch
 // the same with a split tile
 template <int MODE>
 __device__ __forceinline__ void split_rows_tile(const F32RowArgs &g, int block, char *lds) {
+    static_assert(MODE != PLAIN_DH, "no gathered rows, no gates of the gradients");
     constexpr int BP = kSplitTile, BQ = kSplitTile, BF = MODE == PLAIN_FFN1 ? BP / 2 : BP;
-    const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? g.F : g.d;
-    const int KK = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? g.d : g.F;
+    const int NOUT = MODE == PLAIN_FFN1 ? g.F : g.d, KK = MODE == PLAIN_FFN1 ? g.d : g.F;
     const RowTile t = find_row_tile<true>(g.offsets, g.E, BQ, block, (NOUT + BF - 1) / BF);
     if (t.e < 0) return;
     const int p0 = t.col * BF, rows = t.row1 - t.row0, nk = (KK + 31) / 32;
@@ -350,13 +350,10 @@ __device__ __forceinline__ void split_rows_tile(const F32RowArgs &g, int block, 
         P.init(g.W0 + we + (int64_t)p0 * KK, pbytes, KK, u);
 #pragma unroll
         for (int i = 0; i < 4; ++i) P.set_row(i, min(SplitRows::row(u, i), NOUT - p0 - 1));
-        if constexpr (MODE == PLAIN_DH) {
-            split_loop(acc, nk, P, Q, lds, 64 * wp, 64 * wp + 32, 64 * wq);
-        } else {   // one reduction over both halves: dA Wg^T, then dB Wu^T
-            const SplitPair<SplitRows> P2{P, Src{(const char *)(g.W1 + we + (int64_t)p0 * KK), pbytes, 128}, nk};
-            const SplitPair<SplitRows> Q2{Q, Src{(const char *)(g.in1 + (int64_t)t.row0 * KK), Q.src.nbytes, 128}, nk};
-            split_loop(acc, 2 * nk, P2, Q2, lds, 64 * wp, 64 * wp + 32, 64 * wq);
-        }
+        // one reduction over both halves: dA Wg^T, then dB Wu^T
+        const SplitPair<SplitRows> P2{P, Src{(const char *)(g.W1 + we + (int64_t)p0 * KK), pbytes, 128}, nk};
+        const SplitPair<SplitRows> Q2{Q, Src{(const char *)(g.in1 + (int64_t)t.row0 * KK), Q.src.nbytes, 128}, nk};
+        split_loop(acc, 2 * nk, P2, Q2, lds, 64 * wp, 64 * wp + 32, 64 * wq);
     }
 #pragma unroll
     for (int tq = 0; tq < 2; ++tq) {

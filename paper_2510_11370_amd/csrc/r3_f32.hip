@@ -339,11 +339,11 @@ __device__ __forceinline__ void split_rows_tile(const F32RowArgs &g, int block, 
     if constexpr (MODE == PLAIN_FFN1) {
         SplitCols<true> P;   // the same features of both weights, so that a lane holds both pre-activations
         P.init((wave == 0 ? g.W0 : g.W1) + we + p0, wbytes - p0 * 4u, g.F, u);
-        split_loop(acc, nk, P, Q, lds, 32 * wp, 64 + 32 * wp, 64 * wq);
+        split_loop(acc, nk, KK, P, Q, lds, 32 * wp, 64 + 32 * wp, 64 * wq);
     } else if constexpr (MODE == PLAIN_DOWN) {
         SplitCols<false> P;
         P.init(g.W0 + we + p0, wbytes - p0 * 4u, g.d, u);
-        split_loop(acc, nk, P, Q, lds, 64 * wp, 64 * wp + 32, 64 * wq);
+        split_loop(acc, nk, KK, P, Q, lds, 64 * wp, 64 * wp + 32, 64 * wq);
     } else {
         SplitRows P;
         const uint64_t pbytes = (uint64_t)(NOUT - p0) * KK * 4;
@@ -353,7 +353,7 @@ __device__ __forceinline__ void split_rows_tile(const F32RowArgs &g, int block, 
         // one reduction over both halves: dA Wg^T, then dB Wu^T
         const SplitPair<SplitRows> P2{P, Src{(const char *)(g.W1 + we + (int64_t)p0 * KK), pbytes, 128}, nk};
         const SplitPair<SplitRows> Q2{Q, Src{(const char *)(g.in1 + (int64_t)t.row0 * KK), Q.src.nbytes, 128}, nk};
-        split_loop(acc, 2 * nk, P2, Q2, lds, 64 * wp, 64 * wp + 32, 64 * wq);
+        split_loop(acc, 2 * nk, 2 * KK, P2, Q2, lds, 64 * wp, 64 * wp + 32, 64 * wq);
     }
 #pragma unroll
     for (int tq = 0; tq < 2; ++tq) {
@@ -508,9 +508,9 @@ __device__ __forceinline__ void split_wgrad_tile(int E, int T, int K, const int3
     };
     const int nk = (n + 31) / 32;
     if (n > 0) {
-        if (g.pperm) split_loop(acc, nk, gathered(g.Ps, g.NP, p0, g.pperm), plain(g.Qs, g.NQ, q0), lds, 64 * wp, 64 * wp + 32, 64 * wq);
-        else if (g.qperm) split_loop(acc, nk, plain(g.Ps, g.NP, p0), gathered(g.Qs, g.NQ, q0, g.qperm), lds, 64 * wp, 64 * wp + 32, 64 * wq);
-        else split_loop(acc, nk, plain(g.Ps, g.NP, p0), plain(g.Qs, g.NQ, q0), lds, 64 * wp, 64 * wp + 32, 64 * wq);
+        if (g.pperm) split_loop(acc, nk, n, gathered(g.Ps, g.NP, p0, g.pperm), plain(g.Qs, g.NQ, q0), lds, 64 * wp, 64 * wp + 32, 64 * wq);
+        else if (g.qperm) split_loop(acc, nk, n, plain(g.Ps, g.NP, p0), gathered(g.Qs, g.NQ, q0, g.qperm), lds, 64 * wp, 64 * wp + 32, 64 * wq);
+        else split_loop(acc, nk, n, plain(g.Ps, g.NP, p0), plain(g.Qs, g.NQ, q0), lds, 64 * wp, 64 * wp + 32, 64 * wq);
     }
     float *o = g.out + (int64_t)e * g.NQ * g.NP;
 #pragma unroll

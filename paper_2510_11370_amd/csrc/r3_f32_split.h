@@ -299,14 +299,18 @@ __device__ __forceinline__ void plain_chain(SplitAcc &acc, int nk, const Op &op,
     }
 }
 
-// P is staged by waves 0 and 1, Q by waves 2 and 3, each in a loop of its own (they pass the same barriers).
+// P is staged by waves 0 and 1, Q by waves 2 and 3, each in a loop of its own (they pass the same barriers).  `products`: of a result.  One
+// or two are left to the f32 instruction, which has no more than their own roundings (one: 2.5e-8 of the norm, six products' sum 3.5e-8; two
+// 3.1e-8 and 3.4e-8; three 3.6e-8 and 3.3e-8, 32 1.0e-7 and 6.9e-8).
 template <class OpP, class OpQ>
-__device__ __forceinline__ void split_loop(SplitAcc &acc, int nk, const OpP &P, const OpQ &Q, char *lds, int p0, int p1, int q0) {
+__device__ __forceinline__ void split_loop(SplitAcc &acc, int nk, int products, const OpP &P, const OpQ &Q, char *lds, int p0, int p1, int q0) {
     if (nk <= 0) return;
     const bool is_p = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 7)) == 0;
-    const bool lost = is_p ? split_chain(acc, nk, P, lds, 0, p0, p1, q0) : split_chain(acc, nk, Q, lds, 1, p0, p1, q0);
-    if (!split_failed(acc, lost, lds)) return;
-    split_zero(acc);
+    if (products > 2) {
+        const bool lost = is_p ? split_chain(acc, nk, P, lds, 0, p0, p1, q0) : split_chain(acc, nk, Q, lds, 1, p0, p1, q0);
+        if (!split_failed(acc, lost, lds)) return;
+        split_zero(acc);
+    }
     if (is_p) plain_chain(acc, nk, P, lds, 0, p0, p1, q0);
     else plain_chain(acc, nk, Q, lds, 1, p0, p1, q0);
 }

@@ -111,6 +111,22 @@ def test_values_without_a_bf16():
     assert (buf.dW_down.double() - want).norm() <= ROW * want.norm()
 
 
+def test_sums_of_one_and_two_products():
+    """Experts of one and two rows among large ones: a product has one rounding, a sum of two no more than one for each."""
+    c = Case(SPLIT, backward=True, scale_w=5.0)
+    c.t["idx"].copy_(torch.tensor([0, 1]))
+    c.t["idx"][1::2] = torch.tensor([1, 2], dtype=torch.uint8, device="cuda")
+    c.t["idx"][5] = torch.tensor([0, 3], dtype=torch.uint8, device="cuda")
+    c.t["idx"][[9, 1500]] = torch.tensor([2, 4], dtype=torch.uint8, device="cuda")
+    dy = c.t["dy"]
+    buf = run(c, "one", dy)
+    off = buf.offsets.tolist()
+    assert [off[4] - off[3], off[5] - off[4]] == [1, 2]
+    assert torch.equal(buf.dW_down[3], buf.H[off[3]][:, None] * dy[5][None])
+    terms = (buf.H[off[4]:].double()[:, :, None] * dy[[9, 1500]].double()[:, None])
+    assert ((buf.dW_down[4].double() - terms.sum(0)).abs() <= 2.0 ** -23 * terms.abs().sum(0)).all()
+
+
 @pytest.mark.parametrize("calls", ["one", "steps", "copy"])
 @pytest.mark.parametrize("sh", [SPLIT, SH(T=4100, d=260, E=40, K=2, F=1028, act="f32", sigma=0.05, zipf_s=1.2, seed=132)],   # SwiGLU and gradients only, experts of few rows
                          ids=lambda s: "T%d_d%d_F%d_E%d" % (s.T, s.d, s.F, s.E))

@@ -1,7 +1,7 @@
 // The expert network of the f32 layer on the f32 matrix instruction (16x16x4), for widths that are multiples of four
 // (16-byte rows); all other widths and the bf16 layers without a matrix path have the tiles of r3_plain.hip.  Products and
-// sums are those of an f32 FMA chain, in the same order of k as there.  Where there is work for larger tiles, most of it goes
-// to the bf16 instruction at f32 precision instead (r3_f32_split.h; the rule is at split_rows() below).
+// sums are those of an f32 FMA chain, in the same order of k as there.  SwiGLU, down projection and dXp of wide layers, and weight gradients that
+// fill larger tiles, go to the bf16 instruction at f32 precision instead (r3_f32_split.h; the rules are at split_rows() below).
 //
 // What bounds it: the f32 matrix pipe, 256 FLOP per cycle and compute unit (157 TFLOP/s at 2.4 GHz); for layers of a few
 // hundred rows the chain of loads and MFMAs of one tile.  An operand tile (32 k) goes from memory straight to LDS, 1 KB per
@@ -25,19 +25,23 @@ namespace {
 // 4 waves as 2 (P) x 2 (Q), each TP x TQ tiles of 16 x 16; NST tiles of 32 k in LDS, NST - 1 on the way
 template <int TP_, int TQ_, int NST_>
 struct F32Cfg {
-    static constexpr int TP = TP_, TQ = TQ_, NST = NST_, NT = 256, BK = 32;
-    static constexpr int BP = 32 * TP, BQ = 32 * TQ, PBYTES = BP * BK * 4, STAGE = (BP + BQ) * BK * 4;
+    static constexpr bool SPLIT = false;
+    static constexpr int TP = TP_, TQ = TQ_, NST = NST_, NT = 256, BK = 32, MINW = 1;
+    static constexpr int BP = 32 * TP, BQ = 32 * TQ, PBYTES = BP * BK * 4, STAGE = (BP + BQ) * BK * 4, LDS = NST * STAGE;
     static constexpr int LOADS = TP + TQ;   // loads per wave and k-tile (a load of four waves is 4 KB)
 };
-typedef F32Cfg<2, 2, 2> F32Tile;     // 32 KB of LDS: five work-groups on a compute unit, which cover what is not prefetched (four where dH
-                                     // shares its grid with the parts of dW_r, whose padded tiles take 36 KB)
+typedef F32Cfg<2, 2, 2> F32Tile;     // 32 KB of LDS: five work-groups on a compute unit, which cover what is not prefetched (four where the
+                                     // weight gradients share their grid with the parts of dW_r, whose padded tiles take 36 KB)
 typedef F32Cfg<1, 1, 4> F32Short;    // few tiles: four times as many, half the chain each, loads three k-tiles ahead (F32WgradOp: one)
+
+// tiles on the bf16 instruction (r3_f32_split.h)
 typedef F32Cfg<2, 1, 4> F32Short1;   // the same for the SwiGLU, whose P tile holds both weights
 
-// 128 x 128 tiles on the bf16 instruction (r3_f32_split.h)
-struct F32Split {
-    static constexpr int NT = kSplitThreads, BP = kSplitTile, BQ = kSplitTile;
-};
+// tiles on the bf16 instruction (r3_f32_split.h), likewise
+typedef SplitCfg<4, 4, 1, 2> Split128;
+typedef SplitCfg<2, 2, 2, 1> Split64;
+typedef SplitCfg<1, 1, 2, 1> Split32;
+typedef SplitCfg<2, 1, 2, 1> Split32x1;
 
 template <class C> using F32Acc = f32x4_t[C::TP][C::TQ];
 
@@ -313,67 +317,59 @@ __device__ __forceinline__ void f32_rows_tile(const F32RowArgs &g, int block, ch
     }
 }
 
-// the same with a split tile
-template <int MODE>
+// the same with a split tile (not dH)
+template <class C, int MODE>
 __device__ __forceinline__ void split_rows_tile(const F32RowArgs &g, int block, char *lds) {
-    static_assert(MODE != PLAIN_DH, "no gathered rows, no gates of the gradients");
-    constexpr int BP = kSplitTile, BQ = kSplitTile, BF = MODE == PLAIN_FFN1 ? BP / 2 : BP;
-    const int NOUT = MODE == PLAIN_FFN1 ? g.F : g.d, KK = MODE == PLAIN_FFN1 ? g.d : g.F;
+    constexpr bool ONE = MODE == PLAIN_FFN1;
+    constexpr int BP = C::BP, BQ = C::BQ, BF = ONE ? BP / 2 : BP;
+    typedef SplitWave<C, ONE> W;
+    const int NOUT = ONE ? g.F : g.d, KK = ONE ? g.d : g.F;
     const RowTile t = find_row_tile<true>(g.offsets, g.E, BQ, block, (NOUT + BF - 1) / BF);
     if (t.e < 0) return;
     const int p0 = t.col * BF, rows = t.row1 - t.row0, nk = (KK + 31) / 32;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wp = wave & 1, wq = wave >> 1, u = threadIdx.x & 127;
+    const int lane = threadIdx.x & 63, u = threadIdx.x & 127;
     const int64_t we = (int64_t)t.e * g.d * g.F;
     const uint64_t wbytes = (uint64_t)g.d * g.F * 4;
 
-    const bool gather = MODE == PLAIN_FFN1 && g.perm;
-    SplitRows Q;
+    const bool gather = ONE && g.perm;
+    SplitRows<BQ> Q;
     Q.init(gather ? g.in0 : g.in0 + (int64_t)t.row0 * KK, gather ? (uint64_t)g.T * KK * 4 : (uint64_t)rows * KK * 4, KK, u);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = min(SplitRows::row(u, i), rows - 1);
+    for (int i = 0; i < Q.N; ++i) {
+        const int r = min(Q.row(u, i), rows - 1);
         Q.set_row(i, gather ? g.perm[t.row0 + r] / g.K : r);
     }
-    SplitAcc acc;
-    split_zero(acc);
-    if constexpr (MODE == PLAIN_FFN1) {
-        SplitCols<true> P;   // the same features of both weights, so that a lane holds both pre-activations
-        P.init((wave == 0 ? g.W0 : g.W1) + we + p0, wbytes - p0 * 4u, g.F, u);
-        split_loop(acc, nk, KK, P, Q, lds, 32 * wp, 64 + 32 * wp, 64 * wq);
+    SplitAcc<C> acc;
+    if constexpr (ONE) {   // the same features of both weights, so that a lane holds both pre-activations
+        SplitCols<BP, true> P;
+        P.init(((threadIdx.x >> 6) == 0 ? g.W0 : g.W1) + we + p0, wbytes - p0 * 4u, g.F, u);
+        split_loop<C, W>(acc, nk, KK, P, Q, lds);
     } else if constexpr (MODE == PLAIN_DOWN) {
-        SplitCols<false> P;
+        SplitCols<BP, false> P;
         P.init(g.W0 + we + p0, wbytes - p0 * 4u, g.d, u);
-        split_loop(acc, nk, KK, P, Q, lds, 64 * wp, 64 * wp + 32, 64 * wq);
-    } else {
-        SplitRows P;
+        split_loop<C, W>(acc, nk, KK, P, Q, lds);
+    } else {   // one reduction over both halves: dA Wg^T, then dB Wu^T
+        static_assert(MODE == PLAIN_DXP, "");
+        SplitRows<BP> P;
         const uint64_t pbytes = (uint64_t)(NOUT - p0) * KK * 4;
         P.init(g.W0 + we + (int64_t)p0 * KK, pbytes, KK, u);
 #pragma unroll
-        for (int i = 0; i < 4; ++i) P.set_row(i, min(SplitRows::row(u, i), NOUT - p0 - 1));
-        // one reduction over both halves: dA Wg^T, then dB Wu^T
-        const SplitPair<SplitRows> P2{P, Src{(const char *)(g.W1 + we + (int64_t)p0 * KK), pbytes, 128}, nk};
-        const SplitPair<SplitRows> Q2{Q, Src{(const char *)(g.in1 + (int64_t)t.row0 * KK), Q.src.nbytes, 128}, nk};
-        split_loop(acc, 2 * nk, 2 * KK, P2, Q2, lds, 64 * wp, 64 * wp + 32, 64 * wq);
+        for (int i = 0; i < P.N; ++i) P.set_row(i, min(P.row(u, i), NOUT - p0 - 1));
+        const SplitPair<SplitRows<BP>> P2{P, Src{(const char *)(g.W1 + we + (int64_t)p0 * KK), pbytes, 128}, nk};
+        const SplitPair<SplitRows<BQ>> Q2{Q, Src{(const char *)(g.in1 + (int64_t)t.row0 * KK), Q.src.nbytes, 128}, nk};
+        split_loop<C, W>(acc, 2 * nk, 2 * KK, P2, Q2, lds);
     }
 #pragma unroll
-    for (int tq = 0; tq < 2; ++tq) {
-        const int q = 64 * wq + 32 * tq + (lane & 31), row = t.row0 + q;
+    for (int j = 0; j < C::TQ; ++j) {
+        const int q = W::qrow(j) + (lane & 15), row = t.row0 + q;
         if (q >= rows) continue;
-        const float gate = MODE == PLAIN_FFN1 && g.gates ? g.gates[g.perm[row]] : 1.0f;
+        const float gate = ONE && g.gates ? g.gates[g.perm[row]] : 1.0f;
+        auto quad = [&](int i) { return make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]); };
 #pragma unroll
-        for (int k = 0; k < 4; ++k) {
-            const int f = 8 * k + 4 * (lane >> 5);
-            auto quad = [&](int tp) { return make_float4(acc[tp][tq][4 * k], acc[tp][tq][4 * k + 1], acc[tp][tq][4 * k + 2], acc[tp][tq][4 * k + 3]); };
-            if constexpr (MODE == PLAIN_FFN1) {
-                const int c = p0 + 32 * wp + f;
-                if (c < NOUT) f32_rows_store<MODE>(g.FA, g.FB, g.out0, g.out1, g.out2, (int64_t)row * NOUT + c, gate, quad(0), quad(1));
-            } else {
-#pragma unroll
-                for (int tp = 0; tp < 2; ++tp) {
-                    const int c = p0 + 64 * wp + 32 * tp + f;
-                    if (c < NOUT) f32_rows_store<MODE>(g.FA, g.FB, g.out0, g.out1, g.out2, (int64_t)row * NOUT + c, 1.0f, quad(tp), float4());
-                }
-            }
+        for (int i = 0; i < (ONE ? C::TP / 2 : C::TP); ++i) {
+            const int c = p0 + W::prow(i) + 4 * (lane >> 4);
+            if (c >= NOUT) continue;
+            f32_rows_store<MODE>(g.FA, g.FB, g.out0, g.out1, g.out2, (int64_t)row * NOUT + c, gate, quad(i), quad(ONE ? C::TP / 2 + i : i));
         }
     }
 }
@@ -483,75 +479,67 @@ __device__ __forceinline__ void f32_wgrad_tile(int E, int T, int K, const int32_
     }
 }
 
+template <class C>
 __device__ __forceinline__ void split_wgrad_tile(int E, int T, int K, const int32_t *__restrict__ offsets, const F32Wgrad3 &all,
                                                  int accumulate, int block, char *lds) {
+    typedef SplitWave<C, false> W;
     const int per = all.g[0].tiles + all.g[1].tiles + all.g[2].tiles;
     const int e = block / per, t0 = all.g[0].tiles, t1 = t0 + all.g[1].tiles;
     int rem = block - e * per;
     const F32Wgrad g = rem < t0 ? all.g[0] : rem < t1 ? all.g[1] : all.g[2];
     rem -= rem < t0 ? 0 : rem < t1 ? t0 : t1;
-    const int npt = (g.NP + kSplitTile - 1) / kSplitTile;
-    const int qt = rem / npt, q0 = qt * kSplitTile, p0 = (rem - qt * npt) * kSplitTile;
+    const int npt = (g.NP + C::BP - 1) / C::BP;
+    const int qt = rem / npt, q0 = qt * C::BQ, p0 = (rem - qt * npt) * C::BP;
     const int r0 = offsets[e], n = offsets[e + 1] - r0;
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, wp = wave & 1, wq = wave >> 1, u = threadIdx.x & 127;
-    SplitAcc acc;
-    split_zero(acc);
+    const int lane = threadIdx.x & 63, u = threadIdx.x & 127;
+    SplitAcc<C> acc;
     auto plain = [&](const float *m, int ld, int col0) {
-        SplitCols<false> op;
+        SplitCols<C::BP, false> op;
         op.init(m + (int64_t)r0 * ld + col0, (uint64_t)((int64_t)n * ld - col0) * 4, ld, u);
         return op;
     };
     auto gathered = [&](const float *m, int ld, int col0, const int32_t *perm) {
-        SplitGather op;
+        SplitGather<C::BP> op;
         op.init(m + col0, (uint64_t)((int64_t)T * ld - col0) * 4, ld, u, perm + r0, n, K);
         return op;
     };
+    static_assert(C::BP == C::BQ, "");
     const int nk = (n + 31) / 32;
-    if (n > 0) {
-        if (g.pperm) split_loop(acc, nk, n, gathered(g.Ps, g.NP, p0, g.pperm), plain(g.Qs, g.NQ, q0), lds, 64 * wp, 64 * wp + 32, 64 * wq);
-        else if (g.qperm) split_loop(acc, nk, n, plain(g.Ps, g.NP, p0), gathered(g.Qs, g.NQ, q0, g.qperm), lds, 64 * wp, 64 * wp + 32, 64 * wq);
-        else split_loop(acc, nk, n, plain(g.Ps, g.NP, p0), plain(g.Qs, g.NQ, q0), lds, 64 * wp, 64 * wp + 32, 64 * wq);
-    }
+    if (g.pperm) split_loop<C, W>(acc, nk, n, gathered(g.Ps, g.NP, p0, g.pperm), plain(g.Qs, g.NQ, q0), lds);
+    else if (g.qperm) split_loop<C, W>(acc, nk, n, plain(g.Ps, g.NP, p0), gathered(g.Qs, g.NQ, q0, g.qperm), lds);
+    else split_loop<C, W>(acc, nk, n, plain(g.Ps, g.NP, p0), plain(g.Qs, g.NQ, q0), lds);
     float *o = g.out + (int64_t)e * g.NQ * g.NP;
 #pragma unroll
-    for (int tq = 0; tq < 2; ++tq) {
-        const int q = q0 + 64 * wq + 32 * tq + (lane & 31);
+    for (int j = 0; j < C::TQ; ++j) {
+        const int q = q0 + W::qrow(j) + (lane & 15);
         if (q >= g.NQ) continue;
 #pragma unroll
-        for (int tp = 0; tp < 2; ++tp)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int p = p0 + 64 * wp + 32 * tp + 8 * k + 4 * (lane >> 5);
-                if (p >= g.NP) continue;
-                float4 *at = (float4 *)(o + (int64_t)q * g.NP + p);
-                float4 v = make_float4(acc[tp][tq][4 * k], acc[tp][tq][4 * k + 1], acc[tp][tq][4 * k + 2], acc[tp][tq][4 * k + 3]);
-                if (accumulate) {
-                    const float4 old = *at;
-                    v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
-                }
-                *at = v;
+        for (int i = 0; i < C::TP; ++i) {
+            const int p = p0 + W::prow(i) + 4 * (lane >> 4);
+            if (p >= g.NP) continue;
+            float4 *at = (float4 *)(o + (int64_t)q * g.NP + p);
+            float4 v = make_float4(acc[i][j][0], acc[i][j][1], acc[i][j][2], acc[i][j][3]);
+            if (accumulate) {
+                const float4 old = *at;
+                v.x += old.x; v.y += old.y; v.z += old.z; v.w += old.w;
             }
+            *at = v;
+        }
     }
 }
 
 // either kind of tile
-template <class C> constexpr bool kIsSplit = std::is_same<C, F32Split>::value;
-template <class C> constexpr int tile_lds() {
-    if constexpr (kIsSplit<C>) return kSplitLds;
-    else return C::NST * C::STAGE;
-}
 template <class C, int MODE>
 __device__ __forceinline__ void rows_tile(const F32RowArgs &a, int block, char *lds) {
-    if constexpr (kIsSplit<C>) split_rows_tile<MODE>(a, block, lds);
+    if constexpr (C::SPLIT) split_rows_tile<C, MODE>(a, block, lds);
     else f32_rows_tile<C, MODE>(a, block, lds);
 }
 template <class C>
 __device__ __forceinline__ void wgrad_tile(int E, int T, int K, const int32_t *__restrict__ offsets, const F32Wgrad3 &all, int accumulate,
                                            int block, char *lds) {
-    if constexpr (kIsSplit<C>) split_wgrad_tile(E, T, K, offsets, all, accumulate, block, lds);
+    if constexpr (C::SPLIT) split_wgrad_tile<C>(E, T, K, offsets, all, accumulate, block, lds);
     else f32_wgrad_tile<C>(E, T, K, offsets, all, accumulate, block, lds);
 }
-template <class C> constexpr int kMinWaves = kIsSplit<C> ? kSplitMinWaves : 1;
 
 // ---------------------------------------------------------------------------
 // Launches.  What does not wait for each other shares one: a layer of few tokens is a chain of launches, and a larger one
@@ -561,15 +549,15 @@ template <class C> constexpr int kMinWaves = kIsSplit<C> ? kSplitMinWaves : 1;
 // for dH), 44.7 in these three; T=2048 d=512 E=16 K=4 F=1024: 815, 767 (595 with split tiles), 588.
 // ---------------------------------------------------------------------------
 template <class C, int MODE>
-__global__ void __launch_bounds__(C::NT, kMinWaves<C>) f32_rows_kernel(F32RowArgs a) {
-    __shared__ __attribute__((aligned(1024))) char lds[tile_lds<C>()];
+__global__ void __launch_bounds__(C::NT, C::MINW) f32_rows_kernel(F32RowArgs a) {
+    __shared__ __attribute__((aligned(1024))) char lds[C::LDS];
     rows_tile<C, MODE>(a, blockIdx.x, lds);
 }
 
 template <class C>
-__global__ void __launch_bounds__(C::NT, kMinWaves<C>)
+__global__ void __launch_bounds__(C::NT, C::MINW)
 f32_wgrad_kernel(int E, int T, int K, const int32_t *__restrict__ offsets, F32Wgrad3 all, int accumulate) {
-    __shared__ __attribute__((aligned(1024))) char lds[tile_lds<C>()];
+    __shared__ __attribute__((aligned(1024))) char lds[C::LDS];
     wgrad_tile<C>(E, T, K, offsets, all, accumulate, blockIdx.x, lds);
 }
 
@@ -619,9 +607,9 @@ __device__ __forceinline__ void f32_gate_tokens(const F32Gate &a, int block) {
 
 // [0, nt): W_r^T; [nt, ng): the gate's backward; from `first` on (a multiple of 8, so that the rows' tiles keep their XCDs) dH
 template <class C>
-__global__ void __launch_bounds__(C::NT, kMinWaves<C>)
+__global__ void __launch_bounds__(C::NT, C::MINW)
 f32_dh_kernel(F32RowArgs a, F32Gate gate, RouterFinish<float> wrt, int nt, int ng, int first) {
-    __shared__ __attribute__((aligned(1024))) char lds[tile_lds<C>()];
+    __shared__ __attribute__((aligned(1024))) char lds[C::LDS];
     static_assert(sizeof(RouterFinishLds<float>) <= sizeof(lds), "");
     const int b = blockIdx.x;
     if (b >= first) rows_tile<C, PLAIN_DH>(a, b - first, lds);
@@ -631,10 +619,10 @@ f32_dh_kernel(F32RowArgs a, F32Gate gate, RouterFinish<float> wrt, int nt, int n
 
 // [0, first): parts of dW_r; [first, second): dXp; then the weight gradients
 template <class CR, class CW, typename IdxT>
-__global__ void __launch_bounds__(CR::NT, max_int(kMinWaves<CR>, kMinWaves<CW>))
+__global__ void __launch_bounds__(CR::NT, max_int(CR::MINW, CW::MINW))
 f32_grads_kernel(F32RowArgs a, int E, int T, int K, const int32_t *__restrict__ offsets, F32Wgrad3 all, int accumulate,
                  PlainDwr<float, IdxT> w, int nw, int first, int second) {
-    __shared__ __attribute__((aligned(1024))) char lds[max_int(max_int(tile_lds<CR>(), tile_lds<CW>()), PlainSmall::LDS)];
+    __shared__ __attribute__((aligned(1024))) char lds[max_int(max_int(CR::LDS, CW::LDS), PlainSmall::LDS)];
     const int b = blockIdx.x;
     if (b >= second) wgrad_tile<CW>(E, T, K, offsets, all, accumulate, b - second, lds);
     else if (b >= first) rows_tile<CR, PLAIN_DXP>(a, b - first, lds);
@@ -653,25 +641,24 @@ constexpr int kRowsFill = 512;
 // 190.7 | 184.3; 4096 top-2, 256 x 256 (384) 161.3 | 166.2; 300 top-2, 512 x 320, 4 experts (480) 65.5 | 67.6.
 constexpr int kWgradFill = 320;
 
-// Split tiles.  SwiGLU: wherever there are not few tiles (us, 64 x 64 | split, 2048 tokens top-4, 512 x 1024, 16 experts 174 | 128, 4096 top-4,
-// 512 x 512, 128 experts 208 | 167, 1024 top-2, 512 x 512, 8 experts 34.8 | 33.4).
-// Down projection (and dXp in a launch of its own): 2 M results and more, 128 rows per expert, a quarter of the tiles' columns dead at
-// most: 4096 top-2, 512 x 512, 8 experts (4 M) 50 | 45, 1024 top-4, 512 x 1024, 16 experts (2 M) 56.6 | 53.5, 4096 top-4, 512 x 512, 128 experts
-// 98 | 82; 512 top-2, 512 x 512, 8 experts (.5 M) 12.9 | 26.6; 64 rows per expert 34.2 | 35.9; 132 columns of 256 15.7 | 18.9.
-// dH stays with the others: 16 k-tiles and two operands beside the result, 94 | 104.
+// Split tiles.  SwiGLU, down projection and dXp: by the widths alone, so that a token's results are the same bits in a micro-batch and in
+// the whole batch (dH stays on the f32 instruction: 16 k-tiles and two operands beside the result, 94 | 104 us).  From 512 x 512 on: training, us, f32
+// instruction | split, 8 experts top-2 unless given, 128 tokens, 1024 and 4096 or more:  256 x 256 43 | 48, 105 | 101 (2048), 264 | 265 (8192);  384 x 384 53 | 59, 107 |
+// 102, 265 | 263;  512 x 512 62 | 69, 153 | 145, 379 | 366, of 4096 top-4 over 128 experts 855 | 784;  1024 x 1024 105 | 118 (64), 260 | 238 (512);  2048 top-4,
+// 512 x 1024, 16 experts 667 | 573.  (Small tiles only where there were few of the large ones, as the f32 instruction has it, is 10 % faster at the left of these
+// and gives a token other bits there.)
+constexpr int64_t kSplitRows = 1 << 18;
+// Their size.  128 x 128 from 224 tiles on (dXp, beside the weight gradients: 128), with 64 rows per expert and a quarter of the columns dead at most;
+// 64 x 64 from 512 (64).  us, 128 | 64 | 32, by the number of tiles of 128:  SwiGLU 120 50 | 38 | 36, 256 82 | 87 | 103, 376 59 | 79 | 89, 512 93 | 85 | 101,
+// 768 139 | 171 | 210, 32 rows per expert 104 | 93 | 94;  down 64 37 | 23 | 22, 128 37 | 30 | 35, 235 39 | 42 | 56, 256 78 | 84 | 111;
+// dXp and the gradients 16 68 | 30 | 32, 64 71 | 56 | 69, 128 89 | 90 | 125, 256 164 | 166 | 228.
+int64_t split_columns(int n) { return ceil_div(n, Split128::BP) * Split128::BP; }
 // The weight gradients: one tile per compute unit and more, with the same allowance, and 64 rows per expert.  3 x 8 experts: 4096 tokens top-2,
 // 320 x 320 (150 tiles' worth) 97 | 116, 256 x 1024 (384) 230 | 185, 1024 top-2, 512 x 512 (384) 71 | 66; 64 rows per expert 165 | 150, 32
-// 483 | 487, 16 16.1 | 20.9.  With them dXp from .9 M results on,
-// split beside small tiles: 1500 top-1, 640 columns, 5 experts (.96 M) 102 | 109, 2048 top-4, 512, 128 experts 292 | 327, 300 top-2, 1024, 5 experts (.6 M)
-// 102 | 78.
-constexpr int64_t kSplitDown = 1 << 21, kSplitDxp = 900000;
-int64_t split_columns(int n) { return (n + kSplitTile - 1) / kSplitTile * kSplitTile; }
-bool split_rows(int S, int E, int NOUT) {
-    return (int64_t)S * NOUT >= kSplitDown && S >= 128 * (int64_t)E && 4 * (int64_t)NOUT >= 3 * split_columns(NOUT);
-}
+// 483 | 487, 16 16.1 | 20.9.
 bool split_wgrads(int64_t S, int E, int d, int F) {
     const int64_t n = (int64_t)d * F;
-    return S >= 64 * (int64_t)E && 3 * E * n >= 256ll * kSplitTile * kSplitTile && 4 * n >= 3 * split_columns(d) * split_columns(F);
+    return S >= 64 * (int64_t)E && 3 * E * n >= 256ll * Split128::BP * Split128::BP && 4 * n >= 3 * split_columns(d) * split_columns(F);
 }
 
 template <class C, int MODE>
@@ -687,14 +674,30 @@ void rows_launch(int S, const F32RowArgs &a, hipStream_t s) {
 bool few_row_tiles(int S, int E, int NOUT, int width) {
     return ceil_div(S, 64) * ceil_div(NOUT, width) < kRowsFill || S < 64 * (int64_t)E;
 }
+bool split_rows(int d, int F) { return (int64_t)d * F >= kSplitRows; }
+template <class C>
+bool split_fills(int S, int NOUT, int BF, int64_t tiles) {
+    const int64_t columns = ceil_div(NOUT, BF);
+    return ceil_div(S, C::BQ) * columns >= tiles && 4 * (int64_t)NOUT >= 3 * columns * BF;
+}
+// whether a contraction's tiles are 128 x 128, 64 x 64 or 32 x 32
+template <int MODE>
+int split_width(int S, int E, int NOUT) {
+    constexpr int h = MODE == PLAIN_FFN1 ? 2 : 1;   // features of both weights
+    if (S >= 64 * (int64_t)E && split_fills<Split128>(S, NOUT, Split128::BP / h, MODE == PLAIN_DXP ? 128 : 224)) return 128;
+    return split_fills<Split64>(S, NOUT, Split64::BP / h, MODE == PLAIN_DXP ? 64 : 512) ? 64 : 32;
+}
 template <int MODE>
 void rows_by_size(int S, const F32RowArgs &a, hipStream_t s) {
     const int NOUT = (MODE == PLAIN_FFN1 || MODE == PLAIN_DH) ? a.F : a.d;
     typedef typename std::conditional<MODE == PLAIN_FFN1, F32Short1, F32Short>::type Short;
-    typedef typename std::conditional<MODE == PLAIN_FFN1, F32Split, F32Tile>::type Tile;
-    auto f = few_row_tiles(S, a.E, NOUT, MODE == PLAIN_FFN1 ? 32 : 64) ? rows_launch<Short, MODE> : rows_launch<Tile, MODE>;
-    if constexpr (MODE == PLAIN_DOWN || MODE == PLAIN_DXP)
-        if (split_rows(S, a.E, a.d)) f = rows_launch<F32Split, MODE>;
+    auto f = few_row_tiles(S, a.E, NOUT, MODE == PLAIN_FFN1 ? 32 : 64) ? rows_launch<Short, MODE> : rows_launch<F32Tile, MODE>;
+    if constexpr (MODE != PLAIN_DH)
+        if (split_rows(a.d, a.F)) {
+            typedef typename std::conditional<MODE == PLAIN_FFN1, Split32x1, Split32>::type Small;
+            const int w = split_width<MODE>(S, a.E, NOUT);
+            f = w == 128 ? rows_launch<Split128, MODE> : w == 64 ? rows_launch<Split64, MODE> : rows_launch<Small, MODE>;
+        }
     f(S, a, s);
 }
 
@@ -742,7 +745,7 @@ hipError_t f32_rows(int mode, int S, int d, int E, int F, const int32_t *offsets
 hipError_t f32_wgrads(int d, int E, int F, int T, int K, const int32_t *offsets, const float *H, const float *dYrows,
                       const int32_t *dyperm, const float *xrows, const int32_t *xperm, const float *dA, const float *dB,
                       float *dWg, float *dWu, float *dWd, int accumulate, hipStream_t s) {
-    auto f = split_wgrads((int64_t)T * K, E, d, F) ? wgrad_launch<F32Split> : few_wgrad_tiles(E, d, F) ? wgrad_launch<F32Short> : wgrad_launch<F32Tile>;
+    auto f = split_wgrads((int64_t)T * K, E, d, F) ? wgrad_launch<Split128> : few_wgrad_tiles(E, d, F) ? wgrad_launch<F32Short> : wgrad_launch<F32Tile>;
     f(E, T, K, offsets, wgrad_args(d, F, H, dYrows, dyperm, xrows, xperm, dA, dB, dWg, dWu, dWd), accumulate, s);
     return hipGetLastError();
 }
@@ -769,10 +772,17 @@ hipError_t f32_backward(const F32Backward &b, hipStream_t s) {
     auto go = [&](auto idx) {
         typedef typename std::remove_const<typename std::remove_pointer<decltype(idx)>::type>::type IdxT;
         const PlainDwr<float, IdxT> w = {b.T, b.d, b.E, b.K, plain_dwr_rows(b.T, b.d, b.E), b.x, b.dz, idx, b.stride, b.part};
-        auto f = split_wgrads(b.S, b.E, b.d, b.F) ? ((int64_t)b.S * b.d >= kSplitDxp ? grads_launch<F32Split, F32Split, IdxT>
-                                                                               : grads_launch<F32Short, F32Split, IdxT>)
-                 : fr ? (fw ? grads_launch<F32Short, F32Short, IdxT> : grads_launch<F32Short, F32Tile, IdxT>)
-                      : (fw ? grads_launch<F32Tile, F32Short, IdxT> : grads_launch<F32Tile, F32Tile, IdxT>);
+        const bool sw = split_wgrads(b.S, b.E, b.d, b.F);
+        auto split = [&](auto cr) { return sw ? grads_launch<decltype(cr), Split128, IdxT> : grads_launch<decltype(cr), F32Tile, IdxT>; };
+        auto f32 = [&](auto cr) {
+            typedef decltype(cr) CR;
+            return sw ? grads_launch<CR, Split128, IdxT> : fw ? grads_launch<CR, F32Short, IdxT> : grads_launch<CR, F32Tile, IdxT>;
+        };
+        auto f = fr ? f32(F32Short{}) : f32(F32Tile{});
+        if (split_rows(b.d, b.F)) {
+            const int w = split_width<PLAIN_DXP>(b.S, b.E, b.d);
+            f = w == 128 ? split(Split128{}) : w == 64 ? split(Split64{}) : split(Split32{});
+        }
         f(b.S, a, b.T, b.K, b.offsets, all, b.accumulate, w, s);
     };
     if (b.idx_dtype == R3_IDX_U8) go((const uint8_t *)b.idx);

@@ -131,6 +131,56 @@ def host(t):
     return t.detach().float().cpu().numpy() if t.dtype == torch.bfloat16 else t.detach().cpu().numpy()
 
 
+def dx_64(c, buf, dy, scale=False):
+    """dx in float64 on the device from what the forward left (the saved factors, the rows before the combination, the gates).
+    scale: what a relative rounding of its intermediates is relative to: the sum of the terms' magnitudes from dH on, and of dH and the gates'
+    dot products their own magnitude and the root of their terms' squares, which their sums' roundings go with."""
+    K = c.D.K
+
+    def product(a, b):
+        return (a @ b).abs() + (a.square() @ b.square()).sqrt() if scale else a @ b
+
+    m = torch.abs if scale else (lambda t: t)
+    dy, gates, Yp = dy.double(), buf.gates.double(), buf.Yp.double()
+    off, tok = buf.offsets.tolist(), buf.perm.long() // K
+    g = gates.view(-1)[buf.perm.long(), None]
+    dXp = torch.zeros_like(Yp)
+    for e, (a, b) in enumerate(zip(off, off[1:])):
+        dh = g[a:b] * product(dy[tok[a:b]], c.t["Wd"][e].double().T.contiguous())
+        for f, w in ((buf.A, "Wg"), (buf.B, "Wu")):
+            dXp[a:b] += (dh * m(f[a:b].double())) @ m(c.t[w][e].double()).T.contiguous()
+    rows = buf.inv_perm.long().view(-1, K)
+    terms = Yp[rows] * dy[:, None] * (1 if buf.gated else gates[:, :, None])
+    w = terms.sum(-1)
+    if scale:
+        w = w.abs() + 4 * terms.square().sum(-1).sqrt()   # (and the reference's: Yp may be rounded to 16 bits, which the layer's dz does without)
+    dz = w + gates * w.sum(1, keepdim=True) * (1 if scale else -1)
+    return dXp[rows].sum(1) + (dz[:, :, None] * m(c.t["Wr"].double()).T.contiguous()[c.t["idx"].to(torch.int64)]).sum(1)
+
+
+def layer_64(c, buf, dy, x=None):
+    """Every contraction of a layer in float64 on the device, each from the tensors that the layer left before it (dx, dW_gate and dW_up:
+    from the saved factors, so that dH's error is in them too)."""
+    K = c.D.K
+    x, dy = (c.t["x"] if x is None else x).double(), dy.double()
+    Wg, Wu, Wd = c.t["Wg"].double(), c.t["Wu"].double(), c.t["Wd"].double()
+    off, tok = buf.offsets.tolist(), buf.perm.long() // K
+    g = buf.gates.double().view(-1)[buf.perm.long(), None]
+    want = {k: torch.zeros_like(t, dtype=torch.float64) for k, t in
+            (("FA", buf.A), ("FB", buf.B), ("Yp", buf.Yp), ("dW_down", buf.dW_down), ("dW_gate", buf.dW_gate), ("dW_up", buf.dW_up))}
+    for e, (a, b) in enumerate(zip(off, off[1:])):
+        xe, dye, ge, H = x[tok[a:b]], dy[tok[a:b]], g[a:b], buf.H[a:b].double()
+        s, u = xe @ Wg[e], xe @ Wu[e]
+        sg = torch.sigmoid(s)
+        want["FA"][a:b], want["FB"][a:b] = u * sg * (1 + s * (1 - sg)), s * sg
+        want["Yp"][a:b] = H @ Wd[e]
+        want["dW_down"][e] = H.T.contiguous() @ (dye if buf.gated else ge * dye)
+        dh = ge * (dye @ Wd[e].T.contiguous())
+        want["dW_gate"][e], want["dW_up"][e] = (xe.T.contiguous() @ (dh * t[a:b].double()) for t in (buf.A, buf.B))
+    want["dx"] = dx_64(c, buf, dy)
+    return want
+
+
 class Case:
     """One seeded layer: numpy float32 inputs for the oracle, device tensors for the library.
 

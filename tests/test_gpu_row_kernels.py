@@ -6,7 +6,7 @@ import torch
 
 from oracle import sparse
 from paper_2510_11370_amd import r3, synth
-from util import Case, assert_close, host
+from util import Case, assert_close, dx_64, host
 
 pytestmark = pytest.mark.gpu
 SH = synth.LayerShape
@@ -21,12 +21,16 @@ def test_combine_and_dx_rows(d, T, K):
         buf = r3.LayerBuffers(c.D, backward=True, gathered_copy=False)
         w = (c.t["Wg"], c.t["Wu"], c.t["Wd"])
         r3.forward(buf, c.t["x"], c.t["Wr"], c.t["idx"], *w, bias=c.t["bias"])
+        r3.backward(buf, c.t["dy"], c.t["x"], c.t["Wr"], c.t["idx"], *w)
         torch.cuda.synchronize()
         rows = buf.inv_perm.long().view(T, K)
         want = (buf.gates.double()[:, :, None] * buf.Yp.double()[rows]).sum(1)
         # one rounding to the result's type, and K f32 additions
         rel = 2.0 ** -8 if act == "bf16" else 1e-6
         assert ((buf.y.double() - want).abs() <= rel * want.abs() + 1e-6 * want.abs().max()).all()
+        # dA and dB, dXp and dx are rounded to the result's type, as are the rows that the reference's dz comes from; f32 sums of up to 2056 terms
+        rel = 4 * 2.0 ** -9 if act == "bf16" else 1e-5
+        assert ((buf.dx.double() - dx_64(c, buf, c.t["dy"])).abs() <= rel * dx_64(c, buf, c.t["dy"], scale=True)).all()
 
 
 @pytest.mark.parametrize("sh", [

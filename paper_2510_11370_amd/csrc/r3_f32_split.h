@@ -19,7 +19,7 @@
 // with the issue to themselves; splitting its share of the tiles and looking for small values is 200 vector instructions, and the card runs at
 // 1.9-2.1 GHz under all of it.  (On the f32 instruction 4096 at least, at 2.3 GHz.)  So a value is split once per work-group, on its way to LDS, where
 // 48 KB of planes leave room for two work-groups, one of which splits while the other multiplies.  T=2048 d=512 E=16 K=4 F=1024, us, f32 instruction in
-// 64 x 64 tiles -> this: SwiGLU 157 -> 136, down 87 -> 78, all gradients and dXp 405 -> 255.
+// 64 x 64 tiles -> this: SwiGLU 157 -> 122, down 87 -> 80, all gradients and dXp 405 -> 251.
 // Small tiles, which layers of few rows take: the chain of one k-tile (fragments out of LDS, six MFMAs in a row, the next k-tile's splitting
 // among them, the way back into LDS), 750 cycles for 32 x 32 and 580 on the f32 instruction.  128 tokens top-2, 512 x 512, 8 experts: SwiGLU
 // 13.3 -> 16.4, down 9.7 -> 11.6.  No faster: four k-tiles on their way instead of two, fragments a k-tile ahead, two or four k-tiles
@@ -64,6 +64,9 @@ struct SplitRows {
     static constexpr int N = R / 32;
     Src src;
     int voff[N], k0, KK;
+    // whether a k-tile is whole, in any case; the one before the last that may not be, or -1
+    static __device__ __forceinline__ bool inside(int kt, int nk) { return kt < nk - 1; }
+    static __device__ __forceinline__ int middle() { return -1; }
     static __device__ __forceinline__ int row(int u, int i) { return (u >> 2) + 32 * i; }
     static __device__ __forceinline__ int group(int u) { return u & 3; }
     __device__ __forceinline__ void init(const float *base, uint64_t bytes, int KK_, int u) {
@@ -93,6 +96,9 @@ struct SplitCols {
     static constexpr int N = R / 32;
     Src src;
     int voff, ld4;
+    // whether a k-tile is whole, in any case; the one before the last that may not be, or -1
+    static __device__ __forceinline__ bool inside(int kt, int nk) { return kt < nk - 1; }
+    static __device__ __forceinline__ int middle() { return -1; }
     static __device__ __forceinline__ int row(int u, int i) { return (HALVES ? (u >> 6) * (R / 2) + N * (u & 15) : N * (u & 31)) + i; }
     static __device__ __forceinline__ int group(int u) { return HALVES ? (u >> 4) & 3 : u >> 5; }
     // base: first k-row, first feature of the tile (HALVES: of this wave's matrix); ld: floats per k-row
@@ -122,6 +128,9 @@ struct SplitGather {
     Cols op;
     const int32_t *perm;
     int n, K;
+    // whether a k-tile is whole, in any case; the one before the last that may not be, or -1
+    static __device__ __forceinline__ bool inside(int kt, int nk) { return kt < nk - 1; }
+    static __device__ __forceinline__ int middle() { return -1; }
     static __device__ __forceinline__ int row(int u, int i) { return Cols::row(u, i); }
     static __device__ __forceinline__ int group(int u) { return Cols::group(u); }
     __device__ __forceinline__ void init(const float *m, uint64_t bytes, int ld, int u, const int32_t *perm_, int n_, int K_) {
@@ -153,6 +162,8 @@ struct SplitPair {
     Op op;
     Src second;
     int first;
+    __device__ __forceinline__ bool inside(int kt, int nk) const { return kt < nk - 1 && kt != middle(); }
+    __device__ __forceinline__ int middle() const { return op.KK % 32 ? first - 1 : -1; }
     static __device__ __forceinline__ int row(int u, int i) { return Op::row(u, i); }
     static __device__ __forceinline__ int group(int u) { return Op::group(u); }
     __device__ __forceinline__ void load(int kt, SplitRaw<N> &v) const {
@@ -188,19 +199,17 @@ __device__ __forceinline__ void split_store(const float (&f)[8], char *at, int p
         *(uint4 *)(at + p * plane) = make_uint4(w[0], w[1], w[2], w[3]);
     }
 }
+template <class Op>
+__device__ __forceinline__ void split_store_tile(const SplitRaw<Op::N> &v, char *operand, int plane) {
+    const int u = threadIdx.x & 127, g = Op::group(u);
+#pragma unroll
+    for (int i = 0; i < Op::N; ++i) split_store(v.f[i], operand + split_at(Op::row(u, i), g), plane);
+}
 // Which of a thread's rows (bit i: row i) have a value that is not the sum of its pieces because the last of them lies below the smallest
-// bf16, 2^-133: a value of 2^-110 and more has no bits there, zero has none at all.  QUICK: a minimum of two values takes one instruction, and
-// where it is an ordinary number (a tile without padding) that was all; the small tiles, which wait for their MFMAs, do without the branch.
-template <int N, bool QUICK>
+// bf16, 2^-133: a value of 2^-110 and more has no bits there, zero has none at all.
+constexpr float kSplitLeast = 0x1p-110f;
+template <int N>
 __device__ __forceinline__ int split_loses(const SplitRaw<N> &v) {
-    if constexpr (QUICK) {
-        float m[4] = {1.0f, 1.0f, 1.0f, 1.0f};   // (one chain of minima: 575.9 us where four take 573.0)
-#pragma unroll
-        for (int i = 0; i < N; ++i)
-#pragma unroll
-            for (int k = 0; k < 8; k += 2) asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(m[k / 2]) : "v"(v.f[i][k]), "v"(v.f[i][k + 1]));
-        if (fminf(fminf(m[0], m[1]), fminf(m[2], m[3])) >= 0x1p-110f) return 0;
-    }
     int rows = 0;
 #pragma unroll
     for (int i = 0; i < N; ++i) {
@@ -211,13 +220,20 @@ __device__ __forceinline__ int split_loses(const SplitRaw<N> &v) {
     }
     return rows;
 }
-template <class Op, bool QUICK>
-__device__ __forceinline__ int split_store_tile(const SplitRaw<Op::N> &v, char *operand, int plane) {
-    const int u = threadIdx.x & 127, g = Op::group(u), lost = split_loses<Op::N, QUICK>(v);
+// the smallest magnitudes that a thread has seen, one of two chains each, zeros among them: half an instruction a value
+struct SplitLeast {
+    float m[2] = {1.0f, 1.0f};
+    template <int N> __device__ __forceinline__ void take(const SplitRaw<N> &v, bool counts) {
+        float t[2] = {m[0], m[1]};
 #pragma unroll
-    for (int i = 0; i < Op::N; ++i) split_store(v.f[i], operand + split_at(Op::row(u, i), g), plane);
-    return lost;
-}
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int k = 0; k < 8; k += 2) asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(t[k / 2 & 1]) : "v"(v.f[i][k]), "v"(v.f[i][k + 1]));
+#pragma unroll
+        for (int k = 0; k < 2; ++k) m[k] = counts ? t[k] : m[k];
+    }
+    __device__ __forceinline__ bool ordinary() const { return fminf(m[0], m[1]) >= kSplitLeast; }
+};
 // the values as they are, rows of 128 bytes
 template <class Op>
 __device__ __forceinline__ void raw_store_tile(const SplitRaw<Op::N> &v, char *operand) {
@@ -283,31 +299,51 @@ __device__ __forceinline__ void split_zero(SplitAcc<C> &acc) {
         for (int j = 0; j < C::TQ; ++j) acc[i][j] = f32x4_t{0.0f, 0.0f, 0.0f, 0.0f};
 }
 
-// nk > 0 k-tiles, for a wave that stages `op`; which of this thread's rows had a value that was not its pieces' sum
+// nk > 0 k-tiles, for a wave that stages `op`; which of this thread's rows had a value that was not its pieces' sum.
+// One stage: the test costs what it takes of the issue, and a branch in the loop keeps the splitting from among the MFMAs.  So of the k-tiles that cannot be
+// padded the smallest magnitudes are kept, and only where those are not ordinary (a zero or a small value) the operand is gone through
+// once more; the last k-tile of each source, which may be, is tested by itself.  (A minimum and a branch every k-tile: SwiGLU and all of the training
+// of 2048 tokens, 512 x 1024 132 and 571 us, this 122 and 569, no test 119 and 547; 3000 rows, 1024 x 512 71, 57, 59.)  The small tiles, which
+// wait for their MFMAs, test everything.
 template <class C, class W, bool IS_P, class Op>
 __device__ __forceinline__ int split_chain(SplitAcc<C> &acc, int nk, const Op &op, char *lds) {
     constexpr int plane = IS_P ? C::PPLANE : C::QPLANE, at = IS_P ? 0 : 3 * C::PPLANE;
     if constexpr (C::STAGES == 1) {
         SplitRaw<Op::N> v;
+        SplitLeast least;
         op.load(0, v);
-        int lost = split_store_tile<Op, true>(v, lds + at, plane);
-        op.load(1, v);
+        int lost = split_loses(v);
+        split_store_tile<Op>(v, lds + at, plane);
+        op.load(min(1, nk - 1), v);
         split_meet();
-        for (int kt = 0;; ++kt) {
+        for (int kt = 0; kt < nk; ++kt) {
             SplitFrag<C> f;
             split_read<C, W>(f, lds);
             split_multiply<C>(acc, f);
             split_meet();
-            if (kt + 1 == nk) return lost;
-            lost |= split_store_tile<Op, true>(v, lds + at, plane);
-            op.load(kt + 2, v);
+            least.take(v, op.inside(kt + 1, nk));
+            split_store_tile<Op>(v, lds + at, plane);
+            op.load(min(kt + 2, nk - 1), v);
             split_meet();
         }
+        lost |= split_loses(v);
+        const int middle = op.middle();
+        if (middle >= 0) {
+            op.load(middle, v);
+            lost |= split_loses(v);
+        }
+        if (!least.ordinary())
+            for (int kt = 1; kt < nk - 1; ++kt) {
+                op.load(kt, v);
+                lost |= split_loses(v);
+            }
+        return lost;
     } else {
         SplitRaw<Op::N> v[2];
         op.load(0, v[0]);
         op.load(1, v[1]);
-        int lost = split_store_tile<Op, false>(v[0], lds + at, plane);
+        int lost = split_loses(v[0]);
+        split_store_tile<Op>(v[0], lds + at, plane);
         op.load(2, v[0]);
         split_meet();
         for (int k0 = 0;; k0 += 2) {
@@ -316,7 +352,8 @@ __device__ __forceinline__ int split_chain(SplitAcc<C> &acc, int nk, const Op &o
                 SplitFrag<C> f;
                 split_read<C, W>(f, lds + j * C::STAGE);
                 split_multiply<C>(acc, f);
-                lost |= split_store_tile<Op, false>(v[1 - j], lds + (1 - j) * C::STAGE + at, plane);   // (past the last k-tile: zeros)
+                lost |= split_loses(v[1 - j]);
+                split_store_tile<Op>(v[1 - j], lds + (1 - j) * C::STAGE + at, plane);   // (past the last k-tile: zeros)
                 op.load(k0 + j + 3, v[1 - j]);
                 split_meet();
                 if (k0 + j + 1 == nk) return lost;   // (not out of the inner loop alone: the loads would be waited for as on every way round)

@@ -174,11 +174,15 @@ struct SplitPair {
     }
 };
 
-// Where the 16 bytes of group g (8 k) of row r stand in a plane.  Rows are 64 bytes, four to the 256 of all banks; the place in those is a
-// one-to-one function of the row's bits 0-3, which sixteen lanes of a fragment read run through, of bits 2-5, which sixteen lanes storing
-// features that came four to a load do, and of bits 0-1 and the group, which a K-contiguous operand's do.  (With rows in their order
-// and g ^ ((r >> 1) ^ (r >> 3)) the second sort met four ways, conflicts in a fifth of the kernels' cycles: training of 2048 tokens, 512 x 1024, 592 | 586 us.)
-__device__ __forceinline__ int split_at(int r, int g) { return (r ^ ((r >> 4) & 3)) * 64 + ((g ^ ((r >> 2) & 3)) << 4); }
+// Where the 16 bytes of group g (8 k) of row r stand in a plane.  Rows are 64 bytes, four to the 256 of all banks.  Sixteen lanes meet in an access of 16
+// bytes a lane: 0-3, 12-15 and 20-27 of 32, and the others.  A fragment read's are then rows 0-3 and 12-15 of one group and 4-11 of the next; those of a
+// K-contiguous operand's store four rows of all groups; those of features that came four to a load run through the row's bits 2-5: the place is a one-to-one function
+// of each.  (With g itself in place of its permutation a fragment's rows met two by two, conflicts in a tenth of the kernels' cycles; with rows
+// in their order besides the third sort met four ways: training of 2048 tokens, 512 x 1024, 592 | 586 us.)
+__device__ __forceinline__ int split_at(int r, int g) {
+    const int turned = ((g ^ (g >> 1)) & 1) | ((g & 1) << 1);   // 0 3 1 2
+    return (r ^ ((r >> 4) & 3)) * 64 + ((turned ^ ((r >> 2) & 3)) << 4);
+}
 
 // eight f32 as three planes of bf16
 __device__ __forceinline__ void split_store(const float (&f)[8], char *at, int plane) {

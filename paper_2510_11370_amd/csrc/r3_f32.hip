@@ -643,16 +643,16 @@ constexpr int kWgradFill = 320;
 
 // Split tiles.  SwiGLU, down projection and dXp: by the widths alone, so that a token's results are the same bits in a micro-batch and in
 // the whole batch (dH stays on the f32 instruction: 16 k-tiles and two operands beside the result, 94 | 104 us).  From 512 x 512 on: training, us, f32
-// instruction | split, 8 experts top-2 unless given, 128 tokens, 1024 and 4096:  256 x 256 43 | 48, 105 | 101 (2048), 264 | 265 (8192);  384 x 384 53 | 59,
-// 107 | 102, 265 | 263;  512 x 512 62 | 69, 153 | 145, 379 | 349, of 4096 top-4 over 128 experts 855 | 770;  1024 x 1024 105 | 118 (64), 260 | 238 (512);
-// 2048 top-4, 512 x 1024, 16 experts 667 | 569.  (Small tiles only where there were few of the large ones, as the f32 instruction has it, is 13 % faster at 128 tokens and
-// 3 to 5 % at some thousand, and gives a token other bits there.)
+// instruction | split, 8 experts top-2 unless given, 128 tokens, 1024 and 4096:  256 x 256 44 | 47, 105 | 100 (2048), 264 | 261 (8192);  384 x 384 53 | 59,
+// 107 | 104, 265 | 247;  512 x 512 62 | 68, 152 | 143, 378 | 349, of 4096 top-4 over 128 experts 877 | 781;  1024 x 1024 105 | 117 (64), 262 | 240 (512);
+// 2048 top-4, 512 x 1024, 16 experts 663 | 565.  (Small tiles only where there were few of the large ones, as the f32 instruction has it, is 11 % faster at 128 tokens and
+// up to 4 % at some thousand, and gives a token other bits there.)
 constexpr int64_t kSplitRows = 1 << 18;
 // Their size.  128 x 128 from 184 tiles on (dXp, beside the weight gradients: 128), with 64 rows per expert and a quarter of the columns dead at most;
-// 64 x 64 from 512 (down 320, dXp 64).  us, 128 | 64 | 32, by the number of tiles of 128:  SwiGLU 64 36 | 26 | 25, 128 36 | 33 | 37, 176 69 | 56 | 71,
-// 192 57 | 71 | 80, 376 52 | 65 | 72, 512 76 | 80 | 98, 32 rows per expert 104 | 92 | 93, 64 111 | 122 | 130;  down 64 33 | 23 | 22, 88 57 | 38 | 43,
-// 128 34 | 30 | 34, 164 46 | 41 | 55, 188 34 | 38 | 42, 200 39 | 44 | 51, 256 47 | 45 | 57;  dXp and the gradients 32 59 | 34 | 41, 64 60 | 54 | 69, 88 134 | 117 | 162,
-// 128 85 | 88 | 122, 256 251 | 287 | 415, 32 rows per expert 301 | 247 | 255.
+// 64 x 64 from 512 (down 320, dXp 64).  us, 128 | 64 | 32, by the number of tiles of 128:  SwiGLU 64 34 | 25 | 24, 128 35 | 32 | 36, 176 67 | 55 | 71,
+// 192 56 | 70 | 78, 376 51 | 64 | 73, 512 76 | 80 | 97, 32 rows per expert 107 | 92 | 93, 64 113 | 124 | 130;  down 64 32 | 22 | 21, 88 56 | 37 | 41,
+// 128 33 | 29 | 33, 164 45 | 40 | 53, 188 33 | 38 | 42, 200 38 | 43 | 50, 256 47 | 44 | 56;  dXp and the gradients 32 57 | 34 | 40, 64 58 | 53 | 67, 88 136 | 118 | 163,
+// 128 85 | 88 | 119, 256 252 | 291 | 415, 32 rows per expert 305 | 252 | 258.
 int64_t split_columns(int n) { return ceil_div(n, Split128::BP) * Split128::BP; }
 // The weight gradients: one tile per compute unit and more, with the same allowance, and 64 rows per expert.  3 x 8 experts: 4096 tokens top-2,
 // 320 x 320 (150 tiles' worth) 97 | 116, 256 x 1024 (384) 230 | 185, 1024 top-2, 512 x 512 (384) 71 | 66; 64 rows per expert 165 | 150, 32

@@ -19,10 +19,10 @@
 // with the issue to themselves; splitting its share of the tiles and looking for small values is 200 vector instructions, and the card runs at
 // 1.9-2.1 GHz under all of it.  (On the f32 instruction 4096 at least, at 2.3 GHz.)  So a value is split once per work-group, on its way to LDS, where
 // 48 KB of planes leave room for two work-groups, one of which splits while the other multiplies.  T=2048 d=512 E=16 K=4 F=1024, us, f32 instruction in
-// 64 x 64 tiles -> this: SwiGLU 157 -> 122, down 87 -> 80, all gradients and dXp 405 -> 251.
+// 64 x 64 tiles -> this: SwiGLU 156 -> 121, down 87 -> 82, all gradients and dXp 405 -> 249.
 // Small tiles, which layers of few rows take: the chain of one k-tile (fragments out of LDS, six MFMAs in a row, the next k-tile's splitting
 // among them, the way back into LDS), 750 cycles for 32 x 32 and 580 on the f32 instruction.  128 tokens top-2, 512 x 512, 8 experts: SwiGLU
-// 13.3 -> 16.4, down 9.7 -> 11.6.  No faster: four k-tiles on their way instead of two, fragments a k-tile ahead, two or four k-tiles
+// 13.2 -> 16.0, down 9.8 -> 11.6.  No faster: four k-tiles on their way instead of two, fragments a k-tile ahead, two or four k-tiles
 // between barriers, waves that only split beside waves that only multiply (128 x 128: 30 % faster with a compute unit to itself,
 // 12-17 % slower where there is work for two).
 #pragma once
@@ -307,8 +307,8 @@ __device__ __forceinline__ void split_zero(SplitAcc<C> &acc) {
 // One stage: the test costs what it takes of the issue, and a branch in the loop keeps the splitting from among the MFMAs.  So of the k-tiles that cannot be
 // padded the smallest magnitudes are kept, and only where those are not ordinary (a zero or a small value) the operand is gone through
 // once more; the last k-tile of each source, which may be, is tested by itself.  (A minimum and a branch every k-tile: SwiGLU and all of the training
-// of 2048 tokens, 512 x 1024 132 and 571 us, this 122 and 569, no test 119 and 547; 3000 rows, 1024 x 512 71, 57, 59.)  The small tiles, which
-// wait for their MFMAs, test everything.
+// of 2048 tokens, 512 x 1024 132 and 571 us, this 122 and 569, no test 119 and 547; SwiGLU of 3000 rows, 1024 x 512 71, 57, 59.)  The small
+// tiles, which wait for their MFMAs, test everything.
 template <class C, class W, bool IS_P, class Op>
 __device__ __forceinline__ int split_chain(SplitAcc<C> &acc, int nk, const Op &op, char *lds) {
     constexpr int plane = IS_P ? C::PPLANE : C::QPLANE, at = IS_P ? 0 : 3 * C::PPLANE;

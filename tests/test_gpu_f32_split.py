@@ -55,6 +55,7 @@ def test_small_values_beside_ordinary_ones(exp):
     # gradients of a few tokens: dXp
     dy = c.t["dy"].clone()
     dy[toks] *= 2.0 ** exp
+    dy[toks + 1] = 0   # (zeros are no small values)
     buf = run(c, "one", dy)
     assert_rows(buf.dx, layer_64(c, buf, dy)["dx"], toks)
     # features of the gradient: dW_down, the other operand
@@ -165,6 +166,7 @@ def test_nan_stays_with_its_token():
 @pytest.mark.parametrize("sh", [
     SH(T=4200, d=500, E=5, K=2, F=580, act="f32", sigma=0.05, zipf_s=0.8, seed=133),    # split tiles: of 32, 64 and 128 rows
     SH(T=4200, d=132, E=6, K=2, F=260, act="f32", sigma=0.05, zipf_s=0.8, seed=134),    # f32 instruction: of 32 and 64
+    SH(T=4200, d=131, E=6, K=3, F=259, act="f32", sigma=0.05, zipf_s=0.8, seed=138),    # widths that are no multiples of four
 ], ids=lambda s: "d%d_F%d" % (s.d, s.F))
 def test_rows_do_not_depend_on_the_batch(sh, calls):
     """A token's y and dx are the same bits in a micro-batch and in the whole batch."""

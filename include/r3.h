@@ -31,7 +31,9 @@
  *    a duplicate id inside a token, a non-finite logit) OR bits into the
  *    optional device word `status_word` (R3_DATA_*); the affected token's
  *    outputs are then unspecified but no access goes out of bounds.
- *  - Every result is deterministic: the same inputs give the same bits.
+ *  - Every result is deterministic: the same inputs give the same bits.  A
+ *    token's logits and gates, and for f32 its rows of y and dx, are the same
+ *    bits whatever other tokens the call has.
  */
 #ifndef R3_H
 #define R3_H

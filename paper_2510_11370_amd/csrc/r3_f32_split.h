@@ -336,7 +336,7 @@ __device__ __forceinline__ int split_chain(SplitAcc<C> &acc, int nk, const Op &o
             op.load(middle, v);
             lost |= split_loses(v);
         }
-        if (!least.ordinary())
+        if (__ballot(!least.ordinary()))   // (by whole waves: a gathered operand's lanes take its rows from each other)
             for (int kt = 1; kt < nk - 1; ++kt) {
                 op.load(kt, v);
                 lost |= split_loses(v);

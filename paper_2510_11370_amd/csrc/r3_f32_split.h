@@ -307,8 +307,9 @@ __device__ __forceinline__ void split_zero(SplitAcc<C> &acc) {
 // One stage: the test costs what it takes of the issue, and a branch in the loop keeps the splitting from among the MFMAs.  So of the k-tiles that cannot be
 // padded the smallest magnitudes are kept, and only where those are not ordinary (a zero or a small value) the operand is gone through
 // once more; the last k-tile of each source, which may be, is tested by itself.  (A minimum and a branch every k-tile: SwiGLU and all of the training
-// of 2048 tokens, 512 x 1024 132 and 571 us, this 122 and 569, no test 119 and 547; SwiGLU of 3000 rows, 1024 x 512 71, 57, 59.)  The small
-// tiles, which wait for their MFMAs, test everything.
+// of 2048 tokens, 512 x 1024 132 and 571 us, this 122 and 569, no test 119 and 547; SwiGLU of 3000 rows, 1024 x 512 71, 57, 59.  With a
+// gradient of zeros in two tokens of five the weight gradients, whose operands are then gone through twice, 253 -> 277 us.)  The small tiles, which
+// wait for their MFMAs, test everything.
 template <class C, class W, bool IS_P, class Op>
 __device__ __forceinline__ int split_chain(SplitAcc<C> &acc, int nk, const Op &op, char *lds) {
     constexpr int plane = IS_P ? C::PPLANE : C::QPLANE, at = IS_P ? 0 : 3 * C::PPLANE;
@@ -336,11 +337,18 @@ __device__ __forceinline__ int split_chain(SplitAcc<C> &acc, int nk, const Op &o
             op.load(middle, v);
             lost |= split_loses(v);
         }
-        if (__ballot(!least.ordinary()))   // (by whole waves: a gathered operand's lanes take its rows from each other)
-            for (int kt = 1; kt < nk - 1; ++kt) {
-                op.load(kt, v);
-                lost |= split_loses(v);
-            }
+        if (__ballot(!least.ordinary())) {   // (by whole waves: a gathered operand's lanes take its rows from each other)
+            SplitRaw<Op::N> w[3];
+#pragma unroll
+            for (int j = 0; j < 3; ++j) op.load(min(1 + j, nk - 1), w[j]);
+#pragma nounroll
+            for (int kt = 1; kt < nk - 1; kt += 3)
+#pragma unroll
+                for (int j = 0; j < 3; ++j) {   // (some k-tiles twice)
+                    lost |= split_loses(w[j]);
+                    op.load(min(kt + j + 3, nk - 1), w[j]);
+                }
+        }
         return lost;
     } else {
         SplitRaw<Op::N> v[2];

@@ -33,11 +33,9 @@ struct F32Cfg {
 typedef F32Cfg<2, 2, 2> F32Tile;     // 32 KB of LDS: five work-groups on a compute unit, which cover what is not prefetched (four where the
                                      // weight gradients share their grid with the parts of dW_r, whose padded tiles take 36 KB)
 typedef F32Cfg<1, 1, 4> F32Short;    // few tiles: four times as many, half the chain each, loads three k-tiles ahead (F32WgradOp: one)
-
-// tiles on the bf16 instruction (r3_f32_split.h)
 typedef F32Cfg<2, 1, 4> F32Short1;   // the same for the SwiGLU, whose P tile holds both weights
 
-// tiles on the bf16 instruction (r3_f32_split.h), likewise
+// the same on the bf16 instruction (r3_f32_split.h); the last for the SwiGLU
 typedef SplitCfg<4, 4, 1, 2> Split128;
 typedef SplitCfg<2, 2, 2, 1> Split64;
 typedef SplitCfg<1, 1, 2, 1> Split32;
